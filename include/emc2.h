@@ -145,6 +145,45 @@ emc2_status emc2_build_kmap(emc2_ctx* ctx, emc2_conv_kind kind, const int32_t* d
                             int32_t grid_out[3], int32_t* h_n_out, void* stream);
 
 /*
+ * Voxelization and every kernel map of one or more stacks (a stack = one voxel grid and its stride-2 levels) over the same
+ * points, in one call: the buffers and index slots receive what emc2_voxelize followed by emc2_build_kmap per level (in_slot /
+ * out_slot = the levels' slots) would leave in them, in 6 to 8 launches altogether instead of 6 per level and map.
+ *   level[0].d_down_nbr must be NULL (nothing lies below it); level[l].d_down_nbr is the stride-2 map from level l - 1 into
+ *   level l; level[l].d_subm_nbr is the submanifold map of level l or NULL if no layer needs it.
+ *   expert < 0: d_batch as for emc2_voxelize.  expert >= 0: the stack takes the points of the scenes routed to `expert` only:
+ *   d_batch [n_points] holds SCENE ids (NULL: all 0), d_route [spec.n_batch] the expert of every scene (emc2_dispatch) and
+ *   d_slot [spec.n_batch] its position in its expert's group (emc2_group_slots); the same result as voxelizing with
+ *   emc2_group_points' batch ids, without writing them.
+ * Every stack needs a context of its own (one stream at a time per context, as for the calls it replaces); all specs must
+ * agree in stride_f.  At most 4 stacks.
+ */
+#define EMC2_STACK_MAX_LEVELS 5
+typedef struct {
+  int64_t capacity;
+  int32_t* d_coords;      /* [capacity][4] */
+  int32_t* d_n;           /* device count  */
+  int32_t* d_subm_nbr;    /* [27][capacity] or NULL */
+  int32_t* d_down_nbr;    /* [27][capacity]; NULL for level 0 */
+  int32_t slot;           /* index slot of the level; distinct within a stack */
+  int32_t reserved;
+} emc2_stack_level;
+typedef struct {
+  emc2_ctx* ctx;
+  emc2_voxel_spec spec;
+  int32_t expert;
+  int32_t n_levels;
+  emc2_dtype lp_dtype;
+  const int32_t* d_batch;
+  const int32_t* d_route;
+  const int32_t* d_slot;
+  float* d_feats;         /* [level[0].capacity][4] fp32 means */
+  int32_t* d_counts;
+  void* d_feats_lp;       /* copy of the means in lp_dtype, or NULL */
+  emc2_stack_level level[EMC2_STACK_MAX_LEVELS];
+} emc2_stack;
+emc2_status emc2_build_stacks(const emc2_stack* stacks, int32_t n_stacks, const float* d_points, int64_t n_points, void* stream);
+
+/*
  * emc2_build_kmap for callers that cannot allocate device memory and therefore cannot hold a context: code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same operation, arguments and results
  * as emc2_build_kmap with in_slot = out_slot = -1 (the cell index is rebuilt from d_in_coords, nothing is kept),
@@ -223,6 +262,26 @@ emc2_status emc2_spconv(emc2_ctx* ctx, emc2_dtype dtype, const void* d_in, const
                         const float* d_scale, const float* d_shift, emc2_epilogue epilogue,
                         const int32_t* d_nbr, int32_t map_hint, const int32_t* d_n_out, int64_t capacity_out,
                         int64_t n_in_rows, int32_t cin, int32_t cout, void* d_out, void* stream);
+
+/* emc2_spconv for n calls in order, in one host call: the arguments of each as in emc2_spconv. */
+typedef struct {
+  emc2_ctx* ctx;
+  const void* d_in;
+  const void* d_w;
+  const float* d_scale;
+  const float* d_shift;
+  const int32_t* d_nbr;
+  const int32_t* d_n_out;
+  void* d_out;
+  int64_t capacity_out;
+  int64_t n_in_rows;
+  emc2_dtype dtype;
+  emc2_wlayout w_layout;
+  emc2_epilogue epilogue;
+  int32_t map_hint;
+  int32_t cin, cout;
+} emc2_conv_call;
+emc2_status emc2_spconv_list(const emc2_conv_call* calls, int32_t n, void* stream);
 
 /*
  * Inverse (transposed) kernel map of a stride-2 layer, for the decoder half of the LiDAR UNet (paper
@@ -388,6 +447,10 @@ emc2_status emc2_dispatch(emc2_ctx* ctx, const float* d_props, const int32_t* d_
 emc2_status emc2_group_points(emc2_ctx* ctx, const int32_t* d_scene, int64_t n_points, const int32_t* d_expert,
                               const int32_t* d_order, const int32_t* d_counts, int32_t n_scenes, int32_t expert,
                               int32_t* d_slot, int32_t* d_group_batch, void* stream);
+
+/* The slots of emc2_group_points alone (no batch ids): what a routed stack of emc2_build_stacks reads. */
+emc2_status emc2_group_slots(emc2_ctx* ctx, const int32_t* d_expert, const int32_t* d_order, const int32_t* d_counts,
+                             int32_t n_scenes, int32_t* d_slot, void* stream);
 
 /*
  * Point -> image projection with bilinear feature gather (paper Sec. 3.1: image features are

@@ -30,7 +30,8 @@ _TORCH_DTYPE = {F32: torch.float32, F16: torch.float16, BF16: torch.bfloat16}
 EXPORTS = ["emc2_create", "emc2_destroy", "emc2_status_sync", "emc2_last_error", "emc2_voxelize",
            "emc2_build_kmap", "emc2_spconv", "emc2_project_gather", "emc2_pack_weights", "emc2_spconv_uses_mfma",
            "emc2_spconv_kernel", "emc2_build_inverse_kmap", "emc2_bev_flatten", "emc2_pool_image", "emc2_fuse", "emc2_dispatch", "emc2_spconv_i8_supported",
-           "emc2_quantize_i8", "emc2_pack_weights_i8", "emc2_spconv_i8", "emc2_build_kmap_static", "emc2_group_points", "emc2_quantize_e4m3", "emc2_spconv_e4m3"]
+           "emc2_quantize_i8", "emc2_pack_weights_i8", "emc2_spconv_i8", "emc2_build_kmap_static", "emc2_group_points", "emc2_quantize_e4m3", "emc2_spconv_e4m3",
+           "emc2_build_stacks", "emc2_spconv_list", "emc2_group_slots"]
 
 
 class Emc2Error(RuntimeError):
@@ -43,6 +44,36 @@ class _VoxelSpecC(ctypes.Structure):
     _fields_ = [("lo", ctypes.c_float * 3), ("vs", ctypes.c_float * 3), ("grid", ctypes.c_int32 * 3),
                 ("n_batch", ctypes.c_int32), ("r2_min", ctypes.c_float), ("r2_max", ctypes.c_float),
                 ("stride_f", ctypes.c_int32)]
+
+
+def voxel_spec_c(spec: VoxelSpec, stride: int) -> _VoxelSpecC:
+    return _VoxelSpecC((ctypes.c_float * 3)(*spec.lo), (ctypes.c_float * 3)(*spec.vs), (ctypes.c_int32 * 3)(*spec.grid),
+                       spec.n_batch, spec.r2_min, spec.r2_max, stride)
+
+
+STACK_MAX_LEVELS, MAX_STACKS = 5, 4
+
+
+class StackLevelC(ctypes.Structure):
+    """emc2_stack_level"""
+    _fields_ = [("capacity", ctypes.c_int64), ("d_coords", ctypes.c_void_p), ("d_n", ctypes.c_void_p), ("d_subm_nbr", ctypes.c_void_p),
+                ("d_down_nbr", ctypes.c_void_p), ("slot", ctypes.c_int32), ("reserved", ctypes.c_int32)]
+
+
+class StackC(ctypes.Structure):
+    """emc2_stack"""
+    _fields_ = [("ctx", ctypes.c_void_p), ("spec", _VoxelSpecC), ("expert", ctypes.c_int32), ("n_levels", ctypes.c_int32),
+                ("lp_dtype", ctypes.c_int), ("d_batch", ctypes.c_void_p), ("d_route", ctypes.c_void_p), ("d_slot", ctypes.c_void_p),
+                ("d_feats", ctypes.c_void_p), ("d_counts", ctypes.c_void_p), ("d_feats_lp", ctypes.c_void_p),
+                ("level", StackLevelC * STACK_MAX_LEVELS)]
+
+
+class ConvCallC(ctypes.Structure):
+    """emc2_conv_call"""
+    _fields_ = [("ctx", ctypes.c_void_p), ("d_in", ctypes.c_void_p), ("d_w", ctypes.c_void_p), ("d_scale", ctypes.c_void_p),
+                ("d_shift", ctypes.c_void_p), ("d_nbr", ctypes.c_void_p), ("d_n_out", ctypes.c_void_p), ("d_out", ctypes.c_void_p),
+                ("capacity_out", ctypes.c_int64), ("n_in_rows", ctypes.c_int64), ("dtype", ctypes.c_int), ("w_layout", ctypes.c_int),
+                ("epilogue", ctypes.c_int), ("map_hint", ctypes.c_int32), ("cin", ctypes.c_int32), ("cout", ctypes.c_int32)]
 
 
 _lib = None
@@ -106,6 +137,12 @@ def load_library() -> ctypes.CDLL:
     lib.emc2_group_points.argtypes = [vp, vp, i64, vp, vp, vp, i32, i32, vp, vp, vp]
     lib.emc2_project_gather.restype = ctypes.c_int
     lib.emc2_project_gather.argtypes = [vp, vp, i32, i64, ctypes.POINTER(ctypes.c_float), vp, i32, i32, i32, vp, vp, vp, vp]
+    lib.emc2_build_stacks.restype = ctypes.c_int
+    lib.emc2_build_stacks.argtypes = [ctypes.POINTER(StackC), i32, vp, i64, vp]
+    lib.emc2_spconv_list.restype = ctypes.c_int
+    lib.emc2_spconv_list.argtypes = [ctypes.POINTER(ConvCallC), i32, vp]
+    lib.emc2_group_slots.restype = ctypes.c_int
+    lib.emc2_group_slots.argtypes = [vp, vp, vp, vp, i32, vp, vp]
     lib.emc2_build_inverse_kmap.restype = ctypes.c_int
     lib.emc2_build_inverse_kmap.argtypes = [vp, vp, vp, i64, ctypes.POINTER(i32), i32, i32, vp, vp, vp]
     lib.emc2_bev_flatten.restype = ctypes.c_int
@@ -157,6 +194,26 @@ def build_kmap_static(kind: int, in_coords: torch.Tensor, n_in: torch.Tensor, ca
     if st != OK:
         raise Emc2Error(st, lib.emc2_last_error(None).decode())
     return g_out[0], g_out[1], g_out[2]
+
+
+def build_stacks(stacks, n_stacks: int, points: torch.Tensor) -> None:
+    """emc2_build_stacks over a ctypes array of StackC whose buffers the caller keeps alive."""
+    _dev_check(points, torch.float32, "points")
+    n, stride = (points.shape[0], points.shape[1]) if points.dim() == 2 else (0, 4)
+    for i in range(n_stacks):
+        stacks[i].spec.stride_f = stride
+    lib = load_library()
+    st = lib.emc2_build_stacks(stacks, n_stacks, points.data_ptr(), n, torch.cuda.current_stream().cuda_stream)
+    if st != OK:
+        raise Emc2Error(st, lib.emc2_last_error(stacks[0].ctx).decode())
+
+
+def spconv_list(calls, n: int) -> None:
+    """emc2_spconv_list over a ctypes array of ConvCallC whose buffers the caller keeps alive."""
+    lib = load_library()
+    st = lib.emc2_spconv_list(calls, n, torch.cuda.current_stream().cuda_stream)
+    if st != OK:
+        raise Emc2Error(st, next((t for t in (lib.emc2_last_error(calls[i].ctx).decode() for i in range(n)) if t), ""))
 
 
 class Context:
@@ -213,8 +270,7 @@ class Context:
             lp_dtype = {torch.float16: F16, torch.bfloat16: BF16}[feats_lp.dtype]
             if feats_lp.numel() < 4 * capacity or not feats_lp.is_cuda:
                 raise ValueError("feats_lp smaller than capacity")
-        cs = _VoxelSpecC((ctypes.c_float * 3)(*spec.lo), (ctypes.c_float * 3)(*spec.vs), (ctypes.c_int32 * 3)(*spec.grid),
-                         spec.n_batch, spec.r2_min, spec.r2_max, stride)
+        cs = voxel_spec_c(spec, stride)
         h_n = ctypes.c_int32(0)
         self._chk(self.lib.emc2_voxelize(self.h, _ptr(points), _ptr(batch), n, ctypes.byref(cs), capacity, _ptr(coords),
                                          _ptr(feats), _ptr(counts), _ptr(feats_lp), lp_dtype, _ptr(n_voxels),
@@ -476,6 +532,14 @@ class Context:
             raise ValueError("buffers smaller than n_scenes / n_points")
         self._chk(self.lib.emc2_group_points(self.h, _ptr(scene), n_points, _ptr(expert), _ptr(order), _ptr(counts), n_scenes,
                                              e, _ptr(slot), _ptr(group_batch), _stream()))
+
+    def group_slots(self, expert: torch.Tensor, order: torch.Tensor, counts: torch.Tensor, n_scenes: int, slot: torch.Tensor) -> None:
+        """Dispatcher outputs -> slot[n_scenes]: each scene's position in its expert's group (group_points without batch ids)."""
+        for t, nm in ((expert, "expert"), (order, "order"), (counts, "counts"), (slot, "slot")):
+            _dev_check(t, torch.int32, nm)
+        if expert.numel() < n_scenes or order.numel() < n_scenes or counts.numel() < 3 or slot.numel() < n_scenes:
+            raise ValueError("buffers smaller than n_scenes")
+        self._chk(self.lib.emc2_group_slots(self.h, _ptr(expert), _ptr(order), _ptr(counts), n_scenes, _ptr(slot), _stream()))
 
     def project_gather(self, points: torch.Tensor, pmat: Sequence[float], img: torch.Tensor, out: torch.Tensor,
                        valid: torch.Tensor, uv: Optional[torch.Tensor] = None) -> None:

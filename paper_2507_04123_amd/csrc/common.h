@@ -77,6 +77,8 @@ struct emc2_ctx {
   float4* stash;            // [max_voxels][EMC2_VOX_STASH] points of each voxel, in arrival order
   uint32_t* partials;       // scan partial sums
   int64_t n_partials;
+  uint32_t* stack_sums;     // popcount sums of every level of a stack (stack.hip)
+  int64_t n_stack_sums;
   int32_t* dev_words;       // [0] status flags, [2] voxel count of an index rebuilt from coordinates (others unused)
   void* wpack;              // scratch for weights re-ordered per call (27*128*128 16-bit values)
   void* zero_row;           // 256 zero bytes: the feature row an absent neighbour reads

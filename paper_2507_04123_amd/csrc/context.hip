@@ -68,6 +68,13 @@ extern "C" emc2_status emc2_create(emc2_ctx** out, int device, int64_t max_point
   TRY(hipMalloc((void**)&ctx->stash, sizeof(float4) * EMC2_VOX_STASH * (size_t)max_voxels), "hipMalloc(voxel stash)");
   ctx->n_partials = emc2_div_up(ctx->slot_words, EMC2_SCAN_TILE) + 1;
   TRY(hipMalloc((void**)&ctx->partials, sizeof(uint32_t) * (size_t)ctx->n_partials), "hipMalloc(partials)");
+  {
+    // level 0 in tiles, up to EMC2_STACK_MAX_LEVELS - 1 further ones in quarter tiles, and one sum of every 64 sums
+    const int64_t further = n_slots - 1 < EMC2_STACK_MAX_LEVELS - 1 ? n_slots - 1 : EMC2_STACK_MAX_LEVELS - 1;
+    const int64_t units = ctx->slot_tiles * (1 + 4 * further);
+    ctx->n_stack_sums = units + units / 64 + 2 * EMC2_STACK_MAX_LEVELS;
+  }
+  TRY(hipMalloc((void**)&ctx->stack_sums, sizeof(uint32_t) * (size_t)ctx->n_stack_sums), "hipMalloc(stack_sums)");
   TRY(hipMalloc((void**)&ctx->zero_row, 256), "hipMalloc(zero_row)");
   TRY(hipMemset(ctx->zero_row, 0, 256), "hipMemset(zero_row)");
   TRY(hipMalloc((void**)&ctx->pix_rank, sizeof(int32_t) * 4 * (size_t)max_points), "hipMalloc(pixel scratch)");
@@ -103,6 +110,7 @@ extern "C" void emc2_destroy(emc2_ctx* ctx) {
   free(ctx->meta);
   if (ctx->stash) (void)hipFree(ctx->stash);
   if (ctx->partials) (void)hipFree(ctx->partials);
+  if (ctx->stack_sums) (void)hipFree(ctx->stack_sums);
   if (ctx->zero_row) (void)hipFree(ctx->zero_row);
   if (ctx->wpack) (void)hipFree(ctx->wpack);
   if (ctx->pix_rank) (void)hipFree(ctx->pix_rank);

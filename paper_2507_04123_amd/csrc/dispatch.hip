@@ -157,6 +157,16 @@ extern "C" emc2_status emc2_group_points(emc2_ctx* ctx, const int32_t* d_scene, 
   return emc2_check_hip(ctx, hipGetLastError(), "emc2_group_points launch");
 }
 
+extern "C" emc2_status emc2_group_slots(emc2_ctx* ctx, const int32_t* d_expert, const int32_t* d_order, const int32_t* d_counts,
+                                        int32_t n_scenes, int32_t* d_slot, void* stream) {
+  if (!ctx) return EMC2_ERR_INVALID_ARG;
+  if (!d_expert || !d_order || !d_counts || !d_slot || n_scenes < 1 || n_scenes > (1 << 20))
+    return emc2_fail(ctx, EMC2_ERR_INVALID_ARG, "emc2_group_slots: null argument or n_scenes outside [1, 2^20]");
+  hipLaunchKernelGGL(k_group_slots, dim3((unsigned)emc2_div_up(n_scenes, 256)), dim3(256), 0, (hipStream_t)stream, d_expert, d_order,
+                     d_counts, n_scenes, d_slot);
+  return emc2_check_hip(ctx, hipGetLastError(), "emc2_group_slots launch");
+}
+
 extern "C" emc2_status emc2_dispatch(emc2_ctx* ctx, const float* d_props, const int32_t* d_scene, int64_t n_props,
                                      int32_t n_scenes, float dist, float conf, int32_t* d_expert, int32_t* d_counts,
                                      int32_t* d_order, void* stream) {

@@ -439,3 +439,14 @@ extern "C" emc2_status emc2_spconv(emc2_ctx* ctx, emc2_dtype dtype, const void* 
   }
   return emc2_check_hip(ctx, hipGetLastError(), "emc2_spconv launch");
 }
+
+extern "C" emc2_status emc2_spconv_list(const emc2_conv_call* calls, int32_t n, void* stream) {
+  if (n < 0 || (n > 0 && !calls)) return EMC2_ERR_INVALID_ARG;
+  for (int32_t i = 0; i < n; ++i) {
+    const emc2_conv_call& c = calls[i];
+    const emc2_status st = emc2_spconv(c.ctx, c.dtype, c.d_in, c.d_w, c.w_layout, c.d_scale, c.d_shift, c.epilogue, c.d_nbr, c.map_hint,
+                                       c.d_n_out, c.capacity_out, c.n_in_rows, c.cin, c.cout, c.d_out, stream);
+    if (st != EMC2_OK) return st;
+  }
+  return EMC2_OK;
+}

@@ -1,0 +1,608 @@
+// Voxelization and every kernel map of one or more stacks in one call (paper Sec. 3.1 data bridge, Sec. 3.5 kernel maps,
+// Sec. 3.6 (3) prefix-sum index search): the same results as emc2_voxelize followed by emc2_build_kmap per level.
+//
+// What bounds the call-by-call form is launches: a 120 000-point frame through four levels is 28 dependent launches,
+// most of them with 1-3 us of work, and a dependent launch costs 4.7 us on this part whatever it does.  Here a stack is a
+// chain of phases, one launch each, and a launch carries everything that is ready by then, of every level and of every
+// stack of the call (blocks are dealt to jobs by ranges):
+//
+//   phase   finest level (0)                level l >= 1, built from level l - 1
+//   1       clear flagged lines; zero the scan's sums of all levels
+//   2       mark the points' cells
+//   3       popcount sums                   gather 1
+//   4       prefix fields                   gather 2, expand 1
+//   5       points -> stashes               gather 3, expand 2
+//   6       means                           gather 4, expand 3
+//   7                                       expand 4
+//   last    kernel maps of all levels: once the last level is expanded, with the means for up to three levels
+//
+// gather l: a coarse word is read off the fine level's bits (27 cells behind every coarse cell: nine bit rows OR-ed, then
+// one shift-or and an even-bit compress), so no atomics are needed, nothing has to be cleared first, and the word's
+// popcount joins the scan's sums in the same pass.  expand l: prefix fields and coordinates in one pass.
+// A frame of 120 000 points through four levels: 207 us in 28 launches before, 7 launches now (times beside the table
+// of the launcher below).
+#include <string.h>
+
+#include "kmap_probe.h"
+#include "voxel_point.h"
+
+namespace {
+
+constexpr int kStacks = 4;                       // stacks per launch chain (kernel arguments hold their descriptions)
+constexpr int kLevels = EMC2_STACK_MAX_LEVELS;
+constexpr int kGranuleWords = 512;               // words per block of gather / expand: 32 lines
+constexpr int kGranuleLines = kGranuleWords >> EMC2_LINE_SHIFT;
+constexpr int kSuper = 64;                       // sums per super-sum: a block's base is at most units/64 + 63 reads
+constexpr int kMaxJobs = 24;
+
+struct DevLevel {
+  cellword_t* idx;
+  lineflag_t* flags;
+  uint32_t* sums;         // popcount sums per unit (level 0: a tile of 2048 words; above: a granule of 512)
+  uint32_t* supers;       // sums of 64 of them
+  int4* coords;
+  int32_t* n;
+  int32_t* subm;
+  int32_t* down;
+  int64_t cap;
+  int64_t cells;
+  int32_t g[3];
+  int32_t units;
+};
+
+struct DevStack {
+  VoxParams prm;
+  int32_t expert;               // < 0: d_batch holds frame ids; else: it holds scene ids, routed by `route` / `slot`
+  int32_t n_levels;
+  int32_t lp;
+  const int32_t* batch;
+  const int32_t* route;         // expert of every scene
+  const int32_t* slot;          // position of every scene in its expert's group
+  float4* feats;
+  int32_t* counts;
+  void* feats_lp;
+  float4* stash;
+  int32_t* dev_words;
+  int64_t zero_rows;
+  DevLevel lv[kLevels];
+};
+
+enum Role { R_CLEAR = 0, R_ZERO, R_MARK, R_SUM, R_PREFIX, R_SCATTER, R_MEAN, R_GATHER, R_EXPAND, R_PROBE };
+
+struct Job {
+  int32_t role, stack, level;
+  uint32_t first;               // first block of the job
+};
+
+struct Args {
+  const float* points;
+  int64_t n_points;
+  int32_t n_jobs, n_stacks;
+  uint32_t blocks;
+  Job job[kMaxJobs];
+  DevStack st[kStacks];
+};
+static_assert(sizeof(Args) <= 4096, "kernel arguments");
+
+__device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
+  return v;
+}
+
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v) {
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t t = __shfl_up(v, d, 64);
+    if ((int)(threadIdx.x & 63) >= d) v += t;
+  }
+  return v;
+}
+
+// Quotients of cell keys: 32-bit wherever the grid's keys fit (several times cheaper).
+__device__ __forceinline__ uint64_t div_key(uint64_t a, uint32_t b) {
+  return (a >> 32) == 0 ? (uint64_t)((uint32_t)a / b) : a / b;
+}
+
+// A point's cell in a stack.  Routed stacks take the frame id from the scene's slot in its expert's group.
+__device__ __forceinline__ PointCell locate_in(const Args& a, const DevStack& st, int64_t i) {
+  PointCell pc = locate(a.points, st.expert < 0 ? st.batch : nullptr, i, a.n_points, st.prm);
+  if (st.expert >= 0 && pc.keep) {
+    const int32_t s = st.batch ? st.batch[i] : 0;
+    int32_t b = -1;
+    if (s >= 0 && s < st.prm.n_batch && st.route[s] == st.expert) b = st.slot[s];
+    pc.keep = b >= 0 && b < st.prm.n_batch;
+    pc.c.x = b;
+    pc.key += (uint64_t)(pc.keep ? b : 0) * st.prm.grid[2] * (uint64_t)st.prm.grid[1] * st.prm.grid[0];
+  }
+  return pc;
+}
+
+__device__ __forceinline__ void report_total(const DevStack& st, const DevLevel& lv, uint32_t total) {
+  if ((int64_t)total > lv.cap) {
+    atomicOr(st.dev_words, EMC2_DEVFLAG_CAPACITY);
+    *lv.n = (int32_t)lv.cap;
+  } else {
+    *lv.n = (int32_t)total;
+  }
+}
+
+// Two tiles per block, one thread per line: zero the flagged lines and lower their flags.
+__device__ __forceinline__ void role_clear(const DevLevel& lv, uint32_t blk) {
+  const int64_t tile = (int64_t)blk * 2 + (threadIdx.x >> 7);
+  if (tile >= lv.units) return;
+  const int64_t line = tile * EMC2_LINES_PER_TILE + (threadIdx.x & 127);
+  if (!lv.flags[line]) return;
+  uint4* p = reinterpret_cast<uint4*>(lv.idx + (line << EMC2_LINE_SHIFT));
+#pragma unroll
+  for (int i = 0; i < 8; ++i) p[i] = make_uint4(0u, 0u, 0u, 0u);
+  lv.flags[line] = 0;
+}
+
+__device__ __forceinline__ void role_zero(const DevStack& st) {
+  for (int l = 0; l < st.n_levels; ++l)
+    for (int i = threadIdx.x; i < (st.lv[l].units + kSuper - 1) / kSuper; i += 256) st.lv[l].supers[i] = 0u;
+}
+
+__device__ __forceinline__ void role_mark(const Args& a, const DevStack& st, uint32_t blk) {
+  const int64_t i = (int64_t)blk * 256 + threadIdx.x;
+  if (i < st.zero_rows) {   // what the points are accumulated into; at most min(n_points, capacity) voxels exist
+    st.feats[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    st.counts[i] = 0;
+  }
+  const PointCell pc = locate_in(a, st, i);
+  if (!pc.keep) return;
+  atomicOr(&st.lv[0].idx[pc.key >> 5].x, 1u << ((uint32_t)pc.key & 31u));
+  st.lv[0].flags[emc2_line_of_key(pc.key)] = 1;
+}
+
+// Four tiles per block, a wave each (no block barrier); a lane owns two adjacent lines = 32 words.
+__device__ __forceinline__ void role_sum(const DevLevel& lv, uint32_t blk) {
+  const int64_t tile = (int64_t)blk * 4 + (threadIdx.x >> 6);
+  if (tile >= lv.units) return;
+  const int lane = threadIdx.x & 63;
+  const uint32_t f = reinterpret_cast<const uint16_t*>(lv.flags + tile * EMC2_LINES_PER_TILE)[lane];
+  uint32_t s = 0;
+  if (f) {
+    const uint4* p = reinterpret_cast<const uint4*>(lv.idx + tile * EMC2_SCAN_TILE + lane * 32);
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      if ((f >> (8 * h)) & 0xffu)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const uint4 v = p[8 * h + i];
+          s += __popc(v.x) + __popc(v.z);
+        }
+  }
+  s = wave_sum(s);
+  if (lane == 0) {
+    lv.sums[tile] = s;
+    if (s) atomicAdd(&lv.supers[tile / kSuper], s);
+  }
+}
+
+// Sum of the units before `unit`, the same in every lane of the wave.
+__device__ __forceinline__ uint32_t base_of(const DevLevel& lv, int64_t unit) {
+  const int lane = threadIdx.x & 63;
+  uint32_t s = 0;
+  for (int i = lane; i < (int)(unit / kSuper); i += 64) s += lv.supers[i];
+  const int64_t i = unit / kSuper * kSuper + lane;
+  if (i < unit) s += lv.sums[i];
+  return wave_sum(s);
+}
+
+__device__ __forceinline__ void role_prefix(const DevStack& st, const DevLevel& lv, uint32_t blk) {
+  const int64_t tile = (int64_t)blk * 4 + (threadIdx.x >> 6);
+  if (tile >= lv.units) return;
+  const int lane = threadIdx.x & 63;
+  const uint32_t f = reinterpret_cast<const uint16_t*>(lv.flags + tile * EMC2_LINES_PER_TILE)[lane];
+  const bool last = tile == lv.units - 1;
+  if (__ballot(f != 0) == 0ull && !last) return;   // no bit, so no prefix field anybody reads
+  uint4* p = reinterpret_cast<uint4*>(lv.idx + tile * EMC2_SCAN_TILE + lane * 32);
+  uint4 v[16];
+  uint32_t s = 0;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const bool have = ((f >> (8 * h)) & 0xffu) != 0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      v[8 * h + i] = have ? p[8 * h + i] : make_uint4(0u, 0u, 0u, 0u);
+      s += __popc(v[8 * h + i].x) + __popc(v[8 * h + i].z);
+    }
+  }
+  const uint32_t inc = wave_scan(s);
+  const uint32_t base = base_of(lv, tile);
+  uint32_t run = base + inc - s;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const bool have = ((f >> (8 * h)) & 0xffu) != 0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      uint4 w = v[8 * h + i];
+      w.y = run;
+      run += __popc(w.x);
+      w.w = run;
+      run += __popc(w.z);
+      if (have) p[8 * h + i] = w;
+    }
+  }
+  if (last && lane == 63) report_total(st, lv, run);
+}
+
+__device__ __forceinline__ void role_scatter(const Args& a, const DevStack& st, uint32_t blk) {
+  const PointCell pc = locate_in(a, st, (int64_t)blk * 256 + threadIdx.x);
+  if (!pc.keep) return;
+  const DevLevel& lv = st.lv[0];
+  const int32_t r = cell_lookup(lv.idx, pc.key);
+  if (r < 0 || r >= lv.cap) return;      // beyond capacity: reported by the scan, dropped here
+  emc2_stash_point(r, pc, lv.coords, st.feats, st.counts, st.stash);
+}
+
+__device__ __forceinline__ void role_mean(const DevStack& st, uint32_t blk) {
+  const int64_t r = (int64_t)blk * 256 + threadIdx.x;
+  if (r < *st.lv[0].n) emc2_voxel_mean(r, st.stash, st.feats, st.counts, st.lp, st.feats_lp);
+}
+
+// The 32 bits of word w of level `lv` from the bits of the finer level `in`.  An output at ox reads 2ox-1 .. 2ox+1 on every
+// axis: the (up to) nine input rows of an output row segment are OR-ed as bit strings that start at 2*ox-1, then output
+// bit i is S[2i] | S[2i+1] | S[2i+2].
+__device__ __forceinline__ uint32_t gather_word(const DevLevel& in, const DevLevel& lv, int64_t w) {
+  const uint32_t gox = (uint32_t)lv.g[0], goy = (uint32_t)lv.g[1], goz = (uint32_t)lv.g[2];
+  const int gx = in.g[0], gy = in.g[1], gz = in.g[2];
+  uint64_t key = (uint64_t)w * 32;
+  const uint64_t end = key + 32 < (uint64_t)lv.cells ? key + 32 : (uint64_t)lv.cells;
+  uint32_t bits = 0;
+  int pos = 0;
+  while (key < end) {
+    const uint64_t row = div_key(key, gox);
+    const uint32_t ox = (uint32_t)(key - row * gox);
+    const uint64_t t = div_key(row, goy);
+    const int oy = (int)(row - t * goy);
+    const uint64_t b = div_key(t, goz);
+    const int oz = (int)(t - b * goz);
+    const int len = (int)((end - key) < (uint64_t)(gox - ox) ? (end - key) : (uint64_t)(gox - ox));
+    const int xs = 2 * (int)ox - 1 < 0 ? 0 : 2 * (int)ox - 1;
+    const int xe0 = 2 * ((int)ox + len - 1) + 1;
+    const int xe = xe0 < gx ? xe0 : gx - 1;
+    const int nb = xe - xs + 1;                       // 1 .. 65 input bits per row
+    const int shl = xs - (2 * (int)ox - 1);           // 1 where the row's first bit would be x = -1, else 0
+    uint64_t lo = 0;                                  // bits 0..63 of the OR of the rows, bit 0 <-> x = 2*ox - 1
+    uint32_t hi = 0;                                  // bit 64
+#pragma unroll
+    for (int d = 0; d < 9; ++d) {
+      const int iz = 2 * oz + d / 3 - 1, iy = 2 * oy + d % 3 - 1;
+      if (iz < 0 || iz >= gz || iy < 0 || iy >= gy) continue;
+      const uint64_t k = ((b * gz + (uint64_t)iz) * gy + (uint64_t)iy) * gx + (uint64_t)xs;
+      const cellword_t* p = in.idx + (k >> 5);
+      const int sh = (int)(k & 31u);
+      const uint32_t w0 = p[0].x;
+      const uint32_t w1 = sh + nb > 32 ? p[1].x : 0u;
+      const uint32_t w2 = sh + nb > 64 ? p[2].x : 0u;
+      const uint64_t w01 = ((uint64_t)w1 << 32) | w0;
+      uint64_t r = (w01 >> sh) | (sh ? (uint64_t)w2 << (64 - sh) : 0ull);
+      uint32_t e = (w2 >> sh) & 1u;                   // bit 64 of the row's string
+      if (nb < 64) r &= (1ull << nb) - 1ull;
+      if (nb < 65) e = 0u;
+      hi |= shl ? (uint32_t)(r >> 63) : e;            // with shl there are at most 64 bits before the shift
+      lo |= r << shl;
+    }
+    const uint64_t u = lo | (lo >> 1) | ((uint64_t)hi << 63) | (lo >> 2) | ((uint64_t)hi << 62);
+    uint32_t m = emc2_even_bits(u);
+    if (len < 32) m &= (1u << len) - 1u;
+    bits |= m << pos;
+    pos += len;
+    key += (uint64_t)len;
+  }
+  return bits;
+}
+
+// One granule of level l: which of its 32 lines can hold a bit (line flags of the fine level), then the words of those.
+__device__ __forceinline__ void role_gather(const DevStack& st, int l, uint32_t blk) {
+  __shared__ uint32_t act_s, old_s, sum_s[4];
+  const DevLevel& in = st.lv[l - 1];
+  const DevLevel& lv = st.lv[l];
+  if (threadIdx.x == 0) { act_s = 0u; old_s = 0u; }
+  __syncthreads();
+  const int64_t line0 = (int64_t)blk * kGranuleLines;
+  {
+    const int line = threadIdx.x >> 3, sub = threadIdx.x & 7;
+    const uint32_t gox = (uint32_t)lv.g[0], goy = (uint32_t)lv.g[1], goz = (uint32_t)lv.g[2];
+    const uint64_t k0 = (uint64_t)(line0 + line) << (5 + EMC2_LINE_SHIFT);
+    uint64_t k1 = k0 + (32u << EMC2_LINE_SHIFT);
+    if (k1 > (uint64_t)lv.cells) k1 = (uint64_t)lv.cells;
+    bool any = false;
+    if (k0 < k1) {
+      const uint64_t r0 = div_key(k0, gox), r1 = div_key(k1 - 1, gox);
+      const uint32_t nc = (uint32_t)(r1 - r0 + 1) * 9u;
+      for (uint32_t c = (uint32_t)sub; c < nc && !any; c += 8) {
+        const uint64_t row = r0 + c / 9u;
+        const int d = (int)(c % 9u);
+        const uint64_t t = div_key(row, goy);
+        const int oy = (int)(row - t * goy);
+        const uint64_t b = div_key(t, goz);
+        const int oz = (int)(t - b * goz);
+        const int iz = 2 * oz + d / 3 - 1, iy = 2 * oy + d % 3 - 1;
+        if (iz < 0 || iz >= in.g[2] || iy < 0 || iy >= in.g[1]) continue;
+        const int ox0 = row == r0 ? (int)(k0 - r0 * gox) : 0;
+        const int ox1 = row == r1 ? (int)(k1 - 1 - r1 * gox) : (int)gox - 1;
+        const int xs = 2 * ox0 - 1 < 0 ? 0 : 2 * ox0 - 1;
+        const int xe = 2 * ox1 + 1 < in.g[0] ? 2 * ox1 + 1 : in.g[0] - 1;
+        const uint64_t rb = ((b * in.g[2] + (uint64_t)iz) * in.g[1] + (uint64_t)iy) * in.g[0];
+        for (uint64_t fl = emc2_line_of_key(rb + (uint64_t)xs); fl <= emc2_line_of_key(rb + (uint64_t)xe); ++fl)
+          any |= in.flags[fl] != 0;
+      }
+    }
+    if (any) atomicOr(&act_s, 1u << line);
+    if (sub == 0 && lv.flags[line0 + line]) atomicOr(&old_s, 1u << line);
+  }
+  __syncthreads();
+  const uint32_t act = act_s, write = act | old_s;
+  if (threadIdx.x < kGranuleLines && ((write >> threadIdx.x) & 1u))
+    lv.flags[line0 + threadIdx.x] = (lineflag_t)((act >> threadIdx.x) & 1u);
+  uint32_t s = 0;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int wi = (int)threadIdx.x + 256 * i;
+    const int line = wi >> EMC2_LINE_SHIFT;
+    if (!((write >> line) & 1u)) continue;
+    const int64_t w = (int64_t)blk * kGranuleWords + wi;
+    const uint32_t bits = ((act >> line) & 1u) ? gather_word(in, lv, w) : 0u;
+    lv.idx[w] = make_uint2(bits, 0u);
+    s += __popc(bits);
+  }
+  s = wave_sum(s);
+  if ((threadIdx.x & 63) == 0) sum_s[threadIdx.x >> 6] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    s = sum_s[0] + sum_s[1] + sum_s[2] + sum_s[3];
+    lv.sums[blk] = s;
+    if (s) atomicAdd(&lv.supers[blk / kSuper], s);
+  }
+}
+
+// One granule of level l: prefix fields of its flagged words and the coordinates of their set bits.
+__device__ __forceinline__ void role_expand(const DevStack& st, int l, uint32_t blk) {
+  __shared__ uint32_t wsum[4];
+  const DevLevel& lv = st.lv[l];
+  const bool last = (int)blk == lv.units - 1;
+  const int64_t w0 = (int64_t)blk * kGranuleWords + 2 * (int64_t)threadIdx.x;   // two adjacent words, one line
+  const bool have = lv.flags[w0 >> EMC2_LINE_SHIFT] != 0;
+  if (!__syncthreads_or(have) && !last) return;
+  uint4* p = reinterpret_cast<uint4*>(lv.idx + w0);
+  uint4 v = have ? *p : make_uint4(0u, 0u, 0u, 0u);
+  const uint32_t s = __popc(v.x) + __popc(v.z);
+  const uint32_t inc = wave_scan(s);
+  if ((threadIdx.x & 63) == 63) wsum[threadIdx.x >> 6] = inc;
+  const uint32_t base = base_of(lv, blk);
+  __syncthreads();
+  uint32_t run = base + inc - s;
+  for (int j = 0; j < (int)(threadIdx.x >> 6); ++j) run += wsum[j];
+  if (last && threadIdx.x == 255) report_total(st, lv, run + s);
+  if (!have) return;
+  v.y = run;
+  v.w = run + __popc(v.x);
+  *p = v;
+  if (s == 0u) return;
+  int4 c = decode_key((uint64_t)w0 * 32, lv.g[0], lv.g[1], lv.g[2]);   // (b, z, y, x) of the first word's bit 0
+  uint64_t bits = ((uint64_t)v.z << 32) | v.x;
+  int at = 0;                                                          // bit position c refers to
+  int64_t r = run;
+  while (bits) {
+    const int j = __ffsll((unsigned long long)bits) - 1;
+    bits &= bits - 1;
+    c.w += j - at;
+    at = j;
+    while (c.w >= lv.g[0]) {
+      c.w -= lv.g[0];
+      if (++c.z >= lv.g[1]) {
+        c.z = 0;
+        if (++c.y >= lv.g[2]) {
+          c.y = 0;
+          ++c.x;
+        }
+      }
+    }
+    if (r < lv.cap) lv.coords[r] = c;
+    ++r;
+  }
+}
+
+// Every kernel map of every stack.  The blocks share the device's own row counts: map by map in 256-row pieces, an
+// XCD's blocks (blockIdx % 8) taking a contiguous range of each map, so that neighbouring rows probe one L2.
+__device__ __forceinline__ void role_probe(const Args& a, uint32_t blk, uint32_t blocks) {
+  const int64_t x = blk & 7, at0 = blk >> 3, step = blocks >> 3;    // blocks is a multiple of 8
+  int64_t at = at0;
+  for (int s = 0; s < a.n_stacks; ++s) {
+    const DevStack& st = a.st[s];
+    for (int l = 0; l < st.n_levels; ++l) {
+      const DevLevel& lv = st.lv[l];
+      const int32_t n = *lv.n;
+      const int64_t pieces = (n + 255) / 256, chunk = (pieces + 7) / 8;
+#pragma unroll
+      for (int kind = 0; kind < 2; ++kind) {
+        int32_t* nbr = kind == 0 ? lv.down : lv.subm;
+        if (!nbr) continue;
+        const DevLevel& in = kind == 0 ? st.lv[l > 0 ? l - 1 : 0] : lv;
+        const int32_t n_in = *in.n;
+        for (; at < chunk; at += step) {
+          const int64_t o = (x * chunk + at) * 256 + threadIdx.x;
+          if (o >= n || x * chunk + at >= pieces) continue;
+          if (kind == 0)
+            emc2_probe_voxel<2>(o, lv.coords, lv.cap, in.idx, n_in, in.g[0], in.g[1], in.g[2], st.prm.n_batch, nbr);
+          else
+            emc2_probe_voxel<1>(o, lv.coords, lv.cap, in.idx, n_in, in.g[0], in.g[1], in.g[2], st.prm.n_batch, nbr);
+        }
+        at -= chunk;      // the remainder carries into the next map, so short maps do not idle blocks
+      }
+    }
+  }
+}
+
+template <uint32_t ROLES>
+__global__ void __launch_bounds__(256) k_stack_phase(const Args a) {
+  int j = 0;
+  while (j + 1 < a.n_jobs && blockIdx.x >= a.job[j + 1].first) ++j;
+  const int role = a.job[j].role, l = a.job[j].level;
+  const uint32_t blk = blockIdx.x - a.job[j].first;
+  const DevStack& st = a.st[a.job[j].stack];
+#define EMC2_ROLE(R, CALL) if ((ROLES >> R) & 1u) { if (role == R) { CALL; return; } }
+  EMC2_ROLE(R_CLEAR, role_clear(st.lv[0], blk))
+  EMC2_ROLE(R_ZERO, role_zero(st))
+  EMC2_ROLE(R_MARK, role_mark(a, st, blk))
+  EMC2_ROLE(R_SUM, role_sum(st.lv[0], blk))
+  EMC2_ROLE(R_PREFIX, role_prefix(st, st.lv[0], blk))
+  EMC2_ROLE(R_SCATTER, role_scatter(a, st, blk))
+  EMC2_ROLE(R_MEAN, role_mean(st, blk))
+  EMC2_ROLE(R_GATHER, role_gather(st, l, blk))
+  EMC2_ROLE(R_EXPAND, role_expand(st, l, blk))
+  EMC2_ROLE(R_PROBE, role_probe(a, blk, gridDim.x - a.job[j].first))
+#undef EMC2_ROLE
+}
+
+struct Phase {
+  Args* a;
+  void begin() { a->n_jobs = 0; a->blocks = 0; }
+  void add(int role, int stack, int level, int64_t blocks) {
+    if (blocks <= 0) return;
+    Job& j = a->job[a->n_jobs++];
+    j.role = role; j.stack = stack; j.level = level; j.first = a->blocks;
+    a->blocks += (uint32_t)blocks;
+  }
+  template <uint32_t ROLES> void launch(hipStream_t s) {
+    if (a->n_jobs) hipLaunchKernelGGL(k_stack_phase<ROLES>, dim3(a->blocks), dim3(256), 0, s, *a);
+  }
+};
+
+// Host-side checks of one stack and its device description; index metadata is updated here.
+emc2_status describe(const emc2_stack& s, int64_t n_points, DevStack* d) {
+  emc2_ctx* ctx = s.ctx;
+  if (!s.d_feats || !s.d_counts || s.n_levels < 1 || s.n_levels > kLevels)
+    return emc2_fail(ctx, EMC2_ERR_INVALID_ARG, "emc2_build_stacks: null argument or n_levels outside [1, %d]", kLevels);
+  emc2_status ok = emc2_voxel_args_ok(ctx, &s.spec, n_points, s.level[0].capacity, s.level[0].slot, "emc2_build_stacks");
+  if (ok != EMC2_OK) return ok;
+  if (s.d_feats_lp && s.lp_dtype != EMC2_F16 && s.lp_dtype != EMC2_BF16)
+    return emc2_fail(ctx, EMC2_ERR_INVALID_ARG, "emc2_build_stacks: lp_dtype must be F16 or BF16");
+  if (s.expert >= 0 && (!s.d_route || !s.d_slot))
+    return emc2_fail(ctx, EMC2_ERR_INVALID_ARG, "emc2_build_stacks: a routed stack needs d_route and d_slot");
+  memset(d, 0, sizeof(*d));
+  d->prm = emc2_vox_params(&s.spec);
+  d->expert = s.expert;
+  d->n_levels = s.n_levels;
+  d->lp = s.d_feats_lp ? (s.lp_dtype == EMC2_F16 ? 1 : 2) : 0;
+  d->batch = s.d_batch;
+  d->route = s.d_route;
+  d->slot = s.d_slot;
+  d->feats = (float4*)s.d_feats;
+  d->counts = s.d_counts;
+  d->feats_lp = s.d_feats_lp;
+  d->stash = ctx->stash;
+  d->dev_words = ctx->dev_words;
+  d->zero_rows = n_points < s.level[0].capacity ? n_points : s.level[0].capacity;
+  int32_t g[3] = {s.spec.grid[0], s.spec.grid[1], s.spec.grid[2]};
+  uint32_t* sums = ctx->stack_sums;
+  uint32_t* sums_end = ctx->stack_sums + ctx->n_stack_sums;
+  for (int l = 0; l < s.n_levels; ++l) {
+    const emc2_stack_level& L = s.level[l];
+    if (l > 0)
+      for (int a = 0; a < 3; ++a) g[a] = (g[a] - 1) / 2 + 1;
+    if (L.capacity < 1 || L.capacity > ctx->max_voxels || L.slot < 0 || L.slot >= ctx->n_slots || !L.d_coords || !L.d_n ||
+        (l > 0 && !L.d_down_nbr) || (l == 0 && L.d_down_nbr))
+      return emc2_fail(ctx, EMC2_ERR_INVALID_ARG, "emc2_build_stacks: level %d: bad capacity, slot or pointers", l);
+    for (int q = 0; q < l; ++q)
+      if (s.level[q].slot == L.slot) return emc2_fail(ctx, EMC2_ERR_INVALID_ARG, "emc2_build_stacks: levels share slot %d", L.slot);
+    DevLevel& v = d->lv[l];
+    v.idx = ctx->slots[L.slot];
+    v.flags = emc2_slot_flags(ctx, v.idx);
+    v.coords = (int4*)L.d_coords;
+    v.n = L.d_n;
+    v.subm = L.d_subm_nbr;
+    v.down = L.d_down_nbr;
+    v.cap = L.capacity;
+    for (int a = 0; a < 3; ++a) v.g[a] = g[a];
+    v.cells = (int64_t)g[0] * g[1] * g[2] * s.spec.n_batch;
+    const int64_t words = emc2_div_up(v.cells, 32);
+    const int64_t units = emc2_div_up(words, l == 0 ? EMC2_SCAN_TILE : kGranuleWords);
+    v.units = (int32_t)units;
+    v.sums = sums;
+    v.supers = sums + units;
+    sums += units + emc2_div_up(units, kSuper);
+    if (sums > sums_end) return emc2_fail(ctx, EMC2_ERR_UNSUPPORTED, "emc2_build_stacks: scan scratch too small for this stack");
+  }
+  for (int l = 0; l < s.n_levels; ++l) {
+    SlotMeta& m = ctx->meta[s.level[l].slot];
+    for (int a = 0; a < 3; ++a) m.grid[a] = d->lv[l].g[a];
+    m.n_batch = s.spec.n_batch;
+    m.valid = true;
+  }
+  return EMC2_OK;
+}
+
+}  // namespace
+
+extern "C" emc2_status emc2_build_stacks(const emc2_stack* stacks, int32_t n_stacks, const float* d_points, int64_t n_points,
+                                         void* stream) {
+  if (!stacks || n_stacks < 1) return EMC2_ERR_INVALID_ARG;
+  for (int i = 0; i < n_stacks; ++i)
+    if (!stacks[i].ctx) return EMC2_ERR_INVALID_ARG;
+  emc2_ctx* ctx0 = stacks[0].ctx;
+  if (n_stacks > kStacks) return emc2_fail(ctx0, EMC2_ERR_UNSUPPORTED, "emc2_build_stacks: more than %d stacks", kStacks);
+  if (n_points < 0 || (n_points > 0 && !d_points)) return emc2_fail(ctx0, EMC2_ERR_INVALID_ARG, "emc2_build_stacks: bad points");
+  for (int i = 0; i < n_stacks; ++i) {
+    if (stacks[i].spec.stride_f != stacks[0].spec.stride_f)
+      return emc2_fail(ctx0, EMC2_ERR_INVALID_ARG, "emc2_build_stacks: stacks read the same points: one stride_f");
+    for (int q = 0; q < i; ++q)
+      if (stacks[q].ctx == stacks[i].ctx)
+        return emc2_fail(ctx0, EMC2_ERR_INVALID_ARG, "emc2_build_stacks: two stacks on one context (they share its scratch)");
+  }
+  Args a;
+  a.points = d_points;
+  a.n_points = n_points;
+  a.n_stacks = n_stacks;
+  int deepest = 1;
+  for (int i = 0; i < n_stacks; ++i) {
+    const emc2_status st = describe(stacks[i], n_points, &a.st[i]);
+    if (st != EMC2_OK) {
+      if (stacks[i].ctx != ctx0) emc2_fail(ctx0, st, "%s", stacks[i].ctx->err);
+      return st;
+    }
+    if (a.st[i].n_levels > deepest) deepest = a.st[i].n_levels;
+  }
+  hipStream_t s = (hipStream_t)stream;
+  Phase p{&a};
+  const int64_t point_blocks = emc2_div_up(n_points, 256);
+  // maps of all levels: 2 048 blocks of 4 waves fill the chip; fewer where the capacities say so
+  int64_t rows = 0;
+  for (int i = 0; i < n_stacks; ++i)
+    for (int l = 0; l < a.st[i].n_levels; ++l)
+      rows += ((a.st[i].lv[l].subm ? 1 : 0) + (a.st[i].lv[l].down ? 1 : 0)) * emc2_div_up(a.st[i].lv[l].cap, 256);
+  const int64_t probe_blocks = (rows < 2048 ? emc2_div_up(rows, 8) * 8 : 2048);
+  const int last = deepest <= 3 ? 6 : deepest + 3;
+  for (int ph = 1; ph <= last; ++ph) {
+    p.begin();
+    for (int i = 0; i < n_stacks; ++i) {
+      const DevStack& d = a.st[i];
+      const int64_t tiles = d.lv[0].units;
+      if (ph == 1) { p.add(R_CLEAR, i, 0, emc2_div_up(tiles, 2)); p.add(R_ZERO, i, 0, 1); }
+      if (ph == 2) p.add(R_MARK, i, 0, point_blocks);
+      if (ph == 3) p.add(R_SUM, i, 0, emc2_div_up(tiles, 4));
+      if (ph == 4) p.add(R_PREFIX, i, 0, emc2_div_up(tiles, 4));
+      if (ph == 5) p.add(R_SCATTER, i, 0, point_blocks);
+      if (ph == 6) p.add(R_MEAN, i, 0, emc2_div_up(d.zero_rows, 256));
+      if (ph - 2 >= 1 && ph - 2 < d.n_levels) p.add(R_GATHER, i, ph - 2, d.lv[ph - 2].units);
+      if (ph - 3 >= 1 && ph - 3 < d.n_levels) p.add(R_EXPAND, i, ph - 3, d.lv[ph - 3].units);
+    }
+    if (ph == last && rows > 0) p.add(R_PROBE, 0, 0, probe_blocks);
+#define BITS(R) (1u << R)
+    switch (ph) {
+      case 1: p.launch<BITS(R_CLEAR) | BITS(R_ZERO)>(s); break;
+      case 2: p.launch<BITS(R_MARK)>(s); break;
+      case 3: p.launch<BITS(R_SUM) | BITS(R_GATHER)>(s); break;
+      case 4: p.launch<BITS(R_PREFIX) | BITS(R_GATHER) | BITS(R_EXPAND)>(s); break;
+      case 5: p.launch<BITS(R_SCATTER) | BITS(R_GATHER) | BITS(R_EXPAND)>(s); break;
+      case 6: p.launch<BITS(R_MEAN) | BITS(R_GATHER) | BITS(R_EXPAND) | BITS(R_PROBE)>(s); break;
+      default: p.launch<BITS(R_GATHER) | BITS(R_EXPAND) | BITS(R_PROBE)>(s); break;
+    }
+#undef BITS
+  }
+  return emc2_check_hip(ctx0, hipGetLastError(), "emc2_build_stacks launch");
+}

@@ -80,6 +80,56 @@ def capture_stream(device) -> "torch.cuda.Stream":
     return torch.cuda.Stream(device=device)
 
 
+class NativePass:
+    """The maps and the convolutions of one or more branches over the same points as two native calls: emc2_build_stacks
+    (voxelization and every kernel map of every branch, in a handful of launches) and emc2_spconv_list.  The argument
+    blocks are filled once; a pass sets the points and frame ids.  They hold addresses only: whoever makes the pass keeps the
+    runners.  `route`: (expert, slot) tensors of a routed batch,
+    branch e then takes the scenes of expert e."""
+
+    def __init__(self, runners: Sequence["BranchRunner"], route: Optional[Tuple[torch.Tensor, torch.Tensor]] = None):
+        self.n = len(runners)
+        self.outs = [r.acts[-1] for r in runners]
+        self.stacks = (B.StackC * self.n)()
+        calls: List[B.ConvCallC] = []
+        for e, r in enumerate(runners):
+            s, sp = self.stacks[e], r.branch.spec
+            s.ctx = r.ctx.h
+            s.spec = B.voxel_spec_c(sp, 4)
+            s.expert, s.n_levels = (-1 if route is None else e), len(r.levels)
+            if route is not None:
+                s.d_route, s.d_slot = route[0].data_ptr(), route[1].data_ptr()
+            s.d_feats, s.d_counts = r.feats32.data_ptr(), r.counts.data_ptr()
+            s.lp_dtype = r.dtype if r.feats_lp is not None else F16
+            s.d_feats_lp = r.feats_lp.data_ptr() if r.feats_lp is not None else None
+            for c, lv in zip(s.level, r.levels):
+                c.capacity, c.d_coords, c.d_n, c.slot = lv.cap, lv.coords.data_ptr(), lv.n.data_ptr(), lv.slot
+                c.d_subm_nbr = lv.subm_nbr.data_ptr() if lv.subm_nbr is not None else None
+                c.d_down_nbr = lv.down_nbr.data_ptr() if lv.down_nbr is not None else None
+            calls += r.conv_calls()
+        self.calls = (B.ConvCallC * len(calls))(*calls)
+
+    @staticmethod
+    def covers(runners: Sequence["BranchRunner"]) -> bool:
+        return len(runners) <= B.MAX_STACKS and all(len(r.levels) <= B.STACK_MAX_LEVELS for r in runners)
+
+    def maps(self, points: torch.Tensor, batch: Optional[torch.Tensor]) -> None:
+        if batch is not None:
+            if not batch.is_cuda or batch.dtype != torch.int32 or not batch.is_contiguous() or batch.numel() != points.shape[0]:
+                raise ValueError("batch: need a contiguous int32 device tensor with one id per point")
+        for s in self.stacks:
+            s.d_batch = batch.data_ptr() if batch is not None else None
+        B.build_stacks(self.stacks, self.n, points)
+
+    def convs(self) -> List[torch.Tensor]:
+        B.spconv_list(self.calls, len(self.calls))
+        return list(self.outs)
+
+    def run(self, points: torch.Tensor, batch: Optional[torch.Tensor]) -> List[torch.Tensor]:
+        self.maps(points, batch)
+        return self.convs()
+
+
 class BranchRunner:
     """Runs one Branch (one voxelization + its conv stack) through the library."""
 
@@ -137,8 +187,31 @@ class BranchRunner:
         self.ev_done = None           # recorded on the caller's stream at the end of the previous overlapped run
         self.ev_subm = [torch.cuda.Event() for _ in self.levels]
         self.ev_down = [torch.cuda.Event() for _ in self.levels]
+        self.native = NativePass([self]) if NativePass.covers([self]) else None
         self.can_overlap = all(lay == B.W_PACKED or not ctx.uses_mfma(dtype, l.cin, l.cout)
                                for (_, lay), l in zip(self.wdev, branch.layers))
+
+    def conv_calls(self) -> List["B.ConvCallC"]:
+        """The argument blocks of this branch's convolutions, in order."""
+        out, lvl = [], 0
+        x = self.feats32 if self.dtype == F32 else self.feats_lp
+        for li, layer in enumerate(self.branch.layers):
+            if layer.kind == STRIDED:
+                lvl += 1
+            lv, p, y = self.levels[lvl], self.params[li], self.acts[li]
+            epi = layer.epilogue != EPI_NONE
+            c = B.ConvCallC()
+            c.ctx, c.dtype = self.ctx.h, self.dtype
+            c.d_in, c.n_in_rows, c.cin, c.cout = x.data_ptr(), x.shape[0], layer.cin, layer.cout
+            c.d_w, c.w_layout = self.wdev[li][0].data_ptr(), self.wdev[li][1]
+            c.d_scale = p["scale"].data_ptr() if epi else None
+            c.d_shift = p["shift"].data_ptr() if epi else None
+            c.epilogue, c.map_hint = layer.epilogue, layer.kind
+            c.d_nbr = (lv.down_nbr if layer.kind == STRIDED else lv.subm_nbr).data_ptr()
+            c.d_n_out, c.capacity_out, c.d_out = lv.n.data_ptr(), lv.cap, y.data_ptr()
+            out.append(c)
+            x = y
+        return out
 
     @property
     def map_stream(self) -> "torch.cuda.Stream":
@@ -231,7 +304,10 @@ class BranchRunner:
 
     def run(self, points: torch.Tensor, batch: Optional[torch.Tensor], timer=None) -> torch.Tensor:
         """One pass of the branch.  `timer`, if given, is called as timer(tag) and must return a context
-        manager; it brackets each library call (used by the bench to time kernels with stream events)."""
+        manager; it brackets each library call (used by the bench to time kernels with stream events), and the pass is
+        then issued call by call."""
+        if timer is None and self.native is not None:
+            return self.native.run(points, batch)[0]
         ctx, br = self.ctx, self.branch
         tm = timer if timer is not None else _no_timer
         l0 = self.levels[0]
@@ -272,6 +348,9 @@ class BranchRunner:
         """First stage of a pass, on the current stream: voxelization and every kernel map of the branch (all the
         work that uses the context's scratch).  run_convs() is the second stage; together they do what run() does,
         with every map built before the first convolution."""
+        if timer is None and self.native is not None:
+            self.native.maps(points, batch)
+            return
         ctx, br = self.ctx, self.branch
         tm = timer if timer is not None else _no_timer
         l0 = self.levels[0]
@@ -298,6 +377,8 @@ class BranchRunner:
         """Second stage of a pass, on the current stream: every convolution of the branch over the voxels and kernel
         maps run_maps() left in this runner's buffers.  Uses no context scratch when the weights are packed, so it
         may overlap the first stage of another runner."""
+        if timer is None and self.native is not None:
+            return self.native.convs()[0]
         ctx, br = self.ctx, self.branch
         tm = timer if timer is not None else _no_timer
         x = self.feats32 if self.dtype == F32 else self.feats_lp
@@ -359,6 +440,8 @@ class ConfigRunner:
             seed = gen.frame_seed(cfg.index, 0) + len(br.name)
             self.branches.append((ctx, BranchRunner(ctx, br, cfg.dtype, n_points, device_params(br.layers, seed, cfg.dtype),
                                                     capacities=caps, device=device)))
+        runners = [r for _, r in self.branches]
+        self.native = NativePass(runners) if NativePass.covers(runners) else None
         self._side: List["torch.cuda.Stream"] = []
         self._device = device
         self.camera = None
@@ -398,7 +481,12 @@ class ConfigRunner:
                 self.branches[0][0].project_gather(points, c["P"], c["img"], c["out"], c["valid"])
 
     def run(self, points: torch.Tensor, batch: Optional[torch.Tensor], timer=None) -> List[torch.Tensor]:
-        """Everything on the current stream, one call after the other."""
+        """Everything on the current stream: the maps of all branches together, then the convolutions (with a `timer`,
+        call by call, branch by branch)."""
+        if timer is None and self.native is not None:
+            outs = self.native.run(points, batch)
+            self._gather(points, _no_timer)
+            return outs
         tm = timer if timer is not None else _no_timer
         outs = []
         for bi, (_, r) in enumerate(self.branches):
@@ -466,8 +554,11 @@ class ConfigRunner:
             return g, out
 
         def maps():
-            for _, r in self.branches:
-                r.run_maps(points, batch)
+            if self.native is not None:
+                self.native.maps(points, batch)
+            else:
+                for _, r in self.branches:
+                    r.run_maps(points, batch)
             self._gather(points, _no_timer)
 
         self.stage_maps, _ = grab(maps)
@@ -540,8 +631,8 @@ class ConfigRunner:
 class RoutedRunner:
     """Scene-level routing (paper Sec. 3.2): the dispatcher picks an expert per scene from the scene's proposal
     regions, the scenes are grouped by expert, and each expert's stack runs on its own group only.  Sequencing
-    only: emc2_dispatch -> per expert emc2_group_points -> that expert's BranchRunner with the group's batch ids
-    (points of other experts' scenes carry -1 and are dropped by the voxelizer).  Group sizes stay on the device:
+    only: emc2_dispatch -> emc2_group_slots -> the three stacks side by side in one emc2_build_stacks call, each dropping the
+    points of other experts' scenes.  Group sizes stay on the device:
     every expert's buffers are sized for all n_scenes, and nothing here waits for the host."""
 
     def __init__(self, experts: Sequence[Branch], dtype: int, n_points: int, n_scenes: int, seed: int, device: str = "cuda"):
@@ -552,14 +643,15 @@ class RoutedRunner:
         self.order = torch.zeros((n_scenes,), **i32)
         self.slot = torch.zeros((n_scenes,), **i32)
         self.runners: List[Tuple[B.Context, BranchRunner]] = []
-        self.group_batch: List[torch.Tensor] = []
         for e, br in enumerate(experts):
             assert br.spec.n_batch == n_scenes
             caps = default_capacities(br, n_points)
             ctx = B.Context(n_points, max(caps), cells_of(br.spec.grid, n_scenes), n_slots=len(caps))
             self.runners.append((ctx, BranchRunner(ctx, br, dtype, n_points, device_params(br.layers, seed + e, dtype),
                                                    capacities=caps, device=device)))
-            self.group_batch.append(torch.empty((n_points,), **i32))
+        runners = [r for _, r in self.runners]
+        assert NativePass.covers(runners)
+        self.native = NativePass(runners, route=(self.expert, self.slot))
 
     def close(self) -> None:
         for ctx, _ in self.runners:
@@ -590,9 +682,5 @@ class RoutedRunner:
             dist: float, conf: float) -> List[torch.Tensor]:
         ctx0 = self.runners[0][0]
         ctx0.dispatch(props, prop_scene, self.n_scenes, dist, conf, self.expert, self.counts, self.order)
-        outs = []
-        for e, (ctx, r) in enumerate(self.runners):
-            ctx.group_points(scene, self.n_points, self.expert, self.order, self.counts, self.n_scenes, e, self.slot,
-                             self.group_batch[e])
-            outs.append(r.run(points, self.group_batch[e]))
-        return outs
+        ctx0.group_slots(self.expert, self.order, self.counts, self.n_scenes, self.slot)
+        return self.native.run(points, scene)

@@ -1,0 +1,139 @@
+"""GPU tests of emc2_build_stacks (all levels of several stacks in one call) against emc2_voxelize + emc2_build_kmap, which
+are held to the oracle elsewhere: coordinates, counts, means, kernel maps and index slots, bit for bit (voxels of at most
+four points, so the means are exact too)."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2507_04123_amd import binding as B
+from paper_2507_04123_amd.configs import VoxelSpec, out_grid
+from paper_2507_04123_amd.pipeline import cells_of
+
+pytestmark = pytest.mark.gpu
+
+
+def _points(seed, grid, nb, n):
+    """At most one point per cell and frame on average half of the cells' rows, a few outside the grid and with bad frame ids."""
+    rng = np.random.RandomState(seed)
+    cells = grid[0] * grid[1] * grid[2]
+    pick = rng.choice(cells * nb, min(n, cells * nb), replace=False)
+    b, k = pick // cells, pick % cells
+    xyz = np.stack([k % grid[0], k // grid[0] % grid[1], k // (grid[0] * grid[1])], 1) + rng.uniform(0.1, 0.9, (len(pick), 3))
+    pts = np.concatenate([xyz, rng.uniform(0, 1, (len(pick), 1))], 1).astype(np.float32)
+    pts[::17, 0] -= 2 * grid[0]                   # outside
+    b = b.astype(np.int32)
+    b[::23] = -1                                  # dropped
+    return torch.from_numpy(pts).cuda(), torch.from_numpy(b).cuda()
+
+
+class _Bufs:
+    def __init__(self, grid, nb, n_levels, n_points):
+        self.grids, self.cap = [grid], []
+        for _ in range(n_levels - 1):
+            self.grids.append(out_grid(self.grids[-1]))
+        i32 = dict(dtype=torch.int32, device="cuda")
+        prev = n_points
+        self.coords, self.n, self.subm, self.down = [], [], [], []
+        for l, g in enumerate(self.grids):
+            cap = min(prev if l == 0 else 8 * prev, cells_of(g, nb))
+            prev = cap
+            self.cap.append(cap)
+            self.coords.append(torch.full((cap, 4), -9, **i32))
+            self.n.append(torch.full((1,), -9, **i32))
+            self.subm.append(torch.full((27, cap), -9, **i32))
+            self.down.append(torch.full((27, cap), -9, **i32) if l else None)
+        c0 = self.cap[0]
+        self.feats, self.counts = torch.zeros((c0, 4), device="cuda"), torch.zeros((c0,), **i32)
+        self.lp = torch.zeros((c0, 4), dtype=torch.float16, device="cuda")
+        self.ctx = B.Context(max(n_points, 1), max(self.cap), cells_of(grid, nb), n_slots=n_levels)
+
+    def stack(self, spec, batch):
+        s = B.StackC()
+        s.ctx, s.spec, s.expert, s.n_levels, s.lp_dtype = self.ctx.h, B.voxel_spec_c(spec, 4), -1, len(self.grids), B.F16
+        s.d_batch = batch.data_ptr()
+        s.d_feats, s.d_counts, s.d_feats_lp = self.feats.data_ptr(), self.counts.data_ptr(), self.lp.data_ptr()
+        for l in range(len(self.grids)):
+            c = s.level[l]
+            c.capacity, c.slot, c.d_coords, c.d_n = self.cap[l], l, self.coords[l].data_ptr(), self.n[l].data_ptr()
+            c.d_subm_nbr, c.d_down_nbr = self.subm[l].data_ptr(), (self.down[l].data_ptr() if l else None)
+        return s
+
+    def call_by_call(self, pts, batch, spec):
+        ctx, nb = self.ctx, spec.n_batch
+        ctx.voxelize(pts, batch, spec, self.cap[0], self.coords[0], self.feats, self.counts, self.n[0], feats_lp=self.lp, index_slot=0)
+        for l in range(len(self.grids)):
+            if l:
+                ctx.build_kmap(B.STRIDED, self.coords[l - 1], self.n[l - 1], self.cap[l - 1], self.grids[l - 1], nb, self.cap[l],
+                               self.down[l], self.n[l], out_coords=self.coords[l], in_slot=l - 1, out_slot=l)
+            ctx.build_kmap(B.SUBM, self.coords[l], self.n[l], self.cap[l], self.grids[l], nb, self.cap[l], self.subm[l], self.n[l], in_slot=l)
+
+
+def _same(a, b, what):
+    for l in range(len(a.grids)):
+        n = int(b.n[l].item())
+        assert int(a.n[l].item()) == n, f"{what} level {l}: count"
+        assert torch.equal(a.coords[l][:n], b.coords[l][:n]), f"{what} level {l}: coordinates"
+        assert torch.equal(a.subm[l][:, :n], b.subm[l][:, :n]), f"{what} level {l}: submanifold map"
+        if l:
+            assert torch.equal(a.down[l][:, :n], b.down[l][:, :n]), f"{what} level {l}: stride-2 map"
+    n0 = int(b.n[0].item())
+    for t, u, nm in ((a.feats, b.feats, "means"), (a.counts, b.counts, "counts"), (a.lp, b.lp, "fp16 means")):
+        assert torch.equal(t[:n0], u[:n0]), f"{what}: {nm}"
+
+
+# grids whose rows are shorter than a word, straddle words, fill lines exactly, and leave a lone output column; one level to
+# five; batches; more than one granule (16 384 coarse cells) and tile (65 536 cells)
+@pytest.mark.parametrize("grid,nb,levels,n", [((7, 5, 3), 1, 3, 40), ((3, 9, 6), 3, 2, 200), ((1, 1, 1), 2, 1, 2), ((33, 17, 9), 2, 4, 900),
+                                              ((64, 16, 4), 1, 2, 500), ((65, 40, 11), 2, 5, 3000), ((176, 200, 5), 1, 4, 6000),
+                                              ((513, 300, 3), 2, 3, 20000), ((1, 700, 90), 1, 3, 5000)])
+def test_stack_equals_the_calls_it_replaces(grid, nb, levels, n):
+    spec = VoxelSpec((0.0, 0.0, 0.0), (1.0, 1.0, 1.0), grid, nb)
+    a, b = _Bufs(grid, nb, levels, n), _Bufs(grid, nb, levels, n)
+    for k in range(3):                            # later passes meet an index that holds the bits of the one before
+        pts, batch = _points(10 * n + k, grid, nb, n if k != 1 else max(1, n // 9))
+        b.call_by_call(pts, batch, spec)
+        B.build_stacks((B.StackC * 1)(a.stack(spec, batch)), 1, pts)
+        torch.cuda.synchronize()
+        a.ctx.status_sync(); b.ctx.status_sync()
+        _same(a, b, f"{grid} x{nb} pass {k}")
+    # the slots hold the levels' indexes: a map built from them alone
+    l = levels - 1
+    again = torch.full_like(a.subm[l], -9)
+    a.ctx.build_kmap(B.SUBM, a.coords[l], a.n[l], a.cap[l], a.grids[l], nb, a.cap[l], again, a.n[l], in_slot=l)
+    m = int(a.n[l].item())
+    assert torch.equal(again[:, :m], b.subm[l][:, :m])
+    a.ctx.close(); b.ctx.close()
+
+
+def test_several_stacks_in_one_call_and_their_errors():
+    specs = [(VoxelSpec((0.0, 0.0, 0.0), (1.0, 1.0, 1.0), (60, 50, 10), 2), 3), (VoxelSpec((0.0, 0.0, 0.0), (2.0, 2.0, 2.0), (30, 25, 5), 2), 1),
+             (VoxelSpec((0.0, 0.0, 0.0), (4.0, 4.0, 4.0), (15, 13, 3), 2, 0.0, 900.0), 4)]
+    pts, batch = _points(3, (60, 50, 10), 2, 4000)
+    many = [_Bufs(s.grid, 2, lv, 4000) for s, lv in specs]
+    ref = [_Bufs(s.grid, 2, lv, 4000) for s, lv in specs]
+    arr = (B.StackC * 3)(*[m.stack(s, batch) for m, (s, _) in zip(many, specs)])
+    for k in range(2):
+        B.build_stacks(arr, 3, pts)
+    for m, r, (s, _) in zip(many, ref, specs):
+        r.call_by_call(pts, batch, s)
+        torch.cuda.synchronize()
+        for l in range(len(m.grids)):
+            nl = int(r.n[l].item())
+            assert int(m.n[l].item()) == nl and torch.equal(m.coords[l][:nl], r.coords[l][:nl])
+            assert torch.equal(m.subm[l][:, :nl], r.subm[l][:, :nl])
+    arr[1].ctx = arr[0].ctx
+    with pytest.raises(B.Emc2Error, match="one context"):
+        B.build_stacks(arr, 3, pts)
+    arr[1].ctx = many[1].ctx.h
+    arr[0].level[1].slot = 0
+    with pytest.raises(B.Emc2Error, match="share slot"):
+        B.build_stacks(arr, 3, pts)
+    arr[0].level[1].slot, arr[0].level[1].capacity = 1, 5       # more outputs than capacity: reported, in bounds
+    B.build_stacks(arr, 1, pts)
+    torch.cuda.synchronize()
+    assert int(many[0].n[1].item()) == 5
+    with pytest.raises(B.Emc2Error) as ei:
+        many[0].ctx.status_sync()
+    assert ei.value.status == B.ERR_CAPACITY
+    for m in many + ref:
+        m.ctx.close()
