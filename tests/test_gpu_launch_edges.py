@@ -1,0 +1,123 @@
+"""GPU tests at the sizes where a launch changes shape: rounds of the span convolution, the grid limit of the register-direct
+one, vector tails of the quantisers, waves and shared cells of the voxelizer, the three-launch index scan."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2507_04123_amd import binding as B
+from paper_2507_04123_amd.configs import EPI_NONE, F16, VoxelSpec
+from paper_2507_04123_amd.pipeline import cells_of
+
+pytestmark = pytest.mark.gpu
+
+
+def _map(n, seed, shuffled):
+    """27 taps over n rows: row o reads rows near o (ascending along the row where valid, as kernel maps are), a third of the
+    entries absent; `shuffled` permutes a tap, which no interval of rows covers."""
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    o = torch.arange(n, device="cuda")
+    nbr = torch.stack([o + (k % 3 - 1) + 37 * (k // 3 - 4) for k in range(27)])
+    drop = torch.rand((27, n), generator=g, device="cuda") < 1 / 3
+    nbr = torch.where((nbr < 0) | (nbr >= n) | drop, torch.full_like(nbr, -1), nbr)
+    if shuffled:
+        nbr[4] = nbr[4][torch.randperm(n, generator=g, device="cuda")]
+    return nbr.to(torch.int32).contiguous()
+
+
+def _check_conv(n, cin, cout, hint, shuffled, seed=11):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    x = torch.randn((n, cin), generator=g, device="cuda").half()
+    w = (torch.randn((27, cin, cout), generator=g, device="cuda") * 0.1).half()
+    nbr = _map(n, seed, shuffled)
+    ctx = B.Context(16, 16, 64, n_slots=1)
+    wp = torch.empty_like(w)
+    ctx.pack_weights(F16, w, wp)
+    y = torch.full((n + 3, cout), 77.0, dtype=torch.float16, device="cuda")
+    ctx.spconv(F16, x, wp, None, None, EPI_NONE, nbr, torch.tensor([n], dtype=torch.int32, device="cuda"), n, y[:n],
+               w_layout=B.W_PACKED, map_hint=hint)
+    ctx.status_sync()
+    exp = torch.zeros((n, cout), device="cuda")
+    for k in range(27):
+        rows = (nbr[k] >= 0).nonzero().squeeze(1)
+        exp[rows] += x[nbr[k][rows].long()].float() @ w[k].float()
+    # the result is rounded once to fp16 (2^-11 relative); sums of up to 27 * cin fp32 products in another order stay below that
+    rms = float(exp.square().mean().sqrt())
+    err = (y[:n].float() - exp).abs() - 2.0 ** -10 * (exp.abs() + rms)
+    assert float(err.max()) <= 0.0
+    assert bool((y[n:] == 77.0).all())
+    ctx.close()
+
+
+# a round is 131 072 rows; the rest runs in waves of 16, 32, 48 or 64 rows
+@pytest.mark.parametrize("n", [1, 17, 129, 32768, 32769, 65537, 98305, 131071, 131072, 131073, 131072 + 40001, 262144 + 70001])
+def test_span_conv_rounds(n):
+    _check_conv(n, 64, 64, B.SUBM, False)
+
+
+@pytest.mark.parametrize("n", [513, 40001, 70001, 131072 + 5000])
+def test_span_conv_rounds_taps_outside_an_interval(n):
+    _check_conv(n, 64, 64, B.SUBM, True)
+
+
+# 8 192 blocks of 128 rows (256 at 32 -> 32): one tile less, exactly as many, one more, a second tile for most
+@pytest.mark.parametrize("cin,cout,n", [(64, 32, 8192 * 128 - 1), (32, 64, 8192 * 128 + 1), (32, 64, 8192 * 128 * 3 // 2 + 77),
+                                        (32, 32, 8192 * 256 + 300)])
+def test_direct_conv_grid_limit(cin, cout, n):
+    _check_conv(n, cin, cout, B.MAP_ANY, False)
+
+
+@pytest.mark.parametrize("dt", [np.float32, np.float16])
+@pytest.mark.parametrize("n,off", [(1, 0), (7, 0), (8, 0), (9, 0), (2048, 0), (2055, 0), (5000, 1), (5000, 4)])
+def test_quantisers_tails_and_alignment(n, off, dt):
+    x = np.random.RandomState(n).normal(0, 40, n).astype(dt)
+    ctx = B.Context(16, 16, 64, n_slots=1)
+    buf = torch.zeros(n + off, dtype=torch.float32 if dt == np.float32 else torch.float16, device="cuda")
+    buf[off:] = torch.from_numpy(x).cuda()
+    for call, ref, td in ((ctx.quantize_i8, oracle.quantize_i8, torch.int8), (ctx.quantize_e4m3, oracle.quantize_e4m3, torch.uint8)):
+        q = torch.full((off + n + 9,), 99, dtype=td, device="cuda")
+        call(buf[off:], 1.5, q[off:off + n])
+        assert np.array_equal(q[off:off + n].cpu().numpy(), ref(x.astype(np.float32), 1.5))
+        assert q[off + n:].tolist() == [99] * 9 and q[:off].tolist() == [99] * off
+    ctx.close()
+
+
+# cells shared by 1 .. 70 points, waves that end in the middle
+@pytest.mark.parametrize("n,side", [(1, 4), (63, 1), (64, 4), (65, 4), (300, 1), (1000, 8), (1000, 64)])
+def test_voxelize_first_points(n, side):
+    rng = np.random.RandomState(n + side)
+    pts = np.concatenate([rng.uniform(0, side, (n, 3)), rng.uniform(0, 1, (n, 1))], 1).astype(np.float32)
+    pts[::13, 0] = -1.0
+    grid = (side, side, side)
+    spec = VoxelSpec((0.0, 0.0, 0.0), (1.0, 1.0, 1.0), grid)
+    ctx = B.Context(n, n, cells_of(grid, 1), n_slots=1)
+    i32 = dict(dtype=torch.int32, device="cuda")
+    coords, feats, counts, nv = torch.zeros((n, 4), **i32), torch.full((n, 4), 5.0, device="cuda"), torch.full((n,), 5, **i32), torch.zeros(1, **i32)
+    for _ in range(2):                                   # the second pass starts from the first one's buffers
+        ctx.voxelize(torch.from_numpy(pts).cuda(), None, spec, n, coords, feats, counts, nv, index_slot=0)
+    ctx.status_sync()
+    oc, om, on = oracle.voxelize(pts, None, spec.lo, spec.vs, grid)
+    v = len(oc)
+    assert int(nv.item()) == v
+    assert np.array_equal(coords[:v].cpu().numpy(), oc) and np.array_equal(counts[:v].cpu().numpy(), on)
+    # sums of up to n fp32 values in another order: n * 2^-24 relative to the sum of magnitudes, at most side * count
+    assert np.all(np.abs(feats[:v].cpu().numpy() - om) <= (n + 2) * 2.0 ** -24 * max(side, 1))
+    assert not feats[v:].any() and not counts[v:].any()
+    ctx.close()
+
+
+def test_index_scan_of_more_than_16384_tiles():
+    grid, nb, n = (1408, 1600, 40), 13, 20000            # 17 875 tiles of 65 536 cells
+    rng = np.random.RandomState(5)
+    pts = np.concatenate([rng.uniform(0, 1, (n, 3)) * np.array(grid), rng.uniform(0, 1, (n, 1))], 1).astype(np.float32)
+    batch = rng.randint(0, nb, n).astype(np.int32)
+    spec = VoxelSpec((0.0, 0.0, 0.0), (1.0, 1.0, 1.0), grid, n_batch=nb)
+    ctx = B.Context(n, n, cells_of(grid, nb), n_slots=1)
+    i32 = dict(dtype=torch.int32, device="cuda")
+    coords, feats, counts, nv = torch.zeros((n, 4), **i32), torch.zeros((n, 4), device="cuda"), torch.zeros((n,), **i32), torch.zeros(1, **i32)
+    ctx.voxelize(torch.from_numpy(pts).cuda(), torch.from_numpy(batch).cuda(), spec, n, coords, feats, counts, nv, index_slot=0)
+    ctx.status_sync()
+    oc, _, on = oracle.voxelize(pts, batch, spec.lo, spec.vs, grid, n_batch=nb)
+    v = len(oc)
+    assert int(nv.item()) == v and np.array_equal(coords[:v].cpu().numpy(), oc) and np.array_equal(counts[:v].cpu().numpy(), on)
+    ctx.close()
