@@ -69,30 +69,28 @@ __global__ void __launch_bounds__(256) k_scan_reduce(const cellword_t* __restric
   if (threadIdx.x == 0) partials[blockIdx.x] = wsum[0] + wsum[1] + wsum[2] + wsum[3];
 }
 
-// Single block: exclusive scan of the block totals in place, total to *d_total (clamped).
-__global__ void __launch_bounds__(1024) k_scan_partials(uint32_t* __restrict__ partials, int64_t n, int64_t capacity,
-                                                        int32_t* __restrict__ d_total, int32_t* __restrict__ d_flags) {
-  __shared__ uint32_t wsum[16];
-  __shared__ uint32_t carry_s;
-  if (threadIdx.x == 0) carry_s = 0;
+// Exclusive scan of the block totals, 1024 of them per block, out of place: a block first sums everything before its
+// piece (coalesced, from L2; 88 000 totals are 0.35 MB), so pieces need not wait for each other.  One block walking over
+// all of them took 91 us at 88 000 totals.  The last block reports the total (clamped).
+__global__ void __launch_bounds__(1024) k_scan_partials(const uint32_t* __restrict__ totals, int64_t n, int64_t capacity,
+                                                        uint32_t* __restrict__ bases, int32_t* __restrict__ d_total,
+                                                        int32_t* __restrict__ d_flags) {
+  __shared__ uint32_t wsum[16], wbefore[16];
+  const int64_t start = (int64_t)blockIdx.x * 1024;
+  uint32_t before = 0;
+#pragma unroll 8
+  for (int64_t i = threadIdx.x; i < start; i += 1024) before += totals[i];
+  const int64_t i = start + threadIdx.x;
+  const uint32_t v = i < n ? totals[i] : 0u;
+  const uint32_t inc = wave_inclusive_scan(v), binc = wave_inclusive_scan(before);
+  const int w = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 63) { wsum[w] = inc; wbefore[w] = binc; }
   __syncthreads();
-  for (int64_t start = 0; start < n; start += 1024) {
-    const int64_t i = start + threadIdx.x;
-    const uint32_t v = i < n ? partials[i] : 0u;
-    const uint32_t inc = wave_inclusive_scan(v);
-    if ((threadIdx.x & 63) == 63) wsum[threadIdx.x >> 6] = inc;
-    __syncthreads();
-    uint32_t wbase = 0;
-    const int w = threadIdx.x >> 6;
-    for (int j = 0; j < w; ++j) wbase += wsum[j];
-    const uint32_t carry = carry_s;
-    if (i < n) partials[i] = carry + wbase + inc - v;
-    __syncthreads();
-    if (threadIdx.x == 1023) carry_s = carry + wbase + inc;
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    const uint32_t total = carry_s;
+  uint32_t run = inc - v;
+  for (int j = 0; j < 16; ++j) run += wbefore[j] + (j < w ? wsum[j] : 0u);
+  if (i < n) bases[i] = run;
+  if (i == n - 1) {
+    const uint32_t total = run + v;
     if ((int64_t)total > capacity) {
       atomicOr(d_flags, EMC2_DEVFLAG_CAPACITY);
       *d_total = (int32_t)capacity;
@@ -238,13 +236,14 @@ void emc2_index_scan(emc2_ctx* ctx, cellword_t* idx, int64_t n_cells, int64_t ca
   }
   hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)n_blocks), dim3(256), 0, stream, idx, n_words, ctx->partials,
                      emc2_slot_flags(ctx, idx));
-  if (n_blocks <= 16384) {   // each apply block re-sums the earlier totals itself: at most 64 KB from L2
+  if (n_blocks <= EMC2_SCAN_SELF_TILES) {   // each apply block re-sums the earlier totals itself: at most 64 KB from L2
     hipLaunchKernelGGL(k_scan_apply_self, dim3((unsigned)n_blocks), dim3(256), 0, stream, idx, n_words, ctx->partials,
                        capacity, d_total, ctx->dev_words, emc2_slot_flags(ctx, idx));
     return;
   }
-  hipLaunchKernelGGL(k_scan_partials, dim3(1), dim3(1024), 0, stream, ctx->partials, n_blocks, capacity, d_total,
-                     ctx->dev_words);
-  hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)n_blocks), dim3(256), 0, stream, idx, n_words, ctx->partials,
+  uint32_t* bases = ctx->partials + ctx->n_partials;
+  hipLaunchKernelGGL(k_scan_partials, dim3((unsigned)emc2_div_up(n_blocks, 1024)), dim3(1024), 0, stream, ctx->partials, n_blocks,
+                     capacity, bases, d_total, ctx->dev_words);
+  hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)n_blocks), dim3(256), 0, stream, idx, n_words, bases,
                      emc2_slot_flags(ctx, idx));
 }

@@ -74,8 +74,9 @@ struct emc2_ctx {
   int64_t slot_tiles;
   cellword_t** slots;       // host array [n_slots + 2] of device pointers
   SlotMeta* meta;           // host array [n_slots + 2]
-  float4* stash;            // [max_voxels][EMC2_VOX_STASH] points of each voxel, in arrival order
-  uint32_t* partials;       // scan partial sums
+  float4* stash;            // [EMC2_VOX_STASH][max_voxels] points of each voxel: row 0 its first, then in arrival order
+  unsigned long long* first;  // [max_points / 64 + 1] one bit per point: the first of its voxel
+  uint32_t* partials;       // scan partial sums [n_partials], then the bases made of them [n_partials]
   int64_t n_partials;
   uint32_t* stack_sums;     // popcount sums of every level of a stack (stack.hip)
   int64_t n_stack_sums;
@@ -95,6 +96,7 @@ struct emc2_ctx {
 
 #define EMC2_SCAN_TILE 2048  // cellwords per scan block (256 threads x 8)
 #define EMC2_TILE_SHIFT 11   // log2(EMC2_SCAN_TILE)
+#define EMC2_SCAN_SELF_TILES 16384  // scans of up to so many tiles take two launches and no second half of `partials`
 #define EMC2_LINE_SHIFT 4    // log2 of the cellwords per flagged line: 16 words = 128 bytes = 512 cells
 #define EMC2_LINES_PER_TILE (EMC2_SCAN_TILE >> EMC2_LINE_SHIFT)
 

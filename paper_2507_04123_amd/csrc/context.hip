@@ -66,8 +66,9 @@ extern "C" emc2_status emc2_create(emc2_ctx** out, int device, int64_t max_point
     TRY(hipMemset(ctx->slots[s], 0, bytes), "hipMemset(index slot)");  // establishes the line-flag invariant
   }
   TRY(hipMalloc((void**)&ctx->stash, sizeof(float4) * EMC2_VOX_STASH * (size_t)max_voxels), "hipMalloc(voxel stash)");
+  TRY(hipMalloc((void**)&ctx->first, sizeof(unsigned long long) * ((size_t)max_points / 64 + 1)), "hipMalloc(first points)");
   ctx->n_partials = emc2_div_up(ctx->slot_words, EMC2_SCAN_TILE) + 1;
-  TRY(hipMalloc((void**)&ctx->partials, sizeof(uint32_t) * (size_t)ctx->n_partials), "hipMalloc(partials)");
+  TRY(hipMalloc((void**)&ctx->partials, sizeof(uint32_t) * 2 * (size_t)ctx->n_partials), "hipMalloc(partials)");
   {
     // level 0 in tiles, up to EMC2_STACK_MAX_LEVELS - 1 further ones in quarter tiles, and one sum of every 64 sums
     const int64_t further = n_slots - 1 < EMC2_STACK_MAX_LEVELS - 1 ? n_slots - 1 : EMC2_STACK_MAX_LEVELS - 1;
@@ -109,6 +110,7 @@ extern "C" void emc2_destroy(emc2_ctx* ctx) {
   }
   free(ctx->meta);
   if (ctx->stash) (void)hipFree(ctx->stash);
+  if (ctx->first) (void)hipFree(ctx->first);
   if (ctx->partials) (void)hipFree(ctx->partials);
   if (ctx->stack_sums) (void)hipFree(ctx->stack_sums);
   if (ctx->zero_row) (void)hipFree(ctx->zero_row);

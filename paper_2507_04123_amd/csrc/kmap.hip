@@ -249,6 +249,7 @@ namespace {
 
 constexpr int64_t kStaticMaxCells = EMC2_STATIC_KMAP_MAX_CELLS;
 constexpr int64_t kStaticTiles = (kStaticMaxCells / 32 + 1 + EMC2_SCAN_TILE - 1) / EMC2_SCAN_TILE;   // as emc2_create sizes a slot
+static_assert(kStaticTiles <= EMC2_SCAN_SELF_TILES, "the static scratch holds one half of the scan partials");
 constexpr int64_t kStaticWords = kStaticTiles * EMC2_SCAN_TILE;
 constexpr size_t kStaticSlotBytes = sizeof(cellword_t) * (size_t)kStaticWords + sizeof(lineflag_t) * (size_t)(kStaticWords >> EMC2_LINE_SHIFT);
 constexpr size_t kStaticSlotPitch = (kStaticSlotBytes + 255) / 256 * 256;

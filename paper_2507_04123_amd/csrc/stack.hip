@@ -62,6 +62,8 @@ struct DevStack {
   int32_t* counts;
   void* feats_lp;
   float4* stash;
+  int64_t stash_pitch;
+  unsigned long long* first;    // per point: the first of its voxel
   int32_t* dev_words;
   int64_t zero_rows;
   DevLevel lv[kLevels];
@@ -150,10 +152,7 @@ __device__ __forceinline__ void role_mark(const Args& a, const DevStack& st, uin
     st.feats[i] = make_float4(0.f, 0.f, 0.f, 0.f);
     st.counts[i] = 0;
   }
-  const PointCell pc = locate_in(a, st, i);
-  if (!pc.keep) return;
-  atomicOr(&st.lv[0].idx[pc.key >> 5].x, 1u << ((uint32_t)pc.key & 31u));
-  st.lv[0].flags[emc2_line_of_key(pc.key)] = 1;
+  emc2_mark_point(locate_in(a, st, i), i, a.n_points, st.lv[0].idx, st.lv[0].flags, st.first);
 }
 
 // Four tiles per block, a wave each (no block barrier); a lane owns two adjacent lines = 32 words.
@@ -230,17 +229,18 @@ __device__ __forceinline__ void role_prefix(const DevStack& st, const DevLevel& 
 }
 
 __device__ __forceinline__ void role_scatter(const Args& a, const DevStack& st, uint32_t blk) {
-  const PointCell pc = locate_in(a, st, (int64_t)blk * 256 + threadIdx.x);
+  const int64_t i = (int64_t)blk * 256 + threadIdx.x;
+  const PointCell pc = locate_in(a, st, i);
   if (!pc.keep) return;
   const DevLevel& lv = st.lv[0];
   const int32_t r = cell_lookup(lv.idx, pc.key);
   if (r < 0 || r >= lv.cap) return;      // beyond capacity: reported by the scan, dropped here
-  emc2_stash_point(r, pc, lv.coords, st.feats, st.counts, st.stash);
+  emc2_stash_point(i, r, pc, st.first, lv.coords, st.feats, st.counts, st.stash, st.stash_pitch);
 }
 
 __device__ __forceinline__ void role_mean(const DevStack& st, uint32_t blk) {
   const int64_t r = (int64_t)blk * 256 + threadIdx.x;
-  if (r < *st.lv[0].n) emc2_voxel_mean(r, st.stash, st.feats, st.counts, st.lp, st.feats_lp);
+  if (r < *st.lv[0].n) emc2_voxel_mean(r, st.stash, st.stash_pitch, st.feats, st.counts, st.lp, st.feats_lp);
 }
 
 // The 32 bits of word w of level `lv` from the bits of the finer level `in`.  An output at ox reads 2ox-1 .. 2ox+1 on every
@@ -496,6 +496,8 @@ emc2_status describe(const emc2_stack& s, int64_t n_points, DevStack* d) {
   d->counts = s.d_counts;
   d->feats_lp = s.d_feats_lp;
   d->stash = ctx->stash;
+  d->stash_pitch = ctx->max_voxels;
+  d->first = ctx->first;
   d->dev_words = ctx->dev_words;
   d->zero_rows = n_points < s.level[0].capacity ? n_points : s.level[0].capacity;
   int32_t g[3] = {s.spec.grid[0], s.spec.grid[1], s.spec.grid[2]};

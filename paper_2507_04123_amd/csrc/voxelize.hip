@@ -6,13 +6,15 @@
 //   launch zeroes the output rows pass 2 accumulates into.
 // Scan: prefix sum over the index -> the rank of every active cell = its position in key order, and the
 //   number of voxels.
-// Pass 2 (one thread per point): the same key again -> rank r (one 8-byte load) -> position within the
-//   voxel from one returning atomic add on counts[r] -> the point goes to slot `pos` of the voxel's stash
-//   (a plain 16-byte store); only points beyond the stash depth are added atomically into the output row.
+//   The OR returns the word's old bits, which tell the voxel's first point from later ones (one bit kept per point).
+// Pass 2 (one thread per point): the same key again -> rank r (one 8-byte load).  A first point goes to row 0 of the
+//   stash and needs no atomic; a later one gets its position from one returning atomic add on counts[r] and goes to that
+//   row of the stash (a plain 16-byte store); only points beyond the stash depth are added atomically into the output row.
 // Pass 3 (one thread per voxel): sum the stash in the order of the points' values, divide, write the means.
 // Device-scope atomics on this part execute at the memory side of the fabric (the L2s of the 8 XCDs are
-// not coherent with each other), about 17 G/s in aggregate: two per point instead of seven is what
-// this layout buys.
+// not coherent with each other), about 27 G/s in aggregate: one per point (two where points share a voxel) instead of
+// seven is what this layout buys.  The stash is kept row by row, so that pass 3 reads 16 contiguous bytes of a voxel with
+// one point instead of a quarter of its 64.
 #include <math.h>
 
 #include "voxel_point.h"
@@ -21,7 +23,8 @@ namespace {
 
 __global__ void __launch_bounds__(256) k_vox_mark(const float* __restrict__ points, const int32_t* __restrict__ batch,
                                                   int64_t n_points, VoxParams prm, cellword_t* __restrict__ idx,
-                                                  lineflag_t* __restrict__ flags, int64_t zero_rows,
+                                                  lineflag_t* __restrict__ flags,
+                                                  unsigned long long* __restrict__ first, int64_t zero_rows,
                                                   float4* __restrict__ feats, int32_t* __restrict__ counts) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   // the rows pass 2 accumulates into: there are at most min(n_points, capacity) voxels, one thread each
@@ -29,32 +32,30 @@ __global__ void __launch_bounds__(256) k_vox_mark(const float* __restrict__ poin
     feats[i] = make_float4(0.f, 0.f, 0.f, 0.f);
     counts[i] = 0;
   }
-  const PointCell pc = locate(points, batch, i, n_points, prm);
-  if (!pc.keep) return;
-  atomicOr(&idx[pc.key >> 5].x, 1u << ((uint32_t)pc.key & 31u));
-  flags[emc2_line_of_key(pc.key)] = 1;   // this line of the index now holds a bit
+  emc2_mark_point(locate(points, batch, i, n_points, prm), i, n_points, idx, flags, first);
 }
 
 __global__ void __launch_bounds__(256) k_vox_scatter(const float* __restrict__ points, const int32_t* __restrict__ batch,
                                                      int64_t n_points, VoxParams prm, const cellword_t* __restrict__ idx,
-                                                     int64_t capacity, int4* __restrict__ coords,
+                                                     const unsigned long long* __restrict__ first, int64_t capacity, int4* __restrict__ coords,
                                                      float4* __restrict__ feats, int32_t* __restrict__ counts,
-                                                     float4* __restrict__ stash) {
-  const PointCell pc = locate(points, batch, (int64_t)blockIdx.x * blockDim.x + threadIdx.x, n_points, prm);
+                                                     float4* __restrict__ stash, int64_t pitch) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const PointCell pc = locate(points, batch, i, n_points, prm);
   if (!pc.keep) return;
   const int32_t r = cell_lookup(idx, pc.key);
   if (r < 0 || r >= capacity) return;   // beyond capacity: reported by the scan, dropped here
-  emc2_stash_point(r, pc, coords, feats, counts, stash);
+  emc2_stash_point(i, r, pc, first, coords, feats, counts, stash, pitch);
 }
 
 template <int LP>  // 0 none, 1 fp16, 2 bf16
 __global__ void __launch_bounds__(256) k_vox_finalize(const int32_t* __restrict__ d_n, int64_t capacity,
-                                                      const float4* __restrict__ stash, float4* __restrict__ feats,
-                                                      const int32_t* __restrict__ counts, void* __restrict__ feats_lp) {
+                                                      const float4* __restrict__ stash, int64_t pitch,
+                                                      float4* __restrict__ feats, int32_t* __restrict__ counts, void* __restrict__ feats_lp) {
   int64_t n = *d_n;
   if (n > capacity) n = capacity;
   const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (r < n) emc2_voxel_mean(r, stash, feats, counts, LP, feats_lp);
+  if (r < n) emc2_voxel_mean(r, stash, pitch, feats, counts, LP, feats_lp);
 }
 
 }  // namespace
@@ -121,18 +122,18 @@ extern "C" emc2_status emc2_voxelize(emc2_ctx* ctx, const float* d_points, const
   // at most min(n_points, capacity) voxels exist
   const int64_t bound = n_points < capacity ? n_points : capacity;
   if (n_points > 0)
-    hipLaunchKernelGGL(k_vox_mark, pg, blk, 0, s, d_points, d_batch, n_points, prm, idx, emc2_slot_flags(ctx, idx), bound,
+    hipLaunchKernelGGL(k_vox_mark, pg, blk, 0, s, d_points, d_batch, n_points, prm, idx, emc2_slot_flags(ctx, idx), ctx->first, bound,
                        (float4*)d_feats, d_counts);
   emc2_index_scan(ctx, idx, n_cells, capacity, d_n_voxels, s);
   {
     if (bound > 0) {
       const dim3 vg((unsigned)emc2_div_up(bound, 256));
-      hipLaunchKernelGGL(k_vox_scatter, pg, blk, 0, s, d_points, d_batch, n_points, prm, idx, capacity, (int4*)d_coords,
-                         (float4*)d_feats, d_counts, ctx->stash);
+      hipLaunchKernelGGL(k_vox_scatter, pg, blk, 0, s, d_points, d_batch, n_points, prm, idx, ctx->first, capacity,
+                         (int4*)d_coords, (float4*)d_feats, d_counts, ctx->stash, ctx->max_voxels);
       const int lp = d_feats_lp ? (lp_dtype == EMC2_F16 ? 1 : 2) : 0;
 #define FIN(LP)                                                                                                 \
-  hipLaunchKernelGGL(k_vox_finalize<LP>, vg, blk, 0, s, d_n_voxels, capacity, ctx->stash, (float4*)d_feats, d_counts, \
-                     d_feats_lp)
+  hipLaunchKernelGGL(k_vox_finalize<LP>, vg, blk, 0, s, d_n_voxels, capacity, ctx->stash, ctx->max_voxels,      \
+                     (float4*)d_feats, d_counts, d_feats_lp)
       if (lp == 0) FIN(0); else if (lp == 1) FIN(1); else FIN(2);
 #undef FIN
     }
