@@ -268,21 +268,32 @@ __device__ __forceinline__ uint32_t gather_word(const DevLevel& in, const DevLev
     const int shl = xs - (2 * (int)ox - 1);           // 1 where the row's first bit would be x = -1, else 0
     uint64_t lo = 0;                                  // bits 0..63 of the OR of the rows, bit 0 <-> x = 2*ox - 1
     uint32_t hi = 0;                                  // bit 64
+    // All 27 loads of the nine rows are in flight together: a row outside the grid re-reads the centre row's word and is
+    // masked, a second or third word that the row does not reach re-reads the first.  With a branch per row the nine
+    // round trips followed each other (the phase that gathers a 64-beam frame's level 1: 24.0 -> 18.4 us).
+    uint32_t w0[9], w1[9], w2[9];
+    int sh[9];
+    bool in_row[9];
 #pragma unroll
     for (int d = 0; d < 9; ++d) {
       const int iz = 2 * oz + d / 3 - 1, iy = 2 * oy + d % 3 - 1;
-      if (iz < 0 || iz >= gz || iy < 0 || iy >= gy) continue;
-      const uint64_t k = ((b * gz + (uint64_t)iz) * gy + (uint64_t)iy) * gx + (uint64_t)xs;
+      in_row[d] = iz >= 0 && iz < gz && iy >= 0 && iy < gy;
+      const uint64_t k = ((b * gz + (uint64_t)(in_row[d] ? iz : 2 * oz)) * gy + (uint64_t)(in_row[d] ? iy : 2 * oy)) * gx + (uint64_t)xs;
       const cellword_t* p = in.idx + (k >> 5);
-      const int sh = (int)(k & 31u);
-      const uint32_t w0 = p[0].x;
-      const uint32_t w1 = sh + nb > 32 ? p[1].x : 0u;
-      const uint32_t w2 = sh + nb > 64 ? p[2].x : 0u;
-      const uint64_t w01 = ((uint64_t)w1 << 32) | w0;
-      uint64_t r = (w01 >> sh) | (sh ? (uint64_t)w2 << (64 - sh) : 0ull);
-      uint32_t e = (w2 >> sh) & 1u;                   // bit 64 of the row's string
+      sh[d] = (int)(k & 31u);
+      w0[d] = p[0].x;
+      w1[d] = p[sh[d] + nb > 32 ? 1 : 0].x;
+      w2[d] = p[sh[d] + nb > 64 ? 2 : 0].x;
+    }
+#pragma unroll
+    for (int d = 0; d < 9; ++d) {
+      const uint32_t v1 = sh[d] + nb > 32 ? w1[d] : 0u, v2 = sh[d] + nb > 64 ? w2[d] : 0u;
+      const uint64_t w01 = ((uint64_t)v1 << 32) | w0[d];
+      uint64_t r = (w01 >> sh[d]) | (sh[d] ? (uint64_t)v2 << (64 - sh[d]) : 0ull);
+      uint32_t e = (v2 >> sh[d]) & 1u;                // bit 64 of the row's string
       if (nb < 64) r &= (1ull << nb) - 1ull;
       if (nb < 65) e = 0u;
+      if (!in_row[d]) { r = 0ull; e = 0u; }
       hi |= shl ? (uint32_t)(r >> 63) : e;            // with shl there are at most 64 bits before the shift
       lo |= r << shl;
     }
@@ -314,7 +325,7 @@ __device__ __forceinline__ void role_gather(const DevStack& st, int l, uint32_t 
     if (k0 < k1) {
       const uint64_t r0 = div_key(k0, gox), r1 = div_key(k1 - 1, gox);
       const uint32_t nc = (uint32_t)(r1 - r0 + 1) * 9u;
-      for (uint32_t c = (uint32_t)sub; c < nc && !any; c += 8) {
+      for (uint32_t c = (uint32_t)sub; c < nc; c += 8) {
         const uint64_t row = r0 + c / 9u;
         const int d = (int)(c % 9u);
         const uint64_t t = div_key(row, goy);
@@ -328,8 +339,12 @@ __device__ __forceinline__ void role_gather(const DevStack& st, int l, uint32_t 
         const int xs = 2 * ox0 - 1 < 0 ? 0 : 2 * ox0 - 1;
         const int xe = 2 * ox1 + 1 < in.g[0] ? 2 * ox1 + 1 : in.g[0] - 1;
         const uint64_t rb = ((b * in.g[2] + (uint64_t)iz) * in.g[1] + (uint64_t)iy) * in.g[0];
-        for (uint64_t fl = emc2_line_of_key(rb + (uint64_t)xs); fl <= emc2_line_of_key(rb + (uint64_t)xe); ++fl)
-          any |= in.flags[fl] != 0;
+        // at most 512 output cells of a row, so at most 1 025 input cells: they touch up to four lines
+        const uint64_t f0 = emc2_line_of_key(rb + (uint64_t)xs), f1 = emc2_line_of_key(rb + (uint64_t)xe);
+        uint32_t f = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) f |= in.flags[f0 + q < f1 ? f0 + q : f1];
+        any |= f != 0u;
       }
     }
     if (any) atomicOr(&act_s, 1u << line);
@@ -601,8 +616,15 @@ extern "C" emc2_status emc2_build_stacks(const emc2_stack* stacks, int32_t n_sta
       case 3: p.launch<BITS(R_SUM) | BITS(R_GATHER)>(s); break;
       case 4: p.launch<BITS(R_PREFIX) | BITS(R_GATHER) | BITS(R_EXPAND)>(s); break;
       case 5: p.launch<BITS(R_SCATTER) | BITS(R_GATHER) | BITS(R_EXPAND)>(s); break;
-      case 6: p.launch<BITS(R_MEAN) | BITS(R_GATHER) | BITS(R_EXPAND) | BITS(R_PROBE)>(s); break;
-      default: p.launch<BITS(R_GATHER) | BITS(R_EXPAND) | BITS(R_PROBE)>(s); break;
+      // the last phase, at 6 or later, gathers and expands nothing any more: its kernel carries no other role's registers
+      case 6:
+        if (ph == last) p.launch<BITS(R_MEAN) | BITS(R_PROBE)>(s);
+        else p.launch<BITS(R_MEAN) | BITS(R_GATHER) | BITS(R_EXPAND)>(s);
+        break;
+      default:
+        if (ph == last) p.launch<BITS(R_PROBE)>(s);
+        else p.launch<BITS(R_GATHER) | BITS(R_EXPAND)>(s);
+        break;
     }
 #undef BITS
   }
