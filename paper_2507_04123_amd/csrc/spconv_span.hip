@@ -15,7 +15,7 @@
 // rows its tap names.  Results never depend on which mode a group took: the mode is chosen from the
 // table entries themselves, and every entry is range-checked against the tile before use.
 //
-// Block = 8 waves (one per 64 output rows) sharing the weights of a group (3 taps) in a double-buffered
+// Block = 8 waves (one per 64 output rows, or fewer in the last round) sharing the weights of a group (3 taps) in a double-buffered
 // LDS area: one block-wide barrier per group.  All global loads of a group are issued in one burst
 // right after the tile has been written, a whole group (thousands of cycles) before their first use.
 #include <hip/hip_bf16.h>
@@ -48,6 +48,7 @@ template <> struct MmaS<EMC2_BF16> {
 
 constexpr int kSpanWaves = 8;
 constexpr int kSpanThreads = kSpanWaves * 64;
+constexpr int kSpanCUs = 256;   // compute units of the part; one block of this kernel fits each
 
 template <int CIN> struct SpanCfg {
   // rows of the LDS tile (a multiple of the rows one load instruction covers); sized so that 8 tiles and
@@ -106,7 +107,7 @@ __device__ __forceinline__ GroupInfo analyze(const int32_t j[3]) {
 // meet at the same block-wide barrier once per group, but between two barriers they do their memory
 // phase and their matrix phase in opposite order, so the two waves that share a SIMD (wave w and w + 4)
 // do not both want the LDS / the load path / the matrix core at the same time.
-template <int DT, int CIN, int COUT, bool LATE>
+template <int DT, int CIN, int COUT, int MT, bool LATE>
 __device__ __forceinline__ void span_wave(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp,
                                           const float* __restrict__ scale, const float* __restrict__ shift, int epilogue,
                                           const int32_t* __restrict__ nbr, int64_t n_out, int64_t capacity_out,
@@ -115,7 +116,7 @@ __device__ __forceinline__ void span_wave(const uint16_t* __restrict__ in, const
                                           int64_t wave_row0) {
   constexpr int KS = CIN / 32;                // k-steps per tap (v_mfma_f32_16x16x32)
   constexpr int NT = COUT / 16;               // 16-column tiles
-  constexpr int MT = 4;                       // 16-row tiles per wave
+  constexpr int R = 16 * MT;                  // rows per wave (MT 16-row tiles)
   constexpr int W16 = KS * NT * 64;           // 16-byte weight pieces per tap
   constexpr int G16 = 3 * W16;                // ... per group of three taps
   constexpr int WPT = (G16 + kSpanThreads - 1) / kSpanThreads;
@@ -131,7 +132,7 @@ __device__ __forceinline__ void span_wave(const uint16_t* __restrict__ in, const
   const int m = lane & 15, q = lane >> 4;
   if (lane < ROW16) my_tile[ZROW * ROW16 + lane] = u32x4{0u, 0u, 0u, 0u};
 
-  const bool live = wave_row0 + lane < n_out;
+  const bool live = lane < R && wave_row0 + lane < n_out;
   const int32_t* nrow = nbr + (live ? wave_row0 + lane : 0);
   const int32_t dead = live ? 0 : -1;               // rows past n_out have no neighbours
   unsigned long long oob = 0ull;                    // lanes that saw an entry outside [0, n_in)
@@ -189,7 +190,7 @@ __device__ __forceinline__ void span_wave(const uint16_t* __restrict__ in, const
   // gather of exactly the rows one tap names: tile row p <- input row JROW[p] (absent entries re-read row 0)
 #define EMC2_GATHER_TAP(JROW)                                                                              \
   _Pragma("unroll") for (int i_ = 0; i_ < NI; ++i_) {                                                      \
-    if (i_ * RPI < 64) { /* compile time: a tap names 64 rows */                                           \
+    if (i_ * RPI < R) { /* compile time: a tap names R rows */                                             \
       const int p_ = i_ * RPI + srow;                                                                      \
       const int32_t j_ = __shfl((JROW), p_, 64);                                                           \
       sreg[i_] = *(reinterpret_cast<const u32x4*>(in + (int64_t)(j_ >= 0 ? j_ : 0) * CIN) + schunk);       \
@@ -201,8 +202,8 @@ __device__ __forceinline__ void span_wave(const uint16_t* __restrict__ in, const
 #define EMC2_TILE_WRITE_N(ROWS)                                                                            \
   _Pragma("unroll") for (int i_ = 0; i_ < NI; ++i_)                                                        \
     if ((uint32_t)(i_ * RPI) < (uint32_t)(ROWS)) my_tile[(i_ * RPI + srow) * ROW16 + schunk] = sreg[i_];
-  // ... what the main gather of group GI left in the registers: its interval, or the 64 rows of its first tap
-#define EMC2_TILE_WRITE(GI) EMC2_TILE_WRITE_N((GI).span ? (GI).rows : 64u)
+  // ... what the main gather of group GI left in the registers: its interval, or the R rows of its first tap
+#define EMC2_TILE_WRITE(GI) EMC2_TILE_WRITE_N((GI).span ? (GI).rows : (uint32_t)R)
   // Issue order inside a tap (KS = 2, MT = NT = 4: 16 operand reads, 32 matrix instructions): operands are read one
   // to two row tiles ahead of the matrix instructions that use them, so that after the first six reads of a tap a
   // read's latency falls under the four matrix instructions before its use.
@@ -226,8 +227,8 @@ __device__ __forceinline__ void span_wave(const uint16_t* __restrict__ in, const
     const u32x2 h_ = __builtin_amdgcn_permlane32_swap(lr_, lr_, false, false);        /* rows 0101 | 2323 */ \
     const u32x2 lo_ = __builtin_amdgcn_permlane16_swap(h_[0], h_[0], false, false);   /* 0000 | 1111 */    \
     const u32x2 hi_ = __builtin_amdgcn_permlane16_swap(h_[1], h_[1], false, false);   /* 2222 | 3333 */    \
-    const u32x4* ap_[MT] = {my_tile + lo_[0] * ROW16 + q, my_tile + lo_[1] * ROW16 + q,                    \
-                            my_tile + hi_[0] * ROW16 + q, my_tile + hi_[1] * ROW16 + q};                   \
+    const u32x4* ap_[4] = {my_tile + lo_[0] * ROW16 + q, my_tile + lo_[1] * ROW16 + q,                     \
+                           my_tile + hi_[0] * ROW16 + q, my_tile + hi_[1] * ROW16 + q};                    \
     _Pragma("unroll") for (int t = 0; t < KS; ++t) {                                                       \
       u32x4 b[NT], a[MT];                                                                                  \
       _Pragma("unroll") for (int j = 0; j < NT; ++j) b[j] = (WB)[(((KX) * KS + t) * NT + j) * 64 + lane];  \
@@ -248,11 +249,11 @@ __device__ __forceinline__ void span_wave(const uint16_t* __restrict__ in, const
     __builtin_amdgcn_s_setprio(2);                                                                         \
     { const int32_t lrow_ = EMC2_LROW(0, C, GI); EMC2_TAP(0, lrow_, WB) }                                  \
     __builtin_amdgcn_wave_barrier();                                                                       \
-    if (!(GI).span) { EMC2_TILE_WRITE_N(64) EMC2_GATHER_TAP((C)[2]) }                                          \
+    if (!(GI).span) { EMC2_TILE_WRITE_N(R) EMC2_GATHER_TAP((C)[2]) }                                          \
     __builtin_amdgcn_wave_barrier();                                                                       \
     { const int32_t lrow_ = EMC2_LROW(1, C, GI); EMC2_TAP(1, lrow_, WB) }                                  \
     __builtin_amdgcn_wave_barrier();                                                                       \
-    if (!(GI).span) { EMC2_TILE_WRITE_N(64) EMC2_GATHER_MAIN(NXT, CNXT) }                                      \
+    if (!(GI).span) { EMC2_TILE_WRITE_N(R) EMC2_GATHER_MAIN(NXT, CNXT) }                                      \
     __builtin_amdgcn_wave_barrier();                                                                       \
     { const int32_t lrow_ = EMC2_LROW(2, C, GI); EMC2_TAP(2, lrow_, WB) }                                  \
     __builtin_amdgcn_s_setprio(0);                                                                         \
@@ -410,29 +411,56 @@ k_spconv_span(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, con
 
   int64_t n_out = *d_n_out;
   if (n_out > capacity_out) n_out = capacity_out;
-  // XCD-aware tile assignment: workgroup b runs on XCD b % 8; XCD x takes a contiguous range of tiles
-  const int64_t n_tiles = (n_out + kSpanWaves * 64 - 1) / (kSpanWaves * 64);
-  const int64_t chunk = (n_tiles + 7) / 8;
-  const int64_t slot_in_xcd = blockIdx.x / 8;
-  const int64_t tile_id = (int64_t)(blockIdx.x % 8) * chunk + slot_in_xcd;
-  if (slot_in_xcd >= chunk || tile_id >= n_tiles) return;  // uniform for the block
+  // Rows are dealt in rounds of one block per CU (the tiles and weights in LDS leave room for one).  Whole rounds take
+  // 64 rows a wave; what is left, which used to cost a whole round however little it was, is split into the smallest
+  // waves (16, 32, 48 or 64 rows) with which it fits one round.  64-row waves throughout against this, alone on the GPU:
+  // 16 k rows 24.6 / 18.2 us, 69 k 35.5 / 31.0, 223 k 64.6 / 59.5, 573 k 139 / 137 (131 in a grid that fits).
+  constexpr uint32_t kRoundRows = kSpanCUs * kSpanWaves * 64;
+  const uint32_t n = n_out > 0 ? (uint32_t)n_out : 0u;
+  const uint32_t full = n / kRoundRows * kSpanCUs;                // blocks of the whole rounds
+  const uint32_t rem = n % kRoundRows;
+  // XCD-aware tile assignment: workgroup b runs on XCD b % 8; XCD x takes a contiguous range of the tiles of either part
+  const uint32_t x = blockIdx.x % 8, slot = blockIdx.x / 8;
+  // The grid is for the capacity; a block beyond both parts leaves at once (one at a time fits a CU: 22 k of them cost
+  // 25 us when each first worked out the split).
+  if (slot >= full / 8 + (rem ? kSpanCUs / 8 : 0)) return;
   const int wave = threadIdx.x >> 6;
-  const int64_t wave_row0 = tile_id * (kSpanWaves * 64) + (int64_t)wave * 64;
   // waves w and w + 4 share a SIMD: one of each kind per SIMD
-  if (wave < 4)
-    span_wave<DT, CIN, COUT, false>(in, wp, scale, shift, epilogue, nbr, n_out, capacity_out, n_in, dev_flags, out, wl,
-                                    tile[wave], wave_row0);
-  else
-    span_wave<DT, CIN, COUT, true>(in, wp, scale, shift, epilogue, nbr, n_out, capacity_out, n_in, dev_flags, out, wl,
-                                    tile[wave], wave_row0);
+#define EMC2_SPAN_WAVE(MTV)                                                                                               \
+  {                                                                                                                       \
+    const int64_t row0_ = first_row + (int64_t)wave * 16 * (MTV);                                                         \
+    if (wave < 4)                                                                                                         \
+      span_wave<DT, CIN, COUT, MTV, false>(in, wp, scale, shift, epilogue, nbr, n_out, capacity_out, n_in, dev_flags, out, \
+                                           wl, tile[wave], row0_);                                                        \
+    else                                                                                                                  \
+      span_wave<DT, CIN, COUT, MTV, true>(in, wp, scale, shift, epilogue, nbr, n_out, capacity_out, n_in, dev_flags, out,  \
+                                          wl, tile[wave], row0_);                                                         \
+    return;                                                                                                               \
+  }
+  if (slot < full / 8) {   // kSpanCUs is a multiple of 8
+    const int64_t first_row = (int64_t)(x * (full / 8) + slot) * (kSpanWaves * 64);
+    EMC2_SPAN_WAVE(4)
+  }
+  const uint32_t mt = (rem + kRoundRows / 4 - 1) / (kRoundRows / 4);       // 16-row tiles per wave of the rest
+  const uint32_t rows = kSpanWaves * 16 * mt;
+  const uint32_t n_tiles = (rem + rows - 1) / rows, chunk = (n_tiles + 7) / 8;
+  const uint32_t slot2 = slot - full / 8;
+  if (slot2 >= chunk || x * chunk + slot2 >= n_tiles) return;   // uniform for the block
+  const int64_t first_row = (int64_t)full * (kSpanWaves * 64) + (int64_t)(x * chunk + slot2) * rows;
+  if (mt == 1) EMC2_SPAN_WAVE(1)
+  if (mt == 2) EMC2_SPAN_WAVE(2)
+  if (mt == 3) EMC2_SPAN_WAVE(3)
+  EMC2_SPAN_WAVE(4)
+#undef EMC2_SPAN_WAVE
 }
 
 template <int DT, int CIN, int COUT>
 void launch_span(const void* d_in, const void* d_wp, const float* d_scale, const float* d_shift, int epilogue,
                  const int32_t* d_nbr, const int32_t* d_n_out, int64_t capacity_out, int32_t n_in, int32_t* dev_flags,
                  void* d_out, hipStream_t s) {
-  const int64_t rows_per_block = kSpanWaves * 64;
-  hipLaunchKernelGGL((k_spconv_span<DT, CIN, COUT>), dim3((unsigned)(emc2_div_up(capacity_out, rows_per_block) + 8)),
+  // whole rounds of 64-row waves and one round for the rest
+  const int64_t rounds = capacity_out / ((int64_t)kSpanCUs * kSpanWaves * 64) + 1;
+  hipLaunchKernelGGL((k_spconv_span<DT, CIN, COUT>), dim3((unsigned)(rounds * kSpanCUs)),
                      dim3(kSpanThreads), 0, s, (const uint16_t*)d_in, (const u32x4*)d_wp, d_scale, d_shift, epilogue, d_nbr,
                      d_n_out, capacity_out, n_in, dev_flags, (uint16_t*)d_out);
 }
