@@ -51,6 +51,7 @@ template <> struct MmaD<EMC2_BF16> {
 
 constexpr int kDWaves = 4;
 constexpr int kDThreads = kDWaves * 64;
+constexpr int64_t kDGrid = 8192;   // blocks of a launch whose blocks loop over tiles: ten rounds of the chip at 3 blocks a CU
 
 // Packed weight layout of this kernel: piece index ((k*KS + t)*NT + j)*64 + lane, lane = 16*q + n, holds the
 // 8 values W[k][32t + 8q + e][16j + n], e = 0..7 -- the B operand of k-step t, column tile j.
@@ -87,7 +88,7 @@ template <int CIN, int COUT> struct DirectCfg {
   static constexpr int MINW = (CIN >= 128 || COUT >= 128) ? 2 : 3;
 };
 
-template <int DT, int CIN, int COUT>
+template <int DT, int CIN, int COUT, bool LOOP>
 __global__ void __launch_bounds__(kDThreads, (DirectCfg<CIN, COUT>::MINW))
 k_spconv_direct(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, const float* __restrict__ scale,
                 const float* __restrict__ shift, int epilogue, const int32_t* __restrict__ nbr,
@@ -115,12 +116,21 @@ k_spconv_direct(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, c
   // XCD-aware tile assignment: workgroup b runs on XCD b % 8; XCD x takes a contiguous range of tiles
   const int64_t n_tiles = (n_out + kDWaves * R - 1) / (kDWaves * R);
   const int64_t chunk = (n_tiles + 7) / 8;
-  const int64_t slot_in_xcd = blockIdx.x / 8;
-  const int64_t tile_id = (int64_t)(blockIdx.x % 8) * chunk + slot_in_xcd;
-  if (slot_in_xcd >= chunk || tile_id >= n_tiles) return;  // uniform for the block
+  const int64_t xcd_tile0 = (int64_t)(blockIdx.x % 8) * chunk;
+  const int64_t xcd_tiles = n_tiles - xcd_tile0 < chunk ? n_tiles - xcd_tile0 : chunk;
 
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
+  int64_t slot = blockIdx.x / 8;
+  if (slot >= xcd_tiles) return;   // uniform for the block
+  do {
+  const int64_t tile_id = xcd_tile0 + slot;
+  // Opaque copies: the compiler would otherwise keep the addresses of all 27 taps alive from tile to tile and spill up to
+  // 90 registers for it.
+  int tid = threadIdx.x;
+  int64_t nbr_pitch = capacity_out;
+  if constexpr (LOOP) asm volatile("" : "+v"(tid), "+s"(nbr_pitch), "+s"(wp), "+s"(nbr));
+
+  const int lane = tid & 63;
+  const int wave = tid >> 6;
   const int m = lane & 15, q = lane >> 4;
   const int64_t wave_row0 = tile_id * (kDWaves * R) + (int64_t)wave * R;
 
@@ -142,7 +152,7 @@ k_spconv_direct(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, c
 
 #define EMC2_IDX_LOAD(GROUP, DST)                                                                        \
   _Pragma("unroll") for (int kx_ = 0; kx_ < 3; ++kx_)                                                    \
-      jq[DST][kx_] = nrow[(int64_t)(3 * ((GROUP) < 9 ? (GROUP) : 8) + kx_) * capacity_out];
+      jq[DST][kx_] = nrow[(int64_t)(3 * ((GROUP) < 9 ? (GROUP) : 8) + kx_) * nbr_pitch];
   // A operands of one tap: tile mt, k-step ks <- 16 bytes at channel 32*ks + 8*q of row JROW[16*mt + m]
   // The entries of rows 16*mt .. 16*mt+15 sit in lanes 16*mt .. 16*mt+15; every lane needs the one of its
   // column m for each mt.  Three lane-swap instructions broadcast each 16-lane row to all four rows (no LDS
@@ -167,11 +177,11 @@ k_spconv_direct(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, c
   {                                                                                                      \
     const u32x4* wsrc_ = wp + (int64_t)(TAP) * W16;                                                      \
     _Pragma("unroll") for (int i_ = 0; i_ < WPT; ++i_)                                                   \
-        wq[SET][i_] = wsrc_[(threadIdx.x + i_ * kDThreads) & WMASK];                                     \
+        wq[SET][i_] = wsrc_[(tid + i_ * kDThreads) & WMASK];                                     \
   }
 #define EMC2_W_STORE(BUF, SET)                                                                           \
   _Pragma("unroll") for (int i_ = 0; i_ < WPT; ++i_)                                                     \
-      wl[BUF][(threadIdx.x + i_ * kDThreads) & WMASK] = wq[SET][i_];
+      wl[BUF][(tid + i_ * kDThreads) & WMASK] = wq[SET][i_];
 
   // prologue: map entries of groups 0..2; weights of tap 0 to LDS; A operands of taps 0..2
   EMC2_IDX_LOAD(0, 0)
@@ -190,7 +200,7 @@ k_spconv_direct(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, c
     // kernel-map entries of group g + 3, requested a whole group before anything touches them
     int32_t jn[3];
 #pragma unroll
-    for (int kx = 0; kx < 3; ++kx) jn[kx] = nrow[(int64_t)(3 * (g + 3 < 9 ? g + 3 : 8) + kx) * capacity_out];
+    for (int kx = 0; kx < 3; ++kx) jn[kx] = nrow[(int64_t)(3 * (g + 3 < 9 ? g + 3 : 8) + kx) * nbr_pitch];
 #pragma unroll
     for (int kx = 0; kx < 3; ++kx) {
       const int tap = 3 * g + kx;
@@ -265,6 +275,9 @@ k_spconv_direct(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, c
     }
     __builtin_amdgcn_wave_barrier();
   }
+  slot += gridDim.x / 8;
+  if constexpr (LOOP) __syncthreads();   // the next tile refills the weight buffers
+  } while (LOOP && slot < xcd_tiles);
 }
 
 template <int DT, int CIN, int COUT>
@@ -272,9 +285,20 @@ void launch_direct(const void* d_in, const void* d_wp, const float* d_scale, con
                    const int32_t* d_nbr, const int32_t* d_n_out, int64_t capacity_out, int32_t n_in, int32_t* dev_flags,
                    const void* d_zero_row, void* d_out, hipStream_t s) {
   const int64_t rows_per_block = kDWaves * 16 * DirectCfg<CIN, COUT>::MT;
-  hipLaunchKernelGGL((k_spconv_direct<DT, CIN, COUT>), dim3((unsigned)(emc2_div_up(capacity_out, rows_per_block) + 8)),
-                     dim3(kDThreads), 0, s, (const uint16_t*)d_in, (const u32x4*)d_wp, d_scale, d_shift, epilogue, d_nbr,
-                     d_n_out, capacity_out, n_in, dev_flags, (const uint16_t*)d_zero_row, (uint16_t*)d_out);
+  // The host knows a level's capacity, up to 8 times the level below, not how many voxels it got.  Blocks without a tile
+  // cost about 0.25 us per thousand: 32 -> 64 over 573 k rows took 97 us in a grid for 11.3 M rows (88 k blocks) and 75 us
+  // in one for 573 k.  A loop over tiles costs the kernel up to a tenth in registers and instruction order (128 -> 128: 110
+  // against 127 us), so it is used only where the grid would be several times kDGrid; the grid is then kDGrid blocks
+  // (32 -> 64 over 573 k rows 97 -> 80 us, over 852 k 119 -> 109).
+  const int64_t blocks = emc2_div_up(emc2_div_up(capacity_out, rows_per_block), 8) * 8;
+  if (blocks <= 4 * kDGrid)
+    hipLaunchKernelGGL((k_spconv_direct<DT, CIN, COUT, false>), dim3((unsigned)blocks), dim3(kDThreads), 0, s,
+                       (const uint16_t*)d_in, (const u32x4*)d_wp, d_scale, d_shift, epilogue, d_nbr, d_n_out, capacity_out, n_in,
+                       dev_flags, (const uint16_t*)d_zero_row, (uint16_t*)d_out);
+  else
+    hipLaunchKernelGGL((k_spconv_direct<DT, CIN, COUT, true>), dim3((unsigned)kDGrid), dim3(kDThreads), 0, s,
+                       (const uint16_t*)d_in, (const u32x4*)d_wp, d_scale, d_shift, epilogue, d_nbr, d_n_out, capacity_out, n_in,
+                       dev_flags, (const uint16_t*)d_zero_row, (uint16_t*)d_out);
 }
 
 }  // namespace
