@@ -196,6 +196,28 @@ def build_kmap_static(kind: int, in_coords: torch.Tensor, n_in: torch.Tensor, ca
     return g_out[0], g_out[1], g_out[2]
 
 
+def check_conv(dtype: int, x: torch.Tensor, w: torch.Tensor, scale: Optional[torch.Tensor], shift: Optional[torch.Tensor],
+               nbr: torch.Tensor, n_out: torch.Tensor, capacity_out: int, out: torch.Tensor) -> Tuple[int, int]:
+    """What emc2_spconv cannot see of its arguments (devices, types, sizes); returns (Cin, Cout)."""
+    td = _TORCH_DTYPE[dtype]
+    _dev_check(x, td, "x")
+    _dev_check(w, td, "w")
+    _dev_check(out, td, "out")
+    _dev_check(nbr, torch.int32, "nbr")
+    _dev_check(n_out, torch.int32, "n_out")
+    if w.dim() != 3 or w.shape[0] != 27 or x.dim() != 2 or x.shape[1] != w.shape[1]:
+        raise ValueError("w must be [27][Cin][Cout] and x [n][Cin]")
+    cin, cout = int(w.shape[1]), int(w.shape[2])
+    if out.numel() < capacity_out * cout or nbr.numel() < 27 * capacity_out:
+        raise ValueError("out / nbr smaller than capacity_out")
+    if scale is not None:
+        _dev_check(scale, torch.float32, "scale")
+        _dev_check(shift, torch.float32, "shift")
+        if scale.numel() != cout or shift.numel() != cout:
+            raise ValueError("scale/shift must have Cout entries")
+    return cin, cout
+
+
 def build_stacks(stacks, n_stacks: int, points: torch.Tensor) -> None:
     """emc2_build_stacks over a ctypes array of StackC whose buffers the caller keeps alive."""
     _dev_check(points, torch.float32, "points")
@@ -498,22 +520,7 @@ class Context:
                shift: Optional[torch.Tensor], epilogue: int, nbr: torch.Tensor, n_out: torch.Tensor, capacity_out: int,
                out: torch.Tensor, w_layout: int = W_PLAIN, map_hint: int = MAP_ANY, n_in_rows: Optional[int] = None) -> None:
         """n_in_rows: rows of x a map entry may name (default: all rows of the tensor)."""
-        td = _TORCH_DTYPE[dtype]
-        _dev_check(x, td, "x")
-        _dev_check(w, td, "w")
-        _dev_check(out, td, "out")
-        _dev_check(nbr, torch.int32, "nbr")
-        _dev_check(n_out, torch.int32, "n_out")
-        if w.dim() != 3 or w.shape[0] != 27 or x.dim() != 2 or x.shape[1] != w.shape[1]:
-            raise ValueError("w must be [27][Cin][Cout] and x [n][Cin]")
-        cin, cout = int(w.shape[1]), int(w.shape[2])
-        if out.numel() < capacity_out * cout or nbr.numel() < 27 * capacity_out:
-            raise ValueError("out / nbr smaller than capacity_out")
-        if scale is not None:
-            _dev_check(scale, torch.float32, "scale")
-            _dev_check(shift, torch.float32, "shift")
-            if scale.numel() != cout or shift.numel() != cout:
-                raise ValueError("scale/shift must have Cout entries")
+        cin, cout = check_conv(dtype, x, w, scale, shift, nbr, n_out, capacity_out, out)
         self._chk(self.lib.emc2_spconv(self.h, dtype, _ptr(x), _ptr(w), w_layout, _ptr(scale), _ptr(shift), epilogue, _ptr(nbr),
                                        map_hint, _ptr(n_out), capacity_out,
                                        int(x.shape[0]) if n_in_rows is None else n_in_rows, cin, cout, _ptr(out), _stream()))

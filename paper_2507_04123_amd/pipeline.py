@@ -83,22 +83,29 @@ def capture_stream(device) -> "torch.cuda.Stream":
 class NativePass:
     """The maps and the convolutions of one or more branches over the same points as two native calls: emc2_build_stacks
     (voxelization and every kernel map of every branch, in a handful of launches) and emc2_spconv_list.  The argument
-    blocks are filled once; a pass sets the points and frame ids.  They hold addresses only: whoever makes the pass keeps the
-    runners.  `route`: (expert, slot) tensors of a routed batch,
-    branch e then takes the scenes of expert e."""
+    blocks are filled and checked once, and again by the first pass that finds a runner's context or one of its buffers
+    replaced; every pass sets the points and frame ids.  The runners are handed in by each call (they own their passes).
+    `route`: (expert, slot) tensors of a routed batch, branch e then takes the scenes of expert e."""
 
-    def __init__(self, runners: Sequence["BranchRunner"], route: Optional[Tuple[torch.Tensor, torch.Tensor]] = None):
-        self.n = len(runners)
-        self.outs = [r.acts[-1] for r in runners]
-        self.stacks = (B.StackC * self.n)()
-        calls: List[B.ConvCallC] = []
+    def __init__(self, route: Optional[Tuple[torch.Tensor, torch.Tensor]] = None):
+        self.route = route
+        self.stacks = self.calls = None
+        self.stacks_of = self.calls_of = None      # addresses the blocks were filled from
+        self.held: Tuple[torch.Tensor, ...] = ()   # the tensors behind the calls' addresses
+
+    @staticmethod
+    def covers(runners: Sequence["BranchRunner"]) -> bool:
+        return len(runners) <= B.MAX_STACKS and all(len(r.levels) <= B.STACK_MAX_LEVELS for r in runners)
+
+    def _fill_stacks(self, runners: Sequence["BranchRunner"]) -> None:
+        stacks = (B.StackC * len(runners))()
         for e, r in enumerate(runners):
-            s, sp = self.stacks[e], r.branch.spec
+            s, sp = stacks[e], r.branch.spec
             s.ctx = r.ctx.h
             s.spec = B.voxel_spec_c(sp, 4)
-            s.expert, s.n_levels = (-1 if route is None else e), len(r.levels)
-            if route is not None:
-                s.d_route, s.d_slot = route[0].data_ptr(), route[1].data_ptr()
+            s.expert, s.n_levels = (-1 if self.route is None else e), len(r.levels)
+            if self.route is not None:
+                s.d_route, s.d_slot = self.route[0].data_ptr(), self.route[1].data_ptr()
             s.d_feats, s.d_counts = r.feats32.data_ptr(), r.counts.data_ptr()
             s.lp_dtype = r.dtype if r.feats_lp is not None else F16
             s.d_feats_lp = r.feats_lp.data_ptr() if r.feats_lp is not None else None
@@ -106,28 +113,35 @@ class NativePass:
                 c.capacity, c.d_coords, c.d_n, c.slot = lv.cap, lv.coords.data_ptr(), lv.n.data_ptr(), lv.slot
                 c.d_subm_nbr = lv.subm_nbr.data_ptr() if lv.subm_nbr is not None else None
                 c.d_down_nbr = lv.down_nbr.data_ptr() if lv.down_nbr is not None else None
-            calls += r.conv_calls()
-        self.calls = (B.ConvCallC * len(calls))(*calls)
+        self.stacks = stacks
 
-    @staticmethod
-    def covers(runners: Sequence["BranchRunner"]) -> bool:
-        return len(runners) <= B.MAX_STACKS and all(len(r.levels) <= B.STACK_MAX_LEVELS for r in runners)
-
-    def maps(self, points: torch.Tensor, batch: Optional[torch.Tensor]) -> None:
+    def maps(self, runners: Sequence["BranchRunner"], points: torch.Tensor, batch: Optional[torch.Tensor]) -> None:
+        of = [a for r in runners for a in r.map_addresses()]
+        if of != self.stacks_of:
+            self.stacks_of = None
+            self._fill_stacks(runners)
+            self.stacks_of = of
         if batch is not None:
             if not batch.is_cuda or batch.dtype != torch.int32 or not batch.is_contiguous() or batch.numel() != points.shape[0]:
                 raise ValueError("batch: need a contiguous int32 device tensor with one id per point")
         for s in self.stacks:
             s.d_batch = batch.data_ptr() if batch is not None else None
-        B.build_stacks(self.stacks, self.n, points)
+        B.build_stacks(self.stacks, len(runners), points)
 
-    def convs(self) -> List[torch.Tensor]:
+    def convs(self, runners: Sequence["BranchRunner"]) -> List[torch.Tensor]:
+        held = [t for r in runners for t in r.conv_tensors()]
+        of = [v for r in runners for v in (r.ctx.h.value if r.ctx.h else None, r.branch.layers)] + [t.data_ptr() for t in held]
+        if of != self.calls_of:
+            self.calls_of = None
+            calls = [c for r in runners for c in r.conv_calls()]
+            self.calls = (B.ConvCallC * len(calls))(*calls)
+            self.calls_of, self.held = of, tuple(held)
         B.spconv_list(self.calls, len(self.calls))
-        return list(self.outs)
+        return [r.acts[-1] if r.acts else r.conv_input() for r in runners]
 
-    def run(self, points: torch.Tensor, batch: Optional[torch.Tensor]) -> List[torch.Tensor]:
-        self.maps(points, batch)
-        return self.convs()
+    def run(self, runners: Sequence["BranchRunner"], points: torch.Tensor, batch: Optional[torch.Tensor]) -> List[torch.Tensor]:
+        self.maps(runners, points, batch)
+        return self.convs(runners)
 
 
 class BranchRunner:
@@ -187,27 +201,50 @@ class BranchRunner:
         self.ev_done = None           # recorded on the caller's stream at the end of the previous overlapped run
         self.ev_subm = [torch.cuda.Event() for _ in self.levels]
         self.ev_down = [torch.cuda.Event() for _ in self.levels]
-        self.native = NativePass([self]) if NativePass.covers([self]) else None
+        self.native = NativePass() if NativePass.covers([self]) else None
         self.can_overlap = all(lay == B.W_PACKED or not ctx.uses_mfma(dtype, l.cin, l.cout)
                                for (_, lay), l in zip(self.wdev, branch.layers))
 
+    def conv_input(self) -> torch.Tensor:
+        return self.feats32 if self.dtype == F32 else self.feats_lp
+
+    def map_addresses(self) -> list:
+        """The context, the grid and every buffer that voxelization and the kernel maps write (None where there is none)."""
+        out = [self.ctx.h.value if self.ctx.h else None, self.branch.spec, self.feats32.data_ptr(), self.counts.data_ptr(),
+               self.feats_lp.data_ptr() if self.feats_lp is not None else None]
+        for lv in self.levels:
+            out += [lv.cap, lv.slot, lv.coords.data_ptr(), lv.n.data_ptr(), lv.subm_nbr.data_ptr() if lv.subm_nbr is not None else None,
+                    lv.down_nbr.data_ptr() if lv.down_nbr is not None else None]
+        return out
+
+    def conv_tensors(self) -> List[torch.Tensor]:
+        """Every tensor that the convolutions read or write."""
+        out = [self.conv_input(), *self.acts]
+        for (w, _), p, layer in zip(self.wdev, self.params, self.branch.layers):
+            out += [w, p["scale"], p["shift"]] if layer.epilogue != EPI_NONE else [w]
+        for lv in self.levels:
+            out += [t for t in (lv.n, lv.subm_nbr, lv.down_nbr) if t is not None]
+        return out
+
     def conv_calls(self) -> List["B.ConvCallC"]:
-        """The argument blocks of this branch's convolutions, in order."""
+        """The argument blocks of this branch's convolutions, in order, their tensors checked."""
         out, lvl = [], 0
-        x = self.feats32 if self.dtype == F32 else self.feats_lp
+        x = self.conv_input()
         for li, layer in enumerate(self.branch.layers):
             if layer.kind == STRIDED:
                 lvl += 1
             lv, p, y = self.levels[lvl], self.params[li], self.acts[li]
-            epi = layer.epilogue != EPI_NONE
+            nbr = lv.down_nbr if layer.kind == STRIDED else lv.subm_nbr
+            w, scale, shift = self.wdev[li][0], *((p["scale"], p["shift"]) if layer.epilogue != EPI_NONE else (None, None))
             c = B.ConvCallC()
             c.ctx, c.dtype = self.ctx.h, self.dtype
-            c.d_in, c.n_in_rows, c.cin, c.cout = x.data_ptr(), x.shape[0], layer.cin, layer.cout
-            c.d_w, c.w_layout = self.wdev[li][0].data_ptr(), self.wdev[li][1]
-            c.d_scale = p["scale"].data_ptr() if epi else None
-            c.d_shift = p["shift"].data_ptr() if epi else None
+            c.cin, c.cout = B.check_conv(self.dtype, x, w, scale, shift, nbr, lv.n, lv.cap, y)
+            c.d_in, c.n_in_rows = x.data_ptr(), x.shape[0]
+            c.d_w, c.w_layout = w.data_ptr(), self.wdev[li][1]
+            c.d_scale = scale.data_ptr() if scale is not None else None
+            c.d_shift = shift.data_ptr() if shift is not None else None
             c.epilogue, c.map_hint = layer.epilogue, layer.kind
-            c.d_nbr = (lv.down_nbr if layer.kind == STRIDED else lv.subm_nbr).data_ptr()
+            c.d_nbr = nbr.data_ptr()
             c.d_n_out, c.capacity_out, c.d_out = lv.n.data_ptr(), lv.cap, y.data_ptr()
             out.append(c)
             x = y
@@ -307,7 +344,7 @@ class BranchRunner:
         manager; it brackets each library call (used by the bench to time kernels with stream events), and the pass is
         then issued call by call."""
         if timer is None and self.native is not None:
-            return self.native.run(points, batch)[0]
+            return self.native.run((self,), points, batch)[0]
         ctx, br = self.ctx, self.branch
         tm = timer if timer is not None else _no_timer
         l0 = self.levels[0]
@@ -349,7 +386,7 @@ class BranchRunner:
         work that uses the context's scratch).  run_convs() is the second stage; together they do what run() does,
         with every map built before the first convolution."""
         if timer is None and self.native is not None:
-            self.native.maps(points, batch)
+            self.native.maps((self,), points, batch)
             return
         ctx, br = self.ctx, self.branch
         tm = timer if timer is not None else _no_timer
@@ -378,7 +415,7 @@ class BranchRunner:
         maps run_maps() left in this runner's buffers.  Uses no context scratch when the weights are packed, so it
         may overlap the first stage of another runner."""
         if timer is None and self.native is not None:
-            return self.native.convs()[0]
+            return self.native.convs((self,))[0]
         ctx, br = self.ctx, self.branch
         tm = timer if timer is not None else _no_timer
         x = self.feats32 if self.dtype == F32 else self.feats_lp
@@ -440,8 +477,7 @@ class ConfigRunner:
             seed = gen.frame_seed(cfg.index, 0) + len(br.name)
             self.branches.append((ctx, BranchRunner(ctx, br, cfg.dtype, n_points, device_params(br.layers, seed, cfg.dtype),
                                                     capacities=caps, device=device)))
-        runners = [r for _, r in self.branches]
-        self.native = NativePass(runners) if NativePass.covers(runners) else None
+        self.native = NativePass() if NativePass.covers([r for _, r in self.branches]) else None
         self._side: List["torch.cuda.Stream"] = []
         self._device = device
         self.camera = None
@@ -484,7 +520,7 @@ class ConfigRunner:
         """Everything on the current stream: the maps of all branches together, then the convolutions (with a `timer`,
         call by call, branch by branch)."""
         if timer is None and self.native is not None:
-            outs = self.native.run(points, batch)
+            outs = self.native.run([r for _, r in self.branches], points, batch)
             self._gather(points, _no_timer)
             return outs
         tm = timer if timer is not None else _no_timer
@@ -555,7 +591,7 @@ class ConfigRunner:
 
         def maps():
             if self.native is not None:
-                self.native.maps(points, batch)
+                self.native.maps([r for _, r in self.branches], points, batch)
             else:
                 for _, r in self.branches:
                     r.run_maps(points, batch)
@@ -649,9 +685,8 @@ class RoutedRunner:
             ctx = B.Context(n_points, max(caps), cells_of(br.spec.grid, n_scenes), n_slots=len(caps))
             self.runners.append((ctx, BranchRunner(ctx, br, dtype, n_points, device_params(br.layers, seed + e, dtype),
                                                    capacities=caps, device=device)))
-        runners = [r for _, r in self.runners]
-        assert NativePass.covers(runners)
-        self.native = NativePass(runners, route=(self.expert, self.slot))
+        assert NativePass.covers([r for _, r in self.runners])
+        self.native = NativePass(route=(self.expert, self.slot))
 
     def close(self) -> None:
         for ctx, _ in self.runners:
@@ -680,7 +715,9 @@ class RoutedRunner:
 
     def run(self, points: torch.Tensor, scene: torch.Tensor, props: torch.Tensor, prop_scene: Optional[torch.Tensor],
             dist: float, conf: float) -> List[torch.Tensor]:
+        if points.shape[0] != self.n_points or (scene is not None and scene.numel() != self.n_points):
+            raise ValueError("points / scene length != n_points")
         ctx0 = self.runners[0][0]
         ctx0.dispatch(props, prop_scene, self.n_scenes, dist, conf, self.expert, self.counts, self.order)
         ctx0.group_slots(self.expert, self.order, self.counts, self.n_scenes, self.slot)
-        return self.native.run(points, scene)
+        return self.native.run([r for _, r in self.runners], points, scene)

@@ -137,3 +137,74 @@ def test_several_stacks_in_one_call_and_their_errors():
     assert ei.value.status == B.ERR_CAPACITY
     for m in many + ref:
         m.ctx.close()
+
+
+class _Timer:
+    """A timer makes a runner issue its pass call by call."""
+
+    def __call__(self, tag):
+        return self
+
+    def __enter__(self):
+        return self
+
+    def __exit__(self, *exc):
+        return False
+
+
+def _runner(n):
+    import dataclasses
+    from paper_2507_04123_amd.configs import get_config
+    from paper_2507_04123_amd.pipeline import ConfigRunner
+    cfg = get_config(2)
+    return ConfigRunner(dataclasses.replace(cfg, n_points=n, n_frames=1), n)
+
+
+def test_pass_follows_what_its_runner_holds():
+    """A pass works on the tensors and the context that the runner holds when it is issued, checks what it has not seen
+    before, takes a frame without points, and refuses a closed context."""
+    from paper_2507_04123_amd import gen
+    from paper_2507_04123_amd.configs import get_config
+    n = 4000
+    cr = _runner(n)
+    ctx, r = cr.branches[0]
+    pts = torch.from_numpy(gen.make_frames(get_config(2))[0][::30][:n]).cuda().contiguous()
+    first = cr.run(pts, None)[0].clone()
+    k = len(r.params) - 1
+    r.params[k]["scale"] = r.params[k]["scale"] * 2.0       # the tensor that the first pass read is gone
+    r.acts[k - 1] = torch.zeros_like(r.acts[k - 1])
+    torch.cuda.empty_cache()
+    got = cr.run(pts, None)[0].clone()
+    single = r.run(pts, None).clone()
+    m = int(r.levels[-1].n.item())
+    want = cr.run(pts, None, timer=_Timer())[0]
+    assert torch.equal(got[:m], want[:m]) and torch.equal(single[:m], want[:m]) and not torch.equal(got[:m], first[:m])
+    good, r.params[k]["scale"] = r.params[k]["scale"], r.params[k]["scale"].cpu()
+    for _ in range(2):                                      # refused each time, not only by the pass that meets it first
+        with pytest.raises(ValueError, match="scale"):
+            cr.run(pts, None)
+    r.params[k]["scale"] = good
+    cr.run(pts[:0], None)
+    ctx.status_sync()
+    assert all(int(lv.n.item()) == 0 for lv in r.levels)
+    assert torch.equal(cr.run(pts, None)[0][:m], got[:m])
+    ctx.status_sync()
+    ctx.close()
+    with pytest.raises(B.Emc2Error):
+        cr.run(pts, None)
+    with pytest.raises(B.Emc2Error):
+        r.run(pts, None)
+
+
+def test_routed_pass_takes_as_many_points_as_it_was_made_for():
+    from paper_2507_04123_amd.configs import F16, expert_branches
+    from paper_2507_04123_amd.pipeline import RoutedRunner
+    rr = RoutedRunner(expert_branches(2), F16, 512, 2, seed=3)
+    pts, scene = torch.zeros((512, 4), device="cuda"), torch.zeros(512, dtype=torch.int32, device="cuda")
+    props, prop_scene = torch.ones((1, 4), device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
+    rr.run(pts, scene, props, prop_scene, 23.5, 0.5)
+    for p, s in ((pts[:500], scene[:500]), (pts, scene[:500]), (pts[:500], None)):
+        with pytest.raises(ValueError, match="n_points"):
+            rr.run(p, s, props, prop_scene, 23.5, 0.5)
+    rr.status_sync()
+    rr.close()
