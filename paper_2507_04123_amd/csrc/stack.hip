@@ -488,7 +488,7 @@ struct Phase {
   }
 };
 
-// Host-side checks of one stack and its device description; index metadata is updated here.
+// Host-side checks of one stack and its device description.
 emc2_status describe(const emc2_stack& s, int64_t n_points, DevStack* d) {
   emc2_ctx* ctx = s.ctx;
   if (!s.d_feats || !s.d_counts || s.n_levels < 1 || s.n_levels > kLevels)
@@ -545,13 +545,18 @@ emc2_status describe(const emc2_stack& s, int64_t n_points, DevStack* d) {
     sums += units + emc2_div_up(units, kSuper);
     if (sums > sums_end) return emc2_fail(ctx, EMC2_ERR_UNSUPPORTED, "emc2_build_stacks: scan scratch too small for this stack");
   }
+  return EMC2_OK;
+}
+
+// The slots now describe this stack's levels: only once every stack of the call has passed its checks, since none is
+// built when one is refused.
+void publish(const emc2_stack& s, const DevStack& d) {
   for (int l = 0; l < s.n_levels; ++l) {
-    SlotMeta& m = ctx->meta[s.level[l].slot];
-    for (int a = 0; a < 3; ++a) m.grid[a] = d->lv[l].g[a];
+    SlotMeta& m = s.ctx->meta[s.level[l].slot];
+    for (int a = 0; a < 3; ++a) m.grid[a] = d.lv[l].g[a];
     m.n_batch = s.spec.n_batch;
     m.valid = true;
   }
-  return EMC2_OK;
 }
 
 }  // namespace
@@ -584,6 +589,7 @@ extern "C" emc2_status emc2_build_stacks(const emc2_stack* stacks, int32_t n_sta
     }
     if (a.st[i].n_levels > deepest) deepest = a.st[i].n_levels;
   }
+  for (int i = 0; i < n_stacks; ++i) publish(stacks[i], a.st[i]);
   hipStream_t s = (hipStream_t)stream;
   Phase p{&a};
   const int64_t point_blocks = emc2_div_up(n_points, 256);

@@ -139,6 +139,21 @@ def test_several_stacks_in_one_call_and_their_errors():
         m.ctx.close()
 
 
+def test_a_refused_call_leaves_every_slot_as_it_was():
+    spec, (pts, batch) = VoxelSpec((0.0, 0.0, 0.0), (1.0, 1.0, 1.0), (20, 10, 4), 2), _points(5, (20, 10, 4), 2, 300)
+    bufs = [_Bufs(spec.grid, 2, 2, 300) for _ in range(2)]
+    arr = (B.StackC * 2)(*[b.stack(spec, batch) for b in bufs])
+    arr[1].level[1].slot = 7                      # the second stack's fault: the first one is not built either
+    with pytest.raises(B.Emc2Error, match="slot"):
+        B.build_stacks(arr, 2, pts)
+    a = bufs[0]
+    a.n[0].zero_()
+    with pytest.raises(B.Emc2Error):              # no index there to build a map from
+        a.ctx.build_kmap(B.SUBM, a.coords[0], a.n[0], a.cap[0], spec.grid, 2, a.cap[0], a.subm[0], a.n[0], in_slot=0)
+    for b in bufs:
+        b.ctx.close()
+
+
 class _Timer:
     """A timer makes a runner issue its pass call by call."""
 
