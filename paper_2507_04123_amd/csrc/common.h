@@ -133,4 +133,11 @@ void emc2_index_mark_coords(emc2_ctx* ctx, cellword_t* idx, const int32_t* d_coo
 // text of the last host-side error of emc2_build_kmap_static (kmap.hip); what emc2_last_error(NULL) returns
 const char* emc2_static_last_error();
 
+// Blocks of a launch whose threads step through the pieces of a device-side row count: two rounds of the chip.  The host
+// knows only the rows' capacity, several times the count, and blocks without work cost about 0.25 us per thousand.  With the
+// pooling's last pass per block boundary: bridge of a 375 x 1242 image and 120 000 points 160 -> 154 us.
+static inline unsigned emc2_piece_blocks(int64_t pieces, int64_t threads) {
+  const int64_t b = (pieces + threads - 1) / threads;
+  return (unsigned)(b < 4096 ? b : 4096);
+}
 static inline int64_t emc2_div_up(int64_t a, int64_t b) { return (a + b - 1) / b; }

@@ -54,23 +54,26 @@ __global__ void __launch_bounds__(256) k_fill_zero4(uint32_t* __restrict__ p, in
   if (i < n4) p[i] = 0u;
 }
 
-// One thread per (voxel, 4-byte word of its feature row): consecutive threads copy consecutive words, so a
-// row moves as whole cache lines on both sides.
-__global__ void __launch_bounds__(256) k_bev_scatter(const int4* __restrict__ coords, const uint32_t* __restrict__ feats,
+// One piece per (voxel, word of VEC bytes of its feature row), the pieces dealt to the threads in turn: consecutive threads
+// copy consecutive words, so a row moves as whole cache lines on both sides.
+template <typename VEC>
+__global__ void __launch_bounds__(256) k_bev_scatter(const int4* __restrict__ coords, const VEC* __restrict__ feats,
                                                      const int32_t* __restrict__ d_n, int64_t capacity, int gx, int gy, int gz,
-                                                     int n_batch, int row_words, uint32_t* __restrict__ out) {
+                                                     int n_batch, int row_words, VEC* __restrict__ out) {
   int64_t n = *d_n;
   if (n > capacity) n = capacity;
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t v = t / row_words;
-  if (v >= n) return;
-  const int w = (int)(t - v * row_words);
-  const int4 c = coords[v];  // (b, z, y, x)
-  if ((unsigned)c.x >= (unsigned)n_batch || (unsigned)c.y >= (unsigned)gz || (unsigned)c.z >= (unsigned)gy ||
-      (unsigned)c.w >= (unsigned)gx)
-    return;  // malformed coordinate: ignore rather than write out of bounds
-  const int64_t cell = (((int64_t)c.x * gy + c.z) * gx + c.w) * gz + c.y;
-  out[cell * row_words + w] = feats[v * row_words + w];
+  const int64_t pieces = n * row_words, step = (int64_t)gridDim.x * 256;
+  const bool narrow = (pieces >> 32) == 0;          // 32-bit division is several times cheaper
+  for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < pieces; t += step) {
+    const int64_t v = narrow ? (int64_t)((uint32_t)t / (uint32_t)row_words) : t / row_words;
+    const int w = (int)(t - v * row_words);
+    const int4 c = coords[v];  // (b, z, y, x)
+    if ((unsigned)c.x >= (unsigned)n_batch || (unsigned)c.y >= (unsigned)gz || (unsigned)c.z >= (unsigned)gy ||
+        (unsigned)c.w >= (unsigned)gx)
+      continue;  // malformed coordinate: ignore rather than write out of bounds
+    const int64_t cell = (((int64_t)c.x * gy + c.z) * gx + c.w) * gz + c.y;
+    out[cell * row_words + w] = feats[t];
+  }
 }
 
 }  // namespace
@@ -127,8 +130,14 @@ extern "C" emc2_status emc2_bev_flatten(emc2_ctx* ctx, emc2_dtype dtype, const i
   }
   if (words - 4 * n16 > 0)
     hipLaunchKernelGGL(k_fill_zero4, dim3(1), dim3(256), 0, s, (uint32_t*)d_out + 4 * n16, words - 4 * n16);
-  const int64_t threads = capacity * row_words;
-  hipLaunchKernelGGL(k_bev_scatter, dim3((unsigned)emc2_div_up(threads, 256)), dim3(256), 0, s, (const int4*)d_coords,
-                     (const uint32_t*)d_feats, d_n, capacity, grid[0], grid[1], grid[2], n_batch, row_words, (uint32_t*)d_out);
+  // 16 bytes a thread where rows and addresses allow it, else 4.
+  if (row_bytes % 16 == 0 && (((uintptr_t)d_feats | (uintptr_t)d_out) & 15) == 0)
+    hipLaunchKernelGGL(k_bev_scatter<uint4>, dim3(emc2_piece_blocks(capacity * (row_words / 4), 256)), dim3(256), 0, s,
+                       (const int4*)d_coords, (const uint4*)d_feats, d_n, capacity, grid[0], grid[1], grid[2], n_batch,
+                       row_words / 4, (uint4*)d_out);
+  else
+    hipLaunchKernelGGL(k_bev_scatter<uint32_t>, dim3(emc2_piece_blocks(capacity * row_words, 256)), dim3(256), 0, s,
+                       (const int4*)d_coords, (const uint32_t*)d_feats, d_n, capacity, grid[0], grid[1], grid[2], n_batch,
+                       row_words, (uint32_t*)d_out);
   return emc2_check_hip(ctx, hipGetLastError(), "emc2_bev_flatten launch");
 }

@@ -16,7 +16,7 @@
 //            cell are combined in registers, cells inside a group of 8 rows are finished there, partial runs
 //            meet in LDS (plain stores, owner sums), the (at most one per block boundary) cell that continues
 //            into the next block adds its partial result to a small global accumulator
-//   finish   per boundary-crossing cell: accumulator -> mean / max -> fp16
+//   finish   per block boundary, the cell that crosses it: accumulator -> mean / max -> fp16
 #include <hip/hip_fp16.h>
 #include <math.h>
 
@@ -403,20 +403,23 @@ __global__ void __launch_bounds__(256, 4) k_pool_reduce(const __half* __restrict
   }
 }
 
+// One thread per (reduction block, 8 channels): the last row of a block's rows names the only cell that can begin in the
+// block and go on beyond it, and that cell's sum is in the block's accumulator.  A thread per possible cell instead (one
+// per pixel, as the host knows no better bound) was 14 k blocks for a 375 x 1242 image, 57 now.
 template <int MODE>
-__global__ void __launch_bounds__(256) k_pool_finish(const int32_t* __restrict__ starts, const int32_t* __restrict__ d_n,
-                                                     int64_t capacity, int C, int RPB, const uint32_t* __restrict__ acc,
+__global__ void __launch_bounds__(256) k_pool_finish(const int32_t* __restrict__ starts, const int32_t* __restrict__ srank,
+                                                     const int32_t* __restrict__ d_rows, int C, const uint32_t* __restrict__ acc,
                                                      __half* __restrict__ feats) {
-  int64_t n = *d_n;
-  if (n > capacity) n = capacity;
-  const int chunks = C >> 3;
-  const int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t r = w / chunks;
-  if (r >= n) return;
-  const int k = (int)(w - r * chunks);
+  constexpr int64_t RPB = EMC2_POOL_RPB;
+  const uint32_t chunks = (uint32_t)C >> 3;
+  const uint32_t w = blockIdx.x * 256u + threadIdx.x;
+  const uint32_t blk = w / chunks, k = w - blk * chunks;
+  const int64_t t1 = ((int64_t)blk + 1) * RPB;
+  if (t1 >= *d_rows) return;                        // the last block of rows, or none: nothing goes on beyond it
+  const int64_t r = srank[t1 - 1];
   const int64_t a = starts[r], b = starts[r + 1];
-  if (a / RPB == (b - 1) / RPB) return;  // finished by the reduction
-  const uint32_t* src = acc + (a / RPB) * C + 8 * k;
+  if (a < t1 - RPB || b <= t1) return;              // begun in an earlier block, or finished by the reduction
+  const uint32_t* src = acc + (int64_t)blk * C + 8 * k;
   float f[8];
   const float cnt = (float)(b - a);
 #pragma unroll
@@ -484,8 +487,8 @@ __global__ void __launch_bounds__(256) k_fuse_place(const int4* __restrict__ coo
   coords_out[r] = c;  // where both sets hold the site they write the same value
 }
 
-// One thread per (output row, word of VEC bytes): the row is written once, each half copied from its source row
-// or zero-filled, the padding beyond the two halves zeroed.
+// One piece per (output row, word of VEC bytes), the pieces dealt to the threads in turn: the row is written once,
+// each half copied from its source row or zero-filled, the padding beyond the two halves zeroed.
 template <typename VEC>
 __global__ void __launch_bounds__(256) k_fuse_gather(const VEC* __restrict__ feats_l, const VEC* __restrict__ feats_i,
                                                      const int32_t* __restrict__ src_l, const int32_t* __restrict__ src_i,
@@ -493,20 +496,22 @@ __global__ void __launch_bounds__(256) k_fuse_gather(const VEC* __restrict__ fea
                                                      VEC* __restrict__ out) {
   int64_t n = *d_n;
   if (n > capacity) n = capacity;
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t r = t / wo;
-  if (r >= n) return;
-  const int w = (int)(t - r * wo);
-  VEC v;
-  memset(&v, 0, sizeof(VEC));
-  if (w < wl) {
-    const int32_t s = src_l[r];
-    if (s >= 0) v = feats_l[(int64_t)s * wl + w];
-  } else if (w < wl + wi) {
-    const int32_t s = src_i[r];
-    if (s >= 0) v = feats_i[(int64_t)s * wi + (w - wl)];
+  const int64_t pieces = n * wo, step = (int64_t)gridDim.x * 256;
+  const bool narrow = (pieces >> 32) == 0;          // 32-bit division is several times cheaper
+  for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < pieces; t += step) {
+    const int64_t r = narrow ? (int64_t)((uint32_t)t / (uint32_t)wo) : t / wo;
+    const int w = (int)(t - r * wo);
+    VEC v;
+    memset(&v, 0, sizeof(VEC));
+    if (w < wl) {
+      const int32_t s = src_l[r];
+      if (s >= 0) v = feats_l[(int64_t)s * wl + w];
+    } else if (w < wl + wi) {
+      const int32_t s = src_i[r];
+      if (s >= 0) v = feats_i[(int64_t)s * wi + (w - wl)];
+    }
+    out[t] = v;
   }
-  out[t] = v;
 }
 
 }  // namespace
@@ -579,7 +584,7 @@ extern "C" emc2_status emc2_pool_image(emc2_ctx* ctx, const void* d_img, const f
   hipLaunchKernelGGL(k_pool_scatter, pg, blk, 0, s, npix, ctx->pix_rank, ctx->pix_pos, ctx->cell_start, ctx->pix_perm,
                      ctx->pix_srank);
   const size_t lds_bytes = sizeof(float) * (64 * (size_t)C + 32);  // heads and tails of the 32 groups, their cells
-  const dim3 rg((unsigned)red_blocks), fg((unsigned)emc2_div_up(bound * (C / 8), 256));
+  const dim3 rg((unsigned)red_blocks), fg((unsigned)emc2_div_up(red_blocks * (C / 8), 256));
   if (lds_bytes > 65536) {  // C = 256 only: a little over the default per-block limit (the CU has 160 KB)
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pool_reduce<0>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pool_reduce<1>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
@@ -587,13 +592,13 @@ extern "C" emc2_status emc2_pool_image(emc2_ctx* ctx, const void* d_img, const f
   if (mode == EMC2_POOL_MEAN) {
     hipLaunchKernelGGL(k_pool_reduce<0>, rg, blk, lds_bytes, s, (const __half*)d_img, ctx->pix_perm, ctx->pix_srank,
                        ctx->cell_start, ctx->dev_words + 2, C, ctx->pool_acc, (__half*)d_feats);
-    hipLaunchKernelGGL(k_pool_finish<0>, fg, blk, 0, s, ctx->cell_start, d_n_cells, capacity, C, RPB, ctx->pool_acc,
-                       (__half*)d_feats);
+    hipLaunchKernelGGL(k_pool_finish<0>, fg, blk, 0, s, ctx->cell_start, ctx->pix_srank, ctx->dev_words + 2, C,
+                       ctx->pool_acc, (__half*)d_feats);
   } else {
     hipLaunchKernelGGL(k_pool_reduce<1>, rg, blk, lds_bytes, s, (const __half*)d_img, ctx->pix_perm, ctx->pix_srank,
                        ctx->cell_start, ctx->dev_words + 2, C, ctx->pool_acc, (__half*)d_feats);
-    hipLaunchKernelGGL(k_pool_finish<1>, fg, blk, 0, s, ctx->cell_start, d_n_cells, capacity, C, RPB, ctx->pool_acc,
-                       (__half*)d_feats);
+    hipLaunchKernelGGL(k_pool_finish<1>, fg, blk, 0, s, ctx->cell_start, ctx->pix_srank, ctx->dev_words + 2, C,
+                       ctx->pool_acc, (__half*)d_feats);
   }
   emc2_status st = emc2_check_hip(ctx, hipGetLastError(), "emc2_pool_image launch");
   if (st != EMC2_OK) return st;
@@ -657,11 +662,11 @@ extern "C" emc2_status emc2_fuse(emc2_ctx* ctx, emc2_dtype dtype, const int32_t*
                      capacity_i, idx, grid[0], grid[1], grid[2], n_batch, capacity_out, src_l, src_i, (int4*)d_coords_out);
   if (!((bl | bi | bo) & 15)) {
     const int wl = (int)(bl / 16), wi = (int)(bi / 16), wo = (int)(bo / 16);
-    hipLaunchKernelGGL(k_fuse_gather<uint4>, dim3((unsigned)emc2_div_up(bound * wo, 256)), blk, 0, s, (const uint4*)d_feats_l,
+    hipLaunchKernelGGL(k_fuse_gather<uint4>, dim3(emc2_piece_blocks(bound * wo, 256)), blk, 0, s, (const uint4*)d_feats_l,
                        (const uint4*)d_feats_i, src_l, src_i, d_n_out, capacity_out, wl, wi, wo, (uint4*)d_feats_out);
   } else {
     const int wl = (int)(bl / 4), wi = (int)(bi / 4), wo = (int)(bo / 4);
-    hipLaunchKernelGGL(k_fuse_gather<uint32_t>, dim3((unsigned)emc2_div_up(bound * wo, 256)), blk, 0, s,
+    hipLaunchKernelGGL(k_fuse_gather<uint32_t>, dim3(emc2_piece_blocks(bound * wo, 256)), blk, 0, s,
                        (const uint32_t*)d_feats_l, (const uint32_t*)d_feats_i, src_l, src_i, d_n_out, capacity_out, wl, wi, wo,
                        (uint32_t*)d_feats_out);
   }

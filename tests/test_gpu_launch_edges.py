@@ -1,5 +1,6 @@
 """GPU tests at the sizes where a launch changes shape: rounds of the span convolution, the grid limit of the register-direct
-one, vector tails of the quantisers, waves and shared cells of the voxelizer, the three-launch index scan."""
+one, vector tails of the quantisers, waves and shared cells of the voxelizer, the three-launch index scan, more pieces of
+rows than one step of a copy's threads."""
 import numpy as np
 import pytest
 import torch
@@ -67,6 +68,64 @@ def test_direct_conv_grid_limit(cin, cout, n):
     _check_conv(n, cin, cout, B.MAP_ANY, False)
 
 
+# inputs of less than 4 GiB are read through a buffer descriptor, larger ones by address; any negative entry is absent
+@pytest.mark.parametrize("cin,cout,n_in", [(64, 32, 1 << 10), (64, 64, (1 << 25) - 1), (64, 64, 1 << 25), (32, 32, (1 << 25) + 3),
+                                           (128, 128, (1 << 24) - 1)])
+def test_direct_conv_input_sizes_and_negative_entries(cin, cout, n_in):
+    n = 300
+    g = torch.Generator(device="cuda").manual_seed(n_in)
+    x = torch.randn((n_in, cin), generator=g, device="cuda", dtype=torch.float16)
+    w = (torch.randn((27, cin, cout), generator=g, device="cuda") * 0.1).half()
+    nbr = torch.randint(0, n_in, (27, n), generator=g, device="cuda")
+    nbr[:, ::7] = n_in - 1                                     # the last row
+    absent = torch.tensor([-1, -2, -3, -(1 << 24), -(1 << 25) + 1, -(1 << 31) + 1, -(1 << 31)], device="cuda")
+    drop = torch.rand((27, n), generator=g, device="cuda") < 0.5
+    nbr = torch.where(drop, absent[torch.randint(0, 7, (27, n), generator=g, device="cuda")], nbr).to(torch.int32).contiguous()
+    ctx = B.Context(16, 16, 64, n_slots=1)
+    wp = torch.empty_like(w)
+    ctx.pack_weights(F16, w, wp)
+    y = torch.empty((n, cout), dtype=torch.float16, device="cuda")
+    ctx.spconv(F16, x, wp, None, None, EPI_NONE, nbr, torch.tensor([n], dtype=torch.int32, device="cuda"), n, y, w_layout=B.W_PACKED)
+    ctx.status_sync()
+    exp = torch.zeros((n, cout), device="cuda")
+    for k in range(27):
+        rows = (~drop[k]).nonzero().squeeze(1)
+        exp[rows] += x[nbr[k][rows].long()].float() @ w[k].float()
+    rms = float(exp.square().mean().sqrt())
+    assert float(((y.float() - exp).abs() - 2.0 ** -10 * (exp.abs() + rms)).max()) <= 0.0
+    ctx.close()
+
+
+@pytest.mark.parametrize("cin", [64, 128])
+def test_quantised_conv_addressing_and_negative_entries(cin):
+    """Rows by buffer descriptor and (more rows vouched for than 4 GiB hold) by address: the same integers, exactly."""
+    n, n_in, cout = 300, 5000, 64
+    g = torch.Generator(device="cuda").manual_seed(cin)
+    x = torch.randint(-127, 128, (n_in, cin), generator=g, device="cuda").to(torch.int8)
+    w = torch.randint(-3, 4, (27, cin, cout), generator=g, device="cuda").to(torch.int8)
+    nbr = torch.randint(0, n_in, (27, n), generator=g, device="cuda")
+    nbr[:, ::7] = n_in - 1
+    absent = torch.tensor([-1, -2, -(1 << 25), -(1 << 26) + 1, -(1 << 31)], device="cuda")
+    drop = torch.rand((27, n), generator=g, device="cuda") < 0.5
+    nbr = torch.where(drop, absent[torch.randint(0, 5, (27, n), generator=g, device="cuda")], nbr).to(torch.int32).contiguous()
+    exp = torch.zeros((n, cout), device="cuda", dtype=torch.float64)
+    for k in range(27):
+        rows = (~drop[k]).nonzero().squeeze(1)
+        exp[rows] += x[nbr[k][rows].long()].double() @ w[k].double()
+    ctx = B.Context(16, 16, 64, n_slots=1)
+    wp = torch.empty((27 * cin * cout,), dtype=torch.int8, device="cuda")
+    ctx.pack_weights_i8(w, wp)
+    mul, add = torch.full((cout,), 2.0 ** -8, device="cuda"), torch.zeros(cout, device="cuda")
+    want = (exp * 2.0 ** -8).float().half()                      # sums below 2^24: exact until the one rounding to fp16
+    for rows_in in (n_in, 1 << 27):
+        y = torch.empty((n, cout), dtype=torch.float16, device="cuda")
+        ctx.spconv_i8(x, wp, cin, cout, mul, add, False, nbr, torch.tensor([n], dtype=torch.int32, device="cuda"), n, y,
+                      n_in_rows=rows_in)
+        ctx.status_sync()
+        assert torch.equal(y, want)
+    ctx.close()
+
+
 @pytest.mark.parametrize("dt", [np.float32, np.float16])
 @pytest.mark.parametrize("n,off", [(1, 0), (7, 0), (8, 0), (9, 0), (2048, 0), (2055, 0), (5000, 1), (5000, 4)])
 def test_quantisers_tails_and_alignment(n, off, dt):
@@ -120,4 +179,46 @@ def test_index_scan_of_more_than_16384_tiles():
     oc, _, on = oracle.voxelize(pts, batch, spec.lo, spec.vs, grid, n_batch=nb)
     v = len(oc)
     assert int(nv.item()) == v and np.array_equal(coords[:v].cpu().numpy(), oc) and np.array_equal(counts[:v].cpu().numpy(), on)
+    ctx.close()
+
+
+def _sites(n, grid, seed):
+    """n sites of a one-frame grid in key order."""
+    g = torch.Generator().manual_seed(seed)
+    k = torch.randperm(grid[0] * grid[1] * grid[2], generator=g)[:n].sort().values
+    c = torch.stack([torch.zeros_like(k), k // (grid[0] * grid[1]), k // grid[0] % grid[1], k % grid[0]], 1)
+    return k.cuda(), c.to(torch.int32).contiguous().cuda()
+
+
+# 64 half-precision channels are 8 pieces of 16 bytes or, off a 16-byte address, 32 of 4; a step is 4096 x 256 pieces
+@pytest.mark.parametrize("n,off", [(131072, 0), (131073, 0), (150001, 0), (32768, 2), (32769, 2), (70001, 2)])
+def test_bev_flatten_steps_and_alignment(n, off):
+    grid, c = (64, 64, 40), 64
+    ctx = B.Context(16, 16, 64, n_slots=1)
+    _, coords = _sites(n, grid, n)
+    flat = torch.randn(n * c + off, device="cuda").half()
+    feats = flat[off:].view(n, c)
+    out = torch.full((1, grid[1], grid[0], grid[2] * c), 9.0, dtype=torch.float16, device="cuda")
+    ctx.bev_flatten(F16, coords, feats, torch.tensor([n], dtype=torch.int32, device="cuda"), n, grid, 1, out)
+    want = torch.zeros((grid[1], grid[0], grid[2], c), dtype=torch.float16, device="cuda")
+    z, y, x = coords[:, 1].long(), coords[:, 2].long(), coords[:, 3].long()
+    want[y, x, z] = feats
+    assert torch.equal(out.view_as(want), want)
+    ctx.close()
+
+
+@pytest.mark.parametrize("nl,ni", [(40000, 40000), (90000, 70001)])
+def test_fuse_rows_beyond_one_step(nl, ni):
+    grid, cl, ci = (64, 64, 40), 32, 64                       # 12 pieces a row
+    ctx = B.Context(16, nl + ni, cells_of(grid, 1), n_slots=1)
+    (kl, lc), (ki, ic) = _sites(nl, grid, nl), _sites(ni, grid, ni + 1)
+    lf, fi = torch.randn((nl, cl), device="cuda").half(), torch.randn((ni, ci), device="cuda").half()
+    i32 = dict(dtype=torch.int32, device="cuda")
+    co, fo, n = torch.zeros((nl + ni, 4), **i32), torch.full((nl + ni, cl + ci), 9.0, dtype=torch.float16, device="cuda"), torch.zeros(1, **i32)
+    ctx.fuse(F16, lc, lf, torch.tensor([nl], **i32), nl, ic, fi, torch.tensor([ni], **i32), ni, grid, 1, nl + ni, co, fo, n)
+    keys = torch.unique(torch.cat([kl, ki]))
+    want = torch.zeros((len(keys), cl + ci), dtype=torch.float16, device="cuda")
+    want[torch.searchsorted(keys, kl), :cl] = lf
+    want[torch.searchsorted(keys, ki), cl:] = fi
+    assert int(n.item()) == len(keys) and torch.equal(fo[:len(keys)], want) and bool((fo[len(keys):] == 9.0).all())
     ctx.close()
