@@ -11,7 +11,8 @@
 //   consecutive input channels 8q .. 8q+7 of row m of the tile, i.e. 16 contiguous bytes of the feature
 //   row nbr[k][o_m].  Four lanes cover 64 contiguous bytes of one row, so a single global_load_dwordx4
 //   per (16-row tile, 32 channels) IS the A operand: global -> VGPR -> matrix core, nothing in between.
-//   Absent neighbours read a zeroed row instead (an address select, no masking of data).
+//   Absent neighbours read past the end of the input's buffer descriptor, which yields zeros (inputs of 4 GiB and more:
+//   a zeroed row instead, an address select).
 //
 // LDS holds only the weights of the current and the next tap (packed in B-fragment order, copied once
 // per block and tap, requested three taps ahead) and a small tile for the epilogue's transposition.
@@ -88,7 +89,14 @@ template <int CIN, int COUT> struct DirectCfg {
   static constexpr int MINW = (CIN >= 128 || COUT >= 128) ? 2 : 3;
 };
 
-template <int DT, int CIN, int COUT, bool LOOP>
+// Rows of the input through a buffer descriptor: 32-bit offsets, and the hardware returns zero for an offset at or beyond
+// the end without fetching anything, so an absent neighbour costs neither an address select nor a cache access.  64-beam
+// frame 524 -> 512 us; transposed 64 -> 64 over 223 k rows, where seven entries of eight are absent, 65 -> 48 us.
+__device__ __forceinline__ u32x4 buffer_row16(__amdgpu_buffer_rsrc_t rows, uint32_t byte) {
+  return __builtin_amdgcn_raw_buffer_load_b128(rows, (int)byte, 0, 0);
+}
+
+template <int DT, int CIN, int COUT, bool LOOP, bool BUF>
 __global__ void __launch_bounds__(kDThreads, (DirectCfg<CIN, COUT>::MINW))
 k_spconv_direct(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, const float* __restrict__ scale,
                 const float* __restrict__ shift, int epilogue, const int32_t* __restrict__ nbr,
@@ -111,6 +119,9 @@ k_spconv_direct(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, c
   __shared__ u32x4 wl[2][W16];
   __shared__ u32x4 otile_s[kDWaves][16 * (OCH + 1)];
 
+  // raw buffer of the input rows (word 3: 32-bit data format, no swizzle)
+  const __amdgpu_buffer_rsrc_t rows =
+      __builtin_amdgcn_make_buffer_rsrc((void*)const_cast<uint16_t*>(in), 0, BUF ? (int)((uint32_t)n_in * (CIN * 2)) : 0, 0x00020000);
   int64_t n_out = *d_n_out;
   if (n_out > capacity_out) n_out = capacity_out;
   // XCD-aware tile assignment: workgroup b runs on XCD b % 8; XCD x takes a contiguous range of tiles
@@ -159,7 +170,7 @@ k_spconv_direct(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, c
   // round trip: a ds_bpermute per tile costs a serialized ~120-cycle wait each).
 #define EMC2_A_LOAD(JROW, SET)                                                                           \
   {                                                                                                      \
-    const uint32_t jr_ = (uint32_t)(JROW);                                                               \
+    const uint32_t jr_ = (uint32_t)max((JROW), -1);   /* any negative entry is an absent neighbour */    \
     /* R = 64: lane rows are 0123 -> 0101 | 2323;  R = 32: they already are 0101 */                      \
     u32x2 h_ = {jr_, jr_};                                                                               \
     if constexpr (MT == 4) h_ = __builtin_amdgcn_permlane32_swap(jr_, jr_, false, false);                \
@@ -168,9 +179,16 @@ k_spconv_direct(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, c
     const int32_t jm_[4] = {(int32_t)lo_[0], (int32_t)lo_[1], (int32_t)hi_[0], (int32_t)hi_[1]};         \
   _Pragma("unroll") for (int mt_ = 0; mt_ < MT; ++mt_) {                                                 \
     const int32_t j_ = jm_[mt_];                                                                         \
-    const uint16_t* src_ = (j_ >= 0 ? in + (int64_t)j_ * CIN : zrow) + 8 * q;                            \
-    _Pragma("unroll") for (int ks_ = 0; ks_ < KS; ++ks_)                                                 \
-        areg[SET][mt_ * KS + ks_] = *reinterpret_cast<const u32x4*>(src_ + 32 * ks_);                    \
+    if constexpr (BUF) {                                                                                 \
+      /* absent: 2^32 less a row, and a piece of the row: out of range, zero */                          \
+      const uint32_t at_ = (uint32_t)j_ * (uint32_t)(CIN * 2) + 16u * (uint32_t)q;                       \
+      _Pragma("unroll") for (int ks_ = 0; ks_ < KS; ++ks_)                                               \
+          areg[SET][mt_ * KS + ks_] = buffer_row16(rows, at_ + 64u * (uint32_t)ks_);                     \
+    } else {                                                                                             \
+      const uint16_t* src_ = (j_ >= 0 ? in + (int64_t)j_ * CIN : zrow) + 8 * q;                          \
+      _Pragma("unroll") for (int ks_ = 0; ks_ < KS; ++ks_)                                               \
+          areg[SET][mt_ * KS + ks_] = *reinterpret_cast<const u32x4*>(src_ + 32 * ks_);                  \
+    }                                                                                                    \
   }                                                                                                      \
   }
 #define EMC2_W_LOAD(TAP, SET)                                                                            \
@@ -291,14 +309,20 @@ void launch_direct(const void* d_in, const void* d_wp, const float* d_scale, con
   // against 127 us), so it is used only where the grid would be several times kDGrid; the grid is then kDGrid blocks
   // (32 -> 64 over 573 k rows 97 -> 80 us, over 852 k 119 -> 109).
   const int64_t blocks = emc2_div_up(emc2_div_up(capacity_out, rows_per_block), 8) * 8;
-  if (blocks <= 4 * kDGrid)
-    hipLaunchKernelGGL((k_spconv_direct<DT, CIN, COUT, false>), dim3((unsigned)blocks), dim3(kDThreads), 0, s,
-                       (const uint16_t*)d_in, (const u32x4*)d_wp, d_scale, d_shift, epilogue, d_nbr, d_n_out, capacity_out, n_in,
-                       dev_flags, (const uint16_t*)d_zero_row, (uint16_t*)d_out);
-  else
-    hipLaunchKernelGGL((k_spconv_direct<DT, CIN, COUT, true>), dim3((unsigned)kDGrid), dim3(kDThreads), 0, s,
-                       (const uint16_t*)d_in, (const u32x4*)d_wp, d_scale, d_shift, epilogue, d_nbr, d_n_out, capacity_out, n_in,
-                       dev_flags, (const uint16_t*)d_zero_row, (uint16_t*)d_out);
+#define LAUNCH(LOOP, BUF, BLOCKS)                                                                                             \
+  hipLaunchKernelGGL((k_spconv_direct<DT, CIN, COUT, LOOP, BUF>), dim3((unsigned)(BLOCKS)), dim3(kDThreads), 0, s,           \
+                     (const uint16_t*)d_in, (const u32x4*)d_wp, d_scale, d_shift, epilogue, d_nbr, d_n_out, capacity_out,     \
+                     n_in, dev_flags, (const uint16_t*)d_zero_row, (uint16_t*)d_out)
+  // Offsets into the input are 32-bit, and the absent neighbour's, 2^32 less a row, must lie at or beyond its end.
+  const bool buf = ((int64_t)n_in + 1) * CIN * 2 <= ((int64_t)1 << 32);
+  if (blocks <= 4 * kDGrid) {
+    if (buf) LAUNCH(false, true, blocks);
+    else LAUNCH(false, false, blocks);
+  } else {
+    if (buf) LAUNCH(true, true, kDGrid);
+    else LAUNCH(true, false, kDGrid);
+  }
+#undef LAUNCH
 }
 
 }  // namespace
