@@ -5,7 +5,8 @@
 // q = lane / 16), the 16 consecutive input channels 16q .. 16q+15 of row m of the tile, i.e. 16 contiguous bytes
 // of the feature row nbr[k][o_m]; a 64-channel int8 row is exactly the four lanes' 64 bytes, so ONE
 // global_load_dwordx4 per 16-row tile and tap is the A operand (half the bytes and half the cache lines of the
-// fp16 kernel, twice the multiply-accumulates per matrix instruction).  Absent neighbours read a zeroed row.
+// fp16 kernel, twice the multiply-accumulates per matrix instruction).  Absent neighbours read past the end of the input's buffer
+// descriptor, which yields zeros (4 GiB and more: a zeroed row).
 // LDS holds the weights of the current and the next tap in B-fragment order and a small tile that turns the
 // accumulator layout into whole 16-byte pieces of output rows.  Accumulation is exact (int32); the epilogue is
 // a fixed sequence of individually rounded fp32 operations, so results are bit-reproducible.
@@ -131,12 +132,20 @@ template <int CIN, int COUT> struct QCfg { static constexpr int MINW = (CIN == 6
 template <int F8> struct QAcc { typedef intx4 type; };
 template <> struct QAcc<1> { typedef floatx4 type; };
 
-template <int CIN, int COUT, int OUTQ, int F8>
+// Input rows through a buffer descriptor, as in the register-direct 16-bit kernel: zeros at or beyond its end.
+// Layers of a 64-beam frame with their quantiser: int8 138 -> 130 us, E4M3 (half as many points) 146 -> 143 us.
+__device__ __forceinline__ u32x4 buffer_row16(__amdgpu_buffer_rsrc_t rows, uint32_t byte) {
+  return __builtin_amdgcn_raw_buffer_load_b128(rows, (int)byte, 0, 0);
+}
+
+template <int CIN, int COUT, int OUTQ, int F8, bool BUF>
 __global__ void __launch_bounds__(kQThreads, (QCfg<CIN, COUT>::MINW))
 k_spconv_i8(const int8_t* __restrict__ in, const u32x4* __restrict__ wp, const float* __restrict__ mul,
             const float* __restrict__ add, int relu, float inv_out_scale, const int32_t* __restrict__ nbr,
             const int32_t* __restrict__ d_n_out, int64_t capacity_out, int32_t n_in, int32_t* __restrict__ dev_flags,
             const int8_t* __restrict__ zrow, void* __restrict__ out) {
+  const __amdgpu_buffer_rsrc_t rows =
+      __builtin_amdgcn_make_buffer_rsrc((void*)const_cast<int8_t*>(in), 0, BUF ? (int)((uint32_t)n_in * CIN) : 0, 0x00020000);
   constexpr int KS = CIN / 64;                // k-steps per tap
   constexpr int NT = COUT / 16;               // 16-column tiles
   constexpr int MT = 4;                       // 16-row tiles per wave
@@ -190,16 +199,23 @@ k_spconv_i8(const int8_t* __restrict__ in, const u32x4* __restrict__ wp, const f
   // lane-swap instructions broadcast each 16-lane row of the entries to all four rows.
 #define EMC2_A_LOAD(JROW, SET)                                                                           \
   {                                                                                                      \
-    const uint32_t jr_ = (uint32_t)(JROW);                                                               \
+    const uint32_t jr_ = (uint32_t)max((JROW), -1);   /* any negative entry is an absent neighbour */    \
     const u32x2 h_ = __builtin_amdgcn_permlane32_swap(jr_, jr_, false, false);       /* 0101 | 2323 */   \
     const u32x2 lo_ = __builtin_amdgcn_permlane16_swap(h_[0], h_[0], false, false);  /* 0000 | 1111 */   \
     const u32x2 hi_ = __builtin_amdgcn_permlane16_swap(h_[1], h_[1], false, false);  /* 2222 | 3333 */   \
     const int32_t jm_[4] = {(int32_t)lo_[0], (int32_t)lo_[1], (int32_t)hi_[0], (int32_t)hi_[1]};         \
   _Pragma("unroll") for (int mt_ = 0; mt_ < MT; ++mt_) {                                                 \
     const int32_t j_ = jm_[mt_];                                                                         \
-    const int8_t* src_ = (j_ >= 0 ? in + (int64_t)j_ * CIN : zrow) + 16 * q;                             \
-    _Pragma("unroll") for (int ks_ = 0; ks_ < KS; ++ks_)                                                 \
-        areg[SET][mt_ * KS + ks_] = *reinterpret_cast<const u32x4*>(src_ + 64 * ks_);                    \
+    if constexpr (BUF) {                                                                                 \
+      /* absent: 2^32 less a row, and a piece of the row: out of range, zero */                          \
+      const uint32_t at_ = (uint32_t)j_ * (uint32_t)CIN + 16u * (uint32_t)q;                             \
+      _Pragma("unroll") for (int ks_ = 0; ks_ < KS; ++ks_)                                               \
+          areg[SET][mt_ * KS + ks_] = buffer_row16(rows, at_ + 64u * (uint32_t)ks_);                     \
+    } else {                                                                                             \
+      const int8_t* src_ = (j_ >= 0 ? in + (int64_t)j_ * CIN : zrow) + 16 * q;                           \
+      _Pragma("unroll") for (int ks_ = 0; ks_ < KS; ++ks_)                                               \
+          areg[SET][mt_ * KS + ks_] = *reinterpret_cast<const u32x4*>(src_ + 64 * ks_);                  \
+    }                                                                                                    \
   }                                                                                                      \
   }
 #define EMC2_W_LOAD(TAP, SET)                                                                            \
@@ -324,9 +340,14 @@ void launch_i8(const void* d_in, const void* d_wp, const float* d_mul, const flo
                const int32_t* d_nbr, const int32_t* d_n_out, int64_t capacity_out, int32_t n_in, int32_t* dev_flags,
                const void* d_zero_row, void* d_out, hipStream_t s) {
   const int64_t rows_per_block = kQWaves * 64;
-  hipLaunchKernelGGL((k_spconv_i8<CIN, COUT, OUTQ, F8>), dim3((unsigned)(emc2_div_up(capacity_out, rows_per_block) + 8)),
-                     dim3(kQThreads), 0, s, (const int8_t*)d_in, (const u32x4*)d_wp, d_mul, d_add, relu, inv_out_scale, d_nbr,
-                     d_n_out, capacity_out, n_in, dev_flags, (const int8_t*)d_zero_row, d_out);
+#define LAUNCH(BUF)                                                                                                           \
+  hipLaunchKernelGGL((k_spconv_i8<CIN, COUT, OUTQ, F8, BUF>), dim3((unsigned)(emc2_div_up(capacity_out, rows_per_block) + 8)), \
+                     dim3(kQThreads), 0, s, (const int8_t*)d_in, (const u32x4*)d_wp, d_mul, d_add, relu, inv_out_scale, d_nbr, \
+                     d_n_out, capacity_out, n_in, dev_flags, (const int8_t*)d_zero_row, d_out)
+  // Offsets into the input are 32-bit, and the absent neighbour's, 2^32 less a row, must lie at or beyond its end.
+  if (((int64_t)n_in + 1) * CIN <= ((int64_t)1 << 32)) LAUNCH(true);
+  else LAUNCH(false);
+#undef LAUNCH
 }
 
 bool i8_shape_ok(int cin, int cout) { return (cin == 64 || cin == 128) && (cout == 32 || cout == 64); }
