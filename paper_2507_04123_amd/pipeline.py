@@ -84,11 +84,10 @@ class NativePass:
     """The maps and the convolutions of one or more branches over the same points as two native calls: emc2_build_stacks
     (voxelization and every kernel map of every branch, in a handful of launches) and emc2_spconv_list.  The argument
     blocks are filled and checked once, and again by the first pass that finds a runner's context or one of its buffers
-    replaced; every pass sets the points and frame ids.  The runners are handed in by each call (they own their passes).
-    `route`: (expert, slot) tensors of a routed batch, branch e then takes the scenes of expert e."""
+    replaced; every pass sets the points and frame ids.  The runners are handed in by each call (they own their passes),
+    and so is `route`: the (expert, slot) tensors of a routed batch, branch e then takes the scenes of expert e."""
 
-    def __init__(self, route: Optional[Tuple[torch.Tensor, torch.Tensor]] = None):
-        self.route = route
+    def __init__(self):
         self.stacks = self.calls = None
         self.stacks_of = self.calls_of = None      # addresses the blocks were filled from
         self.held: Tuple[torch.Tensor, ...] = ()   # the tensors behind the calls' addresses
@@ -97,15 +96,15 @@ class NativePass:
     def covers(runners: Sequence["BranchRunner"]) -> bool:
         return len(runners) <= B.MAX_STACKS and all(len(r.levels) <= B.STACK_MAX_LEVELS for r in runners)
 
-    def _fill_stacks(self, runners: Sequence["BranchRunner"]) -> None:
+    def _fill_stacks(self, runners: Sequence["BranchRunner"], route: Optional[Tuple[torch.Tensor, torch.Tensor]]) -> None:
         stacks = (B.StackC * len(runners))()
         for e, r in enumerate(runners):
             s, sp = stacks[e], r.branch.spec
             s.ctx = r.ctx.h
             s.spec = B.voxel_spec_c(sp, 4)
-            s.expert, s.n_levels = (-1 if self.route is None else e), len(r.levels)
-            if self.route is not None:
-                s.d_route, s.d_slot = self.route[0].data_ptr(), self.route[1].data_ptr()
+            s.expert, s.n_levels = (-1 if route is None else e), len(r.levels)
+            if route is not None:
+                s.d_route, s.d_slot = route[0].data_ptr(), route[1].data_ptr()
             s.d_feats, s.d_counts = r.feats32.data_ptr(), r.counts.data_ptr()
             s.lp_dtype = r.dtype if r.feats_lp is not None else F16
             s.d_feats_lp = r.feats_lp.data_ptr() if r.feats_lp is not None else None
@@ -115,11 +114,12 @@ class NativePass:
                 c.d_down_nbr = lv.down_nbr.data_ptr() if lv.down_nbr is not None else None
         self.stacks = stacks
 
-    def maps(self, runners: Sequence["BranchRunner"], points: torch.Tensor, batch: Optional[torch.Tensor]) -> None:
-        of = [a for r in runners for a in r.map_addresses()]
+    def maps(self, runners: Sequence["BranchRunner"], points: torch.Tensor, batch: Optional[torch.Tensor],
+             route: Optional[Tuple[torch.Tensor, torch.Tensor]] = None) -> None:
+        of = [a for r in runners for a in r.map_addresses()] + [t.data_ptr() for t in route or ()]
         if of != self.stacks_of:
             self.stacks_of = None
-            self._fill_stacks(runners)
+            self._fill_stacks(runners, route)
             self.stacks_of = of
         if batch is not None:
             if not batch.is_cuda or batch.dtype != torch.int32 or not batch.is_contiguous() or batch.numel() != points.shape[0]:
@@ -139,8 +139,9 @@ class NativePass:
         B.spconv_list(self.calls, len(self.calls))
         return [r.acts[-1] if r.acts else r.conv_input() for r in runners]
 
-    def run(self, runners: Sequence["BranchRunner"], points: torch.Tensor, batch: Optional[torch.Tensor]) -> List[torch.Tensor]:
-        self.maps(runners, points, batch)
+    def run(self, runners: Sequence["BranchRunner"], points: torch.Tensor, batch: Optional[torch.Tensor],
+            route: Optional[Tuple[torch.Tensor, torch.Tensor]] = None) -> List[torch.Tensor]:
+        self.maps(runners, points, batch, route)
         return self.convs(runners)
 
 
@@ -686,7 +687,7 @@ class RoutedRunner:
             self.runners.append((ctx, BranchRunner(ctx, br, dtype, n_points, device_params(br.layers, seed + e, dtype),
                                                    capacities=caps, device=device)))
         assert NativePass.covers([r for _, r in self.runners])
-        self.native = NativePass(route=(self.expert, self.slot))
+        self.native = NativePass()
 
     def close(self) -> None:
         for ctx, _ in self.runners:
@@ -720,4 +721,4 @@ class RoutedRunner:
         ctx0 = self.runners[0][0]
         ctx0.dispatch(props, prop_scene, self.n_scenes, dist, conf, self.expert, self.counts, self.order)
         ctx0.group_slots(self.expert, self.order, self.counts, self.n_scenes, self.slot)
-        return self.native.run([r for _, r in self.runners], points, scene)
+        return self.native.run([r for _, r in self.runners], points, scene, route=(self.expert, self.slot))

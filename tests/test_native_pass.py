@@ -1,0 +1,78 @@
+"""Argument blocks of a native pass without a GPU: host tensors stand in for device buffers and the two native calls record
+what they are handed, so what a pass passes on, keeps and refuses can be seen."""
+import ctypes
+import os
+import sys
+
+import pytest
+import torch
+
+sys.path.insert(0, os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
+
+from paper_2507_04123_amd import binding as B  # noqa: E402
+from paper_2507_04123_amd import pipeline as P  # noqa: E402
+from paper_2507_04123_amd.configs import F16, Branch, Layer, STRIDED, SUBM, VoxelSpec  # noqa: E402
+
+
+class _Ctx:
+    """What a runner asks of its context."""
+    made = 0
+
+    def __init__(self, *a, **k):
+        _Ctx.made += 1
+        self.h = ctypes.c_void_p(4096 * _Ctx.made)
+        self.calls = []
+
+    def uses_mfma(self, dtype, cin, cout):
+        return False
+
+    def __getattr__(self, name):
+        return lambda *a, **k: self.calls.append((name, a, k))
+
+
+@pytest.fixture
+def native(monkeypatch):
+    """The stacks and convolution calls of every pass, copied when they are issued."""
+    seen = {"stacks": [], "convs": []}
+
+    def check(t, dtype, name):
+        if getattr(t, "on_host", False) or t.dtype != dtype or not t.is_contiguous():
+            raise ValueError(f"{name}: need a contiguous {dtype} device tensor")
+
+    monkeypatch.setattr(B, "_dev_check", check)
+    monkeypatch.setattr(B, "Context", _Ctx)
+    monkeypatch.setattr(B, "build_stacks", lambda st, n, pts: seen["stacks"].append((B.StackC * n).from_buffer_copy(st)))
+    monkeypatch.setattr(B, "spconv_list", lambda c, n: seen["convs"].append((B.ConvCallC * n).from_buffer_copy(c)))
+    return seen
+
+
+def _branch(n_levels=2, nb=2):
+    layers = [Layer(SUBM, 4, 16)]
+    for _ in range(n_levels - 1):
+        layers += [Layer(STRIDED, 16, 16), Layer(SUBM, 16, 16)]
+    return Branch("b", VoxelSpec((0.0, 0.0, 0.0), (1.0, 1.0, 1.0), (32, 16, 8), nb), tuple(layers))
+
+
+def _routed(n_levels=2, n=64):
+    rr = P.RoutedRunner([_branch(n_levels) for _ in range(3)], F16, n, 2, seed=1, device="cpu")
+    args = (torch.zeros((n, 4)), None, torch.zeros((1, 4)), None, 23.5, 0.5)
+    return rr, args
+
+
+@pytest.fixture(autouse=True)
+def _host_params(monkeypatch):
+    real = P.device_params
+    monkeypatch.setattr(P, "device_params", lambda layers, seed, dtype: real(layers, seed, dtype, device="cpu"))
+
+
+def test_routed_pass_hands_on_the_routing_it_holds(native):
+    """The stacks are routed by the tensors that this pass's dispatcher and grouping write, not by an earlier pass's."""
+    rr, args = _routed()
+    rr.run(*args)
+    kept = rr.expert, rr.slot                    # an earlier pass's routing, kept by the caller
+    for name in ("expert", "slot"):
+        setattr(rr, name, torch.zeros_like(getattr(rr, name)))
+        rr.run(*args)
+        for s in native["stacks"][-1]:
+            assert (s.d_route, s.d_slot) == (rr.expert.data_ptr(), rr.slot.data_ptr())
+    assert native["stacks"][0][0].d_route == kept[0].data_ptr() != rr.expert.data_ptr()
