@@ -164,6 +164,12 @@ def _dev_check(t: torch.Tensor, dtype: torch.dtype, name: str) -> None:
         raise ValueError(f"{name}: need a contiguous {dtype} device tensor, got {t.dtype} on {t.device}")
 
 
+def tensor_key(t: Optional[torch.Tensor]):
+    """What a call is told of a tensor, and what the checks here look at: arguments filled from a tensor hold for another
+    one with the same key, and for no other."""
+    return None if t is None else (t.data_ptr(), t.shape, t.dtype, t.is_cuda, t.is_contiguous())
+
+
 STATIC_KMAP_MAX_CELLS = 1 << 24
 
 

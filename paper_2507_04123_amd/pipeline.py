@@ -83,14 +83,14 @@ def capture_stream(device) -> "torch.cuda.Stream":
 class NativePass:
     """The maps and the convolutions of one or more branches over the same points as two native calls: emc2_build_stacks
     (voxelization and every kernel map of every branch, in a handful of launches) and emc2_spconv_list.  The argument
-    blocks are filled and checked once, and again by the first pass that finds a runner's context or one of its buffers
-    replaced; every pass sets the points and frame ids.  The runners are handed in by each call (they own their passes),
+    blocks are filled and checked once, and again by the first pass that finds anything that went into them changed: a
+    context, a capacity, a slot, the layers, a weight layout, or a tensor's address, shape, type, place or contiguity.  Every pass sets the points and frame ids.  The runners are handed in by each call (they own their passes),
     and so is `route`: the (expert, slot) tensors of a routed batch, branch e then takes the scenes of expert e."""
 
     def __init__(self):
         self.stacks = self.calls = None
-        self.stacks_of = self.calls_of = None      # addresses the blocks were filled from
-        self.held: Tuple[torch.Tensor, ...] = ()   # the tensors behind the calls' addresses
+        self.stacks_of = self.calls_of = None      # what the blocks were filled from
+        self.held: Tuple[Optional[torch.Tensor], ...] = ()   # the tensors behind the calls' addresses
 
     @staticmethod
     def covers(runners: Sequence["BranchRunner"]) -> bool:
@@ -116,7 +116,7 @@ class NativePass:
 
     def maps(self, runners: Sequence["BranchRunner"], points: torch.Tensor, batch: Optional[torch.Tensor],
              route: Optional[Tuple[torch.Tensor, torch.Tensor]] = None) -> None:
-        of = [a for r in runners for a in r.map_addresses()] + [t.data_ptr() for t in route or ()]
+        of = [v for r in runners for v in r.map_key()] + [B.tensor_key(t) for t in route or ()]
         if of != self.stacks_of:
             self.stacks_of = None
             self._fill_stacks(runners, route)
@@ -130,7 +130,7 @@ class NativePass:
 
     def convs(self, runners: Sequence["BranchRunner"]) -> List[torch.Tensor]:
         held = [t for r in runners for t in r.conv_tensors()]
-        of = [v for r in runners for v in (r.ctx.h.value if r.ctx.h else None, r.branch.layers)] + [t.data_ptr() for t in held]
+        of = [v for r in runners for v in r.conv_key()] + [B.tensor_key(t) for t in held]
         if of != self.calls_of:
             self.calls_of = None
             calls = [c for r in runners for c in r.conv_calls()]
@@ -209,22 +209,26 @@ class BranchRunner:
     def conv_input(self) -> torch.Tensor:
         return self.feats32 if self.dtype == F32 else self.feats_lp
 
-    def map_addresses(self) -> list:
-        """The context, the grid and every buffer that voxelization and the kernel maps write (None where there is none)."""
-        out = [self.ctx.h.value if self.ctx.h else None, self.branch.spec, self.feats32.data_ptr(), self.counts.data_ptr(),
-               self.feats_lp.data_ptr() if self.feats_lp is not None else None]
+    def map_key(self) -> list:
+        """Everything that voxelization and the kernel maps are told of this branch, the points and frame ids apart."""
+        k = B.tensor_key
+        out = [self.ctx.h.value if self.ctx.h else None, self.dtype, self.branch.spec, k(self.feats32), k(self.counts), k(self.feats_lp)]
         for lv in self.levels:
-            out += [lv.cap, lv.slot, lv.coords.data_ptr(), lv.n.data_ptr(), lv.subm_nbr.data_ptr() if lv.subm_nbr is not None else None,
-                    lv.down_nbr.data_ptr() if lv.down_nbr is not None else None]
+            out += [lv.cap, lv.slot, k(lv.coords), k(lv.n), k(lv.subm_nbr), k(lv.down_nbr)]
         return out
 
-    def conv_tensors(self) -> List[torch.Tensor]:
-        """Every tensor that the convolutions read or write."""
+    def conv_key(self) -> list:
+        """Everything but the tensors that the convolutions are told of this branch."""
+        return [self.ctx.h.value if self.ctx.h else None, self.dtype, self.branch.layers, [lay for _, lay in self.wdev],
+                [lv.cap for lv in self.levels]]
+
+    def conv_tensors(self) -> List[Optional[torch.Tensor]]:
+        """Every tensor that the convolutions read or write (None where a level has no such map)."""
         out = [self.conv_input(), *self.acts]
         for (w, _), p, layer in zip(self.wdev, self.params, self.branch.layers):
             out += [w, p["scale"], p["shift"]] if layer.epilogue != EPI_NONE else [w]
         for lv in self.levels:
-            out += [t for t in (lv.n, lv.subm_nbr, lv.down_nbr) if t is not None]
+            out += [lv.n, lv.subm_nbr, lv.down_nbr]
         return out
 
     def conv_calls(self) -> List["B.ConvCallC"]:

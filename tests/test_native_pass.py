@@ -76,3 +76,41 @@ def test_routed_pass_hands_on_the_routing_it_holds(native):
         for s in native["stacks"][-1]:
             assert (s.d_route, s.d_slot) == (rr.expert.data_ptr(), rr.slot.data_ptr())
     assert native["stacks"][0][0].d_route == kept[0].data_ptr() != rr.expert.data_ptr()
+
+
+def _same(a, b):
+    return bytes(a) == bytes(b)
+
+
+def test_kept_blocks_follow_everything_that_went_into_them(native):
+    """A level's capacity is the pitch of its maps for the stacks and for the convolutions; rows, layouts and types count as
+    addresses do; what has not changed is not filled again."""
+    r = P.BranchRunner(_Ctx(), _branch(), F16, 64, P.device_params(_branch().layers, 1, F16), device="cpu")
+    pts = torch.zeros((64, 4))
+
+    def both():
+        r.run(pts, None)
+        return native["stacks"][-1][0], native["convs"][-1]
+
+    s0, c0 = both()
+    blocks = r.native.calls
+    s1, c1 = both()
+    assert _same(s0, s1) and _same(c0, c1) and r.native.calls is blocks
+    r.levels[1].cap -= 5
+    s1, c1 = both()
+    assert s1.level[1].capacity == s0.level[1].capacity - 5
+    assert [c.capacity_out for c in c1] == [c0[0].capacity_out, c0[1].capacity_out - 5, c0[2].capacity_out - 5]
+    r.levels[1].cap += 5
+    full, r.acts[0] = r.acts[0], r.acts[0][:40]            # the same address, fewer rows that a map entry may name
+    with pytest.raises(ValueError, match="smaller than capacity"):
+        r.run(pts, None)                                   # it is also an output of 64 rows
+    r.acts[0] = full
+    r.feats_lp, full = r.feats_lp[:40], r.feats_lp
+    assert r.native.convs((r,)) and native["convs"][-1][0].n_in_rows == 40
+    r.feats_lp = full
+    r.wdev[2] = (r.wdev[2][0], B.W_PACKED)
+    assert [c.w_layout for c in both()[1]] == [B.W_PLAIN, B.W_PLAIN, B.W_PACKED]
+    r.acts[1] = r.acts[1].view(torch.bfloat16)             # the same address, another type
+    for _ in range(2):
+        with pytest.raises(ValueError, match="out"):
+            r.run(pts, None)
