@@ -181,6 +181,49 @@ def build_kmap_static(kind: int, in_coords: torch.Tensor, n_in: torch.Tensor, ca
     if not torch.cuda.is_available():
         raise RuntimeError("emc2 needs a GPU: there is no CPU path")
     lib = load_library()
+    check_kmap(in_coords, n_in, capacity_in, nbr, n_out, capacity_out, out_coords)
+    if status is not None:
+        _dev_check(status, torch.int32, "status")
+    g_in = (ctypes.c_int32 * 3)(*grid_in)
+    g_out = (ctypes.c_int32 * 3)()
+    st = lib.emc2_build_kmap_static(kind, _ptr(in_coords), _ptr(n_in), capacity_in, g_in, n_batch, capacity_out,
+                                    _ptr(out_coords), _ptr(n_out), _ptr(nbr), g_out, _ptr(status), _stream())
+    if st != OK:
+        raise Emc2Error(st, lib.emc2_last_error(None).decode())
+    return g_out[0], g_out[1], g_out[2]
+
+
+def check_points(points: torch.Tensor, batch: Optional[torch.Tensor]) -> Tuple[int, int]:
+    """(number of points, floats per point) of what is voxelized."""
+    _dev_check(points, torch.float32, "points")
+    n, stride = (points.shape[0], points.shape[1]) if points.dim() == 2 else (0, 4)
+    if batch is not None:
+        _dev_check(batch, torch.int32, "batch")
+        if batch.numel() != n:
+            raise ValueError("batch length != number of points")
+    return n, stride
+
+
+def check_voxels(capacity: int, coords: torch.Tensor, feats: torch.Tensor, counts: torch.Tensor, n_voxels: torch.Tensor,
+                 feats_lp: Optional[torch.Tensor]) -> int:
+    """What the library cannot see of a voxelization's outputs (devices, types, sizes); returns the type of the copy."""
+    _dev_check(coords, torch.int32, "coords")
+    _dev_check(feats, torch.float32, "feats")
+    _dev_check(counts, torch.int32, "counts")
+    _dev_check(n_voxels, torch.int32, "n_voxels")
+    if coords.numel() < 4 * capacity or feats.numel() < 4 * capacity or counts.numel() < capacity:
+        raise ValueError("output buffers smaller than capacity")
+    if feats_lp is None:
+        return F16
+    lp_dtype = {torch.float16: F16, torch.bfloat16: BF16}[feats_lp.dtype]
+    if feats_lp.numel() < 4 * capacity or not feats_lp.is_cuda:
+        raise ValueError("feats_lp smaller than capacity")
+    return lp_dtype
+
+
+def check_kmap(in_coords: torch.Tensor, n_in: torch.Tensor, capacity_in: int, nbr: torch.Tensor, n_out: torch.Tensor,
+               capacity_out: int, out_coords: Optional[torch.Tensor]) -> None:
+    """What the library cannot see of a kernel map's arguments."""
     _dev_check(in_coords, torch.int32, "in_coords")
     _dev_check(n_in, torch.int32, "n_in")
     _dev_check(nbr, torch.int32, "nbr")
@@ -191,15 +234,6 @@ def build_kmap_static(kind: int, in_coords: torch.Tensor, n_in: torch.Tensor, ca
         _dev_check(out_coords, torch.int32, "out_coords")
         if out_coords.numel() < 4 * capacity_out:
             raise ValueError("out_coords smaller than capacity_out")
-    if status is not None:
-        _dev_check(status, torch.int32, "status")
-    g_in = (ctypes.c_int32 * 3)(*grid_in)
-    g_out = (ctypes.c_int32 * 3)()
-    st = lib.emc2_build_kmap_static(kind, _ptr(in_coords), _ptr(n_in), capacity_in, g_in, n_batch, capacity_out,
-                                    _ptr(out_coords), _ptr(n_out), _ptr(nbr), g_out, _ptr(status), _stream())
-    if st != OK:
-        raise Emc2Error(st, lib.emc2_last_error(None).decode())
-    return g_out[0], g_out[1], g_out[2]
 
 
 def check_conv(dtype: int, x: torch.Tensor, w: torch.Tensor, scale: Optional[torch.Tensor], shift: Optional[torch.Tensor],
@@ -225,9 +259,8 @@ def check_conv(dtype: int, x: torch.Tensor, w: torch.Tensor, scale: Optional[tor
 
 
 def build_stacks(stacks, n_stacks: int, points: torch.Tensor) -> None:
-    """emc2_build_stacks over a ctypes array of StackC whose buffers the caller keeps alive."""
-    _dev_check(points, torch.float32, "points")
-    n, stride = (points.shape[0], points.shape[1]) if points.dim() == 2 else (0, 4)
+    """emc2_build_stacks over a ctypes array of StackC whose buffers and frame ids the caller has checked and keeps alive."""
+    n, stride = check_points(points, None)
     for i in range(n_stacks):
         stacks[i].spec.stride_f = stride
     lib = load_library()
@@ -281,23 +314,8 @@ class Context:
     def voxelize(self, points: torch.Tensor, batch: Optional[torch.Tensor], spec: VoxelSpec, capacity: int,
                  coords: torch.Tensor, feats: torch.Tensor, counts: torch.Tensor, n_voxels: torch.Tensor,
                  feats_lp: Optional[torch.Tensor] = None, index_slot: int = 0, sync_count: bool = False) -> Optional[int]:
-        _dev_check(points, torch.float32, "points")
-        _dev_check(coords, torch.int32, "coords")
-        _dev_check(feats, torch.float32, "feats")
-        _dev_check(counts, torch.int32, "counts")
-        _dev_check(n_voxels, torch.int32, "n_voxels")
-        n, stride = (points.shape[0], points.shape[1]) if points.dim() == 2 else (0, 4)
-        if coords.numel() < 4 * capacity or feats.numel() < 4 * capacity or counts.numel() < capacity:
-            raise ValueError("output buffers smaller than capacity")
-        if batch is not None:
-            _dev_check(batch, torch.int32, "batch")
-            if batch.numel() != n:
-                raise ValueError("batch length != number of points")
-        lp_dtype = F16
-        if feats_lp is not None:
-            lp_dtype = {torch.float16: F16, torch.bfloat16: BF16}[feats_lp.dtype]
-            if feats_lp.numel() < 4 * capacity or not feats_lp.is_cuda:
-                raise ValueError("feats_lp smaller than capacity")
+        n, stride = check_points(points, batch)
+        lp_dtype = check_voxels(capacity, coords, feats, counts, n_voxels, feats_lp)
         cs = voxel_spec_c(spec, stride)
         h_n = ctypes.c_int32(0)
         self._chk(self.lib.emc2_voxelize(self.h, _ptr(points), _ptr(batch), n, ctypes.byref(cs), capacity, _ptr(coords),
@@ -309,16 +327,7 @@ class Context:
                    n_batch: int, capacity_out: int, nbr: torch.Tensor, n_out: torch.Tensor,
                    out_coords: Optional[torch.Tensor] = None, in_slot: int = -1, out_slot: int = -1,
                    sync_count: bool = False) -> Tuple[Tuple[int, int, int], Optional[int]]:
-        _dev_check(in_coords, torch.int32, "in_coords")
-        _dev_check(n_in, torch.int32, "n_in")
-        _dev_check(nbr, torch.int32, "nbr")
-        _dev_check(n_out, torch.int32, "n_out")
-        if in_coords.numel() < 4 * capacity_in or nbr.numel() < 27 * capacity_out:
-            raise ValueError("buffers smaller than capacity")
-        if out_coords is not None:
-            _dev_check(out_coords, torch.int32, "out_coords")
-            if out_coords.numel() < 4 * capacity_out:
-                raise ValueError("out_coords smaller than capacity_out")
+        check_kmap(in_coords, n_in, capacity_in, nbr, n_out, capacity_out, out_coords)
         g_in = (ctypes.c_int32 * 3)(*grid_in)
         g_out = (ctypes.c_int32 * 3)()
         h_n = ctypes.c_int32(0)

@@ -99,14 +99,14 @@ class NativePass:
     def _fill_stacks(self, runners: Sequence["BranchRunner"], route: Optional[Tuple[torch.Tensor, torch.Tensor]]) -> None:
         stacks = (B.StackC * len(runners))()
         for e, r in enumerate(runners):
-            s, sp = stacks[e], r.branch.spec
+            s, sp, lp_dtype = stacks[e], r.branch.spec, r.check_maps()
             s.ctx = r.ctx.h
             s.spec = B.voxel_spec_c(sp, 4)
             s.expert, s.n_levels = (-1 if route is None else e), len(r.levels)
             if route is not None:
                 s.d_route, s.d_slot = route[0].data_ptr(), route[1].data_ptr()
             s.d_feats, s.d_counts = r.feats32.data_ptr(), r.counts.data_ptr()
-            s.lp_dtype = r.dtype if r.feats_lp is not None else F16
+            s.lp_dtype = lp_dtype
             s.d_feats_lp = r.feats_lp.data_ptr() if r.feats_lp is not None else None
             for c, lv in zip(s.level, r.levels):
                 c.capacity, c.d_coords, c.d_n, c.slot = lv.cap, lv.coords.data_ptr(), lv.n.data_ptr(), lv.slot
@@ -116,14 +116,12 @@ class NativePass:
 
     def maps(self, runners: Sequence["BranchRunner"], points: torch.Tensor, batch: Optional[torch.Tensor],
              route: Optional[Tuple[torch.Tensor, torch.Tensor]] = None) -> None:
+        B.check_points(points, batch)
         of = [v for r in runners for v in r.map_key()] + [B.tensor_key(t) for t in route or ()]
         if of != self.stacks_of:
             self.stacks_of = None
             self._fill_stacks(runners, route)
             self.stacks_of = of
-        if batch is not None:
-            if not batch.is_cuda or batch.dtype != torch.int32 or not batch.is_contiguous() or batch.numel() != points.shape[0]:
-                raise ValueError("batch: need a contiguous int32 device tensor with one id per point")
         for s in self.stacks:
             s.d_batch = batch.data_ptr() if batch is not None else None
         B.build_stacks(self.stacks, len(runners), points)
@@ -214,8 +212,23 @@ class BranchRunner:
         k = B.tensor_key
         out = [self.ctx.h.value if self.ctx.h else None, self.dtype, self.branch.spec, k(self.feats32), k(self.counts), k(self.feats_lp)]
         for lv in self.levels:
-            out += [lv.cap, lv.slot, k(lv.coords), k(lv.n), k(lv.subm_nbr), k(lv.down_nbr)]
+            out += [lv.cap, lv.slot, lv.grid, k(lv.coords), k(lv.n), k(lv.subm_nbr), k(lv.down_nbr)]
         return out
+
+    def check_maps(self) -> int:
+        """The checks of Context.voxelize and Context.build_kmap for every level; returns the type of the means' copy."""
+        l0 = self.levels[0]
+        lp_dtype = B.check_voxels(l0.cap, l0.coords, self.feats32, self.counts, l0.n, self.feats_lp)
+        grid = tuple(self.branch.spec.grid)
+        for i, lv in enumerate(self.levels):
+            if i:
+                src, grid = self.levels[i - 1], out_grid(grid)
+                B.check_kmap(src.coords, src.n, src.cap, lv.down_nbr, lv.n, lv.cap, lv.coords)
+            if lv.subm_nbr is not None:
+                B.check_kmap(lv.coords, lv.n, lv.cap, lv.subm_nbr, lv.n, lv.cap, None)
+            if tuple(lv.grid) != grid and (lv.subm_nbr is not None or i + 1 < len(self.levels)):
+                raise B.Emc2Error(B.ERR_INVALID_ARG, f"level {i}: grid {tuple(lv.grid)}, but its voxel spec makes it {grid}")
+        return lp_dtype
 
     def conv_key(self) -> list:
         """Everything but the tensors that the convolutions are told of this branch."""

@@ -1,5 +1,5 @@
-"""Argument blocks of a native pass without a GPU: host tensors stand in for device buffers and the two native calls record
-what they are handed, so what a pass passes on, keeps and refuses can be seen."""
+"""Argument blocks of a native pass without a GPU: host tensors that call themselves device tensors stand in for the buffers,
+and the two native calls record what they are handed, so what a pass passes on, keeps and refuses can be seen."""
 import ctypes
 import os
 import sys
@@ -12,6 +12,27 @@ sys.path.insert(0, os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
 from paper_2507_04123_amd import binding as B  # noqa: E402
 from paper_2507_04123_amd import pipeline as P  # noqa: E402
 from paper_2507_04123_amd.configs import F16, Branch, Layer, STRIDED, SUBM, VoxelSpec  # noqa: E402
+
+
+class _Dev(torch.Tensor):
+    is_cuda = True
+
+
+def _dev(t):
+    return None if t is None else t.as_subclass(_Dev)
+
+
+def _on_device(r):
+    """The runner with every buffer on the "device"."""
+    for name in ("feats32", "counts", "feats_lp"):
+        setattr(r, name, _dev(getattr(r, name)))
+    for lv in r.levels:
+        for name in ("coords", "n", "subm_nbr", "down_nbr"):
+            setattr(lv, name, _dev(getattr(lv, name)))
+    r.acts = [_dev(t) for t in r.acts]
+    r.wdev = [(_dev(w), lay) for w, lay in r.wdev]
+    r.params = [{k: _dev(t) for k, t in p.items()} for p in r.params]
+    return r
 
 
 class _Ctx:
@@ -34,12 +55,6 @@ class _Ctx:
 def native(monkeypatch):
     """The stacks and convolution calls of every pass, copied when they are issued."""
     seen = {"stacks": [], "convs": []}
-
-    def check(t, dtype, name):
-        if getattr(t, "on_host", False) or t.dtype != dtype or not t.is_contiguous():
-            raise ValueError(f"{name}: need a contiguous {dtype} device tensor")
-
-    monkeypatch.setattr(B, "_dev_check", check)
     monkeypatch.setattr(B, "Context", _Ctx)
     monkeypatch.setattr(B, "build_stacks", lambda st, n, pts: seen["stacks"].append((B.StackC * n).from_buffer_copy(st)))
     monkeypatch.setattr(B, "spconv_list", lambda c, n: seen["convs"].append((B.ConvCallC * n).from_buffer_copy(c)))
@@ -55,8 +70,14 @@ def _branch(n_levels=2, nb=2):
 
 def _routed(n_levels=2, n=64):
     rr = P.RoutedRunner([_branch(n_levels) for _ in range(3)], F16, n, 2, seed=1, device="cpu")
-    args = (torch.zeros((n, 4)), None, torch.zeros((1, 4)), None, 23.5, 0.5)
+    for _, r in rr.runners:
+        _on_device(r)
+    args = (_dev(torch.zeros((n, 4))), None, torch.zeros((1, 4)), None, 23.5, 0.5)
     return rr, args
+
+
+def _runner(n=64):
+    return _on_device(P.BranchRunner(_Ctx(), _branch(), F16, n, P.device_params(_branch().layers, 1, F16), device="cpu"))
 
 
 @pytest.fixture(autouse=True)
@@ -85,8 +106,7 @@ def _same(a, b):
 def test_kept_blocks_follow_everything_that_went_into_them(native):
     """A level's capacity is the pitch of its maps for the stacks and for the convolutions; rows, layouts and types count as
     addresses do; what has not changed is not filled again."""
-    r = P.BranchRunner(_Ctx(), _branch(), F16, 64, P.device_params(_branch().layers, 1, F16), device="cpu")
-    pts = torch.zeros((64, 4))
+    r, pts = _runner(), _dev(torch.zeros((64, 4)))
 
     def both():
         r.run(pts, None)
@@ -114,3 +134,47 @@ def test_kept_blocks_follow_everything_that_went_into_them(native):
     for _ in range(2):
         with pytest.raises(ValueError, match="out"):
             r.run(pts, None)
+
+
+def _host(t):
+    return t.as_subclass(torch.Tensor)
+
+
+# a buffer in turn: half its rows, another type of the same width, every second row of a larger one, on the host
+@pytest.mark.parametrize("name", ["feats32", "counts", "feats_lp", "coords", "n", "subm_nbr", "down_nbr"])
+def test_maps_refuse_buffers_they_would_write_out_of(native, name):
+    r, pts = _runner(), _dev(torch.zeros((64, 4)))
+    at = r if hasattr(r, name) else r.levels[1]
+    r.run_maps(pts, None)
+    good = getattr(at, name)
+    bad = [_host(good)]
+    if name != "n":
+        bad.append(good[: good.shape[0] // 2])
+    if name != "feats_lp":                                  # (its type may be either of two, and it may lie apart)
+        bad += [good.view(torch.float32 if good.dtype == torch.int32 else torch.int32), torch.cat([good, good])[::2]]
+        if name == "n":
+            bad.pop()                                       # one element is contiguous whatever its stride
+    issued = len(native["stacks"])
+    for t in bad:
+        setattr(at, name, t)
+        for _ in range(2):                                  # refused each time, not only by the pass that meets it first
+            with pytest.raises(ValueError):
+                r.run_maps(pts, None)
+        with pytest.raises(ValueError):
+            r.run(pts, None)
+    assert len(native["stacks"]) == issued
+    setattr(at, name, good)
+    r.run_maps(pts, None)
+
+
+def test_maps_refuse_frame_ids_and_grids_that_do_not_fit(native):
+    r, pts, ids = _runner(), _dev(torch.zeros((64, 4))), _dev(torch.zeros(64, dtype=torch.int32))
+    r.run_maps(pts, ids)
+    assert native["stacks"][-1][0].d_batch == ids.data_ptr()
+    for p, b in ((pts, ids[:63]), (pts, ids.long()), (pts, _host(ids)), (pts.view(-1), _dev(torch.zeros(256, dtype=torch.int32)))):
+        with pytest.raises(ValueError):
+            r.run_maps(p, b)
+    r.levels[1].grid = (1, 2, 3)
+    with pytest.raises(B.Emc2Error):
+        r.run_maps(pts, ids)
+    assert len(native["stacks"]) == 1
