@@ -150,10 +150,10 @@ emc2_status emc2_build_kmap(emc2_ctx* ctx, emc2_conv_kind kind, const int32_t* d
  * out_slot = the levels' slots) would leave in them, in 6 to 8 launches altogether instead of 6 per level and map.
  *   level[0].d_down_nbr must be NULL (nothing lies below it); level[l].d_down_nbr is the stride-2 map from level l - 1 into
  *   level l; level[l].d_subm_nbr is the submanifold map of level l or NULL if no layer needs it.
- *   expert < 0: d_batch as for emc2_voxelize.  expert >= 0: the stack takes the points of the scenes routed to `expert` only:
+ *   expert < 0: d_batch as for emc2_voxelize.  expert 0..2: the stack takes the points of the scenes routed to `expert` only:
  *   d_batch [n_points] holds SCENE ids (NULL: all 0), d_route [spec.n_batch] the expert of every scene (emc2_dispatch) and
  *   d_slot [spec.n_batch] its position in its expert's group (emc2_group_slots); the same result as voxelizing with
- *   emc2_group_points' batch ids, without writing them.
+ *   emc2_group_points' batch ids, which go to d_group_batch if it is given.
  * Every stack needs a context of its own (one stream at a time per context, as for the calls it replaces); all specs must
  * agree in stride_f.  At most 4 stacks.
  */
@@ -180,6 +180,7 @@ typedef struct {
   int32_t* d_counts;
   void* d_feats_lp;       /* copy of the means in lp_dtype, or NULL */
   emc2_stack_level level[EMC2_STACK_MAX_LEVELS];
+  int32_t* d_group_batch; /* [n_points] or NULL: the batch ids a routed stack's points got, as emc2_group_points writes them */
 } emc2_stack;
 emc2_status emc2_build_stacks(const emc2_stack* stacks, int32_t n_stacks, const float* d_points, int64_t n_points, void* stream);
 

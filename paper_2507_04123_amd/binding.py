@@ -65,7 +65,7 @@ class StackC(ctypes.Structure):
     _fields_ = [("ctx", ctypes.c_void_p), ("spec", _VoxelSpecC), ("expert", ctypes.c_int32), ("n_levels", ctypes.c_int32),
                 ("lp_dtype", ctypes.c_int), ("d_batch", ctypes.c_void_p), ("d_route", ctypes.c_void_p), ("d_slot", ctypes.c_void_p),
                 ("d_feats", ctypes.c_void_p), ("d_counts", ctypes.c_void_p), ("d_feats_lp", ctypes.c_void_p),
-                ("level", StackLevelC * STACK_MAX_LEVELS)]
+                ("level", StackLevelC * STACK_MAX_LEVELS), ("d_group_batch", ctypes.c_void_p)]
 
 
 class ConvCallC(ctypes.Structure):
@@ -219,6 +219,12 @@ def check_voxels(capacity: int, coords: torch.Tensor, feats: torch.Tensor, count
     if feats_lp.numel() < 4 * capacity or not feats_lp.is_cuda:
         raise ValueError("feats_lp smaller than capacity")
     return lp_dtype
+
+
+def check_group_batch(group_batch: torch.Tensor, n_points: int) -> None:
+    _dev_check(group_batch, torch.int32, "group_batch")
+    if group_batch.numel() != n_points:
+        raise ValueError("group_batch length != number of points")
 
 
 def check_kmap(in_coords: torch.Tensor, n_in: torch.Tensor, capacity_in: int, nbr: torch.Tensor, n_out: torch.Tensor,

@@ -58,6 +58,7 @@ struct DevStack {
   const int32_t* batch;
   const int32_t* route;         // expert of every scene
   const int32_t* slot;          // position of every scene in its expert's group
+  int32_t* group_batch;         // the frame id each point got, or NULL
   float4* feats;
   int32_t* counts;
   void* feats_lp;
@@ -106,13 +107,17 @@ __device__ __forceinline__ uint64_t div_key(uint64_t a, uint32_t b) {
   return (a >> 32) == 0 ? (uint64_t)((uint32_t)a / b) : a / b;
 }
 
-// A point's cell in a stack.  Routed stacks take the frame id from the scene's slot in its expert's group.
+// The frame id of point i in a routed stack: its scene's slot in its expert's group, -1 if another expert's.
+__device__ __forceinline__ int32_t routed_frame(const DevStack& st, int64_t i) {
+  const int32_t s = st.batch ? st.batch[i] : 0;
+  return s >= 0 && s < st.prm.n_batch && st.route[s] == st.expert ? st.slot[s] : -1;
+}
+
+// A point's cell in a stack.
 __device__ __forceinline__ PointCell locate_in(const Args& a, const DevStack& st, int64_t i) {
   PointCell pc = locate(a.points, st.expert < 0 ? st.batch : nullptr, i, a.n_points, st.prm);
   if (st.expert >= 0 && pc.keep) {
-    const int32_t s = st.batch ? st.batch[i] : 0;
-    int32_t b = -1;
-    if (s >= 0 && s < st.prm.n_batch && st.route[s] == st.expert) b = st.slot[s];
+    const int32_t b = routed_frame(st, i);
     pc.keep = b >= 0 && b < st.prm.n_batch;
     pc.c.x = b;
     pc.key += (uint64_t)(pc.keep ? b : 0) * st.prm.grid[2] * (uint64_t)st.prm.grid[1] * st.prm.grid[0];
@@ -152,6 +157,7 @@ __device__ __forceinline__ void role_mark(const Args& a, const DevStack& st, uin
     st.feats[i] = make_float4(0.f, 0.f, 0.f, 0.f);
     st.counts[i] = 0;
   }
+  if (st.expert >= 0 && st.group_batch && i < a.n_points) st.group_batch[i] = routed_frame(st, i);
   emc2_mark_point(locate_in(a, st, i), i, a.n_points, st.lv[0].idx, st.lv[0].flags, st.first);
 }
 
@@ -497,6 +503,7 @@ emc2_status describe(const emc2_stack& s, int64_t n_points, DevStack* d) {
   if (ok != EMC2_OK) return ok;
   if (s.d_feats_lp && s.lp_dtype != EMC2_F16 && s.lp_dtype != EMC2_BF16)
     return emc2_fail(ctx, EMC2_ERR_INVALID_ARG, "emc2_build_stacks: lp_dtype must be F16 or BF16");
+  if (s.expert > 2) return emc2_fail(ctx, EMC2_ERR_INVALID_ARG, "emc2_build_stacks: expert %d beyond 2", s.expert);
   if (s.expert >= 0 && (!s.d_route || !s.d_slot))
     return emc2_fail(ctx, EMC2_ERR_INVALID_ARG, "emc2_build_stacks: a routed stack needs d_route and d_slot");
   memset(d, 0, sizeof(*d));
@@ -507,6 +514,7 @@ emc2_status describe(const emc2_stack& s, int64_t n_points, DevStack* d) {
   d->batch = s.d_batch;
   d->route = s.d_route;
   d->slot = s.d_slot;
+  d->group_batch = s.d_group_batch;
   d->feats = (float4*)s.d_feats;
   d->counts = s.d_counts;
   d->feats_lp = s.d_feats_lp;

@@ -85,7 +85,8 @@ class NativePass:
     (voxelization and every kernel map of every branch, in a handful of launches) and emc2_spconv_list.  The argument
     blocks are filled and checked once, and again by the first pass that finds anything that went into them changed: a
     context, a capacity, a slot, the layers, a weight layout, or a tensor's address, shape, type, place or contiguity.  Every pass sets the points and frame ids.  The runners are handed in by each call (they own their passes),
-    and so is `route`: the (expert, slot) tensors of a routed batch, branch e then takes the scenes of expert e."""
+    and so is `route`: the (expert, slot) tensors of a routed batch and, per expert, the tensor that receives the points' batch
+    ids; branch e then takes the scenes of expert e."""
 
     def __init__(self):
         self.stacks = self.calls = None
@@ -96,7 +97,7 @@ class NativePass:
     def covers(runners: Sequence["BranchRunner"]) -> bool:
         return len(runners) <= B.MAX_STACKS and all(len(r.levels) <= B.STACK_MAX_LEVELS for r in runners)
 
-    def _fill_stacks(self, runners: Sequence["BranchRunner"], route: Optional[Tuple[torch.Tensor, torch.Tensor]]) -> None:
+    def _fill_stacks(self, runners: Sequence["BranchRunner"], route: Optional[Sequence[torch.Tensor]], n_points: int) -> None:
         stacks = (B.StackC * len(runners))()
         for e, r in enumerate(runners):
             s, sp, lp_dtype = stacks[e], r.branch.spec, r.check_maps()
@@ -104,7 +105,8 @@ class NativePass:
             s.spec = B.voxel_spec_c(sp, 4)
             s.expert, s.n_levels = (-1 if route is None else e), len(r.levels)
             if route is not None:
-                s.d_route, s.d_slot = route[0].data_ptr(), route[1].data_ptr()
+                B.check_group_batch(route[2 + e], n_points)
+                s.d_route, s.d_slot, s.d_group_batch = route[0].data_ptr(), route[1].data_ptr(), route[2 + e].data_ptr()
             s.d_feats, s.d_counts = r.feats32.data_ptr(), r.counts.data_ptr()
             s.lp_dtype = lp_dtype
             s.d_feats_lp = r.feats_lp.data_ptr() if r.feats_lp is not None else None
@@ -115,12 +117,14 @@ class NativePass:
         self.stacks = stacks
 
     def maps(self, runners: Sequence["BranchRunner"], points: torch.Tensor, batch: Optional[torch.Tensor],
-             route: Optional[Tuple[torch.Tensor, torch.Tensor]] = None) -> None:
-        B.check_points(points, batch)
-        of = [v for r in runners for v in r.map_key()] + [B.tensor_key(t) for t in route or ()]
+             route: Optional[Sequence[torch.Tensor]] = None) -> None:
+        n_points, _ = B.check_points(points, batch)
+        of = [v for r in runners for v in r.map_key()]
+        if route is not None:
+            of += [n_points, *(B.tensor_key(t) for t in route)]
         if of != self.stacks_of:
             self.stacks_of = None
-            self._fill_stacks(runners, route)
+            self._fill_stacks(runners, route, n_points)
             self.stacks_of = of
         for s in self.stacks:
             s.d_batch = batch.data_ptr() if batch is not None else None
@@ -138,7 +142,7 @@ class NativePass:
         return [r.acts[-1] if r.acts else r.conv_input() for r in runners]
 
     def run(self, runners: Sequence["BranchRunner"], points: torch.Tensor, batch: Optional[torch.Tensor],
-            route: Optional[Tuple[torch.Tensor, torch.Tensor]] = None) -> List[torch.Tensor]:
+            route: Optional[Sequence[torch.Tensor]] = None) -> List[torch.Tensor]:
         self.maps(runners, points, batch, route)
         return self.convs(runners)
 
@@ -685,8 +689,10 @@ class ConfigRunner:
 class RoutedRunner:
     """Scene-level routing (paper Sec. 3.2): the dispatcher picks an expert per scene from the scene's proposal
     regions, the scenes are grouped by expert, and each expert's stack runs on its own group only.  Sequencing
-    only: emc2_dispatch -> emc2_group_slots -> the three stacks side by side in one emc2_build_stacks call, each dropping the
-    points of other experts' scenes.  Group sizes stay on the device:
+    only: emc2_dispatch -> emc2_group_slots -> the experts' stacks side by side in one emc2_build_stacks call, each dropping the
+    points of other experts' scenes (group_batch[e] receives the batch ids that expert e's stack gave the points: -1 for
+    other experts').  Stacks that such a call does not cover go one by one: emc2_group_points, then the expert's
+    BranchRunner with those ids.  Group sizes stay on the device:
     every expert's buffers are sized for all n_scenes, and nothing here waits for the host."""
 
     def __init__(self, experts: Sequence[Branch], dtype: int, n_points: int, n_scenes: int, seed: int, device: str = "cuda"):
@@ -697,14 +703,15 @@ class RoutedRunner:
         self.order = torch.zeros((n_scenes,), **i32)
         self.slot = torch.zeros((n_scenes,), **i32)
         self.runners: List[Tuple[B.Context, BranchRunner]] = []
+        self.group_batch: List[torch.Tensor] = []
         for e, br in enumerate(experts):
             assert br.spec.n_batch == n_scenes
             caps = default_capacities(br, n_points)
             ctx = B.Context(n_points, max(caps), cells_of(br.spec.grid, n_scenes), n_slots=len(caps))
             self.runners.append((ctx, BranchRunner(ctx, br, dtype, n_points, device_params(br.layers, seed + e, dtype),
                                                    capacities=caps, device=device)))
-        assert NativePass.covers([r for _, r in self.runners])
-        self.native = NativePass()
+            self.group_batch.append(torch.empty((n_points,), **i32))
+        self.native = NativePass() if NativePass.covers([r for _, r in self.runners]) else None
 
     def close(self) -> None:
         for ctx, _ in self.runners:
@@ -737,5 +744,12 @@ class RoutedRunner:
             raise ValueError("points / scene length != n_points")
         ctx0 = self.runners[0][0]
         ctx0.dispatch(props, prop_scene, self.n_scenes, dist, conf, self.expert, self.counts, self.order)
-        ctx0.group_slots(self.expert, self.order, self.counts, self.n_scenes, self.slot)
-        return self.native.run([r for _, r in self.runners], points, scene, route=(self.expert, self.slot))
+        if self.native is not None:
+            ctx0.group_slots(self.expert, self.order, self.counts, self.n_scenes, self.slot)
+            return self.native.run([r for _, r in self.runners], points, scene, route=(self.expert, self.slot, *self.group_batch))
+        outs = []
+        for e, (ctx, r) in enumerate(self.runners):
+            ctx.group_points(scene, self.n_points, self.expert, self.order, self.counts, self.n_scenes, e, self.slot,
+                             self.group_batch[e])
+            outs.append(r.run(points, self.group_batch[e]))
+        return outs

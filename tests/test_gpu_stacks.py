@@ -223,3 +223,37 @@ def test_routed_pass_takes_as_many_points_as_it_was_made_for():
             rr.run(p, s, props, prop_scene, 23.5, 0.5)
     rr.status_sync()
     rr.close()
+
+
+@pytest.mark.parametrize("with_scene", [True, False])
+def test_routed_pass_writes_the_batch_ids_that_group_points_writes(with_scene):
+    """Every point's id, those outside the grid and of malformed scenes included; and stacks of more levels than one call
+    takes give the levels they share with shorter ones the same voxels."""
+    import dataclasses
+    from paper_2507_04123_amd.configs import F16, Layer, STRIDED, SUBM, expert_branches
+    from paper_2507_04123_amd.pipeline import RoutedRunner
+    n, ns = 3001, 4
+    base = [dataclasses.replace(b, layers=b.layers[:1] + (Layer(STRIDED, b.layers[0].cout, 32), Layer(SUBM, 32, 32))) for b in expert_branches(ns)]
+    longer = [dataclasses.replace(b, layers=b.layers + (Layer(STRIDED, 32, 32),) * 4) for b in base]
+    g = torch.Generator(device="cuda").manual_seed(7)
+    pts = torch.rand((n, 4), generator=g, device="cuda") * torch.tensor([80.0, 90.0, 5.0, 1.0], device="cuda") - torch.tensor([5.0, 45.0, 3.5, 0.0], device="cuda")
+    scene = torch.randint(-1, ns + 1, (n,), generator=g, device="cuda", dtype=torch.int32) if with_scene else None
+    props = torch.tensor([[10.0, 0.0, 0.0, 0.9], [60.0, 0.0, 0.0, 0.9], [10.0, 1.0, 0.0, 0.1], [50.0, 9.0, 0.0, 0.2]], device="cuda")
+    pscene = torch.tensor([0, 1, 2, 3], dtype=torch.int32, device="cuda")
+    a, b = RoutedRunner(base, F16, n, ns, seed=3), RoutedRunner(longer, F16, n, ns, seed=3)
+    assert a.native is not None and b.native is None
+    for rr in (a, b):
+        rr.run(pts, scene, props, pscene, 23.5, 0.5)
+        rr.status_sync()
+    ctx = a.runners[0][0]
+    seen = set(a.expert.tolist())
+    assert len(seen) > 1
+    for e, ((_, ra), (_, rb)) in enumerate(zip(a.runners, b.runners)):
+        want = torch.full((n,), -7, dtype=torch.int32, device="cuda")
+        ctx.group_points(scene, n, a.expert, a.order, a.counts, ns, e, a.slot, want)
+        assert torch.equal(a.group_batch[e], want) and torch.equal(b.group_batch[e], want)
+        for la, lb in zip(ra.levels, rb.levels):
+            m = int(la.n.item())
+            assert int(lb.n.item()) == m and torch.equal(la.coords[:m], lb.coords[:m])
+    a.close()
+    b.close()

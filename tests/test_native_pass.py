@@ -72,6 +72,7 @@ def _routed(n_levels=2, n=64):
     rr = P.RoutedRunner([_branch(n_levels) for _ in range(3)], F16, n, 2, seed=1, device="cpu")
     for _, r in rr.runners:
         _on_device(r)
+    rr.group_batch = [_dev(t) for t in rr.group_batch]
     args = (_dev(torch.zeros((n, 4))), None, torch.zeros((1, 4)), None, 23.5, 0.5)
     return rr, args
 
@@ -178,3 +179,29 @@ def test_maps_refuse_frame_ids_and_grids_that_do_not_fit(native):
     with pytest.raises(B.Emc2Error):
         r.run_maps(pts, ids)
     assert len(native["stacks"]) == 1
+
+
+def test_routed_pass_of_stacks_with_six_levels_goes_call_by_call(native):
+    """Stacks that one native call does not cover: grouped and run one expert after the other."""
+    rr, args = _routed(n_levels=6)
+    outs = rr.run(*args)
+    assert not native["stacks"] and len(outs) == 3
+    names = [[c[0] for c in ctx.calls] for ctx, _ in rr.runners]
+    assert names[0][:2] == ["dispatch", "group_points"]
+    for e, (ctx, r) in enumerate(rr.runners):
+        i = names[e].index("group_points")
+        assert ctx.calls[i][1][6] == e and ctx.calls[i][1][8] is rr.group_batch[e]
+        assert names[e][i + 1] == "voxelize" and ctx.calls[i + 1][1][1] is rr.group_batch[e]
+        assert names[e].count("build_kmap") == 11 and names[e].count("spconv") == 11
+
+
+def test_routed_pass_writes_the_batch_ids_it_used(native):
+    rr, args = _routed()
+    rr.run(*args)
+    assert [s.d_group_batch for s in native["stacks"][-1]] == [t.data_ptr() for t in rr.group_batch]
+    rr.group_batch[1] = _dev(torch.zeros(64, dtype=torch.int32))
+    rr.run(*args)
+    assert native["stacks"][-1][1].d_group_batch == rr.group_batch[1].data_ptr()
+    rr.group_batch[1] = _dev(torch.zeros(63, dtype=torch.int32))
+    with pytest.raises(ValueError, match="group_batch"):
+        rr.run(*args)
