@@ -155,7 +155,7 @@ emc2_status emc2_build_kmap(emc2_ctx* ctx, emc2_conv_kind kind, const int32_t* d
  *   d_slot [spec.n_batch] its position in its expert's group (emc2_group_slots); the same result as voxelizing with
  *   emc2_group_points' batch ids, which go to d_group_batch if it is given.
  * Every stack needs a context of its own (one stream at a time per context, as for the calls it replaces); all specs must
- * agree in stride_f.  At most 4 stacks.
+ * agree in stride_f.  At most 4 stacks.  After a refusal emc2_last_error of stacks[0].ctx says why.
  */
 #define EMC2_STACK_MAX_LEVELS 5
 typedef struct {
@@ -264,7 +264,8 @@ emc2_status emc2_spconv(emc2_ctx* ctx, emc2_dtype dtype, const void* d_in, const
                         const int32_t* d_nbr, int32_t map_hint, const int32_t* d_n_out, int64_t capacity_out,
                         int64_t n_in_rows, int32_t cin, int32_t cout, void* d_out, void* stream);
 
-/* emc2_spconv for n calls in order, in one host call: the arguments of each as in emc2_spconv. */
+/* emc2_spconv for n calls in order, in one host call: the arguments of each as in emc2_spconv.  Ends at the first call that
+ * is refused; emc2_last_error of calls[0].ctx then says why (nothing is issued if a call has no context). */
 typedef struct {
   emc2_ctx* ctx;
   const void* d_in;

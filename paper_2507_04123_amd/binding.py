@@ -264,6 +264,11 @@ def check_conv(dtype: int, x: torch.Tensor, w: torch.Tensor, scale: Optional[tor
     return cin, cout
 
 
+def _why(lib: ctypes.CDLL, ctx: Optional[int]) -> str:
+    """What a call that takes several contexts says went wrong: kept with the first of them."""
+    return lib.emc2_last_error(ctx).decode() if ctx else "the context is closed"
+
+
 def build_stacks(stacks, n_stacks: int, points: torch.Tensor) -> None:
     """emc2_build_stacks over a ctypes array of StackC whose buffers and frame ids the caller has checked and keeps alive."""
     n, stride = check_points(points, None)
@@ -272,7 +277,7 @@ def build_stacks(stacks, n_stacks: int, points: torch.Tensor) -> None:
     lib = load_library()
     st = lib.emc2_build_stacks(stacks, n_stacks, points.data_ptr(), n, torch.cuda.current_stream().cuda_stream)
     if st != OK:
-        raise Emc2Error(st, lib.emc2_last_error(stacks[0].ctx).decode())
+        raise Emc2Error(st, _why(lib, stacks[0].ctx))
 
 
 def spconv_list(calls, n: int) -> None:
@@ -280,7 +285,7 @@ def spconv_list(calls, n: int) -> None:
     lib = load_library()
     st = lib.emc2_spconv_list(calls, n, torch.cuda.current_stream().cuda_stream)
     if st != OK:
-        raise Emc2Error(st, next((t for t in (lib.emc2_last_error(calls[i].ctx).decode() for i in range(n)) if t), ""))
+        raise Emc2Error(st, _why(lib, calls[0].ctx))
 
 
 class Context:

@@ -442,11 +442,16 @@ extern "C" emc2_status emc2_spconv(emc2_ctx* ctx, emc2_dtype dtype, const void* 
 
 extern "C" emc2_status emc2_spconv_list(const emc2_conv_call* calls, int32_t n, void* stream) {
   if (n < 0 || (n > 0 && !calls)) return EMC2_ERR_INVALID_ARG;
+  for (int32_t i = 0; i < n; ++i)
+    if (!calls[i].ctx) return emc2_fail(calls[0].ctx, EMC2_ERR_INVALID_ARG, "emc2_spconv_list: call %d has no context", i);
   for (int32_t i = 0; i < n; ++i) {
     const emc2_conv_call& c = calls[i];
     const emc2_status st = emc2_spconv(c.ctx, c.dtype, c.d_in, c.d_w, c.w_layout, c.d_scale, c.d_shift, c.epilogue, c.d_nbr, c.map_hint,
                                        c.d_n_out, c.capacity_out, c.n_in_rows, c.cin, c.cout, c.d_out, stream);
-    if (st != EMC2_OK) return st;
+    if (st != EMC2_OK) {   // the caller asks the first call's context what went wrong, whichever call it was
+      if (c.ctx != calls[0].ctx) emc2_fail(calls[0].ctx, st, "%s", c.ctx->err);
+      return st;
+    }
   }
   return EMC2_OK;
 }

@@ -573,7 +573,7 @@ extern "C" emc2_status emc2_build_stacks(const emc2_stack* stacks, int32_t n_sta
                                          void* stream) {
   if (!stacks || n_stacks < 1) return EMC2_ERR_INVALID_ARG;
   for (int i = 0; i < n_stacks; ++i)
-    if (!stacks[i].ctx) return EMC2_ERR_INVALID_ARG;
+    if (!stacks[i].ctx) return emc2_fail(stacks[0].ctx, EMC2_ERR_INVALID_ARG, "emc2_build_stacks: stack %d has no context", i);
   emc2_ctx* ctx0 = stacks[0].ctx;
   if (n_stacks > kStacks) return emc2_fail(ctx0, EMC2_ERR_UNSUPPORTED, "emc2_build_stacks: more than %d stacks", kStacks);
   if (n_points < 0 || (n_points > 0 && !d_points)) return emc2_fail(ctx0, EMC2_ERR_INVALID_ARG, "emc2_build_stacks: bad points");

@@ -257,3 +257,34 @@ def test_routed_pass_writes_the_batch_ids_that_group_points_writes(with_scene):
             assert int(lb.n.item()) == m and torch.equal(la.coords[:m], lb.coords[:m])
     a.close()
     b.close()
+
+
+def test_a_refused_list_says_why_whatever_went_wrong_before():
+    """The text is the failing call's, not an older one of another context in the list."""
+    ctx = [B.Context(16, 16, 64, n_slots=1) for _ in range(2)]
+    i32 = dict(dtype=torch.int32, device="cuda")
+    x, w, y = torch.zeros((16, 4), device="cuda"), torch.zeros((27, 4, 16), device="cuda"), torch.zeros((16, 16), device="cuda")
+    nbr, n = torch.full((27, 16), -1, **i32), torch.zeros(1, **i32)
+    with pytest.raises(B.Emc2Error, match="n_points"):           # an old error of the first context
+        ctx[0].voxelize(torch.zeros((17, 4), device="cuda"), None, VoxelSpec((0.0,) * 3, (1.0,) * 3, (4, 4, 4)), 16,
+                        nbr[:4].view(16, 4), x, nbr[0], n)
+    calls = (B.ConvCallC * 2)()
+    for c, t in zip(calls, ctx):
+        c.ctx, c.d_in, c.d_w, c.d_nbr, c.d_n_out, c.d_out = t.h, x.data_ptr(), w.data_ptr(), nbr.data_ptr(), n.data_ptr(), y.data_ptr()
+        c.capacity_out, c.n_in_rows, c.dtype, c.map_hint, c.cin, c.cout = 16, 16, B.F32, B.MAP_ANY, 4, 16
+    B.spconv_list(calls, 2)
+    calls[1].capacity_out = 0
+    with pytest.raises(B.Emc2Error, match="capacity_out < 1"):
+        B.spconv_list(calls, 2)
+    calls[1].ctx = None
+    with pytest.raises(B.Emc2Error, match="call 1 has no context"):
+        B.spconv_list(calls, 2)
+    calls[0].ctx = None
+    with pytest.raises(B.Emc2Error, match="closed"):
+        B.spconv_list(calls, 2)
+    stacks = (B.StackC * 2)()
+    stacks[0].ctx = ctx[0].h
+    with pytest.raises(B.Emc2Error, match="stack 1 has no context"):
+        B.build_stacks(stacks, 2, x)
+    for t in ctx:
+        t.close()
