@@ -288,3 +288,41 @@ def test_a_refused_list_says_why_whatever_went_wrong_before():
         B.build_stacks(stacks, 2, x)
     for t in ctx:
         t.close()
+
+
+def _kernels_in(issue):
+    """Launches of what `issue` issues: the nodes of a graph that captures it."""
+    import ctypes
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph, stream=torch.cuda.Stream()):
+        issue()
+    count = ctypes.c_size_t(0)
+    hip = B.load_library()                        # (links the runtime)
+    hip.hipGraphGetNodes.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.POINTER(ctypes.c_size_t)]
+    assert hip.hipGraphGetNodes(graph.raw_cuda_graph(), None, ctypes.byref(count)) == 0
+    return count.value
+
+
+# words of the finest index: one tile of 2 048, a word more, the four tiles that one block takes, a word more
+@pytest.mark.parametrize("words,levels,launches", [(2048, 1, 5), (2049, 1, 5), (6250, 1, 5), (8192, 1, 5), (8193, 1, 6), (8192, 2, 6)])
+def test_small_index_scanned_by_one_block(words, levels, launches):
+    grid = (32, words, 1)
+    spec = VoxelSpec((0.0, 0.0, 0.0), (1.0, 1.0, 1.0), grid)
+    for n in (3, 700, 8 * words):
+        a, b = _Bufs(grid, 1, levels, n), _Bufs(grid, 1, levels, n)
+        for k in range(2):
+            pts, batch = _points(n + k, grid, 1, n)
+            if k:
+                pts[:, 1] = words - 0.5           # the last tile alone holds a bit
+            b.call_by_call(pts, batch, spec)
+            arr = (B.StackC * 1)(a.stack(spec, batch))
+            B.build_stacks(arr, 1, pts)
+            torch.cuda.synchronize()
+            a.ctx.status_sync(); b.ctx.status_sync()
+            if k:                                 # (many points to a cell: their means depend on the order)
+                m = int(b.n[0].item())
+                assert int(a.n[0].item()) == m > 0 and torch.equal(a.coords[0][:m], b.coords[0][:m])
+            else:
+                _same(a, b, f"{words} words, {n} points")
+        assert _kernels_in(lambda: B.build_stacks(arr, 1, pts)) == launches
+        a.ctx.close(); b.ctx.close()
