@@ -413,17 +413,24 @@ k_spconv_span(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, con
   if (n_out > capacity_out) n_out = capacity_out;
   // Rows are dealt in rounds of one block per CU (the tiles and weights in LDS leave room for one).  Whole rounds take
   // 64 rows a wave; what is left, which used to cost a whole round however little it was, is split into the smallest
-  // waves (16, 32, 48 or 64 rows) with which it fits one round.  64-row waves throughout against this, alone on the GPU:
-  // 16 k rows 24.6 / 18.2 us, 69 k 35.5 / 31.0, 223 k 64.6 / 59.5, 573 k 139 / 137 (131 in a grid that fits).
+  // waves (16, 32 or 48 rows) with which it fits one round.  64-row waves throughout against this, alone on the GPU:
+  // 16 k rows 24.6 / 18.2 us, 69 k 35.5 / 31.0, 223 k 64.6 / 59.5, 573 k 139 / 137 (131 in a grid that fits).  A rest of
+  // more than 98 304 rows would take 64-row waves too, so it belongs to the whole rounds: as a part of its own it only
+  // tore every XCD's range of rows in two (380 k rows 99.2 / 98.1 us, 852 k rows with a smaller rest 212 / 211).
   constexpr uint32_t kRoundRows = kSpanCUs * kSpanWaves * 64;
   const uint32_t n = n_out > 0 ? (uint32_t)n_out : 0u;
-  const uint32_t full = n / kRoundRows * kSpanCUs;                // blocks of the whole rounds
-  const uint32_t rem = n % kRoundRows;
   // XCD-aware tile assignment: workgroup b runs on XCD b % 8; XCD x takes a contiguous range of the tiles of either part
   const uint32_t x = blockIdx.x % 8, slot = blockIdx.x / 8;
+  const uint32_t rounds = n / kRoundRows;
+  uint32_t rem = n % kRoundRows;
   // The grid is for the capacity; a block beyond both parts leaves at once (one at a time fits a CU: 22 k of them cost
   // 25 us when each first worked out the split).
-  if (slot >= full / 8 + (rem ? kSpanCUs / 8 : 0)) return;
+  if (slot >= (rounds + (rem ? 1 : 0)) * (kSpanCUs / 8)) return;
+  uint32_t full = rounds * kSpanCUs;                              // blocks of 64-row waves
+  if (rem > kRoundRows / 4 * 3) {
+    full += (rem + kSpanWaves * 64 - 1) / (kSpanWaves * 64);
+    rem = 0;
+  }
   const int wave = threadIdx.x >> 6;
   // waves w and w + 4 share a SIMD: one of each kind per SIMD
 #define EMC2_SPAN_WAVE(MTV)                                                                                               \
@@ -437,20 +444,22 @@ k_spconv_span(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, con
                                           wl, tile[wave], row0_);                                                         \
     return;                                                                                                               \
   }
-  if (slot < full / 8) {   // kSpanCUs is a multiple of 8
-    const int64_t first_row = (int64_t)(x * (full / 8) + slot) * (kSpanWaves * 64);
+  const uint32_t chunk = (full + 7) / 8;
+  if (slot < chunk) {
+    if (x * chunk + slot >= full) return;   // uniform for the block
+    const int64_t first_row = (int64_t)(x * chunk + slot) * (kSpanWaves * 64);
     EMC2_SPAN_WAVE(4)
   }
   const uint32_t mt = (rem + kRoundRows / 4 - 1) / (kRoundRows / 4);       // 16-row tiles per wave of the rest
+  if (mt == 0) return;
   const uint32_t rows = kSpanWaves * 16 * mt;
-  const uint32_t n_tiles = (rem + rows - 1) / rows, chunk = (n_tiles + 7) / 8;
-  const uint32_t slot2 = slot - full / 8;
-  if (slot2 >= chunk || x * chunk + slot2 >= n_tiles) return;   // uniform for the block
-  const int64_t first_row = (int64_t)full * (kSpanWaves * 64) + (int64_t)(x * chunk + slot2) * rows;
+  const uint32_t n_tiles = (rem + rows - 1) / rows, chunk2 = (n_tiles + 7) / 8;
+  const uint32_t slot2 = slot - chunk;
+  if (slot2 >= chunk2 || x * chunk2 + slot2 >= n_tiles) return;   // uniform for the block
+  const int64_t first_row = (int64_t)full * (kSpanWaves * 64) + (int64_t)(x * chunk2 + slot2) * rows;
   if (mt == 1) EMC2_SPAN_WAVE(1)
   if (mt == 2) EMC2_SPAN_WAVE(2)
-  if (mt == 3) EMC2_SPAN_WAVE(3)
-  EMC2_SPAN_WAVE(4)
+  EMC2_SPAN_WAVE(3)
 #undef EMC2_SPAN_WAVE
 }
 

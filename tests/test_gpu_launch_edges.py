@@ -50,8 +50,9 @@ def _check_conv(n, cin, cout, hint, shuffled, seed=11):
     ctx.close()
 
 
-# a round is 131 072 rows; the rest runs in waves of 16, 32, 48 or 64 rows
-@pytest.mark.parametrize("n", [1, 17, 129, 32768, 32769, 65537, 98305, 131071, 131072, 131073, 131072 + 40001, 262144 + 70001])
+# a round is 131 072 rows; the rest runs in waves of 16, 32 or 48 rows or, beyond 98 304 rows, as part of the whole rounds
+@pytest.mark.parametrize("n", [1, 17, 129, 32768, 32769, 65537, 98305, 131071, 131072, 131073, 131072 + 40001, 262144 + 70001,
+                               98304, 131072 + 98304, 131072 + 98305, 131072 + 102401, 262144 - 1])
 def test_span_conv_rounds(n):
     _check_conv(n, 64, 64, B.SUBM, False)
 
