@@ -26,21 +26,24 @@ def _map(n, seed, shuffled):
     return nbr.to(torch.int32).contiguous()
 
 
-def _check_conv(n, cin, cout, hint, shuffled, seed=11):
+def _check_conv(n, cin, cout, hint, shuffled, seed=11, cap=None, rows_in=None):
+    """n rows of `cap` (the pitch of the map; what lies beyond n is not read for a result), `rows_in` rows vouched for."""
+    cap = n if cap is None else cap
     g = torch.Generator(device="cuda").manual_seed(seed)
     x = torch.randn((n, cin), generator=g, device="cuda").half()
     w = (torch.randn((27, cin, cout), generator=g, device="cuda") * 0.1).half()
-    nbr = _map(n, seed, shuffled)
+    nbr = torch.zeros((27, cap), dtype=torch.int32, device="cuda")
+    nbr[:, :n] = _map(n, seed, shuffled)
     ctx = B.Context(16, 16, 64, n_slots=1)
     wp = torch.empty_like(w)
     ctx.pack_weights(F16, w, wp)
-    y = torch.full((n + 3, cout), 77.0, dtype=torch.float16, device="cuda")
-    ctx.spconv(F16, x, wp, None, None, EPI_NONE, nbr, torch.tensor([n], dtype=torch.int32, device="cuda"), n, y[:n],
-               w_layout=B.W_PACKED, map_hint=hint)
+    y = torch.full((cap + 3, cout), 77.0, dtype=torch.float16, device="cuda")
+    ctx.spconv(F16, x, wp, None, None, EPI_NONE, nbr, torch.tensor([n], dtype=torch.int32, device="cuda"), cap, y[:cap],
+               w_layout=B.W_PACKED, map_hint=hint, n_in_rows=rows_in)
     ctx.status_sync()
     exp = torch.zeros((n, cout), device="cuda")
     for k in range(27):
-        rows = (nbr[k] >= 0).nonzero().squeeze(1)
+        rows = (nbr[k][:n] >= 0).nonzero().squeeze(1)
         exp[rows] += x[nbr[k][rows].long()].float() @ w[k].float()
     # the result is rounded once to fp16 (2^-11 relative); sums of up to 27 * cin fp32 products in another order stay below that
     rms = float(exp.square().mean().sqrt())
@@ -62,11 +65,18 @@ def test_span_conv_rounds_taps_outside_an_interval(n):
     _check_conv(n, 64, 64, B.SUBM, True)
 
 
-# 8 192 blocks of 128 rows (256 at 32 -> 32): one tile less, exactly as many, one more, a second tile for most
-@pytest.mark.parametrize("cin,cout,n", [(64, 32, 8192 * 128 - 1), (32, 64, 8192 * 128 + 1), (32, 64, 8192 * 128 * 3 // 2 + 77),
-                                        (32, 32, 8192 * 256 + 300)])
-def test_direct_conv_grid_limit(cin, cout, n):
-    _check_conv(n, cin, cout, B.MAP_ANY, False)
+# Blocks of 128 rows (256 at 32 -> 32).  A capacity of up to 4 * 8 192 blocks gets a block for each tile, a row more 8 192
+# blocks that loop over the tiles there are: one tile for all but the last, one more than blocks, a second tile for half of
+# them.  64 -> 32 of 2^25 rows and more reads them by address instead of through a descriptor.
+@pytest.mark.parametrize("cin,cout,rows,n,loop", [(64, 32, 128, 8192 * 128 - 129, True), (32, 64, 128, 8192 * 128 + 1, True),
+                                                  (32, 64, 128, 8192 * 128 * 3 // 2 + 77, True), (64, 32, 128, 8192 * 128 * 3 // 2 + 77, True),
+                                                  (32, 64, 128, 8192 * 128 * 3 // 2 + 77, False), (32, 32, 256, 8192 * 256 + 300, True),
+                                                  (32, 32, 256, 1, True)])
+def test_direct_conv_grid_limit(cin, cout, rows, n, loop):
+    cap = 4 * 8192 * rows + (1 if loop else 0)
+    _check_conv(n, cin, cout, B.MAP_ANY, False, cap=cap)
+    if cin == 64 and loop:
+        _check_conv(n, cin, cout, B.MAP_ANY, False, cap=cap, rows_in=(1 << 25) + 3)
 
 
 # inputs of less than 4 GiB are read through a buffer descriptor, larger ones by address; any negative entry is absent
