@@ -5,9 +5,11 @@ A step is one pass of the whole hot path over one batch of synthetic input, alre
 headline workload is the largest single-GPU configuration, config 5 (eight front-view frames in one batch,
 960 k points, routed by range to a near and a far expert: 2 voxelizations, 8 kernel maps, 11 convs per step);
 `value` = 8 frames / step time.  The other four configurations are measured the same way and listed under
-`per_config`.  Prints ONE JSON line with the throughput, a `roofline` object for the dominant kernel (its own
+`per_config`.  Prints ONE JSON line on stdout with the throughput, a `roofline` object for the dominant kernel (its own
 launch duration, event-bracketed with the GPU to itself; the figure under sharing, bracketed inside the timed
-steps, beside it) and a `cpu_baseline` object (the CPU oracle on this machine's host cores).
+steps, beside it), the other configurations' throughputs and a `cpu_baseline` object (the CPU oracle on this machine's host
+cores).  The whole record (stages, layers, spreads, side measurements) goes to stderr as one JSON line before it: readers
+of stdout that keep only its last 2 000 characters still hold the whole line.
 """
 from __future__ import annotations
 
@@ -845,6 +847,22 @@ def measure_other_configs(args):
     return per
 
 
+def stdout_line(out):
+    """The part of the record that goes to stdout: under 2 000 characters whatever was measured beside it."""
+    line = {k: v for k, v in out.items() if k in ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better",
+                                                  "scaling", "vs_baseline", "dtype", "data")}
+    line["config"] = {k: v for k, v in out["config"].items() if k != "voxels_per_level"}
+    line["roofline"] = {k: v for k, v in out["roofline"].items() if k != "measured"}
+    if "under_sharing" in line["roofline"]:
+        line["roofline"]["under_sharing"] = {k: v for k, v in line["roofline"]["under_sharing"].items() if k != "note"}
+    if out.get("per_config"):
+        line["per_config"] = [{k: r[k] for k in ("config", "value", "ms_per_step") if k in r} if "error" not in r
+                              else {"config": r.get("config"), "error": r["error"][:60]} for r in out["per_config"]]
+    if "cpu_baseline" in out:
+        line["cpu_baseline"] = {k: v for k, v in out["cpu_baseline"].items() if k in ("value", "unit", "cores", "kind")}
+    return json.dumps(line)
+
+
 def main() -> int:
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -944,7 +962,8 @@ def main() -> int:
         import oracle
         threads = min(oracle.max_threads(), 16)
         out["cpu_baseline"] = cpu_baseline(cfg, pts_np, batch_np, threads)
-    print(json.dumps(out))
+    print(json.dumps(out), file=sys.stderr, flush=True)
+    print(stdout_line(out))
     return 0
 
 

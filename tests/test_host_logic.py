@@ -84,3 +84,30 @@ def test_bench_reads_the_committed_traffic_summaries():
         text = open(os.path.join(pdir, name)).read()
         assert "rocprofv3" in text and "bench.py" in text, name
         assert "_work" not in text, name
+
+
+def test_bench_line_is_whole_in_the_last_2000_characters():
+    """Every field of the contract, whatever else was measured, in a line short enough to be kept whole."""
+    import json
+    sys.path.insert(0, ROOT)
+    import bench
+    f = 0.12345678901234567
+    cfg = {"workload": "w" * 400, "frames_per_step": 8, "batches_in_flight": 4, "launch_shape": "s" * 90, "hip_graphs": True,
+           "voxels_per_level": {"near": [10 ** 6] * 9, "far": [10 ** 6] * 9}}
+    roof = {"kernel": "k" * 60, "bound": "mfma", "achieved": f, "peak": 2500.0, "unit": "TFLOP/s", "frac": f, "flops_per_launch": 1e11 * f,
+            "launches_per_step": 4, "avg_launch_ms": f, "measured": "m" * 200, "traffic": 3.603e8,
+            "under_sharing": {"achieved": f, "frac": f, "avg_launch_ms": f, "launches_timed": 8, "note": "n" * 80}}
+    full = {"metric": "m" * 60, "value": 1e4 * f, "unit": "frames/s", "n_gpus": 1, "steps": 20, "warmup": 5, "ms_per_step": f,
+            "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "f16", "data": "synthetic", "config": cfg,
+            "roofline": roof, "conv_layers": [{"x": f}] * 500,
+            "per_config": [{"config": i, "value": 1e4 * f, "ms_per_step": f, "conv_layers": [f] * 99} for i in (1, 2, 3)]
+            + [{"config": 4, "error": "e" * 5000}],
+            "cpu_baseline": {"value": f, "unit": "frames/s", "cores": 16, "kind": "oracle", "sample": "s" * 300}}
+    line = bench.stdout_line(full)
+    assert len(line) < 2000 and "\n" not in line
+    got = json.loads(line)
+    for k in ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling", "vs_baseline", "dtype",
+              "data"):
+        assert got[k] == full[k]
+    assert got["config"]["workload"] == cfg["workload"] and got["roofline"]["frac"] == f
+    assert [r["config"] for r in got["per_config"]] == [1, 2, 3, 4]
