@@ -7,6 +7,7 @@ the calls raise.
 from __future__ import annotations
 
 import ctypes
+import operator
 import os
 from typing import Optional, Sequence, Tuple
 
@@ -164,10 +165,16 @@ def _dev_check(t: torch.Tensor, dtype: torch.dtype, name: str) -> None:
         raise ValueError(f"{name}: need a contiguous {dtype} device tensor, got {t.dtype} on {t.device}")
 
 
-def tensor_key(t: Optional[torch.Tensor]):
-    """What a call is told of a tensor, and what the checks here look at: arguments filled from a tensor hold for another
-    one with the same key, and for no other."""
-    return None if t is None else (t.data_ptr(), t.shape, t.dtype, t.is_cuda, t.is_contiguous())
+_SHAPE_TYPE_PLACE = operator.attrgetter("shape", "dtype", "is_cuda")
+
+
+def tensor_keys(tensors: Sequence[Optional[torch.Tensor]]) -> list:
+    """What calls are told of tensors, and what the checks here look at: arguments filled from them hold for others with the
+    same keys, and for no others.  Attribute by attribute, so that the loops run in C: a pass does this before it launches
+    anything."""
+    held = [t for t in tensors if t is not None]
+    return [[t is None for t in tensors], list(map(torch.Tensor.data_ptr, held)), list(map(_SHAPE_TYPE_PLACE, held)),
+            list(map(torch.Tensor.is_contiguous, held))]
 
 
 STATIC_KMAP_MAX_CELLS = 1 << 24

@@ -84,9 +84,10 @@ class NativePass:
     """The maps and the convolutions of one or more branches over the same points as two native calls: emc2_build_stacks
     (voxelization and every kernel map of every branch, in a handful of launches) and emc2_spconv_list.  The argument
     blocks are filled and checked once, and again by the first pass that finds anything that went into them changed: a
-    context, a capacity, a slot, the layers, a weight layout, or a tensor's address, shape, type, place or contiguity.  Every pass sets the points and frame ids.  The runners are handed in by each call (they own their passes),
-    and so is `route`: the (expert, slot) tensors of a routed batch and, per expert, the tensor that receives the points' batch
-    ids; branch e then takes the scenes of expert e."""
+    context, a capacity, a slot, the layers, a weight layout, or a tensor's address, shape, type, place or contiguity (0.45
+    us a tensor: 20-30 us of host time a pass of the 64-beam backbone, which a replayed graph does not pay).  Every pass sets the points and frame
+    ids.  The runners are handed in by each call (they own their passes), and so is `route`: the (expert, slot) tensors of a
+    routed batch and, per expert, the tensor that receives the points' batch ids; branch e then takes the scenes of expert e."""
 
     def __init__(self):
         self.stacks = self.calls = None
@@ -117,11 +118,11 @@ class NativePass:
         self.stacks = stacks
 
     def maps(self, runners: Sequence["BranchRunner"], points: torch.Tensor, batch: Optional[torch.Tensor],
-             route: Optional[Sequence[torch.Tensor]] = None) -> None:
+             route: Optional[Sequence[torch.Tensor]] = None) -> list:
+        """Issues the maps; returns the map key of the runners, for convs()."""
         n_points, _ = B.check_points(points, batch)
-        of = [v for r in runners for v in r.map_key()]
-        if route is not None:
-            of += [n_points, *(B.tensor_key(t) for t in route)]
+        key = self._map_key(runners)
+        of = key if route is None else [key, n_points, B.tensor_keys(route)]
         if of != self.stacks_of:
             self.stacks_of = None
             self._fill_stacks(runners, route, n_points)
@@ -129,22 +130,27 @@ class NativePass:
         for s in self.stacks:
             s.d_batch = batch.data_ptr() if batch is not None else None
         B.build_stacks(self.stacks, len(runners), points)
+        return key
 
-    def convs(self, runners: Sequence["BranchRunner"]) -> List[torch.Tensor]:
-        held = [t for r in runners for t in r.conv_tensors()]
-        of = [v for r in runners for v in r.conv_key()] + [B.tensor_key(t) for t in held]
+    @staticmethod
+    def _map_key(runners: Sequence["BranchRunner"]) -> list:
+        return [r.map_key() for r in runners] + B.tensor_keys([t for r in runners for t in r.map_tensors()])
+
+    def convs(self, runners: Sequence["BranchRunner"], map_key: Optional[list] = None) -> List[torch.Tensor]:
+        """`map_key`: what maps() of the same pass returned."""
+        tensors = [t for r in runners for t in r.conv_tensors()]
+        of = [self._map_key(runners) if map_key is None else map_key, [r.conv_key() for r in runners], B.tensor_keys(tensors)]
         if of != self.calls_of:
             self.calls_of = None
             calls = [c for r in runners for c in r.conv_calls()]
             self.calls = (B.ConvCallC * len(calls))(*calls)
-            self.calls_of, self.held = of, tuple(held)
+            self.calls_of, self.held = of, tuple(tensors) + tuple(t for r in runners for t in r.map_tensors())
         B.spconv_list(self.calls, len(self.calls))
         return [r.acts[-1] if r.acts else r.conv_input() for r in runners]
 
     def run(self, runners: Sequence["BranchRunner"], points: torch.Tensor, batch: Optional[torch.Tensor],
             route: Optional[Sequence[torch.Tensor]] = None) -> List[torch.Tensor]:
-        self.maps(runners, points, batch, route)
-        return self.convs(runners)
+        return self.convs(runners, self.maps(runners, points, batch, route))
 
 
 class BranchRunner:
@@ -212,11 +218,16 @@ class BranchRunner:
         return self.feats32 if self.dtype == F32 else self.feats_lp
 
     def map_key(self) -> list:
-        """Everything that voxelization and the kernel maps are told of this branch, the points and frame ids apart."""
-        k = B.tensor_key
-        out = [self.ctx.h.value if self.ctx.h else None, self.dtype, self.branch.spec, k(self.feats32), k(self.counts), k(self.feats_lp)]
+        """Everything but the tensors that voxelization and the kernel maps are told of this branch, the points and frame
+        ids apart."""
+        return [self.ctx.h.value if self.ctx.h else None, self.dtype, self.branch.spec,
+                *((lv.cap, lv.slot, lv.grid) for lv in self.levels)]
+
+    def map_tensors(self) -> List[Optional[torch.Tensor]]:
+        """Every tensor that voxelization and the kernel maps write (None where there is none)."""
+        out = [self.feats32, self.counts, self.feats_lp]
         for lv in self.levels:
-            out += [lv.cap, lv.slot, lv.grid, k(lv.coords), k(lv.n), k(lv.subm_nbr), k(lv.down_nbr)]
+            out += [lv.coords, lv.n, lv.subm_nbr, lv.down_nbr]
         return out
 
     def check_maps(self) -> int:
@@ -235,17 +246,14 @@ class BranchRunner:
         return lp_dtype
 
     def conv_key(self) -> list:
-        """Everything but the tensors that the convolutions are told of this branch."""
-        return [self.ctx.h.value if self.ctx.h else None, self.dtype, self.branch.layers, [lay for _, lay in self.wdev],
-                [lv.cap for lv in self.levels]]
+        """What the convolutions are told of this branch beside the map key and their tensors."""
+        return [self.branch.layers, [lay for _, lay in self.wdev]]
 
-    def conv_tensors(self) -> List[Optional[torch.Tensor]]:
-        """Every tensor that the convolutions read or write (None where a level has no such map)."""
-        out = [self.conv_input(), *self.acts]
+    def conv_tensors(self) -> List[torch.Tensor]:
+        """Every tensor that the convolutions read or write beside the levels' counts and maps and the means."""
+        out = list(self.acts)
         for (w, _), p, layer in zip(self.wdev, self.params, self.branch.layers):
             out += [w, p["scale"], p["shift"]] if layer.epilogue != EPI_NONE else [w]
-        for lv in self.levels:
-            out += [lv.n, lv.subm_nbr, lv.down_nbr]
         return out
 
     def conv_calls(self) -> List["B.ConvCallC"]:
