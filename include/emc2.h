@@ -147,7 +147,7 @@ emc2_status emc2_build_kmap(emc2_ctx* ctx, emc2_conv_kind kind, const int32_t* d
 /*
  * Voxelization and every kernel map of one or more stacks (a stack = one voxel grid and its stride-2 levels) over the same
  * points, in one call: the buffers and index slots receive what emc2_voxelize followed by emc2_build_kmap per level (in_slot /
- * out_slot = the levels' slots) would leave in them, in 6 to 8 launches altogether instead of 6 per level and map.
+ * out_slot = the levels' slots) would leave in them, in 5 to 8 launches altogether instead of 6 per level and map.
  *   level[0].d_down_nbr must be NULL (nothing lies below it); level[l].d_down_nbr is the stride-2 map from level l - 1 into
  *   level l; level[l].d_subm_nbr is the submanifold map of level l or NULL if no layer needs it.
  *   expert < 0: d_batch as for emc2_voxelize.  expert 0..2: the stack takes the points of the scenes routed to `expert` only:

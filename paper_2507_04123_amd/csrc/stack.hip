@@ -9,18 +9,18 @@
 //   phase   finest level (0)                  level l >= 1, built from level l - 1
 //   1       clear flagged lines; zero the scan's sums of all levels
 //   2       mark the points' cells
-//   3       popcount sums (not of 1-4 tiles)  gather 1
-//   4       prefix fields                   gather 2, expand 1
-//   5       points -> stashes               gather 3, expand 2
-//   6       means                           gather 4, expand 3
-//   7                                       expand 4
+//   3       popcount sums (over 4 tiles)      gather 1
+//   4       prefix fields                     gather 2, expand 1
+//   5       points -> stashes                 gather 3, expand 2
+//   6       means                             gather 4, expand 3
+//   7                                         expand 4
 //   last    kernel maps of all levels: once the last level is expanded, with the means for up to three levels
+// A phase in which no stack has anything to do is not launched.
 //
 // gather l: a coarse word is read off the fine level's bits (27 cells behind every coarse cell: nine bit rows OR-ed, then
 // one shift-or and an even-bit compress), so no atomics are needed, nothing has to be cleared first, and the word's
 // popcount joins the scan's sums in the same pass.  expand l: prefix fields and coordinates in one pass.
-// A frame of 120 000 points through four levels: 207 us in 28 launches before, 7 launches now (times beside the table
-// of the launcher below).
+// A frame of 120 000 points through four levels: 28 launches before, 7 now.
 #include <string.h>
 
 #include "kmap_probe.h"
@@ -359,11 +359,11 @@ __device__ __forceinline__ void role_gather(const DevStack& st, int l, uint32_t 
         const int xs = 2 * ox0 - 1 < 0 ? 0 : 2 * ox0 - 1;
         const int xe = 2 * ox1 + 1 < in.g[0] ? 2 * ox1 + 1 : in.g[0] - 1;
         const uint64_t rb = ((b * in.g[2] + (uint64_t)iz) * in.g[1] + (uint64_t)iy) * in.g[0];
-        // at most 512 output cells of a row, so at most 1 025 input cells: they touch up to four lines
+        // at most 512 output cells of a row, so at most 1 025 input cells: they touch up to three lines of 512
         const uint64_t f0 = emc2_line_of_key(rb + (uint64_t)xs), f1 = emc2_line_of_key(rb + (uint64_t)xe);
         uint32_t f = 0;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) f |= in.flags[f0 + q < f1 ? f0 + q : f1];
+        for (int q = 0; q < 3; ++q) f |= in.flags[f0 + q < f1 ? f0 + q : f1];
         any |= f != 0u;
       }
     }
