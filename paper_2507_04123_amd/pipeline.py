@@ -85,9 +85,10 @@ class NativePass:
     (voxelization and every kernel map of every branch, in a handful of launches) and emc2_spconv_list.  The argument
     blocks are filled and checked once, and again by the first pass that finds anything that went into them changed: a
     context, a capacity, a slot, the layers, a weight layout, or a tensor's address, shape, type, place or contiguity (0.45
-    us a tensor: 20-30 us of host time a pass of the 64-beam backbone, which a replayed graph does not pay).  Every pass sets the points and frame
-    ids.  The runners are handed in by each call (they own their passes), and so is `route`: the (expert, slot) tensors of a
-    routed batch and, per expert, the tensor that receives the points' batch ids; branch e then takes the scenes of expert e."""
+    us a tensor: 20-30 us of host time a pass of the 64-beam backbone, which a replayed graph does not pay).  Every pass
+    sets the points and frame ids.  The runners are handed in by each call (they own their passes), and so is `route`: the
+    (expert, slot) tensors of a routed batch and, per expert, the tensor that receives the points' batch ids; branch e then
+    takes the scenes of expert e."""
 
     def __init__(self):
         self.stacks = self.calls = None
