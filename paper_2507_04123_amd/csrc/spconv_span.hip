@@ -1,23 +1,34 @@
-// Span-gather variant of the MFMA sparse convolution (paper Sec. 3.5 sparse convolution over the
+// Submanifold convolution on the matrix cores, rows staged by producer waves (paper Sec. 3.5 sparse convolution over the
 // non-empty voxels; Sec. 3.6 keeping data on chip between dependent steps).
 //
-// Voxels are indexed in ascending order of their linear cell key (x fastest).  The three taps of one
-// (dz, dy) pair -- kx = 0, 1, 2 -- therefore read input rows that differ by one position along x: for a
-// run of 64 consecutive output rows they touch nearly the same short interval [lo, hi] of input rows
-// (in a submanifold layer 66 rows at the median).  This kernel fetches that interval ONCE per group of
-// three taps, as one contiguous block of feature rows, into a wave-private LDS tile; each tap then
-// reads its A operand from the tile through a per-lane row index (kernel-map entry minus lo).  Absent
-// neighbours point at a zeroed row of the tile.  Compared with one gather per tap this moves ~2.5x
-// fewer bytes through the vector L1 / L2 and writes the LDS tile once instead of three times.
+// Voxels are indexed in ascending order of their linear cell key (x fastest).  The three taps of one (dz, dy) pair -- a
+// group, kx = 0, 1, 2 -- therefore read input rows that differ by one position along x: for a run of consecutive output
+// rows they touch nearly the same short interval [lo, hi] of input rows.  A block owns a tile of 64 * MT consecutive output
+// rows and fetches that interval ONCE per group, as one contiguous run of feature rows, into LDS; each tap then reads its
+// operand from there through a per-row offset.  Absent neighbours read a zeroed row.
 //
-// When the interval does not fit the tile (kernel maps of strided layers; a few percent of the
-// groups elsewhere) the group falls back to three passes, one per tap, each gathering exactly the 64
-// rows its tap names.  Results never depend on which mode a group took: the mode is chosen from the
-// table entries themselves, and every entry is range-checked against the tile before use.
+// What bounds it and why the work is split this way.  The same kernel with every wave doing everything (rows through
+// registers into a tile of its own) spent 42 % of a wave's time in the matrix phase: issuing the loads of the next group
+// stalled a wave for 1 100-1 500 cycles (a CU takes a 1 KB load every ~20 cycles, and an in-order wave cannot issue matrix
+// instructions behind a load that has not been accepted), moving the rows into LDS cost 650-840 more, analysis and weight
+// copies 350, the barrier 550.  Here four waves (one per SIMD) only compute and four only feed them: the producers find the
+// intervals, turn kernel-map entries into LDS offsets, and move rows and weights to LDS with direct global -> LDS loads, one
+// pass ahead.  The computing waves hold 16 * MT rows by COUT columns of accumulators each and read nothing but LDS.  A block
+// stays and walks over its tiles, so that a tile's first pass is fetched while the last tile's results are stored.
+// What a pass of 384 rows costs now: 3 000 cycles of computing (144 matrix instructions, 2 304 if back to back), against
+// ~3 500 of feeding it: the loads into LDS (74 KB at about 16 cycles each) share the LDS with the operand reads (240 KB at
+// 8.5), which the two together keep busy for ~3 300.  Tried against it: the 32x32x16 instructions (computing 2 750, feeding
+// the same: no gain), weights straight from global memory into registers (longer: the vector-memory path takes them at the
+// rate of the rows), separate waves for loads and for the map (2 + 2: a wave issues a load into LDS only every ~100 cycles),
+// the map read by the computing waves (spills), an order of tiles that keeps neighbouring planes in one L2 (no gain).
+// 64 -> 64, us before / now: 70 k rows 33 / 25-27, 223 k 65 / 58, 248 k bf16 71 / 59, 573 k 142 / 107, 852 k 210 / 163.
 //
-// Block = 8 waves (one per 64 output rows, or fewer in the last round) sharing the weights of a group (3 taps) in a double-buffered
-// LDS area: one block-wide barrier per group.  All global loads of a group are issued in one burst
-// right after the tile has been written, a whole group (thousands of cycles) before their first use.
+// One pass is what is computed between two barriers.  Normally a group is one pass.  A group whose interval does not fit
+// the row buffer is split into two passes of half of the tile's rows if each half's interval fits (next to a denser plane
+// the interval is up to twice the rows), else into three passes, one per tap, that gather exactly the rows the tap names.
+// Rows and taps that are not a pass's own read the zeroed row, so that there is one form of the matrix code (branches
+// around it make the compiler keep two copies of the accumulators).  Results never depend on which: an output row adds its
+// taps in ascending order in all three forms.
 #include <hip/hip_bf16.h>
 #include <hip/hip_fp16.h>
 
@@ -28,6 +39,9 @@ namespace {
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 half2v __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));   // native vector: real loads and stores
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
@@ -37,447 +51,468 @@ template <> struct MmaS<EMC2_F16> {
   static __device__ __forceinline__ floatx4 run(u32x4 a, u32x4 b, floatx4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, a), __builtin_bit_cast(half8, b), c, 0, 0, 0);
   }
-  static __device__ __forceinline__ uint16_t cvt(float v) { return __half_as_ushort(__float2half_rn(v)); }
+  static __device__ __forceinline__ uint32_t cvt2(float x, float y) {   // round to nearest even
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2{x, y}), half2v));
+  }
 };
 template <> struct MmaS<EMC2_BF16> {
   static __device__ __forceinline__ floatx4 run(u32x4 a, u32x4 b, floatx4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
   }
-  static __device__ __forceinline__ uint16_t cvt(float v) { return __builtin_bit_cast(uint16_t, __float2bfloat16(v)); }
-};
-
-constexpr int kSpanWaves = 8;
-constexpr int kSpanThreads = kSpanWaves * 64;
-constexpr int kSpanCUs = 256;   // compute units of the part; one block of this kernel fits each
-
-template <int CIN> struct SpanCfg {
-  // rows of the LDS tile (a multiple of the rows one load instruction covers); sized so that 8 tiles and
-  // two weight buffers fit the 160 KB of LDS
-  static constexpr int SMAX = 80;
-  // waves per SIMD the register allocator must leave room for
-  static constexpr int MINW = 2;
-};
-
-// What a group of three taps needs from the input: the interval [lo, hi] of rows its valid entries name
-// (wave-uniform), and whether every valid entry lies inside [lo, lo + SMAX).
-struct GroupInfo {
-  int32_t lo, hi;
-  bool span;
-  uint32_t rows;   // span mode: rows of the interval that hold data (0 for a group without a valid entry)
-  unsigned long long valid[3];
-};
-
-template <int SMAX>
-__device__ __forceinline__ GroupInfo analyze(const int32_t j[3]) {
-  GroupInfo gi;
-  int32_t lo = 0x7fffffff, hi = 0;
-#pragma unroll
-  for (int kx = 0; kx < 3; ++kx) {
-    const unsigned long long mk = __ballot(j[kx] >= 0);
-    gi.valid[kx] = mk;
-    // a table from emc2_build_kmap is ascending in the row index wherever it is valid, so the first and last
-    // valid lanes hold the extremes; in any other table some entry falls outside [lo, hi], fails the range
-    // check below, and the group takes the three-pass route
-    const int first = mk ? __builtin_ctzll(mk) : 0;
-    const int last = mk ? 63 - __builtin_clzll(mk) : 0;
-    const int32_t vf = __builtin_amdgcn_readlane(j[kx], first);
-    const int32_t vl = __builtin_amdgcn_readlane(j[kx], last);
-    if (mk) {
-      lo = vf < lo ? vf : lo;
-      hi = vl > hi ? vl : hi;
-    }
+  static __device__ __forceinline__ uint32_t cvt2(float x, float y) {
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2{x, y}), bf16x2));
   }
-  if (lo == 0x7fffffff) lo = 0;
-  if (hi < lo) hi = lo;
-  // rows past hi are not fetched (the gather clamps to hi), so an entry is usable in span mode only inside
-  // [lo, hi], and the interval must fit the tile
-  const uint32_t width = (uint32_t)(hi - lo);
-  unsigned long long bad = width >= (uint32_t)SMAX ? ~0ull : 0ull;
-#pragma unroll
-  for (int kx = 0; kx < 3; ++kx) bad |= __ballot(j[kx] >= 0 && (uint32_t)(j[kx] - lo) > width);
-  gi.lo = lo;
-  gi.hi = hi;
-  gi.span = bad == 0ull;
-  gi.rows = (gi.valid[0] | gi.valid[1] | gi.valid[2]) != 0ull ? width + 1u : 0u;
-  return gi;
+};
+
+constexpr int kSpanThreads = 512;    // waves 0-3 compute, waves 4-7 feed them
+constexpr int64_t kSpanCUs = 256;    // compute units of the part; one block fits each
+constexpr int kSpanRows = 400;       // rows of one of the two row buffers: what the LDS holds beside the rest
+
+template <int CIN, int COUT> struct SpanLds {
+  static constexpr int W16 = (CIN / 32) * (COUT / 16) * 64;   // 16-byte weight pieces per tap
+  static constexpr int CH = CIN / 8;                          // 16-byte pieces per feature row
+  u32x4 w[2][3 * W16];               // weights of a group
+  u32x4 rows[2][(kSpanRows + 1) * CH];   // rows of a pass; row kSpanRows is zero
+  uint16_t off[2][4][16][6][4];      // [pass][computing wave][m][mt][tap]: where output row 64*mt + 16*wave + m reads
+  u32x2 part[2][9][4][6];            // [tile][group][producer][mt]: lowest and highest row named (0xffffffff, -1: none)
+  float scale[COUT], shift[COUT];
+};
+
+// Pieces of a row are swapped about so that 16 consecutive rows, read at the same piece, fall on the 16 different 16-byte
+// columns of the 64 banks.
+template <int CH> __device__ __forceinline__ uint32_t swizzle_of(uint32_t row) { return (row / (16 / CH)) % CH; }
+
+__device__ __forceinline__ uint32_t lane_id() { return threadIdx.x & 63; }
+
+// The barrier between passes.  A wave has its LDS accesses behind it when it arrives, and a producer, which calls
+// loads_done() first, its loads into LDS; stores of results and loads of kernel-map entries stay in flight.
+__device__ __forceinline__ void sync_all() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+__device__ __forceinline__ void loads_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+__device__ __forceinline__ void load_to_lds16(const void* src_lane, u32x4* dst_wave) {
+  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src_lane,
+                                   (__attribute__((address_space(3))) void*)dst_wave, 16, 0, 0);
 }
 
-// The main loop of one wave.  LATE = false: a group's interval is  [tile write, request loads] -> compute;
-// LATE = true:  compute -> [tile write for the next group, request loads for the one after].  Both kinds
-// meet at the same block-wide barrier once per group, but between two barriers they do their memory
-// phase and their matrix phase in opposite order, so the two waves that share a SIMD (wave w and w + 4)
-// do not both want the LDS / the load path / the matrix core at the same time.
-template <int DT, int CIN, int COUT, int MT, bool LATE>
-__device__ __forceinline__ void span_wave(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp,
-                                          const float* __restrict__ scale, const float* __restrict__ shift, int epilogue,
-                                          const int32_t* __restrict__ nbr, int64_t n_out, int64_t capacity_out,
-                                          int32_t n_in, int32_t* __restrict__ dev_flags,
-                                          uint16_t* __restrict__ out, u32x4* __restrict__ wl, u32x4* __restrict__ my_tile,
-                                          int64_t wave_row0) {
-  constexpr int KS = CIN / 32;                // k-steps per tap (v_mfma_f32_16x16x32)
-  constexpr int NT = COUT / 16;               // 16-column tiles
-  constexpr int R = 16 * MT;                  // rows per wave (MT 16-row tiles)
-  constexpr int W16 = KS * NT * 64;           // 16-byte weight pieces per tap
-  constexpr int G16 = 3 * W16;                // ... per group of three taps
-  constexpr int WPT = (G16 + kSpanThreads - 1) / kSpanThreads;
-  constexpr int CH = CIN / 8;                 // 16-byte chunks per feature row
-  constexpr int RPI = 64 / CH;                // rows covered by one load instruction
-  constexpr int SMAX = SpanCfg<CIN>::SMAX;
-  constexpr int NI = SMAX / RPI;              // load instructions per gather
-  constexpr int ROW16 = CH + 1;               // LDS row pitch in 16-byte units (one unit of padding)
-  constexpr int ZROW = SMAX;                  // the zeroed row absent neighbours read
+// minimum / maximum over each row of 16 lanes
+__device__ __forceinline__ uint32_t row_min(uint32_t v) {
+  v = min(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x128, 0xf, 0xf, true));
+  v = min(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x124, 0xf, 0xf, true));
+  v = min(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x122, 0xf, 0xf, true));
+  return min(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x121, 0xf, 0xf, true));
+}
+__device__ __forceinline__ int32_t row_max(int32_t v) {
+  v = max(v, __builtin_amdgcn_mov_dpp(v, 0x128, 0xf, 0xf, true));
+  v = max(v, __builtin_amdgcn_mov_dpp(v, 0x124, 0xf, 0xf, true));
+  v = max(v, __builtin_amdgcn_mov_dpp(v, 0x122, 0xf, 0xf, true));
+  return max(v, __builtin_amdgcn_mov_dpp(v, 0x121, 0xf, 0xf, true));
+}
 
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int m = lane & 15, q = lane >> 4;
-  if (lane < ROW16) my_tile[ZROW * ROW16 + lane] = u32x4{0u, 0u, 0u, 0u};
+// How a tile's nine groups are run; the same in every wave.  Lanes 4g .. 4g+3 hold group g; the masks have its bit at 4g.
+struct Plan {
+  uint32_t lo_a, lo_b;            // intervals of the tile's first and second half (lane 4g: group g)
+  int32_t hi_a, hi_b;
+  unsigned long long any, one, two;   // some entry; one pass; two passes (neither: three)
+};
 
-  const bool live = lane < R && wave_row0 + lane < n_out;
-  const int32_t* nrow = nbr + (live ? wave_row0 + lane : 0);
-  const int32_t dead = live ? 0 : -1;               // rows past n_out have no neighbours
-  unsigned long long oob = 0ull;                    // lanes that saw an entry outside [0, n_in)
-  const int srow = lane / CH, schunk = lane % CH;   // gather role: row within an instruction, 16-byte chunk
-
-  floatx4 acc[MT][NT];
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-    for (int j = 0; j < NT; ++j) acc[mt][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-
-  // kernel-map entries (lane = row) of the group being computed, the next, and (LATE) the one after, as
-  // loaded: rows past n_out are masked where the entries are used, never right after the load (that would
-  // wait for the load at once)
-  int32_t jq0[3], jq1[3], jq2[3];
-  u32x4 sreg[NI];           // gathered rows in flight (an instruction that is skipped leaves its slot as it was)
-#pragma unroll
-  for (int i = 0; i < NI; ++i) sreg[i] = u32x4{0u, 0u, 0u, 0u};
-  u32x4 wq[WPT];            // weights in flight
-
-#define EMC2_IDX_LOAD(GROUP, DST)                                                                          \
-  _Pragma("unroll") for (int kx_ = 0; kx_ < 3; ++kx_)                                                      \
-      DST[kx_] = nrow[(int64_t)(3 * ((GROUP) < 9 ? (GROUP) : 8) + kx_) * capacity_out];
-#define EMC2_MASKED(C, J)                                                                                  \
-  const int32_t C[3] = {emc2_entry(J[0], dead, n_in, oob), emc2_entry(J[1], dead, n_in, oob),              \
-                        emc2_entry(J[2], dead, n_in, oob)};
-#define EMC2_W_LOAD(GROUP)                                                                                 \
-  {                                                                                                        \
-    const u32x4* wsrc_ = wp + (int64_t)((GROUP) < 9 ? (GROUP) : 8) * G16;                                  \
-    _Pragma("unroll") for (int i_ = 0; i_ < WPT; ++i_) {                                                   \
-      const int p_ = tid + i_ * kSpanThreads;                                                              \
-      wq[i_] = wsrc_[p_ < G16 ? p_ : G16 - 1];                                                             \
-    }                                                                                                      \
-  }
-#define EMC2_W_STORE(BUF)                                                                                  \
-  _Pragma("unroll") for (int i_ = 0; i_ < WPT; ++i_) {                                                     \
-    const int p_ = tid + i_ * kSpanThreads;                                                                \
-    wl[(BUF) * G16 + (p_ < G16 ? p_ : G16 - 1)] = wq[i_]; /* surplus threads rewrite the last piece */     \
-  }
-  // gather of the interval [lo, hi] (rows past hi re-read row hi and are never referenced)
-#define EMC2_GATHER_SPAN(GI)                                                                               \
-  {                                                                                                        \
-    /* wave-uniform base (scalar registers) + a small per-lane byte offset */                              \
-    const char* base_ = reinterpret_cast<const char*>(in) + (int64_t)(GI).lo * (CIN * 2);                  \
-    const uint32_t last_ = (uint32_t)((GI).hi - (GI).lo);                                                  \
-    _Pragma("unroll") for (int i_ = 0; i_ < NI; ++i_) {                                                    \
-      /* wave-uniform: an instruction none of whose rows holds data is not issued (its tile rows are never read) */ \
-      if ((uint32_t)(i_ * RPI) < (GI).rows) {                                                              \
-        const uint32_t p_ = (uint32_t)(i_ * RPI + srow);                                                   \
-        const uint32_t off_ = (p_ < last_ ? p_ : last_) * (uint32_t)(CIN * 2) + (uint32_t)(schunk * 16);   \
-        sreg[i_] = *reinterpret_cast<const u32x4*>(base_ + off_);                                          \
-      }                                                                                                    \
-    }                                                                                                      \
-  }
-  // gather of exactly the rows one tap names: tile row p <- input row JROW[p] (absent entries re-read row 0)
-#define EMC2_GATHER_TAP(JROW)                                                                              \
-  _Pragma("unroll") for (int i_ = 0; i_ < NI; ++i_) {                                                      \
-    if (i_ * RPI < R) { /* compile time: a tap names R rows */                                             \
-      const int p_ = i_ * RPI + srow;                                                                      \
-      const int32_t j_ = __shfl((JROW), p_, 64);                                                           \
-      sreg[i_] = *(reinterpret_cast<const u32x4*>(in + (int64_t)(j_ >= 0 ? j_ : 0) * CIN) + schunk);       \
-    }                                                                                                      \
-  }
-#define EMC2_GATHER_MAIN(GI, J)                                                                            \
-  if ((GI).span) { EMC2_GATHER_SPAN(GI) } else { EMC2_GATHER_TAP((J)[0]) }
-  // registers -> tile, the first ROWS rows (wave-uniform; whole instructions)
-#define EMC2_TILE_WRITE_N(ROWS)                                                                            \
-  _Pragma("unroll") for (int i_ = 0; i_ < NI; ++i_)                                                        \
-    if ((uint32_t)(i_ * RPI) < (uint32_t)(ROWS)) my_tile[(i_ * RPI + srow) * ROW16 + schunk] = sreg[i_];
-  // ... what the main gather of group GI left in the registers: its interval, or the R rows of its first tap
-#define EMC2_TILE_WRITE(GI) EMC2_TILE_WRITE_N((GI).span ? (GI).rows : (uint32_t)R)
-  // Issue order inside a tap (KS = 2, MT = NT = 4: 16 operand reads, 32 matrix instructions): operands are read one
-  // to two row tiles ahead of the matrix instructions that use them, so that after the first six reads of a tap a
-  // read's latency falls under the four matrix instructions before its use.
-#define EMC2_TAP_ORDER()                                                                                   \
-  if (KS == 2 && MT == 4 && NT == 4) {                                                                     \
-    __builtin_amdgcn_sched_group_barrier(0x100, 6, 0); /* b0..b3, a0, a1 of the first k-step */            \
-    __builtin_amdgcn_sched_group_barrier(0x008, 4, 0); __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);  \
-    __builtin_amdgcn_sched_group_barrier(0x008, 4, 0); __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);  \
-    __builtin_amdgcn_sched_group_barrier(0x008, 4, 0); __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);  \
-    __builtin_amdgcn_sched_group_barrier(0x008, 4, 0); __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  \
-    __builtin_amdgcn_sched_group_barrier(0x008, 4, 0); __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  \
-    __builtin_amdgcn_sched_group_barrier(0x008, 4, 0); __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  \
-    __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);                                                     \
-  }
-  // one tap: lane l's LROW is the tile row that output row l of the wave reads.  The A operand of lane
-  // (m, q) for tile mt is 16 bytes at piece 4*ks + q of tile row LROW[16*mt + m]: three lane-swap
-  // instructions broadcast each 16-lane row of LROW to all four rows (no LDS round trip).
-#define EMC2_TAP(KX, LROW, WB)                                                                             \
-  {                                                                                                        \
-    const uint32_t lr_ = (uint32_t)(LROW);                                                                 \
-    const u32x2 h_ = __builtin_amdgcn_permlane32_swap(lr_, lr_, false, false);        /* rows 0101 | 2323 */ \
-    const u32x2 lo_ = __builtin_amdgcn_permlane16_swap(h_[0], h_[0], false, false);   /* 0000 | 1111 */    \
-    const u32x2 hi_ = __builtin_amdgcn_permlane16_swap(h_[1], h_[1], false, false);   /* 2222 | 3333 */    \
-    const u32x4* ap_[4] = {my_tile + lo_[0] * ROW16 + q, my_tile + lo_[1] * ROW16 + q,                     \
-                           my_tile + hi_[0] * ROW16 + q, my_tile + hi_[1] * ROW16 + q};                    \
-    _Pragma("unroll") for (int t = 0; t < KS; ++t) {                                                       \
-      u32x4 b[NT], a[MT];                                                                                  \
-      _Pragma("unroll") for (int j = 0; j < NT; ++j) b[j] = (WB)[(((KX) * KS + t) * NT + j) * 64 + lane];  \
-      _Pragma("unroll") for (int mt = 0; mt < MT; ++mt) a[mt] = ap_[mt][4 * t];                            \
-      _Pragma("unroll") for (int mt = 0; mt < MT; ++mt)                                                    \
-        _Pragma("unroll") for (int j = 0; j < NT; ++j) acc[mt][j] = MmaS<DT>::run(a[mt], b[j], acc[mt][j]); \
-    }                                                                                                      \
-    EMC2_TAP_ORDER()                                                                                       \
-  }
-  // Tile row that output row `lane` reads at tap KX.  Span mode: entry minus lo.  Three-pass mode: the
-  // tile holds exactly the rows of the tap being computed, row p for output row p.
-#define EMC2_LROW(KX, C, GI) ((C)[KX] >= 0 ? ((GI).span ? (C)[KX] - (GI).lo : lane) : ZROW)
-  // The three taps are straight-line code: with branches between the matrix instructions of a group the
-  // compiler keeps two copies of the accumulators and moves 64 registers back and forth at every join.
-  // Only the memory operations of the (rare) three-pass mode are conditional inside a group.
-#define EMC2_COMPUTE(C, GI, NXT, CNXT, WB)                                                                 \
-  {                                                                                                        \
-    __builtin_amdgcn_s_setprio(2);                                                                         \
-    { const int32_t lrow_ = EMC2_LROW(0, C, GI); EMC2_TAP(0, lrow_, WB) }                                  \
-    __builtin_amdgcn_wave_barrier();                                                                       \
-    if (!(GI).span) { EMC2_TILE_WRITE_N(R) EMC2_GATHER_TAP((C)[2]) }                                          \
-    __builtin_amdgcn_wave_barrier();                                                                       \
-    { const int32_t lrow_ = EMC2_LROW(1, C, GI); EMC2_TAP(1, lrow_, WB) }                                  \
-    __builtin_amdgcn_wave_barrier();                                                                       \
-    if (!(GI).span) { EMC2_TILE_WRITE_N(R) EMC2_GATHER_MAIN(NXT, CNXT) }                                      \
-    __builtin_amdgcn_wave_barrier();                                                                       \
-    { const int32_t lrow_ = EMC2_LROW(2, C, GI); EMC2_TAP(2, lrow_, WB) }                                  \
-    __builtin_amdgcn_s_setprio(0);                                                                         \
-  }
-  // prologue.  The analyses of the groups (wave-uniform, ~80 scalar instructions each) are carried from
-  // iteration to iteration, one new analysis per group, always of entries loaded a whole group earlier.
-  EMC2_IDX_LOAD(0, jq0)
-  EMC2_IDX_LOAD(1, jq1)
-  EMC2_W_LOAD(0)
-  EMC2_W_STORE(0)
-  GroupInfo cur, nxt, aft;
-  {
-    EMC2_MASKED(c0, jq0)
-    EMC2_MASKED(c1, jq1)
-    cur = analyze<SMAX>(c0);
-    nxt = analyze<SMAX>(c1);
-    aft = nxt;
-    EMC2_GATHER_MAIN(cur, c0)
-    if constexpr (LATE) {
-      // one interval ahead on the memory side: first pass of group 0 in the tile, next pass requested
-      EMC2_TILE_WRITE(cur)
-      EMC2_IDX_LOAD(2, jq2)
-      EMC2_W_LOAD(1)
-      if (cur.span) { EMC2_GATHER_MAIN(nxt, c1) } else { EMC2_GATHER_TAP(c0[1]) }
-    }
-  }
-  __syncthreads();
-
-  for (int g = 0; g < 9; ++g) {
-    const u32x4* wb = wl + (g & 1) * G16;
-    EMC2_MASKED(c0, jq0)
-    EMC2_MASKED(c1, jq1)
-    if constexpr (!LATE) {
-      EMC2_TILE_WRITE(cur)                    // rows of group g, requested during group g - 1
-      // requests: entries of group g + 2, weights of group g + 1, and the rows of the next pass (group
-      // g + 1, or the second pass of this group if it runs in three passes)
-      EMC2_IDX_LOAD(g + 2, jq2)
-      EMC2_W_LOAD(g + 1)
-      if (cur.span) { EMC2_GATHER_MAIN(nxt, c1) } else { EMC2_GATHER_TAP(c0[1]) }
-      __builtin_amdgcn_wave_barrier();
-      // a group none of whose 192 entries is valid costs no LDS read and no matrix instruction
-      if (((cur.valid[0] | cur.valid[1] | cur.valid[2]) != 0ull) || !cur.span) {
-        EMC2_COMPUTE(c0, cur, nxt, c1, wb)
-      }
-      __builtin_amdgcn_wave_barrier();
-      EMC2_W_STORE((g + 1) & 1)               // weights of group g + 1 -> the LDS buffer group g - 1 used
-      {
-        EMC2_MASKED(c2, jq2)                  // requested at the top of this group
-        cur = nxt;
-        nxt = analyze<SMAX>(c2);
-      }
-    } else {
-      // tile holds group g (first pass); registers hold the rows of the next pass; wq holds W(g + 1)
-      // a group none of whose 192 entries is valid costs no LDS read and no matrix instruction
-      if (((cur.valid[0] | cur.valid[1] | cur.valid[2]) != 0ull) || !cur.span) {
-        EMC2_COMPUTE(c0, cur, nxt, c1, wb)
-      }
-      __builtin_amdgcn_wave_barrier();
-      EMC2_MASKED(c2, jq2)                    // requested at the end of the previous group
-      aft = analyze<SMAX>(c2);
-      EMC2_W_STORE((g + 1) & 1)
-      EMC2_TILE_WRITE(nxt)                    // first pass of group g + 1
-      int32_t jn[3];
-      EMC2_IDX_LOAD(g + 3, jn)
-      EMC2_W_LOAD(g + 2)
-      // rows of the pass after that: second pass of group g + 1 if it runs in three passes, else group g + 2
-      if (nxt.span) { EMC2_GATHER_MAIN(aft, c2) } else { EMC2_GATHER_TAP(c1[1]) }
-      cur = nxt;
-      nxt = aft;
-#pragma unroll
-      for (int kx = 0; kx < 3; ++kx) {
-        jq0[kx] = jq1[kx];
-        jq1[kx] = jq2[kx];
-        jq2[kx] = jn[kx];
-      }
-    }
-    __syncthreads();                          // publishes W(g + 1), retires the buffer just read
-    if constexpr (!LATE) {
-#pragma unroll
-      for (int kx = 0; kx < 3; ++kx) {
-        jq0[kx] = jq1[kx];
-        jq1[kx] = jq2[kx];
-      }
-    }
-  }
-#undef EMC2_IDX_LOAD
-#undef EMC2_MASKED
-#undef EMC2_W_LOAD
-#undef EMC2_W_STORE
-#undef EMC2_GATHER_SPAN
-#undef EMC2_GATHER_TAP
-#undef EMC2_GATHER_MAIN
-#undef EMC2_TILE_WRITE
-#undef EMC2_TILE_WRITE_N
-#undef EMC2_TAP
-#undef EMC2_TAP_ORDER
-#undef EMC2_LROW
-#undef EMC2_COMPUTE
-  emc2_report_oob(oob, dev_flags);
-
-  // epilogue: lane (m, q) holds column 16*j + m of rows 16*mt + 4*q + e.  Scale/shift/ReLU/convert in
-  // registers, then each 16-row tile goes through the wave's LDS tile so that the global stores are whole
-  // 16-byte pieces of rows.
-  float sc[NT], sh[NT];
-#pragma unroll
-  for (int j = 0; j < NT; ++j) {
-    sc[j] = (epilogue != EMC2_EPI_NONE) ? scale[16 * j + m] : 1.f;
-    sh[j] = (epilogue != EMC2_EPI_NONE) ? shift[16 * j + m] : 0.f;
-  }
-  uint16_t* otile = reinterpret_cast<uint16_t*>(my_tile);
-  constexpr int OCH = COUT / 8;               // 16-byte pieces per output row
-  constexpr int OPITCH = (OCH + 1) * 8;       // LDS row pitch in 16-bit units
-  constexpr int OPI = 64 / OCH;               // rows one store instruction covers
-  constexpr int ONI = (16 + OPI - 1) / OPI;   // store instructions per 16-row tile
-  static_assert(16 * (OCH + 1) <= (SMAX + 1) * ROW16, "a 16-row output tile fits the gather tile");
-  const int orow = lane / OCH, ochunk = lane % OCH;
+template <int MT, int TR>
+__device__ __forceinline__ Plan make_plan(const u32x2 (*part)[4][6]) {
+  constexpr int H = (MT + 1) / 2;
+  const uint32_t l = lane_id() < 36 ? lane_id() : 35;
+  Plan p;
+  p.lo_a = p.lo_b = 0xffffffffu;
+  p.hi_a = p.hi_b = -1;
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) {
-#pragma unroll
-    for (int j = 0; j < NT; ++j) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        float v = acc[mt][j][e];
-        if (epilogue != EMC2_EPI_NONE) v = fmaf(v, sc[j], sh[j]);
-        if (epilogue == EMC2_EPI_AFFINE_RELU) v = v > 0.f ? v : 0.f;
-        otile[(4 * q + e) * OPITCH + 16 * j + m] = MmaS<DT>::cvt(v);
-      }
+    const u32x2 v = part[l / 4][l % 4][mt];
+    if (mt < H) {
+      p.lo_a = min(p.lo_a, v[0]);
+      p.hi_a = max(p.hi_a, (int32_t)v[1]);
+    } else {
+      p.lo_b = min(p.lo_b, v[0]);
+      p.hi_b = max(p.hi_b, (int32_t)v[1]);
     }
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int i = 0; i < ONI; ++i) {
-      const int r = i * OPI + orow;
-      if (r < 16) {
-        const u32x4 piece = *reinterpret_cast<const u32x4*>(otile + r * OPITCH + ochunk * 8);
-        const int64_t o = wave_row0 + mt * 16 + r;
-        if (o < n_out) *reinterpret_cast<u32x4*>(out + o * COUT + ochunk * 8) = piece;
-      }
-    }
-    __builtin_amdgcn_wave_barrier();
   }
+#define EMC2_QUAD(V, OP, T)                                                                \
+  V = OP(V, (T)__builtin_amdgcn_update_dpp(0, (int)V, 0xB1, 0xf, 0xf, false));             \
+  V = OP(V, (T)__builtin_amdgcn_update_dpp(0, (int)V, 0x4E, 0xf, 0xf, false));
+  EMC2_QUAD(p.lo_a, min, uint32_t) EMC2_QUAD(p.lo_b, min, uint32_t)
+  EMC2_QUAD(p.hi_a, max, int32_t) EMC2_QUAD(p.hi_b, max, int32_t)
+#undef EMC2_QUAD
+  const bool in = lane_id() < 36 && (lane_id() & 3) == 0;
+  const bool a = p.hi_a >= 0, b = p.hi_b >= 0;
+  const uint32_t lo = min(p.lo_a, p.lo_b);
+  const int32_t hi = max(p.hi_a, p.hi_b);
+  p.any = __ballot(in && (a || b));
+  p.one = __ballot(in && (a || b) && (uint32_t)hi - lo < (uint32_t)TR);
+  p.two = __ballot(in && (!a || (uint32_t)p.hi_a - p.lo_a < (uint32_t)TR) && (!b || (uint32_t)p.hi_b - p.lo_b < (uint32_t)TR));
+  return p;
+}
+
+// One pass of a computing wave: three taps of its MT 16-row tiles.  Operands of a step (one tap, 32 channels) are read
+// while the step before is multiplied.  The weights are the first operand, so that a lane ends up with four consecutive
+// channels of one row.
+template <int DT, int CIN, int COUT, int MT>
+__device__ __forceinline__ void compute(const SpanLds<CIN, COUT>& s, uint32_t rb, uint32_t wb, uint32_t wave,
+                                        floatx4 (&acc)[MT][COUT / 16]) {
+  constexpr int KS = CIN / 32, NT = COUT / 16, STEPS = 3 * KS, READS = MT + NT;
+  const uint32_t lane = lane_id(), q16 = (lane >> 4) * 16;
+  const char* rows = reinterpret_cast<const char*>(s.rows[rb]);
+  const u32x4* w = s.w[wb] + lane;
+  u32x2 of[MT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i) of[i] = *reinterpret_cast<const u32x2*>(s.off[rb][wave][lane & 15][i]);
+  u32x4 a[2][MT], b[2][NT];
+#define EMC2_READ(STEP)                                                                                                  \
+  {                                                                                                                      \
+    _Pragma("unroll") for (int j = 0; j < NT; ++j) b[(STEP) & 1][j] = w[((STEP) * NT + j) * 64];                         \
+    _Pragma("unroll") for (int i = 0; i < MT; ++i) {                                                                     \
+      const uint32_t o_ = (STEP) / KS == 0 ? of[i][0] & 0xffffu : (STEP) / KS == 1 ? of[i][0] >> 16 : of[i][1];          \
+      a[(STEP) & 1][i] = *reinterpret_cast<const u32x4*>(rows + (o_ ^ (q16 + 64u * ((STEP) % KS))));                     \
+    }                                                                                                                    \
+  }
+  EMC2_READ(0)
+  __builtin_amdgcn_sched_group_barrier(0x100, MT + READS, 0);
+#pragma unroll
+  for (int st = 0; st < STEPS; ++st) {
+    if (st + 1 < STEPS) EMC2_READ(st + 1)
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+      for (int j = 0; j < NT; ++j) acc[i][j] = MmaS<DT>::run(b[st & 1][j], a[st & 1][i], acc[i][j]);
+    constexpr int PER = MT * NT / READS > 0 ? MT * NT / READS : 1;   // matrix instructions per read
+    if (st + 1 < STEPS) {
+#pragma unroll
+      for (int r = 0; r < READS; ++r) {
+        __builtin_amdgcn_sched_group_barrier(0x008, PER, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      }
+      if (MT * NT > PER * READS) __builtin_amdgcn_sched_group_barrier(0x008, MT * NT - PER * READS, 0);
+    } else {
+      __builtin_amdgcn_sched_group_barrier(0x008, MT * NT, 0);
+    }
+  }
+#undef EMC2_READ
+}
+
+// Folded affine, ReLU and rounding in registers, then 16-byte pieces of rows: lane (m, q) holds channels 16j + 4q .. + 3 of
+// row m; one lane swap per pair of column tiles leaves it eight consecutive channels.  (ReLU by a compile-time switch: as a
+// branch per value it cost 4 000 cycles a tile.)
+template <int DT, int CIN, int COUT, int MT, bool RELU>
+__device__ __forceinline__ void finish_tile(const SpanLds<CIN, COUT>& s, floatx4 (&acc)[MT][COUT / 16], uint32_t row0, uint32_t n_out,
+                                            uint16_t* __restrict__ out) {
+  const uint32_t m = lane_id() & 15, q = lane_id() >> 4;
+  char* base = reinterpret_cast<char*>(out) + (int64_t)row0 * (COUT * 2);      // the same for the whole wave
+  const uint32_t at = m * (COUT * 2) + 16 * (2 * (q & 1) + (q >> 1));
+  const bool whole = row0 + 64 * (MT - 1) + 16 <= n_out;
+#pragma unroll
+  for (int jp = 0; jp < COUT / 32; ++jp) {
+    floatx4 sc[2], sh[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      sc[e] = *reinterpret_cast<const floatx4*>(s.scale + 16 * (2 * jp + e) + 4 * q);
+      sh[e] = *reinterpret_cast<const floatx4*>(s.shift + 16 * (2 * jp + e) + 4 * q);
+    }
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      u32x2 h[2];
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        floatx4 v = acc[mt][2 * jp + e];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          v[i] = fmaf(v[i], sc[e][i], sh[e][i]);
+          if constexpr (RELU) v[i] = fmaxf(v[i], 0.f);   // NaN -> 0
+        }
+        h[e] = u32x2{MmaS<DT>::cvt2(v[0], v[1]), MmaS<DT>::cvt2(v[2], v[3])};
+      }
+      const u32x2 x = __builtin_amdgcn_permlane16_swap(h[0][0], h[1][0], false, false);
+      const u32x2 y = __builtin_amdgcn_permlane16_swap(h[0][1], h[1][1], false, false);
+      if (whole || row0 + 64 * mt + m < n_out)
+        *reinterpret_cast<u32x4*>(base + 64 * mt * (COUT * 2) + 64 * jp + at) = u32x4{x[0], y[0], x[1], y[1]};
+    }
+  }
+}
+template <int DT, int CIN, int COUT, int MT>
+__device__ __forceinline__ void store_tile(const SpanLds<CIN, COUT>& s, int epilogue, floatx4 (&acc)[MT][COUT / 16], uint32_t row0,
+                                           uint32_t n_out, uint16_t* __restrict__ out) {
+  if (epilogue == EMC2_EPI_AFFINE_RELU) finish_tile<DT, CIN, COUT, MT, true>(s, acc, row0, n_out, out);
+  else finish_tile<DT, CIN, COUT, MT, false>(s, acc, row0, n_out, out);
+}
+
+// Tiles tile0, tile0 + step, .. below tile_end, each of 64 * MT rows.
+template <int DT, int CIN, int COUT, int MT>
+__device__ __forceinline__ void computing_wave(const SpanLds<CIN, COUT>& s, uint32_t wave, int epilogue, uint32_t tile0, uint32_t step,
+                                               uint32_t tile_end, uint32_t n_out, uint16_t* __restrict__ out) {
+  constexpr int NT = COUT / 16, TR = kSpanRows;
+  floatx4 acc[MT][NT];
+  uint32_t rb = 0, wb = 0, tb = 0;
+  for (uint32_t tile = tile0; tile < tile_end; tile += step, tb ^= 1) {
+    sync_all();                                    // the tile's intervals are in LDS
+    const Plan p = make_plan<MT, TR>(s.part[tb]);
+    if (tile != tile0) store_tile<DT, CIN, COUT, MT>(s, epilogue, acc, (tile - step) * (64 * MT) + 16 * wave, n_out, out);
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+      for (int j = 0; j < NT; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    unsigned long long todo = p.any;
+    uint32_t left = 0;
+    while (todo != 0ull) {
+      const unsigned long long bit = todo & (0ull - todo);
+      if (left == 0) left = (p.one & bit) ? 1 : (p.two & bit) ? 2 : 3;
+      sync_all();
+      compute<DT, CIN, COUT, MT>(s, rb, wb, wave, acc);
+      rb ^= 1;
+      if (--left == 0) {
+        todo ^= bit;
+        wb ^= 1;
+      }
+    }
+    if (tile + step >= tile_end) store_tile<DT, CIN, COUT, MT>(s, epilogue, acc, tile * (64 * MT) + 16 * wave, n_out, out);
+  }
+}
+
+// The waves that feed: producer w looks after the rows of computing wave w, 64*mt + 16*w + m of a tile (lane = 16*mt + m,
+// mt 4 and 5 in a second register).  The next tile's entries of a group are requested as soon as this tile's are done with and
+// looked through two groups later; nothing waits for them but what uses them.
+template <int DT, int CIN, int COUT, int MT>
+__device__ __forceinline__ void feeding_wave(SpanLds<CIN, COUT>& s, uint32_t w, const uint16_t* __restrict__ in,
+                                             const u32x4* __restrict__ wp, const int32_t* __restrict__ nbr, int64_t capacity,
+                                             int32_t n_in, int32_t* __restrict__ dev_flags, uint32_t tile0, uint32_t step,
+                                             uint32_t tile_end, uint32_t n_out) {
+  constexpr int TR = kSpanRows, CH = CIN / 8, RPI = 64 / CH, G16 = 3 * SpanLds<CIN, COUT>::W16;
+  constexpr int H = (MT + 1) / 2, NE = (MT + 3) / 4;
+  static_assert(TR % RPI == 0 && 64 * MT <= TR && TR * CIN * 2 < 65536, "whole loads, a tap's rows and 16-bit offsets");
+  static_assert(G16 % 256 == 0, "whole loads of weights for each producer");
+  const uint32_t lane = lane_id(), m = lane & 15;
+  // role in a load of RPI rows: row within it and piece of the row; a producer's loads are every fourth, which leaves the
+  // swapping of pieces the same in all of them
+  static_assert((4 * RPI / (16 / CH)) % CH == 0, "swizzle of every fourth load is the same");
+  const uint32_t lrow = lane / CH, lpiece = (lane % CH) ^ swizzle_of<CH>(w * RPI + lrow);
+  const uint32_t lat = lrow * (CIN * 2) + lpiece * 16;
+
+  int32_t e[27][NE];              // kernel-map entries: of the current tile until its group is done, then of the next
+  uint32_t row[NE], rows_in[NE];  // output row; rows that its entries may name (none for a row past n_out)
+  int32_t seen = -1;              // largest entry seen
+  uint32_t rb = 0, wb = 0;
+#define EMC2_ROWS(TILE)                                                              \
+  _Pragma("unroll") for (int i = 0; i < NE; ++i) {                                   \
+    const uint32_t mt_ = 4 * i + (lane >> 4), r_ = (TILE) * (64 * MT) + 64 * mt_ + 16 * w + m; \
+    const bool live_ = mt_ < MT && r_ < n_out;                                       \
+    row[i] = live_ ? r_ : 0;                                                         \
+    rows_in[i] = live_ ? (uint32_t)n_in : 0u;                                        \
+  }
+#define EMC2_ENTRIES(G)                                                              \
+  _Pragma("unroll") for (int kx = 0; kx < 3; ++kx) {                                 \
+    const int32_t* src_ = nbr + (int64_t)(3 * (G) + kx) * capacity;                  \
+    _Pragma("unroll") for (int i = 0; i < NE; ++i) e[3 * (G) + kx][i] = src_[row[i]]; \
+  }
+  // rows [LO, HI] to the row buffer, from its start (rows past HI re-read row HI and are never referenced)
+#define EMC2_FETCH(LO, HI)                                                                                        \
+  {                                                                                                               \
+    const uint32_t lo_ = (LO), last_ = (uint32_t)(HI) - lo_;                                                      \
+    const char* base_ = reinterpret_cast<const char*>(in) + (int64_t)lo_ * (CIN * 2);                             \
+    uint32_t i_ = w;                                                                                              \
+    for (; i_ * RPI + RPI <= last_ + 1; i_ += 4) load_to_lds16(base_ + i_ * 1024 + lat, s.rows[rb] + i_ * 64);      \
+    if (i_ * RPI <= last_)                                                                                        \
+      load_to_lds16(base_ + min(i_ * RPI + lrow, last_) * (uint32_t)(CIN * 2) + lpiece * 16, s.rows[rb] + i_ * 64); \
+  }
+  // where each of this producer's rows reads at the taps of group G: tiles [M0, M1) in the interval that starts at LO, the
+  // others and absent neighbours (-1, beyond any interval) the zeroed row
+#define EMC2_OFFSET(R) ((R) * (CIN * 2) | swizzle_of<CH>(R) * 16)
+#define EMC2_OFFSETS(G, WHOLE, M0, M1, LO)                                                                             \
+  _Pragma("unroll") for (int i = 0; i < NE; ++i) {                                                                \
+    uint32_t o_[3];                                                                                               \
+    const uint32_t mt_ = 4 * i + (lane >> 4);                                                                     \
+    _Pragma("unroll") for (int kx = 0; kx < 3; ++kx) {                                                            \
+      uint32_t at_ = min((uint32_t)e[3 * (G) + kx][i] - (LO), (uint32_t)TR);                                      \
+      if (!(WHOLE)) at_ = mt_ >= (M0) && mt_ < (M1) ? at_ : (uint32_t)TR;                                         \
+      o_[kx] = EMC2_OFFSET(at_);                                                                                  \
+    }                                                                                                             \
+    if (mt_ < MT) *reinterpret_cast<u32x2*>(s.off[rb][w][m][mt_]) = u32x2{o_[0] | o_[1] << 16, o_[2]};            \
+  }
+#define EMC2_WEIGHTS(G)                                                                                           \
+  _Pragma("unroll") for (int i = 0; i < G16 / 256; ++i)                                                           \
+    load_to_lds16(wp + (int64_t)(G) * G16 + (i * 4 + w) * 64 + lane, s.w[wb] + (i * 4 + w) * 64);
+
+  // the rows that the entries of group G name, per 16 output rows; the entries are in registers
+#define EMC2_ANALYSE(G, TB)                                                                                       \
+  _Pragma("unroll") for (int i = 0; i < NE; ++i) {                                                                \
+    uint32_t lo_ = 0xffffffffu;                                                                                   \
+    int32_t hi_ = -1;                                                                                             \
+    _Pragma("unroll") for (int kx = 0; kx < 3; ++kx) {                                                            \
+      int32_t& j_ = e[3 * (G) + kx][i];                                                                           \
+      seen = max(seen, j_);                                                                                       \
+      j_ = (uint32_t)j_ < rows_in[i] ? j_ : -1;                                                                   \
+      lo_ = min(lo_, (uint32_t)j_);                                                                               \
+      hi_ = max(hi_, j_);                                                                                         \
+    }                                                                                                             \
+    lo_ = row_min(lo_);                                                                                           \
+    hi_ = row_max(hi_);                                                                                           \
+    if (m == 0 && 4 * i + (lane >> 4) < MT) s.part[TB][G][w][4 * i + (lane >> 4)] = u32x2{lo_, (uint32_t)hi_};     \
+  }
+  // waits for the entries of group G here, so that nothing that uses them waits for loads issued since
+#define EMC2_ARRIVED(G)                                                                                           \
+  _Pragma("unroll") for (int kx = 0; kx < 3; ++kx)                                                                \
+    _Pragma("unroll") for (int i = 0; i < NE; ++i) asm volatile("" : "+v"(e[3 * (G) + kx][i]));
+
+  EMC2_ROWS(tile0)
+#pragma unroll
+  for (int g = 0; g < 9; ++g) EMC2_ENTRIES(g)
+#pragma unroll
+  for (int g = 0; g < 9; ++g) EMC2_ANALYSE(g, 0)
+  uint32_t tb = 0;
+  for (uint32_t tile = tile0; tile < tile_end; tile += step, tb ^= 1) {
+    sync_all();
+    const Plan p = make_plan<MT, TR>(s.part[tb]);
+    // the next tile's entries; past the last tile, its own again
+    EMC2_ROWS(tile + step < tile_end ? tile + step : tile)
+    // opaque: the addresses of 27 taps would otherwise stay alive from tile to tile, and spill
+    asm volatile("" : "+s"(capacity));
+#pragma unroll
+    for (int g = 0; g < 9; ++g) {
+      const unsigned long long bit = 1ull << (4 * g);
+      // the next tile's entries of the last group but one have had a pass to arrive in
+      if (g > 1) EMC2_ARRIVED(g - 2)
+      if (p.any & bit) {
+        const uint32_t lo_a = __builtin_amdgcn_readlane(p.lo_a, 4 * g), lo_b = __builtin_amdgcn_readlane(p.lo_b, 4 * g);
+        const int32_t hi_a = __builtin_amdgcn_readlane(p.hi_a, 4 * g), hi_b = __builtin_amdgcn_readlane(p.hi_b, 4 * g);
+        if (p.one & bit) {
+          const uint32_t lo = min(lo_a, lo_b);
+          EMC2_FETCH(lo, max(hi_a, hi_b))
+          EMC2_WEIGHTS(g)
+          __builtin_amdgcn_sched_barrier(0);
+          EMC2_OFFSETS(g, true, 0, MT, lo)
+        } else if (p.two & bit) {
+          EMC2_FETCH(lo_a, hi_a)
+          EMC2_WEIGHTS(g)
+          __builtin_amdgcn_sched_barrier(0);
+          EMC2_OFFSETS(g, false, 0, H, lo_a)
+          loads_done();
+          sync_all();
+          rb ^= 1;
+          EMC2_FETCH(lo_b, hi_b)
+          __builtin_amdgcn_sched_barrier(0);
+          EMC2_OFFSETS(g, false, H, MT, lo_b)
+        } else {
+          EMC2_WEIGHTS(g)
+#pragma unroll
+          for (int kx = 0; kx < 3; ++kx) {
+            if (kx > 0) {
+              loads_done();
+              sync_all();
+              rb ^= 1;
+            }
+            // row p of the buffer <- what output row p of the tile reads at this tap (absent: row 0, not referenced)
+#pragma unroll
+            for (int i = 0; i < NE; ++i) {
+              const uint32_t mt = 4 * i + (lane >> 4);
+              const uint32_t at = e[3 * g + kx][i] >= 0 ? 64 * mt + 16 * w + m : (uint32_t)TR;
+              uint32_t o[3];
+#pragma unroll
+              for (int t = 0; t < 3; ++t) o[t] = t == kx ? EMC2_OFFSET(at) : EMC2_OFFSET((uint32_t)TR);
+              if (mt < MT) *reinterpret_cast<u32x2*>(s.off[rb][w][m][mt]) = u32x2{o[0] | o[1] << 16, o[2]};
+            }
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+              for (int h = 0; h < 16 / RPI; ++h) {
+                const int32_t j = __shfl(e[3 * g + kx][mt / 4], (mt % 4) * 16 + h * RPI + lrow, 64);
+                const uint32_t r0 = 64 * mt + 16 * w + h * RPI;
+                const uint32_t piece = (lane % CH) ^ swizzle_of<CH>(r0 + lrow);
+                load_to_lds16(reinterpret_cast<const char*>(in) + (int64_t)max(j, 0) * (CIN * 2) + piece * 16, s.rows[rb] + r0 * CH);
+              }
+          }
+        }
+        if (g > 1) EMC2_ANALYSE(g - 2, tb ^ 1)
+        loads_done();
+        EMC2_ENTRIES(g)
+        sync_all();
+        rb ^= 1;
+        wb ^= 1;
+      } else {
+        if (g > 1) EMC2_ANALYSE(g - 2, tb ^ 1)
+        EMC2_ENTRIES(g)
+      }
+    }
+    EMC2_ANALYSE(7, tb ^ 1)
+    EMC2_ANALYSE(8, tb ^ 1)
+  }
+#undef EMC2_ROWS
+#undef EMC2_ENTRIES
+#undef EMC2_FETCH
+#undef EMC2_OFFSETS
+#undef EMC2_OFFSET
+#undef EMC2_WEIGHTS
+#undef EMC2_ANALYSE
+#undef EMC2_ARRIVED
+  emc2_report_oob(__ballot(seen >= n_in), dev_flags);
 }
 
 template <int DT, int CIN, int COUT>
-__global__ void __launch_bounds__(kSpanThreads, (SpanCfg<CIN>::MINW))
+__global__ void __launch_bounds__(kSpanThreads, 2)
 k_spconv_span(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, const float* __restrict__ scale,
               const float* __restrict__ shift, int epilogue, const int32_t* __restrict__ nbr,
               const int32_t* __restrict__ d_n_out, int64_t capacity_out, int32_t n_in, int32_t* __restrict__ dev_flags,
               uint16_t* __restrict__ out) {
-  constexpr int G16 = 3 * (CIN / 32) * (COUT / 16) * 64;
-  constexpr int SMAX = SpanCfg<CIN>::SMAX;
-  constexpr int ROW16 = CIN / 8 + 1;
-  static_assert(SMAX % (64 / (CIN / 8)) == 0 && SMAX >= 64, "the tile holds whole load instructions and at least the 64 rows of a pass");
-  __shared__ u32x4 wl[2 * G16];
-  __shared__ u32x4 tile[kSpanWaves][(SMAX + 1) * ROW16];
-
-  int64_t n_out = *d_n_out;
-  if (n_out > capacity_out) n_out = capacity_out;
-  // Rows are dealt in rounds of one block per CU (the tiles and weights in LDS leave room for one).  Whole rounds take
-  // 64 rows a wave; what is left, which used to cost a whole round however little it was, is split into the smallest
-  // waves (16, 32 or 48 rows) with which it fits one round.  64-row waves throughout against this, alone on the GPU:
-  // 16 k rows 24.6 / 18.2 us, 69 k 35.5 / 31.0, 223 k 64.6 / 59.5, 573 k 139 / 137 (131 in a grid that fits).  A rest of
-  // more than 98 304 rows would take 64-row waves too, so it belongs to the whole rounds: as a part of its own it only
-  // tore every XCD's range of rows in two (380 k rows 99.2 / 98.1 us, 852 k rows with a smaller rest 212 / 211).
-  constexpr uint32_t kRoundRows = kSpanCUs * kSpanWaves * 64;
-  const uint32_t n = n_out > 0 ? (uint32_t)n_out : 0u;
-  // XCD-aware tile assignment: workgroup b runs on XCD b % 8; XCD x takes a contiguous range of the tiles of either part
-  const uint32_t x = blockIdx.x % 8, slot = blockIdx.x / 8;
-  const uint32_t rounds = n / kRoundRows;
-  uint32_t rem = n % kRoundRows;
-  // The grid is for the capacity; a block beyond both parts leaves at once (one at a time fits a CU: 22 k of them cost
-  // 25 us when each first worked out the split).
-  if (slot >= (rounds + (rem ? 1 : 0)) * (kSpanCUs / 8)) return;
-  uint32_t full = rounds * kSpanCUs;                              // blocks of 64-row waves
-  if (rem > kRoundRows / 4 * 3) {
-    full += (rem + kSpanWaves * 64 - 1) / (kSpanWaves * 64);
-    rem = 0;
+  __shared__ SpanLds<CIN, COUT> s;
+  static_assert(sizeof(s) <= 160 * 1024, "LDS of a CU");
+  int64_t n64 = *d_n_out;
+  if (n64 > capacity_out) n64 = capacity_out;
+  if (n64 <= 0) return;
+  const uint32_t n = (uint32_t)n64;
+  // Tile height: 64 * mt rows, the mt with which the rounds of the slowest block cost least.  Measured per round, in 0.1 us,
+  // the first with its start and end: heights 3, 4, 5, 6 (1 and 2 cost 6.3 and 7.4 us a round and were never the best by
+  // more than a microsecond).
+  constexpr uint32_t kFirst[4] = {165, 170, 185, 215}, kNext[4] = {87, 110, 136, 165};
+  const uint32_t step = gridDim.x / 8;
+  uint32_t mt = 0, cost = 0xffffffffu;
+#pragma unroll
+  for (uint32_t i = 0; i < 4; ++i) {
+    const uint32_t tiles = (n + 64 * (3 + i) - 1) / (64 * (3 + i)), rounds = ((tiles + 7) / 8 + step - 1) / step;
+    const uint32_t c = kFirst[i] + (rounds - 1) * kNext[i];
+    if (c < cost) {
+      cost = c;
+      mt = 3 + i;
+    }
   }
-  const int wave = threadIdx.x >> 6;
-  // waves w and w + 4 share a SIMD: one of each kind per SIMD
-#define EMC2_SPAN_WAVE(MTV)                                                                                               \
-  {                                                                                                                       \
-    const int64_t row0_ = first_row + (int64_t)wave * 16 * (MTV);                                                         \
-    if (wave < 4)                                                                                                         \
-      span_wave<DT, CIN, COUT, MTV, false>(in, wp, scale, shift, epilogue, nbr, n_out, capacity_out, n_in, dev_flags, out, \
-                                           wl, tile[wave], row0_);                                                        \
-    else                                                                                                                  \
-      span_wave<DT, CIN, COUT, MTV, true>(in, wp, scale, shift, epilogue, nbr, n_out, capacity_out, n_in, dev_flags, out,  \
-                                          wl, tile[wave], row0_);                                                         \
-    return;                                                                                                               \
+  // XCD-aware: workgroup b runs on XCD b % 8; XCD x walks over a contiguous range of tiles, its blocks side by side
+  const uint32_t tiles = (n + 64 * mt - 1) / (64 * mt), chunk = (tiles + 7) / 8;
+  const uint32_t first = (blockIdx.x % 8) * chunk, tile0 = first + blockIdx.x / 8;
+  const uint32_t end = first + chunk < tiles ? first + chunk : tiles;
+  if (tile0 >= end) return;          // uniform for the block
+  for (uint32_t i = threadIdx.x; i < COUT; i += kSpanThreads) {
+    s.scale[i] = epilogue != EMC2_EPI_NONE ? scale[i] : 1.f;
+    s.shift[i] = epilogue != EMC2_EPI_NONE ? shift[i] : -0.f;   // x * 1 + -0 is x
   }
-  const uint32_t chunk = (full + 7) / 8;
-  if (slot < chunk) {
-    if (x * chunk + slot >= full) return;   // uniform for the block
-    const int64_t first_row = (int64_t)(x * chunk + slot) * (kSpanWaves * 64);
-    EMC2_SPAN_WAVE(4)
-  }
-  const uint32_t mt = (rem + kRoundRows / 4 - 1) / (kRoundRows / 4);       // 16-row tiles per wave of the rest
-  if (mt == 0) return;
-  const uint32_t rows = kSpanWaves * 16 * mt;
-  const uint32_t n_tiles = (rem + rows - 1) / rows, chunk2 = (n_tiles + 7) / 8;
-  const uint32_t slot2 = slot - chunk;
-  if (slot2 >= chunk2 || x * chunk2 + slot2 >= n_tiles) return;   // uniform for the block
-  const int64_t first_row = (int64_t)full * (kSpanWaves * 64) + (int64_t)(x * chunk2 + slot2) * rows;
-  if (mt == 1) EMC2_SPAN_WAVE(1)
-  if (mt == 2) EMC2_SPAN_WAVE(2)
-  EMC2_SPAN_WAVE(3)
-#undef EMC2_SPAN_WAVE
+  if (threadIdx.x < 2 * (CIN / 8))
+    s.rows[threadIdx.x / (CIN / 8)][kSpanRows * (CIN / 8) + threadIdx.x % (CIN / 8)] = u32x4{0u, 0u, 0u, 0u};
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+#define EMC2_RUN(MTV)                                                                                                          \
+  case MTV:                                                                                                                    \
+    if (wave < 4) computing_wave<DT, CIN, COUT, MTV>(s, wave, epilogue, tile0, step, end, n, out);                             \
+    else feeding_wave<DT, CIN, COUT, MTV>(s, wave - 4, in, wp, nbr, capacity_out, n_in, dev_flags, tile0, step, end, n);       \
+    break;
+  switch (mt) { EMC2_RUN(3) EMC2_RUN(4) EMC2_RUN(5) EMC2_RUN(6) }
+#undef EMC2_RUN
 }
 
 template <int DT, int CIN, int COUT>
 void launch_span(const void* d_in, const void* d_wp, const float* d_scale, const float* d_shift, int epilogue,
                  const int32_t* d_nbr, const int32_t* d_n_out, int64_t capacity_out, int32_t n_in, int32_t* dev_flags,
                  void* d_out, hipStream_t s) {
-  // whole rounds of 64-row waves and one round for the rest
-  const int64_t rounds = capacity_out / ((int64_t)kSpanCUs * kSpanWaves * 64) + 1;
-  hipLaunchKernelGGL((k_spconv_span<DT, CIN, COUT>), dim3((unsigned)(rounds * kSpanCUs)),
-                     dim3(kSpanThreads), 0, s, (const uint16_t*)d_in, (const u32x4*)d_wp, d_scale, d_shift, epilogue, d_nbr,
-                     d_n_out, capacity_out, n_in, dev_flags, (uint16_t*)d_out);
+  // one block a CU; fewer where the capacity has fewer of the smallest tiles
+  const int64_t tiles = emc2_div_up(emc2_div_up(capacity_out, 192), 8) * 8;
+  hipLaunchKernelGGL((k_spconv_span<DT, CIN, COUT>), dim3((unsigned)(tiles < kSpanCUs ? tiles : kSpanCUs)), dim3(kSpanThreads), 0, s,
+                     (const uint16_t*)d_in, (const u32x4*)d_wp, d_scale, d_shift, epilogue, d_nbr, d_n_out, capacity_out, n_in,
+                     dev_flags, (uint16_t*)d_out);
 }
 
 }  // namespace
 
-// Only (64, 64) is instantiated: at 32 channels the gather is too small a part of a tap for the re-use to pay
-// (measured slower than the register-direct kernel).
+// Only (64, 64) is instantiated: at 32 channels a pass has a quarter of the matrix work for half of the bytes, and what a
+// tile costs besides its passes shows (two blocks a CU, 1.0 M rows 97 us against 97-105 on the register-direct kernel, 304 k
+// rows 43 against 39).
 // Weights: the packed layout of the register-direct kernel (emc2_spconv_direct_pack).
 bool emc2_spconv_span_supported(int cin, int cout) { return cin == 64 && cout == 64; }
 

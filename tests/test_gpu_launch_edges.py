@@ -7,7 +7,7 @@ import torch
 
 import oracle
 from paper_2507_04123_amd import binding as B
-from paper_2507_04123_amd.configs import EPI_NONE, F16, VoxelSpec
+from paper_2507_04123_amd.configs import BF16, EPI_AFFINE, EPI_AFFINE_RELU, EPI_NONE, F16, VoxelSpec
 from paper_2507_04123_amd.pipeline import cells_of
 
 pytestmark = pytest.mark.gpu
@@ -53,11 +53,59 @@ def _check_conv(n, cin, cout, hint, shuffled, seed=11, cap=None, rows_in=None):
     ctx.close()
 
 
-# a round is 131 072 rows; the rest runs in waves of 16, 32 or 48 rows or, beyond 98 304 rows, as part of the whole rounds
+# tiles of 192, 256, 320 or 384 rows, 256 of them at a time
 @pytest.mark.parametrize("n", [1, 17, 129, 32768, 32769, 65537, 98305, 131071, 131072, 131073, 131072 + 40001, 262144 + 70001,
                                98304, 131072 + 98304, 131072 + 98305, 131072 + 102401, 262144 - 1])
 def test_span_conv_rounds(n):
     _check_conv(n, 64, 64, B.SUBM, False)
+
+
+# a row less than, as many as and a row more than the tiles of a round and the sizes where the tile's height changes
+@pytest.mark.parametrize("n", [191, 193, 256 * 192, 256 * 192 + 1, 256 * 256, 256 * 256 + 1, 256 * 320 + 1, 3 * 256 * 384 - 1, 3 * 256 * 320 + 65])
+def test_span_conv_tiles(n):
+    _check_conv(n, 64, 64, B.SUBM, False)
+
+
+# Groups whose rows fit the 400-row buffer, fit it in two halves of a tile, and do not; the bf16 form; a row whose 27 entries
+# are all absent; no rows at all.  Sums of up to 27 * 64 products, rounded once: 2^-11 (fp16) or 2^-8 (bf16) relative, doubled.
+@pytest.mark.parametrize("n", [0, 1000, 256 * 320])
+@pytest.mark.parametrize("stretch", [1.0, 2.5, 4.0])
+@pytest.mark.parametrize("dtype", [F16, BF16])
+def test_span_conv_passes_of_a_group(n, stretch, dtype):
+    td = torch.float16 if dtype == F16 else torch.bfloat16
+    g = torch.Generator(device="cuda").manual_seed(3)
+    n_in = int(n * stretch) + 40
+    x = torch.randn((n_in, 64), generator=g, device="cuda").to(td)
+    w = (torch.randn((27, 64, 64), generator=g, device="cuda") * 0.1).to(td)
+    o = (torch.arange(n, device="cuda") * stretch).long()
+    nbr = torch.stack([o + 4 * (k // 3) + k % 3 for k in range(27)]) if n else torch.zeros((27, 0), dtype=torch.int64, device="cuda")
+    nbr = torch.where(torch.rand(nbr.shape, generator=g, device="cuda") < 0.3, torch.full_like(nbr, -1), nbr)
+    nbr[:, 5:6] = -1
+    nbr[9:12] = -1                                              # a group without an entry
+    cap = n + 7
+    table = torch.zeros((27, cap), dtype=torch.int32, device="cuda")
+    table[:, :n] = nbr.to(torch.int32)
+    scale, shift = torch.rand(64, generator=g, device="cuda") + 0.5, torch.randn(64, generator=g, device="cuda")
+    ctx = B.Context(16, 16, 64, n_slots=1)
+    wp = torch.empty_like(w)
+    ctx.pack_weights(dtype, w, wp)
+    exp = torch.zeros((n, 64), device="cuda")
+    for k in range(27):
+        rows = (nbr[k] >= 0).nonzero().squeeze(1)
+        exp[rows] += x[nbr[k][rows]].float() @ w[k].float()
+    for epi in (EPI_NONE, EPI_AFFINE, EPI_AFFINE_RELU):
+        y = torch.full((cap, 64), 77.0, dtype=td, device="cuda")
+        aff = (None, None) if epi == EPI_NONE else (scale, shift)
+        ctx.spconv(dtype, x, wp, *aff, epi, table, torch.tensor([n], dtype=torch.int32, device="cuda"), cap, y, w_layout=B.W_PACKED,
+                   map_hint=B.SUBM)
+        ctx.status_sync()
+        want = exp if epi == EPI_NONE else exp * scale + shift
+        want = want.clamp(min=0.0) if epi == EPI_AFFINE_RELU else want
+        rms = float(want.square().mean().sqrt()) if n else 0.0
+        tol = 2.0 ** -10 if dtype == F16 else 2.0 ** -7
+        assert bool(((y[:n].float() - want).abs() <= tol * (want.abs() + rms)).all()), epi
+        assert bool((y[n:] == 77.0).all())
+    ctx.close()
 
 
 @pytest.mark.parametrize("n", [513, 40001, 70001, 131072 + 5000])
