@@ -424,7 +424,7 @@ extern "C" emc2_status emc2_spconv(emc2_ctx* ctx, emc2_dtype dtype, const void* 
                               cin, cout, d_out, s);
     else
       emc2_spconv_direct_launch(dtype, d_in, wp, d_scale, d_shift, (int)epilogue, d_nbr, d_n_out, capacity_out, n_in, flags,
-                                cin, cout, ctx->zero_row, d_out, s);
+                                cin, cout, ctx->zero_row, map_hint != EMC2_CONV_SUBM, d_out, s);
   } else if (dtype == EMC2_F32) {
     launch_alu<float>(d_in, d_w, d_scale, d_shift, (int)epilogue, d_nbr, d_n_out, capacity_out, n_in, flags, cin, cout, d_out, s);
   } else if (dtype == EMC2_F16 && launch_rows<EMC2_F16>(d_in, d_w, d_scale, d_shift, (int)epilogue, d_nbr, d_n_out, capacity_out,

@@ -22,6 +22,13 @@
 // taps ahead of their use; kernel-map entries two (dz,dy) groups ahead.  Every load is unconditional so the
 // compiler can count the loads in flight.  Shapes: Cin, Cout in {32, 64}, and 64 -> 128 / 128 -> 128, where a
 // tap's matrix work per gathered byte doubles and the kernel leaves the staged per-tap kernel behind by a third.
+//
+// SKIP: a block first reads all 27 map entries of its rows, keeps them in LDS, and runs only the (dz, dy) groups in which
+// some row has one.  A stride-2 map leaves 31-41 % of the (group, 128 rows) pairs empty, a transposed one 52-62 % (a line of
+// fine sites has one or two of three dy and dz).  Alone, us before / with it: transposed 64 -> 64 over 223 k rows 59 / 45,
+// 64 -> 32 over 304 k 60 / 48; stride-2 32 -> 64 over 573 k 82 / 71, over 852 k 114 / 90, over 223 k 35 / 34.  Submanifold maps
+// (a fifth of the groups empty) and 128 output channels gain less than the longer way to the first operands costs (32 -> 32
+// over 304 k 40 / 43, 64 -> 128 over 67 k 50 / 52, 128 -> 128 103 / 113), so they keep the straight walk over the 27 taps.
 #include <hip/hip_bf16.h>
 #include <hip/hip_fp16.h>
 
@@ -96,7 +103,7 @@ __device__ __forceinline__ u32x4 buffer_row16(__amdgpu_buffer_rsrc_t rows, uint3
   return __builtin_amdgcn_raw_buffer_load_b128(rows, (int)byte, 0, 0);
 }
 
-template <int DT, int CIN, int COUT, bool LOOP, bool BUF>
+template <int DT, int CIN, int COUT, bool LOOP, bool BUF, bool SKIP>
 __global__ void __launch_bounds__(kDThreads, (DirectCfg<CIN, COUT>::MINW))
 k_spconv_direct(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, const float* __restrict__ scale,
                 const float* __restrict__ shift, int epilogue, const int32_t* __restrict__ nbr,
@@ -116,8 +123,11 @@ k_spconv_direct(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, c
   constexpr int NA = MT * KS;                 // A-operand loads per tap
   constexpr int OCH = COUT / 8;               // 16-byte pieces per output row
   constexpr int OPITCH = (OCH + 1) * 8;       // epilogue tile row pitch in 16-bit units
+  // per wave: a 16-row tile of the epilogue and, before it, its rows' map entries
+  constexpr int OWN16 = SKIP && 27 * R / 4 > 16 * (OCH + 1) ? 27 * R / 4 : 16 * (OCH + 1);
   __shared__ u32x4 wl[2][W16];
-  __shared__ u32x4 otile_s[kDWaves][16 * (OCH + 1)];
+  __shared__ u32x4 otile_s[kDWaves][OWN16];
+  __shared__ uint32_t groups_s[SKIP ? kDWaves : 1];
 
   // raw buffer of the input rows (word 3: 32-bit data format, no swizzle)
   const __amdgpu_buffer_rsrc_t rows =
@@ -201,6 +211,76 @@ k_spconv_direct(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, c
   _Pragma("unroll") for (int i_ = 0; i_ < WPT; ++i_)                                                     \
       wl[BUF][(tid + i_ * kDThreads) & WMASK] = wq[SET][i_];
 
+  // the matrix work of one tap: operands of set SET, weights in WB
+#define EMC2_TAP(WB, SET)                                                                                \
+  _Pragma("unroll") for (int ks = 0; ks < KS; ++ks) {                                                    \
+    u32x4 b[NT];                                                                                         \
+    _Pragma("unroll") for (int j = 0; j < NT; ++j) b[j] = (WB)[(ks * NT + j) * 64 + lane];               \
+    _Pragma("unroll") for (int mt = 0; mt < MT; ++mt)                                                    \
+      _Pragma("unroll") for (int j = 0; j < NT; ++j)                                                     \
+          acc[mt][j] = MmaD<DT>::run(areg[SET][mt * KS + ks], b[j], acc[mt][j]);                         \
+  }
+  if constexpr (SKIP) {
+    // The entries as rows the kernel may read (absent and beyond the input: -1), [tap][row], and the groups to run.
+    int32_t* ent = reinterpret_cast<int32_t*>(otile_s[wave]);
+    constexpr int TPI = 64 / R, NL = (27 + TPI - 1) / TPI;     // taps of one load; loads
+    const int sub = lane / R, row = lane % R;
+    int32_t e[NL];
+#pragma unroll
+    for (int i = 0; i < NL; ++i) e[i] = nrow[(int64_t)(TPI * i + sub < 27 ? TPI * i + sub : 26) * nbr_pitch];
+    uint32_t groups = 0;
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int32_t j = max(emc2_entry(e[i], dead, n_in, oob), -1);
+      const unsigned long long some = __ballot(j >= 0);
+#pragma unroll
+      for (int t = 0; t < TPI; ++t)
+        if (TPI * i + t < 27 && (TPI == 1 ? some : t == 0 ? some & 0xffffffffull : some >> 32) != 0ull) groups |= 1u << ((TPI * i + t) / 3);
+      if (TPI * i + sub < 27) ent[(TPI * i + sub) * R + row] = j;
+    }
+    if (lane == 0) groups_s[wave] = groups;
+    __syncthreads();
+    groups = 0;
+#pragma unroll
+    for (int w = 0; w < kDWaves; ++w) groups |= groups_s[w];
+    groups = __builtin_amdgcn_readfirstlane(groups);
+#define EMC2_ENTRIES(GROUP) \
+  _Pragma("unroll") for (int kx_ = 0; kx_ < 3; ++kx_) jq[0][kx_] = ent[(3 * (GROUP) + kx_) * R + row];
+    if (groups != 0) {
+      // prologue: entries, operands and weights of the first group; the weights of its first tap to LDS
+      int g = __builtin_ctz(groups);
+      groups &= groups - 1;
+#pragma unroll
+      for (int kx = 0; kx < 3; ++kx) EMC2_W_LOAD(3 * g + kx, kx)
+      EMC2_ENTRIES(g)
+#pragma unroll
+      for (int kx = 0; kx < 3; ++kx) EMC2_A_LOAD(jq[0][kx], kx)
+      EMC2_W_STORE(0, 0)
+      __syncthreads();
+      uint32_t buf = 0;
+      while (true) {
+        const int32_t past = groups != 0 ? 0 : -1;        // after the last group: no operands, the same weights again
+        g = groups != 0 ? __builtin_ctz(groups) : g;
+        EMC2_ENTRIES(g)
+#pragma unroll
+        for (int kx = 0; kx < 3; ++kx) {
+          // weights of the next group's tap: global -> registers (the set was emptied at the end of the previous tap)
+          EMC2_W_LOAD(3 * g + kx, kx)
+          EMC2_TAP(wl[buf], kx)
+          EMC2_A_LOAD(jq[0][kx] | past, kx)               // the freed register set takes the next group's operands
+          __builtin_amdgcn_wave_barrier();
+          // weights of the next tap: registers -> the other LDS buffer; the barrier publishes them and retires the buffer
+          // just read
+          buf ^= 1;
+          EMC2_W_STORE(buf, (kx + 1) % 3)
+          __syncthreads();
+        }
+        if (past != 0) break;
+        groups &= groups - 1;
+      }
+    }
+#undef EMC2_ENTRIES
+  } else {
   // prologue: map entries of groups 0..2; weights of tap 0 to LDS; A operands of taps 0..2
   EMC2_IDX_LOAD(0, 0)
   EMC2_IDX_LOAD(1, 1)
@@ -224,17 +304,7 @@ k_spconv_direct(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, c
       const int tap = 3 * g + kx;
       // weights of tap + 3: global -> registers (the set was emptied at the end of the previous tap)
       EMC2_W_LOAD(tap + 3 < 27 ? tap + 3 : 26, kx)
-      const u32x4* wb = wl[tap & 1];
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        u32x4 b[NT];
-#pragma unroll
-        for (int j = 0; j < NT; ++j) b[j] = wb[(ks * NT + j) * 64 + lane];
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-          for (int j = 0; j < NT; ++j) acc[mt][j] = MmaD<DT>::run(areg[kx][mt * KS + ks], b[j], acc[mt][j]);
-      }
+      EMC2_TAP(wl[tap & 1], kx)
       // the freed register set takes the A operands of tap + 3 (entries of "group 9" do not exist)
       const int32_t past = g < 8 ? 0 : -1;
       EMC2_A_LOAD(emc2_entry(jq[1][kx], dead | past, n_in, oob), kx)
@@ -251,10 +321,12 @@ k_spconv_direct(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, c
       jq[2][kx] = jn[kx];
     }
   }
+  }
 #undef EMC2_IDX_LOAD
 #undef EMC2_A_LOAD
 #undef EMC2_W_LOAD
 #undef EMC2_W_STORE
+#undef EMC2_TAP
   emc2_report_oob(oob, dev_flags);
 
   // epilogue: lane (m, q) holds column 16*j + m of rows 16*mt + 4*q + e.  Scale/shift/ReLU/convert in
@@ -301,7 +373,7 @@ k_spconv_direct(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, c
 template <int DT, int CIN, int COUT>
 void launch_direct(const void* d_in, const void* d_wp, const float* d_scale, const float* d_shift, int epilogue,
                    const int32_t* d_nbr, const int32_t* d_n_out, int64_t capacity_out, int32_t n_in, int32_t* dev_flags,
-                   const void* d_zero_row, void* d_out, hipStream_t s) {
+                   const void* d_zero_row, bool skip, void* d_out, hipStream_t s) {
   const int64_t rows_per_block = kDWaves * 16 * DirectCfg<CIN, COUT>::MT;
   // The host knows a level's capacity, up to 8 times the level below, not how many voxels it got.  Blocks without a tile
   // cost about 0.25 us per thousand: 32 -> 64 over 573 k rows took 97 us in a grid for 11.3 M rows (88 k blocks) and 75 us
@@ -309,19 +381,28 @@ void launch_direct(const void* d_in, const void* d_wp, const float* d_scale, con
   // against 127 us), so it is used only where the grid would be several times kDGrid; the grid is then kDGrid blocks
   // (32 -> 64 over 573 k rows 97 -> 80 us, over 852 k 119 -> 109).
   const int64_t blocks = emc2_div_up(emc2_div_up(capacity_out, rows_per_block), 8) * 8;
-#define LAUNCH(LOOP, BUF, BLOCKS)                                                                                             \
-  hipLaunchKernelGGL((k_spconv_direct<DT, CIN, COUT, LOOP, BUF>), dim3((unsigned)(BLOCKS)), dim3(kDThreads), 0, s,           \
+#define LAUNCH(LOOP, BUF, SKIP, BLOCKS)                                                                                           \
+  hipLaunchKernelGGL((k_spconv_direct<DT, CIN, COUT, LOOP, BUF, SKIP>), dim3((unsigned)(BLOCKS)), dim3(kDThreads), 0, s,           \
                      (const uint16_t*)d_in, (const u32x4*)d_wp, d_scale, d_shift, epilogue, d_nbr, d_n_out, capacity_out,     \
                      n_in, dev_flags, (const uint16_t*)d_zero_row, (uint16_t*)d_out)
   // Offsets into the input are 32-bit, and the absent neighbour's, 2^32 less a row, must lie at or beyond its end.
   const bool buf = ((int64_t)n_in + 1) * CIN * 2 <= ((int64_t)1 << 32);
-  if (blocks <= 4 * kDGrid) {
-    if (buf) LAUNCH(false, true, blocks);
-    else LAUNCH(false, false, blocks);
-  } else {
-    if (buf) LAUNCH(true, true, kDGrid);
-    else LAUNCH(true, false, kDGrid);
+#define LAUNCH_FORM(SKIP)                           \
+  if (blocks <= 4 * kDGrid) {                       \
+    if (buf) LAUNCH(false, true, SKIP, blocks);     \
+    else LAUNCH(false, false, SKIP, blocks);        \
+  } else {                                          \
+    if (buf) LAUNCH(true, true, SKIP, kDGrid);      \
+    else LAUNCH(true, false, SKIP, kDGrid);         \
   }
+  if constexpr (CIN + COUT > 64 && COUT <= 64) {
+    if (skip) {
+      LAUNCH_FORM(true)
+      return;
+    }
+  }
+  LAUNCH_FORM(false)
+#undef LAUNCH_FORM
 #undef LAUNCH
 }
 
@@ -340,11 +421,11 @@ void emc2_spconv_direct_pack(const void* d_w, int cin, int cout, void* d_packed,
 void emc2_spconv_direct_launch(emc2_dtype dtype, const void* d_in, const void* d_wp, const float* d_scale,
                                const float* d_shift, int epilogue, const int32_t* d_nbr, const int32_t* d_n_out,
                                int64_t capacity_out, int32_t n_in, int32_t* dev_flags, int cin, int cout,
-                               const void* d_zero_row, void* d_out, hipStream_t stream) {
+                               const void* d_zero_row, bool skip, void* d_out, hipStream_t stream) {
 #define CASE(DTV, CI, CO)                                                                                              \
   if (dtype == DTV && cin == CI && cout == CO) {                                                                       \
     launch_direct<DTV, CI, CO>(d_in, d_wp, d_scale, d_shift, epilogue, d_nbr, d_n_out, capacity_out, n_in, dev_flags,  \
-                               d_zero_row, d_out, stream);                                                             \
+                               d_zero_row, skip, d_out, stream);                                                       \
     return;                                                                                                            \
   }
   CASE(EMC2_F16, 32, 32) CASE(EMC2_F16, 32, 64) CASE(EMC2_F16, 64, 32) CASE(EMC2_F16, 64, 64)

@@ -127,6 +127,40 @@ def test_direct_conv_grid_limit(cin, cout, rows, n, loop):
         _check_conv(n, cin, cout, B.MAP_ANY, False, cap=cap, rows_in=(1 << 25) + 3)
 
 
+# Blocks of 128 rows that have entries in no group, in one, in every one, and whose waves differ; the last block ragged.
+@pytest.mark.parametrize("cin,cout", [(32, 64), (64, 32), (64, 64)])
+@pytest.mark.parametrize("n", [1, 128, 129, 1000])
+def test_direct_conv_groups_without_entries(cin, cout, n):
+    g = torch.Generator(device="cuda").manual_seed(cin + cout + n)
+    n_in = 500
+    x = torch.randn((n_in, cin), generator=g, device="cuda").half()
+    w = (torch.randn((27, cin, cout), generator=g, device="cuda") * 0.1).half()
+    nbr = torch.randint(0, n_in, (27, n), generator=g, device="cuda")
+    group, block, wave = torch.arange(27, device="cuda") // 3, torch.arange(n, device="cuda") // 128, torch.arange(n, device="cuda") // 32
+    keep = (block % 4 == 1)[None, :] & (group[:, None] == block[None, :] % 9) | (block % 4 == 2)[None, :] | \
+        (block % 4 == 3)[None, :] & (group[:, None] == wave[None, :] % 9)      # blocks 0, 4, ..: nothing
+    nbr = torch.where(keep & (torch.rand((27, n), generator=g, device="cuda") < 0.7), nbr, torch.full_like(nbr, -1)).to(torch.int32).contiguous()
+    exp = torch.zeros((n, cout), device="cuda")
+    for k in range(27):
+        rows = (nbr[k] >= 0).nonzero().squeeze(1)
+        exp[rows] += x[nbr[k][rows].long()].float() @ w[k].float()
+    rms = float(exp.square().mean().sqrt())
+    ctx = B.Context(16, 16, 64, n_slots=1)
+    wp = torch.empty_like(w)
+    ctx.pack_weights(F16, w, wp)
+    got = []
+    for hint in (B.MAP_ANY, B.STRIDED, B.SUBM):
+        y = torch.full((n + 2, cout), 77.0, dtype=torch.float16, device="cuda")
+        ctx.spconv(F16, x, wp, None, None, EPI_NONE, nbr, torch.tensor([n], dtype=torch.int32, device="cuda"), n, y[:n],
+                   w_layout=B.W_PACKED, map_hint=hint)
+        ctx.status_sync()
+        assert float(((y[:n].float() - exp).abs() - 2.0 ** -10 * (exp.abs() + rms)).max()) <= 0.0     # as in _check_conv
+        assert bool((y[n:] == 77.0).all())
+        got.append(y)
+    assert torch.equal(got[0], got[1]) and torch.equal(got[0], got[2])         # the hint chooses a way, never a result
+    ctx.close()
+
+
 # inputs of less than 4 GiB are read through a buffer descriptor, larger ones by address; any negative entry is absent
 @pytest.mark.parametrize("cin,cout,n_in", [(64, 32, 1 << 10), (64, 64, (1 << 25) - 1), (64, 64, 1 << 25), (32, 32, (1 << 25) + 3),
                                            (128, 128, (1 << 24) - 1)])
