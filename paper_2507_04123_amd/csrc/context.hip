@@ -70,9 +70,9 @@ extern "C" emc2_status emc2_create(emc2_ctx** out, int device, int64_t max_point
   ctx->n_partials = emc2_div_up(ctx->slot_words, EMC2_SCAN_TILE) + 1;
   TRY(hipMalloc((void**)&ctx->partials, sizeof(uint32_t) * 2 * (size_t)ctx->n_partials), "hipMalloc(partials)");
   {
-    // level 0 in tiles, up to EMC2_STACK_MAX_LEVELS - 1 further ones in quarter tiles, and one sum of every 64 sums
+    // level 0 in tiles, up to EMC2_STACK_MAX_LEVELS - 1 further ones in sixteenths of tiles, and one sum of every 64 sums
     const int64_t further = n_slots - 1 < EMC2_STACK_MAX_LEVELS - 1 ? n_slots - 1 : EMC2_STACK_MAX_LEVELS - 1;
-    const int64_t units = ctx->slot_tiles * (1 + 4 * further);
+    const int64_t units = ctx->slot_tiles * (1 + 16 * further);
     ctx->n_stack_sums = units + units / 64 + 2 * EMC2_STACK_MAX_LEVELS;
   }
   TRY(hipMalloc((void**)&ctx->stack_sums, sizeof(uint32_t) * (size_t)ctx->n_stack_sums), "hipMalloc(stack_sums)");

@@ -20,7 +20,7 @@
 // gather l: a coarse word is read off the fine level's bits (27 cells behind every coarse cell: nine bit rows OR-ed, then
 // one shift-or and an even-bit compress), so no atomics are needed, nothing has to be cleared first, and the word's
 // popcount joins the scan's sums in the same pass.  expand l: prefix fields and coordinates in one pass.
-// A frame of 120 000 points through four levels: 28 launches before, 7 now.
+// A frame of 120 000 points through four levels: 28 launches before, 7 now; 109 us, the last launch at the rate of a copy.
 #include <string.h>
 
 #include "kmap_probe.h"
@@ -30,8 +30,13 @@ namespace {
 
 constexpr int kStacks = 4;                       // stacks per launch chain (kernel arguments hold their descriptions)
 constexpr int kLevels = EMC2_STACK_MAX_LEVELS;
-constexpr int kGranuleWords = 512;               // words per block of gather / expand: 32 lines
-constexpr int kGranuleLines = kGranuleWords >> EMC2_LINE_SHIFT;
+// Words per block of gather / expand: 8 lines where a level is at most 1 024 such granules (half a round of the chip), else
+// 32 lines.  A coarse level is a chain of dependent loads on little data, which more blocks shorten: levels 2 and 3 of a
+// 64-beam frame, gathers and expansions, 22 + 12 us of launches before, 11 + 8 now.  A fine one is mostly empty granules, which
+// cost their blocks: levels 1 of eight routed frames in small granules 66 -> 119 us.
+constexpr int kGranuleWords = 128;
+constexpr int kGranuleMax = 512;
+constexpr int64_t kSmallGranules = 1024;
 constexpr int kSuper = 64;                       // sums per super-sum: a block's base is at most units/64 + 63 reads
 constexpr int kPrefixTiles = 4;                  // tiles per block of the prefix pass
 constexpr int kMaxJobs = 24;
@@ -39,7 +44,7 @@ constexpr int kMaxJobs = 24;
 struct DevLevel {
   cellword_t* idx;
   lineflag_t* flags;
-  uint32_t* sums;         // popcount sums per unit (level 0: a tile of 2048 words; above: a granule of 512)
+  uint32_t* sums;         // popcount sums per unit (level 0: a tile of 2048 words; above: a granule)
   uint32_t* supers;       // sums of 64 of them
   int4* coords;
   int32_t* n;
@@ -49,6 +54,7 @@ struct DevLevel {
   int64_t cells;
   int32_t g[3];
   int32_t units;
+  int32_t words;          // of a unit
 };
 
 struct DevStack {
@@ -191,6 +197,7 @@ __device__ __forceinline__ void role_sum(const DevLevel& lv, uint32_t blk) {
 __device__ __forceinline__ uint32_t base_of(const DevLevel& lv, int64_t unit) {
   const int lane = threadIdx.x & 63;
   uint32_t s = 0;
+#pragma unroll 4
   for (int i = lane; i < (int)(unit / kSuper); i += 64) s += lv.supers[i];
   const int64_t i = unit / kSuper * kSuper + lane;
   if (i < unit) s += lv.sums[i];
@@ -327,16 +334,17 @@ __device__ __forceinline__ uint32_t gather_word(const DevLevel& in, const DevLev
   return bits;
 }
 
-// One granule of level l: which of its 32 lines can hold a bit (line flags of the fine level), then the words of those.
+// One granule of level l: which of its lines can hold a bit (line flags of the fine level), then the words of those.  All
+// threads look at flags, 8 or 32 to a line; then a word each.
 __device__ __forceinline__ void role_gather(const DevStack& st, int l, uint32_t blk) {
-  __shared__ uint32_t act_s, old_s, sum_s[4];
+  __shared__ uint32_t act_s[4], old_s[4], sum_s[4];
   const DevLevel& in = st.lv[l - 1];
   const DevLevel& lv = st.lv[l];
-  if (threadIdx.x == 0) { act_s = 0u; old_s = 0u; }
-  __syncthreads();
-  const int64_t line0 = (int64_t)blk * kGranuleLines;
+  const int lines = lv.words >> EMC2_LINE_SHIFT, subs = 256 / lines;     // 8 and 32, or 32 and 8
+  const int wave = threadIdx.x >> 6;
+  const int64_t line0 = (int64_t)blk * lines;
   {
-    const int line = threadIdx.x >> 3, sub = threadIdx.x & 7;
+    const int line = (int)threadIdx.x / subs, sub = (int)threadIdx.x % subs;
     const uint32_t gox = (uint32_t)lv.g[0], goy = (uint32_t)lv.g[1], goz = (uint32_t)lv.g[2];
     const uint64_t k0 = (uint64_t)(line0 + line) << (5 + EMC2_LINE_SHIFT);
     uint64_t k1 = k0 + (32u << EMC2_LINE_SHIFT);
@@ -345,7 +353,7 @@ __device__ __forceinline__ void role_gather(const DevStack& st, int l, uint32_t 
     if (k0 < k1) {
       const uint64_t r0 = div_key(k0, gox), r1 = div_key(k1 - 1, gox);
       const uint32_t nc = (uint32_t)(r1 - r0 + 1) * 9u;
-      for (uint32_t c = (uint32_t)sub; c < nc; c += 8) {
+      for (uint32_t c = (uint32_t)sub; c < nc; c += (uint32_t)subs) {
         const uint64_t row = r0 + c / 9u;
         const int d = (int)(c % 9u);
         const uint64_t t = div_key(row, goy);
@@ -367,26 +375,41 @@ __device__ __forceinline__ void role_gather(const DevStack& st, int l, uint32_t 
         any |= f != 0u;
       }
     }
-    if (any) atomicOr(&act_s, 1u << line);
-    if (sub == 0 && lv.flags[line0 + line]) atomicOr(&old_s, 1u << line);
+    // lines of this wave (64 / subs of them), a bit each
+    const unsigned long long some = __ballot(any), was = __ballot(sub == 0 && lv.flags[line0 + line] != 0);
+    uint32_t act = 0, old = 0;
+    for (int q = 0; q < 64 / subs; ++q) {
+      const unsigned long long m = ((1ull << subs) - 1ull) << (q * subs);     // subs is 8 or 32
+      act |= (some & m) != 0ull ? 1u << q : 0u;
+      old |= (was & m) != 0ull ? 1u << q : 0u;
+    }
+    if ((threadIdx.x & 63) == 0) {
+      act_s[wave] = act;
+      old_s[wave] = old;
+    }
   }
   __syncthreads();
-  const uint32_t act = act_s, write = act | old_s;
-  if (threadIdx.x < kGranuleLines && ((write >> threadIdx.x) & 1u))
-    lv.flags[line0 + threadIdx.x] = (lineflag_t)((act >> threadIdx.x) & 1u);
+  uint32_t act = 0, old = 0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    act |= act_s[q] << (q * lines / 4);
+    old |= old_s[q] << (q * lines / 4);
+  }
+  const uint32_t write = act | old;
+  if ((int)threadIdx.x < lines && ((write >> threadIdx.x) & 1u)) lv.flags[line0 + threadIdx.x] = (lineflag_t)((act >> threadIdx.x) & 1u);
   uint32_t s = 0;
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
+  for (int i = 0; i < kGranuleMax / 256; ++i) {
     const int wi = (int)threadIdx.x + 256 * i;
     const int line = wi >> EMC2_LINE_SHIFT;
-    if (!((write >> line) & 1u)) continue;
-    const int64_t w = (int64_t)blk * kGranuleWords + wi;
+    if (wi >= lv.words || !((write >> line) & 1u)) continue;
+    const int64_t w = (int64_t)blk * lv.words + wi;
     const uint32_t bits = ((act >> line) & 1u) ? gather_word(in, lv, w) : 0u;
     lv.idx[w] = make_uint2(bits, 0u);
     s += __popc(bits);
   }
   s = wave_sum(s);
-  if ((threadIdx.x & 63) == 0) sum_s[threadIdx.x >> 6] = s;
+  if ((threadIdx.x & 63) == 0) sum_s[wave] = s;
   __syncthreads();
   if (threadIdx.x == 0) {
     s = sum_s[0] + sum_s[1] + sum_s[2] + sum_s[3];
@@ -395,50 +418,84 @@ __device__ __forceinline__ void role_gather(const DevStack& st, int l, uint32_t 
   }
 }
 
-// One granule of level l: prefix fields of its flagged words and the coordinates of their set bits.
+// x past the row's end goes on in the next row, plane, frame.
+__device__ __forceinline__ void carry(int4& c, const DevLevel& lv) {
+  while (c.w >= lv.g[0]) {
+    c.w -= lv.g[0];
+    if (++c.z >= lv.g[1]) {
+      c.z = 0;
+      if (++c.y >= lv.g[2]) {
+        c.y = 0;
+        ++c.x;
+      }
+    }
+  }
+}
+
+// One granule of level l: prefix fields of its flagged words and the coordinates of their set bits.  In a small granule (a
+// coarse level: few, dense words) a half wave takes a word, a lane its bit, so that a store writes consecutive rows; in a
+// large one (many words, mostly empty) a thread walks the bits of its two words.  The other way round either costs more:
+// level 3 of a 64-beam frame 13 us by walking and 9 so, the levels 1 of eight routed frames 43 us by walking and 48 so.
 __device__ __forceinline__ void role_expand(const DevStack& st, int l, uint32_t blk) {
-  __shared__ uint32_t wsum[4];
+  __shared__ uint32_t wsum[4], word_s[kGranuleWords], pre_s[kGranuleWords];
+  __shared__ int4 at_s[kGranuleWords];                                // (b, z, y, x) of a word's bit 0
   const DevLevel& lv = st.lv[l];
   const bool last = (int)blk == lv.units - 1;
-  const int64_t w0 = (int64_t)blk * kGranuleWords + 2 * (int64_t)threadIdx.x;   // two adjacent words, one line
-  const bool have = lv.flags[w0 >> EMC2_LINE_SHIFT] != 0;
+  const int words = lv.words, wi = 2 * (int)threadIdx.x;              // two adjacent words, one line
+  const int64_t w0 = (int64_t)blk * words + wi;
+  const bool have = wi < words && lv.flags[w0 >> EMC2_LINE_SHIFT] != 0;
   if (!__syncthreads_or(have) && !last) return;
   uint4* p = reinterpret_cast<uint4*>(lv.idx + w0);
   uint4 v = have ? *p : make_uint4(0u, 0u, 0u, 0u);
+  const uint32_t base = base_of(lv, blk);
   const uint32_t s = __popc(v.x) + __popc(v.z);
   const uint32_t inc = wave_scan(s);
   if ((threadIdx.x & 63) == 63) wsum[threadIdx.x >> 6] = inc;
-  const uint32_t base = base_of(lv, blk);
   __syncthreads();
-  uint32_t run = base + inc - s;
+  uint32_t run = inc - s;                                             // rows of the granule before these words
   for (int j = 0; j < (int)(threadIdx.x >> 6); ++j) run += wsum[j];
-  if (last && threadIdx.x == 255) report_total(st, lv, run + s);
-  if (!have) return;
-  v.y = run;
-  v.w = run + __popc(v.x);
-  *p = v;
-  if (s == 0u) return;
-  int4 c = decode_key((uint64_t)w0 * 32, lv.g[0], lv.g[1], lv.g[2]);   // (b, z, y, x) of the first word's bit 0
-  uint64_t bits = ((uint64_t)v.z << 32) | v.x;
-  int at = 0;                                                          // bit position c refers to
-  int64_t r = run;
-  while (bits) {
-    const int j = __ffsll((unsigned long long)bits) - 1;
-    bits &= bits - 1;
-    c.w += j - at;
-    at = j;
-    while (c.w >= lv.g[0]) {
-      c.w -= lv.g[0];
-      if (++c.z >= lv.g[1]) {
-        c.z = 0;
-        if (++c.y >= lv.g[2]) {
-          c.y = 0;
-          ++c.x;
-        }
-      }
+  const uint32_t total = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+  if (last && threadIdx.x == 0) report_total(st, lv, base + total);
+  if (have) {
+    v.y = base + run;
+    v.w = base + run + __popc(v.x);
+    *p = v;
+  }
+  if (words == kGranuleMax) {
+    if (s == 0u) return;
+    int4 c = decode_key((uint64_t)w0 * 32, lv.g[0], lv.g[1], lv.g[2]);   // (b, z, y, x) of the first word's bit 0
+    uint64_t bits = ((uint64_t)v.z << 32) | v.x;
+    int at = 0;                                                          // bit position c refers to
+    int64_t r = base + run;
+    while (bits) {
+      const int j = __ffsll((unsigned long long)bits) - 1;
+      bits &= bits - 1;
+      c.w += j - at;
+      at = j;
+      carry(c, lv);
+      if (r < lv.cap) lv.coords[r] = c;
+      ++r;
     }
-    if (r < lv.cap) lv.coords[r] = c;
-    ++r;
+    return;
+  }
+  if (wi < words) {
+    word_s[wi] = v.x;
+    word_s[wi + 1] = v.z;
+    pre_s[wi] = base + run;
+    pre_s[wi + 1] = base + run + __popc(v.x);
+  }
+  if ((int)threadIdx.x < words) at_s[threadIdx.x] = decode_key(((uint64_t)blk * words + threadIdx.x) * 32, lv.g[0], lv.g[1], lv.g[2]);
+  __syncthreads();
+  const int bit = threadIdx.x & 31;
+#pragma unroll 4
+  for (int i = (int)threadIdx.x >> 5; i < kGranuleWords; i += 8) {
+    const uint32_t w = word_s[i];
+    if (!((w >> bit) & 1u)) continue;
+    const uint32_t r = pre_s[i] + __popc(w & ((1u << bit) - 1u));
+    int4 c = at_s[i];
+    c.w += bit;
+    carry(c, lv);
+    if ((int64_t)r < lv.cap) lv.coords[r] = c;
   }
 }
 
@@ -560,7 +617,8 @@ emc2_status describe(const emc2_stack& s, int64_t n_points, DevStack* d) {
     for (int a = 0; a < 3; ++a) v.g[a] = g[a];
     v.cells = (int64_t)g[0] * g[1] * g[2] * s.spec.n_batch;
     const int64_t words = emc2_div_up(v.cells, 32);
-    const int64_t units = emc2_div_up(words, l == 0 ? EMC2_SCAN_TILE : kGranuleWords);
+    v.words = l == 0 ? EMC2_SCAN_TILE : emc2_div_up(words, kGranuleWords) <= kSmallGranules ? kGranuleWords : kGranuleMax;
+    const int64_t units = emc2_div_up(words, v.words);
     v.units = (int32_t)units;
     v.sums = sums;
     v.supers = sums + units;

@@ -82,10 +82,12 @@ def _same(a, b, what):
 
 
 # grids whose rows are shorter than a word, straddle words, fill lines exactly, and leave a lone output column; one level to
-# five; batches; more than one granule (16 384 coarse cells) and tile (65 536 cells)
+# five; batches; more than one granule (4 096 coarse cells) and tile (65 536 cells); a level 1 of large granules (4.5 million
+# cells) over a level 2 of small ones
 @pytest.mark.parametrize("grid,nb,levels,n", [((7, 5, 3), 1, 3, 40), ((3, 9, 6), 3, 2, 200), ((1, 1, 1), 2, 1, 2), ((33, 17, 9), 2, 4, 900),
                                               ((64, 16, 4), 1, 2, 500), ((65, 40, 11), 2, 5, 3000), ((176, 200, 5), 1, 4, 6000),
-                                              ((513, 300, 3), 2, 3, 20000), ((1, 700, 90), 1, 3, 5000)])
+                                              ((513, 300, 3), 2, 3, 20000), ((1, 700, 90), 1, 3, 5000),
+                                              ((1408, 800, 32), 1, 3, 20000)])
 def test_stack_equals_the_calls_it_replaces(grid, nb, levels, n):
     spec = VoxelSpec((0.0, 0.0, 0.0), (1.0, 1.0, 1.0), grid, nb)
     a, b = _Bufs(grid, nb, levels, n), _Bufs(grid, nb, levels, n)
