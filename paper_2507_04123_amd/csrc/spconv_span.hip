@@ -21,7 +21,9 @@
 // the same: no gain), weights straight from global memory into registers (longer: the vector-memory path takes them at the
 // rate of the rows), separate waves for loads and for the map (2 + 2: a wave issues a load into LDS only every ~100 cycles),
 // the map read by the computing waves (spills), an order of tiles that keeps neighbouring planes in one L2 (no gain).
-// 64 -> 64, us before / now: 70 k rows 33 / 25-27, 223 k 65 / 58, 248 k bf16 71 / 59, 573 k 142 / 107, 852 k 210 / 163.
+// 64 -> 64, us before / now: 70 k rows 33 / 25-28, 223 k 65 / 58, 248 k bf16 71 / 60, 573 k 142 / 107, 852 k 210 / 161.
+// 128 -> 128 (bf16) on the register-direct kernel, which its gather bounds (two cache lines a row, each touched twice), / here:
+// 4 k rows 36 / 19, 32 k 39 / 26, 48 k 70 / 39, 67 k 104 / 71.
 //
 // One pass is what is computed between two barriers.  Normally a group is one pass.  A group whose interval does not fit
 // the row buffer is split into two passes of half of the tile's rows if each half's interval fits (next to a denser plane
@@ -66,15 +68,32 @@ template <> struct MmaS<EMC2_BF16> {
 
 constexpr int kSpanThreads = 512;    // waves 0-3 compute, waves 4-7 feed them
 constexpr int64_t kSpanCUs = 256;    // compute units of the part; one block fits each
-constexpr int kSpanRows = 400;       // rows of one of the two row buffers: what the LDS holds beside the rest
+// A pass takes 64 input channels: 128 are two passes a group, the lower channels of its three taps and then the upper.
+constexpr int kPassChannels = 64;
+
+// TR: rows of one of the two row buffers, what the LDS holds beside the rest.  A tile is 64 * mt rows, mt in
+// [MT0, MT0 + 4); kFirst, kNext: what a block's first tile (with the launch's start and end) and each further one cost,
+// measured in 0.1 us.
+template <int CIN, int COUT> struct SpanCfg;
+template <> struct SpanCfg<64, 64> {    // (heights 1 and 2 cost 6.3 and 7.4 us a tile and were never the best by more than 1 us)
+  static constexpr int TR = 400, MT0 = 3, MTS = 4;
+  static constexpr uint32_t kFirst[MTS] = {165, 170, 185, 215}, kNext[MTS] = {87, 110, 136, 165};
+};
+template <> struct SpanCfg<128, 128> {
+  static constexpr int TR = 224, MT0 = 1, MTS = 3;
+  static constexpr uint32_t kFirst[MTS] = {185, 215, 250}, kNext[MTS] = {180, 260, 330};
+};
 
 template <int CIN, int COUT> struct SpanLds {
-  static constexpr int W16 = (CIN / 32) * (COUT / 16) * 64;   // 16-byte weight pieces per tap
-  static constexpr int CH = CIN / 8;                          // 16-byte pieces per feature row
+  static constexpr int CH = kPassChannels / 8;                // 16-byte pieces of a row in a pass
+  static constexpr int KS = kPassChannels / 32;               // steps of a tap in a pass
+  static constexpr int KH = CIN / kPassChannels;              // passes that make up the channels
+  static constexpr int W16 = KS * (COUT / 16) * 64;           // 16-byte weight pieces per tap
+  static constexpr int TR = SpanCfg<CIN, COUT>::TR, MTM = SpanCfg<CIN, COUT>::MT0 + SpanCfg<CIN, COUT>::MTS - 1;
   u32x4 w[2][3 * W16];               // weights of a group
-  u32x4 rows[2][(kSpanRows + 1) * CH];   // rows of a pass; row kSpanRows is zero
-  uint16_t off[2][4][16][6][4];      // [pass][computing wave][m][mt][tap]: where output row 64*mt + 16*wave + m reads
-  u32x2 part[2][9][4][6];            // [tile][group][producer][mt]: lowest and highest row named (0xffffffff, -1: none)
+  u32x4 rows[2][(TR + 1) * CH];      // rows of a pass; row TR is zero
+  uint16_t off[2][4][16][MTM][4];    // [pass][computing wave][m][mt][tap]: where output row 64*mt + 16*wave + m reads
+  u32x2 part[2][9][4][MTM];          // [tile][group][producer][mt]: lowest and highest row named (0xffffffff, -1: none)
   float scale[COUT], shift[COUT];
 };
 
@@ -115,8 +134,9 @@ struct Plan {
   unsigned long long any, one, two;   // some entry; one pass; two passes (neither: three)
 };
 
-template <int MT, int TR>
-__device__ __forceinline__ Plan make_plan(const u32x2 (*part)[4][6]) {
+template <int CIN, int COUT, int MT>
+__device__ __forceinline__ Plan make_plan(const SpanLds<CIN, COUT>& s, uint32_t tb) {
+  constexpr int TR = SpanLds<CIN, COUT>::TR;
   constexpr int H = (MT + 1) / 2;
   const uint32_t l = lane_id() < 36 ? lane_id() : 35;
   Plan p;
@@ -124,7 +144,7 @@ __device__ __forceinline__ Plan make_plan(const u32x2 (*part)[4][6]) {
   p.hi_a = p.hi_b = -1;
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) {
-    const u32x2 v = part[l / 4][l % 4][mt];
+    const u32x2 v = s.part[tb][l / 4][l % 4][mt];
     if (mt < H) {
       p.lo_a = min(p.lo_a, v[0]);
       p.hi_a = max(p.hi_a, (int32_t)v[1]);
@@ -155,7 +175,7 @@ __device__ __forceinline__ Plan make_plan(const u32x2 (*part)[4][6]) {
 template <int DT, int CIN, int COUT, int MT>
 __device__ __forceinline__ void compute(const SpanLds<CIN, COUT>& s, uint32_t rb, uint32_t wb, uint32_t wave,
                                         floatx4 (&acc)[MT][COUT / 16]) {
-  constexpr int KS = CIN / 32, NT = COUT / 16, STEPS = 3 * KS, READS = MT + NT;
+  constexpr int KS = SpanLds<CIN, COUT>::KS, NT = COUT / 16, STEPS = 3 * KS, READS = MT + NT;
   const uint32_t lane = lane_id(), q16 = (lane >> 4) * 16;
   const char* rows = reinterpret_cast<const char*>(s.rows[rb]);
   const u32x4* w = s.w[wb] + lane;
@@ -244,29 +264,29 @@ __device__ __forceinline__ void store_tile(const SpanLds<CIN, COUT>& s, int epil
 template <int DT, int CIN, int COUT, int MT>
 __device__ __forceinline__ void computing_wave(const SpanLds<CIN, COUT>& s, uint32_t wave, int epilogue, uint32_t tile0, uint32_t step,
                                                uint32_t tile_end, uint32_t n_out, uint16_t* __restrict__ out) {
-  constexpr int NT = COUT / 16, TR = kSpanRows;
+  constexpr int NT = COUT / 16;
   floatx4 acc[MT][NT];
   uint32_t rb = 0, wb = 0, tb = 0;
   for (uint32_t tile = tile0; tile < tile_end; tile += step, tb ^= 1) {
     sync_all();                                    // the tile's intervals are in LDS
-    const Plan p = make_plan<MT, TR>(s.part[tb]);
+    const Plan p = make_plan<CIN, COUT, MT>(s, tb);
     if (tile != tile0) store_tile<DT, CIN, COUT, MT>(s, epilogue, acc, (tile - step) * (64 * MT) + 16 * wave, n_out, out);
 #pragma unroll
     for (int i = 0; i < MT; ++i)
 #pragma unroll
       for (int j = 0; j < NT; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
     unsigned long long todo = p.any;
-    uint32_t left = 0;
+    uint32_t left = 0;                             // passes of the group, the same number for each share of the channels
     while (todo != 0ull) {
       const unsigned long long bit = todo & (0ull - todo);
-      if (left == 0) left = (p.one & bit) ? 1 : (p.two & bit) ? 2 : 3;
+      const uint32_t kinds = (p.one & bit) ? 1 : (p.two & bit) ? 2 : 3;
+      if (left == 0) left = kinds * SpanLds<CIN, COUT>::KH;
       sync_all();
       compute<DT, CIN, COUT, MT>(s, rb, wb, wave, acc);
       rb ^= 1;
-      if (--left == 0) {
-        todo ^= bit;
-        wb ^= 1;
-      }
+      --left;
+      if (left == 0 || left == kinds) wb ^= 1;     // the next pass has other weights
+      if (left == 0) todo ^= bit;
     }
     if (tile + step >= tile_end) store_tile<DT, CIN, COUT, MT>(s, epilogue, acc, tile * (64 * MT) + 16 * wave, n_out, out);
   }
@@ -280,10 +300,11 @@ __device__ __forceinline__ void feeding_wave(SpanLds<CIN, COUT>& s, uint32_t w, 
                                              const u32x4* __restrict__ wp, const int32_t* __restrict__ nbr, int64_t capacity,
                                              int32_t n_in, int32_t* __restrict__ dev_flags, uint32_t tile0, uint32_t step,
                                              uint32_t tile_end, uint32_t n_out) {
-  constexpr int TR = kSpanRows, CH = CIN / 8, RPI = 64 / CH, G16 = 3 * SpanLds<CIN, COUT>::W16;
+  using L = SpanLds<CIN, COUT>;
+  constexpr int TR = L::TR, CH = L::CH, RPI = 64 / CH, W16 = L::W16, G16 = 3 * W16;
   constexpr int H = (MT + 1) / 2, NE = (MT + 3) / 4;
-  static_assert(TR % RPI == 0 && 64 * MT <= TR && TR * CIN * 2 < 65536, "whole loads, a tap's rows and 16-bit offsets");
-  static_assert(G16 % 256 == 0, "whole loads of weights for each producer");
+  static_assert(TR % RPI == 0 && 64 * MT <= TR && TR * CH * 16 < 65536, "whole loads, a tap's rows and 16-bit offsets");
+  static_assert(G16 % 256 == 0 && W16 % 64 == 0, "whole loads of weights for each producer, of one tap each");
   const uint32_t lane = lane_id(), m = lane & 15;
   // role in a load of RPI rows: row within it and piece of the row; a producer's loads are every fourth, which leaves the
   // swapping of pieces the same in all of them
@@ -311,15 +332,15 @@ __device__ __forceinline__ void feeding_wave(SpanLds<CIN, COUT>& s, uint32_t w, 
 #define EMC2_FETCH(LO, HI)                                                                                        \
   {                                                                                                               \
     const uint32_t lo_ = (LO), last_ = (uint32_t)(HI) - lo_;                                                      \
-    const char* base_ = reinterpret_cast<const char*>(in) + (int64_t)lo_ * (CIN * 2);                             \
+    const char* base_ = in_h + (int64_t)lo_ * (CIN * 2);                                                          \
     uint32_t i_ = w;                                                                                              \
-    for (; i_ * RPI + RPI <= last_ + 1; i_ += 4) load_to_lds16(base_ + i_ * 1024 + lat, s.rows[rb] + i_ * 64);      \
+    for (; i_ * RPI + RPI <= last_ + 1; i_ += 4) load_to_lds16(base_ + i_ * (RPI * CIN * 2) + lat, s.rows[rb] + i_ * 64); \
     if (i_ * RPI <= last_)                                                                                        \
       load_to_lds16(base_ + min(i_ * RPI + lrow, last_) * (uint32_t)(CIN * 2) + lpiece * 16, s.rows[rb] + i_ * 64); \
   }
   // where each of this producer's rows reads at the taps of group G: tiles [M0, M1) in the interval that starts at LO, the
   // others and absent neighbours (-1, beyond any interval) the zeroed row
-#define EMC2_OFFSET(R) ((R) * (CIN * 2) | swizzle_of<CH>(R) * 16)
+#define EMC2_OFFSET(R) ((R) * (CH * 16) | swizzle_of<CH>(R) * 16)
 #define EMC2_OFFSETS(G, WHOLE, M0, M1, LO)                                                                             \
   _Pragma("unroll") for (int i = 0; i < NE; ++i) {                                                                \
     uint32_t o_[3];                                                                                               \
@@ -333,7 +354,8 @@ __device__ __forceinline__ void feeding_wave(SpanLds<CIN, COUT>& s, uint32_t w, 
   }
 #define EMC2_WEIGHTS(G)                                                                                           \
   _Pragma("unroll") for (int i = 0; i < G16 / 256; ++i)                                                           \
-    load_to_lds16(wp + (int64_t)(G) * G16 + (i * 4 + w) * 64 + lane, s.w[wb] + (i * 4 + w) * 64);
+    load_to_lds16(wp + (int64_t)((3 * (G) + (i * 4 + w) * 64 / W16) * L::KH + h) * W16 + (i * 4 + w) * 64 % W16 + lane, \
+                  s.w[wb] + (i * 4 + w) * 64);
 
   // the rows that the entries of group G name, per 16 output rows; the entries are in registers
 #define EMC2_ANALYSE(G, TB)                                                                                       \
@@ -364,7 +386,7 @@ __device__ __forceinline__ void feeding_wave(SpanLds<CIN, COUT>& s, uint32_t w, 
   uint32_t tb = 0;
   for (uint32_t tile = tile0; tile < tile_end; tile += step, tb ^= 1) {
     sync_all();
-    const Plan p = make_plan<MT, TR>(s.part[tb]);
+    const Plan p = make_plan<CIN, COUT, MT>(s, tb);
     // the next tile's entries; past the last tile, its own again
     EMC2_ROWS(tile + step < tile_end ? tile + step : tile)
     // opaque: the addresses of 27 taps would otherwise stay alive from tile to tile, and spill
@@ -377,51 +399,61 @@ __device__ __forceinline__ void feeding_wave(SpanLds<CIN, COUT>& s, uint32_t w, 
       if (p.any & bit) {
         const uint32_t lo_a = __builtin_amdgcn_readlane(p.lo_a, 4 * g), lo_b = __builtin_amdgcn_readlane(p.lo_b, 4 * g);
         const int32_t hi_a = __builtin_amdgcn_readlane(p.hi_a, 4 * g), hi_b = __builtin_amdgcn_readlane(p.hi_b, 4 * g);
-        if (p.one & bit) {
-          const uint32_t lo = min(lo_a, lo_b);
-          EMC2_FETCH(lo, max(hi_a, hi_b))
-          EMC2_WEIGHTS(g)
-          __builtin_amdgcn_sched_barrier(0);
-          EMC2_OFFSETS(g, true, 0, MT, lo)
-        } else if (p.two & bit) {
-          EMC2_FETCH(lo_a, hi_a)
-          EMC2_WEIGHTS(g)
-          __builtin_amdgcn_sched_barrier(0);
-          EMC2_OFFSETS(g, false, 0, H, lo_a)
-          loads_done();
-          sync_all();
-          rb ^= 1;
-          EMC2_FETCH(lo_b, hi_b)
-          __builtin_amdgcn_sched_barrier(0);
-          EMC2_OFFSETS(g, false, H, MT, lo_b)
-        } else {
-          EMC2_WEIGHTS(g)
+#pragma unroll 1
+        for (uint32_t h = 0; h < (uint32_t)L::KH; ++h) {       // the channels of the pass
+          const char* in_h = reinterpret_cast<const char*>(in) + h * (kPassChannels * 2);
+          if (h > 0) {
+            loads_done();
+            sync_all();
+            rb ^= 1;
+            wb ^= 1;
+          }
+          if (p.one & bit) {
+            const uint32_t lo = min(lo_a, lo_b);
+            EMC2_FETCH(lo, max(hi_a, hi_b))
+            EMC2_WEIGHTS(g)
+            __builtin_amdgcn_sched_barrier(0);
+            EMC2_OFFSETS(g, true, 0, MT, lo)
+          } else if (p.two & bit) {
+            EMC2_FETCH(lo_a, hi_a)
+            EMC2_WEIGHTS(g)
+            __builtin_amdgcn_sched_barrier(0);
+            EMC2_OFFSETS(g, false, 0, H, lo_a)
+            loads_done();
+            sync_all();
+            rb ^= 1;
+            EMC2_FETCH(lo_b, hi_b)
+            __builtin_amdgcn_sched_barrier(0);
+            EMC2_OFFSETS(g, false, H, MT, lo_b)
+          } else {
+            EMC2_WEIGHTS(g)
 #pragma unroll
-          for (int kx = 0; kx < 3; ++kx) {
-            if (kx > 0) {
-              loads_done();
-              sync_all();
-              rb ^= 1;
-            }
-            // row p of the buffer <- what output row p of the tile reads at this tap (absent: row 0, not referenced)
-#pragma unroll
-            for (int i = 0; i < NE; ++i) {
-              const uint32_t mt = 4 * i + (lane >> 4);
-              const uint32_t at = e[3 * g + kx][i] >= 0 ? 64 * mt + 16 * w + m : (uint32_t)TR;
-              uint32_t o[3];
-#pragma unroll
-              for (int t = 0; t < 3; ++t) o[t] = t == kx ? EMC2_OFFSET(at) : EMC2_OFFSET((uint32_t)TR);
-              if (mt < MT) *reinterpret_cast<u32x2*>(s.off[rb][w][m][mt]) = u32x2{o[0] | o[1] << 16, o[2]};
-            }
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-              for (int h = 0; h < 16 / RPI; ++h) {
-                const int32_t j = __shfl(e[3 * g + kx][mt / 4], (mt % 4) * 16 + h * RPI + lrow, 64);
-                const uint32_t r0 = 64 * mt + 16 * w + h * RPI;
-                const uint32_t piece = (lane % CH) ^ swizzle_of<CH>(r0 + lrow);
-                load_to_lds16(reinterpret_cast<const char*>(in) + (int64_t)max(j, 0) * (CIN * 2) + piece * 16, s.rows[rb] + r0 * CH);
+            for (int kx = 0; kx < 3; ++kx) {
+              if (kx > 0) {
+                loads_done();
+                sync_all();
+                rb ^= 1;
               }
+              // row p of the buffer <- what output row p of the tile reads at this tap (absent: row 0, not referenced)
+#pragma unroll
+              for (int i = 0; i < NE; ++i) {
+                const uint32_t mt = 4 * i + (lane >> 4);
+                const uint32_t at = e[3 * g + kx][i] >= 0 ? 64 * mt + 16 * w + m : (uint32_t)TR;
+                uint32_t o[3];
+#pragma unroll
+                for (int t = 0; t < 3; ++t) o[t] = t == kx ? EMC2_OFFSET(at) : EMC2_OFFSET((uint32_t)TR);
+                if (mt < MT) *reinterpret_cast<u32x2*>(s.off[rb][w][m][mt]) = u32x2{o[0] | o[1] << 16, o[2]};
+              }
+#pragma unroll
+              for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int q = 0; q < 16 / RPI; ++q) {
+                  const int32_t j = __shfl(e[3 * g + kx][mt / 4], (mt % 4) * 16 + q * RPI + lrow, 64);
+                  const uint32_t r0 = 64 * mt + 16 * w + q * RPI;
+                  const uint32_t piece = (lane % CH) ^ swizzle_of<CH>(r0 + lrow);
+                  load_to_lds16(in_h + (int64_t)max(j, 0) * (CIN * 2) + piece * 16, s.rows[rb] + r0 * CH);
+                }
+            }
           }
         }
         if (g > 1) EMC2_ANALYSE(g - 2, tb ^ 1)
@@ -461,19 +493,17 @@ k_spconv_span(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, con
   if (n64 > capacity_out) n64 = capacity_out;
   if (n64 <= 0) return;
   const uint32_t n = (uint32_t)n64;
-  // Tile height: 64 * mt rows, the mt with which the rounds of the slowest block cost least.  Measured per round, in 0.1 us,
-  // the first with its start and end: heights 3, 4, 5, 6 (1 and 2 cost 6.3 and 7.4 us a round and were never the best by
-  // more than a microsecond).
-  constexpr uint32_t kFirst[4] = {165, 170, 185, 215}, kNext[4] = {87, 110, 136, 165};
+  // Tile height: the one with which the tiles of the slowest block cost least.
+  using Cfg = SpanCfg<CIN, COUT>;
   const uint32_t step = gridDim.x / 8;
   uint32_t mt = 0, cost = 0xffffffffu;
 #pragma unroll
-  for (uint32_t i = 0; i < 4; ++i) {
-    const uint32_t tiles = (n + 64 * (3 + i) - 1) / (64 * (3 + i)), rounds = ((tiles + 7) / 8 + step - 1) / step;
-    const uint32_t c = kFirst[i] + (rounds - 1) * kNext[i];
+  for (uint32_t i = 0; i < (uint32_t)Cfg::MTS; ++i) {
+    const uint32_t rows = 64 * (Cfg::MT0 + i), tiles = (n + rows - 1) / rows, rounds = ((tiles + 7) / 8 + step - 1) / step;
+    const uint32_t c = Cfg::kFirst[i] + (rounds - 1) * Cfg::kNext[i];
     if (c < cost) {
       cost = c;
-      mt = 3 + i;
+      mt = Cfg::MT0 + i;
     }
   }
   // XCD-aware: workgroup b runs on XCD b % 8; XCD x walks over a contiguous range of tiles, its blocks side by side
@@ -485,15 +515,19 @@ k_spconv_span(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, con
     s.scale[i] = epilogue != EMC2_EPI_NONE ? scale[i] : 1.f;
     s.shift[i] = epilogue != EMC2_EPI_NONE ? shift[i] : -0.f;   // x * 1 + -0 is x
   }
-  if (threadIdx.x < 2 * (CIN / 8))
-    s.rows[threadIdx.x / (CIN / 8)][kSpanRows * (CIN / 8) + threadIdx.x % (CIN / 8)] = u32x4{0u, 0u, 0u, 0u};
+  constexpr int CH = SpanLds<CIN, COUT>::CH;
+  if (threadIdx.x < 2 * CH) s.rows[threadIdx.x / CH][Cfg::TR * CH + threadIdx.x % CH] = u32x4{0u, 0u, 0u, 0u};
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-#define EMC2_RUN(MTV)                                                                                                          \
-  case MTV:                                                                                                                    \
-    if (wave < 4) computing_wave<DT, CIN, COUT, MTV>(s, wave, epilogue, tile0, step, end, n, out);                             \
-    else feeding_wave<DT, CIN, COUT, MTV>(s, wave - 4, in, wp, nbr, capacity_out, n_in, dev_flags, tile0, step, end, n);       \
-    break;
-  switch (mt) { EMC2_RUN(3) EMC2_RUN(4) EMC2_RUN(5) EMC2_RUN(6) }
+#define EMC2_RUN(I)                                                                                                            \
+  if constexpr (I < Cfg::MTS) {                                                                                                \
+    if (mt == Cfg::MT0 + I) {                                                                                                  \
+      constexpr int MT = Cfg::MT0 + I;                                                                                         \
+      if (wave < 4) computing_wave<DT, CIN, COUT, MT>(s, wave, epilogue, tile0, step, end, n, out);                            \
+      else feeding_wave<DT, CIN, COUT, MT>(s, wave - 4, in, wp, nbr, capacity_out, n_in, dev_flags, tile0, step, end, n);      \
+      return;                                                                                                                  \
+    }                                                                                                                          \
+  }
+  EMC2_RUN(0) EMC2_RUN(1) EMC2_RUN(2) EMC2_RUN(3)
 #undef EMC2_RUN
 }
 
@@ -502,7 +536,7 @@ void launch_span(const void* d_in, const void* d_wp, const float* d_scale, const
                  const int32_t* d_nbr, const int32_t* d_n_out, int64_t capacity_out, int32_t n_in, int32_t* dev_flags,
                  void* d_out, hipStream_t s) {
   // one block a CU; fewer where the capacity has fewer of the smallest tiles
-  const int64_t tiles = emc2_div_up(emc2_div_up(capacity_out, 192), 8) * 8;
+  const int64_t tiles = emc2_div_up(emc2_div_up(capacity_out, 64 * SpanCfg<CIN, COUT>::MT0), 8) * 8;
   hipLaunchKernelGGL((k_spconv_span<DT, CIN, COUT>), dim3((unsigned)(tiles < kSpanCUs ? tiles : kSpanCUs)), dim3(kSpanThreads), 0, s,
                      (const uint16_t*)d_in, (const u32x4*)d_wp, d_scale, d_shift, epilogue, d_nbr, d_n_out, capacity_out, n_in,
                      dev_flags, (uint16_t*)d_out);
@@ -510,11 +544,11 @@ void launch_span(const void* d_in, const void* d_wp, const float* d_scale, const
 
 }  // namespace
 
-// Only (64, 64) is instantiated: at 32 channels a pass has a quarter of the matrix work for half of the bytes, and what a
+// 64 -> 64 and 128 -> 128: at 32 channels a pass has a quarter of the matrix work for half of the bytes, and what a
 // tile costs besides its passes shows (two blocks a CU, 1.0 M rows 97 us against 97-105 on the register-direct kernel, 304 k
 // rows 43 against 39).
 // Weights: the packed layout of the register-direct kernel (emc2_spconv_direct_pack).
-bool emc2_spconv_span_supported(int cin, int cout) { return cin == 64 && cout == 64; }
+bool emc2_spconv_span_supported(int cin, int cout) { return (cin == 64 && cout == 64) || (cin == 128 && cout == 128); }
 
 void emc2_spconv_span_launch(emc2_dtype dtype, const void* d_in, const void* d_wp, const float* d_scale,
                              const float* d_shift, int epilogue, const int32_t* d_nbr, const int32_t* d_n_out,
@@ -526,6 +560,6 @@ void emc2_spconv_span_launch(emc2_dtype dtype, const void* d_in, const void* d_w
                              d_out, stream);                                                                        \
     return;                                                                                                         \
   }
-  CASE(EMC2_F16, 64, 64) CASE(EMC2_BF16, 64, 64)
+  CASE(EMC2_F16, 64, 64) CASE(EMC2_BF16, 64, 64) CASE(EMC2_F16, 128, 128) CASE(EMC2_BF16, 128, 128)
 #undef CASE
 }

@@ -66,17 +66,23 @@ def test_span_conv_tiles(n):
     _check_conv(n, 64, 64, B.SUBM, False)
 
 
-# Groups whose rows fit the 400-row buffer, fit it in two halves of a tile, and do not; the bf16 form; a row whose 27 entries
-# are all absent; no rows at all.  Sums of up to 27 * 64 products, rounded once: 2^-11 (fp16) or 2^-8 (bf16) relative, doubled.
+@pytest.mark.parametrize("n", [1, 63, 65, 256 * 64 + 1, 256 * 128 + 1, 256 * 192, 256 * 192 + 1, 2 * 256 * 192 + 70])
+def test_span_conv_tiles_of_128_channels(n):
+    _check_conv(n, 128, 128, B.SUBM, n == 65)
+
+
+# Groups whose rows fit the row buffer, fit it in two halves of a tile, and do not; the bf16 form; a row whose 27 entries
+# are all absent; no rows at all; 128 channels, in two passes.  Sums of up to 27 * 128 products, rounded once: 2^-11 (fp16) or 2^-8 (bf16) relative, doubled.
 @pytest.mark.parametrize("n", [0, 1000, 256 * 320])
 @pytest.mark.parametrize("stretch", [1.0, 2.5, 4.0])
 @pytest.mark.parametrize("dtype", [F16, BF16])
-def test_span_conv_passes_of_a_group(n, stretch, dtype):
+@pytest.mark.parametrize("ch", [64, 128])
+def test_span_conv_passes_of_a_group(n, stretch, dtype, ch):
     td = torch.float16 if dtype == F16 else torch.bfloat16
     g = torch.Generator(device="cuda").manual_seed(3)
     n_in = int(n * stretch) + 40
-    x = torch.randn((n_in, 64), generator=g, device="cuda").to(td)
-    w = (torch.randn((27, 64, 64), generator=g, device="cuda") * 0.1).to(td)
+    x = torch.randn((n_in, ch), generator=g, device="cuda").to(td)
+    w = (torch.randn((27, ch, ch), generator=g, device="cuda") * 0.1).to(td)
     o = (torch.arange(n, device="cuda") * stretch).long()
     nbr = torch.stack([o + 4 * (k // 3) + k % 3 for k in range(27)]) if n else torch.zeros((27, 0), dtype=torch.int64, device="cuda")
     nbr = torch.where(torch.rand(nbr.shape, generator=g, device="cuda") < 0.3, torch.full_like(nbr, -1), nbr)
@@ -85,16 +91,16 @@ def test_span_conv_passes_of_a_group(n, stretch, dtype):
     cap = n + 7
     table = torch.zeros((27, cap), dtype=torch.int32, device="cuda")
     table[:, :n] = nbr.to(torch.int32)
-    scale, shift = torch.rand(64, generator=g, device="cuda") + 0.5, torch.randn(64, generator=g, device="cuda")
+    scale, shift = torch.rand(ch, generator=g, device="cuda") + 0.5, torch.randn(ch, generator=g, device="cuda")
     ctx = B.Context(16, 16, 64, n_slots=1)
     wp = torch.empty_like(w)
     ctx.pack_weights(dtype, w, wp)
-    exp = torch.zeros((n, 64), device="cuda")
+    exp = torch.zeros((n, ch), device="cuda")
     for k in range(27):
         rows = (nbr[k] >= 0).nonzero().squeeze(1)
         exp[rows] += x[nbr[k][rows]].float() @ w[k].float()
     for epi in (EPI_NONE, EPI_AFFINE, EPI_AFFINE_RELU):
-        y = torch.full((cap, 64), 77.0, dtype=td, device="cuda")
+        y = torch.full((cap, ch), 77.0, dtype=td, device="cuda")
         aff = (None, None) if epi == EPI_NONE else (scale, shift)
         ctx.spconv(dtype, x, wp, *aff, epi, table, torch.tensor([n], dtype=torch.int32, device="cuda"), cap, y, w_layout=B.W_PACKED,
                    map_hint=B.SUBM)
