@@ -126,14 +126,21 @@ __global__ void __launch_bounds__(256) k_pack_weights_i8(const int8_t* __restric
 //     (two v_mfma_f32_16x16x32_fp8_fp8 per 16-byte operand: its low and its high 8 bytes; features and packed weights
 //     split the same way, so the contraction pairs the same channels).
 // OUTQ: int8 operands: 1 = int8 output (re-quantised), 0 = fp16 output; E4M3 operands: 1 = fp32 output, 0 = fp16 output.
-// waves per SIMD the register allocator must leave room for: three where the operands in flight are few
-template <int CIN, int COUT> struct QCfg { static constexpr int MINW = (CIN == 64 && COUT == 32) ? 3 : 2; };
+// 16-row tiles per wave, and waves per SIMD the register allocator must leave room for.  A launch is bound by the chain of
+// 27 taps (operand latency, weights through LDS, a barrier each) until enough waves cover each other: 64-row waves left a
+// level of 69 k rows with one block a CU and one of 223 k with 1.7, half of the second round idle.  With 32 rows 64 -> 64 took,
+// before / now: int8 223 k rows 39.6 / 37.0 us, 69 k 24.5 / 20.5; E4M3 175 k 35.5 / 34.6, 57 k 24.0 / 20.5; 16 rows: E4M3 the same
+// for small levels, int8 223 k 10 % slower (each operand read feeds half the products).  The other shapes spill at four waves.
+template <int CIN, int COUT> struct QCfg {
+  static constexpr int MT = 2;
+  static constexpr int MINW = CIN == 64 && COUT == 64 ? 4 : 3;
+};
 
 template <int F8> struct QAcc { typedef intx4 type; };
 template <> struct QAcc<1> { typedef floatx4 type; };
 
 // Input rows through a buffer descriptor, as in the register-direct 16-bit kernel: zeros at or beyond its end.
-// Layers of a 64-beam frame with their quantiser: int8 138 -> 130 us, E4M3 (half as many points) 146 -> 143 us.
+// Layers of a 64-beam frame with their quantiser, still with 64-row waves: int8 138 -> 130 us, E4M3 (half as many points) 146 -> 143 us.
 __device__ __forceinline__ u32x4 buffer_row16(__amdgpu_buffer_rsrc_t rows, uint32_t byte) {
   return __builtin_amdgcn_raw_buffer_load_b128(rows, (int)byte, 0, 0);
 }
@@ -148,10 +155,11 @@ k_spconv_i8(const int8_t* __restrict__ in, const u32x4* __restrict__ wp, const f
       __builtin_amdgcn_make_buffer_rsrc((void*)const_cast<int8_t*>(in), 0, BUF ? (int)((uint32_t)n_in * CIN) : 0, 0x00020000);
   constexpr int KS = CIN / 64;                // k-steps per tap
   constexpr int NT = COUT / 16;               // 16-column tiles
-  constexpr int MT = 4;                       // 16-row tiles per wave
+  constexpr int MT = QCfg<CIN, COUT>::MT;     // 16-row tiles per wave
   constexpr int R = 16 * MT;                  // rows per wave
   constexpr int W16 = KS * NT * 64;           // 16-byte weight pieces per tap
   constexpr int WPT = (W16 + kQThreads - 1) / kQThreads;
+  static_assert(MT == 2, "the lane-swap broadcast below handles two tiles");
   static_assert((W16 & (W16 - 1)) == 0, "piece count is a power of two");
   constexpr int WMASK = W16 - 1;              // surplus threads copy redundantly rather than under a branch
   constexpr int NA = MT * KS;                 // A-operand loads per tap
@@ -175,9 +183,9 @@ k_spconv_i8(const int8_t* __restrict__ in, const u32x4* __restrict__ wp, const f
   const int m = lane & 15, q = lane >> 4;
   const int64_t wave_row0 = tile_id * (kQWaves * R) + (int64_t)wave * R;
 
-  // lane l holds the kernel-map entries of row l of this wave's 64 rows
-  const bool live = wave_row0 + lane < n_out;
-  const int32_t* nrow = nbr + (live ? wave_row0 + lane : 0);
+  // lane l holds the kernel-map entries of row l % R of this wave's R rows
+  const bool live = wave_row0 + lane % R < n_out;
+  const int32_t* nrow = nbr + (live ? wave_row0 + lane % R : 0);
   const int32_t dead = live ? 0 : -1;   // OR-ed into kernel-map entries: rows past n_out have no neighbours
   unsigned long long oob = 0ull;        // lanes that saw an entry outside [0, n_in)
 
@@ -195,17 +203,14 @@ k_spconv_i8(const int8_t* __restrict__ in, const u32x4* __restrict__ wp, const f
 #define EMC2_IDX_LOAD(GROUP, DST)                                                                        \
   _Pragma("unroll") for (int kx_ = 0; kx_ < 3; ++kx_)                                                    \
       jq[DST][kx_] = nrow[(int64_t)(3 * ((GROUP) < 9 ? (GROUP) : 8) + kx_) * capacity_out];
-  // A operands of one tap: tile mt, k-step ks <- 16 bytes at channel 64*ks + 16*q of row JROW[16*mt + m].  Three
-  // lane-swap instructions broadcast each 16-lane row of the entries to all four rows.
+  // A operands of one tap: tile mt, k-step ks <- 16 bytes at channel 64*ks + 16*q of row JROW[16*mt + m].  A
+  // lane-swap instruction broadcasts both 16-lane rows of the entries (0101) to all four rows.
 #define EMC2_A_LOAD(JROW, SET)                                                                           \
   {                                                                                                      \
     const uint32_t jr_ = (uint32_t)max((JROW), -1);   /* any negative entry is an absent neighbour */    \
-    const u32x2 h_ = __builtin_amdgcn_permlane32_swap(jr_, jr_, false, false);       /* 0101 | 2323 */   \
-    const u32x2 lo_ = __builtin_amdgcn_permlane16_swap(h_[0], h_[0], false, false);  /* 0000 | 1111 */   \
-    const u32x2 hi_ = __builtin_amdgcn_permlane16_swap(h_[1], h_[1], false, false);  /* 2222 | 3333 */   \
-    const int32_t jm_[4] = {(int32_t)lo_[0], (int32_t)lo_[1], (int32_t)hi_[0], (int32_t)hi_[1]};         \
+    const u32x2 jm_ = __builtin_amdgcn_permlane16_swap(jr_, jr_, false, false);      /* 0000 | 1111 */   \
   _Pragma("unroll") for (int mt_ = 0; mt_ < MT; ++mt_) {                                                 \
-    const int32_t j_ = jm_[mt_];                                                                         \
+    const int32_t j_ = (int32_t)jm_[mt_];                                                                \
     if constexpr (BUF) {                                                                                 \
       /* absent: 2^32 less a row, and a piece of the row: out of range, zero */                          \
       const uint32_t at_ = (uint32_t)j_ * (uint32_t)CIN + 16u * (uint32_t)q;                             \
@@ -339,7 +344,7 @@ template <int CIN, int COUT, int OUTQ, int F8 = 0>
 void launch_i8(const void* d_in, const void* d_wp, const float* d_mul, const float* d_add, int relu, float inv_out_scale,
                const int32_t* d_nbr, const int32_t* d_n_out, int64_t capacity_out, int32_t n_in, int32_t* dev_flags,
                const void* d_zero_row, void* d_out, hipStream_t s) {
-  const int64_t rows_per_block = kQWaves * 64;
+  const int64_t rows_per_block = kQWaves * 16 * QCfg<CIN, COUT>::MT;
 #define LAUNCH(BUF)                                                                                                           \
   hipLaunchKernelGGL((k_spconv_i8<CIN, COUT, OUTQ, F8, BUF>), dim3((unsigned)(emc2_div_up(capacity_out, rows_per_block) + 8)), \
                      dim3(kQThreads), 0, s, (const int8_t*)d_in, (const u32x4*)d_wp, d_mul, d_add, relu, inv_out_scale, d_nbr, \

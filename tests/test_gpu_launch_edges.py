@@ -225,6 +225,40 @@ def test_quantised_conv_addressing_and_negative_entries(cin):
     ctx.close()
 
 
+@pytest.mark.parametrize("e4m3", [False, True])
+@pytest.mark.parametrize("cin,cout", [(64, 64), (128, 32)])
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 31, 32, 33, 127, 128, 129, 1025])
+def test_quantised_conv_row_counts(n, cin, cout, e4m3):
+    """Row counts at the edges of a tile (16), a wave (32) and a block (128).  Small whole numbers, so both forms are exact."""
+    n_in = 300
+    g = torch.Generator(device="cuda").manual_seed(n + cin)
+    xv = torch.randint(-2, 3, (n_in, cin), generator=g, device="cuda")
+    wv = torch.randint(-1, 2, (27, cin, cout), generator=g, device="cuda")
+    nbr = torch.randint(-n_in, n_in, (27, n + 5), generator=g, device="cuda").clamp_(min=-1).to(torch.int32)
+    exp = torch.zeros((n, cout), device="cuda", dtype=torch.float64)
+    for k in range(27):
+        j = nbr[k, :n].long()
+        exp += torch.where((j >= 0)[:, None], xv[j.clamp(min=0)].double() @ wv[k].double(), 0.0)
+    ctx = B.Context(16, 16, 64, n_slots=1)
+    if e4m3:
+        x = torch.empty((n_in, cin), dtype=torch.uint8, device="cuda")
+        w = torch.empty((27, cin, cout), dtype=torch.uint8, device="cuda")
+        ctx.quantize_e4m3(xv.float(), 1.0, x)
+        ctx.quantize_e4m3(wv.float(), 1.0, w)
+    else:
+        x, w = xv.to(torch.int8), wv.to(torch.int8)
+    wp = torch.empty((27 * cin * cout,), dtype=torch.int8, device="cuda")
+    ctx.pack_weights_i8(w.view(torch.int8), wp)
+    one, zero = torch.ones(cout, device="cuda"), torch.zeros(cout, device="cuda")
+    y = torch.full((n + 5, cout), 7.0, dtype=torch.float16, device="cuda")
+    call = ctx.spconv_e4m3 if e4m3 else ctx.spconv_i8
+    call(x, wp, cin, cout, one, zero, False, nbr, torch.tensor([n], dtype=torch.int32, device="cuda"), n + 5, y, n_in_rows=n_in)
+    ctx.status_sync()
+    assert exp.abs().max() <= 2048                               # every sum is a whole number that fp16 holds
+    assert torch.equal(y[:n].double(), exp) and bool((y[n:] == 7.0).all())
+    ctx.close()
+
+
 @pytest.mark.parametrize("dt", [np.float32, np.float16])
 @pytest.mark.parametrize("n,off", [(1, 0), (7, 0), (8, 0), (9, 0), (2048, 0), (2055, 0), (5000, 1), (5000, 4)])
 def test_quantisers_tails_and_alignment(n, off, dt):
