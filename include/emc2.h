@@ -249,12 +249,14 @@ emc2_status emc2_pack_weights(emc2_ctx* ctx, emc2_dtype dtype, const void* d_w, 
  * are not written.
  *   map_hint: EMC2_CONV_SUBM / EMC2_CONV_STRIDED if d_nbr came from emc2_build_kmap with that kind, else
  *   EMC2_MAP_ANY.  A scheduling hint only (submanifold maps over key-sorted voxels let the three kx
- *   taps of a (dz, dy) pair share one fetch of input rows): results do not depend on it, for any table.
+ *   taps of a (dz, dy) pair share one fetch of input rows): no table is read wrongly under any hint.  The fp32 sum may be taken
+ *   in another order (128 -> 128: 64 channels of three taps at a time under EMC2_CONV_SUBM), so 16-bit results of that shape can
+ *   differ in their rounding; each order is fixed, run to run.
  */
 #define EMC2_MAP_ANY (-1)
 /*
  * Name of the device kernel emc2_spconv launches for these arguments ("k_spconv_span", "k_spconv_direct",
- * "k_spconv_mfma", "k_spconv_rows", "k_spconv_small" or "k_spconv_alu"): lets a profile be matched to a layer.  Host-only
+ * "k_spconv_narrow", "k_spconv_mfma", "k_spconv_rows", "k_spconv_small" or "k_spconv_alu"): lets a profile be matched to a layer.  Host-only
  * query about this library's kernel selection (no GPU work, no passage of the paper behind it); the string
  * is static.  NULL for a dtype emc2_spconv rejects.
  */

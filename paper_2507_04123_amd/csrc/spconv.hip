@@ -344,14 +344,14 @@ extern "C" int32_t emc2_spconv_uses_mfma(emc2_dtype dtype, int32_t cin, int32_t 
   return (dtype == EMC2_F16 || dtype == EMC2_BF16) && emc2_spconv_mfma_supported(cin, cout) ? 1 : 0;
 }
 
-// shapes of the thread-per-row vector-ALU kernel (fp32) and of the small-channel matrix-core kernel (16-bit); 16 -> 32
-// was tried on the latter and is three times slower there than on the staged MFMA kernel
+// shapes of the thread-per-row vector-ALU kernel (fp32) and of the small-channel matrix-core kernel (16-bit)
 static bool small_covers(int cin, int cout) { return (cin == 4 && (cout == 16 || cout == 32)) || (cin == 16 && cout == 16); }
 static bool rows_covers(int cin, int cout) { return small_covers(cin, cout); }
 
 extern "C" const char* emc2_spconv_kernel(emc2_dtype dtype, int32_t cin, int32_t cout, int32_t map_hint) {
   if (dtype != EMC2_F32 && dtype != EMC2_F16 && dtype != EMC2_BF16) return nullptr;
   if (emc2_spconv_uses_mfma(dtype, cin, cout)) {
+    if (emc2_spconv_narrow_supported(cin, cout)) return "k_spconv_narrow";
     if (!emc2_spconv_direct_supported(cin, cout)) return "k_spconv_mfma";
     return (map_hint == EMC2_CONV_SUBM && emc2_spconv_span_supported(cin, cout)) ? "k_spconv_span" : "k_spconv_direct";
   }
@@ -415,7 +415,10 @@ extern "C" emc2_status emc2_spconv(emc2_ctx* ctx, emc2_dtype dtype, const void* 
       else emc2_spconv_mfma_pack(d_w, cin, cout, ctx->wpack, s);
       wp = ctx->wpack;
     }
-    if (!direct)
+    if (emc2_spconv_narrow_supported(cin, cout))
+      emc2_spconv_narrow_launch(dtype, d_in, wp, d_scale, d_shift, (int)epilogue, d_nbr, d_n_out, capacity_out, n_in, flags,
+                                cin, ctx->zero_row, d_out, s);
+    else if (!direct)
       emc2_spconv_mfma_launch(dtype, d_in, wp, d_scale, d_shift, (int)epilogue, d_nbr, d_n_out, capacity_out, n_in, flags,
                               cin, cout, d_out, s);
     else if (map_hint == EMC2_CONV_SUBM && emc2_spconv_span_supported(cin, cout))

@@ -17,18 +17,18 @@
 // LDS holds only the weights of the current and the next tap (packed in B-fragment order, copied once
 // per block and tap, requested three taps ahead) and a small tile for the epilogue's transposition.
 //
-// A block is 4 waves; a wave owns 32 consecutive output rows (2 tiles of 16; 64 rows = 4 tiles at 32 -> 32, where
-// the accumulators are few) and all Cout columns, so the fp32 accumulators never leave registers.  Gathers run 3
+// A block is 4 waves; a wave owns 32 consecutive output rows (2 tiles of 16) and all Cout columns, so the fp32
+// accumulators never leave registers.  Gathers run 3
 // taps ahead of their use; kernel-map entries two (dz,dy) groups ahead.  Every load is unconditional so the
-// compiler can count the loads in flight.  Shapes: Cin, Cout in {32, 64}, and 64 -> 128 / 128 -> 128, where a
+// compiler can count the loads in flight.  Shapes: 32 -> 64, 64 -> 32, 64 -> 64, and 64 -> 128 / 128 -> 128, where a
 // tap's matrix work per gathered byte doubles and the kernel leaves the staged per-tap kernel behind by a third.
 //
 // SKIP: a block first reads all 27 map entries of its rows, keeps them in LDS, and runs only the (dz, dy) groups in which
 // some row has one.  A stride-2 map leaves 31-41 % of the (group, 128 rows) pairs empty, a transposed one 52-62 % (a line of
 // fine sites has one or two of three dy and dz).  Alone, us before / with it: transposed 64 -> 64 over 223 k rows 59 / 45,
 // 64 -> 32 over 304 k 60 / 48; stride-2 32 -> 64 over 573 k 82 / 71, over 852 k 114 / 90, over 223 k 35 / 34.  Submanifold maps
-// (a fifth of the groups empty) and 128 output channels gain less than the longer way to the first operands costs (32 -> 32
-// over 304 k 40 / 43, 64 -> 128 over 67 k 50 / 52, 128 -> 128 103 / 113), so they keep the straight walk over the 27 taps.
+// (a fifth of the groups empty) and 128 output channels gain less than the longer way to the first operands costs
+// (64 -> 128 over 67 k 50 / 52, 128 -> 128 103 / 113), so they keep the straight walk over the 27 taps.
 #include <hip/hip_bf16.h>
 #include <hip/hip_fp16.h>
 
@@ -85,9 +85,9 @@ __global__ void __launch_bounds__(256) k_pack_weights_direct(const uint16_t* __r
 }
 
 template <int CIN, int COUT> struct DirectCfg {
-  // 16-row tiles per wave (2 or 4): fewer rows per wave mean fewer accumulators and operands in flight, so more
+  // 16-row tiles per wave: fewer rows per wave mean fewer accumulators and operands in flight, so more
   // waves fit a SIMD and cover each other's stalls; more rows per wave reuse a weight fragment read more often
-  static constexpr int MT = (CIN <= 32 && COUT <= 32) ? 4 : 2;
+  static constexpr int MT = 2;
   // waves per SIMD the register allocator must leave room for (the 128-channel shapes keep 64-128 accumulators
   // and as many operands in flight)
   // (128 -> 128 ends up at one wave per SIMD whatever is asked for here -- 83 KB of LDS, 360 registers -- and the
@@ -113,7 +113,7 @@ k_spconv_direct(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, c
   constexpr int NT = COUT / 16;               // 16-column tiles
   constexpr int MT = DirectCfg<CIN, COUT>::MT;   // 16-row tiles per wave
   constexpr int R = 16 * MT;                  // rows per wave
-  static_assert(MT == 2 || MT == 4, "the lane-swap broadcast below handles 2 or 4 tiles");
+  static_assert(MT == 2, "the lane-swap broadcast below handles two tiles");
   constexpr int W16 = KS * NT * 64;           // 16-byte weight pieces per tap
   constexpr int WPT = (W16 + kDThreads - 1) / kDThreads;
   static_assert((W16 & (W16 - 1)) == 0, "piece count is a power of two");
@@ -175,20 +175,15 @@ k_spconv_direct(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, c
   _Pragma("unroll") for (int kx_ = 0; kx_ < 3; ++kx_)                                                    \
       jq[DST][kx_] = nrow[(int64_t)(3 * ((GROUP) < 9 ? (GROUP) : 8) + kx_) * nbr_pitch];
   // A operands of one tap: tile mt, k-step ks <- 16 bytes at channel 32*ks + 8*q of row JROW[16*mt + m]
-  // The entries of rows 16*mt .. 16*mt+15 sit in lanes 16*mt .. 16*mt+15; every lane needs the one of its
-  // column m for each mt.  Three lane-swap instructions broadcast each 16-lane row to all four rows (no LDS
+  // The entries of rows 16*mt .. 16*mt+15 sit in lanes 16*mt .. 16*mt+15 of both halves; every lane needs the one of
+  // its column m for each mt.  A lane-swap instruction broadcasts each 16-lane row to all four rows (no LDS
   // round trip: a ds_bpermute per tile costs a serialized ~120-cycle wait each).
 #define EMC2_A_LOAD(JROW, SET)                                                                           \
   {                                                                                                      \
     const uint32_t jr_ = (uint32_t)max((JROW), -1);   /* any negative entry is an absent neighbour */    \
-    /* R = 64: lane rows are 0123 -> 0101 | 2323;  R = 32: they already are 0101 */                      \
-    u32x2 h_ = {jr_, jr_};                                                                               \
-    if constexpr (MT == 4) h_ = __builtin_amdgcn_permlane32_swap(jr_, jr_, false, false);                \
-    const u32x2 lo_ = __builtin_amdgcn_permlane16_swap(h_[0], h_[0], false, false);  /* 0000 | 1111 */   \
-    const u32x2 hi_ = __builtin_amdgcn_permlane16_swap(h_[1], h_[1], false, false);  /* 2222 | 3333 */   \
-    const int32_t jm_[4] = {(int32_t)lo_[0], (int32_t)lo_[1], (int32_t)hi_[0], (int32_t)hi_[1]};         \
+    const u32x2 jm_ = __builtin_amdgcn_permlane16_swap(jr_, jr_, false, false);      /* 0101 -> 0000 | 1111 */ \
   _Pragma("unroll") for (int mt_ = 0; mt_ < MT; ++mt_) {                                                 \
-    const int32_t j_ = jm_[mt_];                                                                         \
+    const int32_t j_ = (int32_t)jm_[mt_];                                                                \
     if constexpr (BUF) {                                                                                 \
       /* absent: 2^32 less a row, and a piece of the row: out of range, zero */                          \
       const uint32_t at_ = (uint32_t)j_ * (uint32_t)(CIN * 2) + 16u * (uint32_t)q;                       \
@@ -395,7 +390,7 @@ void launch_direct(const void* d_in, const void* d_wp, const float* d_scale, con
     if (buf) LAUNCH(true, true, SKIP, kDGrid);      \
     else LAUNCH(true, false, SKIP, kDGrid);         \
   }
-  if constexpr (CIN + COUT > 64 && COUT <= 64) {
+  if constexpr (COUT <= 64) {
     if (skip) {
       LAUNCH_FORM(true)
       return;
@@ -428,8 +423,8 @@ void emc2_spconv_direct_launch(emc2_dtype dtype, const void* d_in, const void* d
                                d_zero_row, skip, d_out, stream);                                                       \
     return;                                                                                                            \
   }
-  CASE(EMC2_F16, 32, 32) CASE(EMC2_F16, 32, 64) CASE(EMC2_F16, 64, 32) CASE(EMC2_F16, 64, 64)
-  CASE(EMC2_BF16, 32, 32) CASE(EMC2_BF16, 32, 64) CASE(EMC2_BF16, 64, 32) CASE(EMC2_BF16, 64, 64)
+  CASE(EMC2_F16, 32, 64) CASE(EMC2_F16, 64, 32) CASE(EMC2_F16, 64, 64)
+  CASE(EMC2_BF16, 32, 64) CASE(EMC2_BF16, 64, 32) CASE(EMC2_BF16, 64, 64)
   CASE(EMC2_F16, 128, 128) CASE(EMC2_F16, 64, 128) CASE(EMC2_BF16, 128, 128) CASE(EMC2_BF16, 64, 128)
 #undef CASE
 }

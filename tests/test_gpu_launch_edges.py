@@ -225,6 +225,38 @@ def test_quantised_conv_addressing_and_negative_entries(cin):
     ctx.close()
 
 
+# around a wave's 32 rows, a block's 128 or 256, and the rows of all resident blocks (131 072); more rows vouched for than 4 GiB hold
+@pytest.mark.parametrize("dt", [torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("cin", [16, 32])
+@pytest.mark.parametrize("n,rows_in", [(0, None), (1, None), (31, None), (32, 1 << 28), (33, None), (127, None), (129, None), (255, None),
+                                       (257, 1 << 28), (131072, None), (131073, None), (262144 + 4001, None)])
+def test_narrow_conv_row_counts(n, rows_in, cin, dt):
+    """Small whole numbers: every fp32 sum is exact in any order, and both 16-bit types hold it."""
+    n_in, cout, cap = 4000, 32, n + 7
+    g = torch.Generator(device="cuda").manual_seed(n + cin)
+    x = torch.randint(-1, 2, (n_in, cin), generator=g, device="cuda").to(dt)
+    w = torch.randint(-1, 2, (27, cin, cout), generator=g, device="cuda").to(dt)
+    nbr = torch.randint(-n_in, n_in, (27, cap), generator=g, device="cuda")
+    nbr = torch.where(nbr < 0, torch.where(nbr % 3 == 0, nbr * 100000, -1), nbr).to(torch.int32).contiguous()
+    ctx = B.Context(16, 16, 64, n_slots=1)
+    edt = F16 if dt == torch.float16 else BF16
+    wp = torch.empty_like(w)
+    ctx.pack_weights(edt, w, wp)
+    y = torch.full((cap, cout), 77.0, dtype=dt, device="cuda")
+    scale, shift = torch.full((cout,), 0.5, device="cuda"), torch.full((cout,), 1.0, device="cuda")
+    ctx.spconv(edt, x, wp, scale, shift, EPI_AFFINE_RELU, nbr, torch.tensor([n], dtype=torch.int32, device="cuda"), cap, y,
+               w_layout=B.W_PACKED, n_in_rows=rows_in)
+    ctx.status_sync()
+    exp = torch.zeros((n, cout), device="cuda")
+    for k in range(27):
+        rows = (nbr[k][:n] >= 0).nonzero().squeeze(1)
+        exp[rows] += x[nbr[k][rows].long()].float() @ w[k].float()
+    assert n == 0 or float(exp.abs().max()) <= 254               # half of it and one: at most 128, a half at the least step
+    want = (exp * 0.5 + 1.0).clamp_(min=0.0)
+    assert torch.equal(y[:n].float(), want.to(dt).float()) and bool((y[n:] == 77.0).all())
+    ctx.close()
+
+
 @pytest.mark.parametrize("e4m3", [False, True])
 @pytest.mark.parametrize("cin,cout", [(64, 64), (128, 32)])
 @pytest.mark.parametrize("n", [1, 15, 16, 17, 31, 32, 33, 127, 128, 129, 1025])
