@@ -88,9 +88,6 @@ template <int CIN, int COUT> struct Pipe {
   static constexpr int NB = WD == 3 ? 3 : 2;                      // weight buffers in LDS
   // waves per SIMD the register allocator must leave room for (2 where LDS also lets two blocks share a CU)
   static constexpr int MINW = (CIN <= 64 && COUT <= 64) ? 2 : 1;
-  // skip the LDS and matrix work of a tap at which none of the wave's 64 rows has a neighbour: measured to
-  // pay only where a tap is expensive (Cin = 64) and the accumulators live in ordinary VGPRs (MINW = 2)
-  static constexpr bool SKIP = (CIN == 64 && COUT <= 64);
 };
 
 template <int DT, int CIN, int COUT, int MT>
@@ -224,12 +221,8 @@ __global__ void __launch_bounds__(kThreads, (Pipe<CIN, COUT>::MINW)) k_spconv_mf
       // weights of tap + WD: global -> registers (the set was emptied at the end of the previous tap)
       EMC2_W_LOAD(tap + WD < 27 ? tap + WD : 26, kx % WD)
       // gathered rows of this tap: registers -> wave-private LDS tile
-      // a tap at which none of the wave's 64 rows has a neighbour does no LDS or matrix work at all; the
-      // loads stay unconditional (see above), only their use is skipped (wave-uniform branch)
-      if (!Pipe<CIN, COUT>::SKIP || mask != 0ull) {
 #pragma unroll
-        for (int i = 0; i < NI; ++i) my_tile[(i * RPI + srow) * ROW16 + (SWZ ? (schunk ^ (((i * RPI + srow) >> SWSH) & (CH - 1))) : schunk)] = sreg[kx % D][i];
-      }
+      for (int i = 0; i < NI; ++i) my_tile[(i * RPI + srow) * ROW16 + (SWZ ? (schunk ^ (((i * RPI + srow) >> SWSH) & (CH - 1))) : schunk)] = sreg[kx % D][i];
       // the freed register set takes the gather of tap + D (absent entries re-read row 0 and are masked)
       const int32_t past = g < 8 ? 0 : -1;   // entries of "group 9" do not exist
       if constexpr (D == 3) {
@@ -239,25 +232,22 @@ __global__ void __launch_bounds__(kThreads, (Pipe<CIN, COUT>::MINW)) k_spconv_mf
       }
       __builtin_amdgcn_wave_barrier();
       const u32x4* wb = wl[tap % NB];
-      if (!Pipe<CIN, COUT>::SKIP || mask != 0ull) {
-        // no per-tile branches inside: with finer-grained conditions around the MFMAs the compiler starts
-        // copying accumulators between register classes on every tap
-        const bool v0 = (mask >> m) & 1ull, v1 = (mask >> (32 + m)) & 1ull;
+      // no branches around the MFMAs: with them the compiler copies accumulators between register classes on every tap
+      const bool v0 = (mask >> m) & 1ull, v1 = (mask >> (32 + m)) & 1ull;
 #pragma unroll
-        for (int t = 0; t < KS; ++t) {
-          u32x4 b[NT];
+      for (int t = 0; t < KS; ++t) {
+        u32x4 b[NT];
 #pragma unroll
-          for (int j = 0; j < NT; ++j) b[j] = wb[(t * NT + j) * 64 + lane];
-          const int ca = SWZ ? ((2 * t + h) ^ ((m >> SWSH) & (CH - 1))) : 2 * t + h;   // rows m and 32 + m share a key
-          u32x4 a0 = my_tile[m * ROW16 + ca];
-          u32x4 a1 = my_tile[(32 + m) * ROW16 + ca];
-          a0 = v0 ? a0 : u32x4{0u, 0u, 0u, 0u};
-          a1 = v1 ? a1 : u32x4{0u, 0u, 0u, 0u};
+        for (int j = 0; j < NT; ++j) b[j] = wb[(t * NT + j) * 64 + lane];
+        const int ca = SWZ ? ((2 * t + h) ^ ((m >> SWSH) & (CH - 1))) : 2 * t + h;   // rows m and 32 + m share a key
+        u32x4 a0 = my_tile[m * ROW16 + ca];
+        u32x4 a1 = my_tile[(32 + m) * ROW16 + ca];
+        a0 = v0 ? a0 : u32x4{0u, 0u, 0u, 0u};
+        a1 = v1 ? a1 : u32x4{0u, 0u, 0u, 0u};
 #pragma unroll
-          for (int j = 0; j < NT; ++j) {
-            acc[0][j] = Mma<DT>::run(a0, b[j], acc[0][j]);
-            acc[1][j] = Mma<DT>::run(a1, b[j], acc[1][j]);
-          }
+        for (int j = 0; j < NT; ++j) {
+          acc[0][j] = Mma<DT>::run(a0, b[j], acc[0][j]);
+          acc[1][j] = Mma<DT>::run(a1, b[j], acc[1][j]);
         }
       }
       __builtin_amdgcn_wave_barrier();
