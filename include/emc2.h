@@ -249,9 +249,7 @@ emc2_status emc2_pack_weights(emc2_ctx* ctx, emc2_dtype dtype, const void* d_w, 
  * are not written.
  *   map_hint: EMC2_CONV_SUBM / EMC2_CONV_STRIDED if d_nbr came from emc2_build_kmap with that kind, else
  *   EMC2_MAP_ANY.  A scheduling hint only (submanifold maps over key-sorted voxels let the three kx
- *   taps of a (dz, dy) pair share one fetch of input rows): no table is read wrongly under any hint.  The fp32 sum may be taken
- *   in another order (128 -> 128: 64 channels of three taps at a time under EMC2_CONV_SUBM), so 16-bit results of that shape can
- *   differ in their rounding; each order is fixed, run to run.
+ *   taps of a (dz, dy) pair share one fetch of input rows): results do not depend on it, for any table.
  */
 #define EMC2_MAP_ANY (-1)
 /*

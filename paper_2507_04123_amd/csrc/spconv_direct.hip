@@ -23,12 +23,18 @@
 // compiler can count the loads in flight.  Shapes: 32 -> 64, 64 -> 32, 64 -> 64, and 64 -> 128 / 128 -> 128, where a
 // tap's matrix work per gathered byte doubles and the kernel leaves the staged per-tap kernel behind by a third.
 //
+// 128 input channels are taken in two shares, the lower 64 of a group's three taps and then the upper: the order in which
+// the kernel of the submanifold maps adds, so that the map hint never changes a bit.  A row's two 128-byte lines are still
+// read once each.  Against whole taps (83 KB of LDS, 360 registers, one block a CU; now 50 KB, 250, two): transposed 128 -> 128
+// over 304 k rows 310 / 255 us, stride-2 over 69 k 104 / 93, over 27 k 35.4 / 38.0 (a block a CU: twice the barriers show; a
+// barrier for every two steps, with 64 KB of weights, 36.9 there and 258 over 304 k).
+//
 // SKIP: a block first reads all 27 map entries of its rows, keeps them in LDS, and runs only the (dz, dy) groups in which
 // some row has one.  A stride-2 map leaves 31-41 % of the (group, 128 rows) pairs empty, a transposed one 52-62 % (a line of
 // fine sites has one or two of three dy and dz).  Alone, us before / with it: transposed 64 -> 64 over 223 k rows 59 / 45,
 // 64 -> 32 over 304 k 60 / 48; stride-2 32 -> 64 over 573 k 82 / 71, over 852 k 114 / 90, over 223 k 35 / 34.  Submanifold maps
 // (a fifth of the groups empty) and 128 output channels gain less than the longer way to the first operands costs
-// (64 -> 128 over 67 k 50 / 52, 128 -> 128 103 / 113), so they keep the straight walk over the 27 taps.
+// (64 -> 128 over 67 k 50 / 52, 128 -> 128 in whole taps 103 / 113), so they keep the straight walk over the 27 taps.
 #include <hip/hip_bf16.h>
 #include <hip/hip_fp16.h>
 
@@ -90,9 +96,6 @@ template <int CIN, int COUT> struct DirectCfg {
   static constexpr int MT = 2;
   // waves per SIMD the register allocator must leave room for (the 128-channel shapes keep 64-128 accumulators
   // and as many operands in flight)
-  // (128 -> 128 ends up at one wave per SIMD whatever is asked for here -- 83 KB of LDS, 360 registers -- and the
-  // compiler says so in a warning; asking for one outright, or forcing two with a shorter weight prefetch, were
-  // both measured slower)
   static constexpr int MINW = (CIN >= 128 || COUT >= 128) ? 2 : 3;
 };
 
@@ -109,18 +112,19 @@ k_spconv_direct(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, c
                 const float* __restrict__ shift, int epilogue, const int32_t* __restrict__ nbr,
                 const int32_t* __restrict__ d_n_out, int64_t capacity_out, int32_t n_in, int32_t* __restrict__ dev_flags,
                 const uint16_t* __restrict__ zrow, uint16_t* __restrict__ out) {
-  constexpr int KS = CIN / 32;                // k-steps per tap
+  constexpr int KH = CIN > 64 ? CIN / 64 : 1; // shares of the channels, one after the other over the three taps of a group
+  constexpr int KS = CIN / 32 / KH;           // k-steps per tap and share
   constexpr int NT = COUT / 16;               // 16-column tiles
   constexpr int MT = DirectCfg<CIN, COUT>::MT;   // 16-row tiles per wave
   constexpr int R = 16 * MT;                  // rows per wave
   static_assert(MT == 2, "the lane-swap broadcast below handles two tiles");
-  constexpr int W16 = KS * NT * 64;           // 16-byte weight pieces per tap
+  constexpr int W16 = KS * NT * 64;           // 16-byte weight pieces per tap and share
   constexpr int WPT = (W16 + kDThreads - 1) / kDThreads;
   static_assert((W16 & (W16 - 1)) == 0, "piece count is a power of two");
   // a tap with fewer pieces than threads is copied redundantly by the surplus threads (same values to the
   // same place) rather than under a branch
   constexpr int WMASK = W16 - 1;
-  constexpr int NA = MT * KS;                 // A-operand loads per tap
+  constexpr int NA = MT * KS;                 // A-operand loads per tap and share
   constexpr int OCH = COUT / 8;               // 16-byte pieces per output row
   constexpr int OPITCH = (OCH + 1) * 8;       // epilogue tile row pitch in 16-bit units
   // per wave: a 16-row tile of the epilogue and, before it, its rows' map entries
@@ -174,11 +178,11 @@ k_spconv_direct(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, c
 #define EMC2_IDX_LOAD(GROUP, DST)                                                                        \
   _Pragma("unroll") for (int kx_ = 0; kx_ < 3; ++kx_)                                                    \
       jq[DST][kx_] = nrow[(int64_t)(3 * ((GROUP) < 9 ? (GROUP) : 8) + kx_) * nbr_pitch];
-  // A operands of one tap: tile mt, k-step ks <- 16 bytes at channel 32*ks + 8*q of row JROW[16*mt + m]
+  // A operands of one tap and share: tile mt, k-step ks <- 16 bytes at channel 64*SHARE + 32*ks + 8*q of row JROW[16*mt + m]
   // The entries of rows 16*mt .. 16*mt+15 sit in lanes 16*mt .. 16*mt+15 of both halves; every lane needs the one of
   // its column m for each mt.  A lane-swap instruction broadcasts each 16-lane row to all four rows (no LDS
   // round trip: a ds_bpermute per tile costs a serialized ~120-cycle wait each).
-#define EMC2_A_LOAD(JROW, SET)                                                                           \
+#define EMC2_A_LOAD(JROW, SHARE, SET)                                                                    \
   {                                                                                                      \
     const uint32_t jr_ = (uint32_t)max((JROW), -1);   /* any negative entry is an absent neighbour */    \
     const u32x2 jm_ = __builtin_amdgcn_permlane16_swap(jr_, jr_, false, false);      /* 0101 -> 0000 | 1111 */ \
@@ -186,19 +190,19 @@ k_spconv_direct(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, c
     const int32_t j_ = (int32_t)jm_[mt_];                                                                \
     if constexpr (BUF) {                                                                                 \
       /* absent: 2^32 less a row, and a piece of the row: out of range, zero */                          \
-      const uint32_t at_ = (uint32_t)j_ * (uint32_t)(CIN * 2) + 16u * (uint32_t)q;                       \
+      const uint32_t at_ = (uint32_t)j_ * (uint32_t)(CIN * 2) + 16u * (uint32_t)q + 128u * (SHARE);      \
       _Pragma("unroll") for (int ks_ = 0; ks_ < KS; ++ks_)                                               \
           areg[SET][mt_ * KS + ks_] = buffer_row16(rows, at_ + 64u * (uint32_t)ks_);                     \
     } else {                                                                                             \
-      const uint16_t* src_ = (j_ >= 0 ? in + (int64_t)j_ * CIN : zrow) + 8 * q;                          \
+      const uint16_t* src_ = (j_ >= 0 ? in + (int64_t)j_ * CIN : zrow) + 8 * q + 64 * (SHARE);           \
       _Pragma("unroll") for (int ks_ = 0; ks_ < KS; ++ks_)                                               \
           areg[SET][mt_ * KS + ks_] = *reinterpret_cast<const u32x4*>(src_ + 32 * ks_);                  \
     }                                                                                                    \
   }                                                                                                      \
   }
-#define EMC2_W_LOAD(TAP, SET)                                                                            \
+#define EMC2_W_LOAD(TAP, SHARE, SET)                                                                     \
   {                                                                                                      \
-    const u32x4* wsrc_ = wp + (int64_t)(TAP) * W16;                                                      \
+    const u32x4* wsrc_ = wp + (int64_t)((TAP) * KH + (SHARE)) * W16;                                     \
     _Pragma("unroll") for (int i_ = 0; i_ < WPT; ++i_)                                                   \
         wq[SET][i_] = wsrc_[(tid + i_ * kDThreads) & WMASK];                                     \
   }
@@ -246,10 +250,10 @@ k_spconv_direct(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, c
       int g = __builtin_ctz(groups);
       groups &= groups - 1;
 #pragma unroll
-      for (int kx = 0; kx < 3; ++kx) EMC2_W_LOAD(3 * g + kx, kx)
+      for (int kx = 0; kx < 3; ++kx) EMC2_W_LOAD(3 * g + kx, 0, kx)
       EMC2_ENTRIES(g)
 #pragma unroll
-      for (int kx = 0; kx < 3; ++kx) EMC2_A_LOAD(jq[0][kx], kx)
+      for (int kx = 0; kx < 3; ++kx) EMC2_A_LOAD(jq[0][kx], 0, kx)
       EMC2_W_STORE(0, 0)
       __syncthreads();
       uint32_t buf = 0;
@@ -260,9 +264,9 @@ k_spconv_direct(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, c
 #pragma unroll
         for (int kx = 0; kx < 3; ++kx) {
           // weights of the next group's tap: global -> registers (the set was emptied at the end of the previous tap)
-          EMC2_W_LOAD(3 * g + kx, kx)
+          EMC2_W_LOAD(3 * g + kx, 0, kx)
           EMC2_TAP(wl[buf], kx)
-          EMC2_A_LOAD(jq[0][kx] | past, kx)               // the freed register set takes the next group's operands
+          EMC2_A_LOAD(jq[0][kx] | past, 0, kx)            // the freed register set takes the next group's operands
           __builtin_amdgcn_wave_barrier();
           // weights of the next tap: registers -> the other LDS buffer; the barrier publishes them and retires the buffer
           // just read
@@ -280,13 +284,13 @@ k_spconv_direct(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, c
   EMC2_IDX_LOAD(0, 0)
   EMC2_IDX_LOAD(1, 1)
   EMC2_IDX_LOAD(2, 2)
-  EMC2_W_LOAD(0, 0)
+  EMC2_W_LOAD(0, 0, 0)
   EMC2_W_STORE(0, 0)
-  EMC2_W_LOAD(1, 1)
-  EMC2_W_LOAD(2, 2)
-  EMC2_A_LOAD(emc2_entry(jq[0][0], dead, n_in, oob), 0)
-  EMC2_A_LOAD(emc2_entry(jq[0][1], dead, n_in, oob), 1)
-  EMC2_A_LOAD(emc2_entry(jq[0][2], dead, n_in, oob), 2)
+  EMC2_W_LOAD(1, 0, 1)
+  EMC2_W_LOAD(2, 0, 2)
+  EMC2_A_LOAD(emc2_entry(jq[0][0], dead, n_in, oob), 0, 0)
+  EMC2_A_LOAD(emc2_entry(jq[0][1], dead, n_in, oob), 0, 1)
+  EMC2_A_LOAD(emc2_entry(jq[0][2], dead, n_in, oob), 0, 2)
   __syncthreads();
 
   for (int g = 0; g < 9; ++g) {
@@ -294,20 +298,25 @@ k_spconv_direct(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, c
     int32_t jn[3];
 #pragma unroll
     for (int kx = 0; kx < 3; ++kx) jn[kx] = nrow[(int64_t)(3 * (g + 3 < 9 ? g + 3 : 8) + kx) * nbr_pitch];
+    const int32_t past = g < 8 ? 0 : -1;      // entries of "group 9" do not exist
 #pragma unroll
-    for (int kx = 0; kx < 3; ++kx) {
-      const int tap = 3 * g + kx;
-      // weights of tap + 3: global -> registers (the set was emptied at the end of the previous tap)
-      EMC2_W_LOAD(tap + 3 < 27 ? tap + 3 : 26, kx)
-      EMC2_TAP(wl[tap & 1], kx)
-      // the freed register set takes the A operands of tap + 3 (entries of "group 9" do not exist)
-      const int32_t past = g < 8 ? 0 : -1;
-      EMC2_A_LOAD(emc2_entry(jq[1][kx], dead | past, n_in, oob), kx)
-      __builtin_amdgcn_wave_barrier();
-      // weights of tap + 1: registers -> the other LDS buffer; the barrier publishes them and retires the
-      // buffer just read
-      EMC2_W_STORE((tap + 1) & 1, (kx + 1) % 3)
-      __syncthreads();
+    for (int h = 0; h < KH; ++h) {
+#pragma unroll
+      for (int kx = 0; kx < 3; ++kx) {
+        const int at = 3 * (KH * g + h) + kx; // steps are numbered in the order in which they are taken
+        // weights three steps on: global -> registers (the set was emptied at the end of the previous step)
+        if (h + 1 < KH) EMC2_W_LOAD(3 * g + kx, h + 1, kx)
+        else EMC2_W_LOAD(g < 8 ? 3 * (g + 1) + kx : 26, 0, kx)
+        EMC2_TAP(wl[at & 1], kx)
+        // the freed register set takes the A operands three steps on
+        if (h + 1 < KH) EMC2_A_LOAD(emc2_entry(jq[0][kx], dead, n_in, oob), h + 1, kx)
+        else EMC2_A_LOAD(emc2_entry(jq[1][kx], dead | past, n_in, oob), 0, kx)
+        __builtin_amdgcn_wave_barrier();
+        // weights of the next step: registers -> the other LDS buffer; the barrier publishes them and retires the
+        // buffer just read
+        EMC2_W_STORE((at + 1) & 1, (kx + 1) % 3)
+        __syncthreads();
+      }
     }
 #pragma unroll
     for (int kx = 0; kx < 3; ++kx) {

@@ -22,7 +22,7 @@
 // rate of the rows), separate waves for loads and for the map (2 + 2: a wave issues a load into LDS only every ~100 cycles),
 // the map read by the computing waves (spills), an order of tiles that keeps neighbouring planes in one L2 (no gain).
 // 64 -> 64, us before / now: 70 k rows 33 / 25-28, 223 k 65 / 58, 248 k bf16 71 / 60, 573 k 142 / 107, 852 k 210 / 161.
-// 128 -> 128 (bf16) on the register-direct kernel, which its gather bounds (two cache lines a row, each touched twice), / here:
+// 128 -> 128 (bf16) on the register-direct kernel (whole taps at a time then), / here:
 // 4 k rows 36 / 19, 32 k 39 / 26, 48 k 70 / 39, 67 k 104 / 71.
 //
 // One pass is what is computed between two barriers.  Normally a group is one pass.  A group whose interval does not fit

@@ -114,6 +114,43 @@ def test_span_conv_passes_of_a_group(n, stretch, dtype, ch):
     ctx.close()
 
 
+def _stretched(n, stretch):
+    """27 taps over n rows: row o reads about row o * stretch, three neighbouring rows at the taps of a group, so that a tile's
+    interval is about `stretch` times its rows; a third of the entries absent, all of a row's and all of a group's too."""
+    g = torch.Generator(device="cuda").manual_seed(7)
+    o = (torch.arange(n, device="cuda") * stretch).long()
+    nbr = torch.stack([o + 4 * (k // 3) + k % 3 for k in range(27)])
+    nbr = torch.where(torch.rand(nbr.shape, generator=g, device="cuda") < 1 / 3, torch.full_like(nbr, -1), nbr)
+    nbr[:, n // 2] = -1
+    nbr[9:12] = -1
+    return nbr.to(torch.int32).contiguous(), int(n * stretch) + 40
+
+
+# The kernels of the hints add in one order: the same bits, whichever form a group takes (one pass, two halves, three taps)
+@pytest.mark.parametrize("n,stretch", [(1, 1.0), (129, 1.0), (1000, 4.0), (16385, 2.5), (81920, 1.0), (81920, 1.5)])
+@pytest.mark.parametrize("dtype", [F16, BF16])
+@pytest.mark.parametrize("ch", [64, 128])
+def test_hint_never_changes_a_bit(n, stretch, dtype, ch):
+    td = torch.float16 if dtype == F16 else torch.bfloat16
+    nbr, n_in = _stretched(n, stretch)
+    g = torch.Generator(device="cuda").manual_seed(n + ch)
+    x = torch.randn((n_in, ch), generator=g, device="cuda").to(td)
+    w = (torch.randn((27, ch, ch), generator=g, device="cuda") * 0.1).to(td)
+    ctx = B.Context(16, 16, 64, n_slots=1)
+    wp = torch.empty_like(w)
+    ctx.pack_weights(dtype, w, wp)
+    got = []
+    for hint, rows in ((B.SUBM, None), (B.MAP_ANY, None), (B.STRIDED, None), (B.MAP_ANY, 1 << 26)):    # the last: rows by address
+        y = torch.empty((n, ch), dtype=td, device="cuda")
+        ctx.spconv(dtype, x, wp, None, None, EPI_NONE, nbr, torch.tensor([n], dtype=torch.int32, device="cuda"), n, y,
+                   w_layout=B.W_PACKED, map_hint=hint, n_in_rows=rows)
+        ctx.status_sync()
+        got.append(y.view(torch.int16))
+    for other in got[1:]:
+        assert torch.equal(got[0], other)
+    ctx.close()
+
+
 @pytest.mark.parametrize("n", [513, 40001, 70001, 131072 + 5000])
 def test_span_conv_rounds_taps_outside_an_interval(n):
     _check_conv(n, 64, 64, B.SUBM, True)
