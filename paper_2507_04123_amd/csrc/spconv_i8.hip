@@ -126,14 +126,23 @@ __global__ void __launch_bounds__(256) k_pack_weights_i8(const int8_t* __restric
 //     (two v_mfma_f32_16x16x32_fp8_fp8 per 16-byte operand: its low and its high 8 bytes; features and packed weights
 //     split the same way, so the contraction pairs the same channels).
 // OUTQ: int8 operands: 1 = int8 output (re-quantised), 0 = fp16 output; E4M3 operands: 1 = fp32 output, 0 = fp16 output.
-// 16-row tiles per wave, and waves per SIMD the register allocator must leave room for.  A launch is bound by the chain of
-// 27 taps (operand latency, weights through LDS, a barrier each) until enough waves cover each other: 64-row waves left a
-// level of 69 k rows with one block a CU and one of 223 k with 1.7, half of the second round idle.  With 32 rows 64 -> 64 took,
-// before / now: int8 223 k rows 39.6 / 37.0 us, 69 k 24.5 / 20.5; E4M3 175 k 35.5 / 34.6, 57 k 24.0 / 20.5; 16 rows: E4M3 the same
-// for small levels, int8 223 k 10 % slower (each operand read feeds half the products).  The other shapes spill at four waves.
-template <int CIN, int COUT> struct QCfg {
-  static constexpr int MT = 2;
-  static constexpr int MINW = CIN == 64 && COUT == 64 ? 4 : 3;
+// Rows a wave.  A launch is bound by the chain of 27 taps (operand latency, weights through LDS, a barrier each) until enough
+// waves cover each other, then by LDS reads of weights, which feed half the products with 32 rows a wave that they feed with
+// 64.  A level of up to kQSmall rows, three blocks of 32-row waves a CU, runs those: 64 -> 64 with 64 rows / 32 rows, us: int8
+// 8 k rows 12.2 / 8.3, 40 k 13.1 / 11.2, 69 k 20.3 / 17.7, 93 k 18.5 / 16.0; E4M3 8 k 14.5 / 9.8, 69 k 23.1 / 19.4.  Beyond, 64 rows:
+// int8 108 k 19.5 / 20.9, 304 k 46 / 53, 562 k 86 / 99; 64 -> 32 over 304 k int8 39 / 43, E4M3 40 / 44.  The row count is the
+// device's, so a kernel holds both forms; the grid, which the host sizes, has a block for each tile of either.  E4M3 runs
+// two matrix instructions for every operand read, so that 32 rows are the better ones there at every size (64 -> 64 163 k
+// rows 34.1 / 29.4, 223 k 43.6 / 38.0, 304 k 57.8 / 57.7; 128 -> 64 60 / 52, 76 / 69, 112 / 115), 64 -> 32 apart.
+// 16 rows: E4M3 the same for small levels, int8 223 k 10 % slower.
+constexpr int64_t kQSmall = 3 * 256 * 128;
+
+// TALL: levels of more than kQSmall rows run 64 rows a wave.  MINW: waves per SIMD the register allocator must leave room for,
+// as many as neither form spills at.
+template <int CIN, int COUT, int F8, bool BUF> struct QCfg {
+  static constexpr bool TALL = !F8 || (CIN == 64 && COUT == 32);
+  static constexpr int MINW = !TALL ? (CIN == 64 && COUT == 64 && BUF ? 4 : 3)
+                                    : CIN == 64 && (COUT == 32 || BUF) ? 3 : 2;
 };
 
 template <int F8> struct QAcc { typedef intx4 type; };
@@ -145,32 +154,35 @@ __device__ __forceinline__ u32x4 buffer_row16(__amdgpu_buffer_rsrc_t rows, uint3
   return __builtin_amdgcn_raw_buffer_load_b128(rows, (int)byte, 0, 0);
 }
 
-template <int CIN, int COUT, int OUTQ, int F8, bool BUF>
-__global__ void __launch_bounds__(kQThreads, (QCfg<CIN, COUT>::MINW))
-k_spconv_i8(const int8_t* __restrict__ in, const u32x4* __restrict__ wp, const float* __restrict__ mul,
-            const float* __restrict__ add, int relu, float inv_out_scale, const int32_t* __restrict__ nbr,
-            const int32_t* __restrict__ d_n_out, int64_t capacity_out, int32_t n_in, int32_t* __restrict__ dev_flags,
-            const int8_t* __restrict__ zrow, void* __restrict__ out) {
+template <int CIN, int COUT, int OUTQ, int F8> struct QLds {
+  static constexpr int W16 = CIN / 64 * (COUT / 16) * 64;    // 16-byte weight pieces per tap
+  static constexpr int ES = F8 ? (OUTQ ? 4 : 2) : (OUTQ ? 1 : 2);   // bytes per output element
+  static constexpr int OCH = COUT * ES / 16;                 // 16-byte pieces per output row
+  u32x4 w[2][W16];
+  u32x4 otile[kQWaves][16 * (OCH + 1)];
+};
+
+// One block's rows, 16 * MT a wave.
+template <int CIN, int COUT, int OUTQ, int F8, bool BUF, int MT>
+__device__ __forceinline__ void
+run_i8(QLds<CIN, COUT, OUTQ, F8>& lds, const int8_t* __restrict__ in, const u32x4* __restrict__ wp, const float* __restrict__ mul,
+       const float* __restrict__ add, int relu, float inv_out_scale, const int32_t* __restrict__ nbr, int64_t n_out,
+       int64_t capacity_out, int32_t n_in, int32_t* __restrict__ dev_flags, const int8_t* __restrict__ zrow, void* __restrict__ out) {
   const __amdgpu_buffer_rsrc_t rows =
       __builtin_amdgcn_make_buffer_rsrc((void*)const_cast<int8_t*>(in), 0, BUF ? (int)((uint32_t)n_in * CIN) : 0, 0x00020000);
   constexpr int KS = CIN / 64;                // k-steps per tap
   constexpr int NT = COUT / 16;               // 16-column tiles
-  constexpr int MT = QCfg<CIN, COUT>::MT;     // 16-row tiles per wave
   constexpr int R = 16 * MT;                  // rows per wave
-  constexpr int W16 = KS * NT * 64;           // 16-byte weight pieces per tap
+  constexpr int W16 = QLds<CIN, COUT, OUTQ, F8>::W16;
   constexpr int WPT = (W16 + kQThreads - 1) / kQThreads;
-  static_assert(MT == 2, "the lane-swap broadcast below handles two tiles");
+  static_assert(MT == 2 || MT == 4, "the lane-swap broadcast below handles two or four tiles");
   static_assert((W16 & (W16 - 1)) == 0, "piece count is a power of two");
   constexpr int WMASK = W16 - 1;              // surplus threads copy redundantly rather than under a branch
   constexpr int NA = MT * KS;                 // A-operand loads per tap
-  constexpr int ES = F8 ? (OUTQ ? 4 : 2) : (OUTQ ? 1 : 2);   // bytes per output element
-  constexpr int OCH = COUT * ES / 16;         // 16-byte pieces per output row
+  constexpr int ES = QLds<CIN, COUT, OUTQ, F8>::ES, OCH = QLds<CIN, COUT, OUTQ, F8>::OCH;
   constexpr int OPITCH = (OCH + 1) * 16;      // epilogue tile row pitch in bytes
-  __shared__ u32x4 wl[2][W16];
-  __shared__ u32x4 otile_s[kQWaves][16 * (OCH + 1)];
+  u32x4 (*wl)[W16] = lds.w;
 
-  int64_t n_out = *d_n_out;
-  if (n_out > capacity_out) n_out = capacity_out;
   // XCD-aware tile assignment: workgroup b runs on XCD b % 8; XCD x takes a contiguous range of tiles
   const int64_t n_tiles = (n_out + kQWaves * R - 1) / (kQWaves * R);
   const int64_t chunk = (n_tiles + 7) / 8;
@@ -203,14 +215,18 @@ k_spconv_i8(const int8_t* __restrict__ in, const u32x4* __restrict__ wp, const f
 #define EMC2_IDX_LOAD(GROUP, DST)                                                                        \
   _Pragma("unroll") for (int kx_ = 0; kx_ < 3; ++kx_)                                                    \
       jq[DST][kx_] = nrow[(int64_t)(3 * ((GROUP) < 9 ? (GROUP) : 8) + kx_) * capacity_out];
-  // A operands of one tap: tile mt, k-step ks <- 16 bytes at channel 64*ks + 16*q of row JROW[16*mt + m].  A
-  // lane-swap instruction broadcasts both 16-lane rows of the entries (0101) to all four rows.
+  // A operands of one tap: tile mt, k-step ks <- 16 bytes at channel 64*ks + 16*q of row JROW[16*mt + m].
+  // Lane-swap instructions broadcast each 16-lane row of the entries (0123, of 32 rows 0101) to all four rows.
 #define EMC2_A_LOAD(JROW, SET)                                                                           \
   {                                                                                                      \
     const uint32_t jr_ = (uint32_t)max((JROW), -1);   /* any negative entry is an absent neighbour */    \
-    const u32x2 jm_ = __builtin_amdgcn_permlane16_swap(jr_, jr_, false, false);      /* 0000 | 1111 */   \
+    u32x2 h_ = {jr_, jr_};                                                                               \
+    if constexpr (MT == 4) h_ = __builtin_amdgcn_permlane32_swap(jr_, jr_, false, false);  /* 0101 | 2323 */ \
+    const u32x2 lo_ = __builtin_amdgcn_permlane16_swap(h_[0], h_[0], false, false);  /* 0000 | 1111 */   \
+    const u32x2 hi_ = __builtin_amdgcn_permlane16_swap(h_[1], h_[1], false, false);  /* 2222 | 3333 */   \
+    const int32_t jm_[4] = {(int32_t)lo_[0], (int32_t)lo_[1], (int32_t)hi_[0], (int32_t)hi_[1]};         \
   _Pragma("unroll") for (int mt_ = 0; mt_ < MT; ++mt_) {                                                 \
-    const int32_t j_ = (int32_t)jm_[mt_];                                                                \
+    const int32_t j_ = jm_[mt_];                                                                         \
     if constexpr (BUF) {                                                                                 \
       /* absent: 2^32 less a row, and a piece of the row: out of range, zero */                          \
       const uint32_t at_ = (uint32_t)j_ * (uint32_t)CIN + 16u * (uint32_t)q;                             \
@@ -306,7 +322,7 @@ k_spconv_i8(const int8_t* __restrict__ in, const u32x4* __restrict__ wp, const f
     ml[j] = mul[16 * j + m];
     ad[j] = add[16 * j + m];
   }
-  uint8_t* otile = reinterpret_cast<uint8_t*>(otile_s[wave]);
+  uint8_t* otile = reinterpret_cast<uint8_t*>(lds.otile[wave]);
   constexpr int OPI = 64 / OCH;               // rows one store instruction covers
   constexpr int ONI = (16 + OPI - 1) / OPI;   // store instructions per 16-row tile
   const int orow = lane / OCH, ochunk = lane % OCH;
@@ -340,13 +356,36 @@ k_spconv_i8(const int8_t* __restrict__ in, const u32x4* __restrict__ wp, const f
   }
 }
 
+template <int CIN, int COUT, int OUTQ, int F8, bool BUF>
+__global__ void __launch_bounds__(kQThreads, (QCfg<CIN, COUT, F8, BUF>::MINW))
+k_spconv_i8(const int8_t* __restrict__ in, const u32x4* __restrict__ wp, const float* __restrict__ mul,
+            const float* __restrict__ add, int relu, float inv_out_scale, const int32_t* __restrict__ nbr,
+            const int32_t* __restrict__ d_n_out, int64_t capacity_out, int32_t n_in, int32_t* __restrict__ dev_flags,
+            const int8_t* __restrict__ zrow, void* __restrict__ out) {
+  __shared__ QLds<CIN, COUT, OUTQ, F8> lds;
+  int64_t n_out = *d_n_out;
+  if (n_out > capacity_out) n_out = capacity_out;
+  using Cfg = QCfg<CIN, COUT, F8, BUF>;
+  if constexpr (Cfg::TALL) {
+    if (n_out > kQSmall) {
+      run_i8<CIN, COUT, OUTQ, F8, BUF, 4>(lds, in, wp, mul, add, relu, inv_out_scale, nbr, n_out, capacity_out, n_in, dev_flags, zrow, out);
+      return;
+    }
+  }
+  run_i8<CIN, COUT, OUTQ, F8, BUF, 2>(lds, in, wp, mul, add, relu, inv_out_scale, nbr, n_out, capacity_out, n_in, dev_flags, zrow, out);
+}
+
 template <int CIN, int COUT, int OUTQ, int F8 = 0>
 void launch_i8(const void* d_in, const void* d_wp, const float* d_mul, const float* d_add, int relu, float inv_out_scale,
                const int32_t* d_nbr, const int32_t* d_n_out, int64_t capacity_out, int32_t n_in, int32_t* dev_flags,
                const void* d_zero_row, void* d_out, hipStream_t s) {
-  const int64_t rows_per_block = kQWaves * 16 * QCfg<CIN, COUT>::MT;
+  int64_t blocks = emc2_div_up(capacity_out, kQWaves * 32);
+  if (QCfg<CIN, COUT, F8, true>::TALL && capacity_out > kQSmall) {
+    const int64_t tall = emc2_div_up(capacity_out, kQWaves * 64);
+    blocks = tall > kQSmall / (kQWaves * 32) ? tall : kQSmall / (kQWaves * 32);
+  }
 #define LAUNCH(BUF)                                                                                                           \
-  hipLaunchKernelGGL((k_spconv_i8<CIN, COUT, OUTQ, F8, BUF>), dim3((unsigned)(emc2_div_up(capacity_out, rows_per_block) + 8)), \
+  hipLaunchKernelGGL((k_spconv_i8<CIN, COUT, OUTQ, F8, BUF>), dim3((unsigned)(blocks + 8)),            \
                      dim3(kQThreads), 0, s, (const int8_t*)d_in, (const u32x4*)d_wp, d_mul, d_add, relu, inv_out_scale, d_nbr, \
                      d_n_out, capacity_out, n_in, dev_flags, (const int8_t*)d_zero_row, d_out)
   // Offsets into the input are 32-bit, and the absent neighbour's, 2^32 less a row, must lie at or beyond its end.

@@ -298,12 +298,26 @@ def test_narrow_conv_row_counts(n, rows_in, cin, dt):
 @pytest.mark.parametrize("cin,cout", [(64, 64), (128, 32)])
 @pytest.mark.parametrize("n", [1, 15, 16, 17, 31, 32, 33, 127, 128, 129, 1025])
 def test_quantised_conv_row_counts(n, cin, cout, e4m3):
-    """Row counts at the edges of a tile (16), a wave (32) and a block (128).  Small whole numbers, so both forms are exact."""
+    """Row counts at the edges of a tile (16), a wave (32) and a block (128)."""
+    _check_quantised(n, n + 5, cin, cout, e4m3)
+
+
+# Levels of up to 98 304 rows run 32 rows a wave, larger ones (but 128 channels and 64 -> 64 in E4M3) 64; the grid holds the
+# tiles of either, whatever the capacity: at the line, one beyond, and few rows of a capacity on either side of it
+@pytest.mark.parametrize("e4m3", [False, True])
+@pytest.mark.parametrize("cin,cout", [(64, 32), (64, 64), (128, 32), (128, 64)])
+@pytest.mark.parametrize("n,cap", [(98304, 98304), (98304, 98305), (98305, 98305), (98304 + 255, 200000), (300, 200000), (98200, 400000)])
+def test_quantised_conv_rows_a_wave(n, cap, cin, cout, e4m3):
+    _check_quantised(n, cap, cin, cout, e4m3)
+
+
+def _check_quantised(n, cap, cin, cout, e4m3):
+    """n rows of `cap`.  Small whole numbers, so both types are exact."""
     n_in = 300
     g = torch.Generator(device="cuda").manual_seed(n + cin)
     xv = torch.randint(-2, 3, (n_in, cin), generator=g, device="cuda")
     wv = torch.randint(-1, 2, (27, cin, cout), generator=g, device="cuda")
-    nbr = torch.randint(-n_in, n_in, (27, n + 5), generator=g, device="cuda").clamp_(min=-1).to(torch.int32)
+    nbr = torch.randint(-n_in, n_in, (27, cap), generator=g, device="cuda").clamp_(min=-1).to(torch.int32)
     exp = torch.zeros((n, cout), device="cuda", dtype=torch.float64)
     for k in range(27):
         j = nbr[k, :n].long()
@@ -319,9 +333,9 @@ def test_quantised_conv_row_counts(n, cin, cout, e4m3):
     wp = torch.empty((27 * cin * cout,), dtype=torch.int8, device="cuda")
     ctx.pack_weights_i8(w.view(torch.int8), wp)
     one, zero = torch.ones(cout, device="cuda"), torch.zeros(cout, device="cuda")
-    y = torch.full((n + 5, cout), 7.0, dtype=torch.float16, device="cuda")
+    y = torch.full((cap, cout), 7.0, dtype=torch.float16, device="cuda")
     call = ctx.spconv_e4m3 if e4m3 else ctx.spconv_i8
-    call(x, wp, cin, cout, one, zero, False, nbr, torch.tensor([n], dtype=torch.int32, device="cuda"), n + 5, y, n_in_rows=n_in)
+    call(x, wp, cin, cout, one, zero, False, nbr, torch.tensor([n], dtype=torch.int32, device="cuda"), cap, y, n_in_rows=n_in)
     ctx.status_sync()
     assert exp.abs().max() <= 2048                               # every sum is a whole number that fp16 holds
     assert torch.equal(y[:n].double(), exp) and bool((y[n:] == 7.0).all())
