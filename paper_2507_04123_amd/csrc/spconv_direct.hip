@@ -29,7 +29,7 @@
 // over 304 k rows 310 / 255 us, stride-2 over 69 k 104 / 93, over 27 k 35.4 / 38.0 (a block a CU: twice the barriers show; a
 // barrier for every two steps, with 64 KB of weights, 36.9 there and 258 over 304 k).
 //
-// SKIP: a block first reads all 27 map entries of its rows, keeps them in LDS, and runs only the (dz, dy) groups in which
+// Leaving out: a block first reads all 27 map entries of its rows, keeps them in LDS, and runs only the (dz, dy) groups in which
 // some row has one.  A stride-2 map leaves 31-41 % of the (group, 128 rows) pairs empty, a transposed one 52-62 % (a line of
 // fine sites has one or two of three dy and dz).  Alone, us before / with it: transposed 64 -> 64 over 223 k rows 59 / 45,
 // 64 -> 32 over 304 k 60 / 48; stride-2 32 -> 64 over 573 k 82 / 71, over 852 k 114 / 90, over 223 k 35 / 34.  Submanifold maps
@@ -90,14 +90,19 @@ __global__ void __launch_bounds__(256) k_pack_weights_direct(const uint16_t* __r
   packed[p] = make_uint4(v[0], v[1], v[2], v[3]);
 }
 
-template <int CIN, int COUT> struct DirectCfg {
+template <int CIN, int COUT, bool BUF> struct DirectCfg {
   // 16-row tiles per wave: fewer rows per wave mean fewer accumulators and operands in flight, so more
   // waves fit a SIMD and cover each other's stalls; more rows per wave reuse a weight fragment read more often
   static constexpr int MT = 2;
-  // waves per SIMD the register allocator must leave room for (the 128-channel shapes keep 64-128 accumulators
-  // and as many operands in flight)
-  static constexpr int MINW = (CIN >= 128 || COUT >= 128) ? 2 : 3;
+  // waves per SIMD the register allocator must leave room for, as many as no form spills at (the 128-channel shapes keep
+  // 64 accumulators and as many operands in flight)
+  static constexpr int MINW = CIN >= 128 || COUT >= 128 ? 2 : (CIN == 64 && COUT == 64) || (COUT == 64 && !BUF) ? 3 : 4;
 };
+
+// Levels of at most so many tiles, a block a CU, walk straight over the 27 taps: there the entries' way to the first operands
+// shows, and a block has no neighbour to hide it.  Straight / leaving out, us: stride-2 32 -> 64 10 k rows 8.4 / 9.4, 30 k 9.1 / 10.1,
+// 64 -> 32 10 k 9.0 / 9.7; transposed 32 -> 64 27 k 9.0 / 9.8, 40 k 11.2 / 10.2, 64 -> 32 40 k 14.0 / 12.1, 64 -> 64 40 k 18.8 / 14.9.
+constexpr int64_t kStraightTiles = 256;
 
 // Rows of the input through a buffer descriptor: 32-bit offsets, and the hardware returns zero for an offset at or beyond
 // the end without fetching anything, so an absent neighbour costs neither an address select nor a cache access.  64-beam
@@ -106,16 +111,16 @@ __device__ __forceinline__ u32x4 buffer_row16(__amdgpu_buffer_rsrc_t rows, uint3
   return __builtin_amdgcn_raw_buffer_load_b128(rows, (int)byte, 0, 0);
 }
 
-template <int DT, int CIN, int COUT, bool LOOP, bool BUF, bool SKIP>
-__global__ void __launch_bounds__(kDThreads, (DirectCfg<CIN, COUT>::MINW))
+template <int DT, int CIN, int COUT, bool LOOP, bool BUF>
+__global__ void __launch_bounds__(kDThreads, (DirectCfg<CIN, COUT, BUF>::MINW))
 k_spconv_direct(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, const float* __restrict__ scale,
                 const float* __restrict__ shift, int epilogue, const int32_t* __restrict__ nbr,
                 const int32_t* __restrict__ d_n_out, int64_t capacity_out, int32_t n_in, int32_t* __restrict__ dev_flags,
-                const uint16_t* __restrict__ zrow, uint16_t* __restrict__ out) {
+                const uint16_t* __restrict__ zrow, int64_t straight_tiles, uint16_t* __restrict__ out) {
   constexpr int KH = CIN > 64 ? CIN / 64 : 1; // shares of the channels, one after the other over the three taps of a group
   constexpr int KS = CIN / 32 / KH;           // k-steps per tap and share
   constexpr int NT = COUT / 16;               // 16-column tiles
-  constexpr int MT = DirectCfg<CIN, COUT>::MT;   // 16-row tiles per wave
+  constexpr int MT = DirectCfg<CIN, COUT, BUF>::MT;   // 16-row tiles per wave
   constexpr int R = 16 * MT;                  // rows per wave
   static_assert(MT == 2, "the lane-swap broadcast below handles two tiles");
   constexpr int W16 = KS * NT * 64;           // 16-byte weight pieces per tap and share
@@ -127,6 +132,7 @@ k_spconv_direct(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, c
   constexpr int NA = MT * KS;                 // A-operand loads per tap and share
   constexpr int OCH = COUT / 8;               // 16-byte pieces per output row
   constexpr int OPITCH = (OCH + 1) * 8;       // epilogue tile row pitch in 16-bit units
+  constexpr bool SKIP = COUT <= 64;           // can leave groups out
   // per wave: a 16-row tile of the epilogue and, before it, its rows' map entries
   constexpr int OWN16 = SKIP && 27 * R / 4 > 16 * (OCH + 1) ? 27 * R / 4 : 16 * (OCH + 1);
   __shared__ u32x4 wl[2][W16];
@@ -219,7 +225,8 @@ k_spconv_direct(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, c
       _Pragma("unroll") for (int j = 0; j < NT; ++j)                                                     \
           acc[mt][j] = MmaD<DT>::run(areg[SET][mt * KS + ks], b[j], acc[mt][j]);                         \
   }
-  if constexpr (SKIP) {
+  const bool skip = SKIP && n_tiles > straight_tiles;     // the same for all blocks
+  if (skip) {
     // The entries as rows the kernel may read (absent and beyond the input: -1), [tap][row], and the groups to run.
     int32_t* ent = reinterpret_cast<int32_t*>(otile_s[wave]);
     constexpr int TPI = 64 / R, NL = (27 + TPI - 1) / TPI;     // taps of one load; loads
@@ -279,7 +286,8 @@ k_spconv_direct(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, c
       }
     }
 #undef EMC2_ENTRIES
-  } else {
+  }
+  if (!skip) {
   // prologue: map entries of groups 0..2; weights of tap 0 to LDS; A operands of taps 0..2
   EMC2_IDX_LOAD(0, 0)
   EMC2_IDX_LOAD(1, 1)
@@ -378,35 +386,26 @@ template <int DT, int CIN, int COUT>
 void launch_direct(const void* d_in, const void* d_wp, const float* d_scale, const float* d_shift, int epilogue,
                    const int32_t* d_nbr, const int32_t* d_n_out, int64_t capacity_out, int32_t n_in, int32_t* dev_flags,
                    const void* d_zero_row, bool skip, void* d_out, hipStream_t s) {
-  const int64_t rows_per_block = kDWaves * 16 * DirectCfg<CIN, COUT>::MT;
+  const int64_t rows_per_block = kDWaves * 16 * DirectCfg<CIN, COUT, true>::MT;
   // The host knows a level's capacity, up to 8 times the level below, not how many voxels it got.  Blocks without a tile
   // cost about 0.25 us per thousand: 32 -> 64 over 573 k rows took 97 us in a grid for 11.3 M rows (88 k blocks) and 75 us
   // in one for 573 k.  A loop over tiles costs the kernel up to a tenth in registers and instruction order (128 -> 128: 110
   // against 127 us), so it is used only where the grid would be several times kDGrid; the grid is then kDGrid blocks
   // (32 -> 64 over 573 k rows 97 -> 80 us, over 852 k 119 -> 109).
   const int64_t blocks = emc2_div_up(emc2_div_up(capacity_out, rows_per_block), 8) * 8;
-#define LAUNCH(LOOP, BUF, SKIP, BLOCKS)                                                                                           \
-  hipLaunchKernelGGL((k_spconv_direct<DT, CIN, COUT, LOOP, BUF, SKIP>), dim3((unsigned)(BLOCKS)), dim3(kDThreads), 0, s,           \
+#define LAUNCH(LOOP, BUF, BLOCKS)                                                                                           \
+  hipLaunchKernelGGL((k_spconv_direct<DT, CIN, COUT, LOOP, BUF>), dim3((unsigned)(BLOCKS)), dim3(kDThreads), 0, s,           \
                      (const uint16_t*)d_in, (const u32x4*)d_wp, d_scale, d_shift, epilogue, d_nbr, d_n_out, capacity_out,     \
-                     n_in, dev_flags, (const uint16_t*)d_zero_row, (uint16_t*)d_out)
+                     n_in, dev_flags, (const uint16_t*)d_zero_row, skip ? kStraightTiles : INT64_MAX, (uint16_t*)d_out)
   // Offsets into the input are 32-bit, and the absent neighbour's, 2^32 less a row, must lie at or beyond its end.
   const bool buf = ((int64_t)n_in + 1) * CIN * 2 <= ((int64_t)1 << 32);
-#define LAUNCH_FORM(SKIP)                           \
-  if (blocks <= 4 * kDGrid) {                       \
-    if (buf) LAUNCH(false, true, SKIP, blocks);     \
-    else LAUNCH(false, false, SKIP, blocks);        \
-  } else {                                          \
-    if (buf) LAUNCH(true, true, SKIP, kDGrid);      \
-    else LAUNCH(true, false, SKIP, kDGrid);         \
+  if (blocks <= 4 * kDGrid) {
+    if (buf) LAUNCH(false, true, blocks);
+    else LAUNCH(false, false, blocks);
+  } else {
+    if (buf) LAUNCH(true, true, kDGrid);
+    else LAUNCH(true, false, kDGrid);
   }
-  if constexpr (COUT <= 64) {
-    if (skip) {
-      LAUNCH_FORM(true)
-      return;
-    }
-  }
-  LAUNCH_FORM(false)
-#undef LAUNCH_FORM
 #undef LAUNCH
 }
 

@@ -204,6 +204,40 @@ def test_direct_conv_groups_without_entries(cin, cout, n):
     ctx.close()
 
 
+# Levels of up to 256 blocks walk straight over the taps, larger ones leave out the groups no row of a block has, submanifold
+# ones never: the same bits on both sides of the line
+@pytest.mark.parametrize("cin,cout", [(32, 64), (64, 32), (64, 64)])
+@pytest.mark.parametrize("n", [256 * 128, 256 * 128 + 1])
+def test_direct_conv_straight_and_leaving_out(cin, cout, n):
+    g = torch.Generator(device="cuda").manual_seed(cin + cout)
+    n_in = 5000
+    x = torch.randn((n_in, cin), generator=g, device="cuda").half()
+    w = (torch.randn((27, cin, cout), generator=g, device="cuda") * 0.1).half()
+    nbr = torch.randint(0, n_in, (27, n), generator=g, device="cuda")
+    block = torch.arange(n, device="cuda") // 128
+    keep = (torch.arange(27, device="cuda")[:, None] // 3 + block[None, :]) % 4 == 0          # two or three groups of a block
+    keep &= torch.rand((27, n), generator=g, device="cuda") < 0.7
+    nbr = torch.where(keep, nbr, torch.full_like(nbr, -1)).to(torch.int32).contiguous()
+    ctx = B.Context(16, 16, 64, n_slots=1)
+    wp = torch.empty_like(w)
+    ctx.pack_weights(F16, w, wp)
+    got = []
+    for hint in (B.MAP_ANY, B.SUBM):
+        y = torch.empty((n, cout), dtype=torch.float16, device="cuda")
+        ctx.spconv(F16, x, wp, None, None, EPI_NONE, nbr, torch.tensor([n], dtype=torch.int32, device="cuda"), n, y,
+                   w_layout=B.W_PACKED, map_hint=hint)
+        ctx.status_sync()
+        got.append(y)
+    exp = torch.zeros((n, cout), device="cuda")
+    for k in range(27):
+        rows = (nbr[k] >= 0).nonzero().squeeze(1)
+        exp[rows] += x[nbr[k][rows].long()].float() @ w[k].float()
+    rms = float(exp.square().mean().sqrt())
+    assert float(((got[0].float() - exp).abs() - 2.0 ** -10 * (exp.abs() + rms)).max()) <= 0.0     # as in _check_conv
+    assert torch.equal(got[0], got[1])
+    ctx.close()
+
+
 # inputs of less than 4 GiB are read through a buffer descriptor, larger ones by address; any negative entry is absent
 @pytest.mark.parametrize("cin,cout,n_in", [(64, 32, 1 << 10), (64, 64, (1 << 25) - 1), (64, 64, 1 << 25), (32, 32, (1 << 25) + 3),
                                            (128, 128, (1 << 24) - 1)])
