@@ -106,8 +106,9 @@ k_spconv_narrow(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, c
         e[i] = *reinterpret_cast<const int32_t*>(reinterpret_cast<const char*>(nbr + ((int64_t)(2 * i) * capacity_out + row0)) +
                                                  (i < 13 ? off : even));
     } else {
+      const int32_t* at_row = nbr + row0 + own;
 #pragma unroll
-      for (int i = 0; i < 14; ++i) e[i] = nbr[(int64_t)(2 * i + h < 27 ? 2 * i + h : 26) * capacity_out + row0 + own];
+      for (int i = 0; i < 14; ++i) e[i] = (at_row + (int64_t)(2 * i) * capacity_out)[i < 13 && h ? capacity_out : 0];
     }
   };
   entries(slot);
