@@ -368,7 +368,7 @@ extern "C" emc2_status emc2_pack_weights(emc2_ctx* ctx, emc2_dtype dtype, const 
                      cout);
   // the fragment order is a function of (Cin, Cout) alone: whichever kernel a call later selects for this
   // shape reads the same packed weights
-  if (emc2_spconv_direct_supported(cin, cout))
+  if (emc2_spconv_direct_order(cin, cout))
     emc2_spconv_direct_pack(d_w, cin, cout, d_packed, (hipStream_t)stream);
   else
     emc2_spconv_mfma_pack(d_w, cin, cout, d_packed, (hipStream_t)stream);
@@ -407,18 +407,17 @@ extern "C" emc2_status emc2_spconv(emc2_ctx* ctx, emc2_dtype dtype, const void* 
   hipStream_t s = (hipStream_t)stream;
   int32_t* flags = ctx->dev_words;
   if (mfma) {
-    const bool direct = emc2_spconv_direct_supported(cin, cout);
     const void* wp = d_w;
     if (w_layout == EMC2_W_PLAIN) {
       // stream order protects the shared scratch
-      if (direct) emc2_spconv_direct_pack(d_w, cin, cout, ctx->wpack, s);
+      if (emc2_spconv_direct_order(cin, cout)) emc2_spconv_direct_pack(d_w, cin, cout, ctx->wpack, s);
       else emc2_spconv_mfma_pack(d_w, cin, cout, ctx->wpack, s);
       wp = ctx->wpack;
     }
     if (emc2_spconv_narrow_supported(cin, cout))
       emc2_spconv_narrow_launch(dtype, d_in, wp, d_scale, d_shift, (int)epilogue, d_nbr, d_n_out, capacity_out, n_in, flags,
                                 cin, ctx->zero_row, d_out, s);
-    else if (!direct)
+    else if (!emc2_spconv_direct_supported(cin, cout))
       emc2_spconv_mfma_launch(dtype, d_in, wp, d_scale, d_shift, (int)epilogue, d_nbr, d_n_out, capacity_out, n_in, flags,
                               cin, cout, d_out, s);
     else if (map_hint == EMC2_CONV_SUBM && emc2_spconv_span_supported(cin, cout))

@@ -229,20 +229,20 @@ k_spconv_direct(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, c
   if (skip) {
     // The entries as rows the kernel may read (absent and beyond the input: -1), [tap][row], and the groups to run.
     int32_t* ent = reinterpret_cast<int32_t*>(otile_s[wave]);
-    constexpr int TPI = 64 / R, NL = (27 + TPI - 1) / TPI;     // taps of one load; loads
+    constexpr int NL = 14;                                     // loads, of two taps each (a half of the wave)
     const int sub = lane / R, row = lane % R;
     int32_t e[NL];
 #pragma unroll
-    for (int i = 0; i < NL; ++i) e[i] = nrow[(int64_t)(TPI * i + sub < 27 ? TPI * i + sub : 26) * nbr_pitch];
+    for (int i = 0; i < NL; ++i) e[i] = nrow[(int64_t)(2 * i + sub < 27 ? 2 * i + sub : 26) * nbr_pitch];
     uint32_t groups = 0;
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
       const int32_t j = max(emc2_entry(e[i], dead, n_in, oob), -1);
       const unsigned long long some = __ballot(j >= 0);
 #pragma unroll
-      for (int t = 0; t < TPI; ++t)
-        if (TPI * i + t < 27 && (TPI == 1 ? some : t == 0 ? some & 0xffffffffull : some >> 32) != 0ull) groups |= 1u << ((TPI * i + t) / 3);
-      if (TPI * i + sub < 27) ent[(TPI * i + sub) * R + row] = j;
+      for (int t = 0; t < 2; ++t)
+        if (2 * i + t < 27 && (t == 0 ? some & 0xffffffffull : some >> 32) != 0ull) groups |= 1u << ((2 * i + t) / 3);
+      if (2 * i + sub < 27) ent[(2 * i + sub) * R + row] = j;
     }
     if (lane == 0) groups_s[wave] = groups;
     __syncthreads();
@@ -412,8 +412,10 @@ void launch_direct(const void* d_in, const void* d_wp, const float* d_scale, con
 }  // namespace
 
 bool emc2_spconv_direct_supported(int cin, int cout) {
-  return ((cin == 32 || cin == 64) && (cout == 32 || cout == 64)) || (cin == 128 && cout == 128) || (cin == 64 && cout == 128);
+  return (cin == 32 && cout == 64) || (cin == 64 && (cout == 32 || cout == 64 || cout == 128)) || (cin == 128 && cout == 128);
 }
+
+bool emc2_spconv_direct_order(int cin, int cout) { return emc2_spconv_direct_supported(cin, cout) || (cin == 32 && cout == 32); }
 
 void emc2_spconv_direct_pack(const void* d_w, int cin, int cout, void* d_packed, hipStream_t stream) {
   const int total = 27 * (cin / 32) * (cout / 16) * 64;

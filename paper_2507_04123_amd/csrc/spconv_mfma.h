@@ -36,10 +36,12 @@ void emc2_spconv_narrow_launch(emc2_dtype dtype, const void* d_in, const void* d
                                int32_t* dev_flags, int cin, const void* d_zero_row, void* d_out, hipStream_t stream);
 
 // Register-direct variant (A operands straight from global memory, 16x16x32 MFMA; LDS holds weights only).
-// Its packed weight layout differs from the other kernels': shapes it supports are packed by
-// emc2_spconv_direct_pack.  d_zero_row: >= 256 zero bytes in device memory.  skip: leave out the groups
-// of taps that no row of a block has (pays where the map is not a submanifold one; results differ in nothing).
+// Its packed weight layout, emc2_spconv_direct_pack's, differs from the staged kernel's; emc2_spconv_direct_order: the shapes
+// packed so, those of this kernel and of the span kernel and 32 -> 32.  d_zero_row: >= 256 zero bytes in device memory.  skip:
+// larger levels leave out the groups of taps that no row of a block has (pays where the map is not a submanifold one; the
+// results are the same for finite weights).
 bool emc2_spconv_direct_supported(int cin, int cout);
+bool emc2_spconv_direct_order(int cin, int cout);
 void emc2_spconv_direct_pack(const void* d_w, int cin, int cout, void* d_packed, hipStream_t stream);
 void emc2_spconv_direct_launch(emc2_dtype dtype, const void* d_in, const void* d_wp, const float* d_scale,
                                const float* d_shift, int epilogue, const int32_t* d_nbr, const int32_t* d_n_out,
