@@ -1,6 +1,9 @@
-"""GPU tests at the sizes where a launch changes shape: rounds of the span convolution, the grid limit of the register-direct
-one, vector tails of the quantisers, waves and shared cells of the voxelizer, the three-launch index scan, more pieces of
+"""GPU tests at the sizes where a launch changes shape: tiles and passes of the span convolution, the grid limit and the two
+walks of the register-direct one, rows a wave of the quantised one, vector tails of the quantisers, waves and shared cells of the voxelizer, the three-launch index scan, more pieces of
 rows than one step of a copy's threads."""
+import os
+import re
+
 import numpy as np
 import pytest
 import torch
@@ -126,13 +129,81 @@ def _stretched(n, stretch):
     return nbr.to(torch.int32).contiguous(), int(n * stretch) + 40
 
 
+def _span_forms(nbr, n, cap, ch):
+    """Forms (1, 2 or 3: passes) in which the span kernel runs the groups of this map, and the tile height it takes: its rule
+    over the constants in its source."""
+    src = open(os.path.join(os.path.dirname(B.__file__), "csrc", "spconv_span.hip")).read()
+    cfg = re.search(r"struct SpanCfg<%d, %d> \{.*?\n\};" % (ch, ch), src, re.S).group(0)
+    tr, mt0, mts = (int(v) for v in re.search(r"TR = (\d+), MT0 = (\d+), MTS = (\d+);", cfg).groups())
+    first, nxt = ([int(v) for v in re.search(name + r"\[MTS\] = \{([^}]*)\}", cfg).group(1).split(",")] for name in ("kFirst", "kNext"))
+    step = min(-(-(-(-cap // (64 * mt0))) // 8) * 8, 256) // 8
+    cost = [first[i] + (-(-(-(-(-(-n // (64 * (mt0 + i)))) // 8)) // step) - 1) * nxt[i] for i in range(mts)]
+    mt = mt0 + cost.index(min(cost))
+    forms = set()
+    t = nbr[:, :n].cpu().numpy().reshape(9, 3, n)
+    for r0 in range(0, n, 64 * mt):
+        split = r0 + 64 * ((mt + 1) // 2)
+        for g in t[:, :, r0:r0 + 64 * mt]:
+            lengths = []
+            for part in (g, g[:, :split - r0], g[:, split - r0:]):
+                e = part[part >= 0]
+                lengths.append(int(e.max()) - int(e.min()) + 1 if e.size else 0)
+            if lengths[0]:
+                forms.add(1 if lengths[0] <= tr else 2 if max(lengths[1:]) <= tr else 3)
+    return forms, mt
+
+
+# A group's interval one row below, at and one beyond the row buffer (400 rows at 64 channels, 224 at 128): of a whole tile
+# (one pass, else two), and of a tile's first half where the whole does not fit anyway (two passes, else three).  A tile of
+# 192 rows at 64 channels, of 128 at 128 (16 385 rows and more).
+@pytest.mark.parametrize("ch,rows,n,limit", [(64, 192, 192, 400), (128, 128, 16385, 224)])
+@pytest.mark.parametrize("beyond", [-1, 0, 1])
+@pytest.mark.parametrize("half", [False, True])
+@pytest.mark.parametrize("dtype", [F16, BF16])
+def test_span_conv_row_buffer_limit(ch, rows, n, limit, beyond, half, dtype):
+    td = torch.float16 if dtype == F16 else torch.bfloat16
+    part = 64 * ((rows // 64 + 1) // 2) if half else rows        # the rows that share the interval
+    r = torch.arange(n, device="cuda") % rows
+    at = torch.where(r < part, r * (limit + beyond - 3) // (part - 1), limit + 100 + r - part)
+    at = at + (torch.arange(n, device="cuda") // rows * 640) % 20000
+    nbr = torch.stack([at + k % 3 for k in range(27)])
+    nbr[:, 7::11] = -1                                           # (neither of a tile's ends)
+    nbr = nbr.to(torch.int32).contiguous()
+    forms, mt = _span_forms(nbr, n, n, ch)
+    assert 64 * mt == rows and (3 if half else 2) - (beyond <= 0) in forms
+    n_in = int(nbr.max()) + 1
+    g = torch.Generator(device="cuda").manual_seed(limit + beyond)
+    x = torch.randn((n_in, ch), generator=g, device="cuda").to(td)
+    w = (torch.randn((27, ch, ch), generator=g, device="cuda") * 0.1).to(td)
+    ctx = B.Context(16, 16, 64, n_slots=1)
+    wp = torch.empty_like(w)
+    ctx.pack_weights(dtype, w, wp)
+    got = []
+    for hint in (B.SUBM, B.MAP_ANY):
+        y = torch.empty((n, ch), dtype=td, device="cuda")
+        ctx.spconv(dtype, x, wp, None, None, EPI_NONE, nbr, torch.tensor([n], dtype=torch.int32, device="cuda"), n, y,
+                   w_layout=B.W_PACKED, map_hint=hint)
+        ctx.status_sync()
+        got.append(y)
+    exp = torch.zeros((n, ch), device="cuda")
+    for k in range(27):
+        rs = (nbr[k] >= 0).nonzero().squeeze(1)
+        exp[rs] += x[nbr[k][rs].long()].float() @ w[k].float()
+    rms, tol = float(exp.square().mean().sqrt()), 2.0 ** -10 if dtype == F16 else 2.0 ** -7      # as in _check_conv
+    assert bool(((got[0].float() - exp).abs() <= tol * (exp.abs() + rms)).all())
+    assert torch.equal(got[0].view(torch.int16), got[1].view(torch.int16))
+    ctx.close()
+
+
 # The kernels of the hints add in one order: the same bits, whichever form a group takes (one pass, two halves, three taps)
-@pytest.mark.parametrize("n,stretch", [(1, 1.0), (129, 1.0), (1000, 4.0), (16385, 2.5), (81920, 1.0), (81920, 1.5)])
+@pytest.mark.parametrize("n,stretch,forms", [(2, 1.0, ({1}, {1})), (129, 1.0, ({1}, {1})), (1000, 4.0, ({3}, {3})), (16385, 2.5, ({2}, {2})),
+                                             (81920, 1.0, ({1}, {1})), (81920, 1.5, ({2}, {2}))])
 @pytest.mark.parametrize("dtype", [F16, BF16])
 @pytest.mark.parametrize("ch", [64, 128])
-def test_hint_never_changes_a_bit(n, stretch, dtype, ch):
+def test_hint_never_changes_a_bit(n, stretch, forms, dtype, ch):
     td = torch.float16 if dtype == F16 else torch.bfloat16
     nbr, n_in = _stretched(n, stretch)
+    assert _span_forms(nbr, n, n, ch)[0] >= forms[ch == 128]     # (a ragged last tile's may be another)
     g = torch.Generator(device="cuda").manual_seed(n + ch)
     x = torch.randn((n_in, ch), generator=g, device="cuda").to(td)
     w = (torch.randn((27, ch, ch), generator=g, device="cuda") * 0.1).to(td)
@@ -156,24 +227,44 @@ def test_span_conv_rounds_taps_outside_an_interval(n):
     _check_conv(n, 64, 64, B.SUBM, True)
 
 
-# Blocks of 128 rows (256 at 32 -> 32).  A capacity of up to 4 * 8 192 blocks gets a block for each tile, a row more 8 192
-# blocks that loop over the tiles there are: one tile for all but the last, one more than blocks, a second tile for half of
-# them.  64 -> 32 of 2^25 rows and more reads them by address instead of through a descriptor.
-@pytest.mark.parametrize("cin,cout,rows,n,loop", [(64, 32, 128, 8192 * 128 - 129, True), (32, 64, 128, 8192 * 128 + 1, True),
-                                                  (32, 64, 128, 8192 * 128 * 3 // 2 + 77, True), (64, 32, 128, 8192 * 128 * 3 // 2 + 77, True),
-                                                  (32, 64, 128, 8192 * 128 * 3 // 2 + 77, False), (32, 32, 256, 8192 * 256 + 300, True),
-                                                  (32, 32, 256, 1, True)])
-def test_direct_conv_grid_limit(cin, cout, rows, n, loop):
+# Blocks of 128 rows.  A capacity of up to 4 * 8 192 blocks gets a block for each tile, a row more 8 192 blocks that loop over
+# the tiles there are: one tile for all but the last, one more than blocks, a second tile for half of them.  64 channels of
+# 2^25 rows and more (128 of 2^24) are read by address instead of through a descriptor.  Levels of this size leave groups out
+# but for submanifold maps and 128 output channels, which walk straight over the taps.
+@pytest.mark.parametrize("cin,cout,rows,n,loop,hint", [
+    (64, 32, 128, 8192 * 128 - 129, True, B.MAP_ANY), (32, 64, 128, 8192 * 128 + 1, True, B.MAP_ANY),
+    (32, 64, 128, 8192 * 128 * 3 // 2 + 77, True, B.MAP_ANY), (64, 32, 128, 8192 * 128 * 3 // 2 + 77, True, B.MAP_ANY),
+    (32, 64, 128, 8192 * 128 * 3 // 2 + 77, False, B.MAP_ANY), (64, 32, 128, 8192 * 128 * 3 // 2 + 77, True, B.SUBM),
+    (32, 64, 128, 8192 * 128 + 1, True, B.SUBM), (64, 32, 128, 300, True, B.SUBM),
+    (64, 64, 128, 8192 * 128 + 77, True, B.STRIDED), (64, 128, 128, 8192 * 128 + 77, True, B.STRIDED),
+    (128, 128, 128, 8192 * 128 + 77, True, B.MAP_ANY)])
+def test_direct_conv_grid_limit(cin, cout, rows, n, loop, hint):
+    assert _kernel(cin, cout, hint) == "k_spconv_direct"
     cap = 4 * 8192 * rows + (1 if loop else 0)
-    _check_conv(n, cin, cout, B.MAP_ANY, False, cap=cap)
-    if cin == 64 and loop:
-        _check_conv(n, cin, cout, B.MAP_ANY, False, cap=cap, rows_in=(1 << 25) + 3)
+    _check_conv(n, cin, cout, hint, False, cap=cap)
+    if cin >= 64 and loop:
+        _check_conv(n, cin, cout, hint, False, cap=cap, rows_in=(1 << 25) + 3)
 
 
-# Blocks of 128 rows that have entries in no group, in one, in every one, and whose waves differ; the last block ragged.
+# 32 -> 32 in a capacity of many times its grid, which loops over the tiles of 32 rows a wave there are
+@pytest.mark.parametrize("n", [1, 8192 * 256 + 300])
+def test_narrow_conv_grid_limit(n):
+    assert _kernel(32, 32, B.MAP_ANY) == "k_spconv_narrow"
+    _check_conv(n, 32, 32, B.MAP_ANY, False, cap=4 * 8192 * 256 + 1)
+
+
+def _kernel(cin, cout, hint):
+    ctx = B.Context(16, 16, 64, n_slots=1)
+    name = ctx.spconv_kernel(F16, cin, cout, hint)
+    ctx.close()
+    return name
+
+
+# Blocks of 128 rows that have entries in no group, in one, in every one, and whose waves differ; the last block ragged.  Up to
+# 256 blocks walk straight over the taps, more of them leave groups out, in a loop over the tiles where the capacity is large.
 @pytest.mark.parametrize("cin,cout", [(32, 64), (64, 32), (64, 64)])
-@pytest.mark.parametrize("n", [1, 128, 129, 1000])
-def test_direct_conv_groups_without_entries(cin, cout, n):
+@pytest.mark.parametrize("n,cap", [(1, 1), (128, 128), (129, 129), (1000, 1000), (33000, 33000), (40001, 40001), (8192 * 128 + 300, 4 * 8192 * 128 + 1)])
+def test_direct_conv_groups_without_entries(cin, cout, n, cap):
     g = torch.Generator(device="cuda").manual_seed(cin + cout + n)
     n_in = 500
     x = torch.randn((n_in, cin), generator=g, device="cuda").half()
@@ -182,7 +273,9 @@ def test_direct_conv_groups_without_entries(cin, cout, n):
     group, block, wave = torch.arange(27, device="cuda") // 3, torch.arange(n, device="cuda") // 128, torch.arange(n, device="cuda") // 32
     keep = (block % 4 == 1)[None, :] & (group[:, None] == block[None, :] % 9) | (block % 4 == 2)[None, :] | \
         (block % 4 == 3)[None, :] & (group[:, None] == wave[None, :] % 9)      # blocks 0, 4, ..: nothing
-    nbr = torch.where(keep & (torch.rand((27, n), generator=g, device="cuda") < 0.7), nbr, torch.full_like(nbr, -1)).to(torch.int32).contiguous()
+    nbr = torch.where(keep & (torch.rand((27, n), generator=g, device="cuda") < 0.7), nbr, torch.full_like(nbr, -1)).to(torch.int32)
+    table = torch.zeros((27, cap), dtype=torch.int32, device="cuda")
+    table[:, :n] = nbr
     exp = torch.zeros((n, cout), device="cuda")
     for k in range(27):
         rows = (nbr[k] >= 0).nonzero().squeeze(1)
@@ -193,8 +286,8 @@ def test_direct_conv_groups_without_entries(cin, cout, n):
     ctx.pack_weights(F16, w, wp)
     got = []
     for hint in (B.MAP_ANY, B.STRIDED, B.SUBM):
-        y = torch.full((n + 2, cout), 77.0, dtype=torch.float16, device="cuda")
-        ctx.spconv(F16, x, wp, None, None, EPI_NONE, nbr, torch.tensor([n], dtype=torch.int32, device="cuda"), n, y[:n],
+        y = torch.full((cap + 2, cout), 77.0, dtype=torch.float16, device="cuda")
+        ctx.spconv(F16, x, wp, None, None, EPI_NONE, table, torch.tensor([n], dtype=torch.int32, device="cuda"), cap, y[:cap],
                    w_layout=B.W_PACKED, map_hint=hint)
         ctx.status_sync()
         assert float(((y[:n].float() - exp).abs() - 2.0 ** -10 * (exp.abs() + rms)).max()) <= 0.0     # as in _check_conv

@@ -328,11 +328,11 @@ def test_spconv_subm_and_strided_small(dtype, cin, cout, grid, n, epi):
 
 @pytest.mark.parametrize("dtype", [F16, BF16])
 def test_spconv_arbitrary_table_under_every_hint(dtype):
-    """A table with no structure at all (random rows, random gaps, not ascending) and one whose groups span
-    just under / just over the row interval a submanifold-tuned kernel can hold: same results under any hint."""
+    """A table with no structure at all (random rows, random gaps, not ascending) and ones whose groups span row intervals of
+    all lengths, those just under and over what the submanifold-tuned kernel holds among them: same results under any hint."""
     ctx = B.Context(16, 16, 64, n_slots=1)
     cin = cout = 64
-    n_in, n_out = 2000, 1357                                     # several 512-row blocks and a ragged tail
+    n_in, n_out = 2000, 1357                                     # several tiles and a ragged tail
     st = gen.Stream(4242 + dtype, 9)
     x = gen.round_to_dtype(st.normal(n_in * cin).astype(np.float32).reshape(-1, cin), dtype)
     w = gen.round_to_dtype(st.normal(27 * cin * cout, 0.1).astype(np.float32).reshape(27, cin, cout), dtype)
@@ -341,9 +341,9 @@ def test_spconv_arbitrary_table_under_every_hint(dtype):
     rnd = (st.bits(27 * n_out) % np.uint64(n_in)).astype(np.int32).reshape(27, n_out)
     keep = st.uniform(27 * n_out, 0.0, 1.0).reshape(27, n_out) < 0.4
     random_table = np.where(keep, rnd, -1).astype(np.int32)
-    # ascending tables whose 64-row groups span `width` input rows: row r reads r*width/64 + kx
+    # ascending tables whose 64-row groups span `width` input rows, a tile of 192 128 more: row r reads r*width/64 + kx
     tables = {"random": random_table}
-    for width in (60, 78, 79, 80, 81, 96, 200):
+    for width in (60, 78, 79, 80, 81, 96, 200, 271, 272, 273):
         t = -np.ones((27, n_out), np.int32)
         r = np.arange(n_out)
         base = (r // 64) * 64 + ((r % 64) * (width - 3)) // 63
@@ -351,8 +351,8 @@ def test_spconv_arbitrary_table_under_every_hint(dtype):
             t[k] = np.minimum(base + (k % 3), n_in - 1)
         t[:, ::7] = -1
         tables[f"span{width}"] = t
-    # entries shuffled inside short windows: every 64-row group names rows of one interval narrower than the tile
-    # a span-gather kernel holds, but neither ascending nor bounded by the group's first and last valid lanes
+    # entries shuffled inside short windows: every 64-row group names rows of one short interval, but neither ascending nor
+    # bounded by the group's first and last valid lanes
     for width in (20, 64, 79):
         t = -np.ones((27, n_out), np.int32)
         for k in range(27):
