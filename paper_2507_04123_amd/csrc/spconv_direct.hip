@@ -99,10 +99,11 @@ template <int CIN, int COUT, bool BUF> struct DirectCfg {
   static constexpr int MINW = CIN >= 128 || COUT >= 128 ? 2 : (CIN == 64 && COUT == 64) || (COUT == 64 && !BUF) ? 3 : 4;
 };
 
-// Levels of at most so many tiles, a block a CU, walk straight over the 27 taps: there the entries' way to the first operands
-// shows, and a block has no neighbour to hide it.  Straight / leaving out, us: stride-2 32 -> 64 10 k rows 8.4 / 9.4, 30 k 9.1 / 10.1,
-// 64 -> 32 10 k 9.0 / 9.7; transposed 32 -> 64 27 k 9.0 / 9.8, 40 k 11.2 / 10.2, 64 -> 32 40 k 14.0 / 12.1, 64 -> 64 40 k 18.8 / 14.9.
-constexpr int64_t kStraightTiles = 256;
+// Levels of at most so many tiles, a block a CU (two where a tap is short), walk straight over the 27 taps: there the entries' way
+// to the first operands shows, with few neighbours to hide it.  Straight / leaving out, us: 64 -> 32 10 k 9.0 / 9.7, transposed
+// 40 k 14.0 / 12.1, 64 -> 64 40 k 18.8 / 14.9; 32 -> 64 stride-2 10 k 8.4 / 9.4, 30 k 9.1 / 10.1, 44 k 10.5 / 11.2, 55 k 11.1 / 11.8,
+// 62 k 12.6 / 13.4, 73 k 13.9 / 13.5, transposed 44 k 10.5 / 10.1, 55 k 10.9 / 11.1, 61 k 11.5 / 11.2, 73 k 14.0 / 11.8.
+template <int CIN> constexpr int64_t kStraightTiles = CIN == 32 ? 512 : 256;
 
 // Rows of the input through a buffer descriptor: 32-bit offsets, and the hardware returns zero for an offset at or beyond
 // the end without fetching anything, so an absent neighbour costs neither an address select nor a cache access.  64-beam
@@ -396,7 +397,7 @@ void launch_direct(const void* d_in, const void* d_wp, const float* d_scale, con
 #define LAUNCH(LOOP, BUF, BLOCKS)                                                                                           \
   hipLaunchKernelGGL((k_spconv_direct<DT, CIN, COUT, LOOP, BUF>), dim3((unsigned)(BLOCKS)), dim3(kDThreads), 0, s,           \
                      (const uint16_t*)d_in, (const u32x4*)d_wp, d_scale, d_shift, epilogue, d_nbr, d_n_out, capacity_out,     \
-                     n_in, dev_flags, (const uint16_t*)d_zero_row, skip ? kStraightTiles : INT64_MAX, (uint16_t*)d_out)
+                     n_in, dev_flags, (const uint16_t*)d_zero_row, skip ? kStraightTiles<CIN> : INT64_MAX, (uint16_t*)d_out)
   // Offsets into the input are 32-bit, and the absent neighbour's, 2^32 less a row, must lie at or beyond its end.
   const bool buf = ((int64_t)n_in + 1) * CIN * 2 <= ((int64_t)1 << 32);
   if (blocks <= 4 * kDGrid) {

@@ -261,9 +261,10 @@ def _kernel(cin, cout, hint):
 
 
 # Blocks of 128 rows that have entries in no group, in one, in every one, and whose waves differ; the last block ragged.  Up to
-# 256 blocks walk straight over the taps, more of them leave groups out, in a loop over the tiles where the capacity is large.
+# 256 blocks (512 at 32 -> 64) walk straight over the taps, more of them leave groups out, in a loop over the tiles where the
+# capacity is large.
 @pytest.mark.parametrize("cin,cout", [(32, 64), (64, 32), (64, 64)])
-@pytest.mark.parametrize("n,cap", [(1, 1), (128, 128), (129, 129), (1000, 1000), (33000, 33000), (40001, 40001), (8192 * 128 + 300, 4 * 8192 * 128 + 1)])
+@pytest.mark.parametrize("n,cap", [(1, 1), (128, 128), (129, 129), (1000, 1000), (33000, 33000), (66000, 66000), (8192 * 128 + 300, 4 * 8192 * 128 + 1)])
 def test_direct_conv_groups_without_entries(cin, cout, n, cap):
     g = torch.Generator(device="cuda").manual_seed(cin + cout + n)
     n_in = 500
@@ -297,11 +298,12 @@ def test_direct_conv_groups_without_entries(cin, cout, n, cap):
     ctx.close()
 
 
-# Levels of up to 256 blocks walk straight over the taps, larger ones leave out the groups no row of a block has, submanifold
-# ones never: the same bits on both sides of the line
-@pytest.mark.parametrize("cin,cout", [(32, 64), (64, 32), (64, 64)])
-@pytest.mark.parametrize("n", [256 * 128, 256 * 128 + 1])
-def test_direct_conv_straight_and_leaving_out(cin, cout, n):
+# Levels of up to 256 blocks (512 at 32 -> 64) walk straight over the taps, larger ones leave out the groups no row of a block
+# has, submanifold ones never: the same bits on both sides of the line
+@pytest.mark.parametrize("cin,cout,line", [(32, 64, 512 * 128), (64, 32, 256 * 128), (64, 64, 256 * 128)])
+@pytest.mark.parametrize("beyond", [0, 1])
+def test_direct_conv_straight_and_leaving_out(cin, cout, line, beyond):
+    n = line + beyond
     g = torch.Generator(device="cuda").manual_seed(cin + cout)
     n_in = 5000
     x = torch.randn((n_in, cin), generator=g, device="cuda").half()
