@@ -249,7 +249,8 @@ emc2_status emc2_pack_weights(emc2_ctx* ctx, emc2_dtype dtype, const void* d_w, 
  * are not written.
  *   map_hint: EMC2_CONV_SUBM / EMC2_CONV_STRIDED if d_nbr came from emc2_build_kmap with that kind, else
  *   EMC2_MAP_ANY.  A scheduling hint only (submanifold maps over key-sorted voxels let the three kx
- *   taps of a (dz, dy) pair share one fetch of input rows): results do not depend on it, for any table.
+ *   taps of a (dz, dy) pair share one fetch of input rows): results do not depend on it, for any table and finite weights (an
+ *   absent neighbour counts as a row of zeros or is left out, which differs only where a weight is infinite or NaN).
  */
 #define EMC2_MAP_ANY (-1)
 /*

@@ -29,8 +29,8 @@
 // the row buffer is split into two passes of half of the tile's rows if each half's interval fits (next to a denser plane
 // the interval is up to twice the rows), else into three passes, one per tap, that gather exactly the rows the tap names.
 // Rows and taps that are not a pass's own read the zeroed row, so that there is one form of the matrix code (branches
-// around it make the compiler keep two copies of the accumulators).  Results never depend on which: an output row adds its
-// taps in ascending order in all three forms.
+// around it make the compiler keep two copies of the accumulators).  With finite weights results never depend on which: an
+// output row adds its taps in ascending order in all three forms, and what reads the zeroed row adds nothing.
 #include <hip/hip_bf16.h>
 #include <hip/hip_fp16.h>
 
