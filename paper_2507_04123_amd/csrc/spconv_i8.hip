@@ -129,18 +129,24 @@ __global__ void __launch_bounds__(256) k_pack_weights_i8(const int8_t* __restric
 // Rows a wave.  A launch is bound by the chain of 27 taps (operand latency, weights through LDS, a barrier each) until enough
 // waves cover each other, then by LDS reads of weights, which feed half the products with 32 rows a wave that they feed with
 // 64.  A level of up to kQSmall rows, three blocks of 32-row waves a CU, runs those: 64 -> 64 with 64 rows / 32 rows, us: int8
-// 8 k rows 12.2 / 8.3, 40 k 13.1 / 11.2, 69 k 20.3 / 17.7, 93 k 18.5 / 16.0; E4M3 8 k 14.5 / 9.8, 69 k 23.1 / 19.4.  Beyond, 64 rows:
-// int8 108 k 19.5 / 20.9, 304 k 46 / 53, 562 k 86 / 99; 64 -> 32 over 304 k int8 39 / 43, E4M3 40 / 44.  The row count is the
-// device's, so a kernel holds both forms; the grid, which the host sizes, has a block for each tile of either.  E4M3 runs
-// two matrix instructions for every operand read, so that 32 rows are the better ones there at every size (64 -> 64 163 k
-// rows 34.1 / 29.4, 223 k 43.6 / 38.0, 304 k 57.8 / 57.7; 128 -> 64 60 / 52, 76 / 69, 112 / 115), 64 -> 32 apart.
-// 16 rows: E4M3 the same for small levels, int8 223 k 10 % slower.
+// 8 k rows 12.2 / 8.3, 40 k 13.1 / 11.2, 69 k 20.3 / 17.7, 93 k 18.5 / 16.0; E4M3 8 k 14.5 / 9.8, 69 k 23.1 / 19.4.  Beyond, 64 rows,
+// but a step of them, a block a CU, takes nearly as long if few of its blocks are there, so that a rest of less than half a
+// step runs 32 rows, behind the whole steps of the same launch.  All 64 rows / all 32 / both, fp16 out, us: int8 64 -> 64 108 k
+// 20.5 / 20.5 / 20.0, 148 k 25.4 / 23.7 / 21.6, 166 k 26.9 / 27.3 / 27.7 (its rest just over half a step, in 32 rows), 223 k 34.5 /
+// 32.4 / 30.4, 266 k 36.1 / 35.5 / 33.3, 304 k 40.7 / 43.8 / 41.1, 596 k 74.7 / 83.3 / 71.9, 2.4 M 314 / 363 / 316; stride-2 223 k 30.9 /
+// 30.4 / 28.2; 128 -> 64 223 k 86 / 81 / 73; 64 -> 32 148 k 20.8 / 19.7 / 17.9, E4M3 21.0 / 21.0 / 19.0.  The row count is the
+// device's, so a kernel holds both forms.  Not so E4M3 but for 64 -> 32: it runs two matrix instructions for every operand read,
+// so that 32 rows are the better ones nearly everywhere (64 -> 64 163 k rows 34.1 / 29.4, 223 k 43.6 / 38.0, 304 k 57.8 / 57.7, but
+// 2.4 M 350 / 373; both in one kernel spill; 128 -> 64 60 / 52, 76 / 69, 112 / 115), and int8 128 -> 32, where 64 rows gain 4 % at some
+// sizes and lose 15 % at others (223 k 78 / 74, 304 k 87 / 87, 471 k 75 / 69).  16 rows: E4M3 the same for small levels, int8 223 k
+// 10 % slower.
 constexpr int64_t kQSmall = 3 * 256 * 128;
+constexpr int64_t kQStep = 256 * 256;    // rows of a block of 64-row waves a CU
 
-// TALL: levels of more than kQSmall rows run 64 rows a wave.  MINW: waves per SIMD the register allocator must leave room for,
-// as many as neither form spills at.
+// TALL: holds the form with 64 rows a wave too.  MINW: waves per SIMD the register allocator must leave room for, as many as
+// neither form spills at.
 template <int CIN, int COUT, int F8, bool BUF> struct QCfg {
-  static constexpr bool TALL = !F8 || (CIN == 64 && COUT == 32);
+  static constexpr bool TALL = F8 ? CIN == 64 && COUT == 32 : !(CIN == 128 && COUT == 32);
   static constexpr int MINW = !TALL ? (CIN == 64 && COUT == 64 && BUF ? 4 : 3)
                                     : CIN == 64 && (COUT == 32 || BUF) ? 3 : 2;
 };
@@ -162,12 +168,13 @@ template <int CIN, int COUT, int OUTQ, int F8> struct QLds {
   u32x4 otile[kQWaves][16 * (OCH + 1)];
 };
 
-// One block's rows, 16 * MT a wave.
+// One block's rows, 16 * MT a wave: tile `slot` of this block's XCD among those of rows [row_begin, n_out).
 template <int CIN, int COUT, int OUTQ, int F8, bool BUF, int MT>
 __device__ __forceinline__ void
-run_i8(QLds<CIN, COUT, OUTQ, F8>& lds, const int8_t* __restrict__ in, const u32x4* __restrict__ wp, const float* __restrict__ mul,
-       const float* __restrict__ add, int relu, float inv_out_scale, const int32_t* __restrict__ nbr, int64_t n_out,
-       int64_t capacity_out, int32_t n_in, int32_t* __restrict__ dev_flags, const int8_t* __restrict__ zrow, void* __restrict__ out) {
+run_i8(int64_t slot, int64_t row_begin, QLds<CIN, COUT, OUTQ, F8>& lds, const int8_t* __restrict__ in, const u32x4* __restrict__ wp,
+       const float* __restrict__ mul, const float* __restrict__ add, int relu, float inv_out_scale, const int32_t* __restrict__ nbr,
+       int64_t n_out, int64_t capacity_out, int32_t n_in, int32_t* __restrict__ dev_flags, const int8_t* __restrict__ zrow,
+       void* __restrict__ out) {
   const __amdgpu_buffer_rsrc_t rows =
       __builtin_amdgcn_make_buffer_rsrc((void*)const_cast<int8_t*>(in), 0, BUF ? (int)((uint32_t)n_in * CIN) : 0, 0x00020000);
   constexpr int KS = CIN / 64;                // k-steps per tap
@@ -184,16 +191,15 @@ run_i8(QLds<CIN, COUT, OUTQ, F8>& lds, const int8_t* __restrict__ in, const u32x
   u32x4 (*wl)[W16] = lds.w;
 
   // XCD-aware tile assignment: workgroup b runs on XCD b % 8; XCD x takes a contiguous range of tiles
-  const int64_t n_tiles = (n_out + kQWaves * R - 1) / (kQWaves * R);
+  const int64_t n_tiles = (n_out - row_begin + kQWaves * R - 1) / (kQWaves * R);
   const int64_t chunk = (n_tiles + 7) / 8;
-  const int64_t slot_in_xcd = blockIdx.x / 8;
-  const int64_t tile_id = (int64_t)(blockIdx.x % 8) * chunk + slot_in_xcd;
-  if (slot_in_xcd >= chunk || tile_id >= n_tiles) return;  // uniform for the block
+  const int64_t tile_id = (int64_t)(blockIdx.x % 8) * chunk + slot;
+  if (slot >= chunk || tile_id >= n_tiles) return;         // uniform for the block
 
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int m = lane & 15, q = lane >> 4;
-  const int64_t wave_row0 = tile_id * (kQWaves * R) + (int64_t)wave * R;
+  const int64_t wave_row0 = row_begin + tile_id * (kQWaves * R) + (int64_t)wave * R;
 
   // lane l holds the kernel-map entries of row l % R of this wave's R rows
   const bool live = wave_row0 + lane % R < n_out;
@@ -365,14 +371,29 @@ k_spconv_i8(const int8_t* __restrict__ in, const u32x4* __restrict__ wp, const f
   __shared__ QLds<CIN, COUT, OUTQ, F8> lds;
   int64_t n_out = *d_n_out;
   if (n_out > capacity_out) n_out = capacity_out;
+  // rows [0, tall) in tiles of 64-row waves, the others in tiles of 32-row waves
   using Cfg = QCfg<CIN, COUT, F8, BUF>;
+  int64_t slot = blockIdx.x / 8, tall = 0;
   if constexpr (Cfg::TALL) {
     if (n_out > kQSmall) {
-      run_i8<CIN, COUT, OUTQ, F8, BUF, 4>(lds, in, wp, mul, add, relu, inv_out_scale, nbr, n_out, capacity_out, n_in, dev_flags, zrow, out);
-      return;
+      tall = n_out - n_out % kQStep;
+      if (n_out - tall >= kQStep / 2) tall = n_out;
     }
   }
-  run_i8<CIN, COUT, OUTQ, F8, BUF, 2>(lds, in, wp, mul, add, relu, inv_out_scale, nbr, n_out, capacity_out, n_in, dev_flags, zrow, out);
+  const int64_t tall_slots = (tall + 8 * kQWaves * 64 - 1) / (8 * kQWaves * 64);
+  // Blocks without a tile, of which a large capacity has many, end before anything else is computed: 40 k rows in a capacity of
+  // 6 M, int8 64 -> 64 13.6 -> 11.0, 64 -> 32 12.7 -> 10.1, 128 -> 64 20.9 -> 18.0.
+  if ((slot - tall_slots) * (8 * kQWaves * 32) >= n_out - tall + 7 * kQWaves * 32) return;
+  if constexpr (Cfg::TALL) {
+    if (slot < tall_slots) {
+      run_i8<CIN, COUT, OUTQ, F8, BUF, 4>(slot, 0, lds, in, wp, mul, add, relu, inv_out_scale,
+                                          nbr, tall, capacity_out, n_in, dev_flags, zrow, out);
+      return;
+    }
+    slot -= tall_slots;
+  }
+  run_i8<CIN, COUT, OUTQ, F8, BUF, 2>(slot, tall, lds, in, wp, mul, add, relu, inv_out_scale,
+                                      nbr, n_out, capacity_out, n_in, dev_flags, zrow, out);
 }
 
 template <int CIN, int COUT, int OUTQ, int F8 = 0>
@@ -381,8 +402,9 @@ void launch_i8(const void* d_in, const void* d_wp, const float* d_mul, const flo
                const void* d_zero_row, void* d_out, hipStream_t s) {
   int64_t blocks = emc2_div_up(capacity_out, kQWaves * 32);
   if (QCfg<CIN, COUT, F8, true>::TALL && capacity_out > kQSmall) {
-    const int64_t tall = emc2_div_up(capacity_out, kQWaves * 64);
-    blocks = tall > kQSmall / (kQWaves * 32) ? tall : kQSmall / (kQWaves * 32);
+    // kQSmall rows in small tiles, or whole steps in large ones and half a step in small ones
+    const int64_t mixed = capacity_out / (kQWaves * 64) + kQStep / 2 / (kQWaves * 32) + 1;
+    blocks = mixed > kQSmall / (kQWaves * 32) ? mixed : kQSmall / (kQWaves * 32);
   }
 #define LAUNCH(BUF)                                                                                                           \
   hipLaunchKernelGGL((k_spconv_i8<CIN, COUT, OUTQ, F8, BUF>), dim3((unsigned)(blocks + 8)),            \

@@ -431,13 +431,23 @@ def test_quantised_conv_row_counts(n, cin, cout, e4m3):
     _check_quantised(n, n + 5, cin, cout, e4m3)
 
 
-# Levels of up to 98 304 rows run 32 rows a wave, larger ones (but 128 channels and 64 -> 64 in E4M3) 64; the grid holds the
-# tiles of either, whatever the capacity: at the line, one beyond, and few rows of a capacity on either side of it
+# Levels of up to 98 304 rows run 32 rows a wave.  Larger ones (E4M3 only 64 -> 32, int8 all but 128 -> 32) run whole steps of 65 536
+# rows with 64 a wave, the rest too if it is half a step, else with 32; the grid holds the tiles, whatever the capacity: both
+# sides of each line, rests of a row, a tile and just under half a step, and few rows of a large capacity.
 @pytest.mark.parametrize("e4m3", [False, True])
 @pytest.mark.parametrize("cin,cout", [(64, 32), (64, 64), (128, 32), (128, 64)])
-@pytest.mark.parametrize("n,cap", [(98304, 98304), (98304, 98305), (98305, 98305), (98304 + 255, 200000), (300, 200000), (98200, 400000)])
+@pytest.mark.parametrize("n,cap", [(98304, 98304), (98304, 98305), (98305, 98305), (131072, 131072), (131073, 131073), (131072 + 129, 300000),
+                                   (300, 200000), (98200, 400000), (163839, 163839), (163840, 200000), (196608, 196609),
+                                   (196608 + 32767, 196608 + 32767), (5 * 65536 + 1025, 5 * 65536 + 1025), (9 * 65536 - 1, 700000)])
 def test_quantised_conv_rows_a_wave(n, cap, cin, cout, e4m3):
     _check_quantised(n, cap, cin, cout, e4m3)
+
+
+# A capacity of many times the rows; and the rows of thousands of blocks
+@pytest.mark.parametrize("cin,cout,e4m3", [(128, 32, False), (64, 64, True), (128, 32, True), (128, 64, True), (64, 64, False)])
+@pytest.mark.parametrize("n", [300, 8192 * 128 + 77])
+def test_quantised_conv_large_capacity(n, cin, cout, e4m3):
+    _check_quantised(n, 4 * 8192 * 128, cin, cout, e4m3)
 
 
 def _check_quantised(n, cap, cin, cout, e4m3):
