@@ -16,14 +16,19 @@
 // pass ahead.  The computing waves hold 16 * MT rows by COUT columns of accumulators each and read nothing but LDS.  A block
 // stays and walks over its tiles, so that a tile's first pass is fetched while the last tile's results are stored.
 // What a pass of 384 rows costs now: 3 000 cycles of computing (144 matrix instructions, 2 304 if back to back), against
-// ~3 500 of feeding it: the loads into LDS (74 KB at about 16 cycles each) share the LDS with the operand reads (240 KB at
-// 8.5), which the two together keep busy for ~3 300.  Tried against it: the 32x32x16 instructions (computing 2 750, feeding
-// the same: no gain), weights straight from global memory into registers (longer: the vector-memory path takes them at the
-// rate of the rows), separate waves for loads and for the map (2 + 2: a wave issues a load into LDS only every ~100 cycles),
-// the map read by the computing waves (spills), an order of tiles that keeps neighbouring planes in one L2 (no gain).
+// ~3 500 of feeding it.  Neither is a unit's rate: the loads into LDS (74 KB) take 16.4 cycles a KB, 1 200, when issued without
+// a stop, the operand reads (240 KB) 4.2, 1 000, and a third more for bank conflicts; side by side the two do not slow each
+// other (measured on kernels of only reads, only loads, both).  What is left of the 3 500 is the wait for a pass's loads, which
+// are one pass ahead, with the analysis of map entries and the offsets in front of them.  (LdsUtil, 28 %, counts 4 cycles a
+// read and no load into LDS.)  Tried against it: the 32x32x16 instructions (computing 2 750, feeding the same: no gain),
+// weights straight from global memory into registers (longer: the vector-memory path takes them at the rate of the rows),
+// separate waves for loads and for the map (2 + 2: longer), the map read by the computing waves (spills), an order of tiles that
+// keeps neighbouring planes in one L2 (no gain).
 // 64 -> 64, us before / now: 70 k rows 33 / 25-28, 223 k 65 / 58, 248 k bf16 71 / 60, 573 k 142 / 107, 852 k 210 / 161.
 // 128 -> 128 (bf16) on the register-direct kernel (whole taps at a time then), / here:
-// 4 k rows 36 / 19, 32 k 39 / 26, 48 k 70 / 39, 67 k 104 / 71.
+// 4 k rows 36 / 19, 32 k 39 / 26, 48 k 70 / 39, 67 k 104 / 71; 29 k rows of a sparse frame 33 / 39: a tile across two planes needs
+// three passes for some groups, up to 30 in all where the others have 12-18, and with a tile a block it sets the time.  (128 -> 128 spills 302 scalar
+// registers into vector lanes, addresses of the 27 taps and of the weights, in the feeding waves.)
 //
 // One pass is what is computed between two barriers.  Normally a group is one pass.  A group whose interval does not fit
 // the row buffer is split into two passes of half of the tile's rows if each half's interval fits (next to a denser plane
