@@ -27,8 +27,8 @@
 // 64 -> 64, us before / now: 70 k rows 33 / 25-28, 223 k 65 / 58, 248 k bf16 71 / 60, 573 k 142 / 107, 852 k 210 / 161.
 // 128 -> 128 (bf16) on the register-direct kernel (whole taps at a time then), / here:
 // 4 k rows 36 / 19, 32 k 39 / 26, 48 k 70 / 39, 67 k 104 / 71; 29 k rows of a sparse frame 33 / 39: a tile across two planes needs
-// three passes for some groups, up to 30 in all where the others have 12-18, and with a tile a block it sets the time.  (128 -> 128 spills 302 scalar
-// registers into vector lanes, addresses of the 27 taps and of the weights, in the feeding waves.)
+// three passes for some groups, up to 30 in all where the others have 12-18, and with a tile a block it sets the time.
+// 128 -> 128 spills 302 scalar registers into vector lanes (64 -> 64 none).
 //
 // One pass is what is computed between two barriers.  Normally a group is one pass.  A group whose interval does not fit
 // the row buffer is split into two passes of half of the tile's rows if each half's interval fits (next to a denser plane
