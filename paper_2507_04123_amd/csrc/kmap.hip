@@ -109,6 +109,8 @@ __global__ void __launch_bounds__(256) k_probe(const int4* __restrict__ out_coor
                                                int32_t* __restrict__ nbr) {
   int64_t n = *d_n_out;
   if (n > capacity_out) n = capacity_out;
+  // (An eighth of the rows for each XCD reads 422 instead of 721 MB of coordinates and index for 7.5 M rows, and takes 5 % longer:
+  // the 27 taps are then written at 216 places at a time.)
   const int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (o < n) emc2_probe_voxel<S>(o, out_coords, capacity_out, in_idx, *d_n_in, gx, gy, gz, n_batch, nbr);
 }
