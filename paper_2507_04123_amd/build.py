@@ -12,7 +12,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libemc2.so")
 PROBE_LIB = os.path.join(HERE, "libemc2probe.so")     # measurement probes of the bench (include/emc2_probe.h)
-SOURCES = ["context.hip", "cellindex.hip", "voxelize.hip", "kmap.hip", "spconv.hip", "spconv_mfma.hip", "spconv_narrow.hip", "spconv_span.hip",
+SOURCES = ["context.hip", "cellindex.hip", "voxelize.hip", "voxel_bins.hip", "kmap.hip", "spconv.hip", "spconv_mfma.hip", "spconv_narrow.hip", "spconv_span.hip",
            "spconv_direct.hip", "project.hip", "decoder.hip", "pool.hip", "dispatch.hip", "spconv_i8.hip",
            "stack.hip"]
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC",

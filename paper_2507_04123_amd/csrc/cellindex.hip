@@ -225,6 +225,12 @@ void emc2_index_mark_coords(emc2_ctx* ctx, cellword_t* idx, const int32_t* d_coo
                      (const int4*)d_coords, d_n, capacity, grid[0], grid[1], grid[2], n_batch, emc2_slot_flags(ctx, idx));
 }
 
+void emc2_scan_totals(emc2_ctx* ctx, const uint32_t* totals, int64_t n, int64_t capacity, uint32_t* bases, int32_t* d_total,
+                      hipStream_t stream) {
+  hipLaunchKernelGGL(k_scan_partials, dim3((unsigned)emc2_div_up(n, 1024)), dim3(1024), 0, stream, totals, n, capacity, bases, d_total,
+                     ctx->dev_words);
+}
+
 void emc2_index_scan(emc2_ctx* ctx, cellword_t* idx, int64_t n_cells, int64_t capacity, int32_t* d_total,
                      hipStream_t stream) {
   const int64_t n_words = emc2_div_up(n_cells, 32);
@@ -242,8 +248,7 @@ void emc2_index_scan(emc2_ctx* ctx, cellword_t* idx, int64_t n_cells, int64_t ca
     return;
   }
   uint32_t* bases = ctx->partials + ctx->n_partials;
-  hipLaunchKernelGGL(k_scan_partials, dim3((unsigned)emc2_div_up(n_blocks, 1024)), dim3(1024), 0, stream, ctx->partials, n_blocks,
-                     capacity, bases, d_total, ctx->dev_words);
+  emc2_scan_totals(ctx, ctx->partials, n_blocks, capacity, bases, d_total, stream);
   hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)n_blocks), dim3(256), 0, stream, idx, n_words, bases,
                      emc2_slot_flags(ctx, idx));
 }

@@ -78,6 +78,8 @@ struct emc2_ctx {
   unsigned long long* first;  // [max_points / 64 + 1] one bit per point: the first of its voxel
   uint32_t* partials;       // scan partial sums [n_partials], then the bases made of them [n_partials]
   int64_t n_partials;
+  uint32_t* bins;           // [7 * n_bins + 4] large clouds by bin of cells (voxel_bins.hip)
+  int64_t n_bins;
   uint32_t* stack_sums;     // popcount sums of every level of a stack (stack.hip)
   int64_t n_stack_sums;
   int32_t* dev_words;       // [0] status flags, [2] voxel count of an index rebuilt from coordinates (others unused)
@@ -99,6 +101,11 @@ struct emc2_ctx {
 #define EMC2_SCAN_SELF_TILES 16384  // scans of up to so many tiles take two launches and no second half of `partials`
 #define EMC2_LINE_SHIFT 4    // log2 of the cellwords per flagged line: 16 words = 128 bytes = 512 cells
 #define EMC2_LINES_PER_TILE (EMC2_SCAN_TILE >> EMC2_LINE_SHIFT)
+
+// Bins of the voxelization of large clouds: 2^14 cells, or a whole scan tile of 2^16 where that makes more than EMC2_BINS_MAX.
+#define EMC2_BIN_SHIFT_FINE 14
+#define EMC2_BIN_SHIFT_TILE (5 + EMC2_TILE_SHIFT)
+#define EMC2_BINS_MAX 131072
 
 // Line flags of an index slot.  The active cells of a LiDAR frame fill a fraction of a percent of the finest
 // grid, and scattered objects touch single cache lines of it, so every index slot carries one flag byte per
@@ -126,6 +133,9 @@ void emc2_index_clear(emc2_ctx* ctx, cellword_t* idx, hipStream_t stream);
 // and raises EMC2_DEVFLAG_CAPACITY when total > capacity
 void emc2_index_scan(emc2_ctx* ctx, cellword_t* idx, int64_t n_cells, int64_t capacity, int32_t* d_total,
                      hipStream_t stream);
+// bases[i] = sum of the n totals before i; the sum of all, clamped and reported like that of the index, to d_total
+void emc2_scan_totals(emc2_ctx* ctx, const uint32_t* totals, int64_t n, int64_t capacity, uint32_t* bases, int32_t* d_total,
+                      hipStream_t stream);
 // set the bits of coords[0..*d_n) (b,z,y,x) in a cleared index
 void emc2_index_mark_coords(emc2_ctx* ctx, cellword_t* idx, const int32_t* d_coords, const int32_t* d_n,
                             int64_t capacity, const int32_t grid[3], int32_t n_batch, hipStream_t stream);

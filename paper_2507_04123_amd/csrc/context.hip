@@ -69,6 +69,10 @@ extern "C" emc2_status emc2_create(emc2_ctx** out, int device, int64_t max_point
   TRY(hipMalloc((void**)&ctx->first, sizeof(unsigned long long) * ((size_t)max_points / 64 + 1)), "hipMalloc(first points)");
   ctx->n_partials = emc2_div_up(ctx->slot_words, EMC2_SCAN_TILE) + 1;
   TRY(hipMalloc((void**)&ctx->partials, sizeof(uint32_t) * 2 * (size_t)ctx->n_partials), "hipMalloc(partials)");
+  // fine bins as long as they are few enough, the slot's tiles beyond (and one more of either)
+  ctx->n_bins = (4 * ctx->slot_tiles < EMC2_BINS_MAX ? 4 * ctx->slot_tiles : EMC2_BINS_MAX) + 1;
+  if (ctx->n_bins < ctx->n_partials) ctx->n_bins = ctx->n_partials;
+  TRY(hipMalloc((void**)&ctx->bins, sizeof(uint32_t) * (7 * (size_t)ctx->n_bins + 4)), "hipMalloc(bins)");
   {
     // level 0 in tiles, up to EMC2_STACK_MAX_LEVELS - 1 further ones in sixteenths of tiles, and one sum of every 64 sums
     const int64_t further = n_slots - 1 < EMC2_STACK_MAX_LEVELS - 1 ? n_slots - 1 : EMC2_STACK_MAX_LEVELS - 1;
@@ -112,6 +116,7 @@ extern "C" void emc2_destroy(emc2_ctx* ctx) {
   if (ctx->stash) (void)hipFree(ctx->stash);
   if (ctx->first) (void)hipFree(ctx->first);
   if (ctx->partials) (void)hipFree(ctx->partials);
+  if (ctx->bins) (void)hipFree(ctx->bins);
   if (ctx->stack_sums) (void)hipFree(ctx->stack_sums);
   if (ctx->zero_row) (void)hipFree(ctx->zero_row);
   if (ctx->wpack) (void)hipFree(ctx->wpack);

@@ -101,22 +101,12 @@ __device__ __forceinline__ void emc2_stash_point(int64_t i, int32_t r, const Poi
   }
 }
 
-// Mean of voxel r from its stash, the number of points after its first (which becomes the count) and what overflowed the
-// stash; lp: 0 none, 1 fp16, 2 bf16 copy.
-__device__ __forceinline__ void emc2_voxel_mean(int64_t r, const float4* __restrict__ stash, int64_t pitch,
-                                                float4* __restrict__ feats, int32_t* __restrict__ counts, int lp,
-                                                void* __restrict__ feats_lp) {
-  const int32_t cnt = counts[r] + 1;
-  counts[r] = cnt;
-  float4 s = feats[r];   // what overflowed the stash (zero for almost every voxel)
-  const int k = cnt < EMC2_VOX_STASH ? cnt : EMC2_VOX_STASH;
-  // The stash holds the points in arrival order, which differs from run to run.  They are summed in the order
-  // of their values (x, then y, z, intensity) instead, so that a voxel of up to EMC2_VOX_STASH points -- nearly
-  // every voxel of a LiDAR frame -- gets the same mean, bit for bit, in every run and for every order of the input.
-  float4 v[EMC2_VOX_STASH];
-#pragma unroll
-  for (int j = 0; j < EMC2_VOX_STASH; ++j)
-    v[j] = j < k ? stash[j * pitch + r] : make_float4(INFINITY, INFINITY, INFINITY, INFINITY);
+// Mean of voxel r: the points v (at most EMC2_VOX_STASH, the rest at infinity), the sum s of its further ones, cnt in all; lp: 0
+// none, 1 fp16, 2 bf16 copy.  The points come in arrival order, which differs from run to run.  They are summed in the order of
+// their values (x, then y, z, intensity) instead, so that a voxel of up to EMC2_VOX_STASH points -- nearly every voxel of a LiDAR
+// frame -- gets the same mean, bit for bit, in every run and for every order of the input.
+__device__ __forceinline__ void emc2_store_mean(int64_t r, float4 (&v)[EMC2_VOX_STASH], float4 s, int32_t cnt, float4* __restrict__ feats,
+                                                int lp, void* __restrict__ feats_lp) {
   auto before = [](const float4& a, const float4& b) {
     if (a.x != b.x) return a.x < b.x;
     if (a.y != b.y) return a.y < b.y;
@@ -130,7 +120,7 @@ __device__ __forceinline__ void emc2_voxel_mean(int64_t r, const float4* __restr
   order(0, 1); order(2, 3); order(0, 2); order(1, 3); order(1, 2);
 #pragma unroll
   for (int j = 0; j < EMC2_VOX_STASH; ++j)
-    if (j < k) { s.x += v[j].x; s.y += v[j].y; s.z += v[j].z; s.w += v[j].w; }
+    if (j < cnt) { s.x += v[j].x; s.y += v[j].y; s.z += v[j].z; s.w += v[j].w; }
   const float c = (float)cnt;
   const float4 m = make_float4(s.x / c, s.y / c, s.z / c, s.w / c);
   feats[r] = m;
@@ -145,7 +135,29 @@ __device__ __forceinline__ void emc2_voxel_mean(int64_t r, const float4* __restr
   }
 }
 
+// Mean of voxel r from its stash, the number of points after its first (which becomes the count) and what overflowed the
+// stash.
+__device__ __forceinline__ void emc2_voxel_mean(int64_t r, const float4* __restrict__ stash, int64_t pitch,
+                                                float4* __restrict__ feats, int32_t* __restrict__ counts, int lp,
+                                                void* __restrict__ feats_lp) {
+  const int32_t cnt = counts[r] + 1;
+  counts[r] = cnt;
+  const float4 s = feats[r];   // what overflowed the stash (zero for almost every voxel)
+  const int k = cnt < EMC2_VOX_STASH ? cnt : EMC2_VOX_STASH;
+  float4 v[EMC2_VOX_STASH];
+#pragma unroll
+  for (int j = 0; j < EMC2_VOX_STASH; ++j)
+    v[j] = j < k ? stash[j * pitch + r] : make_float4(INFINITY, INFINITY, INFINITY, INFINITY);
+  emc2_store_mean(r, v, s, cnt, feats, lp, feats_lp);
+}
+
 // Host side (voxelize.hip): the checks of a voxelization's arguments, and the kernels' view of a grid.
 emc2_status emc2_voxel_args_ok(emc2_ctx* ctx, const emc2_voxel_spec* spec, int64_t n_points, int64_t capacity, int32_t index_slot,
                                const char* who);
 VoxParams emc2_vox_params(const emc2_voxel_spec* spec);
+
+// Voxelization of large clouds by bin of cells (voxel_bins.hip): whether a call takes it, and its launches.
+bool emc2_bins_pay(int64_t n_points, int64_t n_cells);
+void emc2_voxelize_bins(emc2_ctx* ctx, const float* d_points, const int32_t* d_batch, int64_t n_points, const VoxParams& prm,
+                        int64_t n_cells, cellword_t* idx, int64_t capacity, int32_t* d_coords, float* d_feats, int32_t* d_counts,
+                        void* d_feats_lp, int lp, int32_t* d_n_voxels, hipStream_t s);

@@ -2,6 +2,7 @@
 // Sec. 3.5 configurable pool size; Sec. 3.6 (3) prefix-sum index search).
 //
 // The voxel index of a cell is its rank in the prefix-summed cell index, so no hash table is needed:
+// (Clouds of more than half a million points: voxel_bins.hip.)
 // Pass 1 (one thread per point): cell key -> set the cell's bit in the index (one atomic OR per point); the same
 //   launch zeroes the output rows pass 2 accumulates into.
 // Scan: prefix sum over the index -> the rank of every active cell = its position in key order, and the
@@ -93,6 +94,28 @@ VoxParams emc2_vox_params(const emc2_voxel_spec* spec) {
   return prm;
 }
 
+static void voxelize_points(emc2_ctx* ctx, const float* d_points, const int32_t* d_batch, int64_t n_points, const VoxParams& prm,
+                            int64_t n_cells, cellword_t* idx, int64_t capacity, int32_t* d_coords, float* d_feats, int32_t* d_counts,
+                            void* d_feats_lp, int lp, int32_t* d_n_voxels, hipStream_t s) {
+  emc2_index_clear(ctx, idx, s);
+  const dim3 pg((unsigned)emc2_div_up(n_points > 0 ? n_points : 1, 256)), blk(256);
+  // at most min(n_points, capacity) voxels exist
+  const int64_t bound = n_points < capacity ? n_points : capacity;
+  if (n_points > 0)
+    hipLaunchKernelGGL(k_vox_mark, pg, blk, 0, s, d_points, d_batch, n_points, prm, idx, emc2_slot_flags(ctx, idx), ctx->first, bound,
+                       (float4*)d_feats, d_counts);
+  emc2_index_scan(ctx, idx, n_cells, capacity, d_n_voxels, s);
+  if (bound <= 0) return;
+  const dim3 vg((unsigned)emc2_div_up(bound, 256));
+  hipLaunchKernelGGL(k_vox_scatter, pg, blk, 0, s, d_points, d_batch, n_points, prm, idx, ctx->first, capacity,
+                     (int4*)d_coords, (float4*)d_feats, d_counts, ctx->stash, ctx->max_voxels);
+#define FIN(LP)                                                                                                 \
+  hipLaunchKernelGGL(k_vox_finalize<LP>, vg, blk, 0, s, d_n_voxels, capacity, ctx->stash, ctx->max_voxels,      \
+                     (float4*)d_feats, d_counts, d_feats_lp)
+  if (lp == 0) FIN(0); else if (lp == 1) FIN(1); else FIN(2);
+#undef FIN
+}
+
 extern "C" emc2_status emc2_voxelize(emc2_ctx* ctx, const float* d_points, const int32_t* d_batch, int64_t n_points,
                                      const emc2_voxel_spec* spec, int64_t capacity, int32_t* d_coords, float* d_feats,
                                      int32_t* d_counts, void* d_feats_lp, emc2_dtype lp_dtype, int32_t* d_n_voxels,
@@ -117,27 +140,9 @@ extern "C" emc2_status emc2_voxelize(emc2_ctx* ctx, const float* d_points, const
   mt.valid = true;
 
   const VoxParams prm = emc2_vox_params(spec);
-  emc2_index_clear(ctx, idx, s);
-  const dim3 pg((unsigned)emc2_div_up(n_points > 0 ? n_points : 1, 256)), blk(256);
-  // at most min(n_points, capacity) voxels exist
-  const int64_t bound = n_points < capacity ? n_points : capacity;
-  if (n_points > 0)
-    hipLaunchKernelGGL(k_vox_mark, pg, blk, 0, s, d_points, d_batch, n_points, prm, idx, emc2_slot_flags(ctx, idx), ctx->first, bound,
-                       (float4*)d_feats, d_counts);
-  emc2_index_scan(ctx, idx, n_cells, capacity, d_n_voxels, s);
-  {
-    if (bound > 0) {
-      const dim3 vg((unsigned)emc2_div_up(bound, 256));
-      hipLaunchKernelGGL(k_vox_scatter, pg, blk, 0, s, d_points, d_batch, n_points, prm, idx, ctx->first, capacity,
-                         (int4*)d_coords, (float4*)d_feats, d_counts, ctx->stash, ctx->max_voxels);
-      const int lp = d_feats_lp ? (lp_dtype == EMC2_F16 ? 1 : 2) : 0;
-#define FIN(LP)                                                                                                 \
-  hipLaunchKernelGGL(k_vox_finalize<LP>, vg, blk, 0, s, d_n_voxels, capacity, ctx->stash, ctx->max_voxels,      \
-                     (float4*)d_feats, d_counts, d_feats_lp)
-      if (lp == 0) FIN(0); else if (lp == 1) FIN(1); else FIN(2);
-#undef FIN
-    }
-  }
+  const int lp = d_feats_lp ? (lp_dtype == EMC2_F16 ? 1 : 2) : 0;
+  const auto pass = emc2_bins_pay(n_points, n_cells) ? emc2_voxelize_bins : voxelize_points;
+  pass(ctx, d_points, d_batch, n_points, prm, n_cells, idx, capacity, d_coords, d_feats, d_counts, d_feats_lp, lp, d_n_voxels, s);
   emc2_status st = emc2_check_hip(ctx, hipGetLastError(), "emc2_voxelize launch");
   if (st != EMC2_OK) return st;
   if (h_n_voxels) {
