@@ -58,7 +58,8 @@ __global__ void __launch_bounds__(256) k_spconv_alu(const T* __restrict__ in, co
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 
-template <typename T, int CIN, int COUT>
+// SPLIT: neighbouring threads that share a row, COUT / SPLIT channels each.
+template <typename T, int CIN, int COUT, int SPLIT>
 __global__ void __launch_bounds__(256) k_spconv_small(const T* __restrict__ in, const T* __restrict__ w,
                                                       const float* __restrict__ scale, const float* __restrict__ shift,
                                                       int epilogue, const int32_t* __restrict__ nbr,
@@ -68,7 +69,9 @@ __global__ void __launch_bounds__(256) k_spconv_small(const T* __restrict__ in, 
   for (int i = threadIdx.x; i < 27 * CIN * COUT; i += 256) wl[i] = to_f32(w[i]);
   int64_t n = *d_n_out;
   if (n > capacity_out) n = capacity_out;
-  const int64_t o = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  constexpr int CO = COUT / SPLIT;
+  const int64_t o = ((int64_t)blockIdx.x * 256 + threadIdx.x) / SPLIT;
+  const int d0 = (int)threadIdx.x % SPLIT * CO;
   const bool live = o < n;
   const int32_t* nrow = nbr + (live ? o : 0);
   const int32_t dead = live ? 0 : -1;
@@ -80,9 +83,9 @@ __global__ void __launch_bounds__(256) k_spconv_small(const T* __restrict__ in, 
   unsigned long long oob = 0ull;   // lanes that saw an entry outside [0, n_in)
 #pragma unroll
   for (int k = 0; k < 27; ++k) j[k] = nrow[(int64_t)k * capacity_out];
-  float acc[COUT];
+  float acc[CO];
 #pragma unroll
-  for (int d = 0; d < COUT; ++d) acc[d] = 0.f;
+  for (int d = 0; d < CO; ++d) acc[d] = 0.f;
   __syncthreads();   // weights in LDS
 #pragma unroll
   for (int k0 = 0; k0 < 27; k0 += TB) {
@@ -108,7 +111,7 @@ __global__ void __launch_bounds__(256) k_spconv_small(const T* __restrict__ in, 
       const bool have = j[k] >= 0;
       if (__ballot(have) == 0ull) continue;  // wave-uniform
       if (have) {
-        const float* wk = wl + k * CIN * COUT;
+        const float* wk = wl + k * CIN * COUT + d0;
 #pragma unroll
         for (int c = 0; c < CIN; ++c) {
           T xe;
@@ -120,24 +123,24 @@ __global__ void __launch_bounds__(256) k_spconv_small(const T* __restrict__ in, 
           }
           const float xv = to_f32(xe);
 #pragma unroll
-          for (int d = 0; d < COUT; ++d) acc[d] = fmaf(xv, wk[c * COUT + d], acc[d]);
+          for (int d = 0; d < CO; ++d) acc[d] = fmaf(xv, wk[c * COUT + d], acc[d]);
         }
       }
     }
   }
   emc2_report_oob(oob, dev_flags);
   if (!live) return;
-  alignas(16) T yr[COUT];
+  alignas(16) T yr[CO];
 #pragma unroll
-  for (int d = 0; d < COUT; ++d) {
+  for (int d = 0; d < CO; ++d) {
     float v = acc[d];
-    if (epilogue != EMC2_EPI_NONE) v = fmaf(v, scale[d], shift[d]);
+    if (epilogue != EMC2_EPI_NONE) v = fmaf(v, scale[d0 + d], shift[d0 + d]);
     if (epilogue == EMC2_EPI_AFFINE_RELU) v = v > 0.f ? v : 0.f;
     from_f32(&yr[d], v);
   }
-  constexpr int OUT_BYTES = COUT * (int)sizeof(T);
+  constexpr int OUT_BYTES = CO * (int)sizeof(T);
   static_assert(OUT_BYTES % 16 == 0, "output rows are written with 16-byte stores");
-  char* dst = reinterpret_cast<char*>(out + o * COUT);
+  char* dst = reinterpret_cast<char*>(out + o * COUT + d0);
 #pragma unroll
   for (int q = 0; q < OUT_BYTES / 16; ++q) reinterpret_cast<u32x4_t*>(dst)[q] = reinterpret_cast<const u32x4_t*>(yr)[q];
 }
@@ -310,19 +313,28 @@ bool launch_rows(const void* d_in, const void* d_w, const float* d_scale, const 
   return false;
 }
 
+// Rows of a launch up to which four threads share a row (fp32): a launch of so many is bound by the chain of a thread's multiply-adds
+// and LDS reads of weights, a quarter as long so.  A thread a row / four, us: 4 -> 16 2 000 rows 13.2 / 7.0, 20 000 13.4 / 7.4, 65 536
+// 14.6 / 10.0; 4 -> 32 24.0 / 9.9, 24.1 / 10.4, 26.4 / 14.3; 16 -> 16 42.0 / 16.3, 42.2 / 18.3, 43.8 / 36.9.
+constexpr int64_t kSplitRows = 65536;
+
 template <typename T>
 bool launch_small(const void* d_in, const void* d_w, const float* d_scale, const float* d_shift, int epilogue,
                   const int32_t* d_nbr, const int32_t* d_n_out, int64_t capacity_out, int32_t n_in, int32_t* dev_flags,
                   int cin, int cout, void* d_out, hipStream_t s) {
+#define EMC2_SMALL_AS(CI, CO, SPLIT)                                                                                             \
+  hipLaunchKernelGGL((k_spconv_small<T, CI, CO, SPLIT>), dim3((unsigned)emc2_div_up(capacity_out * SPLIT, 256)), dim3(256), 0, s, \
+                     (const T*)d_in, (const T*)d_w, d_scale, d_shift, epilogue, d_nbr, d_n_out, capacity_out, n_in, dev_flags,    \
+                     (T*)d_out)
 #define EMC2_SMALL(CI, CO)                                                                                            \
   if (cin == CI && cout == CO) {                                                                                      \
-    hipLaunchKernelGGL((k_spconv_small<T, CI, CO>), dim3((unsigned)emc2_div_up(capacity_out, 256)), dim3(256), 0, s,  \
-                       (const T*)d_in, (const T*)d_w, d_scale, d_shift, epilogue, d_nbr, d_n_out, capacity_out,       \
-                       n_in, dev_flags, (T*)d_out);                                                                   \
+    if (sizeof(T) == 4 && capacity_out <= kSplitRows) EMC2_SMALL_AS(CI, CO, (sizeof(T) == 4 ? 4 : 1));                \
+    else EMC2_SMALL_AS(CI, CO, 1);                                                                                    \
     return true;                                                                                                      \
   }
   EMC2_SMALL(4, 16) EMC2_SMALL(4, 32) EMC2_SMALL(16, 16)
 #undef EMC2_SMALL
+#undef EMC2_SMALL_AS
   return false;
 }
 
