@@ -15,7 +15,7 @@
 //   6       means                             gather 4, expand 3
 //   7                                         expand 4
 //   last    kernel maps of all levels: once the last level is expanded, with the means for up to three levels
-// A phase in which no stack has anything to do is not launched.
+// A phase in which no stack has anything to do is not launched; a small cloud on a small grid is one launch (k_stack_small).
 //
 // gather l: a coarse word is read off the fine level's bits (27 cells behind every coarse cell: nine bit rows OR-ed, then
 // one shift-or and an even-bit compress), so no atomics are needed, nothing has to be cleared first, and the word's
@@ -551,6 +551,137 @@ __global__ void __launch_bounds__(256) k_stack_phase(const Args a) {
 #undef EMC2_ROLE
 }
 
+// A small cloud on a small grid in ONE launch: a level of at most kPrefixTiles tiles and kSmallCloud points.  The whole index fits the
+// LDS of a CU, so every block of the launch builds all of it (bits, and ranks of their words) from all the points, and then
+// takes a share of the voxels, from their points to their kernel-map entries, which it looks up in its own copy: nothing
+// waits for another block.  On 200 000 cells, with the convolution behind it, as a graph, us, phases / so: 1 100 points 31 / 18,
+// 2 000 32 / 19, 8 000 36 / 25, 15 000 36 / 31 (all blocks read all points).  A cloud of fewer points than the block has threads
+// keeps the phases.
+constexpr int kSmallThreads = 1024, kSmallPer = 15;
+constexpr int64_t kSmallCloud = kSmallThreads * kSmallPer;
+constexpr int kSmallBlocks = 32;
+constexpr int kSmallShare = (int)kSmallCloud / kSmallBlocks + 1;    // voxels of a block
+constexpr int kSmallWords = kPrefixTiles * EMC2_SCAN_TILE;
+
+__global__ void __launch_bounds__(kSmallThreads) k_stack_small(const Args a) {
+  __shared__ uint32_t bits_s[kSmallWords];
+  __shared__ uint16_t pre_s[kSmallWords];                             // voxels before each word: at most kSmallCloud
+  __shared__ uint32_t wsum[kSmallThreads / 64];
+  __shared__ uint32_t cnt_s[kSmallShare];                             // points of each voxel of the share, the first of them, the sum
+  __shared__ uint16_t first_s[EMC2_VOX_STASH][kSmallShare];           // of the others
+  __shared__ float rest_s[4][kSmallShare];
+  const DevStack& st = a.st[blockIdx.y];
+  const DevLevel& lv = st.lv[0];
+  const int t = threadIdx.x, n_points = (int)a.n_points;
+  constexpr int WPT = kSmallWords / kSmallThreads;                    // words a thread: half a line
+  uint32_t key[kSmallPer];                                            // cell of each of the thread's points (-1: dropped)
+  float4 pt[kSmallPer];
+#pragma unroll
+  for (int j = 0; j < kSmallPer; ++j) {
+    key[j] = 0xffffffffu;
+    if (j * kSmallThreads < n_points) {                               // uniform
+      const PointCell pc = locate(a.points, st.batch, j * kSmallThreads + t, n_points, st.prm);
+      if (pc.keep) key[j] = (uint32_t)pc.key;
+      pt[j] = pc.p;
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < WPT; ++j) bits_s[j * kSmallThreads + t] = 0u;
+  if (t < kSmallShare) {
+    cnt_s[t] = 0u;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) rest_s[j][t] = 0.f;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kSmallPer; ++j)
+    if (key[j] != 0xffffffffu) atomicOr(&bits_s[key[j] >> 5], 1u << (key[j] & 31u));
+  __syncthreads();
+  uint32_t b[WPT], s = 0;
+#pragma unroll
+  for (int j = 0; j < WPT; ++j) {
+    b[j] = bits_s[t * WPT + j];
+    s += __popc(b[j]);
+  }
+  const uint32_t inc = wave_scan(s);
+  if ((t & 63) == 63) wsum[t >> 6] = inc;
+  __syncthreads();
+  uint32_t run = inc - s, total = 0;
+#pragma unroll
+  for (int j = 0; j < kSmallThreads / 64; ++j) {
+    run += j < (t >> 6) ? wsum[j] : 0u;
+    total += wsum[j];
+  }
+  const uint32_t in_line = s + __shfl_xor(s, 1, 64);
+  // the index: the lines that hold bits and those that held some before, dealt to the blocks
+  if ((t >> 1) % kSmallBlocks == (int)blockIdx.x && (t >> 8) < lv.units) {
+    const bool stale = lv.flags[t >> 1] != 0;                         // a line's two threads are neighbours
+    if (in_line || stale) {
+      uint4* p = reinterpret_cast<uint4*>(lv.idx + t * WPT);
+      uint32_t r = run;
+#pragma unroll
+      for (int j = 0; j < WPT; j += 2) {
+        const uint32_t r1 = r + __popc(b[j]);
+        p[j / 2] = make_uint4(b[j], r, b[j + 1], r1);
+        r = r1 + __popc(b[j + 1]);
+      }
+    }
+    if (!(t & 1) && (in_line != 0) != stale) lv.flags[t >> 1] = in_line != 0;
+  }
+#pragma unroll
+  for (int j = 0; j < WPT; ++j) {
+    pre_s[t * WPT + j] = (uint16_t)run;
+    run += __popc(b[j]);
+  }
+  if (blockIdx.x == 0 && t == 0) report_total(st, lv, total);
+  const int32_t n = (int64_t)total > lv.cap ? (int32_t)lv.cap : (int32_t)total;
+  for (int64_t r = n + (int64_t)blockIdx.x * kSmallThreads + t; r < st.zero_rows; r += kSmallBlocks * kSmallThreads) {
+    st.feats[r] = make_float4(0.f, 0.f, 0.f, 0.f);
+    st.counts[r] = 0;
+  }
+  __syncthreads();
+  const int32_t v0 = (int32_t)((int64_t)n * blockIdx.x / kSmallBlocks), share = (int32_t)((int64_t)n * (blockIdx.x + 1) / kSmallBlocks) - v0;
+#pragma unroll
+  for (int j = 0; j < kSmallPer; ++j) {
+    if (key[j] == 0xffffffffu) continue;
+    const uint32_t v = pre_s[key[j] >> 5] + __popc(bits_s[key[j] >> 5] & ((1u << (key[j] & 31u)) - 1u)) - (uint32_t)v0;
+    if (v >= (uint32_t)share) continue;
+    const uint32_t pos = atomicAdd(&cnt_s[v], 1u);
+    if (pos < EMC2_VOX_STASH) {
+      first_s[pos][v] = (uint16_t)(j * kSmallThreads + t);
+    } else {
+      unsafeAtomicAdd(&rest_s[0][v], pt[j].x);
+      unsafeAtomicAdd(&rest_s[1][v], pt[j].y);
+      unsafeAtomicAdd(&rest_s[2][v], pt[j].z);
+      unsafeAtomicAdd(&rest_s[3][v], pt[j].w);
+    }
+  }
+  __syncthreads();
+  // a thread a voxel
+  if (t < share) {
+    const int64_t r = v0 + t;
+    const int32_t k = (int32_t)cnt_s[t];
+    float4 q[EMC2_VOX_STASH];
+    PointCell pc;
+#pragma unroll
+    for (int j = 0; j < EMC2_VOX_STASH; ++j) {
+      q[j] = make_float4(INFINITY, INFINITY, INFINITY, INFINITY);
+      if (j < k) {
+        const PointCell at = locate(a.points, st.batch, first_s[j][t], n_points, st.prm);
+        q[j] = at.p;
+        if (j == 0) pc = at;
+      }
+    }
+    lv.coords[r] = pc.c;
+    st.counts[r] = k;
+    emc2_store_mean(r, q, make_float4(rest_s[0][t], rest_s[1][t], rest_s[2][t], rest_s[3][t]), k, st.feats, st.lp, st.feats_lp);
+    if (lv.subm) {
+      auto word = [&](uint64_t w) { return make_uint2(bits_s[w], (uint32_t)pre_s[w]); };
+      emc2_probe_at<1>(r, pc.c, true, lv.cap, word, n, lv.g[0], lv.g[1], lv.g[2], lv.subm);
+    }
+  }
+}
+
 struct Phase {
   Args* a;
   void begin() { a->n_jobs = 0; a->blocks = 0; }
@@ -671,6 +802,12 @@ extern "C" emc2_status emc2_build_stacks(const emc2_stack* stacks, int32_t n_sta
   }
   for (int i = 0; i < n_stacks; ++i) publish(stacks[i], a.st[i]);
   hipStream_t s = (hipStream_t)stream;
+  bool small = n_points >= kSmallThreads && n_points <= kSmallCloud;
+  for (int i = 0; i < n_stacks; ++i) small = small && a.st[i].n_levels == 1 && a.st[i].expert < 0 && a.st[i].lv[0].units <= kPrefixTiles;
+  if (small) {
+    hipLaunchKernelGGL(k_stack_small, dim3(kSmallBlocks, (unsigned)n_stacks), dim3(kSmallThreads), 0, s, a);
+    return emc2_check_hip(ctx0, hipGetLastError(), "emc2_build_stacks launch");
+  }
   Phase p{&a};
   const int64_t point_blocks = emc2_div_up(n_points, 256);
   // maps of all levels: 2 048 blocks of 4 waves fill the chip; fewer where the capacities say so
