@@ -13,7 +13,7 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libemc2.so")
 PROBE_LIB = os.path.join(HERE, "libemc2probe.so")     # measurement probes of the bench (include/emc2_probe.h)
 SOURCES = ["context.hip", "cellindex.hip", "voxelize.hip", "voxel_bins.hip", "kmap.hip", "spconv.hip", "spconv_mfma.hip", "spconv_narrow.hip", "spconv_span.hip",
-           "spconv_direct.hip", "project.hip", "decoder.hip", "pool.hip", "dispatch.hip", "spconv_i8.hip",
+           "spconv_direct.hip", "spconv_resident.hip", "project.hip", "decoder.hip", "pool.hip", "dispatch.hip", "spconv_i8.hip",
            "stack.hip"]
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

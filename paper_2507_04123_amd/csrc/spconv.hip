@@ -364,6 +364,7 @@ extern "C" const char* emc2_spconv_kernel(emc2_dtype dtype, int32_t cin, int32_t
   if (dtype != EMC2_F32 && dtype != EMC2_F16 && dtype != EMC2_BF16) return nullptr;
   if (emc2_spconv_uses_mfma(dtype, cin, cout)) {
     if (emc2_spconv_narrow_supported(cin, cout)) return "k_spconv_narrow";
+    if (emc2_spconv_resident_supported(cin, cout)) return "k_spconv_direct";   // (its form with resident weights)
     if (!emc2_spconv_direct_supported(cin, cout)) return "k_spconv_mfma";
     return (map_hint == EMC2_CONV_SUBM && emc2_spconv_span_supported(cin, cout)) ? "k_spconv_span" : "k_spconv_direct";
   }
@@ -429,6 +430,9 @@ extern "C" emc2_status emc2_spconv(emc2_ctx* ctx, emc2_dtype dtype, const void* 
     if (emc2_spconv_narrow_supported(cin, cout))
       emc2_spconv_narrow_launch(dtype, d_in, wp, d_scale, d_shift, (int)epilogue, d_nbr, d_n_out, capacity_out, n_in, flags,
                                 cin, ctx->zero_row, d_out, s);
+    else if (emc2_spconv_resident_supported(cin, cout))
+      emc2_spconv_resident_launch(dtype, d_in, wp, d_scale, d_shift, (int)epilogue, d_nbr, d_n_out, capacity_out, n_in, flags,
+                                  cin, ctx->zero_row, d_out, s);
     else if (!emc2_spconv_direct_supported(cin, cout))
       emc2_spconv_mfma_launch(dtype, d_in, wp, d_scale, d_shift, (int)epilogue, d_nbr, d_n_out, capacity_out, n_in, flags,
                               cin, cout, d_out, s);

@@ -20,8 +20,8 @@
 // A block is 4 waves; a wave owns 32 consecutive output rows (2 tiles of 16) and all Cout columns, so the fp32
 // accumulators never leave registers.  Gathers run 3
 // taps ahead of their use; kernel-map entries two (dz,dy) groups ahead.  Every load is unconditional so the
-// compiler can count the loads in flight.  Shapes: 32 -> 64, 64 -> 32, 64 -> 64, and 64 -> 128 / 128 -> 128, where a
-// tap's matrix work per gathered byte doubles and the kernel leaves the staged per-tap kernel behind by a third.
+// compiler can count the loads in flight.  Shapes: 64 -> 64, and 64 -> 128 / 128 -> 128, where a tap's matrix work per gathered byte
+// doubles and the kernel leaves the staged per-tap kernel behind by a third.  (32 -> 64 and 64 -> 32: spconv_resident.hip.)
 //
 // 128 input channels are taken in two shares, the lower 64 of a group's three taps and then the upper: the order in which
 // the kernel of the submanifold maps adds, so that the map hint never changes a bit.  A row's two 128-byte lines are still
@@ -31,9 +31,8 @@
 //
 // Leaving out: a block first reads all 27 map entries of its rows, keeps them in LDS, and runs only the (dz, dy) groups in which
 // some row has one.  A stride-2 map leaves 31-41 % of the (group, 128 rows) pairs empty, a transposed one 52-62 % (a line of
-// fine sites has one or two of three dy and dz).  Alone, us before / with it: transposed 64 -> 64 over 223 k rows 59 / 45,
-// 64 -> 32 over 304 k 60 / 48; stride-2 32 -> 64 over 573 k 82 / 71, over 852 k 114 / 90, over 223 k 35 / 34.  Submanifold maps
-// (a fifth of the groups empty) and 128 output channels gain less than the longer way to the first operands costs
+// fine sites has one or two of three dy and dz).  Alone, us before / with it: transposed 64 -> 64 over 223 k rows 59 / 45.
+// Submanifold maps (a fifth of the groups empty) and 128 output channels gain less than the longer way to the first operands costs
 // (64 -> 128 over 67 k 50 / 52, 128 -> 128 in whole taps 103 / 113), so they keep the straight walk over the 27 taps.
 #include <hip/hip_bf16.h>
 #include <hip/hip_fp16.h>
@@ -96,14 +95,12 @@ template <int CIN, int COUT, bool BUF> struct DirectCfg {
   static constexpr int MT = 2;
   // waves per SIMD the register allocator must leave room for, as many as no form spills at (the 128-channel shapes keep
   // 64 accumulators and as many operands in flight)
-  static constexpr int MINW = CIN >= 128 || COUT >= 128 ? 2 : (CIN == 64 && COUT == 64) || (COUT == 64 && !BUF) ? 3 : 4;
+  static constexpr int MINW = CIN >= 128 || COUT >= 128 ? 2 : 3;
 };
 
-// Levels of at most so many tiles, a block a CU (two where a tap is short), walk straight over the 27 taps: there the entries' way
-// to the first operands shows, with few neighbours to hide it.  Straight / leaving out, us: 64 -> 32 10 k 9.0 / 9.7, transposed
-// 40 k 14.0 / 12.1, 64 -> 64 40 k 18.8 / 14.9; 32 -> 64 stride-2 10 k 8.4 / 9.4, 30 k 9.1 / 10.1, 44 k 10.5 / 11.2, 55 k 11.1 / 11.8,
-// 62 k 12.6 / 13.4, 73 k 13.9 / 13.5, transposed 44 k 10.5 / 10.1, 55 k 10.9 / 11.1, 61 k 11.5 / 11.2, 73 k 14.0 / 11.8.
-template <int CIN> constexpr int64_t kStraightTiles = CIN == 32 ? 512 : 256;
+// Levels of at most so many tiles, a block a CU, walk straight over the 27 taps: there the entries' way to the first operands shows,
+// with few neighbours to hide it: 64 -> 64 over 21 k rows 12.6 / 14; at 40 k, beyond the line, straight / leaving out 18.8 / 14.9.
+constexpr int64_t kStraightTiles = 256;
 
 // Rows of the input through a buffer descriptor: 32-bit offsets, and the hardware returns zero for an offset at or beyond
 // the end without fetching anything, so an absent neighbour costs neither an address select nor a cache access.  64-beam
@@ -397,7 +394,7 @@ void launch_direct(const void* d_in, const void* d_wp, const float* d_scale, con
 #define LAUNCH(LOOP, BUF, BLOCKS)                                                                                           \
   hipLaunchKernelGGL((k_spconv_direct<DT, CIN, COUT, LOOP, BUF>), dim3((unsigned)(BLOCKS)), dim3(kDThreads), 0, s,           \
                      (const uint16_t*)d_in, (const u32x4*)d_wp, d_scale, d_shift, epilogue, d_nbr, d_n_out, capacity_out,     \
-                     n_in, dev_flags, (const uint16_t*)d_zero_row, skip ? kStraightTiles<CIN> : INT64_MAX, (uint16_t*)d_out)
+                     n_in, dev_flags, (const uint16_t*)d_zero_row, skip ? kStraightTiles : INT64_MAX, (uint16_t*)d_out)
   // Offsets into the input are 32-bit, and the absent neighbour's, 2^32 less a row, must lie at or beyond its end.
   const bool buf = ((int64_t)n_in + 1) * CIN * 2 <= ((int64_t)1 << 32);
   if (blocks <= 4 * kDGrid) {
@@ -413,10 +410,12 @@ void launch_direct(const void* d_in, const void* d_wp, const float* d_scale, con
 }  // namespace
 
 bool emc2_spconv_direct_supported(int cin, int cout) {
-  return (cin == 32 && cout == 64) || (cin == 64 && (cout == 32 || cout == 64 || cout == 128)) || (cin == 128 && cout == 128);
+  return (cin == 64 && (cout == 64 || cout == 128)) || (cin == 128 && cout == 128);
 }
 
-bool emc2_spconv_direct_order(int cin, int cout) { return emc2_spconv_direct_supported(cin, cout) || (cin == 32 && cout == 32); }
+bool emc2_spconv_direct_order(int cin, int cout) {
+  return emc2_spconv_direct_supported(cin, cout) || emc2_spconv_resident_supported(cin, cout) || (cin == 32 && cout == 32);
+}
 
 void emc2_spconv_direct_pack(const void* d_w, int cin, int cout, void* d_packed, hipStream_t stream) {
   const int total = 27 * (cin / 32) * (cout / 16) * 64;
@@ -434,8 +433,7 @@ void emc2_spconv_direct_launch(emc2_dtype dtype, const void* d_in, const void* d
                                d_zero_row, skip, d_out, stream);                                                       \
     return;                                                                                                            \
   }
-  CASE(EMC2_F16, 32, 64) CASE(EMC2_F16, 64, 32) CASE(EMC2_F16, 64, 64)
-  CASE(EMC2_BF16, 32, 64) CASE(EMC2_BF16, 64, 32) CASE(EMC2_BF16, 64, 64)
+  CASE(EMC2_F16, 64, 64) CASE(EMC2_BF16, 64, 64)
   CASE(EMC2_F16, 128, 128) CASE(EMC2_F16, 64, 128) CASE(EMC2_BF16, 128, 128) CASE(EMC2_BF16, 64, 128)
 #undef CASE
 }

@@ -47,3 +47,9 @@ void emc2_spconv_direct_launch(emc2_dtype dtype, const void* d_in, const void* d
                                const float* d_shift, int epilogue, const int32_t* d_nbr, const int32_t* d_n_out,
                                int64_t capacity_out, int32_t n_in, int32_t* dev_flags, int cin, int cout,
                                const void* d_zero_row, bool skip, void* d_out, hipStream_t stream);
+
+// Register-direct with all weights of a block's columns in LDS: the shapes and the packed layout of the register-direct kernel.
+bool emc2_spconv_resident_supported(int cin, int cout);
+void emc2_spconv_resident_launch(emc2_dtype dtype, const void* d_in, const void* d_wp, const float* d_scale, const float* d_shift,
+                                 int epilogue, const int32_t* d_nbr, const int32_t* d_n_out, int64_t capacity_out, int32_t n_in,
+                                 int32_t* dev_flags, int cin, const void* d_zero_row, void* d_out, hipStream_t stream);

@@ -1,0 +1,243 @@
+// Register-direct convolution with resident weights (paper Sec. 3.5 sparse convolution over the non-empty voxels; Sec. 3.6 keeping
+// data on chip between dependent steps): 32 -> 64 and 64 -> 32, every map.
+//
+// The operands as in spconv_direct.hip: lane (m, q) of v_mfma_f32_16x16x32 supplies 16 contiguous bytes of the feature row that its
+// output row names, so a load from global memory is the operand; absent neighbours read past the end of the input's buffer
+// descriptor (inputs of 4 GiB and more: a zeroed row).  There a block of four waves copied each tap's weights through registers to
+// LDS, with a barrier a tap, and ran every (dz, dy) group that some row of its 128 had: a group of three taps took 3.3 us of a
+// CU's time, of which the gathers were a third.  These shapes' weights are 110 KB, which the LDS of a CU holds whole.  A block of 12
+// waves, one a CU, copies them once, behind the only barrier; then each wave takes tiles of 32 rows by itself, runs only the
+// groups that its own rows have (5.1 of nine under a stride-2 map where blocks of 128 rows have 5.8, 2.7 where they have 3.5 under a
+// transposed one), reads weights from LDS wherever it is, and takes the next tile when it is done (tiles of one group next to
+// tiles of nine).  It is bound by the gathers' loads: as many waves as fit (15, with spills) or two groups requested ahead gain
+// nothing, and loads that take whole 128-byte rows, lanes swapped afterwards, neither.  64 -> 64 in two halves of the columns,
+// gathering twice, is 6 % slower than spconv_direct.hip (223 k rows transposed 38 / 41, stride-2 51 / 64).
+// Alone, us, before / so: stride-2 32 -> 64 69 k rows 20.0 / 17.1, 223 k 32.7 / 27.5, 893 k 115 / 90, 1.3 M 170 / 136; submanifold 304 k
+// 46 / 40, 1.2 M 180 / 140; transposed 64 -> 32 54 k 12.8 / 10.6, 223 k 32 / 26, 304 k 43 / 33, 893 k 101 / 70; submanifold 87 / 85; any
+// row from anywhere 223 k 85 / 88 and 103 / 103.
+#include <hip/hip_bf16.h>
+#include <hip/hip_fp16.h>
+
+#include "common.h"
+#include "spconv_mfma.h"
+
+namespace {
+
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 half2v __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));   // native vector: real loads and stores
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
+template <int DT> struct MmaR;
+template <> struct MmaR<EMC2_F16> {
+  static __device__ __forceinline__ floatx4 run(u32x4 a, u32x4 b, floatx4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, a), __builtin_bit_cast(half8, b), c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ uint32_t cvt2(float x, float y) {   // round to nearest even
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2{x, y}), half2v));
+  }
+};
+template <> struct MmaR<EMC2_BF16> {
+  static __device__ __forceinline__ floatx4 run(u32x4 a, u32x4 b, floatx4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ uint32_t cvt2(float x, float y) {
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2{x, y}), bf16x2));
+  }
+};
+
+constexpr int kRWaves = 12;               // three a SIMD, what the LDS beside the weights leaves room for
+constexpr int kRThreads = kRWaves * 64;
+constexpr int kRRows = 32;                // output rows of a wave
+constexpr int64_t kRCUs = 256;            // compute units of the part; one block fits each
+
+
+template <int DT, int CIN, int COUT, bool BUF>
+__global__ void __launch_bounds__(kRThreads, 3)
+k_spconv_direct_resident(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, const float* __restrict__ scale,
+                         const float* __restrict__ shift, int epilogue, const int32_t* __restrict__ nbr,
+                         const int32_t* __restrict__ d_n_out, int64_t capacity_out, int32_t n_in, int32_t* __restrict__ dev_flags,
+                         const uint16_t* __restrict__ zrow, uint16_t* __restrict__ out) {
+  constexpr int KS = CIN / 32, NT = COUT / 16, MT = 2;
+  constexpr int WT = KS * NT * 64;          // 16-byte weight pieces of a tap
+  constexpr int NA = MT * KS;               // operand loads of a tap
+  __shared__ u32x4 wl[27 * WT];
+  __shared__ int32_t ent_s[kRWaves][27 * kRRows];
+  __shared__ uint32_t taken_s;              // tiles of the block that its waves have taken
+  int64_t n_out = *d_n_out;
+  if (n_out > capacity_out) n_out = capacity_out;
+  // XCD-aware: workgroup b runs on XCD b % 8; XCD x takes a contiguous range of wave tiles.  Its blocks take the tiles one by one, so
+  // that few tiles are spread over all of them.
+  const uint32_t blocks = gridDim.x / 8, blk = blockIdx.x / 8;
+  const int64_t n_tiles = (n_out + kRRows - 1) / kRRows, chunk = (n_tiles + 7) / 8;
+  const int64_t tile0 = (int64_t)(blockIdx.x % 8) * chunk;
+  const int64_t tiles = n_tiles - tile0 < chunk ? n_tiles - tile0 : chunk;
+  if ((int64_t)blk >= tiles) return;        // uniform for the block
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int m = lane & 15, q = lane >> 4, half = lane >> 5, row = lane & 31;
+  const __amdgpu_buffer_rsrc_t rows =
+      __builtin_amdgcn_make_buffer_rsrc((void*)const_cast<uint16_t*>(in), 0, BUF ? (int)((uint32_t)n_in * (CIN * 2)) : 0, 0x00020000);
+  unsigned long long oob = 0ull;            // lanes that saw an entry outside [0, n_in)
+  if (threadIdx.x == 0) taken_s = kRWaves;
+  // a wave takes the block's next tile while it works on the last: tiles have from one to nine groups
+  const auto take = [&] {
+    uint32_t k = 0;
+    if (lane == 0) k = atomicAdd(&taken_s, 1u);
+    return (int64_t)blk + (int64_t)__builtin_amdgcn_readfirstlane(k) * blocks;
+  };
+  int64_t slot = blk + (int64_t)wave * blocks, next_slot = 0;
+
+  // half h of the wave holds the entries of taps 2i + h of the 32 rows (past the last tile: the last one's again)
+  int32_t e[14];
+  const auto entries = [&](int64_t at) {
+    const int64_t r0 = (tile0 + (at < tiles ? at : tiles - 1)) * kRRows;
+    const int32_t* p = nbr + r0 + (r0 + row < n_out ? row : 0);
+#pragma unroll
+    for (int i = 0; i < 14; ++i) e[i] = (p + (int64_t)(2 * i) * capacity_out)[i < 13 && half ? capacity_out : 0];
+  };
+  entries(slot);
+  for (int p = threadIdx.x; p < 27 * WT; p += kRThreads) wl[p] = wp[p];
+  __syncthreads();
+  int32_t* ent = ent_s[wave];
+
+  for (; slot < tiles; slot = next_slot) {
+    const int64_t row0 = (tile0 + slot) * kRRows;
+    const int32_t dead = row0 + row < n_out ? 0 : -1;
+    // the entries as rows the kernel may read (absent and beyond the input: -1), [tap][row], and the groups to run
+    uint32_t groups = 0;
+#pragma unroll
+    for (int i = 0; i < 14; ++i) {
+      const int32_t j = max(emc2_entry(e[i], dead, n_in, oob), -1);
+      const unsigned long long some = __ballot(j >= 0);
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+        if (2 * i + t < 27 && (t == 0 ? some & 0xffffffffull : some >> 32) != 0ull) groups |= 1u << ((2 * i + t) / 3);
+      if (2 * i + half < 27) ent[(2 * i + half) * kRRows + row] = j;
+    }
+    __builtin_amdgcn_wave_barrier();        // LDS accesses of a wave are in order
+    floatx4 acc[MT][NT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int j = 0; j < NT; ++j) acc[mt][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    u32x4 a[3][NA];                         // operands in flight, of a group's three taps
+#define EMC2_LOAD(G, KX)                                                                                                     \
+  _Pragma("unroll") for (int mt_ = 0; mt_ < MT; ++mt_) {                                                                     \
+    const int32_t j_ = ent[(3 * (G) + (KX)) * kRRows + 16 * mt_ + m];                                                        \
+    _Pragma("unroll") for (int ks_ = 0; ks_ < KS; ++ks_) {                                                                   \
+      if constexpr (BUF)   /* absent: 2^32 less a row, and a piece of the row: out of range, zero */                         \
+        a[KX][mt_ * KS + ks_] =                                                                                              \
+            __builtin_amdgcn_raw_buffer_load_b128(rows, (int)((uint32_t)j_ * (CIN * 2u) + 16u * (uint32_t)q + 64u * ks_), 0, 0); \
+      else                                                                                                                   \
+        a[KX][mt_ * KS + ks_] = *reinterpret_cast<const u32x4*>((j_ >= 0 ? in + (int64_t)j_ * CIN : zrow) + 8 * q + 32 * ks_); \
+    }                                                                                                                        \
+  }
+  // the weights are the first operand, so that a lane ends up with four consecutive channels of one row
+#define EMC2_TAP(G, KX)                                                                                                      \
+  _Pragma("unroll") for (int ks = 0; ks < KS; ++ks) {                                                                        \
+    const u32x4* w_ = wl + ((3 * (G) + (KX)) * KS + ks) * (NT * 64) + lane;                                                  \
+    u32x4 b[NT];                                                                                                             \
+    _Pragma("unroll") for (int j = 0; j < NT; ++j) b[j] = w_[j * 64];                                                        \
+    _Pragma("unroll") for (int mt = 0; mt < MT; ++mt)                                                                        \
+      _Pragma("unroll") for (int j = 0; j < NT; ++j) acc[mt][j] = MmaR<DT>::run(b[j], a[KX][mt * KS + ks], acc[mt][j]);       \
+  }
+    uint32_t g = 0;                         // (a tile without a neighbour runs group 0 on zeros)
+    if (groups != 0) {
+      g = __builtin_ctz(groups);
+      groups &= groups - 1;
+#pragma unroll
+      for (int kx = 0; kx < 3; ++kx) EMC2_LOAD(g, kx)
+    } else {
+#pragma unroll
+      for (int kx = 0; kx < 3; ++kx)
+#pragma unroll
+        for (int i = 0; i < NA; ++i) a[kx][i] = u32x4{0u, 0u, 0u, 0u};
+    }
+    next_slot = take();
+    entries(next_slot);
+    while (groups != 0) {
+      const uint32_t next = __builtin_ctz(groups);
+      groups &= groups - 1;
+#pragma unroll
+      for (int kx = 0; kx < 3; ++kx) {
+        EMC2_TAP(g, kx)
+        EMC2_LOAD(next, kx)
+      }
+      g = next;
+    }
+#pragma unroll
+    for (int kx = 0; kx < 3; ++kx) EMC2_TAP(g, kx)
+#undef EMC2_LOAD
+#undef EMC2_TAP
+    // Folded affine, ReLU and rounding in registers: lane (m, q) holds channels 16j + 4q .. + 3 of row m; one lane swap per pair of
+    // column tiles leaves it eight consecutive channels.
+#pragma unroll
+    for (int jp = 0; jp < NT / 2; ++jp) {
+      floatx4 sc[2], sh[2];
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int c = 16 * (2 * jp + t) + 4 * q + i;
+          sc[t][i] = epilogue != EMC2_EPI_NONE ? scale[c] : 1.f;
+          sh[t][i] = epilogue != EMC2_EPI_NONE ? shift[c] : -0.f;     // x * 1 + -0 is x
+        }
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) {
+        u32x2 h[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          floatx4 v = acc[mt][2 * jp + t];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            v[i] = fmaf(v[i], sc[t][i], sh[t][i]);
+            if (epilogue == EMC2_EPI_AFFINE_RELU) v[i] = fmaxf(v[i], 0.f);   // NaN -> 0
+          }
+          h[t] = u32x2{MmaR<DT>::cvt2(v[0], v[1]), MmaR<DT>::cvt2(v[2], v[3])};
+        }
+        const u32x2 x = __builtin_amdgcn_permlane16_swap(h[0][0], h[1][0], false, false);
+        const u32x2 y = __builtin_amdgcn_permlane16_swap(h[0][1], h[1][1], false, false);
+        const int64_t o = row0 + 16 * mt + m;
+        if (o < n_out)
+          *reinterpret_cast<u32x4*>(out + o * COUT + 32 * jp + 8 * (2 * (q & 1) + (q >> 1))) = u32x4{x[0], y[0], x[1], y[1]};
+      }
+    }
+  }
+  emc2_report_oob(oob, dev_flags);
+}
+
+template <int DT, int CIN, int COUT>
+void launch_resident(const void* d_in, const void* d_wp, const float* d_scale, const float* d_shift, int epilogue, const int32_t* d_nbr,
+                     const int32_t* d_n_out, int64_t capacity_out, int32_t n_in, int32_t* dev_flags, const void* d_zero_row, void* d_out,
+                     hipStream_t s) {
+  int64_t blocks = emc2_div_up(emc2_div_up(capacity_out, kRRows), 8) * 8;
+  if (blocks > kRCUs) blocks = kRCUs;
+  // Offsets into the input are 32-bit, and the absent neighbour's, 2^32 less a row, must lie at or beyond its end.
+  const bool buf = ((int64_t)n_in + 1) * CIN * 2 <= ((int64_t)1 << 32);
+#define LAUNCH(BUF)                                                                                                               \
+  hipLaunchKernelGGL((k_spconv_direct_resident<DT, CIN, COUT, BUF>), dim3((unsigned)blocks), dim3(kRThreads), 0, s,               \
+                     (const uint16_t*)d_in, (const u32x4*)d_wp, d_scale, d_shift, epilogue, d_nbr, d_n_out, capacity_out, n_in,   \
+                     dev_flags, (const uint16_t*)d_zero_row, (uint16_t*)d_out)
+  if (buf) LAUNCH(true);
+  else LAUNCH(false);
+#undef LAUNCH
+}
+
+}  // namespace
+
+bool emc2_spconv_resident_supported(int cin, int cout) { return (cin == 32 && cout == 64) || (cin == 64 && cout == 32); }
+
+void emc2_spconv_resident_launch(emc2_dtype dtype, const void* d_in, const void* d_wp, const float* d_scale, const float* d_shift,
+                                 int epilogue, const int32_t* d_nbr, const int32_t* d_n_out, int64_t capacity_out, int32_t n_in,
+                                 int32_t* dev_flags, int cin, const void* d_zero_row, void* d_out, hipStream_t stream) {
+#define CASE(D, CI, CO)                                                                                                      \
+  if (dtype == D && cin == CI)                                                                                               \
+    launch_resident<D, CI, CO>(d_in, d_wp, d_scale, d_shift, epilogue, d_nbr, d_n_out, capacity_out, n_in, dev_flags,        \
+                               d_zero_row, d_out, stream);
+  CASE(EMC2_F16, 32, 64) CASE(EMC2_BF16, 32, 64) CASE(EMC2_F16, 64, 32) CASE(EMC2_BF16, 64, 32)
+#undef CASE
+}
