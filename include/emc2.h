@@ -265,8 +265,9 @@ emc2_status emc2_spconv(emc2_ctx* ctx, emc2_dtype dtype, const void* d_in, const
                         const int32_t* d_nbr, int32_t map_hint, const int32_t* d_n_out, int64_t capacity_out,
                         int64_t n_in_rows, int32_t cin, int32_t cout, void* d_out, void* stream);
 
-/* emc2_spconv for n calls in order, in one host call: the arguments of each as in emc2_spconv.  Ends at the first call that
- * is refused; emc2_last_error of calls[0].ctx then says why (nothing is issued if a call has no context). */
+/* emc2_spconv for n calls in one host call, with the results of the calls in their order: the arguments of each as in emc2_spconv.
+ * Calls of one kernel that neither write what another one touches nor wait for a call between them may share a launch.  Ends at the
+ * first call that is refused; emc2_last_error of calls[0].ctx then says why (nothing is issued if a call has no context). */
 typedef struct {
   emc2_ctx* ctx;
   const void* d_in;

@@ -178,12 +178,10 @@ template <> struct Mma4<EMC2_BF16> {
 };
 
 template <int DT, int CIN, int COUT>
-__global__ void __launch_bounds__(256, 4) k_spconv_rows(const uint16_t* __restrict__ in, const uint16_t* __restrict__ w,
-                                                     const float* __restrict__ scale, const float* __restrict__ shift,
-                                                     int epilogue, const int32_t* __restrict__ nbr,
-                                                     const int32_t* __restrict__ d_n_out, int64_t capacity_out,
-                                                     int32_t n_in, int32_t* __restrict__ dev_flags,
-                                                     uint16_t* __restrict__ out) {
+__device__ __forceinline__ void run_rows(uint32_t block, const uint16_t* __restrict__ in, const uint16_t* __restrict__ w,
+                                         const float* __restrict__ scale, const float* __restrict__ shift, int epilogue,
+                                         const int32_t* __restrict__ nbr, const int32_t* __restrict__ d_n_out, int64_t capacity_out,
+                                         int32_t n_in, int32_t* __restrict__ dev_flags, uint16_t* __restrict__ out) {
   constexpr int KB = CIN / 4;                 // 4-channel blocks of an input row
   constexpr int G = COUT / 4;                 // 4-channel groups of an output row
   constexpr int RG = 2;                       // groups of 64 rows per wave (a weight block read serves both)
@@ -204,7 +202,7 @@ __global__ void __launch_bounds__(256, 4) k_spconv_rows(const uint16_t* __restri
   int64_t n = *d_n_out;
   if (n > capacity_out) n = capacity_out;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t row0 = (int64_t)blockIdx.x * (4 * RG * 64) + (int64_t)wave * (RG * 64) + lane;
+  const int64_t row0 = (int64_t)block * (4 * RG * 64) + (int64_t)wave * (RG * 64) + lane;
   bool live[RG];
   const int32_t* nrow[RG];
   int32_t dead[RG];
@@ -297,20 +295,27 @@ __global__ void __launch_bounds__(256, 4) k_spconv_rows(const uint16_t* __restri
   }
 }
 
-template <int DT>
-bool launch_rows(const void* d_in, const void* d_w, const float* d_scale, const float* d_shift, int epilogue,
-                 const int32_t* d_nbr, const int32_t* d_n_out, int64_t capacity_out, int32_t n_in, int32_t* dev_flags,
-                 int cin, int cout, void* d_out, hipStream_t s) {
-#define EMC2_ROWS(CI, CO)                                                                                             \
-  if (cin == CI && cout == CO) {                                                                                      \
-    hipLaunchKernelGGL((k_spconv_rows<DT, CI, CO>), dim3((unsigned)emc2_div_up(capacity_out, 512)), dim3(256), 0, s,  \
-                       (const uint16_t*)d_in, (const uint16_t*)d_w, d_scale, d_shift, epilogue, d_nbr, d_n_out,       \
-                       capacity_out, n_in, dev_flags, (uint16_t*)d_out);                                              \
-    return true;                                                                                                      \
+template <int DT, int CIN, int COUT> __global__ void __launch_bounds__(256, 4) k_spconv_rows(const emc2_conv_batch b) {
+  const int i = emc2_conv_of_block(b);
+  const emc2_conv_args& c = b.call[i];
+  run_rows<DT, CIN, COUT>(blockIdx.x - b.first[i], (const uint16_t*)c.d_in, (const uint16_t*)c.d_w, c.d_scale, c.d_shift, c.epilogue,
+                          c.d_nbr, c.d_n_out, c.capacity_out, c.n_in, c.dev_flags, (uint16_t*)c.d_out);
+}
+
+void launch_rows(emc2_dtype dtype, int cin, int cout, const emc2_conv_args* calls, int n, hipStream_t s) {
+  emc2_conv_batch b;
+  b.n = n;
+  uint32_t blocks = 0;
+  for (int i = 0; i < n; ++i) {
+    b.call[i] = calls[i];
+    b.first[i] = blocks;
+    blocks += (uint32_t)emc2_div_up(calls[i].capacity_out, 512);
   }
-  EMC2_ROWS(4, 16) EMC2_ROWS(4, 32) EMC2_ROWS(16, 16)
+#define EMC2_ROWS(D, CI, CO) \
+  if (dtype == D && cin == CI && cout == CO) hipLaunchKernelGGL((k_spconv_rows<D, CI, CO>), dim3(blocks), dim3(256), 0, s, b);
+  EMC2_ROWS(EMC2_F16, 4, 16) EMC2_ROWS(EMC2_F16, 4, 32) EMC2_ROWS(EMC2_F16, 16, 16)
+  EMC2_ROWS(EMC2_BF16, 4, 16) EMC2_ROWS(EMC2_BF16, 4, 32) EMC2_ROWS(EMC2_BF16, 16, 16)
 #undef EMC2_ROWS
-  return false;
 }
 
 // Rows of a launch up to which four threads share a row (fp32): a launch of so many is bound by the chain of a thread's multiply-adds
@@ -388,13 +393,27 @@ extern "C" emc2_status emc2_pack_weights(emc2_ctx* ctx, emc2_dtype dtype, const 
   return emc2_check_hip(ctx, hipGetLastError(), "emc2_pack_weights launch");
 }
 
-extern "C" emc2_status emc2_spconv(emc2_ctx* ctx, emc2_dtype dtype, const void* d_in, const void* d_w,
-                                   emc2_wlayout w_layout, const float* d_scale, const float* d_shift,
-                                   emc2_epilogue epilogue, const int32_t* d_nbr, int32_t map_hint,
-                                   const int32_t* d_n_out, int64_t capacity_out, int64_t n_in_rows, int32_t cin,
-                                   int32_t cout, void* d_out, void* stream) {
+// The kernels that a launch can hold several calls of.
+enum ConvKind { CONV_SINGLE, CONV_ROWS, CONV_NARROW, CONV_RESIDENT };
+
+static ConvKind kind_of(emc2_dtype dtype, int cin, int cout) {
+  if (dtype == EMC2_F32) return CONV_SINGLE;
+  if (emc2_spconv_narrow_supported(cin, cout)) return CONV_NARROW;
+  if (emc2_spconv_resident_supported(cin, cout)) return CONV_RESIDENT;
+  return !emc2_spconv_uses_mfma(dtype, cin, cout) && rows_covers(cin, cout) ? CONV_ROWS : CONV_SINGLE;
+}
+
+static emc2_status check_conv(const emc2_conv_call& c) {
+  emc2_ctx* ctx = c.ctx;
   if (!ctx) return EMC2_ERR_INVALID_ARG;
-  if (!d_in || !d_w || !d_nbr || !d_n_out || !d_out)
+  const emc2_dtype dtype = c.dtype;
+  const emc2_wlayout w_layout = c.w_layout;
+  const emc2_epilogue epilogue = c.epilogue;
+  const int32_t map_hint = c.map_hint, cin = c.cin, cout = c.cout;
+  const int64_t capacity_out = c.capacity_out, n_in_rows = c.n_in_rows;
+  const void *d_in = c.d_in, *d_w = c.d_w, *d_out = c.d_out;
+  const float *d_scale = c.d_scale, *d_shift = c.d_shift;
+  if (!d_in || !d_w || !c.d_nbr || !c.d_n_out || !d_out)
     return emc2_fail(ctx, EMC2_ERR_INVALID_ARG, "emc2_spconv: null argument");
   if (epilogue != EMC2_EPI_NONE && epilogue != EMC2_EPI_AFFINE && epilogue != EMC2_EPI_AFFINE_RELU)
     return emc2_fail(ctx, EMC2_ERR_INVALID_ARG, "emc2_spconv: bad epilogue");
@@ -402,7 +421,6 @@ extern "C" emc2_status emc2_spconv(emc2_ctx* ctx, emc2_dtype dtype, const void* 
     return emc2_fail(ctx, EMC2_ERR_INVALID_ARG, "emc2_spconv: scale/shift must be given iff the epilogue is affine");
   if (capacity_out < 1) return emc2_fail(ctx, EMC2_ERR_INVALID_ARG, "emc2_spconv: capacity_out < 1");
   if (n_in_rows < 0) return emc2_fail(ctx, EMC2_ERR_INVALID_ARG, "emc2_spconv: n_in_rows < 0");
-  const int32_t n_in = n_in_rows > 0x7fffffff ? 0x7fffffff : (int32_t)n_in_rows;
   if (cin < 1 || cout < 1 || cin > 1024 || cout > 256)
     return emc2_fail(ctx, EMC2_ERR_UNSUPPORTED, "emc2_spconv: channels outside Cin<=1024, Cout<=256");
   if (dtype != EMC2_F32 && dtype != EMC2_F16 && dtype != EMC2_BF16)
@@ -417,59 +435,141 @@ extern "C" emc2_status emc2_spconv(emc2_ctx* ctx, emc2_dtype dtype, const void* 
   // the matrix-core and small-channel kernels move rows as 8- or 16-byte pieces
   if (dtype != EMC2_F32 && (((uintptr_t)d_in | (uintptr_t)d_out | (uintptr_t)d_w) & 15u))
     return emc2_fail(ctx, EMC2_ERR_INVALID_ARG, "emc2_spconv: 16-bit d_in, d_w and d_out must be 16-byte aligned");
-  hipStream_t s = (hipStream_t)stream;
-  int32_t* flags = ctx->dev_words;
-  if (mfma) {
-    const void* wp = d_w;
-    if (w_layout == EMC2_W_PLAIN) {
+  return EMC2_OK;
+}
+
+// n calls of one kind, checked; of CONV_SINGLE one.
+static emc2_status issue_convs(const emc2_conv_call* const* calls, int n, hipStream_t s) {
+  const emc2_conv_call& c = *calls[0];
+  emc2_ctx* ctx = c.ctx;
+  const emc2_dtype dtype = c.dtype;
+  const int cin = c.cin, cout = c.cout;
+  emc2_conv_args a[kConvBatch];
+  for (int i = 0; i < n; ++i) {
+    const emc2_conv_call& t = *calls[i];
+    const void* w = t.d_w;
+    if (t.w_layout == EMC2_W_PLAIN && emc2_spconv_uses_mfma(dtype, cin, cout)) {
       // stream order protects the shared scratch
-      if (emc2_spconv_direct_order(cin, cout)) emc2_spconv_direct_pack(d_w, cin, cout, ctx->wpack, s);
-      else emc2_spconv_mfma_pack(d_w, cin, cout, ctx->wpack, s);
-      wp = ctx->wpack;
+      if (emc2_spconv_direct_order(cin, cout)) emc2_spconv_direct_pack(w, cin, cout, t.ctx->wpack, s);
+      else emc2_spconv_mfma_pack(w, cin, cout, t.ctx->wpack, s);
+      w = t.ctx->wpack;
     }
-    if (emc2_spconv_narrow_supported(cin, cout))
-      emc2_spconv_narrow_launch(dtype, d_in, wp, d_scale, d_shift, (int)epilogue, d_nbr, d_n_out, capacity_out, n_in, flags,
-                                cin, ctx->zero_row, d_out, s);
-    else if (emc2_spconv_resident_supported(cin, cout))
-      emc2_spconv_resident_launch(dtype, d_in, wp, d_scale, d_shift, (int)epilogue, d_nbr, d_n_out, capacity_out, n_in, flags,
-                                  cin, ctx->zero_row, d_out, s);
-    else if (!emc2_spconv_direct_supported(cin, cout))
-      emc2_spconv_mfma_launch(dtype, d_in, wp, d_scale, d_shift, (int)epilogue, d_nbr, d_n_out, capacity_out, n_in, flags,
-                              cin, cout, d_out, s);
-    else if (map_hint == EMC2_CONV_SUBM && emc2_spconv_span_supported(cin, cout))
-      // pays where the three kx taps of a group name nearly the same rows
-      emc2_spconv_span_launch(dtype, d_in, wp, d_scale, d_shift, (int)epilogue, d_nbr, d_n_out, capacity_out, n_in, flags,
-                              cin, cout, d_out, s);
-    else
-      emc2_spconv_direct_launch(dtype, d_in, wp, d_scale, d_shift, (int)epilogue, d_nbr, d_n_out, capacity_out, n_in, flags,
-                                cin, cout, ctx->zero_row, map_hint != EMC2_CONV_SUBM, d_out, s);
-  } else if (dtype == EMC2_F32) {
-    launch_alu<float>(d_in, d_w, d_scale, d_shift, (int)epilogue, d_nbr, d_n_out, capacity_out, n_in, flags, cin, cout, d_out, s);
-  } else if (dtype == EMC2_F16 && launch_rows<EMC2_F16>(d_in, d_w, d_scale, d_shift, (int)epilogue, d_nbr, d_n_out, capacity_out,
-                                                        n_in, flags, cin, cout, d_out, s)) {
-  } else if (dtype == EMC2_BF16 && launch_rows<EMC2_BF16>(d_in, d_w, d_scale, d_shift, (int)epilogue, d_nbr, d_n_out,
-                                                          capacity_out, n_in, flags, cin, cout, d_out, s)) {
-  } else if (dtype == EMC2_F16) {
-    launch_alu<__half>(d_in, d_w, d_scale, d_shift, (int)epilogue, d_nbr, d_n_out, capacity_out, n_in, flags, cin, cout, d_out, s);
-  } else {
-    launch_alu<__hip_bfloat16>(d_in, d_w, d_scale, d_shift, (int)epilogue, d_nbr, d_n_out, capacity_out, n_in, flags, cin, cout,
-                               d_out, s);
+    a[i] = emc2_conv_args{t.d_in, w, t.d_scale, t.d_shift, t.d_nbr, t.d_n_out, t.ctx->zero_row, t.d_out, t.capacity_out,
+                          t.n_in_rows > 0x7fffffff ? 0x7fffffff : (int32_t)t.n_in_rows, (int32_t)t.epilogue, t.ctx->dev_words};
+  }
+  const emc2_conv_args& x = a[0];
+  switch (kind_of(dtype, cin, cout)) {
+    case CONV_ROWS: launch_rows(dtype, cin, cout, a, n, s); break;
+    case CONV_NARROW: emc2_spconv_narrow_launch(dtype, cin, a, n, s); break;
+    case CONV_RESIDENT: emc2_spconv_resident_launch(dtype, cin, a, n, s); break;
+    default:
+#define ALU(T)                                                                                                                    \
+  launch_alu<T>(x.d_in, x.d_w, x.d_scale, x.d_shift, x.epilogue, x.d_nbr, x.d_n_out, x.capacity_out, x.n_in, x.dev_flags, cin, cout, \
+                x.d_out, s)
+      if (dtype == EMC2_F32) ALU(float);
+      else if (!emc2_spconv_uses_mfma(dtype, cin, cout)) {
+        if (dtype == EMC2_F16) ALU(__half);
+        else ALU(__hip_bfloat16);
+      }
+#undef ALU
+      else if (!emc2_spconv_direct_supported(cin, cout))
+        emc2_spconv_mfma_launch(dtype, x.d_in, x.d_w, x.d_scale, x.d_shift, x.epilogue, x.d_nbr, x.d_n_out, x.capacity_out, x.n_in,
+                                x.dev_flags, cin, cout, x.d_out, s);
+      else if (c.map_hint == EMC2_CONV_SUBM && emc2_spconv_span_supported(cin, cout))
+        // pays where the three kx taps of a group name nearly the same rows
+        emc2_spconv_span_launch(dtype, x.d_in, x.d_w, x.d_scale, x.d_shift, x.epilogue, x.d_nbr, x.d_n_out, x.capacity_out, x.n_in,
+                                x.dev_flags, cin, cout, x.d_out, s);
+      else
+        emc2_spconv_direct_launch(dtype, x.d_in, x.d_w, x.d_scale, x.d_shift, x.epilogue, x.d_nbr, x.d_n_out, x.capacity_out, x.n_in,
+                                  x.dev_flags, cin, cout, x.d_zero_row, c.map_hint != EMC2_CONV_SUBM, x.d_out, s);
   }
   return emc2_check_hip(ctx, hipGetLastError(), "emc2_spconv launch");
 }
+
+extern "C" emc2_status emc2_spconv(emc2_ctx* ctx, emc2_dtype dtype, const void* d_in, const void* d_w,
+                                   emc2_wlayout w_layout, const float* d_scale, const float* d_shift,
+                                   emc2_epilogue epilogue, const int32_t* d_nbr, int32_t map_hint,
+                                   const int32_t* d_n_out, int64_t capacity_out, int64_t n_in_rows, int32_t cin,
+                                   int32_t cout, void* d_out, void* stream) {
+  const emc2_conv_call c = {ctx, d_in, d_w, d_scale, d_shift, d_nbr, d_n_out, d_out, capacity_out, n_in_rows, dtype, w_layout, epilogue,
+                            map_hint, cin, cout};
+  const emc2_status st = check_conv(c);
+  if (st != EMC2_OK) return st;
+  const emc2_conv_call* one = &c;
+  return issue_convs(&one, 1, (hipStream_t)stream);
+}
+
+// What a call reads and writes, in bytes.
+struct Touched {
+  uintptr_t lo[7], hi[7];   // [0]: the output; the input, weights, scale, shift, map and row count
+};
+static Touched touched_by(const emc2_conv_call& c) {
+  const int64_t esz = c.dtype == EMC2_F32 ? 4 : 2;
+  const void* at[7] = {c.d_out, c.d_in, c.d_w, c.d_scale, c.d_shift, c.d_nbr, c.d_n_out};
+  const int64_t bytes[7] = {c.capacity_out * c.cout * esz, c.n_in_rows * c.cin * esz, 27 * (int64_t)c.cin * c.cout * esz,
+                            c.d_scale ? 4 * (int64_t)c.cout : 0, c.d_shift ? 4 * (int64_t)c.cout : 0, 27 * c.capacity_out * 4, 4};
+  Touched t;
+  for (int i = 0; i < 7; ++i) {
+    t.lo[i] = (uintptr_t)at[i];
+    t.hi[i] = t.lo[i] + (uintptr_t)bytes[i];
+  }
+  return t;
+}
+// One writes what the other reads or writes: their order matters.
+static bool ordered(const Touched& a, const Touched& b) {
+  for (int i = 0; i < 7; ++i)
+    if ((a.lo[0] < b.hi[i] && b.lo[i] < a.hi[0]) || (b.lo[0] < a.hi[i] && a.lo[i] < b.hi[0])) return true;
+  return false;
+}
+
+static bool in_launch(const emc2_conv_call* const* batch, int m, const emc2_conv_call* c) {
+  for (int i = 0; i < m; ++i)
+    if (batch[i] == c) return true;
+  return false;
+}
+
+constexpr int kListPlanned = 64;     // calls of a list that are looked at together
 
 extern "C" emc2_status emc2_spconv_list(const emc2_conv_call* calls, int32_t n, void* stream) {
   if (n < 0 || (n > 0 && !calls)) return EMC2_ERR_INVALID_ARG;
   for (int32_t i = 0; i < n; ++i)
     if (!calls[i].ctx) return emc2_fail(calls[0].ctx, EMC2_ERR_INVALID_ARG, "emc2_spconv_list: call %d has no context", i);
-  for (int32_t i = 0; i < n; ++i) {
+  // Calls of one kernel that do not wait for anything still to be issued share a launch: small levels of several branches -- three
+  // scales of a frame, experts without a scene -- fill a fraction of the chip each and take a launch's 4.5 us at least, and one
+  // after the other each ends in a tail of its own.  4 -> 16 -> 32 of three scales (64-beam frame): 6 launches 68 us, 2 launches 41;
+  // five small scenes' layers 1373 -> 1330 us a pass.  Otherwise the order stays that of the list.  (Plain weights of the matrix
+  // kernels go through scratch, one call at a time.)
+  emc2_status refused = EMC2_OK;
+  int32_t end = 0;                     // the first refused call: nothing behind it is issued
+  while (end < n && (refused = check_conv(calls[end])) == EMC2_OK) ++end;
+  bool done[kListPlanned] = {};
+  Touched t[kListPlanned];
+  const bool planned = end <= kListPlanned;
+  for (int32_t i = 0; planned && i < end; ++i) t[i] = touched_by(calls[i]);
+  const emc2_conv_call* at = nullptr;
+  emc2_status st = EMC2_OK;
+  for (int32_t i = 0; st == EMC2_OK && i < end; ++i) {
+    if (planned && done[i]) continue;
     const emc2_conv_call& c = calls[i];
-    const emc2_status st = emc2_spconv(c.ctx, c.dtype, c.d_in, c.d_w, c.w_layout, c.d_scale, c.d_shift, c.epilogue, c.d_nbr, c.map_hint,
-                                       c.d_n_out, c.capacity_out, c.n_in_rows, c.cin, c.cout, c.d_out, stream);
-    if (st != EMC2_OK) {   // the caller asks the first call's context what went wrong, whichever call it was
-      if (c.ctx != calls[0].ctx) emc2_fail(calls[0].ctx, st, "%s", c.ctx->err);
-      return st;
+    const emc2_conv_call* batch[kConvBatch] = {&c};
+    int m = 1;
+    if (planned && kind_of(c.dtype, c.cin, c.cout) != CONV_SINGLE &&
+        (c.w_layout == EMC2_W_PACKED || !emc2_spconv_uses_mfma(c.dtype, c.cin, c.cout))) {
+      for (int32_t j = i + 1; j < end && m < kConvBatch; ++j) {
+        const emc2_conv_call& d = calls[j];
+        if (done[j] || d.dtype != c.dtype || d.cin != c.cin || d.cout != c.cout || d.w_layout != c.w_layout) continue;
+        bool waits = false;             // for an earlier call still to be issued, or for one of this launch
+        for (int32_t k = i; !waits && k < j; ++k) waits = (!done[k] || k == i || in_launch(batch, m, calls + k)) && ordered(t[k], t[j]);
+        if (waits) continue;
+        batch[m++] = &d;
+        done[j] = true;
+      }
     }
+    st = issue_convs(batch, m, (hipStream_t)stream);
+    at = &c;
   }
-  return EMC2_OK;
+  if (st == EMC2_OK && end < n) st = refused, at = calls + end;
+  // the caller asks the first call's context what went wrong, whichever call it was
+  if (st != EMC2_OK && at->ctx != calls[0].ctx) emc2_fail(calls[0].ctx, st, "%s", at->ctx->err);
+  return st;
 }

@@ -5,6 +5,30 @@
 
 #include "emc2.h"
 
+// What a convolution's launch is given, checked; one of several in a launch (their blocks come one after the other).
+struct emc2_conv_args {
+  const void *d_in, *d_w;               // d_w as the kernel reads it
+  const float *d_scale, *d_shift;
+  const int32_t *d_nbr, *d_n_out;
+  const void* d_zero_row;
+  void* d_out;
+  int64_t capacity_out;
+  int32_t n_in, epilogue;
+  int32_t* dev_flags;
+};
+constexpr int kConvBatch = 4;
+struct emc2_conv_batch {
+  int32_t n;
+  uint32_t first[kConvBatch];           // first block of each, a multiple of 8
+  emc2_conv_args call[kConvBatch];
+};
+// The call that this block belongs to.
+__device__ __forceinline__ int emc2_conv_of_block(const emc2_conv_batch& b) {
+  int i = 0;
+  while (i + 1 < b.n && blockIdx.x >= b.first[i + 1]) ++i;
+  return i;
+}
+
 // true iff (cin, cout) is covered by an MFMA instantiation (16-bit dtypes only)
 bool emc2_spconv_mfma_supported(int cin, int cout);
 
@@ -31,9 +55,7 @@ void emc2_spconv_span_launch(emc2_dtype dtype, const void* d_in, const void* d_w
 // 16 -> 32 and 32 -> 32, every map.  Weights as emc2_spconv_mfma_pack (16) and emc2_spconv_direct_pack (32) order them.
 // d_zero_row: >= 256 zero bytes in device memory.
 bool emc2_spconv_narrow_supported(int cin, int cout);
-void emc2_spconv_narrow_launch(emc2_dtype dtype, const void* d_in, const void* d_wp, const float* d_scale, const float* d_shift,
-                               int epilogue, const int32_t* d_nbr, const int32_t* d_n_out, int64_t capacity_out, int32_t n_in,
-                               int32_t* dev_flags, int cin, const void* d_zero_row, void* d_out, hipStream_t stream);
+void emc2_spconv_narrow_launch(emc2_dtype dtype, int cin, const emc2_conv_args* calls, int n, hipStream_t stream);
 
 // Register-direct variant (A operands straight from global memory, 16x16x32 MFMA; LDS holds weights only).
 // Its packed weight layout, emc2_spconv_direct_pack's, differs from the staged kernel's; emc2_spconv_direct_order: the shapes
@@ -50,6 +72,4 @@ void emc2_spconv_direct_launch(emc2_dtype dtype, const void* d_in, const void* d
 
 // Register-direct with all weights of a block's columns in LDS: the shapes and the packed layout of the register-direct kernel.
 bool emc2_spconv_resident_supported(int cin, int cout);
-void emc2_spconv_resident_launch(emc2_dtype dtype, const void* d_in, const void* d_wp, const float* d_scale, const float* d_shift,
-                                 int epilogue, const int32_t* d_nbr, const int32_t* d_n_out, int64_t capacity_out, int32_t n_in,
-                                 int32_t* dev_flags, int cin, const void* d_zero_row, void* d_out, hipStream_t stream);
+void emc2_spconv_resident_launch(emc2_dtype dtype, int cin, const emc2_conv_args* calls, int n, hipStream_t stream);

@@ -67,11 +67,11 @@ template <int CIN> struct NarrowCfg {
 };
 
 template <int DT, int CIN, bool BUF>
-__global__ void __launch_bounds__(NarrowCfg<CIN>::WAVES * 64, 4)
-k_spconv_narrow(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, const float* __restrict__ scale,
-                const float* __restrict__ shift, int epilogue, const int32_t* __restrict__ nbr, const int32_t* __restrict__ d_n_out,
-                int64_t capacity_out, int32_t n_in, int32_t* __restrict__ dev_flags, const uint16_t* __restrict__ zrow,
-                uint16_t* __restrict__ out) {
+__device__ __forceinline__ void run_narrow(uint32_t block, uint32_t n_blocks, const uint16_t* __restrict__ in, const u32x4* __restrict__ wp,
+                                           const float* __restrict__ scale, const float* __restrict__ shift, int epilogue,
+                                           const int32_t* __restrict__ nbr, const int32_t* __restrict__ d_n_out, int64_t capacity_out,
+                                           int32_t n_in, int32_t* __restrict__ dev_flags, const uint16_t* __restrict__ zrow,
+                                           uint16_t* __restrict__ out) {
   using C = NarrowCfg<CIN>;
   constexpr int D = C::DEPTH, LPT = C::LPT;
   __shared__ u32x4 wl[C::PIECES];
@@ -83,14 +83,14 @@ k_spconv_narrow(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, c
   // XCD-aware: workgroup b runs on XCD b % 8; XCD x takes a contiguous range of wave tiles
   const int64_t n_tiles = (n_out + kNRows - 1) / kNRows;
   const int64_t chunk = (n_tiles + 7) / 8;
-  const int64_t tile0 = (int64_t)(blockIdx.x % 8) * chunk;
+  const int64_t tile0 = (int64_t)(block % 8) * chunk;
   const int64_t tiles = n_tiles - tile0 < chunk ? n_tiles - tile0 : chunk;
-  if ((int64_t)(blockIdx.x / 8) * C::WAVES >= tiles) return;   // uniform for the block
+  if ((int64_t)(block / 8) * C::WAVES >= tiles) return;   // uniform for the block
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int m = lane & 31, h = lane >> 5;                      // entries: row and half
   const int piece0 = CIN == 16 ? h : lane >> 4;                // operands: 16-byte piece of the row
-  const int64_t step = (int64_t)(gridDim.x / 8) * C::WAVES;
-  int64_t slot = (int64_t)(blockIdx.x / 8) * C::WAVES + wave;
+  const int64_t step = (int64_t)(n_blocks / 8) * C::WAVES;
+  int64_t slot = (int64_t)(block / 8) * C::WAVES + wave;
 
   unsigned long long oob = 0ull;   // lanes that saw an entry outside [0, n_in)
   // half h of the wave holds the entries of taps 2i + h of the 32 rows
@@ -197,36 +197,41 @@ k_spconv_narrow(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, c
   emc2_report_oob(oob, dev_flags);
 }
 
-template <int DT, int CIN>
-void launch_narrow(const void* d_in, const void* d_wp, const float* d_scale, const float* d_shift, int epilogue, const int32_t* d_nbr,
-                   const int32_t* d_n_out, int64_t capacity_out, int32_t n_in, int32_t* dev_flags, const void* d_zero_row, void* d_out,
-                   hipStream_t s) {
+template <int DT, int CIN, bool BUF>
+__global__ void __launch_bounds__(NarrowCfg<CIN>::WAVES * 64, 4) k_spconv_narrow(const emc2_conv_batch b) {
+  const int i = emc2_conv_of_block(b);
+  const emc2_conv_args& c = b.call[i];
+  run_narrow<DT, CIN, BUF>(blockIdx.x - b.first[i], (i + 1 < b.n ? b.first[i + 1] : gridDim.x) - b.first[i], (const uint16_t*)c.d_in,
+                           (const u32x4*)c.d_w, c.d_scale, c.d_shift, c.epilogue, c.d_nbr, c.d_n_out, c.capacity_out, c.n_in, c.dev_flags,
+                           (const uint16_t*)c.d_zero_row, (uint16_t*)c.d_out);
+}
+
+template <int DT, int CIN> void launch_narrow(const emc2_conv_args* calls, int n, hipStream_t s) {
   using C = NarrowCfg<CIN>;
-  int64_t blocks = emc2_div_up(emc2_div_up(capacity_out, kNRows * C::WAVES), 8) * 8;
-  if (blocks > C::GRID) blocks = C::GRID;
+  emc2_conv_batch b;
+  b.n = n;
+  uint32_t blocks = 0;
   // Offsets into the input are 32-bit, and the absent neighbour's, 2^32 less a row, must lie at or beyond its end; so are the
   // offsets into two taps of the map.
-  const bool buf = ((int64_t)n_in + 1) * CIN * 2 <= ((int64_t)1 << 32) && capacity_out < ((int64_t)1 << 29);
-#define LAUNCH(BUF)                                                                                                         \
-  hipLaunchKernelGGL((k_spconv_narrow<DT, CIN, BUF>), dim3((unsigned)blocks), dim3(C::WAVES * 64), 0, s, (const uint16_t*)d_in,      \
-                     (const u32x4*)d_wp, d_scale, d_shift, epilogue, d_nbr, d_n_out, capacity_out, n_in, dev_flags,         \
-                     (const uint16_t*)d_zero_row, (uint16_t*)d_out)
-  if (buf) LAUNCH(true);
-  else LAUNCH(false);
-#undef LAUNCH
+  bool buf = true;
+  for (int i = 0; i < n; ++i) {
+    b.call[i] = calls[i];
+    b.first[i] = blocks;
+    const int64_t own = emc2_div_up(emc2_div_up(calls[i].capacity_out, kNRows * C::WAVES), 8) * 8;
+    blocks += (uint32_t)(own < C::GRID ? own : C::GRID);
+    buf = buf && ((int64_t)calls[i].n_in + 1) * CIN * 2 <= ((int64_t)1 << 32) && calls[i].capacity_out < ((int64_t)1 << 29);
+  }
+  if (buf) hipLaunchKernelGGL((k_spconv_narrow<DT, CIN, true>), dim3(blocks), dim3(C::WAVES * 64), 0, s, b);
+  else hipLaunchKernelGGL((k_spconv_narrow<DT, CIN, false>), dim3(blocks), dim3(C::WAVES * 64), 0, s, b);
 }
 
 }  // namespace
 
 bool emc2_spconv_narrow_supported(int cin, int cout) { return (cin == 16 || cin == 32) && cout == kNCout; }
 
-void emc2_spconv_narrow_launch(emc2_dtype dtype, const void* d_in, const void* d_wp, const float* d_scale, const float* d_shift,
-                               int epilogue, const int32_t* d_nbr, const int32_t* d_n_out, int64_t capacity_out, int32_t n_in,
-                               int32_t* dev_flags, int cin, const void* d_zero_row, void* d_out, hipStream_t stream) {
-#define CASE(D, CI)                                                                                                          \
-  if (dtype == D && cin == CI)                                                                                               \
-    launch_narrow<D, CI>(d_in, d_wp, d_scale, d_shift, epilogue, d_nbr, d_n_out, capacity_out, n_in, dev_flags, d_zero_row,  \
-                         d_out, stream);
+void emc2_spconv_narrow_launch(emc2_dtype dtype, int cin, const emc2_conv_args* calls, int n, hipStream_t stream) {
+#define CASE(D, CI) \
+  if (dtype == D && cin == CI) launch_narrow<D, CI>(calls, n, stream);
   CASE(EMC2_F16, 16) CASE(EMC2_BF16, 16) CASE(EMC2_F16, 32) CASE(EMC2_BF16, 32)
 #undef CASE
 }

@@ -57,11 +57,11 @@ constexpr int64_t kRCUs = 256;            // compute units of the part; one bloc
 
 
 template <int DT, int CIN, int COUT, bool BUF>
-__global__ void __launch_bounds__(kRThreads, 3)
-k_spconv_direct_resident(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, const float* __restrict__ scale,
-                         const float* __restrict__ shift, int epilogue, const int32_t* __restrict__ nbr,
-                         const int32_t* __restrict__ d_n_out, int64_t capacity_out, int32_t n_in, int32_t* __restrict__ dev_flags,
-                         const uint16_t* __restrict__ zrow, uint16_t* __restrict__ out) {
+__device__ __forceinline__ void run_resident(uint32_t block, uint32_t n_blocks, const uint16_t* __restrict__ in, const u32x4* __restrict__ wp,
+                                             const float* __restrict__ scale, const float* __restrict__ shift, int epilogue,
+                                             const int32_t* __restrict__ nbr, const int32_t* __restrict__ d_n_out, int64_t capacity_out,
+                                             int32_t n_in, int32_t* __restrict__ dev_flags, const uint16_t* __restrict__ zrow,
+                                             uint16_t* __restrict__ out) {
   constexpr int KS = CIN / 32, NT = COUT / 16, MT = 2;
   constexpr int WT = KS * NT * 64;          // 16-byte weight pieces of a tap
   constexpr int NA = MT * KS;               // operand loads of a tap
@@ -72,9 +72,9 @@ k_spconv_direct_resident(const uint16_t* __restrict__ in, const u32x4* __restric
   if (n_out > capacity_out) n_out = capacity_out;
   // XCD-aware: workgroup b runs on XCD b % 8; XCD x takes a contiguous range of wave tiles.  Its blocks take the tiles one by one, so
   // that few tiles are spread over all of them.
-  const uint32_t blocks = gridDim.x / 8, blk = blockIdx.x / 8;
+  const uint32_t blocks = n_blocks / 8, blk = block / 8;
   const int64_t n_tiles = (n_out + kRRows - 1) / kRRows, chunk = (n_tiles + 7) / 8;
-  const int64_t tile0 = (int64_t)(blockIdx.x % 8) * chunk;
+  const int64_t tile0 = (int64_t)(block % 8) * chunk;
   const int64_t tiles = n_tiles - tile0 < chunk ? n_tiles - tile0 : chunk;
   if ((int64_t)blk >= tiles) return;        // uniform for the block
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -210,34 +210,39 @@ k_spconv_direct_resident(const uint16_t* __restrict__ in, const u32x4* __restric
   emc2_report_oob(oob, dev_flags);
 }
 
-template <int DT, int CIN, int COUT>
-void launch_resident(const void* d_in, const void* d_wp, const float* d_scale, const float* d_shift, int epilogue, const int32_t* d_nbr,
-                     const int32_t* d_n_out, int64_t capacity_out, int32_t n_in, int32_t* dev_flags, const void* d_zero_row, void* d_out,
-                     hipStream_t s) {
-  int64_t blocks = emc2_div_up(emc2_div_up(capacity_out, kRRows), 8) * 8;
-  if (blocks > kRCUs) blocks = kRCUs;
+template <int DT, int CIN, int COUT, bool BUF>
+__global__ void __launch_bounds__(kRThreads, 3) k_spconv_direct_resident(const emc2_conv_batch b) {
+  const int i = emc2_conv_of_block(b);
+  const emc2_conv_args& c = b.call[i];
+  run_resident<DT, CIN, COUT, BUF>(blockIdx.x - b.first[i], (i + 1 < b.n ? b.first[i + 1] : gridDim.x) - b.first[i],
+                                   (const uint16_t*)c.d_in, (const u32x4*)c.d_w, c.d_scale, c.d_shift, c.epilogue, c.d_nbr, c.d_n_out,
+                                   c.capacity_out, c.n_in, c.dev_flags, (const uint16_t*)c.d_zero_row, (uint16_t*)c.d_out);
+}
+
+template <int DT, int CIN, int COUT> void launch_resident(const emc2_conv_args* calls, int n, hipStream_t s) {
+  emc2_conv_batch b;
+  b.n = n;
+  uint32_t blocks = 0;
   // Offsets into the input are 32-bit, and the absent neighbour's, 2^32 less a row, must lie at or beyond its end.
-  const bool buf = ((int64_t)n_in + 1) * CIN * 2 <= ((int64_t)1 << 32);
-#define LAUNCH(BUF)                                                                                                               \
-  hipLaunchKernelGGL((k_spconv_direct_resident<DT, CIN, COUT, BUF>), dim3((unsigned)blocks), dim3(kRThreads), 0, s,               \
-                     (const uint16_t*)d_in, (const u32x4*)d_wp, d_scale, d_shift, epilogue, d_nbr, d_n_out, capacity_out, n_in,   \
-                     dev_flags, (const uint16_t*)d_zero_row, (uint16_t*)d_out)
-  if (buf) LAUNCH(true);
-  else LAUNCH(false);
-#undef LAUNCH
+  bool buf = true;
+  for (int i = 0; i < n; ++i) {
+    b.call[i] = calls[i];
+    b.first[i] = blocks;
+    const int64_t own = emc2_div_up(emc2_div_up(calls[i].capacity_out, kRRows), 8) * 8;
+    blocks += (uint32_t)(own < kRCUs ? own : kRCUs);
+    buf = buf && ((int64_t)calls[i].n_in + 1) * CIN * 2 <= ((int64_t)1 << 32);
+  }
+  if (buf) hipLaunchKernelGGL((k_spconv_direct_resident<DT, CIN, COUT, true>), dim3(blocks), dim3(kRThreads), 0, s, b);
+  else hipLaunchKernelGGL((k_spconv_direct_resident<DT, CIN, COUT, false>), dim3(blocks), dim3(kRThreads), 0, s, b);
 }
 
 }  // namespace
 
 bool emc2_spconv_resident_supported(int cin, int cout) { return (cin == 32 && cout == 64) || (cin == 64 && cout == 32); }
 
-void emc2_spconv_resident_launch(emc2_dtype dtype, const void* d_in, const void* d_wp, const float* d_scale, const float* d_shift,
-                                 int epilogue, const int32_t* d_nbr, const int32_t* d_n_out, int64_t capacity_out, int32_t n_in,
-                                 int32_t* dev_flags, int cin, const void* d_zero_row, void* d_out, hipStream_t stream) {
-#define CASE(D, CI, CO)                                                                                                      \
-  if (dtype == D && cin == CI)                                                                                               \
-    launch_resident<D, CI, CO>(d_in, d_wp, d_scale, d_shift, epilogue, d_nbr, d_n_out, capacity_out, n_in, dev_flags,        \
-                               d_zero_row, d_out, stream);
+void emc2_spconv_resident_launch(emc2_dtype dtype, int cin, const emc2_conv_args* calls, int n, hipStream_t stream) {
+#define CASE(D, CI, CO) \
+  if (dtype == D && cin == CI) launch_resident<D, CI, CO>(calls, n, stream);
   CASE(EMC2_F16, 32, 64) CASE(EMC2_BF16, 32, 64) CASE(EMC2_F16, 64, 32) CASE(EMC2_BF16, 64, 32)
 #undef CASE
 }
