@@ -31,7 +31,8 @@
 //
 // Leaving out: a block first reads all 27 map entries of its rows, keeps them in LDS, and runs only the (dz, dy) groups in which
 // some row has one.  A stride-2 map leaves 31-41 % of the (group, 128 rows) pairs empty, a transposed one 52-62 % (a line of
-// fine sites has one or two of three dy and dz).  Alone, us before / with it: transposed 64 -> 64 over 223 k rows 59 / 45.
+// fine sites has one or two of three dy and dz).  Alone, us before / with it: transposed 64 -> 64 over 223 k rows 59 / 45
+// (38 since the XCDs take the rows in runs).
 // Submanifold maps (a fifth of the groups empty) and 128 output channels gain less than the longer way to the first operands costs
 // (64 -> 128 over 67 k 50 / 52, 128 -> 128 in whole taps 103 / 113), so they keep the straight walk over the 27 taps.
 #include <hip/hip_bf16.h>
@@ -101,6 +102,7 @@ template <int CIN, int COUT, bool BUF> struct DirectCfg {
 // Levels of at most so many tiles, a block a CU, walk straight over the 27 taps: there the entries' way to the first operands shows,
 // with few neighbours to hide it: 64 -> 64 over 21 k rows 12.6 / 14; at 40 k, beyond the line, straight / leaving out 18.8 / 14.9.
 constexpr int64_t kStraightTiles = 256;
+constexpr int kRun = 4;                  // tiles of a run: 512 rows
 
 // Rows of the input through a buffer descriptor: 32-bit offsets, and the hardware returns zero for an offset at or beyond
 // the end without fetching anything, so an absent neighbour costs neither an address select nor a cache access.  64-beam
@@ -142,16 +144,12 @@ k_spconv_direct(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, c
       __builtin_amdgcn_make_buffer_rsrc((void*)const_cast<uint16_t*>(in), 0, BUF ? (int)((uint32_t)n_in * (CIN * 2)) : 0, 0x00020000);
   int64_t n_out = *d_n_out;
   if (n_out > capacity_out) n_out = capacity_out;
-  // XCD-aware tile assignment: workgroup b runs on XCD b % 8; XCD x takes a contiguous range of tiles
   const int64_t n_tiles = (n_out + kDWaves * R - 1) / (kDWaves * R);
-  const int64_t chunk = (n_tiles + 7) / 8;
-  const int64_t xcd_tile0 = (int64_t)(blockIdx.x % 8) * chunk;
-  const int64_t xcd_tiles = n_tiles - xcd_tile0 < chunk ? n_tiles - xcd_tile0 : chunk;
-
+  const int64_t xcd_tiles = emc2_xcd_tiles<kRun>(blockIdx.x % 8, n_tiles);
   int64_t slot = blockIdx.x / 8;
   if (slot >= xcd_tiles) return;   // uniform for the block
   do {
-  const int64_t tile_id = xcd_tile0 + slot;
+  const int64_t tile_id = emc2_xcd_tile<kRun>(blockIdx.x % 8, slot);
   // Opaque copies: the compiler would otherwise keep the addresses of all 27 taps alive from tile to tile and spill up to
   // 90 registers for it.
   int tid = threadIdx.x;
@@ -390,7 +388,7 @@ void launch_direct(const void* d_in, const void* d_wp, const float* d_scale, con
   // in one for 573 k.  A loop over tiles costs the kernel up to a tenth in registers and instruction order (128 -> 128: 110
   // against 127 us), so it is used only where the grid would be several times kDGrid; the grid is then kDGrid blocks
   // (32 -> 64 over 573 k rows 97 -> 80 us, over 852 k 119 -> 109).
-  const int64_t blocks = emc2_div_up(emc2_div_up(capacity_out, rows_per_block), 8) * 8;
+  const int64_t blocks = emc2_div_up(emc2_div_up(capacity_out, rows_per_block), 8 * kRun) * (8 * kRun);
 #define LAUNCH(LOOP, BUF, BLOCKS)                                                                                           \
   hipLaunchKernelGGL((k_spconv_direct<DT, CIN, COUT, LOOP, BUF>), dim3((unsigned)(BLOCKS)), dim3(kDThreads), 0, s,           \
                      (const uint16_t*)d_in, (const u32x4*)d_wp, d_scale, d_shift, epilogue, d_nbr, d_n_out, capacity_out,     \

@@ -55,6 +55,7 @@ template <> struct MmaN<EMC2_BF16> {
 };
 
 constexpr int kNRows = 32;                // output rows per wave
+constexpr int kNRun = 32;                 // tiles of a run: 1024 rows
 constexpr int kNCout = 32;
 constexpr int kNPitch = kNCout / 8 + 1;   // epilogue tile row pitch in 16-byte pieces
 
@@ -80,11 +81,8 @@ __device__ __forceinline__ void run_narrow(uint32_t block, uint32_t n_blocks, co
       __builtin_amdgcn_make_buffer_rsrc((void*)const_cast<uint16_t*>(in), 0, BUF ? (int)((uint32_t)n_in * (CIN * 2)) : 0, 0x00020000);
   int64_t n_out = *d_n_out;
   if (n_out > capacity_out) n_out = capacity_out;
-  // XCD-aware: workgroup b runs on XCD b % 8; XCD x takes a contiguous range of wave tiles
   const int64_t n_tiles = (n_out + kNRows - 1) / kNRows;
-  const int64_t chunk = (n_tiles + 7) / 8;
-  const int64_t tile0 = (int64_t)(block % 8) * chunk;
-  const int64_t tiles = n_tiles - tile0 < chunk ? n_tiles - tile0 : chunk;
+  const int64_t tiles = emc2_xcd_tiles<kNRun>(block % 8, n_tiles);
   if ((int64_t)(block / 8) * C::WAVES >= tiles) return;   // uniform for the block
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int m = lane & 31, h = lane >> 5;                      // entries: row and half
@@ -97,7 +95,7 @@ __device__ __forceinline__ void run_narrow(uint32_t block, uint32_t n_blocks, co
   int32_t e[14];
   // (past the last tile: the last one's again)
   const auto entries = [&](int64_t at) {
-    const int64_t row0 = (tile0 + (at < tiles ? at : tiles - 1)) * kNRows;
+    const int64_t row0 = emc2_xcd_tile<kNRun>(block % 8, at < tiles ? at : tiles - 1) * kNRows;
     const int32_t own = row0 + m < n_out ? m : 0;
     if constexpr (BUF) {   // one address in scalar registers and a 32-bit offset per half
       const uint32_t even = 4u * (uint32_t)own, off = even + (h ? 4u * (uint32_t)capacity_out : 0u);
@@ -123,7 +121,7 @@ __device__ __forceinline__ void run_narrow(uint32_t block, uint32_t n_blocks, co
   __syncthreads();
 
   for (; slot < tiles; slot += step) {
-    const int64_t row0 = (tile0 + slot) * kNRows;
+    const int64_t row0 = emc2_xcd_tile<kNRun>(block % 8, slot) * kNRows;
     const int32_t dead = row0 + m < n_out ? 0 : -1;
     int32_t j[28][LPT];
     u32x4 a[D][LPT];

@@ -53,6 +53,7 @@ template <> struct MmaR<EMC2_BF16> {
 constexpr int kRWaves = 12;               // three a SIMD, what the LDS beside the weights leaves room for
 constexpr int kRThreads = kRWaves * 64;
 constexpr int kRRows = 32;                // output rows of a wave
+constexpr int kRRun = 16;                 // tiles of a run: 512 rows
 constexpr int64_t kRCUs = 256;            // compute units of the part; one block fits each
 
 
@@ -70,12 +71,9 @@ __device__ __forceinline__ void run_resident(uint32_t block, uint32_t n_blocks, 
   __shared__ uint32_t taken_s;              // tiles of the block that its waves have taken
   int64_t n_out = *d_n_out;
   if (n_out > capacity_out) n_out = capacity_out;
-  // XCD-aware: workgroup b runs on XCD b % 8; XCD x takes a contiguous range of wave tiles.  Its blocks take the tiles one by one, so
-  // that few tiles are spread over all of them.
+  // The blocks of an XCD take its tiles one by one, so that few tiles are spread over all of them.
   const uint32_t blocks = n_blocks / 8, blk = block / 8;
-  const int64_t n_tiles = (n_out + kRRows - 1) / kRRows, chunk = (n_tiles + 7) / 8;
-  const int64_t tile0 = (int64_t)(block % 8) * chunk;
-  const int64_t tiles = n_tiles - tile0 < chunk ? n_tiles - tile0 : chunk;
+  const int64_t n_tiles = (n_out + kRRows - 1) / kRRows, tiles = emc2_xcd_tiles<kRRun>(block % 8, n_tiles);
   if ((int64_t)blk >= tiles) return;        // uniform for the block
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int m = lane & 15, q = lane >> 4, half = lane >> 5, row = lane & 31;
@@ -94,7 +92,7 @@ __device__ __forceinline__ void run_resident(uint32_t block, uint32_t n_blocks, 
   // half h of the wave holds the entries of taps 2i + h of the 32 rows (past the last tile: the last one's again)
   int32_t e[14];
   const auto entries = [&](int64_t at) {
-    const int64_t r0 = (tile0 + (at < tiles ? at : tiles - 1)) * kRRows;
+    const int64_t r0 = emc2_xcd_tile<kRRun>(block % 8, at < tiles ? at : tiles - 1) * kRRows;
     const int32_t* p = nbr + r0 + (r0 + row < n_out ? row : 0);
 #pragma unroll
     for (int i = 0; i < 14; ++i) e[i] = (p + (int64_t)(2 * i) * capacity_out)[i < 13 && half ? capacity_out : 0];
@@ -105,7 +103,7 @@ __device__ __forceinline__ void run_resident(uint32_t block, uint32_t n_blocks, 
   int32_t* ent = ent_s[wave];
 
   for (; slot < tiles; slot = next_slot) {
-    const int64_t row0 = (tile0 + slot) * kRRows;
+    const int64_t row0 = emc2_xcd_tile<kRRun>(block % 8, slot) * kRRows;
     const int32_t dead = row0 + row < n_out ? 0 : -1;
     // the entries as rows the kernel may read (absent and beyond the input: -1), [tap][row], and the groups to run
     uint32_t groups = 0;
