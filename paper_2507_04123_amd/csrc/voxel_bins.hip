@@ -160,7 +160,7 @@ __global__ void __launch_bounds__(256) k_bin_distinct(BinState* __restrict__ sta
                                                       const uint16_t* __restrict__ cells, uint32_t* __restrict__ voxels,
                                                       uint32_t* __restrict__ items) {
   __shared__ uint4 bits_s[4][kWords<SHIFT> / 4];
-  __shared__ uint32_t fresh_s;
+  __shared__ uint32_t fresh_s, at_s;                     // a larger bin's voxels; where its items begin (waves may still read the first)
   const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   uint32_t fresh = 0;
   if (blockIdx.x < kLargeBlocks) {
@@ -182,10 +182,10 @@ __global__ void __launch_bounds__(256) k_bin_distinct(BinState* __restrict__ sta
       const uint32_t v = fresh_s, n = (v + kItemVoxels - 1) / kItemVoxels;       // at most 512
       if (threadIdx.x == 0) {
         voxels[bin] = v;
-        fresh_s = atomicAdd(&state->items, n);
+        at_s = atomicAdd(&state->items, n);
       }
       __syncthreads();
-      const uint32_t at = fresh_s;
+      const uint32_t at = at_s;
       for (uint32_t i = threadIdx.x; i < n; i += 256) items[at + i] = bin << 9 | i;
       __syncthreads();
     }

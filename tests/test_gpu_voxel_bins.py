@@ -91,6 +91,29 @@ def test_points_of_the_fullest_bin(fullest, heavy):
     ctx.close()
 
 
+@pytest.mark.parametrize("layers,shift", [(16, 14), (40, 16)])
+def test_more_large_bins_than_blocks(layers, shift):
+    """More bins of over 3 072 points than the 512 blocks that count their voxels, and more shares of 128 voxels than the 1 024 blocks
+    that take them: each block takes a second one, of another number of voxels.  Bins of a quarter of a tile (16 layers: 4 096 tiles,
+    over 200 points each) and of a whole one (40 layers: 10 240, fewer)."""
+    grid, large, n = (4096, 4096, layers), 600, 1950000
+    rng = np.random.RandomState(shift)
+    n_bins = 4096 * 4096 * layers >> shift
+    assert n >= 200 * 256 * layers if shift == 14 else n < 200 * 256 * layers
+    bins = rng.permutation(n_bins)[:large].astype(np.int64)
+    points = 3073 + rng.randint(0, 80, large)
+    # cells that its points are drawn from: a share's 128 voxels, one less and one more among them, and all of the bin's
+    span = np.array([16, 127, 128, 129, 1000, 1 << 13, 1 << shift])[np.arange(large) % 7]
+    key = np.concatenate([np.repeat(bins << shift, points) + rng.randint(0, 1 << 30, points.sum()) % np.repeat(span, points),
+                          rng.randint(0, n_bins << shift, n - points.sum())])
+    key = key[rng.permutation(n)]
+    p = np.empty((n, 4), np.float32)
+    p[:, 0], p[:, 1], p[:, 2], p[:, 3] = key % 4096 + 0.5, key // 4096 % 4096 + 0.25, key // 4096 ** 2 + 0.75, rng.uniform(0, 1, n)
+    ctx = B.Context(n, n, cells_of(grid, 1), n_slots=1)
+    _check(ctx, p, np.zeros(n, np.int32), VoxelSpec((0.0, 0.0, 0.0), (1.0, 1.0, 1.0), grid), n)
+    ctx.close()
+
+
 def test_points_of_all_frames_mixed_and_capacity():
     """Bins of a tile; frames in any order: a block's points lie in more bins than it counts in LDS at a time.  Then a capacity below the voxels, and a cloud of
     one point less than the limit, which takes the pass over single points, into the same slot."""
