@@ -6,6 +6,7 @@
 #include <hip/hip_fp16.h>
 
 #include "common.h"
+#include "conv_order.h"
 #include "spconv_mfma.h"
 
 namespace {
@@ -499,29 +500,6 @@ extern "C" emc2_status emc2_spconv(emc2_ctx* ctx, emc2_dtype dtype, const void* 
   return issue_convs(&one, 1, (hipStream_t)stream);
 }
 
-// What a call reads and writes, in bytes.
-struct Touched {
-  uintptr_t lo[7], hi[7];   // [0]: the output; the input, weights, scale, shift, map and row count
-};
-static Touched touched_by(const emc2_conv_call& c) {
-  const int64_t esz = c.dtype == EMC2_F32 ? 4 : 2;
-  const void* at[7] = {c.d_out, c.d_in, c.d_w, c.d_scale, c.d_shift, c.d_nbr, c.d_n_out};
-  const int64_t bytes[7] = {c.capacity_out * c.cout * esz, c.n_in_rows * c.cin * esz, 27 * (int64_t)c.cin * c.cout * esz,
-                            c.d_scale ? 4 * (int64_t)c.cout : 0, c.d_shift ? 4 * (int64_t)c.cout : 0, 27 * c.capacity_out * 4, 4};
-  Touched t;
-  for (int i = 0; i < 7; ++i) {
-    t.lo[i] = (uintptr_t)at[i];
-    t.hi[i] = t.lo[i] + (uintptr_t)bytes[i];
-  }
-  return t;
-}
-// One writes what the other reads or writes: their order matters.
-static bool ordered(const Touched& a, const Touched& b) {
-  for (int i = 0; i < 7; ++i)
-    if ((a.lo[0] < b.hi[i] && b.lo[i] < a.hi[0]) || (b.lo[0] < a.hi[i] && a.lo[i] < b.hi[0])) return true;
-  return false;
-}
-
 static bool in_launch(const emc2_conv_call* const* batch, int m, const emc2_conv_call* c) {
   for (int i = 0; i < m; ++i)
     if (batch[i] == c) return true;
@@ -543,9 +521,9 @@ extern "C" emc2_status emc2_spconv_list(const emc2_conv_call* calls, int32_t n, 
   int32_t end = 0;                     // the first refused call: nothing behind it is issued
   while (end < n && (refused = check_conv(calls[end])) == EMC2_OK) ++end;
   bool done[kListPlanned] = {};
-  Touched t[kListPlanned];
+  emc2_touched t[kListPlanned];
   const bool planned = end <= kListPlanned;
-  for (int32_t i = 0; planned && i < end; ++i) t[i] = touched_by(calls[i]);
+  for (int32_t i = 0; planned && i < end; ++i) t[i] = emc2_touched_by(calls[i]);
   const emc2_conv_call* at = nullptr;
   emc2_status st = EMC2_OK;
   for (int32_t i = 0; st == EMC2_OK && i < end; ++i) {
@@ -559,7 +537,7 @@ extern "C" emc2_status emc2_spconv_list(const emc2_conv_call* calls, int32_t n, 
         const emc2_conv_call& d = calls[j];
         if (done[j] || d.dtype != c.dtype || d.cin != c.cin || d.cout != c.cout || d.w_layout != c.w_layout) continue;
         bool waits = false;             // for an earlier call still to be issued, or for one of this launch
-        for (int32_t k = i; !waits && k < j; ++k) waits = (!done[k] || k == i || in_launch(batch, m, calls + k)) && ordered(t[k], t[j]);
+        for (int32_t k = i; !waits && k < j; ++k) waits = (!done[k] || k == i || in_launch(batch, m, calls + k)) && emc2_ordered(t[k], t[j]);
         if (waits) continue;
         batch[m++] = &d;
         done[j] = true;
