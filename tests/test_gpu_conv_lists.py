@@ -4,7 +4,7 @@ import pytest
 import torch
 
 from paper_2507_04123_amd import binding as B
-from paper_2507_04123_amd.configs import BF16, EPI_AFFINE_RELU, F16, F32
+from paper_2507_04123_amd.configs import BF16, EPI_AFFINE, EPI_AFFINE_RELU, F16, F32
 from test_gpu_stacks import _kernels_in
 
 pytestmark = pytest.mark.gpu
@@ -14,6 +14,7 @@ class _Pool:
     def __init__(self, seed):
         self.g = torch.Generator(device="cuda").manual_seed(seed)
         self.ctx, self.keep = [B.Context(16, 16, 64, n_slots=1) for _ in range(2)], []
+        self.maps, self.outs = [], []     # places of the calls' maps in `keep`; the calls' outputs
 
     def rows(self, n, ch, dt):
         td = {F16: torch.float16, BF16: torch.bfloat16, F32: torch.float32}[dt]
@@ -33,6 +34,8 @@ class _Pool:
             w = wp
         sc, sh = torch.rand(cout, generator=self.g, device="cuda"), torch.randn(cout, generator=self.g, device="cuda")
         nn = torch.tensor([n], dtype=torch.int32, device="cuda")
+        self.maps.append(len(self.keep))
+        self.outs.append(y)
         self.keep += [nbr, w, sc, sh, nn]
         c = B.ConvCallC()
         c.ctx, c.d_in, c.d_w, c.d_scale, c.d_shift = self.ctx[ctx].h, x.data_ptr(), w.data_ptr(), sc.data_ptr(), sh.data_ptr()
@@ -85,11 +88,48 @@ def test_what_waits_stays_in_order():
     calls = [p.call(a, b, 16, 16, F16), p.call(a, c, 16, 16, F16), p.call(c, a, 16, 16, F16), p.call(b, c, 16, 16, F16),
              p.call(a, d, 16, 16, F16), p.call(d, tail, 16, 16, F16), p.call(b, p.rows(900, 16, F16), 16, 16, F16)]
     _both(p, calls, [a, b, c, d])
-    # weights, map and row count that an earlier call of the list writes
-    x, y, z = p.rows(600, 4, F32), p.rows(600, 16, F32), p.rows(600, 16, F32)
-    first, second = p.call(x, y, 4, 16, F32), p.call(x, z, 4, 16, F32)
-    second.d_w = y.data_ptr()
+
+
+# (fp32 calls never share a launch; 16-bit ones of one shape do, by one of three kernels)
+@pytest.mark.parametrize("cin,cout", [(4, 16), (16, 16), (16, 32), (32, 32), (32, 64), (64, 32)])
+@pytest.mark.parametrize("what", ["d_in", "no limit", "d_w", "d_scale", "d_shift", "d_nbr", "d_n_out", "d_out", None])
+def test_buffers_that_an_earlier_call_of_the_list_writes(cin, cout, what):
+    """Two calls of one kernel, the second of which reads the first one's output as `what`, wait for each other: two launches, where
+    calls that share nothing take one.  The values the second finds there before the first is done are valid and give other results."""
+    p = _Pool(cin + cout)
+    x, z = p.rows(300, cin, F16), p.rows(40, cout, F16)
+    y = p.rows(4096, cout, F16)                # room for a map of 40 rows and for every shape's weights
+    first, second = p.call(x, y, cin, cout, F16), p.call(x, z, cin, cout, F16)
+    if what == "d_nbr":                        # a map before; afterwards -1.0 everywhere, whose bits are a negative entry: no neighbour
+        sc, sh = torch.zeros(cout, device="cuda"), torch.full((cout,), -1.0, device="cuda")
+        p.keep += [sc, sh]
+        first.d_scale, first.d_shift, first.epilogue = sc.data_ptr(), sh.data_ptr(), EPI_AFFINE
+        y.view(torch.int32).view(-1)[: 27 * 40] = p.keep[p.maps[1]].view(-1)
+    if what == "d_n_out":                      # five rows before; afterwards a number beyond the capacity: all of them
+        sc, sh = torch.zeros(cout, device="cuda"), torch.ones(cout, device="cuda")
+        p.keep += [sc, sh]
+        first.d_scale, first.d_shift = sc.data_ptr(), sh.data_ptr()
+        y.view(torch.int32)[0, 0] = 5
+    if what == "no limit":
+        second.d_in, second.n_in_rows = y.data_ptr(), 1 << 62
+    elif what == "d_out":                      # its rows are some of the first one's
+        second.d_out = y[1000:].data_ptr()
+    elif what is not None:
+        setattr(second, what, y.data_ptr())
+    arr = (B.ConvCallC * 2)(first, second)
+    assert _kernels_in(lambda: B.spconv_list(arr, 2)) == (1 if what is None else 2)
     _both(p, [first, second], [y, z])
+
+
+def test_list_of_more_calls_than_are_planned():
+    """Over 64 calls: one by one, in the order of the list."""
+    p = _Pool(66)
+    bufs = [p.rows(200 + i, 16, F16) for i in range(4)]
+    calls = [p.call(bufs[i % 4], bufs[(i + 1) % 4], 16, 16, F16, ctx=i % 2) for i in range(33)]
+    calls += [p.call(bufs[i % 3], p.rows(100, 16, F16), 16, 16, F16) for i in range(33)]
+    arr = _both(p, calls, bufs + p.outs[-33:])
+    assert _kernels_in(lambda: B.spconv_list(arr, len(calls))) == 66
+    assert _kernels_in(lambda: B.spconv_list((B.ConvCallC * 33)(*calls[33:]), 33)) == 9
 
 
 def test_refused_call_in_a_list():
