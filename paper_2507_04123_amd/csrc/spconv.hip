@@ -370,7 +370,7 @@ extern "C" const char* emc2_spconv_kernel(emc2_dtype dtype, int32_t cin, int32_t
   if (dtype != EMC2_F32 && dtype != EMC2_F16 && dtype != EMC2_BF16) return nullptr;
   if (emc2_spconv_uses_mfma(dtype, cin, cout)) {
     if (emc2_spconv_narrow_supported(cin, cout)) return "k_spconv_narrow";
-    if (emc2_spconv_resident_supported(cin, cout)) return "k_spconv_direct";   // (its form with resident weights)
+    if (emc2_spconv_resident_supported(cin, cout)) return "k_spconv_direct_resident";
     if (!emc2_spconv_direct_supported(cin, cout)) return "k_spconv_mfma";
     return (map_hint == EMC2_CONV_SUBM && emc2_spconv_span_supported(cin, cout)) ? "k_spconv_span" : "k_spconv_direct";
   }

@@ -228,22 +228,36 @@ def test_span_conv_rounds_taps_outside_an_interval(n):
 
 
 # Blocks of 128 rows.  A capacity of up to 4 * 8 192 blocks gets a block for each tile, a row more 8 192 blocks that loop over
-# the tiles there are: one tile for all but the last, one more than blocks, a second tile for half of them.  64 channels of
+# the tiles there are: one tile for all but the last, one more than blocks, a second tile for half of those of every XCD.  64 channels of
 # 2^25 rows and more (128 of 2^24) are read by address instead of through a descriptor.  Levels of this size leave groups out
 # but for submanifold maps and 128 output channels, which walk straight over the taps.
-@pytest.mark.parametrize("cin,cout,rows,n,loop,hint", [
-    (64, 32, 128, 8192 * 128 - 129, True, B.MAP_ANY), (32, 64, 128, 8192 * 128 + 1, True, B.MAP_ANY),
-    (32, 64, 128, 8192 * 128 * 3 // 2 + 77, True, B.MAP_ANY), (64, 32, 128, 8192 * 128 * 3 // 2 + 77, True, B.MAP_ANY),
-    (32, 64, 128, 8192 * 128 * 3 // 2 + 77, False, B.MAP_ANY), (64, 32, 128, 8192 * 128 * 3 // 2 + 77, True, B.SUBM),
-    (32, 64, 128, 8192 * 128 + 1, True, B.SUBM), (64, 32, 128, 300, True, B.SUBM),
-    (64, 64, 128, 8192 * 128 + 77, True, B.STRIDED), (64, 128, 128, 8192 * 128 + 77, True, B.STRIDED),
-    (128, 128, 128, 8192 * 128 + 77, True, B.MAP_ANY)])
-def test_direct_conv_grid_limit(cin, cout, rows, n, loop, hint):
+@pytest.mark.parametrize("cin,cout,n,loop,hint", [
+    (64, 64, 8192 * 128 - 129, True, B.MAP_ANY), (64, 64, 8192 * 128 + 1, True, B.MAP_ANY), (64, 64, 8192 * 128 + 77, True, B.STRIDED),
+    (64, 64, 8192 * 128 * 3 // 2 + 77, True, B.MAP_ANY), (64, 64, 8192 * 128 * 3 // 2 + 77, False, B.MAP_ANY),
+    (64, 128, 300, True, B.SUBM), (64, 128, 8192 * 128 - 129, True, B.MAP_ANY), (64, 128, 8192 * 128 + 1, True, B.SUBM),
+    (64, 128, 8192 * 128 + 77, True, B.STRIDED), (64, 128, 8192 * 128 * 3 // 2 + 77, True, B.SUBM),
+    (64, 128, 8192 * 128 * 3 // 2 + 77, False, B.MAP_ANY),
+    (128, 128, 8192 * 128 + 77, True, B.MAP_ANY), (128, 128, 8192 * 128 * 3 // 2 + 77, True, B.MAP_ANY)])
+def test_direct_conv_grid_limit(cin, cout, n, loop, hint):
     assert _kernel(cin, cout, hint) == "k_spconv_direct"
-    cap = 4 * 8192 * rows + (1 if loop else 0)
+    cap = 4 * 8192 * 128 + (1 if loop else 0)
     _check_conv(n, cin, cout, hint, False, cap=cap)
-    if cin >= 64 and loop:
+    if loop:
         _check_conv(n, cin, cout, hint, False, cap=cap, rows_in=(1 << 25) + 3)
+
+
+# Tiles of 32 rows to 256 blocks of 12 waves, a block in a CU, whose waves take the block's tiles one by one: a tile, fewer tiles than
+# blocks, as many, some of a block's waves with a tile, a tile less and more than all waves, many a wave; a capacity of the rows and of
+# many times as many.  32 channels of 2^26 rows and more (64 of 2^25) are read by address.
+@pytest.mark.parametrize("cin,cout", [(32, 64), (64, 32)])
+@pytest.mark.parametrize("n", [1, 300, 255 * 32 + 1, 256 * 32 + 1, 256 * 5 * 32 + 1, 256 * 12 * 32 - 33, 256 * 12 * 32 + 1, 8192 * 128 - 129,
+                               8192 * 128 * 3 // 2 + 77])
+def test_resident_conv_grid_limit(cin, cout, n):
+    for hint in (B.SUBM, B.STRIDED, B.MAP_ANY):
+        assert _kernel(cin, cout, hint) == "k_spconv_direct_resident"
+    _check_conv(n, cin, cout, B.MAP_ANY, False)
+    _check_conv(n, cin, cout, B.SUBM, False, cap=4 * 8192 * 128 + 1)
+    _check_conv(n, cin, cout, B.STRIDED, False, cap=n + 5, rows_in=((1 << 31) // cin) + 3)
 
 
 # 32 -> 32 in a capacity of many times its grid, which loops over the tiles of 32 rows a wave there are
@@ -260,9 +274,9 @@ def _kernel(cin, cout, hint):
     return name
 
 
-# Blocks of 128 rows that have entries in no group, in one, in every one, and whose waves differ; the last block ragged.  Up to
-# 256 blocks (512 at 32 -> 64) walk straight over the taps, more of them leave groups out, in a loop over the tiles where the
-# capacity is large.
+# Blocks of 128 rows that have entries in no group, in one, in every one, and whose waves differ; the last block ragged.  At 64 -> 64 up to
+# 256 blocks walk straight over the taps, more of them leave groups out, in a loop over the tiles where the capacity is large; at
+# 32 -> 64 and 64 -> 32 each wave leaves out the groups its own rows do not have.
 @pytest.mark.parametrize("cin,cout", [(32, 64), (64, 32), (64, 64)])
 @pytest.mark.parametrize("n,cap", [(1, 1), (128, 128), (129, 129), (1000, 1000), (33000, 33000), (66000, 66000), (8192 * 128 + 300, 4 * 8192 * 128 + 1)])
 def test_direct_conv_groups_without_entries(cin, cout, n, cap):
@@ -298,8 +312,8 @@ def test_direct_conv_groups_without_entries(cin, cout, n, cap):
     ctx.close()
 
 
-# Levels of up to 256 blocks (512 at 32 -> 64) walk straight over the taps, larger ones leave out the groups no row of a block
-# has, submanifold ones never: the same bits on both sides of the line
+# 64 -> 64: levels of up to 256 blocks walk straight over the taps, larger ones leave out the groups no row of a block has, submanifold
+# ones never: the same bits on both sides of the line.  (32 -> 64 and 64 -> 32 take one way at all sizes and hints.)
 @pytest.mark.parametrize("cin,cout,line", [(32, 64, 512 * 128), (64, 32, 256 * 128), (64, 64, 256 * 128)])
 @pytest.mark.parametrize("beyond", [0, 1])
 def test_direct_conv_straight_and_leaving_out(cin, cout, line, beyond):
