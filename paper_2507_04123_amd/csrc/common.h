@@ -60,22 +60,6 @@ __device__ __forceinline__ void emc2_report_oob(unsigned long long oob, int32_t*
   if (oob != 0ull && (threadIdx.x & 63) == 0) atomicOr(flags, EMC2_DEVFLAG_MAP);
 }
 
-// Tiles of consecutive rows by XCD.  Workgroup b runs on XCD b % 8, and each XCD has its own L2, so neighbouring tiles, which gather
-// largely the same rows, belong on one; but the neighbours a row has grow along the rows (z slowest: the ground's layers are dense,
-// those far above and below it are not), and with an eighth of the rows each the XCD of the densest sets the time.  So the XCDs
-// take runs of RUN consecutive tiles in turn, of 512 or 1024 rows: us, an eighth each / in runs: stride-2 64 -> 64 over 66 k rows
-// 37 / 29.5, transposed over 223 k 44 / 38, 32 -> 32 over 304 k 66 / 59, stride-2 32 -> 64 over 223 k 40 / 35; runs of 256 to 2048 rows
-// differ by 2 %.  (Not in k_spconv_span, whose tiles cost much the same and share planes: rounds of tiles dealt out, 60 / 65 over
-// 248 k rows, 124 / 117 over 500 k; nor in k_spconv_i8: 111.1 / 111.7 a pass.)
-template <int RUN> __device__ __forceinline__ int64_t emc2_xcd_tile(uint32_t xcd, int64_t slot) {   // the slot-th of the XCD's tiles
-  const uint32_t at = (uint32_t)slot;        // row numbers are 32-bit
-  return (at / RUN * 8 + xcd) * RUN + at % RUN;
-}
-template <int RUN> __device__ __forceinline__ int64_t emc2_xcd_tiles(uint32_t xcd, int64_t n_tiles) {   // how many it has
-  const int64_t rest = n_tiles % (8 * RUN) - (int64_t)xcd * RUN;
-  return n_tiles / (8 * RUN) * RUN + (rest < 0 ? 0 : rest < RUN ? rest : RUN);
-}
-
 struct SlotMeta {
   int32_t grid[3];
   int32_t n_batch;

@@ -40,6 +40,7 @@
 
 #include "common.h"
 #include "spconv_mfma.h"
+#include "xcd_tiles.h"
 
 namespace {
 
@@ -149,12 +150,12 @@ k_spconv_direct(const uint16_t* __restrict__ in, const u32x4* __restrict__ wp, c
   int64_t slot = blockIdx.x / 8;
   if (slot >= xcd_tiles) return;   // uniform for the block
   do {
-  const int64_t tile_id = emc2_xcd_tile<kRun>(blockIdx.x % 8, slot);
+  const int64_t tile_id = emc2_xcd_tile<kRun>(blockIdx.x % 8, slot, n_tiles);
   // Opaque copies: the compiler would otherwise keep the addresses of all 27 taps alive from tile to tile and spill up to
   // 90 registers for it.
   int tid = threadIdx.x;
   int64_t nbr_pitch = capacity_out;
-  if constexpr (LOOP) asm volatile("" : "+v"(tid), "+s"(nbr_pitch), "+s"(wp), "+s"(nbr));
+  if constexpr (LOOP) asm volatile("" : "+v"(tid), "+s"(nbr_pitch), "+s"(wp), "+s"(nbr), "+s"(zrow));
 
   const int lane = tid & 63;
   const int wave = tid >> 6;
@@ -388,7 +389,7 @@ void launch_direct(const void* d_in, const void* d_wp, const float* d_scale, con
   // in one for 573 k.  A loop over tiles costs the kernel up to a tenth in registers and instruction order (128 -> 128: 110
   // against 127 us), so it is used only where the grid would be several times kDGrid; the grid is then kDGrid blocks
   // (32 -> 64 over 573 k rows 97 -> 80 us, over 852 k 119 -> 109).
-  const int64_t blocks = emc2_div_up(emc2_div_up(capacity_out, rows_per_block), 8 * kRun) * (8 * kRun);
+  const int64_t blocks = emc2_div_up(emc2_div_up(capacity_out, rows_per_block), 8) * 8;
 #define LAUNCH(LOOP, BUF, BLOCKS)                                                                                           \
   hipLaunchKernelGGL((k_spconv_direct<DT, CIN, COUT, LOOP, BUF>), dim3((unsigned)(BLOCKS)), dim3(kDThreads), 0, s,           \
                      (const uint16_t*)d_in, (const u32x4*)d_wp, d_scale, d_shift, epilogue, d_nbr, d_n_out, capacity_out,     \

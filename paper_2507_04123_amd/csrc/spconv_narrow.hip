@@ -24,6 +24,7 @@
 
 #include "common.h"
 #include "spconv_mfma.h"
+#include "xcd_tiles.h"
 
 namespace {
 
@@ -95,7 +96,7 @@ __device__ __forceinline__ void run_narrow(uint32_t block, uint32_t n_blocks, co
   int32_t e[14];
   // (past the last tile: the last one's again)
   const auto entries = [&](int64_t at) {
-    const int64_t row0 = emc2_xcd_tile<kNRun>(block % 8, at < tiles ? at : tiles - 1) * kNRows;
+    const int64_t row0 = emc2_xcd_tile<kNRun>(block % 8, at < tiles ? at : tiles - 1, n_tiles) * kNRows;
     const int32_t own = row0 + m < n_out ? m : 0;
     if constexpr (BUF) {   // one address in scalar registers and a 32-bit offset per half
       const uint32_t even = 4u * (uint32_t)own, off = even + (h ? 4u * (uint32_t)capacity_out : 0u);
@@ -121,7 +122,7 @@ __device__ __forceinline__ void run_narrow(uint32_t block, uint32_t n_blocks, co
   __syncthreads();
 
   for (; slot < tiles; slot += step) {
-    const int64_t row0 = emc2_xcd_tile<kNRun>(block % 8, slot) * kNRows;
+    const int64_t row0 = emc2_xcd_tile<kNRun>(block % 8, slot, n_tiles) * kNRows;
     const int32_t dead = row0 + m < n_out ? 0 : -1;
     int32_t j[28][LPT];
     u32x4 a[D][LPT];

@@ -20,6 +20,7 @@
 
 #include "common.h"
 #include "spconv_mfma.h"
+#include "xcd_tiles.h"
 
 namespace {
 
@@ -92,7 +93,7 @@ __device__ __forceinline__ void run_resident(uint32_t block, uint32_t n_blocks, 
   // half h of the wave holds the entries of taps 2i + h of the 32 rows (past the last tile: the last one's again)
   int32_t e[14];
   const auto entries = [&](int64_t at) {
-    const int64_t r0 = emc2_xcd_tile<kRRun>(block % 8, at < tiles ? at : tiles - 1) * kRRows;
+    const int64_t r0 = emc2_xcd_tile<kRRun>(block % 8, at < tiles ? at : tiles - 1, n_tiles) * kRRows;
     const int32_t* p = nbr + r0 + (r0 + row < n_out ? row : 0);
 #pragma unroll
     for (int i = 0; i < 14; ++i) e[i] = (p + (int64_t)(2 * i) * capacity_out)[i < 13 && half ? capacity_out : 0];
@@ -103,7 +104,7 @@ __device__ __forceinline__ void run_resident(uint32_t block, uint32_t n_blocks, 
   int32_t* ent = ent_s[wave];
 
   for (; slot < tiles; slot = next_slot) {
-    const int64_t row0 = emc2_xcd_tile<kRRun>(block % 8, slot) * kRRows;
+    const int64_t row0 = emc2_xcd_tile<kRRun>(block % 8, slot, n_tiles) * kRRows;
     const int32_t dead = row0 + row < n_out ? 0 : -1;
     // the entries as rows the kernel may read (absent and beyond the input: -1), [tap][row], and the groups to run
     uint32_t groups = 0;
