@@ -296,15 +296,16 @@ __device__ __forceinline__ void run_rows(uint32_t block, const uint16_t* __restr
   }
 }
 
-template <int DT, int CIN, int COUT> __global__ void __launch_bounds__(256, 4) k_spconv_rows(const emc2_conv_batch b) {
-  const int i = emc2_conv_of_block(b);
-  const emc2_conv_args& c = b.call[i];
-  run_rows<DT, CIN, COUT>(blockIdx.x - b.first[i], (const uint16_t*)c.d_in, (const uint16_t*)c.d_w, c.d_scale, c.d_shift, c.epilogue,
+template <int DT, int CIN, int COUT, int CALLS>
+__global__ void __launch_bounds__(256, 4) k_spconv_rows(const emc2_conv_batch<CALLS> b) {
+  const emc2_conv_place at = emc2_conv_of_block(b);
+  const emc2_conv_args& c = b.call[at.call];
+  run_rows<DT, CIN, COUT>(at.block, (const uint16_t*)c.d_in, (const uint16_t*)c.d_w, c.d_scale, c.d_shift, c.epilogue,
                           c.d_nbr, c.d_n_out, c.capacity_out, c.n_in, c.dev_flags, (uint16_t*)c.d_out);
 }
 
 void launch_rows(emc2_dtype dtype, int cin, int cout, const emc2_conv_args* calls, int n, hipStream_t s) {
-  emc2_conv_batch b;
+  emc2_conv_batch<kConvBatch> b;
   b.n = n;
   uint32_t blocks = 0;
   for (int i = 0; i < n; ++i) {
@@ -312,8 +313,11 @@ void launch_rows(emc2_dtype dtype, int cin, int cout, const emc2_conv_args* call
     b.first[i] = blocks;
     blocks += (uint32_t)emc2_div_up(calls[i].capacity_out, 512);
   }
-#define EMC2_ROWS(D, CI, CO) \
-  if (dtype == D && cin == CI && cout == CO) hipLaunchKernelGGL((k_spconv_rows<D, CI, CO>), dim3(blocks), dim3(256), 0, s, b);
+#define EMC2_ROWS(D, CI, CO)                                                                                                     \
+  if (dtype == D && cin == CI && cout == CO) {                                                                                   \
+    if (n == 1) hipLaunchKernelGGL((k_spconv_rows<D, CI, CO, 1>), dim3(blocks), dim3(256), 0, s, emc2_conv_one(b));              \
+    else hipLaunchKernelGGL((k_spconv_rows<D, CI, CO, kConvBatch>), dim3(blocks), dim3(256), 0, s, b);                           \
+  }
   EMC2_ROWS(EMC2_F16, 4, 16) EMC2_ROWS(EMC2_F16, 4, 32) EMC2_ROWS(EMC2_F16, 16, 16)
   EMC2_ROWS(EMC2_BF16, 4, 16) EMC2_ROWS(EMC2_BF16, 4, 32) EMC2_ROWS(EMC2_BF16, 16, 16)
 #undef EMC2_ROWS

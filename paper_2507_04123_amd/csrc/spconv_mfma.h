@@ -16,17 +16,22 @@ struct emc2_conv_args {
   int32_t n_in, epilogue;
   int32_t* dev_flags;
 };
-constexpr int kConvBatch = 4;
-struct emc2_conv_batch {
+constexpr int kConvBatch = 4;           // calls a launch can hold
+// A launch of one call has a form of its own: where the block looks for its call, the arguments are read a dependent scalar load later.
+// us, looked for / so: 16 -> 32 over 4 000 rows 4.9 / 4.8, 32 -> 64 8.0 / 7.75, over 12 000 8.55 / 8.25, 64 -> 32 over 4 000 8.0 / 7.8.
+template <int CALLS> struct emc2_conv_batch {
   int32_t n;
-  uint32_t first[kConvBatch];           // first block of each, a multiple of 8
-  emc2_conv_args call[kConvBatch];
+  uint32_t first[CALLS];                // first block of each (of kernels that deal tiles to XCDs a multiple of 8)
+  emc2_conv_args call[CALLS];
 };
-// The call that this block belongs to.
-__device__ __forceinline__ int emc2_conv_of_block(const emc2_conv_batch& b) {
+static inline emc2_conv_batch<1> emc2_conv_one(const emc2_conv_batch<kConvBatch>& b) { return {1, {0}, {b.call[0]}}; }
+// The call that this block belongs to, the block's number in it and how many blocks it has.
+struct emc2_conv_place { int call; uint32_t block, blocks; };
+template <int CALLS> __device__ __forceinline__ emc2_conv_place emc2_conv_of_block(const emc2_conv_batch<CALLS>& b) {
+  if constexpr (CALLS == 1) return {0, blockIdx.x, gridDim.x};
   int i = 0;
   while (i + 1 < b.n && blockIdx.x >= b.first[i + 1]) ++i;
-  return i;
+  return {i, blockIdx.x - b.first[i], (i + 1 < b.n ? b.first[i + 1] : gridDim.x) - b.first[i]};
 }
 
 // true iff (cin, cout) is covered by an MFMA instantiation (16-bit dtypes only)

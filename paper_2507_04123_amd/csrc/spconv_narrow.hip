@@ -85,7 +85,7 @@ __device__ __forceinline__ void run_narrow(uint32_t block, uint32_t n_blocks, co
   const int64_t n_tiles = (n_out + kNRows - 1) / kNRows;
   const int64_t tiles = emc2_xcd_tiles<kNRun>(block % 8, n_tiles);
   if ((int64_t)(block / 8) * C::WAVES >= tiles) return;   // uniform for the block
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int m = lane & 31, h = lane >> 5;                      // entries: row and half
   const int piece0 = CIN == 16 ? h : lane >> 4;                // operands: 16-byte piece of the row
   const int64_t step = (int64_t)(n_blocks / 8) * C::WAVES;
@@ -196,18 +196,17 @@ __device__ __forceinline__ void run_narrow(uint32_t block, uint32_t n_blocks, co
   emc2_report_oob(oob, dev_flags);
 }
 
-template <int DT, int CIN, bool BUF>
-__global__ void __launch_bounds__(NarrowCfg<CIN>::WAVES * 64, 4) k_spconv_narrow(const emc2_conv_batch b) {
-  const int i = emc2_conv_of_block(b);
-  const emc2_conv_args& c = b.call[i];
-  run_narrow<DT, CIN, BUF>(blockIdx.x - b.first[i], (i + 1 < b.n ? b.first[i + 1] : gridDim.x) - b.first[i], (const uint16_t*)c.d_in,
-                           (const u32x4*)c.d_w, c.d_scale, c.d_shift, c.epilogue, c.d_nbr, c.d_n_out, c.capacity_out, c.n_in, c.dev_flags,
-                           (const uint16_t*)c.d_zero_row, (uint16_t*)c.d_out);
+template <int DT, int CIN, bool BUF, int CALLS>
+__global__ void __launch_bounds__(NarrowCfg<CIN>::WAVES * 64, 4) k_spconv_narrow(const emc2_conv_batch<CALLS> b) {
+  const emc2_conv_place at = emc2_conv_of_block(b);
+  const emc2_conv_args& c = b.call[at.call];
+  run_narrow<DT, CIN, BUF>(at.block, at.blocks, (const uint16_t*)c.d_in, (const u32x4*)c.d_w, c.d_scale, c.d_shift, c.epilogue, c.d_nbr,
+                           c.d_n_out, c.capacity_out, c.n_in, c.dev_flags, (const uint16_t*)c.d_zero_row, (uint16_t*)c.d_out);
 }
 
 template <int DT, int CIN> void launch_narrow(const emc2_conv_args* calls, int n, hipStream_t s) {
   using C = NarrowCfg<CIN>;
-  emc2_conv_batch b;
+  emc2_conv_batch<kConvBatch> b;
   b.n = n;
   uint32_t blocks = 0;
   // Offsets into the input are 32-bit, and the absent neighbour's, 2^32 less a row, must lie at or beyond its end; so are the
@@ -220,8 +219,16 @@ template <int DT, int CIN> void launch_narrow(const emc2_conv_args* calls, int n
     blocks += (uint32_t)(own < C::GRID ? own : C::GRID);
     buf = buf && ((int64_t)calls[i].n_in + 1) * CIN * 2 <= ((int64_t)1 << 32) && calls[i].capacity_out < ((int64_t)1 << 29);
   }
-  if (buf) hipLaunchKernelGGL((k_spconv_narrow<DT, CIN, true>), dim3(blocks), dim3(C::WAVES * 64), 0, s, b);
-  else hipLaunchKernelGGL((k_spconv_narrow<DT, CIN, false>), dim3(blocks), dim3(C::WAVES * 64), 0, s, b);
+#define LAUNCH(BUF, CALLS, ARGS) \
+  hipLaunchKernelGGL((k_spconv_narrow<DT, CIN, BUF, CALLS>), dim3(blocks), dim3(C::WAVES * 64), 0, s, ARGS)
+  if (n == 1) {
+    if (buf) LAUNCH(true, 1, emc2_conv_one(b));
+    else LAUNCH(false, 1, emc2_conv_one(b));
+  } else {
+    if (buf) LAUNCH(true, kConvBatch, b);
+    else LAUNCH(false, kConvBatch, b);
+  }
+#undef LAUNCH
 }
 
 }  // namespace

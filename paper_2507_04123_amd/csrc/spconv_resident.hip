@@ -209,17 +209,17 @@ __device__ __forceinline__ void run_resident(uint32_t block, uint32_t n_blocks, 
   emc2_report_oob(oob, dev_flags);
 }
 
-template <int DT, int CIN, int COUT, bool BUF>
-__global__ void __launch_bounds__(kRThreads, 3) k_spconv_direct_resident(const emc2_conv_batch b) {
-  const int i = emc2_conv_of_block(b);
-  const emc2_conv_args& c = b.call[i];
-  run_resident<DT, CIN, COUT, BUF>(blockIdx.x - b.first[i], (i + 1 < b.n ? b.first[i + 1] : gridDim.x) - b.first[i],
-                                   (const uint16_t*)c.d_in, (const u32x4*)c.d_w, c.d_scale, c.d_shift, c.epilogue, c.d_nbr, c.d_n_out,
-                                   c.capacity_out, c.n_in, c.dev_flags, (const uint16_t*)c.d_zero_row, (uint16_t*)c.d_out);
+template <int DT, int CIN, int COUT, bool BUF, int CALLS>
+__global__ void __launch_bounds__(kRThreads, 3) k_spconv_direct_resident(const emc2_conv_batch<CALLS> b) {
+  const emc2_conv_place at = emc2_conv_of_block(b);
+  const emc2_conv_args& c = b.call[at.call];
+  run_resident<DT, CIN, COUT, BUF>(at.block, at.blocks, (const uint16_t*)c.d_in, (const u32x4*)c.d_w, c.d_scale, c.d_shift, c.epilogue,
+                                   c.d_nbr, c.d_n_out, c.capacity_out, c.n_in, c.dev_flags, (const uint16_t*)c.d_zero_row,
+                                   (uint16_t*)c.d_out);
 }
 
 template <int DT, int CIN, int COUT> void launch_resident(const emc2_conv_args* calls, int n, hipStream_t s) {
-  emc2_conv_batch b;
+  emc2_conv_batch<kConvBatch> b;
   b.n = n;
   uint32_t blocks = 0;
   // Offsets into the input are 32-bit, and the absent neighbour's, 2^32 less a row, must lie at or beyond its end.
@@ -231,8 +231,16 @@ template <int DT, int CIN, int COUT> void launch_resident(const emc2_conv_args* 
     blocks += (uint32_t)(own < kRCUs ? own : kRCUs);
     buf = buf && ((int64_t)calls[i].n_in + 1) * CIN * 2 <= ((int64_t)1 << 32);
   }
-  if (buf) hipLaunchKernelGGL((k_spconv_direct_resident<DT, CIN, COUT, true>), dim3(blocks), dim3(kRThreads), 0, s, b);
-  else hipLaunchKernelGGL((k_spconv_direct_resident<DT, CIN, COUT, false>), dim3(blocks), dim3(kRThreads), 0, s, b);
+#define LAUNCH(BUF, CALLS, ARGS) \
+  hipLaunchKernelGGL((k_spconv_direct_resident<DT, CIN, COUT, BUF, CALLS>), dim3(blocks), dim3(kRThreads), 0, s, ARGS)
+  if (n == 1) {
+    if (buf) LAUNCH(true, 1, emc2_conv_one(b));
+    else LAUNCH(false, 1, emc2_conv_one(b));
+  } else {
+    if (buf) LAUNCH(true, kConvBatch, b);
+    else LAUNCH(false, kConvBatch, b);
+  }
+#undef LAUNCH
 }
 
 }  // namespace

@@ -13,8 +13,8 @@
 // 248 k rows, 124 / 117 over 500 k; nor in k_spconv_i8: 111.1 / 111.7 a pass.)
 // What is left of the tiles behind the last whole turn of eight runs goes to the XCDs by an eighth each, so that none has more than one
 // tile above the least, and a level of less than a turn is on all of them: whole runs there left XCDs without a row and others with
-// twice the rounds.  Capacity of the rows, us, an eighth each of all tiles / whole runs only / so: 32 -> 32 500 rows 5.3 / 12.3 / 5.5, 1 000
-// 6.0 / 21.7 / 6.2, 12 000 9.0 / 13.7 / 9.1, 66 000 10.3 / 16.4 / 11.2; 16 -> 32 1 000 4.5 / 14.3 / 4.9; 64 -> 32 500 9.1 / 14.8 / 7.8.
+// twice the rounds.  Capacity of the rows, us, an eighth each of all tiles / whole runs only / so: 32 -> 32 500 rows 5.3 / 12.3 / 5.3, 1 000
+// 6.0 / 21.7 / 6.1, 12 000 9.0 / 13.7 / 9.1, 66 000 10.3 / 16.4 / 10.9; 16 -> 32 1 000 4.5 / 14.3 / 4.7; 64 -> 32 500 9.1 / 14.8 / 7.6.
 template <int RUN> __host__ __device__ __forceinline__ int64_t emc2_xcd_tile(uint32_t xcd, int64_t slot, int64_t n_tiles) {   // the slot-th of the XCD's
   const uint32_t at = (uint32_t)slot, n = (uint32_t)n_tiles, left = n % (8 * RUN), whole = (n - left) / 8;   // row numbers are 32-bit
   return at < whole ? (at / RUN * 8 + xcd) * RUN + at % RUN : n - left + xcd * left / 8 + (at - whole);
