@@ -486,19 +486,22 @@ void launch_bins(emc2_ctx* ctx, const float* d_points, const int32_t* d_batch, i
 
 }  // namespace
 
-// Points of a call from which on the bins pay; and, of its points a scan tile on average, from where on a bin is a quarter of a tile
-// and up to where bins pay at all (beyond, single bins hold so many points that their blocks set the time).  Point pass / bins, us, on
-// grids of 85 to 90 M cells a frame: 540 k points of 9 frames (43 a tile) 117 / 84, 600 k of 5 (87) 102 / 90, 480 k of 4 (87) 85 / 86;
-// with bins of a tile / of a quarter: 960 k of 8 (87) 103 / 122 (point pass 149), 1.9 M of 16 (87) 138 / 213 (273), 600 k of 2 denser ones
-// (231) 108 / 84 (83), 2.4 M of 8 (231) 187 / 166 (256), 1.9 M on cells of twice the size (700) 160 / 110 (193), 1.0 M of one frame
-// (770) 195 / 118 (107), 3.0 M (2 300) 762 / 332 (267).  Frames mixed point by point, 1.9 M of 16: 289 / 166.
-constexpr int64_t kBinPoints = 524288, kBinTiles = 1024, kFinePoints = 200, kMostPoints = 720;
+// Points of a call from which on the bins pay, if they are kDensePoints a scan tile or fewer on average, and if they are more; of its
+// points a tile, from where on a bin is a quarter of a tile, and up to where bins pay at all.  The passes' launches and the bins of many
+// points set the time of small clouds, the atomics on an index that fits no L2 that of the point pass.  On grids of 85 to 90 M cells a
+// frame, points a tile in brackets, us, point pass / bins of a tile / of a quarter: 480 k of 4 (87) 85 / 86, 540 k of 9 (43) 117 / 84, 600 k of
+// 5 (87) 101 / 91, 960 k of 8 (87) 149 / 100 / 122, 1.9 M of 16 (87) 273 / 138 / 213; 600 k of 4 (115) 94 / 109 / 79, of 3 (154) 87 / 108 / 81,
+// 1.5 M of 6 (192) 176 / 128 / 116; and of a quarter 600 k of 2 (231) 83 / 85, of one (436) 78 / 92, 900 k of one (694) 98 / 116, 1.0 M of 2
+// (385) 114 / 112, 1.2 M of 4 (231) 142 / 104, 1.4 M of 2 (539) 147 / 125, 1.0 M of one (770) 107 / 118, 3.0 M (2 300) 267 / 332.  Frames mixed
+// point by point, 1.9 M of 16: 288 / 166.
+constexpr int64_t kBinPoints = 524288, kDenseBinPoints = 1000000, kDensePoints = 200, kBinTiles = 1024, kFinePoints = 100, kMostPoints = 720;
 
 static int64_t tiles_of(int64_t n_cells) { return emc2_div_up(n_cells, (int64_t)1 << EMC2_BIN_SHIFT_TILE); }
 
 bool emc2_bins_pay(int64_t n_points, int64_t n_cells) {
   const int64_t tiles = tiles_of(n_cells);               // (an item names its bin in 23 bits)
-  return n_points >= kBinPoints && tiles >= kBinTiles && tiles < ((int64_t)1 << 21) && n_points <= kMostPoints * tiles;
+  return n_points >= (n_points <= kDensePoints * tiles ? kBinPoints : kDenseBinPoints) && tiles >= kBinTiles && tiles < ((int64_t)1 << 21) &&
+         n_points <= kMostPoints * tiles;
 }
 
 void emc2_voxelize_bins(emc2_ctx* ctx, const float* d_points, const int32_t* d_batch, int64_t n_points, const VoxParams& prm,
