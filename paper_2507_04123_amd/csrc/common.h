@@ -78,8 +78,9 @@ struct emc2_ctx {
   unsigned long long* first;  // [max_points / 64 + 1] one bit per point: the first of its voxel
   uint32_t* partials;       // scan partial sums [n_partials], then the bases made of them [n_partials]
   int64_t n_partials;
-  uint32_t* bins;           // [7 * n_bins + 4] large clouds by bin of cells (voxel_bins.hip)
+  uint32_t* bins;           // [6 * n_bins + 4] large clouds by bin of cells (voxel_bins.hip)
   int64_t n_bins;
+  bool bins_zeroed;         // the first n_bins of them are zero
   uint32_t* stack_sums;     // popcount sums of every level of a stack (stack.hip)
   int64_t n_stack_sums;
   int32_t* dev_words;       // [0] status flags, [2] voxel count of an index rebuilt from coordinates (others unused)

@@ -72,7 +72,9 @@ extern "C" emc2_status emc2_create(emc2_ctx** out, int device, int64_t max_point
   // fine bins as long as they are few enough, the slot's tiles beyond (and one more of either)
   ctx->n_bins = (4 * ctx->slot_tiles < EMC2_BINS_MAX ? 4 * ctx->slot_tiles : EMC2_BINS_MAX) + 1;
   if (ctx->n_bins < ctx->n_partials) ctx->n_bins = ctx->n_partials;
-  TRY(hipMalloc((void**)&ctx->bins, sizeof(uint32_t) * (7 * (size_t)ctx->n_bins + 4)), "hipMalloc(bins)");
+  TRY(hipMalloc((void**)&ctx->bins, sizeof(uint32_t) * (6 * (size_t)ctx->n_bins + 4)), "hipMalloc(bins)");
+  TRY(hipMemset(ctx->bins, 0, sizeof(uint32_t) * (size_t)ctx->n_bins), "hipMemset(bins)");
+  ctx->bins_zeroed = true;
   {
     // level 0 in tiles, up to EMC2_STACK_MAX_LEVELS - 1 further ones in sixteenths of tiles, and one sum of every 64 sums
     const int64_t further = n_slots - 1 < EMC2_STACK_MAX_LEVELS - 1 ? n_slots - 1 : EMC2_STACK_MAX_LEVELS - 1;

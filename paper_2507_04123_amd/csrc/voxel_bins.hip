@@ -4,14 +4,16 @@
 // whatever the address, the scope or the XCD that asks), then an 8-byte load (55 G/s at random places of an index of gigabytes, 200
 // where a block stays inside 256 KB) and a 16-byte store (30 and 190).  Here the points are first moved next to the others of their
 // bin of consecutive cells, and a block then owns a bin: its bits, ranks, counts and the order of its points live in LDS, every line
-// of the index is written once, and the only atomics that leave a CU are one per bin and 8 192 points.
+// of the index is written once, and the atomics that leave a CU are two per bin and 8 192 points (of points in no order at all up to two
+// a point), one per word of a larger bin and 16 384 points, and the counters of the lists.
 //
 //   k_bin_points     points per bin
-//   k_bin_starts     exclusive scan of them; the bins that have any
+//   k_bin_starts     exclusive scan of them; the bins that have any, and what the larger ones are divided into
 //   k_bin_points     the points again, each to its place: (x, y, z, intensity) and the cell inside the bin
-//   k_bin_distinct   voxels per bin
+//   k_bin_distinct   voxels per bin; the bits of the larger ones
 //   k_scan_partials  exclusive scan of those (cellindex.hip): the rank of a bin's first voxel, the number of voxels
-//   k_bin_voxels     a block a bin: index lines and flags, stale lines of the slot cleared, coordinates, counts, means
+//   k_bin_voxels     a block a bin of up to kSmallBin points: index lines and flags, coordinates, counts, means; stale lines cleared
+//   k_bin_parts      the same of the larger bins, in parts of their voxels
 //
 // Bound by memory and by the chain of a block's phases in LDS: 64 frames of 120 000 points (7.5 M voxels, of 5.8 G cells), us: count 36,
 // move 121 (154 MB read, 264 written), voxels of the bins 34, scans 30, the bins 265 (690 MB); 1 081 -> 491 in all.  The point pass
@@ -24,14 +26,24 @@ constexpr int kMoveThreads = 1024, kMovePoints = 8;     // points a thread
 constexpr int kWindow = 8192;                           // bins a block counts at a time
 constexpr int kSmallPoints = 12;                        // points a thread of a small bin's block
 constexpr uint32_t kSmallBin = 256 * kSmallPoints;      // points of a bin that one block takes
-constexpr uint32_t kItemVoxels = 128;                   // voxels of a larger bin that one block takes
-constexpr int kItemBlocks = 1024, kLargeBlocks = 512;
+constexpr uint32_t kChunk = 16384;                      // points of a larger bin that one block marks
+constexpr int kChunkBlocks = 512;
+constexpr int kPartThreads = 1024, kPartBlocks = 256;   // one a CU
+constexpr uint32_t kPartVoxels = 4096, kPartPoints = 16384;   // voxels, and points of them, of a larger bin that one block takes
+constexpr uint32_t kLongVoxel = 32;                     // points of a voxel that a wave adds up from
 
 // words (of 32 cells) and lines (of 16 words) of a bin
 template <int SHIFT> constexpr int kWords = 1 << (SHIFT - 5);
 template <int SHIFT> constexpr int kLines = kWords<SHIFT> >> EMC2_LINE_SHIFT;
 
-struct BinState { uint32_t small, large, items, unused; };   // bins of up to kSmallBin points, of more, blocks' shares of the latter
+// Bins of up to kSmallBin points, of more; the latter's chunks of points, and parts of voxels.
+struct BinState { uint32_t small, large, chunks, parts; };
+
+// Parts of a larger bin of so many points and at most so many voxels: so many voxels fit a block's LDS, and where they have many points a
+// part has fewer of them, since each point is five atomics in LDS (up to as many parts as there are blocks: each looks at all points).
+__device__ __forceinline__ uint32_t bin_parts(uint32_t points, uint32_t voxels) {
+  return max((voxels + kPartVoxels - 1) / kPartVoxels, min((points + kPartPoints - 1) / kPartPoints, (uint32_t)kPartBlocks));
+}
 
 __device__ __forceinline__ uint32_t wave_scan(uint32_t v) {   // inclusive
 #pragma unroll
@@ -47,10 +59,9 @@ __device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
   return v;
 }
 
-__global__ void __launch_bounds__(1024) k_bin_zero(uint32_t* __restrict__ counts, int64_t n, BinState* __restrict__ state) {
+__global__ void __launch_bounds__(1024) k_bin_zero(uint32_t* __restrict__ counts, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * 1024 + threadIdx.x;
   if (i < n) counts[i] = 0u;
-  if (i == 0) *state = BinState{0u, 0u, 0u, 0u};
 }
 
 // The bins that a block's kept points lie in, lowest and highest (hi < 0: none kept).  Frames come one after the other, so these
@@ -74,12 +85,21 @@ __device__ __forceinline__ Range block_range(const int32_t (&bin)[kMovePoints]) 
   return Range{lo_s, hi_s};
 }
 
-// Counts (MOVE: and places) a block's points.  moved, cells: point and cell inside the bin, at the point's place.
+// Counts (MOVE: and places) a block's points.  moved, cells: point and cell inside the bin, at the point's place.  On the way the first
+// of the two launches resets the state, and the second one clears the bits of the larger bins.
 template <int SHIFT, bool MOVE>
 __global__ void __launch_bounds__(kMoveThreads) k_bin_points(const float* __restrict__ points, const int32_t* __restrict__ batch,
                                                              int64_t n_points, VoxParams prm, uint32_t* __restrict__ counts,
-                                                             float4* __restrict__ moved, uint16_t* __restrict__ cells) {
+                                                             float4* __restrict__ moved, uint16_t* __restrict__ cells,
+                                                             BinState* __restrict__ state, uint4* __restrict__ bits) {
   __shared__ uint32_t win[kWindow];
+  if (!MOVE) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) *state = BinState{0u, 0u, 0u, 0u};
+  } else {
+    const int64_t n = (int64_t)state->large * (kWords<SHIFT> / 4);
+    for (int64_t i = (int64_t)blockIdx.x * kMoveThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kMoveThreads)
+      bits[i] = make_uint4(0u, 0u, 0u, 0u);
+  }
   const int64_t base = (int64_t)blockIdx.x * (kMoveThreads * kMovePoints) + threadIdx.x;
   int32_t bin[kMovePoints];
   uint32_t cell[kMovePoints], pos[kMovePoints];
@@ -119,12 +139,14 @@ __global__ void __launch_bounds__(kMoveThreads) k_bin_points(const float* __rest
   }
 }
 
-// starts[i] = points before bin i (starts[n] = all), cursors the same; no voxels yet.  list: the bins of up to kSmallBin points from
-// the front, those of more from the back, in any order: two bins of three of a frame have no point, and a block that finds that out
-// takes 2 us.
-__global__ void __launch_bounds__(1024) k_bin_starts(const uint32_t* __restrict__ counts, int64_t n, uint32_t* __restrict__ starts,
-                                                     uint32_t* __restrict__ cursors, uint32_t* __restrict__ voxels,
-                                                     uint32_t* __restrict__ list, BinState* __restrict__ state) {
+// starts[i] = points before bin i (starts[n] = all), cursors the same; no voxels yet.  list: the bins of up to kSmallBin points, in any
+// order: two bins of three of a frame have no point, and a block that finds that out takes 2 us.  The larger bins have a number each,
+// and are divided into chunks (number, bin, first point, end) and parts (number, bin, part); a bin has no more voxels than points or
+// cells.
+__global__ void __launch_bounds__(1024) k_bin_starts(const uint32_t* __restrict__ counts, int64_t n, uint32_t bin_cells,
+                                                     uint32_t* __restrict__ starts, uint32_t* __restrict__ cursors,
+                                                     uint32_t* __restrict__ voxels, uint32_t* __restrict__ list,
+                                                     uint4* __restrict__ chunks, uint4* __restrict__ parts, BinState* __restrict__ state) {
   __shared__ uint32_t wsum[16], wbefore[16], wsmall[16], small_s;
   const int64_t first = (int64_t)blockIdx.x * 1024;
   uint32_t before = 0;
@@ -138,7 +160,6 @@ __global__ void __launch_bounds__(1024) k_bin_starts(const uint32_t* __restrict_
   const bool small = v > 0u && v <= kSmallBin;
   const unsigned long long smalls = __ballot(small);
   if (lane == 63) { wsum[w] = inc; wbefore[w] = before; wsmall[w] = (uint32_t)__popcll(smalls); }
-  if (v > kSmallBin) list[n - 1 - atomicAdd(&state->large, 1u)] = (uint32_t)i;
   __syncthreads();
   uint32_t run = inc - v, at = (uint32_t)__popcll(smalls & ((1ull << lane) - 1ull)), all = 0;
   for (int j = 0; j < 16; ++j) {
@@ -149,49 +170,56 @@ __global__ void __launch_bounds__(1024) k_bin_starts(const uint32_t* __restrict_
   if (threadIdx.x == 0) small_s = all ? atomicAdd(&state->small, all) : 0u;
   __syncthreads();
   if (small) list[small_s + at] = (uint32_t)i;
+  if (v > kSmallBin) {
+    const uint32_t place = atomicAdd(&state->large, 1u);
+    const uint32_t c = (v + kChunk - 1) / kChunk, q = bin_parts(v, min(v, bin_cells));
+    const uint32_t c0 = atomicAdd(&state->chunks, c), q0 = atomicAdd(&state->parts, q);
+    for (uint32_t j = 0; j < c; ++j) chunks[c0 + j] = make_uint4(place, (uint32_t)i, run + j * kChunk, run + min(v, (j + 1) * kChunk));
+    for (uint32_t j = 0; j < q; ++j) parts[q0 + j] = make_uint4(place, (uint32_t)i, j, 0u);
+  }
   if (i < n) { starts[i] = run; cursors[i] = run; voxels[i] = 0u; }
   if (i == n - 1) starts[n] = run + v;
 }
 
-// Voxels of the bins with points: a wave a small bin; kLargeBlocks blocks share the larger ones and divide their voxels into items.
+// Voxels of the bins with points: a wave a small bin; kChunkBlocks blocks share the larger ones' points, and their bits.  The counts of
+// the points go back to zero, as the next call finds them.
 template <int SHIFT>
-__global__ void __launch_bounds__(256) k_bin_distinct(BinState* __restrict__ state, const uint32_t* __restrict__ list,
+__global__ void __launch_bounds__(256) k_bin_distinct(const BinState* __restrict__ state, const uint32_t* __restrict__ list,
                                                       const uint32_t* __restrict__ starts, int64_t n_bins,
-                                                      const uint16_t* __restrict__ cells, uint32_t* __restrict__ voxels,
-                                                      uint32_t* __restrict__ items) {
+                                                      const uint16_t* __restrict__ cells, const uint4* __restrict__ chunks,
+                                                      uint32_t* __restrict__ voxels, uint32_t* __restrict__ all_bits,
+                                                      uint32_t* __restrict__ counts) {
   __shared__ uint4 bits_s[4][kWords<SHIFT> / 4];
-  __shared__ uint32_t fresh_s, at_s;                     // a larger bin's voxels; where its items begin (waves may still read the first)
   const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t zero = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (zero < n_bins) counts[zero] = 0u;
   uint32_t fresh = 0;
-  if (blockIdx.x < kLargeBlocks) {
+  if (blockIdx.x < kChunkBlocks) {
     uint32_t* bits = reinterpret_cast<uint32_t*>(bits_s[0]);
-    for (uint32_t k = blockIdx.x; k < state->large; k += kLargeBlocks) {
-      const uint32_t bin = list[n_bins - 1 - k], begin = starts[bin], end = starts[bin + 1];
+    for (uint32_t k = blockIdx.x; k < state->chunks; k += kChunkBlocks) {
+      const uint4 chunk = chunks[k];
+      const uint32_t bin = chunk.y, begin = chunk.z, end = chunk.w;
       for (int i = threadIdx.x; i < kWords<SHIFT>; i += 256) bits[i] = 0u;
-      if (threadIdx.x == 0) fresh_s = 0u;
       __syncthreads();
+      for (uint32_t i = begin + threadIdx.x; i < end; i += 8 * 256) {
+        uint32_t c[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) c[q] = cells[min(i + q * 256, end - 1)];      // (the last point again: no other bit)
+#pragma unroll
+        for (int q = 0; q < 8; ++q) atomicOr(&bits[c[q] >> 5], 1u << (c[q] & 31));
+      }
+      __syncthreads();
+      uint32_t* to = all_bits + (int64_t)chunk.x * kWords<SHIFT>;
       fresh = 0;
-#pragma unroll 8
-      for (uint32_t i = begin + threadIdx.x; i < end; i += 256) {
-        const uint32_t c = cells[i], bit = 1u << (c & 31);
-        fresh += (atomicOr(&bits[c >> 5], bit) & bit) == 0u;
-      }
+      for (int i = threadIdx.x; i < kWords<SHIFT>; i += 256)
+        if (bits[i]) fresh += __popc(bits[i] & ~atomicOr(&to[i], bits[i]));
       fresh = wave_sum(fresh);
-      if (lane == 0) atomicAdd(&fresh_s, fresh);
-      __syncthreads();
-      const uint32_t v = fresh_s, n = (v + kItemVoxels - 1) / kItemVoxels;       // at most 512
-      if (threadIdx.x == 0) {
-        voxels[bin] = v;
-        at_s = atomicAdd(&state->items, n);
-      }
-      __syncthreads();
-      const uint32_t at = at_s;
-      for (uint32_t i = threadIdx.x; i < n; i += 256) items[at + i] = bin << 9 | i;
-      __syncthreads();
+      if (lane == 0) atomicAdd(&voxels[bin], fresh);
+      __syncthreads();                                   // the next chunk writes over this one's bits
     }
     return;
   }
-  const uint32_t k = (blockIdx.x - kLargeBlocks) * 4 + wave;
+  const uint32_t k = (blockIdx.x - kChunkBlocks) * 4 + wave;
   if (k >= state->small) return;
   const uint32_t bin = list[k], begin = starts[bin], end = starts[bin + 1];
 #pragma unroll
@@ -211,7 +239,9 @@ __global__ void __launch_bounds__(256) k_bin_distinct(BinState* __restrict__ sta
 struct BinArgs {
   VoxParams prm;
   const BinState* state;
-  const uint32_t *list, *starts, *bases, *items;
+  const uint32_t *list, *starts, *bases, *voxels;
+  const uint4* bits;
+  const uint4* parts;
   const float4* moved;
   const uint16_t* cells;
   cellword_t* idx;
@@ -238,19 +268,20 @@ template <int SHIFT> struct BinLds {
       uint32_t bits[kWords<SHIFT>];                      // occupancy of the bin
       uint16_t pre[kWords<SHIFT>];                       // its voxels before each word
     };
-    uint16_t list[kSmallBin];                            // small bin: its points ordered by voxel, once bits and pre are done with
+    uint16_t list[kSmallBin];                            // its points ordered by voxel, once bits and pre are done with
   };
-  union {
-    uint32_t count[kSmallBin / 2 + 1];                   // small bin: points of each voxel, then where they begin; 16 bits each
-    struct {                                             // an item's voxels: points, the first of them, the sum of the others
-      uint32_t n[kItemVoxels], first[EMC2_VOX_STASH][kItemVoxels];
-      float sum[4][kItemVoxels];
-    } item;
-  };
+  uint32_t count[kSmallBin / 2 + 1];                     // points of each voxel, then where they begin; 16 bits each
   uint32_t wsum[4];
 };
+template <int SHIFT> struct PartLds {
+  uint32_t bits[kWords<SHIFT>];
+  uint16_t pre[kWords<SHIFT>];
+  uint32_t n[kPartVoxels], first[EMC2_VOX_STASH][kPartVoxels];          // a voxel's points, the first of them, the sum of the others
+  float sum[4][kPartVoxels];
+  uint32_t wsum[kPartThreads / 64];
+};
 
-__device__ __forceinline__ uint32_t block_before(uint32_t v, uint32_t (&wsum)[4]) {   // exclusive
+template <int WAVES> __device__ __forceinline__ uint32_t block_before(uint32_t v, uint32_t (&wsum)[WAVES]) {   // exclusive
   const uint32_t inc = wave_scan(v);
   __syncthreads();
   if ((threadIdx.x & 63) == 63) wsum[threadIdx.x >> 6] = inc;
@@ -264,50 +295,47 @@ __device__ __forceinline__ uint32_t rank_in(const uint32_t* bits, const uint16_t
   return pre[cell >> 5] + __popc(bits[cell >> 5] & ((1u << (cell & 31)) - 1u));
 }
 
-// Bits and ranks of the bin to LDS; WRITE: and its lines of the index, those that hold bits and those that held some before this
-// call.  Returns the bin's voxels.
-template <int SHIFT>
-__device__ __forceinline__ uint32_t bin_ranks(BinLds<SHIFT>& s, const BinArgs& a, uint32_t bin, uint32_t begin, uint32_t n, uint32_t base,
-                                              bool write) {
-  constexpr int WPT = kWords<SHIFT> / 256;               // words a thread: 2, or 8 (half a line)
+// Ranks of the bin's words from its bits in LDS; write: and its lines of the index, those that hold bits and those that held some
+// before this call.  Every thread of the block calls it, behind a barrier; the ranks are there when it returns.
+template <int SHIFT, int WAVES, typename Lds>
+__device__ __forceinline__ uint32_t bin_ranks(Lds& s, const BinArgs& a, uint32_t bin, uint32_t base, bool write) {
+  constexpr int USED = WAVES * 64 < kWords<SHIFT> / 2 ? WAVES * 64 : kWords<SHIFT> / 2;
+  constexpr int WPT = kWords<SHIFT> / USED;              // words a thread: 2, or 8 (half a line)
   constexpr int TPL = 16 / WPT;                          // threads a line
-#pragma unroll
-  for (int j = 0; j < WPT; ++j) s.bits[threadIdx.x * WPT + j] = 0u;
-  __syncthreads();
-#pragma unroll 4
-  for (uint32_t i = threadIdx.x; i < n; i += 256) {
-    const uint32_t c = a.cells[begin + i];
-    atomicOr(&s.bits[c >> 5], 1u << (c & 31));
-  }
-  __syncthreads();
+  const bool used = (int)threadIdx.x < USED;
   uint32_t bits[WPT], sum = 0;
 #pragma unroll
   for (int j = 0; j < WPT; ++j) {
-    bits[j] = s.bits[threadIdx.x * WPT + j];
+    bits[j] = used ? s.bits[threadIdx.x * WPT + j] : 0u;
     sum += __popc(bits[j]);
   }
-  uint32_t run = block_before(sum, s.wsum), in_line = sum;
+  uint32_t run = block_before<WAVES>(sum, s.wsum), in_line = sum;
 #pragma unroll
   for (int d = 1; d < TPL; d <<= 1) in_line += __shfl_xor(in_line, d, 64);
-  alignas(16) uint2 word[WPT];
+  if (used) {
+    alignas(16) uint2 word[WPT];
 #pragma unroll
-  for (int j = 0; j < WPT; ++j) {
-    s.pre[threadIdx.x * WPT + j] = (uint16_t)run;
-    word[j] = in_line ? make_uint2(bits[j], base + run) : make_uint2(0u, 0u);
-    run += __popc(bits[j]);
-  }
-  if (write) {
-    lineflag_t* flag = a.flags + (int64_t)bin * kLines<SHIFT> + threadIdx.x / TPL;
-    const bool stale = *flag != 0;                       // a line's threads are neighbours in one wave: all read before one writes
-    if (in_line || stale) {
-      uint4* dst = reinterpret_cast<uint4*>(a.idx + (int64_t)bin * kWords<SHIFT> + threadIdx.x * WPT);
-#pragma unroll
-      for (int j = 0; j < WPT / 2; ++j) dst[j] = reinterpret_cast<const uint4*>(word)[j];
+    for (int j = 0; j < WPT; ++j) {
+      s.pre[threadIdx.x * WPT + j] = (uint16_t)run;
+      word[j] = in_line ? make_uint2(bits[j], base + run) : make_uint2(0u, 0u);
+      run += __popc(bits[j]);
     }
-    if (threadIdx.x % TPL == 0 && (in_line != 0) != stale) *flag = in_line != 0;
+    if (write) {
+      lineflag_t* flag = a.flags + (int64_t)bin * kLines<SHIFT> + threadIdx.x / TPL;
+      const bool stale = *flag != 0;                     // a line's threads are neighbours in one wave: all read before one writes
+      if (in_line || stale) {
+        uint4* dst = reinterpret_cast<uint4*>(a.idx + (int64_t)bin * kWords<SHIFT> + threadIdx.x * WPT);
+#pragma unroll
+        for (int j = 0; j < WPT / 2; ++j) dst[j] = reinterpret_cast<const uint4*>(word)[j];
+      }
+      if (threadIdx.x % TPL == 0 && (in_line != 0) != stale) *flag = in_line != 0;
+    }
   }
   __syncthreads();
-  return s.wsum[0] + s.wsum[1] + s.wsum[2] + s.wsum[3];
+  uint32_t all = 0;
+#pragma unroll
+  for (int j = 0; j < WAVES; ++j) all += s.wsum[j];
+  return all;
 }
 
 // Voxel r of k points: the first of them in q, the sum of the others in rest.
@@ -323,7 +351,15 @@ __device__ __forceinline__ void put_voxel(const BinArgs& a, int64_t r, const int
 template <int SHIFT, int LP>
 __device__ __forceinline__ void small_bin(BinLds<SHIFT>& s, const BinArgs& a, uint32_t bin, uint32_t begin, uint32_t n, uint32_t base,
                                           const int4& c0) {
-  const uint32_t voxels = bin_ranks<SHIFT>(s, a, bin, begin, n, base, true);
+  for (int i = threadIdx.x; i < kWords<SHIFT>; i += 256) s.bits[i] = 0u;
+  __syncthreads();
+#pragma unroll 4
+  for (uint32_t i = threadIdx.x; i < n; i += 256) {
+    const uint32_t c = a.cells[begin + i];
+    atomicOr(&s.bits[c >> 5], 1u << (c & 31));
+  }
+  __syncthreads();
+  const uint32_t voxels = bin_ranks<SHIFT, 4>(s, a, bin, base, true);
   for (uint32_t i = threadIdx.x; i < voxels / 2 + 1; i += 256) s.count[i] = 0u;
   __syncthreads();
   uint32_t vp[kSmallPoints];                             // voxel, and position among its points, of this thread's points
@@ -342,7 +378,7 @@ __device__ __forceinline__ void small_bin(BinLds<SHIFT>& s, const BinArgs& a, ui
   uint32_t mine = 0;
   for (uint32_t j = 0; j < per; ++j)
     if (v0 + j < voxels) mine += count[v0 + j];
-  uint32_t at = block_before(mine, s.wsum);
+  uint32_t at = block_before<4>(mine, s.wsum);
   for (uint32_t j = 0; j < per; ++j)
     if (v0 + j < voxels) {
       const uint32_t c = count[v0 + j];
@@ -354,76 +390,47 @@ __device__ __forceinline__ void small_bin(BinLds<SHIFT>& s, const BinArgs& a, ui
   for (int j = 0; j < kSmallPoints; ++j)
     if (j * 256u < n && threadIdx.x + j * 256 < n) s.list[count[vp[j] & 0xffffu] + (vp[j] >> 16)] = (uint16_t)(threadIdx.x + j * 256);
   __syncthreads();
-  for (uint32_t v = threadIdx.x; v < voxels && (int64_t)base + v < a.capacity; v += 256) {   // beyond: reported by the scan
-    const uint32_t from = count[v], k = (v + 1 < voxels ? count[v + 1] : n) - from;
-    float4 q[EMC2_VOX_STASH], rest = make_float4(0.f, 0.f, 0.f, 0.f);
+  const uint32_t lane = threadIdx.x & 63;
+  for (uint32_t v = threadIdx.x; v - threadIdx.x < voxels; v += 256) {       // the same for the whole block
+    const bool live = v < voxels && (int64_t)base + v < a.capacity;          // beyond: reported by the scan
+    const uint32_t from = live ? count[v] : 0u, k = live ? (v + 1 < voxels ? count[v + 1] : n) - from : 0u;
+    float4 rest = make_float4(0.f, 0.f, 0.f, 0.f);
+    const auto add = [&](float4& to, uint32_t j) {
+      const float4 p = a.moved[begin + s.list[j]];
+      to.x += p.x; to.y += p.y; to.z += p.z; to.w += p.w;
+    };
+    if (k <= kLongVoxel)
+      for (uint32_t j = EMC2_VOX_STASH; j < k; ++j) add(rest, from + j);
+    // (Many points of a voxel one after the other, by the thread that has it, set the time of a bin -- frames padded with points at the
+    // origin: 600 000 points of 8 frames, in each a voxel of 2 500 419 / 127 us, 8 of 300 172 / 129, 20 of 40 108 / 102.)
+    for (unsigned long long left = __ballot(k > kLongVoxel); left != 0ull; left &= left - 1ull) {
+      const int owner = __ffsll(left) - 1;
+      const uint32_t f = __shfl(from, owner, 64), m = __shfl(k, owner, 64);
+      float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+      for (uint32_t j = EMC2_VOX_STASH + lane; j < m; j += 64) add(sum, f + j);
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) {
+        sum.x += __shfl_xor(sum.x, d, 64); sum.y += __shfl_xor(sum.y, d, 64);
+        sum.z += __shfl_xor(sum.z, d, 64); sum.w += __shfl_xor(sum.w, d, 64);
+      }
+      if ((int)lane == owner) rest = sum;
+    }
+    if (!live) continue;
+    float4 q[EMC2_VOX_STASH];
 #pragma unroll
     for (int j = 0; j < EMC2_VOX_STASH; ++j)
       q[j] = (uint32_t)j < k ? a.moved[begin + s.list[from + j]] : make_float4(INFINITY, INFINITY, INFINITY, INFINITY);
-    for (uint32_t j = EMC2_VOX_STASH; j < k; ++j) {
-      const float4 p = a.moved[begin + s.list[from + j]];
-      rest.x += p.x; rest.y += p.y; rest.z += p.z; rest.w += p.w;
-    }
     put_voxel<LP>(a, (int64_t)base + v, c0, a.cells[begin + s.list[from]], q, rest, k);
   }
 }
 
-// Voxels [v0, v0 + kItemVoxels) of a larger bin, however many points they have: the block looks at all points of the bin.
-template <int SHIFT, int LP>
-__device__ __forceinline__ void item_of_bin(BinLds<SHIFT>& s, const BinArgs& a, uint32_t bin, uint32_t v0, uint32_t begin, uint32_t n,
-                                            uint32_t base, const int4& c0) {
-  const uint32_t voxels = bin_ranks<SHIFT>(s, a, bin, begin, n, base, v0 == 0);
-  if (threadIdx.x < kItemVoxels) {
-    s.item.n[threadIdx.x] = 0u;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) s.item.sum[j][threadIdx.x] = 0.f;
-  }
-  __syncthreads();
-#pragma unroll 4
-  for (uint32_t i = threadIdx.x; i < n; i += 256) {
-    const uint32_t v = rank_in(s.bits, s.pre, a.cells[begin + i]) - v0;
-    if (v >= kItemVoxels) continue;
-    const uint32_t pos = atomicAdd(&s.item.n[v], 1u);
-    if (pos < EMC2_VOX_STASH) {
-      s.item.first[pos][v] = i;
-    } else {
-      const float4 p = a.moved[begin + i];
-      unsafeAtomicAdd(&s.item.sum[0][v], p.x);
-      unsafeAtomicAdd(&s.item.sum[1][v], p.y);
-      unsafeAtomicAdd(&s.item.sum[2][v], p.z);
-      unsafeAtomicAdd(&s.item.sum[3][v], p.w);
-    }
-  }
-  __syncthreads();
-  const uint32_t v = threadIdx.x;
-  if (v >= kItemVoxels || v0 + v >= voxels || (int64_t)base + v0 + v >= a.capacity) return;
-  const uint32_t k = s.item.n[v];
-  float4 q[EMC2_VOX_STASH];
-#pragma unroll
-  for (int j = 0; j < EMC2_VOX_STASH; ++j)
-    q[j] = (uint32_t)j < k ? a.moved[begin + s.item.first[j][v]] : make_float4(INFINITY, INFINITY, INFINITY, INFINITY);
-  put_voxel<LP>(a, (int64_t)base + v0 + v, c0, a.cells[begin + s.item.first[0][v]], q,
-                make_float4(s.item.sum[0][v], s.item.sum[1][v], s.item.sum[2][v], s.item.sum[3][v]), k);
-}
-
-// Blocks [0, kItemBlocks) share the items of the larger bins.  Behind them a block for every bin of the slot and one more: the first
-// state->small have a bin of the list (blocks that stay and take every 1 792nd were 20 % slower: bins have 1 to kSmallBin points).  They
-// also share what the bins without points ask for, those past the grid among them -- stale lines cleared -- and the rows past the
-// last voxel.
+// A block for every bin of the slot and one more: the first state->small have a bin of the list (blocks that stay and take every
+// 1 792nd were 20 % slower: bins have 1 to kSmallBin points).  They also share what the bins without points ask for, those past the
+// grid among them -- stale lines cleared -- and the rows past the last voxel.
 template <int SHIFT, int LP>
 __global__ void __launch_bounds__(256) k_bin_voxels(const BinArgs a) {
   __shared__ BinLds<SHIFT> s;
-  const BinState st = *a.state;
-  if (blockIdx.x < kItemBlocks) {
-    for (uint32_t k = blockIdx.x; k < st.items; k += kItemBlocks) {
-      const uint32_t item = a.items[k], bin = item >> 9, begin = a.starts[bin];
-      const int4 c0 = decode_key((uint64_t)bin << SHIFT, a.prm.grid[0], a.prm.grid[1], a.prm.grid[2]);
-      item_of_bin<SHIFT, LP>(s, a, bin, (item & 511u) * kItemVoxels, begin, a.starts[bin + 1] - begin, a.bases[bin], c0);
-      __syncthreads();                                   // the next item writes over this one's bits
-    }
-    return;
-  }
-  const uint32_t blk = blockIdx.x - kItemBlocks;
+  const uint32_t small = a.state->small, blk = blockIdx.x;
   constexpr int FT = kLines<SHIFT> / 8;                  // threads that look at a bin's flags
   if (threadIdx.x < FT && blk < a.slot_bins) {
     const int64_t i = (int64_t)blk * FT + threadIdx.x;
@@ -439,16 +446,81 @@ __global__ void __launch_bounds__(256) k_bin_voxels(const BinArgs a) {
       *f = make_uint2(0u, 0u);
     }
   }
-  if (blk < st.small) {
+  if (blk < small) {
     const uint32_t bin = a.list[blk], begin = a.starts[bin];
     const int4 c0 = decode_key((uint64_t)bin << SHIFT, a.prm.grid[0], a.prm.grid[1], a.prm.grid[2]);
     small_bin<SHIFT, LP>(s, a, bin, begin, a.starts[bin + 1] - begin, a.bases[bin], c0);
     return;
   }
-  const int64_t stride = (int64_t)(a.slot_bins + 1 - st.small) * 256;
-  for (int64_t r = *a.n_voxels + (int64_t)(blk - st.small) * 256 + threadIdx.x; r < a.bound; r += stride) {
+  const int64_t stride = (int64_t)(a.slot_bins + 1 - small) * 256;
+  for (int64_t r = *a.n_voxels + (int64_t)(blk - small) * 256 + threadIdx.x; r < a.bound; r += stride) {
     a.feats[r] = make_float4(0.f, 0.f, 0.f, 0.f);
     a.counts[r] = 0;
+  }
+}
+
+// The bins of more points than that, in parts of kPartVoxels voxels, however many points these have: a block takes the bin's bits as
+// k_bin_distinct left them and looks at all points of the bin once, so a part's voxels are as many as the LDS of a CU has room for.
+// us, 128 voxels a block of 256 threads that marks the bin anew (the point pass in brackets) / so: 960 000 points in a layer each of 8 frames
+// 148 (120) / 97, in 100 tiles 234 (116) / 104, in 10 860 (115) / 118, half of them in one 1 490 (254) / 295, all 3 115 (282) / 361, all in
+// 3 000 cells 4 188 (1 067) / 362; 7.7 M of 64 frames, a layer each 978 (863) / 423, in 100 tiles 5 141 (921) / 627.  A cloud that
+// lies in one bin is the slower one still: every part looks at all of its points.
+template <int SHIFT, int LP>
+__global__ void __launch_bounds__(kPartThreads) k_bin_parts(const BinArgs a) {
+  __shared__ PartLds<SHIFT> s;
+  constexpr int B = 8;                                   // points a thread looks at together
+  const uint32_t t = threadIdx.x, parts = a.state->parts;
+  for (uint32_t at = blockIdx.x; at < parts; at += kPartBlocks) {
+    const uint4 part = a.parts[at];
+    const uint32_t bin = part.y, begin = a.starts[bin], n = a.starts[bin + 1] - begin, base = a.bases[bin];
+    const uint32_t voxels = a.voxels[bin], each = (voxels + bin_parts(n, voxels) - 1) / bin_parts(n, voxels), v0 = part.z * each;
+    if (v0 >= voxels) continue;                          // the same for the whole block; the parts were counted before the voxels
+    for (int i = t; i < kWords<SHIFT> / 4; i += kPartThreads)
+      reinterpret_cast<uint4*>(s.bits)[i] = a.bits[(int64_t)part.x * (kWords<SHIFT> / 4) + i];
+    for (uint32_t i = t; i < each; i += kPartThreads) {
+      s.n[i] = 0u;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) s.sum[j][i] = 0.f;
+    }
+    __syncthreads();
+    bin_ranks<SHIFT, kPartThreads / 64>(s, a, bin, base, v0 == 0);
+    for (uint32_t i0 = t; i0 < n; i0 += B * kPartThreads) {
+      uint32_t v[B], pos[B];
+#pragma unroll
+      for (int q = 0; q < B; ++q) v[q] = a.cells[begin + min(i0 + q * kPartThreads, n - 1)];
+#pragma unroll
+      for (int q = 0; q < B; ++q) v[q] = i0 + q * kPartThreads < n ? rank_in(s.bits, s.pre, v[q]) - v0 : each;
+#pragma unroll
+      for (int q = 0; q < B; ++q) {
+        pos[q] = v[q] < each ? atomicAdd(&s.n[v[q]], 1u) : 0u;
+        if (v[q] < each && pos[q] < EMC2_VOX_STASH) s.first[pos[q]][v[q]] = i0 + q * kPartThreads;
+      }
+      float4 p[B];
+#pragma unroll
+      for (int q = 0; q < B; ++q)
+        if (pos[q] >= EMC2_VOX_STASH) p[q] = a.moved[begin + i0 + q * kPartThreads];
+#pragma unroll
+      for (int q = 0; q < B; ++q)
+        if (pos[q] >= EMC2_VOX_STASH) {
+          unsafeAtomicAdd(&s.sum[0][v[q]], p[q].x);
+          unsafeAtomicAdd(&s.sum[1][v[q]], p[q].y);
+          unsafeAtomicAdd(&s.sum[2][v[q]], p[q].z);
+          unsafeAtomicAdd(&s.sum[3][v[q]], p[q].w);
+        }
+    }
+    __syncthreads();
+    const int4 c0 = decode_key((uint64_t)bin << SHIFT, a.prm.grid[0], a.prm.grid[1], a.prm.grid[2]);
+    for (uint32_t v = t; v < each; v += kPartThreads) {
+      if (v0 + v >= voxels || (int64_t)base + v0 + v >= a.capacity) break;
+      const uint32_t k = s.n[v];
+      float4 q[EMC2_VOX_STASH];
+#pragma unroll
+      for (int j = 0; j < EMC2_VOX_STASH; ++j)
+        q[j] = (uint32_t)j < k ? a.moved[begin + s.first[j][v]] : make_float4(INFINITY, INFINITY, INFINITY, INFINITY);
+      put_voxel<LP>(a, (int64_t)base + v0 + v, c0, a.cells[begin + s.first[0][v]], q,
+                    make_float4(s.sum[0][v], s.sum[1][v], s.sum[2][v], s.sum[3][v]), k);
+    }
+    __syncthreads();                                     // the next part writes over this one's
   }
 }
 
@@ -464,24 +536,36 @@ void launch_bins(emc2_ctx* ctx, const float* d_points, const int32_t* d_batch, i
   uint32_t* voxels = list + ctx->n_bins;
   uint32_t* bases = voxels + ctx->n_bins;
   BinState* state = reinterpret_cast<BinState*>(bases + ctx->n_bins);
-  float4* moved = reinterpret_cast<float4*>(ctx->pix_rank);         // scratch of the image pooling: 16 bytes a point,
-  uint16_t* cells = reinterpret_cast<uint16_t*>(ctx->pool_acc);     // and 16 more, 2 for its cell,
-  uint32_t* items = ctx->pool_acc + ctx->max_points;                // less than 1 for the items
+  // scratch of the image pooling, of 16 bytes a point each: the points moved; and, a quarter each, their cells (2 bytes a point), the
+  // bits of the larger bins (at most a third of a bit mask a point of theirs: 2.7), their chunks, and their parts (far less than 1)
+  float4* moved = reinterpret_cast<float4*>(ctx->pix_rank);
+  const int64_t quarter = (ctx->max_points + 3) / 4 * 4;             // (the scratch ends 256 words and more behind max_points * 4)
+  uint16_t* cells = reinterpret_cast<uint16_t*>(ctx->pool_acc);
+  uint32_t* bits = ctx->pool_acc + quarter;
+  uint4* chunks = reinterpret_cast<uint4*>(ctx->pool_acc + 2 * quarter);
+  uint4* parts = reinterpret_cast<uint4*>(ctx->pool_acc + 3 * quarter);
   const dim3 pg((unsigned)emc2_div_up(n_points, kMoveThreads * kMovePoints)), pb(kMoveThreads);
   const dim3 sg((unsigned)emc2_div_up(n, 1024)), sb(1024);
-  hipLaunchKernelGGL(k_bin_zero, sg, sb, 0, s, counts, n, state);
-  hipLaunchKernelGGL((k_bin_points<SHIFT, false>), pg, pb, 0, s, d_points, d_batch, n_points, prm, counts, nullptr, nullptr);
-  hipLaunchKernelGGL(k_bin_starts, sg, sb, 0, s, counts, n, starts, cursors, voxels, list, state);
-  hipLaunchKernelGGL((k_bin_points<SHIFT, true>), pg, pb, 0, s, d_points, d_batch, n_points, prm, cursors, moved, cells);
-  hipLaunchKernelGGL(k_bin_distinct<SHIFT>, dim3((unsigned)(kLargeBlocks + emc2_div_up(n, 4))), dim3(256), 0, s, state, list, starts, n,
-                     cells, voxels, items);
+  // The counts are zero between calls, unless a launch of the last one failed.
+  if (!ctx->bins_zeroed) hipLaunchKernelGGL(k_bin_zero, dim3((unsigned)emc2_div_up(ctx->n_bins, 1024)), sb, 0, s, counts, ctx->n_bins);
+  ctx->bins_zeroed = false;
+  hipLaunchKernelGGL((k_bin_points<SHIFT, false>), pg, pb, 0, s, d_points, d_batch, n_points, prm, counts, nullptr, nullptr, state, nullptr);
+  hipLaunchKernelGGL(k_bin_starts, sg, sb, 0, s, counts, n, 1u << SHIFT, starts, cursors, voxels, list, chunks, parts, state);
+  hipLaunchKernelGGL((k_bin_points<SHIFT, true>), pg, pb, 0, s, d_points, d_batch, n_points, prm, cursors, moved, cells, state, (uint4*)bits);
+  hipLaunchKernelGGL(k_bin_distinct<SHIFT>, dim3((unsigned)(kChunkBlocks + emc2_div_up(n, 4))), dim3(256), 0, s, state, list, starts, n,
+                     cells, chunks, voxels, bits, counts);
   emc2_scan_totals(ctx, voxels, n, capacity, bases, d_n_voxels, s);
-  const BinArgs a = {prm, state, list, starts, bases, items, moved, cells, idx, emc2_slot_flags(ctx, idx), d_n_voxels, n, slot_bins,
-                     capacity, n_points < capacity ? n_points : capacity, (int4*)d_coords, (float4*)d_feats, d_counts, d_feats_lp};
-  const dim3 vg((unsigned)(kItemBlocks + slot_bins + 1)), vb(256);
-  if (lp == 0) hipLaunchKernelGGL((k_bin_voxels<SHIFT, 0>), vg, vb, 0, s, a);
-  else if (lp == 1) hipLaunchKernelGGL((k_bin_voxels<SHIFT, 1>), vg, vb, 0, s, a);
-  else hipLaunchKernelGGL((k_bin_voxels<SHIFT, 2>), vg, vb, 0, s, a);
+  const BinArgs a = {prm, state, list, starts, bases, voxels, (const uint4*)bits, parts, moved, cells, idx, emc2_slot_flags(ctx, idx), d_n_voxels,
+                     n, slot_bins, capacity, n_points < capacity ? n_points : capacity, (int4*)d_coords, (float4*)d_feats, d_counts,
+                     d_feats_lp};
+#define VOXELS(LP)                                                                                                          \
+  {                                                                                                                         \
+    hipLaunchKernelGGL((k_bin_voxels<SHIFT, LP>), dim3((unsigned)(slot_bins + 1)), dim3(256), 0, s, a);                      \
+    hipLaunchKernelGGL((k_bin_parts<SHIFT, LP>), dim3(kPartBlocks), dim3(kPartThreads), 0, s, a);                            \
+  }
+  if (lp == 0) VOXELS(0) else if (lp == 1) VOXELS(1) else VOXELS(2)
+#undef VOXELS
+  ctx->bins_zeroed = hipPeekAtLastError() == hipSuccess;
 }
 
 }  // namespace
@@ -499,7 +583,7 @@ constexpr int64_t kBinPoints = 524288, kDenseBinPoints = 1000000, kDensePoints =
 static int64_t tiles_of(int64_t n_cells) { return emc2_div_up(n_cells, (int64_t)1 << EMC2_BIN_SHIFT_TILE); }
 
 bool emc2_bins_pay(int64_t n_points, int64_t n_cells) {
-  const int64_t tiles = tiles_of(n_cells);               // (an item names its bin in 23 bits)
+  const int64_t tiles = tiles_of(n_cells);
   return n_points >= (n_points <= kDensePoints * tiles ? kBinPoints : kDenseBinPoints) && tiles >= kBinTiles && tiles < ((int64_t)1 << 21) &&
          n_points <= kMostPoints * tiles;
 }
