@@ -11,7 +11,7 @@
 // transposed one), reads weights from LDS wherever it is, and takes the next tile when it is done (tiles of one group next to
 // tiles of nine).  It is bound by the gathers' loads: as many waves as fit (15, with spills) or two groups requested ahead gain
 // nothing, and loads that take whole 128-byte rows, lanes swapped afterwards, neither.  64 -> 64 in two halves of the columns,
-// gathering twice, is 6 % slower than spconv_direct.hip (223 k rows transposed 38 / 41, stride-2 51 / 64).
+// gathering twice, is 8 and 25 % slower than spconv_direct.hip (223 k rows transposed 38 / 41, stride-2 51 / 64).
 // Alone, us, before / so: stride-2 32 -> 64 69 k rows 20.0 / 17.1, 223 k 32.7 / 27.5, 893 k 115 / 90, 1.3 M 170 / 136; submanifold 304 k
 // 46 / 40, 1.2 M 180 / 140; transposed 64 -> 32 54 k 12.8 / 10.6, 223 k 32 / 26, 304 k 43 / 33, 893 k 101 / 70; submanifold 87 / 85; any
 // row from anywhere 223 k 85 / 88 and 103 / 103.

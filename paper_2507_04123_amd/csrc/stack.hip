@@ -555,8 +555,8 @@ __global__ void __launch_bounds__(256) k_stack_phase(const Args a) {
 // LDS of a CU, so every block of the launch builds all of it (bits, and ranks of their words) from all the points, and then
 // takes a share of the voxels, from their points to their kernel-map entries, which it looks up in its own copy: nothing
 // waits for another block.  On 200 000 cells, with the convolution behind it, as a graph, us, phases / so: 1 100 points 31 / 18,
-// 2 000 32 / 19, 8 000 36 / 25, 15 000 36 / 31 (all blocks read all points).  A cloud of fewer points than the block has threads
-// keeps the phases.
+// 2 000 32 / 19, 8 000 36 / 25, 15 000 36 / 31 (all blocks read all points).  A cloud of fewer points than the block has threads, or of
+// more than 15 a thread, keeps the phases; neither line is where this stops paying: 3 points 25 / 16, 500 30 / 18, 900 31 / 18, 16 384 35 / 32.
 constexpr int kSmallThreads = 1024, kSmallPer = 15;
 constexpr int64_t kSmallCloud = kSmallThreads * kSmallPer;
 constexpr int kSmallBlocks = 32;
