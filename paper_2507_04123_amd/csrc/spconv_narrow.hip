@@ -16,9 +16,9 @@
 // 16 -> 32 stride-2 to 985 k rows 76 / 58, to 529 k in bf16 45 / 33.5, submanifold over 60 k 14.6 / 10.8, 11.5 / 7.7 in a 16-beam
 // frame; 32 -> 32 submanifold over 985 k 107 / 97, bf16 over 529 k 70 / 66, 64-beam frame 40.4 / 37.4.
 // Requests 6, 9, 12, 18, 27 taps ahead: 63, 61, 58, 59, 58 (16 -> 32); 4, 6, 9, 12: 98, 97, 96, 97 (32 -> 32).  The next tile's
-// entries requested a whole tile ahead: the same.  2048 blocks instead of what is resident: 62.  What is left is traffic: 352 MB
-// a launch for 32 -> 32 over 985 k rows, 3.6 TB/s where a copy reaches 4.3, 232 of them necessary (rows fetched by more than one
-// L2, or again after they were displaced); 187 MB and 3.2 TB/s for 16 -> 32.
+// entries requested a whole tile ahead: the same.  2048 blocks instead of what is resident: 62.  What is left is traffic: 395 MB
+// a launch for 32 -> 32 over 985 k rows, 4.1 TB/s where a copy reaches 4.3, 232 of them necessary (rows fetched by more than one
+// L2, or again after they were displaced; with an eighth of the rows an XCD 352, in the same time); 191 MB and 3.3 TB/s for 16 -> 32.
 #include <hip/hip_bf16.h>
 #include <hip/hip_fp16.h>
 

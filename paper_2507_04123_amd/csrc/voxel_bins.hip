@@ -15,9 +15,10 @@
 //   k_bin_voxels     a block a bin of up to kSmallBin points: index lines and flags, coordinates, counts, means; stale lines cleared
 //   k_bin_parts      the same of the larger bins, in parts of their voxels
 //
-// Bound by memory and by the chain of a block's phases in LDS: 64 frames of 120 000 points (7.5 M voxels, of 5.8 G cells), us: count 36,
-// move 121 (154 MB read, 264 written), voxels of the bins 34, scans 30, the bins 265 (690 MB); 1 081 -> 491 in all.  The point pass
-// there: clear 81, mark 295, scan 261, second pass 367, means 77.
+// Bound by memory and by the chain of a block's phases in LDS: a 64-beam frame 64 times (7.5 M voxels, of 5.8 G cells), us: count 55, move
+// 123 (154 MB read, 303 written), voxels of the bins 35, scans 35, the bins 254 (177 MB read, 469 written; a wave issues in 18 % of its
+// cycles, LDS busy 24 %), no larger ones 4; 1 081 -> 507 in all.  The point pass there: clear 81, mark 295, scan 261, second pass 367,
+// means 77.
 #include "voxel_point.h"
 
 namespace {
