@@ -1,18 +1,23 @@
 // Quantised sparse convolution on the int8 matrix cores (paper Sec. 3.6 (2): model quantisation is one of the
 // deployment optimisations; the paper gives no scheme, the one here is stated in emc2.h).
 //
-// Same shape as the register-direct 16-bit kernel: v_mfma_i32_16x16x64_i8 takes, in lane (m = lane % 16,
+// As in the register-direct 16-bit kernels: v_mfma_i32_16x16x64_i8 takes, in lane (m = lane % 16,
 // q = lane / 16), the 16 consecutive input channels 16q .. 16q+15 of row m of the tile, i.e. 16 contiguous bytes
 // of the feature row nbr[k][o_m]; a 64-channel int8 row is exactly the four lanes' 64 bytes, so ONE
-// global_load_dwordx4 per 16-row tile and tap is the A operand (half the bytes and half the cache lines of the
+// global_load_dwordx4 per 16-row tile and tap is the operand (half the bytes and half the cache lines of the
 // fp16 kernel, twice the multiply-accumulates per matrix instruction).  Absent neighbours read past the end of the input's buffer
 // descriptor, which yields zeros (4 GiB and more: a zeroed row).
-// LDS holds the weights of the current and the next tap in B-fragment order and a small tile that turns the
-// accumulator layout into whole 16-byte pieces of output rows.  Accumulation is exact (int32); the epilogue is
+// Up to 64 x 64 and 128 x 32 channels (110 KB of weights at most) a block keeps all weights in LDS and its waves take tiles by
+// themselves (resident_walk.h); 128 -> 64 takes the weights of a tap at a time.  The former for all shapes / so, us, submanifold, int8
+// and E4M3: 64 -> 64 69 k rows 16.8 / 13.2 and 17.9 / 15.8, 165 k 28.0 / 24.3 and 30.4 / 28.1, 304 k 43 / 37 and 48 / 43, stride-2 69 k
+// 19.5 / 14.5, transposed 223 k 28 / 22; 64 -> 32 69 k 14.2 / 10.1; 128 -> 32 304 k 87 / 59.  What that form lost: a barrier and a copy of
+// weights a tap, taps that none of a wave's rows have, and the last round of blocks.  Slower (2 to 9 %) are maps that name any row from anywhere.
+// Accumulation is exact (int32); the epilogue is
 // a fixed sequence of individually rounded fp32 operations, so results are bit-reproducible.
 #include <hip/hip_fp16.h>
 
 #include "common.h"
+#include "resident_walk.h"
 
 #pragma clang fp contract(off)
 
@@ -126,36 +131,28 @@ __global__ void __launch_bounds__(256) k_pack_weights_i8(const int8_t* __restric
 //     (two v_mfma_f32_16x16x32_fp8_fp8 per 16-byte operand: its low and its high 8 bytes; features and packed weights
 //     split the same way, so the contraction pairs the same channels).
 // OUTQ: int8 operands: 1 = int8 output (re-quantised), 0 = fp16 output; E4M3 operands: 1 = fp32 output, 0 = fp16 output.
-// Rows a wave.  A launch is bound by the chain of 27 taps (operand latency, weights through LDS, a barrier each) until enough
+// 128 -> 64.  Rows a wave: a launch is bound by the chain of 27 taps (operand latency, weights through LDS, a barrier each) until enough
 // waves cover each other, then by LDS reads of weights, which feed half the products with 32 rows a wave that they feed with
-// 64.  A level of up to kQSmall rows, three blocks of 32-row waves a CU, runs those: 64 -> 64 with 64 rows / 32 rows, us: int8
-// 8 k rows 12.2 / 8.3, 40 k 13.1 / 11.2, 69 k 20.3 / 17.7, 93 k 18.5 / 16.0; E4M3 8 k 14.5 / 9.8, 69 k 23.1 / 19.4.  Beyond, 64 rows,
+// 64.  A level of up to kQSmall rows, three blocks of 32-row waves a CU, runs those.  Beyond, int8 runs 64 rows,
 // but a step of them, a block a CU, takes nearly as long if few of its blocks are there, so that a rest of less than half a
-// step runs 32 rows, behind the whole steps of the same launch.  All 64 rows / all 32 / both, fp16 out, us: int8 64 -> 64 108 k
-// 20.5 / 20.5 / 20.0, 148 k 25.4 / 23.7 / 21.6, 166 k 26.9 / 27.3 / 27.7 (its rest just over half a step, in 32 rows), 223 k 34.5 /
-// 32.4 / 30.4, 266 k 36.1 / 35.5 / 33.3, 304 k 40.7 / 43.8 / 41.1, 596 k 74.7 / 83.3 / 71.9, 2.4 M 314 / 363 / 316; stride-2 223 k 30.9 /
-// 30.4 / 28.2; 128 -> 64 223 k 86 / 81 / 73; 64 -> 32 148 k 20.8 / 19.7 / 17.9, E4M3 21.0 / 21.0 / 19.0.  The row count is the
-// device's, so a kernel holds both forms.  Not so E4M3 but for 64 -> 32: it runs two matrix instructions for every operand read,
-// so that 32 rows are the better ones nearly everywhere (64 -> 64 163 k rows 34.1 / 29.4, 223 k 43.6 / 38.0, 304 k 57.8 / 57.7, but
-// 2.4 M 350 / 373; both in one kernel spill; 128 -> 64 60 / 52, 76 / 69, 112 / 115), and int8 128 -> 32, where 64 rows gain 4 % at some
-// sizes and lose 15 % at others (223 k 78 / 74, 304 k 87 / 87, 471 k 75 / 69).  16 rows: E4M3 the same for small levels, int8 223 k
-// 10 % slower.
+// step runs 32 rows, behind the whole steps of the same launch: all 64 rows / all 32 / both, fp16 out, 223 k rows 86 / 81 / 73 us.
+// The row count is the device's, so the kernel holds both forms.  E4M3 runs two matrix instructions for every operand read, so that
+// 32 rows are the better ones nearly everywhere (60 / 52, 76 / 69, 112 / 115).
 constexpr int64_t kQSmall = 3 * 256 * 128;
 constexpr int64_t kQStep = 256 * 256;    // rows of a block of 64-row waves a CU
 
 // TALL: holds the form with 64 rows a wave too.  MINW: waves per SIMD the register allocator must leave room for, as many as
 // neither form spills at.
-template <int CIN, int COUT, int F8, bool BUF> struct QCfg {
-  static constexpr bool TALL = F8 ? CIN == 64 && COUT == 32 : !(CIN == 128 && COUT == 32);
-  static constexpr int MINW = !TALL ? (CIN == 64 && COUT == 64 && BUF ? 4 : 3)
-                                    : CIN == 64 && (COUT == 32 || BUF) ? 3 : 2;
+template <int F8> struct QCfg {
+  static constexpr bool TALL = !F8;
+  static constexpr int MINW = TALL ? 2 : 3;
 };
 
 template <int F8> struct QAcc { typedef intx4 type; };
 template <> struct QAcc<1> { typedef floatx4 type; };
 
 // Input rows through a buffer descriptor, as in the register-direct 16-bit kernel: zeros at or beyond its end.
-// Layers of a 64-beam frame with their quantiser, still with 64-row waves: int8 138 -> 130 us, E4M3 (half as many points) 146 -> 143 us.
+// Against a zeroed row, with the kernel below for all shapes: layers of a 64-beam frame with their quantiser int8 138 -> 130 us.
 __device__ __forceinline__ u32x4 buffer_row16(__amdgpu_buffer_rsrc_t rows, uint32_t byte) {
   return __builtin_amdgcn_raw_buffer_load_b128(rows, (int)byte, 0, 0);
 }
@@ -363,7 +360,7 @@ run_i8(int64_t slot, int64_t row_begin, QLds<CIN, COUT, OUTQ, F8>& lds, const in
 }
 
 template <int CIN, int COUT, int OUTQ, int F8, bool BUF>
-__global__ void __launch_bounds__(kQThreads, (QCfg<CIN, COUT, F8, BUF>::MINW))
+__global__ void __launch_bounds__(kQThreads, (QCfg<F8>::MINW))
 k_spconv_i8(const int8_t* __restrict__ in, const u32x4* __restrict__ wp, const float* __restrict__ mul,
             const float* __restrict__ add, int relu, float inv_out_scale, const int32_t* __restrict__ nbr,
             const int32_t* __restrict__ d_n_out, int64_t capacity_out, int32_t n_in, int32_t* __restrict__ dev_flags,
@@ -372,7 +369,7 @@ k_spconv_i8(const int8_t* __restrict__ in, const u32x4* __restrict__ wp, const f
   int64_t n_out = *d_n_out;
   if (n_out > capacity_out) n_out = capacity_out;
   // rows [0, tall) in tiles of 64-row waves, the others in tiles of 32-row waves
-  using Cfg = QCfg<CIN, COUT, F8, BUF>;
+  using Cfg = QCfg<F8>;
   int64_t slot = blockIdx.x / 8, tall = 0;
   if constexpr (Cfg::TALL) {
     if (n_out > kQSmall) {
@@ -396,24 +393,136 @@ k_spconv_i8(const int8_t* __restrict__ in, const u32x4* __restrict__ wp, const f
                                       nbr, n_out, capacity_out, n_in, dev_flags, zrow, out);
 }
 
+// Shapes whose weights a CU's LDS holds whole: the walk of resident_walk.h.
+template <int CIN, int COUT, int OUTQ, int F8> struct Op8 {
+  static constexpr int KS = CIN / 64, NT = COUT / 16;
+  typedef typename QAcc<F8>::type acc_t;
+  const float *mul, *add;
+  int relu;
+  float inv_out_scale;
+  void* out;
+  static __device__ __forceinline__ acc_t run(u32x4 w, u32x4 a, acc_t c) {
+    if constexpr (F8) {
+      const long w_lo = (long)(((unsigned long)w.y << 32) | w.x), w_hi = (long)(((unsigned long)w.w << 32) | w.z);
+      const long a_lo = (long)(((unsigned long)a.y << 32) | a.x), a_hi = (long)(((unsigned long)a.w << 32) | a.z);
+      c = __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8(w_lo, a_lo, c, 0, 0, 0);
+      return __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8(w_hi, a_hi, c, 0, 0, 0);
+    } else {
+      return __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(intx4, w), __builtin_bit_cast(intx4, a), c, 0, 0, 0);
+    }
+  }
+  // int -> fp32, multiply, add (each rounded on its own), ReLU, convert; lane swaps gather a lane's 16 (or, of 32 int8 columns, 8) bytes
+  // of a row.
+  __device__ __forceinline__ void store(int64_t row0, int m, int q, int64_t n_out, acc_t (&acc)[2][NT]) const {
+    uint32_t w[2][NT];                        // int8: four channels each
+#pragma unroll
+    for (int jp = 0; jp < NT / 2; ++jp) {
+      floatx4 ml[2], ad[2];
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          ml[t][e] = mul[16 * (2 * jp + t) + 4 * q + e];
+          ad[t][e] = add[16 * (2 * jp + t) + 4 * q + e];
+        }
+#pragma unroll
+      for (int mt = 0; mt < 2; ++mt) {
+        const int64_t o = row0 + 16 * mt + m;
+        u32x2 h[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          floatx4 v;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            float x = (float)acc[mt][2 * jp + t][e];
+            x = x * ml[t][e];
+            x = x + ad[t][e];
+            if (relu) x = x > 0.f ? x : 0.f;
+            v[e] = x;
+          }
+          if constexpr (F8 && OUTQ) {
+            if (o < n_out) *reinterpret_cast<floatx4*>(reinterpret_cast<float*>(out) + o * COUT + 16 * (2 * jp + t) + 4 * q) = v;
+          } else if constexpr (OUTQ) {
+            uint32_t p = 0u;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) p |= ((uint32_t)quant_i8(v[e], inv_out_scale) & 0xffu) << (8 * e);
+            w[mt][2 * jp + t] = p;
+          } else {
+#pragma unroll
+            for (int e = 0; e < 2; ++e)
+              h[t][e] = (uint32_t)__half_as_ushort(__float2half_rn(v[2 * e])) | (uint32_t)__half_as_ushort(__float2half_rn(v[2 * e + 1])) << 16;
+          }
+        }
+        if constexpr (!OUTQ) {
+          const u32x2 x = __builtin_amdgcn_permlane16_swap(h[0][0], h[1][0], false, false);
+          const u32x2 y = __builtin_amdgcn_permlane16_swap(h[0][1], h[1][1], false, false);
+          if (o < n_out)
+            *reinterpret_cast<u32x4*>(reinterpret_cast<uint16_t*>(out) + o * COUT + 32 * jp + 8 * (2 * (q & 1) + (q >> 1))) =
+                u32x4{x[0], y[0], x[1], y[1]};
+        }
+      }
+    }
+    if constexpr (!F8 && OUTQ) {
+#pragma unroll
+      for (int mt = 0; mt < 2; ++mt) {
+        const int64_t o = row0 + 16 * mt + m;
+        uint8_t* dst = reinterpret_cast<uint8_t*>(out) + o * COUT;
+        if constexpr (NT == 4) {   // rows of lanes and column tiles change places
+          const u32x2 a = __builtin_amdgcn_permlane32_swap(w[mt][0], w[mt][2], false, false);
+          const u32x2 b = __builtin_amdgcn_permlane32_swap(w[mt][1], w[mt][3], false, false);
+          const u32x2 c = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false);
+          const u32x2 d = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
+          if (o < n_out) *reinterpret_cast<u32x4*>(dst + 16 * q) = u32x4{c[0], c[1], d[0], d[1]};
+        } else {
+          const u32x2 x = __builtin_amdgcn_permlane16_swap(w[mt][0], w[mt][1], false, false);
+          if (o < n_out) *reinterpret_cast<u32x2*>(dst + 16 * (q & 1) + 8 * (q >> 1)) = x;
+        }
+      }
+    }
+  }
+};
+
+template <int CIN, int COUT, int OUTQ, int F8, bool BUF>
+__global__ void __launch_bounds__(emc2_resident::kRThreads, 3)
+k_spconv_i8_resident(const int8_t* __restrict__ in, const u32x4* __restrict__ wp, const float* __restrict__ mul,
+                     const float* __restrict__ add, int relu, float inv_out_scale, const int32_t* __restrict__ nbr,
+                     const int32_t* __restrict__ d_n_out, int64_t capacity_out, int32_t n_in, int32_t* __restrict__ dev_flags,
+                     const int8_t* __restrict__ zrow, void* __restrict__ out) {
+  const Op8<CIN, COUT, OUTQ, F8> op = {mul, add, relu, inv_out_scale, out};
+  emc2_resident::walk<Op8<CIN, COUT, OUTQ, F8>, BUF>(op, blockIdx.x, gridDim.x, in, wp, nbr, d_n_out, capacity_out, n_in, dev_flags, zrow);
+}
+
 template <int CIN, int COUT, int OUTQ, int F8 = 0>
 void launch_i8(const void* d_in, const void* d_wp, const float* d_mul, const float* d_add, int relu, float inv_out_scale,
                const int32_t* d_nbr, const int32_t* d_n_out, int64_t capacity_out, int32_t n_in, int32_t* dev_flags,
                const void* d_zero_row, void* d_out, hipStream_t s) {
-  int64_t blocks = emc2_div_up(capacity_out, kQWaves * 32);
-  if (QCfg<CIN, COUT, F8, true>::TALL && capacity_out > kQSmall) {
-    // kQSmall rows in small tiles, or whole steps in large ones and half a step in small ones
-    const int64_t mixed = capacity_out / (kQWaves * 64) + kQStep / 2 / (kQWaves * 32) + 1;
-    blocks = mixed > kQSmall / (kQWaves * 32) ? mixed : kQSmall / (kQWaves * 32);
-  }
+  // Offsets into the input are 32-bit, and the absent neighbour's, 2^32 less a row, must lie at or beyond its end.
+  const bool buf = ((int64_t)n_in + 1) * CIN <= ((int64_t)1 << 32);
+  if constexpr (CIN * COUT <= 4096) {       // the LDS of a CU holds the weights of all taps
+    const int64_t own = emc2_div_up(emc2_div_up(capacity_out, emc2_resident::kRRows), 8) * 8;
+    const unsigned blocks = (unsigned)(own < emc2_resident::kRCUs ? own : emc2_resident::kRCUs);
+#define LAUNCH(BUF)                                                                                                           \
+  hipLaunchKernelGGL((k_spconv_i8_resident<CIN, COUT, OUTQ, F8, BUF>), dim3(blocks), dim3(emc2_resident::kRThreads), 0, s,    \
+                     (const int8_t*)d_in, (const u32x4*)d_wp, d_mul, d_add, relu, inv_out_scale, d_nbr, d_n_out,             \
+                     capacity_out, n_in, dev_flags, (const int8_t*)d_zero_row, d_out)
+    if (buf) LAUNCH(true);
+    else LAUNCH(false);
+#undef LAUNCH
+  } else {
+    int64_t blocks = emc2_div_up(capacity_out, kQWaves * 32);
+    if (QCfg<F8>::TALL && capacity_out > kQSmall) {
+      // kQSmall rows in small tiles, or whole steps in large ones and half a step in small ones
+      const int64_t mixed = capacity_out / (kQWaves * 64) + kQStep / 2 / (kQWaves * 32) + 1;
+      blocks = mixed > kQSmall / (kQWaves * 32) ? mixed : kQSmall / (kQWaves * 32);
+    }
 #define LAUNCH(BUF)                                                                                                           \
   hipLaunchKernelGGL((k_spconv_i8<CIN, COUT, OUTQ, F8, BUF>), dim3((unsigned)(blocks + 8)),            \
                      dim3(kQThreads), 0, s, (const int8_t*)d_in, (const u32x4*)d_wp, d_mul, d_add, relu, inv_out_scale, d_nbr, \
                      d_n_out, capacity_out, n_in, dev_flags, (const int8_t*)d_zero_row, d_out)
-  // Offsets into the input are 32-bit, and the absent neighbour's, 2^32 less a row, must lie at or beyond its end.
-  if (((int64_t)n_in + 1) * CIN <= ((int64_t)1 << 32)) LAUNCH(true);
-  else LAUNCH(false);
+    if (buf) LAUNCH(true);
+    else LAUNCH(false);
 #undef LAUNCH
+  }
 }
 
 bool i8_shape_ok(int cin, int cout) { return (cin == 64 || cin == 128) && (cout == 32 || cout == 64); }

@@ -1,5 +1,5 @@
 // Register-direct convolution with resident weights (paper Sec. 3.5 sparse convolution over the non-empty voxels; Sec. 3.6 keeping
-// data on chip between dependent steps): 32 -> 64 and 64 -> 32, every map.
+// data on chip between dependent steps): 32 -> 64 and 64 -> 32, every map.  The walk itself: resident_walk.h.
 //
 // The operands as in spconv_direct.hip: lane (m, q) of v_mfma_f32_16x16x32 supplies 16 contiguous bytes of the feature row that its
 // output row names, so a load from global memory is the operand; absent neighbours read past the end of the input's buffer
@@ -20,8 +20,8 @@
 #include <hip/hip_fp16.h>
 
 #include "common.h"
+#include "resident_walk.h"
 #include "spconv_mfma.h"
-#include "xcd_tiles.h"
 
 namespace {
 
@@ -31,8 +31,8 @@ typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));   // native vector: real loads and stores
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef emc2_resident::u32x4 u32x4;
+typedef emc2_resident::u32x2 u32x2;
 
 template <int DT> struct MmaR;
 template <> struct MmaR<EMC2_F16> {
@@ -52,127 +52,18 @@ template <> struct MmaR<EMC2_BF16> {
   }
 };
 
-constexpr int kRWaves = 12;               // three a SIMD, what the LDS beside the weights leaves room for
-constexpr int kRThreads = kRWaves * 64;
-constexpr int kRRows = 32;                // output rows of a wave
-constexpr int kRRun = 16;                 // tiles of a run: 512 rows
-constexpr int64_t kRCUs = 256;            // compute units of the part; one block fits each
+using emc2_resident::kRCUs;
+using emc2_resident::kRRows;
+using emc2_resident::kRThreads;
 
-
-template <int DT, int CIN, int COUT, bool BUF>
-__device__ __forceinline__ void run_resident(uint32_t block, uint32_t n_blocks, const uint16_t* __restrict__ in, const u32x4* __restrict__ wp,
-                                             const float* __restrict__ scale, const float* __restrict__ shift, int epilogue,
-                                             const int32_t* __restrict__ nbr, const int32_t* __restrict__ d_n_out, int64_t capacity_out,
-                                             int32_t n_in, int32_t* __restrict__ dev_flags, const uint16_t* __restrict__ zrow,
-                                             uint16_t* __restrict__ out) {
-  constexpr int KS = CIN / 32, NT = COUT / 16, MT = 2;
-  constexpr int WT = KS * NT * 64;          // 16-byte weight pieces of a tap
-  constexpr int NA = MT * KS;               // operand loads of a tap
-  __shared__ u32x4 wl[27 * WT];
-  __shared__ int32_t ent_s[kRWaves][27 * kRRows];
-  __shared__ uint32_t taken_s;              // tiles of the block that its waves have taken
-  int64_t n_out = *d_n_out;
-  if (n_out > capacity_out) n_out = capacity_out;
-  // The blocks of an XCD take its tiles one by one, so that few tiles are spread over all of them.
-  const uint32_t blocks = n_blocks / 8, blk = block / 8;
-  const int64_t n_tiles = (n_out + kRRows - 1) / kRRows, tiles = emc2_xcd_tiles<kRRun>(block % 8, n_tiles);
-  if ((int64_t)blk >= tiles) return;        // uniform for the block
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int m = lane & 15, q = lane >> 4, half = lane >> 5, row = lane & 31;
-  const __amdgpu_buffer_rsrc_t rows =
-      __builtin_amdgcn_make_buffer_rsrc((void*)const_cast<uint16_t*>(in), 0, BUF ? (int)((uint32_t)n_in * (CIN * 2)) : 0, 0x00020000);
-  unsigned long long oob = 0ull;            // lanes that saw an entry outside [0, n_in)
-  if (threadIdx.x == 0) taken_s = kRWaves;
-  // a wave takes the block's next tile while it works on the last: tiles have from one to nine groups
-  const auto take = [&] {
-    uint32_t k = 0;
-    if (lane == 0) k = atomicAdd(&taken_s, 1u);
-    return (int64_t)blk + (int64_t)__builtin_amdgcn_readfirstlane(k) * blocks;
-  };
-  int64_t slot = blk + (int64_t)wave * blocks, next_slot = 0;
-
-  // half h of the wave holds the entries of taps 2i + h of the 32 rows (past the last tile: the last one's again)
-  int32_t e[14];
-  const auto entries = [&](int64_t at) {
-    const int64_t r0 = emc2_xcd_tile<kRRun>(block % 8, at < tiles ? at : tiles - 1, n_tiles) * kRRows;
-    const int32_t* p = nbr + r0 + (r0 + row < n_out ? row : 0);
-#pragma unroll
-    for (int i = 0; i < 14; ++i) e[i] = (p + (int64_t)(2 * i) * capacity_out)[i < 13 && half ? capacity_out : 0];
-  };
-  entries(slot);
-  for (int p = threadIdx.x; p < 27 * WT; p += kRThreads) wl[p] = wp[p];
-  __syncthreads();
-  int32_t* ent = ent_s[wave];
-
-  for (; slot < tiles; slot = next_slot) {
-    const int64_t row0 = emc2_xcd_tile<kRRun>(block % 8, slot, n_tiles) * kRRows;
-    const int32_t dead = row0 + row < n_out ? 0 : -1;
-    // the entries as rows the kernel may read (absent and beyond the input: -1), [tap][row], and the groups to run
-    uint32_t groups = 0;
-#pragma unroll
-    for (int i = 0; i < 14; ++i) {
-      const int32_t j = max(emc2_entry(e[i], dead, n_in, oob), -1);
-      const unsigned long long some = __ballot(j >= 0);
-#pragma unroll
-      for (int t = 0; t < 2; ++t)
-        if (2 * i + t < 27 && (t == 0 ? some & 0xffffffffull : some >> 32) != 0ull) groups |= 1u << ((2 * i + t) / 3);
-      if (2 * i + half < 27) ent[(2 * i + half) * kRRows + row] = j;
-    }
-    __builtin_amdgcn_wave_barrier();        // LDS accesses of a wave are in order
-    floatx4 acc[MT][NT];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int j = 0; j < NT; ++j) acc[mt][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-    u32x4 a[3][NA];                         // operands in flight, of a group's three taps
-#define EMC2_LOAD(G, KX)                                                                                                     \
-  _Pragma("unroll") for (int mt_ = 0; mt_ < MT; ++mt_) {                                                                     \
-    const int32_t j_ = ent[(3 * (G) + (KX)) * kRRows + 16 * mt_ + m];                                                        \
-    _Pragma("unroll") for (int ks_ = 0; ks_ < KS; ++ks_) {                                                                   \
-      if constexpr (BUF)   /* absent: 2^32 less a row, and a piece of the row: out of range, zero */                         \
-        a[KX][mt_ * KS + ks_] =                                                                                              \
-            __builtin_amdgcn_raw_buffer_load_b128(rows, (int)((uint32_t)j_ * (CIN * 2u) + 16u * (uint32_t)q + 64u * ks_), 0, 0); \
-      else                                                                                                                   \
-        a[KX][mt_ * KS + ks_] = *reinterpret_cast<const u32x4*>((j_ >= 0 ? in + (int64_t)j_ * CIN : zrow) + 8 * q + 32 * ks_); \
-    }                                                                                                                        \
-  }
-  // the weights are the first operand, so that a lane ends up with four consecutive channels of one row
-#define EMC2_TAP(G, KX)                                                                                                      \
-  _Pragma("unroll") for (int ks = 0; ks < KS; ++ks) {                                                                        \
-    const u32x4* w_ = wl + ((3 * (G) + (KX)) * KS + ks) * (NT * 64) + lane;                                                  \
-    u32x4 b[NT];                                                                                                             \
-    _Pragma("unroll") for (int j = 0; j < NT; ++j) b[j] = w_[j * 64];                                                        \
-    _Pragma("unroll") for (int mt = 0; mt < MT; ++mt)                                                                        \
-      _Pragma("unroll") for (int j = 0; j < NT; ++j) acc[mt][j] = MmaR<DT>::run(b[j], a[KX][mt * KS + ks], acc[mt][j]);       \
-  }
-    uint32_t g = 0;                         // (a tile without a neighbour runs group 0 on zeros)
-    if (groups != 0) {
-      g = __builtin_ctz(groups);
-      groups &= groups - 1;
-#pragma unroll
-      for (int kx = 0; kx < 3; ++kx) EMC2_LOAD(g, kx)
-    } else {
-#pragma unroll
-      for (int kx = 0; kx < 3; ++kx)
-#pragma unroll
-        for (int i = 0; i < NA; ++i) a[kx][i] = u32x4{0u, 0u, 0u, 0u};
-    }
-    next_slot = take();
-    entries(next_slot);
-    while (groups != 0) {
-      const uint32_t next = __builtin_ctz(groups);
-      groups &= groups - 1;
-#pragma unroll
-      for (int kx = 0; kx < 3; ++kx) {
-        EMC2_TAP(g, kx)
-        EMC2_LOAD(next, kx)
-      }
-      g = next;
-    }
-#pragma unroll
-    for (int kx = 0; kx < 3; ++kx) EMC2_TAP(g, kx)
-#undef EMC2_LOAD
-#undef EMC2_TAP
+template <int DT, int CIN, int COUT> struct Op16 {
+  static constexpr int KS = CIN / 32, NT = COUT / 16;
+  typedef floatx4 acc_t;
+  const float *scale, *shift;
+  int epilogue;
+  uint16_t* out;
+  static __device__ __forceinline__ floatx4 run(u32x4 w, u32x4 a, floatx4 c) { return MmaR<DT>::run(w, a, c); }
+  __device__ __forceinline__ void store(int64_t row0, int m, int q, int64_t n_out, floatx4 (&acc)[2][NT]) const {
     // Folded affine, ReLU and rounding in registers: lane (m, q) holds channels 16j + 4q .. + 3 of row m; one lane swap per pair of
     // column tiles leaves it eight consecutive channels.
 #pragma unroll
@@ -187,7 +78,7 @@ __device__ __forceinline__ void run_resident(uint32_t block, uint32_t n_blocks, 
           sh[t][i] = epilogue != EMC2_EPI_NONE ? shift[c] : -0.f;     // x * 1 + -0 is x
         }
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
+      for (int mt = 0; mt < 2; ++mt) {
         u32x2 h[2];
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
@@ -207,16 +98,15 @@ __device__ __forceinline__ void run_resident(uint32_t block, uint32_t n_blocks, 
       }
     }
   }
-  emc2_report_oob(oob, dev_flags);
-}
+};
 
 template <int DT, int CIN, int COUT, bool BUF, int CALLS>
 __global__ void __launch_bounds__(kRThreads, 3) k_spconv_direct_resident(const emc2_conv_batch<CALLS> b) {
   const emc2_conv_place at = emc2_conv_of_block(b);
   const emc2_conv_args& c = b.call[at.call];
-  run_resident<DT, CIN, COUT, BUF>(at.block, at.blocks, (const uint16_t*)c.d_in, (const u32x4*)c.d_w, c.d_scale, c.d_shift, c.epilogue,
-                                   c.d_nbr, c.d_n_out, c.capacity_out, c.n_in, c.dev_flags, (const uint16_t*)c.d_zero_row,
-                                   (uint16_t*)c.d_out);
+  const Op16<DT, CIN, COUT> op = {c.d_scale, c.d_shift, c.epilogue, (uint16_t*)c.d_out};
+  emc2_resident::walk<Op16<DT, CIN, COUT>, BUF>(op, at.block, at.blocks, c.d_in, (const u32x4*)c.d_w, c.d_nbr, c.d_n_out, c.capacity_out, c.n_in,
+                                                c.dev_flags, c.d_zero_row);
 }
 
 template <int DT, int CIN, int COUT> void launch_resident(const emc2_conv_args* calls, int n, hipStream_t s) {

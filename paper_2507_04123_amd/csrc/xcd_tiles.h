@@ -10,7 +10,7 @@
 // take runs of RUN consecutive tiles in turn, of 512 or 1024 rows: us, an eighth each / in runs: stride-2 64 -> 64 over 66 k rows
 // 37 / 29.5, transposed over 223 k 44 / 38, 32 -> 32 over 304 k 66 / 59, stride-2 32 -> 64 over 223 k 40 / 35; runs of 256 to 2048 rows
 // differ by 2 %.  (Not in k_spconv_span, whose tiles cost much the same and share planes: rounds of tiles dealt out, 60 / 65 over
-// 248 k rows, 124 / 117 over 500 k; nor in k_spconv_i8: 111.1 / 111.7 a pass.)
+// 248 k rows, 124 / 117 over 500 k; nor in k_spconv_i8, when it ran all 8-bit shapes: 111.1 / 111.7 a pass.)
 // What is left of the tiles behind the last whole turn of eight runs goes to the XCDs by an eighth each, so that none has more than one
 // tile above the least, and a level of less than a turn is on all of them: whole runs there left XCDs without a row and others with
 // twice the rounds.  Capacity of the rows, us, an eighth each of all tiles / whole runs only / so: 32 -> 32 500 rows 5.3 / 12.3 / 5.3, 1 000
