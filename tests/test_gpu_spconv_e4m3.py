@@ -65,6 +65,17 @@ def test_quantize_e4m3_bit_exact():
     ctx.close()
 
 
+@pytest.mark.parametrize("inv", [1.0, 2.0 ** -8, 0.37])
+def test_quantize_e4m3_every_half(inv):
+    """All 65 536 fp16 values, eight a thread: subnormal codes, ties, saturation, both zeros, infinities and numbers that are none."""
+    x = np.arange(65536, dtype=np.uint16).view(np.float16)
+    ctx = B.Context(16, 16, 64, n_slots=1)
+    q = torch.empty(len(x), dtype=torch.uint8, device="cuda")
+    ctx.quantize_e4m3(dev(x), inv, q)
+    assert np.array_equal(q.cpu().numpy(), oracle.quantize_e4m3(x.astype(np.float32), inv))
+    ctx.close()
+
+
 def _check_conv(ctx, xq, wq, mul, add, relu, nbr_np, cap):
     n_out = nbr_np.shape[1]
     cin, cout = wq.shape[1], wq.shape[2]
