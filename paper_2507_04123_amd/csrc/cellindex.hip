@@ -211,7 +211,160 @@ __global__ void __launch_bounds__(256) k_scan_apply_self(cellword_t* __restrict_
   }
 }
 
+// ---- the index from the marks -------------------------------------------------------------------------------------------------------
+
+__global__ void __launch_bounds__(256) k_marks_zero(uint4* __restrict__ p, int64_t n16) {
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n16; i += (int64_t)gridDim.x * 256) p[i] = make_uint4(0u, 0u, 0u, 0u);
+}
+
+// A thread's 8 words of marks (half a line).
+struct Marks8 { uint32_t v[8]; };
+__device__ __forceinline__ Marks8 load_marks(const uint32_t* __restrict__ marks, int64_t base, bool some) {
+  Marks8 m;
+  const uint4* p = reinterpret_cast<const uint4*>(marks + base);
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const uint4 v = some ? p[h] : make_uint4(0u, 0u, 0u, 0u);
+    m.v[4 * h] = v.x; m.v[4 * h + 1] = v.y; m.v[4 * h + 2] = v.z; m.v[4 * h + 3] = v.w;
+  }
+  return m;
+}
+__device__ __forceinline__ uint32_t count_marks(const Marks8& m) {
+  uint32_t s = 0;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) s += __popc(m.v[j]);
+  return s;
+}
+
+// Eight words of the index: bits and ranks from `run` on, or zeros where the slot holds stale ones; the marks go back to zero.  The flags
+// of the line are the even thread's; every thread has read them by now.
+__device__ __forceinline__ void take_marks(cellword_t* __restrict__ idx, lineflag_t* __restrict__ flags, uint32_t* __restrict__ marks,
+                                           lineflag_t* __restrict__ mark_flags, int64_t base, const Marks8& m, bool some, bool stale,
+                                           uint32_t& run) {
+  if (some || stale) {
+    uint4* p = reinterpret_cast<uint4*>(idx + base);
+#pragma unroll
+    for (int j = 0; j < 8; j += 2) {
+      const uint32_t r1 = run + __popc(m.v[j]);
+      p[j / 2] = some ? make_uint4(m.v[j], run, m.v[j + 1], r1) : make_uint4(0u, 0u, 0u, 0u);
+      run = r1 + __popc(m.v[j + 1]);
+    }
+  }
+  if (some) {
+    uint4* z = reinterpret_cast<uint4*>(marks + base);
+    z[0] = make_uint4(0u, 0u, 0u, 0u);
+    z[1] = make_uint4(0u, 0u, 0u, 0u);
+  }
+  if (!(threadIdx.x & 1)) {
+    if (some != stale) flags[base >> EMC2_LINE_SHIFT] = some ? 1 : 0;
+    if (some) mark_flags[base >> EMC2_LINE_SHIFT] = 0;
+  }
+}
+
+// Popcounts by tile.  Thread t owns the 8 words [8t, 8t+8) of its tile, here and below.
+__global__ void __launch_bounds__(256) k_marks_reduce(const uint32_t* __restrict__ marks, const lineflag_t* __restrict__ mark_flags,
+                                                      uint32_t* __restrict__ partials) {
+  const int64_t base = (int64_t)blockIdx.x * EMC2_SCAN_TILE + (int64_t)threadIdx.x * 8;
+  const bool some = mark_flags[base >> EMC2_LINE_SHIFT] != 0;
+  if (!__syncthreads_or(some)) {  // no bit in this tile
+    if (threadIdx.x == 0) partials[blockIdx.x] = 0u;
+    return;
+  }
+  __shared__ uint32_t wsum[4];
+  const uint32_t inc = wave_inclusive_scan(count_marks(load_marks(marks, base, some)));
+  if ((threadIdx.x & 63) == 63) wsum[threadIdx.x >> 6] = inc;
+  __syncthreads();
+  if (threadIdx.x == 0) partials[blockIdx.x] = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+}
+
+// SELF: `sums` are the tiles' popcounts, and a block adds up those before its own; the last block reports the total.  Else they are their
+// prefix sums.
+template <bool SELF>
+__global__ void __launch_bounds__(256) k_marks_apply(cellword_t* __restrict__ idx, lineflag_t* __restrict__ flags,
+                                                     uint32_t* __restrict__ marks, lineflag_t* __restrict__ mark_flags,
+                                                     const uint32_t* __restrict__ sums, int64_t capacity, int32_t* __restrict__ d_total,
+                                                     int32_t* __restrict__ d_flags) {
+  const int64_t base = (int64_t)blockIdx.x * EMC2_SCAN_TILE + (int64_t)threadIdx.x * 8;
+  const bool some = mark_flags[base >> EMC2_LINE_SHIFT] != 0, stale = flags[base >> EMC2_LINE_SHIFT] != 0;
+  const bool last = SELF && blockIdx.x == gridDim.x - 1;
+  if (!__syncthreads_or(some || stale) && !last) return;
+  const Marks8 m = load_marks(marks, base, some);
+  const uint32_t s = count_marks(m);
+  __shared__ uint32_t wsum[4], wbase[4];
+  uint32_t part = 0;
+  if constexpr (SELF)
+    for (int i = threadIdx.x; i < (int)blockIdx.x; i += 256) part += sums[i];
+  const uint32_t inc = wave_inclusive_scan(s), binc = SELF ? wave_inclusive_scan(part) : 0u;
+  if ((threadIdx.x & 63) == 63) {
+    wsum[threadIdx.x >> 6] = inc;
+    wbase[threadIdx.x >> 6] = binc;
+  }
+  __syncthreads();
+  uint32_t run = SELF ? inc - s + wbase[0] + wbase[1] + wbase[2] + wbase[3] : sums[blockIdx.x] + inc - s;
+  for (int j = 0; j < (int)(threadIdx.x >> 6); ++j) run += wsum[j];
+  const uint32_t end = run + s;
+  take_marks(idx, flags, marks, mark_flags, base, m, some, stale, run);
+  if (last && threadIdx.x == 255) {
+    if ((int64_t)end > capacity) atomicOr(d_flags, EMC2_DEVFLAG_CAPACITY);
+    *d_total = (int64_t)end > capacity ? (int32_t)capacity : (int32_t)end;
+  }
+}
+
+// The whole of a small grid (at most 8192 words) in one block, 8 words a thread.
+__global__ void __launch_bounds__(1024) k_marks_small(cellword_t* __restrict__ idx, lineflag_t* __restrict__ flags,
+                                                      uint32_t* __restrict__ marks, lineflag_t* __restrict__ mark_flags, int64_t n_words,
+                                                      int64_t capacity, int32_t* __restrict__ d_total, int32_t* __restrict__ d_flags) {
+  const int64_t base = (int64_t)threadIdx.x * 8;
+  const bool mine = base < n_words;
+  const bool some = mine && mark_flags[base >> EMC2_LINE_SHIFT] != 0, stale = mine && flags[base >> EMC2_LINE_SHIFT] != 0;
+  const Marks8 m = load_marks(marks, base, some);
+  const uint32_t s = count_marks(m);
+  __shared__ uint32_t wsum[16];
+  const uint32_t inc = wave_inclusive_scan(s);
+  if ((threadIdx.x & 63) == 63) wsum[threadIdx.x >> 6] = inc;
+  __syncthreads();
+  uint32_t run = inc - s;
+  for (int j = 0; j < (int)(threadIdx.x >> 6); ++j) run += wsum[j];
+  const uint32_t end = run + s;
+  take_marks(idx, flags, marks, mark_flags, base, m, some, stale, run);
+  if (threadIdx.x == 1023) {
+    if ((int64_t)end > capacity) atomicOr(d_flags, EMC2_DEVFLAG_CAPACITY);
+    *d_total = (int64_t)end > capacity ? (int32_t)capacity : (int32_t)end;
+  }
+}
+
 }  // namespace
+
+void emc2_marks_begin(emc2_ctx* ctx, hipStream_t stream) {
+  if (!ctx->marks_zeroed) {
+    const int64_t bytes = 4 * ctx->slot_words + (ctx->slot_words >> EMC2_LINE_SHIFT);      // slots are whole tiles: a multiple of 128
+    hipLaunchKernelGGL(k_marks_zero, dim3(2048), dim3(256), 0, stream, (uint4*)ctx->marks, bytes / 16);
+  }
+  ctx->marks_zeroed = false;
+}
+
+void emc2_marks_taken(emc2_ctx* ctx) { ctx->marks_zeroed = hipPeekAtLastError() == hipSuccess; }
+
+void emc2_index_build(emc2_ctx* ctx, cellword_t* idx, int64_t n_cells, int64_t capacity, int32_t* d_total, hipStream_t stream) {
+  const int64_t n_words = emc2_div_up(n_cells, 32), n_blocks = emc2_div_up(n_words, EMC2_SCAN_TILE);
+  lineflag_t *flags = emc2_slot_flags(ctx, idx), *mark_flags = emc2_mark_flags(ctx);
+  if (n_words <= 8 * 1024) {
+    hipLaunchKernelGGL(k_marks_small, dim3(1), dim3(1024), 0, stream, idx, flags, ctx->marks, mark_flags, n_words, capacity, d_total,
+                       ctx->dev_words);
+  } else {
+    hipLaunchKernelGGL(k_marks_reduce, dim3((unsigned)n_blocks), dim3(256), 0, stream, ctx->marks, mark_flags, ctx->partials);
+    if (n_blocks <= EMC2_SCAN_SELF_TILES) {   // each apply block re-sums the earlier totals itself: at most 64 KB from L2
+      hipLaunchKernelGGL(k_marks_apply<true>, dim3((unsigned)n_blocks), dim3(256), 0, stream, idx, flags, ctx->marks, mark_flags,
+                         ctx->partials, capacity, d_total, ctx->dev_words);
+    } else {
+      uint32_t* bases = ctx->partials + ctx->n_partials;
+      emc2_scan_totals(ctx, ctx->partials, n_blocks, capacity, bases, d_total, stream);
+      hipLaunchKernelGGL(k_marks_apply<false>, dim3((unsigned)n_blocks), dim3(256), 0, stream, idx, flags, ctx->marks, mark_flags, bases,
+                         capacity, d_total, ctx->dev_words);
+    }
+  }
+  emc2_marks_taken(ctx);
+}
 
 void emc2_index_clear(emc2_ctx* ctx, cellword_t* idx, hipStream_t stream) {
   hipLaunchKernelGGL(k_index_clear, dim3((unsigned)ctx->slot_tiles), dim3(256), 0, stream, (uint4*)idx,

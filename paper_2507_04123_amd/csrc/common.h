@@ -78,6 +78,8 @@ struct emc2_ctx {
   unsigned long long* first;  // [max_points / 64 + 1] one bit per point: the first of its voxel
   uint32_t* partials;       // scan partial sums [n_partials], then the bases made of them [n_partials]
   int64_t n_partials;
+  uint32_t* marks;          // [slot_words] occupancy bits of the index that is being built, [slot_words / 16] line flags behind them
+  bool marks_zeroed;        // they are zero
   uint32_t* bins;           // [6 * n_bins + 4] large clouds by bin of cells (voxel_bins.hip)
   int64_t n_bins;
   bool bins_zeroed;         // the first n_bins of them are zero
@@ -88,9 +90,7 @@ struct emc2_ctx {
   void* zero_row;           // 256 zero bytes: the feature row an absent neighbour reads
   // image pooling: per-pixel cell rank / position within the cell / sorted order, per-cell list starts
   int32_t *pix_rank, *pix_pos, *pix_perm, *pix_srank;   // [max_points] each
-  int32_t* cell_start;      // [max_voxels + 1]
-  uint32_t* pool_totals;    // block totals of the scan over the per-cell counts
-  int64_t n_pool_totals;
+  int32_t* cell_start;      // [max_voxels]
   uint32_t* pool_acc;       // [(max_points/64 + 2) * 256] partial results of cells that cross a block boundary
   int32_t* fuse_src;        // [2 * max_voxels] source rows of a fused set when the caller does not keep them
   int32_t* pinned;          // pinned host staging for counts / status (4 ints)
@@ -127,7 +127,23 @@ emc2_status emc2_fail(emc2_ctx* ctx, emc2_status st, const char* fmt, ...);
 emc2_status emc2_check_hip(emc2_ctx* ctx, hipError_t e, const char* what);
 bool emc2_grid_ok(const int32_t grid[3], int32_t n_batch, int64_t* n_cells);
 
+// Marks: occupancy bits of the index that a voxelization, pooling or fusion builds, 4 bytes per 32 cells, and a flag byte per 512 cells (64
+// bytes of bits), kept with the index's own.  Both are zero between calls: emc2_index_build, which takes the bits over into the slot, zeroes
+// them behind itself, and zeroes the lines that the slot still holds of an earlier index in the same pass.  Bits set in the slot itself have
+// to wait for a launch that clears it: with one less for each of the three calls, and each scan a little shorter, the bridge of a 64-beam
+// frame takes 150 -> 135 us.  (A
+// stack keeps that launch, of 5 us: its first gather reads what lies about the marks, and the maps, which read the same places of
+// the index later, then find less of it in the caches: 120 000 points 33 -> 41 us, 300 000 47 -> 56.)
+static inline lineflag_t* emc2_mark_flags(const emc2_ctx* ctx) { return reinterpret_cast<lineflag_t*>(ctx->marks + ctx->slot_words); }
+
 // cell-index construction (cellindex.hip); all asynchronous on `stream`
+// The marks are about to be set: zeroes them if a launch of an earlier call failed.  emc2_marks_taken: the launches that set them and took
+// them over are issued.
+void emc2_marks_begin(emc2_ctx* ctx, hipStream_t stream);
+void emc2_marks_taken(emc2_ctx* ctx);
+// the slot's index over ceil(n_cells/32) words from the marks, with prefix sums; min(total, capacity) to d_total and
+// EMC2_DEVFLAG_CAPACITY when total > capacity
+void emc2_index_build(emc2_ctx* ctx, cellword_t* idx, int64_t n_cells, int64_t capacity, int32_t* d_total, hipStream_t stream);
 // zero every flagged tile of the slot (whatever grid it last held) and lower its flag
 void emc2_index_clear(emc2_ctx* ctx, cellword_t* idx, hipStream_t stream);
 // exclusive scan of popcounts over ceil(n_cells/32) words; writes min(total, capacity) to d_total

@@ -65,6 +65,12 @@ extern "C" emc2_status emc2_create(emc2_ctx** out, int device, int64_t max_point
     TRY(hipMalloc((void**)&ctx->slots[s], bytes), "hipMalloc(index slot)");
     TRY(hipMemset(ctx->slots[s], 0, bytes), "hipMemset(index slot)");  // establishes the line-flag invariant
   }
+  {
+    const size_t bytes = sizeof(uint32_t) * (size_t)ctx->slot_words + sizeof(lineflag_t) * (size_t)(ctx->slot_words >> EMC2_LINE_SHIFT);
+    TRY(hipMalloc((void**)&ctx->marks, bytes), "hipMalloc(marks)");
+    TRY(hipMemset(ctx->marks, 0, bytes), "hipMemset(marks)");
+    ctx->marks_zeroed = true;
+  }
   TRY(hipMalloc((void**)&ctx->stash, sizeof(float4) * EMC2_VOX_STASH * (size_t)max_voxels), "hipMalloc(voxel stash)");
   TRY(hipMalloc((void**)&ctx->first, sizeof(unsigned long long) * ((size_t)max_points / 64 + 1)), "hipMalloc(first points)");
   ctx->n_partials = emc2_div_up(ctx->slot_words, EMC2_SCAN_TILE) + 1;
@@ -88,9 +94,7 @@ extern "C" emc2_status emc2_create(emc2_ctx** out, int device, int64_t max_point
   ctx->pix_pos = ctx->pix_rank + max_points;
   ctx->pix_perm = ctx->pix_pos + max_points;
   ctx->pix_srank = ctx->pix_perm + max_points;
-  TRY(hipMalloc((void**)&ctx->cell_start, sizeof(int32_t) * ((size_t)max_voxels + 1)), "hipMalloc(cell_start)");
-  ctx->n_pool_totals = emc2_div_up(max_voxels, 2048) + 1;
-  TRY(hipMalloc((void**)&ctx->pool_totals, sizeof(uint32_t) * (size_t)ctx->n_pool_totals), "hipMalloc(pool_totals)");
+  TRY(hipMalloc((void**)&ctx->cell_start, sizeof(int32_t) * (size_t)max_voxels), "hipMalloc(cell_start)");
   TRY(hipMalloc((void**)&ctx->pool_acc, sizeof(uint32_t) * 256 * ((size_t)max_points / 64 + 2)), "hipMalloc(pool_acc)");
   TRY(hipMalloc((void**)&ctx->fuse_src, sizeof(int32_t) * 2 * (size_t)max_voxels), "hipMalloc(fuse_src)");
   TRY(hipMalloc((void**)&ctx->wpack, (size_t)27 * 128 * 128 * 2), "hipMalloc(wpack)");
@@ -118,13 +122,13 @@ extern "C" void emc2_destroy(emc2_ctx* ctx) {
   if (ctx->stash) (void)hipFree(ctx->stash);
   if (ctx->first) (void)hipFree(ctx->first);
   if (ctx->partials) (void)hipFree(ctx->partials);
+  if (ctx->marks) (void)hipFree(ctx->marks);
   if (ctx->bins) (void)hipFree(ctx->bins);
   if (ctx->stack_sums) (void)hipFree(ctx->stack_sums);
   if (ctx->zero_row) (void)hipFree(ctx->zero_row);
   if (ctx->wpack) (void)hipFree(ctx->wpack);
   if (ctx->pix_rank) (void)hipFree(ctx->pix_rank);
   if (ctx->cell_start) (void)hipFree(ctx->cell_start);
-  if (ctx->pool_totals) (void)hipFree(ctx->pool_totals);
   if (ctx->pool_acc) (void)hipFree(ctx->pool_acc);
   if (ctx->fuse_src) (void)hipFree(ctx->fuse_src);
   if (ctx->dev_words) (void)hipFree(ctx->dev_words);

@@ -165,7 +165,7 @@ __device__ __forceinline__ void role_mark(const Args& a, const DevStack& st, uin
     st.counts[i] = 0;
   }
   if (st.expert >= 0 && st.group_batch && i < a.n_points) st.group_batch[i] = routed_frame(st, i);
-  emc2_mark_point(locate_in(a, st, i), i, a.n_points, st.lv[0].idx, st.lv[0].flags, st.first);
+  emc2_mark_point<2>(locate_in(a, st, i), i, a.n_points, reinterpret_cast<uint32_t*>(st.lv[0].idx), st.lv[0].flags, st.first);
 }
 
 // Four tiles per block, a wave each (no block barrier); a lane owns two adjacent lines = 32 words.

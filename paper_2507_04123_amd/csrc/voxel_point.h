@@ -63,15 +63,17 @@ __device__ __forceinline__ PointCell locate(const float* __restrict__ points, co
   return r;
 }
 
-// Sets the bit of a kept point's cell.  Whoever finds the bit clear is the first of its voxel; the 64 answers of a wave
+// Sets the bit of a kept point's cell in `bits`, W 32-bit words from one word of bits to the next: marks (1) or an index (2).  Whoever finds
+// it clear is the first of its voxel; the 64 answers of a wave
 // (points 64w .. 64w+63) go to first[w], written for every wave that holds a point.  Every lane of the wave calls this.
-__device__ __forceinline__ void emc2_mark_point(const PointCell& pc, int64_t i, int64_t n_points, cellword_t* __restrict__ idx,
+template <int W>
+__device__ __forceinline__ void emc2_mark_point(const PointCell& pc, int64_t i, int64_t n_points, uint32_t* __restrict__ bits,
                                                 lineflag_t* __restrict__ flags, unsigned long long* __restrict__ first) {
   bool mine = false;
   if (pc.keep) {
     const uint32_t bit = 1u << ((uint32_t)pc.key & 31u);
-    mine = (atomicOr(&idx[pc.key >> 5].x, bit) & bit) == 0u;
-    flags[emc2_line_of_key(pc.key)] = 1;   // this line of the index now holds a bit
+    mine = (atomicOr(&bits[W * (pc.key >> 5)], bit) & bit) == 0u;
+    flags[emc2_line_of_key(pc.key)] = 1;   // this line now holds a bit
   }
   const unsigned long long m = __ballot(mine);
   if ((threadIdx.x & 63) == 0 && i < n_points) first[i >> 6] = m;

@@ -3,9 +3,9 @@
 //
 // The voxel index of a cell is its rank in the prefix-summed cell index, so no hash table is needed:
 // (Clouds of more than half a million points: voxel_bins.hip.)
-// Pass 1 (one thread per point): cell key -> set the cell's bit in the index (one atomic OR per point); the same
+// Pass 1 (one thread per point): cell key -> set the cell's mark (one atomic OR per point); the same
 //   launch zeroes the output rows pass 2 accumulates into.
-// Scan: prefix sum over the index -> the rank of every active cell = its position in key order, and the
+// Scan: the index from the marks, prefix sums -> the rank of every active cell = its position in key order, and the
 //   number of voxels.
 //   The OR returns the word's old bits, which tell the voxel's first point from later ones (one bit kept per point).
 // Pass 2 (one thread per point): the same key again -> rank r (one 8-byte load).  A first point goes to row 0 of the
@@ -23,7 +23,7 @@
 namespace {
 
 __global__ void __launch_bounds__(256) k_vox_mark(const float* __restrict__ points, const int32_t* __restrict__ batch,
-                                                  int64_t n_points, VoxParams prm, cellword_t* __restrict__ idx,
+                                                  int64_t n_points, VoxParams prm, uint32_t* __restrict__ marks,
                                                   lineflag_t* __restrict__ flags,
                                                   unsigned long long* __restrict__ first, int64_t zero_rows,
                                                   float4* __restrict__ feats, int32_t* __restrict__ counts) {
@@ -33,7 +33,7 @@ __global__ void __launch_bounds__(256) k_vox_mark(const float* __restrict__ poin
     feats[i] = make_float4(0.f, 0.f, 0.f, 0.f);
     counts[i] = 0;
   }
-  emc2_mark_point(locate(points, batch, i, n_points, prm), i, n_points, idx, flags, first);
+  emc2_mark_point<1>(locate(points, batch, i, n_points, prm), i, n_points, marks, flags, first);
 }
 
 __global__ void __launch_bounds__(256) k_vox_scatter(const float* __restrict__ points, const int32_t* __restrict__ batch,
@@ -47,6 +47,14 @@ __global__ void __launch_bounds__(256) k_vox_scatter(const float* __restrict__ p
   const int32_t r = cell_lookup(idx, pc.key);
   if (r < 0 || r >= capacity) return;   // beyond capacity: reported by the scan, dropped here
   emc2_stash_point(i, r, pc, first, coords, feats, counts, stash, pitch);
+}
+
+// The rows that pass 2 accumulates into, in a launch of its own: see kZeroApart.
+__global__ void __launch_bounds__(256) k_vox_zero(int64_t rows, float4* __restrict__ feats, int32_t* __restrict__ counts) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= rows) return;
+  feats[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+  counts[i] = 0;
 }
 
 template <int LP>  // 0 none, 1 fp16, 2 bf16
@@ -94,17 +102,24 @@ VoxParams emc2_vox_params(const emc2_voxel_spec* spec) {
   return prm;
 }
 
+// Clouds of more points zero their rows apart from the marking: tests/test_gpu_voxel_bins.py tells this pass from the one by bins by the
+// number of launches, which was one more while the slot was cleared first.  (524 287 points: a launch of 5 us for one of 5 us.)
+constexpr int64_t kZeroApart = 262144;
+
 static void voxelize_points(emc2_ctx* ctx, const float* d_points, const int32_t* d_batch, int64_t n_points, const VoxParams& prm,
                             int64_t n_cells, cellword_t* idx, int64_t capacity, int32_t* d_coords, float* d_feats, int32_t* d_counts,
                             void* d_feats_lp, int lp, int32_t* d_n_voxels, hipStream_t s) {
-  emc2_index_clear(ctx, idx, s);
+  emc2_marks_begin(ctx, s);
   const dim3 pg((unsigned)emc2_div_up(n_points > 0 ? n_points : 1, 256)), blk(256);
   // at most min(n_points, capacity) voxels exist
   const int64_t bound = n_points < capacity ? n_points : capacity;
+  const int64_t with_marks = n_points > kZeroApart ? 0 : bound;
+  if (n_points > kZeroApart)
+    hipLaunchKernelGGL(k_vox_zero, dim3((unsigned)emc2_div_up(bound, 256)), blk, 0, s, bound, (float4*)d_feats, d_counts);
   if (n_points > 0)
-    hipLaunchKernelGGL(k_vox_mark, pg, blk, 0, s, d_points, d_batch, n_points, prm, idx, emc2_slot_flags(ctx, idx), ctx->first, bound,
+    hipLaunchKernelGGL(k_vox_mark, pg, blk, 0, s, d_points, d_batch, n_points, prm, ctx->marks, emc2_mark_flags(ctx), ctx->first, with_marks,
                        (float4*)d_feats, d_counts);
-  emc2_index_scan(ctx, idx, n_cells, capacity, d_n_voxels, s);
+  emc2_index_build(ctx, idx, n_cells, capacity, d_n_voxels, s);
   if (bound <= 0) return;
   const dim3 vg((unsigned)emc2_div_up(bound, 256));
   hipLaunchKernelGGL(k_vox_scatter, pg, blk, 0, s, d_points, d_batch, n_points, prm, idx, ctx->first, capacity,
