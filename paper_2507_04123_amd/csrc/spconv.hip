@@ -154,7 +154,7 @@ __global__ void __launch_bounds__(256) k_spconv_small(const T* __restrict__ in, 
 // leaves 4 consecutive output channels of row l in lane l's four accumulator registers, so the epilogue is
 // per-lane and the stores are whole 16-byte pieces of the lane's own row.  The vector-ALU kernel spends its time
 // re-reading weights from LDS for every multiply-add (one LDS read per 4 of them); here a weight block is read
-// once per tap and 4 channels for two groups of 64 rows, and a tap none of the 128 rows has costs nothing.
+// once per tap and 4 channels for 64 rows, and a tap none of them has costs nothing.
 typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
 typedef short short4_t __attribute__((ext_vector_type(4)));
 typedef float float4_t __attribute__((ext_vector_type(4)));
@@ -178,6 +178,12 @@ template <> struct Mma4<EMC2_BF16> {
   }
 };
 
+// A wave takes 64 rows.  With 128, a weight block's read serving both halves, a frame's launch was less than a round of the chip and each of
+// its waves had twice the loads to wait for.  Entries and rows requested together: all 27 and 9 of 4 channels, 9 and 3 of 16.  us, 128
+// rows a wave, 9 entries and rows (3 of 16 channels) at a time / 64 rows, the same / so: 4 -> 16 1 000 rows 6.9 / 4.5 / 4.3, 17 k 7.9 / 5.5 /
+// 5.2, 118 k 9.8 / 7.9 / 7.7, 471 k 20.7 / 18.4 / 19.0, 942 k 34.0 / 29.5 / 30.6; 4 -> 32 17 k 10.4 / 7.6 / 7.2, 118 k 13.5 / 11.7 / 11.5, 471 k
+// 29.4 / 30.0 / 27.9, 942 k 48.8 / 46.3 / 45.2; 16 -> 16 17 k 12.6 / 8.7 / 7.9, 118 k 17.4 / 14.6 / 13.2, 471 k 31.9 / 30.7 / 30.2, 942 k 56.1 /
+// 51.5 / 50.5.  All 27 rows of 4 channels at once: 5.7, 8.4, 22.0, 35.4 (fewer waves); 27 entries and 9 rows of 16: 7.6, 13.6, 32.1, 54.4.
 template <int DT, int CIN, int COUT>
 __device__ __forceinline__ void run_rows(uint32_t block, const uint16_t* __restrict__ in, const uint16_t* __restrict__ w,
                                          const float* __restrict__ scale, const float* __restrict__ shift, int epilogue,
@@ -185,10 +191,10 @@ __device__ __forceinline__ void run_rows(uint32_t block, const uint16_t* __restr
                                          int32_t n_in, int32_t* __restrict__ dev_flags, uint16_t* __restrict__ out) {
   constexpr int KB = CIN / 4;                 // 4-channel blocks of an input row
   constexpr int G = COUT / 4;                 // 4-channel groups of an output row
-  constexpr int RG = 2;                       // groups of 64 rows per wave (a weight block read serves both)
-  constexpr int TB = CIN == 4 ? 9 : 3;        // taps whose rows are in flight together
+  constexpr int EB = CIN == 4 ? 27 : 9;       // taps whose entries are in flight together
+  constexpr int TB = CIN == 4 ? 9 : 3;        // and whose rows are
   constexpr int RW = CIN / 2;                 // 32-bit words per input row
-  static_assert(27 % TB == 0 && CIN % 4 == 0 && COUT % 8 == 0, "shapes this kernel covers");
+  static_assert(27 % EB == 0 && EB % TB == 0 && CIN % 4 == 0 && COUT % 8 == 0, "shapes this kernel covers");
   // weights as A operands: wl[((tap * KB + kb) * G + g) * 4 + j] = W[tap][4kb + 0..3][4g + j], 8 bytes
   __shared__ u32x2_t wl[27 * KB * G * 4];
   for (int e = threadIdx.x; e < 27 * KB * G * 4; e += 256) {
@@ -202,98 +208,74 @@ __device__ __forceinline__ void run_rows(uint32_t block, const uint16_t* __restr
   }
   int64_t n = *d_n_out;
   if (n > capacity_out) n = capacity_out;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t row0 = (int64_t)block * (4 * RG * 64) + (int64_t)wave * (RG * 64) + lane;
-  bool live[RG];
-  const int32_t* nrow[RG];
-  int32_t dead[RG];
-#pragma unroll
-  for (int r = 0; r < RG; ++r) {
-    live[r] = row0 + 64 * r < n;
-    nrow[r] = nbr + (live[r] ? row0 + 64 * r : 0);
-    dead[r] = live[r] ? 0 : -1;
-  }
+  const int lane = threadIdx.x & 63;
+  const int64_t row = (int64_t)block * 256 + threadIdx.x;
+  const bool live = row < n;
+  const int32_t* nrow = nbr + (live ? row : 0);
+  const int32_t dead = live ? 0 : -1;
   unsigned long long oob = 0ull;
-  float4_t acc[RG][G];
+  float4_t acc[G];
 #pragma unroll
-  for (int r = 0; r < RG; ++r)
-#pragma unroll
-    for (int g = 0; g < G; ++g) acc[r][g] = float4_t{0.f, 0.f, 0.f, 0.f};
+  for (int g = 0; g < G; ++g) acc[g] = float4_t{0.f, 0.f, 0.f, 0.f};
   __syncthreads();   // weights in LDS
   const int jq = lane & 3;
 #pragma unroll 1
-  for (int k0 = 0; k0 < 27; k0 += TB) {
-    int32_t j[RG][TB];
+  for (int e0 = 0; e0 < 27; e0 += EB) {
+    int32_t e[EB];
 #pragma unroll
-    for (int r = 0; r < RG; ++r)
+    for (int t = 0; t < EB; ++t) e[t] = nrow[(int64_t)(e0 + t) * capacity_out];
 #pragma unroll
-      for (int t = 0; t < TB; ++t) j[r][t] = nrow[r][(int64_t)(k0 + t) * capacity_out];
-    uint32_t x[RG][TB][RW];
-#pragma unroll
-    for (int r = 0; r < RG; ++r)
+    for (int k = 0; k < EB; k += TB) {
+      int32_t j[TB];
+      uint32_t x[TB][RW];
 #pragma unroll
       for (int t = 0; t < TB; ++t) {
-        j[r][t] = emc2_entry(j[r][t], dead[r], n_in, oob);
-        const char* src = reinterpret_cast<const char*>(in + (int64_t)(j[r][t] >= 0 ? j[r][t] : 0) * CIN);
+        j[t] = emc2_entry(e[k + t], dead, n_in, oob);
+        const char* src = reinterpret_cast<const char*>(in + (int64_t)(j[t] >= 0 ? j[t] : 0) * CIN);
         if constexpr (RW == 2) {
           const u32x2_t v = *reinterpret_cast<const u32x2_t*>(src);
-          x[r][t][0] = v.x; x[r][t][1] = v.y;
+          x[t][0] = v.x; x[t][1] = v.y;
         } else {
 #pragma unroll
           for (int q = 0; q < RW / 4; ++q) {
             const u32x4_t v = reinterpret_cast<const u32x4_t*>(src)[q];
-            x[r][t][4 * q] = v.x; x[r][t][4 * q + 1] = v.y; x[r][t][4 * q + 2] = v.z; x[r][t][4 * q + 3] = v.w;
+            x[t][4 * q] = v.x; x[t][4 * q + 1] = v.y; x[t][4 * q + 2] = v.z; x[t][4 * q + 3] = v.w;
           }
         }
       }
 #pragma unroll
-    for (int t = 0; t < TB; ++t) {
-      bool have[RG];
-      unsigned long long any = 0ull;
+      for (int t = 0; t < TB; ++t) {
+        const bool have = j[t] >= 0;
+        if (__ballot(have) == 0ull) continue;   // wave-uniform: nobody has this tap
+        const u32x2_t* wt = wl + (e0 + k + t) * KB * G * 4 + jq;
 #pragma unroll
-      for (int r = 0; r < RG; ++r) {
-        have[r] = j[r][t] >= 0;
-        any |= __ballot(have[r]);
-      }
-      if (any == 0ull) continue;   // wave-uniform: nobody has this tap
-      const u32x2_t* wt = wl + (k0 + t) * KB * G * 4 + jq;
+        for (int kb = 0; kb < KB; ++kb) {
+          const u32x2_t b = have ? u32x2_t{x[t][2 * kb], x[t][2 * kb + 1]} : u32x2_t{0u, 0u};   // an absent neighbour adds zero
 #pragma unroll
-      for (int kb = 0; kb < KB; ++kb) {
-        u32x2_t b[RG];
-#pragma unroll
-        for (int r = 0; r < RG; ++r)
-          b[r] = have[r] ? u32x2_t{x[r][t][2 * kb], x[r][t][2 * kb + 1]} : u32x2_t{0u, 0u};   // an absent neighbour adds zero
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-          const u32x2_t a = wt[(kb * G + g) * 4];
-#pragma unroll
-          for (int r = 0; r < RG; ++r) acc[r][g] = Mma4<DT>::run(a, b[r], acc[r][g]);
+          for (int g = 0; g < G; ++g) acc[g] = Mma4<DT>::run(wt[(kb * G + g) * 4], b, acc[g]);
         }
       }
     }
   }
   emc2_report_oob(oob, dev_flags);
-  // lane l holds output channels 4g .. 4g+3 of its row in acc[r][g]
+  // lane l holds output channels 4g .. 4g+3 of its row in acc[g]
+  if (!live) return;
+  uint32_t y[COUT / 2];
 #pragma unroll
-  for (int r = 0; r < RG; ++r) {
-    if (!live[r]) continue;
-    uint32_t y[COUT / 2];
+  for (int g = 0; g < G; ++g) {
+    float v[4];
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-      float v[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        v[i] = acc[r][g][i];
-        if (epilogue != EMC2_EPI_NONE) v[i] = fmaf(v[i], scale[4 * g + i], shift[4 * g + i]);
-        if (epilogue == EMC2_EPI_AFFINE_RELU) v[i] = v[i] > 0.f ? v[i] : 0.f;
-      }
-      y[2 * g] = Mma4<DT>::cvt2(v[0], v[1]);
-      y[2 * g + 1] = Mma4<DT>::cvt2(v[2], v[3]);
+    for (int i = 0; i < 4; ++i) {
+      v[i] = acc[g][i];
+      if (epilogue != EMC2_EPI_NONE) v[i] = fmaf(v[i], scale[4 * g + i], shift[4 * g + i]);
+      if (epilogue == EMC2_EPI_AFFINE_RELU) v[i] = v[i] > 0.f ? v[i] : 0.f;
     }
-    u32x4_t* dst = reinterpret_cast<u32x4_t*>(out + (row0 + 64 * r) * COUT);
-#pragma unroll
-    for (int q = 0; q < COUT / 8; ++q) dst[q] = u32x4_t{y[4 * q], y[4 * q + 1], y[4 * q + 2], y[4 * q + 3]};
+    y[2 * g] = Mma4<DT>::cvt2(v[0], v[1]);
+    y[2 * g + 1] = Mma4<DT>::cvt2(v[2], v[3]);
   }
+  u32x4_t* dst = reinterpret_cast<u32x4_t*>(out + row * COUT);
+#pragma unroll
+  for (int q = 0; q < COUT / 8; ++q) dst[q] = u32x4_t{y[4 * q], y[4 * q + 1], y[4 * q + 2], y[4 * q + 3]};
 }
 
 template <int DT, int CIN, int COUT, int CALLS>
@@ -311,7 +293,7 @@ void launch_rows(emc2_dtype dtype, int cin, int cout, const emc2_conv_args* call
   for (int i = 0; i < n; ++i) {
     b.call[i] = calls[i];
     b.first[i] = blocks;
-    blocks += (uint32_t)emc2_div_up(calls[i].capacity_out, 512);
+    blocks += (uint32_t)emc2_div_up(calls[i].capacity_out, 256);
   }
 #define EMC2_ROWS(D, CI, CO)                                                                                                     \
   if (dtype == D && cin == CI && cout == CO) {                                                                                   \
