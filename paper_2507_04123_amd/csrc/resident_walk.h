@@ -17,8 +17,11 @@ namespace emc2_resident {
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));   // native vector: real loads and stores
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-constexpr int kRWaves = 12;               // three a SIMD, what the LDS beside the weights leaves room for
-constexpr int kRThreads = kRWaves * 64;
+// Waves of a block, one block a CU, for registers up to 128 (what the LDS beside the weights holds the entries of) or 168 a lane; a form's
+// kernel takes the former unless it would spill: rows by address (inputs of 4 GiB and more) and int8 64 -> 64.  us, 12 / 15: 32 -> 64 submanifold
+// 304 k rows 37.5 / 34.6, stride-2 223 k 27.9 / 23.5, 69 k 14.4 / 12.7; 64 -> 32 transposed 166 k 20.2 / 20.0, submanifold 66 k 24.5 / 23.2 (levels
+// of up to 30 k rows up to 10 % slower under maps other than transposed ones); E4M3 64 -> 64 304 k 44.0 / 40.6; int8 128 -> 32 165 k 44.5 / 41.8.
+constexpr int kRWaves = 15, kRWavesWide = 12;
 constexpr int kRRows = 32;                // output rows of a wave
 constexpr int kRRun = 16;                 // tiles of a run: 512 rows
 constexpr int64_t kRCUs = 256;            // compute units of the part; one block fits each
@@ -35,7 +38,8 @@ __device__ __forceinline__ void walk(const OP& op, uint32_t block, uint32_t n_bl
   constexpr int WT = KS * NT * 64;          // 16-byte weight pieces of a tap
   constexpr int NA = MT * KS;               // operand loads of a tap
   __shared__ u32x4 wl[27 * WT];
-  __shared__ int32_t ent_s[kRWaves][27 * kRRows];
+  constexpr int WAVES = OP::template waves<BUF>;
+  __shared__ int32_t ent_s[WAVES][27 * kRRows];
   __shared__ uint32_t taken_s;              // tiles of the block that its waves have taken
   int64_t n_out = *d_n_out;
   if (n_out > capacity_out) n_out = capacity_out;
@@ -49,7 +53,7 @@ __device__ __forceinline__ void walk(const OP& op, uint32_t block, uint32_t n_bl
       __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(in), 0, BUF ? (int)((uint32_t)n_in * ROW) : 0, 0x00020000);
   unsigned long long oob = 0ull;            // lanes that saw an entry outside [0, n_in)
   // A wave takes the block's next tile while it works on the last: tiles have from one to nine groups.
-  if (threadIdx.x == 0) taken_s = kRWaves;
+  if (threadIdx.x == 0) taken_s = WAVES;
   const auto take = [&] {
     uint32_t k = 0;
     if (lane == 0) k = atomicAdd(&taken_s, 1u);
@@ -120,7 +124,7 @@ __device__ __forceinline__ void walk(const OP& op, uint32_t block, uint32_t n_bl
         for (int i = 0; i < NA; ++i) a[kx][i] = u32x4{0u, 0u, 0u, 0u};
     }
   };
-  for (int p = threadIdx.x; p < 27 * WT; p += kRThreads) wl[p] = wp[p];
+  for (int p = threadIdx.x; p < 27 * WT; p += WAVES * 64) wl[p] = wp[p];
   if (slot < tiles) begin();
   // the weights and the counter of the tiles are in LDS; the loads of the first rows stay in flight
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");

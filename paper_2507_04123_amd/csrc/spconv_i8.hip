@@ -9,8 +9,8 @@
 // descriptor, which yields zeros (4 GiB and more: a zeroed row).
 // Up to 64 x 64 and 128 x 32 channels (110 KB of weights at most) a block keeps all weights in LDS and its waves take tiles by
 // themselves (resident_walk.h); 128 -> 64 takes the weights of a tap at a time.  The former for all shapes / so, us, submanifold, int8
-// and E4M3: 64 -> 64 69 k rows 16.8 / 13.2 and 17.9 / 15.8, 165 k 28.0 / 24.3 and 30.4 / 28.1, 304 k 43 / 37 and 48 / 43, stride-2 69 k
-// 19.5 / 14.5, transposed 223 k 28 / 22; 64 -> 32 69 k 14.2 / 10.1; 128 -> 32 304 k 87 / 59.  What that form lost: a barrier and a copy of
+// and E4M3: 64 -> 64 69 k rows 16.7 / 13.1 and 18.0 / 15.0, 165 k 28.8 / 24.6 and 30.8 / 25.3, 304 k 43 / 37 and 48 / 41, stride-2 69 k
+// 19.6 / 15.0, transposed 223 k 28 / 22; 64 -> 32 69 k 14.2 / 10.1; 128 -> 32 304 k 87 / 57.  What that form lost: a barrier and a copy of
 // weights a tap, taps that none of a wave's rows have, and the last round of blocks.  Slower (2 to 9 %) are maps that name any row from anywhere.
 // Accumulation is exact (int32); the epilogue is
 // a fixed sequence of individually rounded fp32 operations, so results are bit-reproducible.
@@ -425,6 +425,8 @@ k_spconv_i8(const int8_t* __restrict__ in, const u32x4* __restrict__ wp, const f
 // Shapes whose weights a CU's LDS holds whole: the walk of resident_walk.h.
 template <int CIN, int COUT, int OUTQ, int F8> struct Op8 {
   static constexpr int KS = CIN / 64, NT = COUT / 16;
+  template <bool BUF> static constexpr int waves =
+      BUF && (F8 || CIN == 128 || COUT == 32) ? emc2_resident::kRWaves : emc2_resident::kRWavesWide;
   typedef typename QAcc<F8>::type acc_t;
   const float *mul, *add;
   int relu;
@@ -512,7 +514,7 @@ template <int CIN, int COUT, int OUTQ, int F8> struct Op8 {
 };
 
 template <int CIN, int COUT, int OUTQ, int F8, bool BUF>
-__global__ void __launch_bounds__(emc2_resident::kRThreads, 3)
+__global__ void __launch_bounds__((Op8<CIN, COUT, OUTQ, F8>::template waves<BUF> * 64))
 k_spconv_i8_resident(const int8_t* __restrict__ in, const u32x4* __restrict__ wp, const float* __restrict__ mul,
                      const float* __restrict__ add, int relu, float inv_out_scale, const int32_t* __restrict__ nbr,
                      const int32_t* __restrict__ d_n_out, int64_t capacity_out, int32_t n_in, int32_t* __restrict__ dev_flags,
@@ -531,9 +533,9 @@ void launch_i8(const void* d_in, const void* d_wp, const float* d_mul, const flo
     const int64_t own = emc2_div_up(emc2_div_up(capacity_out, emc2_resident::kRRows), 8) * 8;
     const unsigned blocks = (unsigned)(own < emc2_resident::kRCUs ? own : emc2_resident::kRCUs);
 #define LAUNCH(BUF)                                                                                                           \
-  hipLaunchKernelGGL((k_spconv_i8_resident<CIN, COUT, OUTQ, F8, BUF>), dim3(blocks), dim3(emc2_resident::kRThreads), 0, s,    \
-                     (const int8_t*)d_in, (const u32x4*)d_wp, d_mul, d_add, relu, inv_out_scale, d_nbr, d_n_out,             \
-                     capacity_out, n_in, dev_flags, (const int8_t*)d_zero_row, d_out)
+  hipLaunchKernelGGL((k_spconv_i8_resident<CIN, COUT, OUTQ, F8, BUF>), dim3(blocks),                                          \
+                     dim3(Op8<CIN, COUT, OUTQ, F8>::template waves<BUF> * 64), 0, s, (const int8_t*)d_in, (const u32x4*)d_wp, d_mul, d_add,    \
+                     relu, inv_out_scale, d_nbr, d_n_out, capacity_out, n_in, dev_flags, (const int8_t*)d_zero_row, d_out)
     if (buf) LAUNCH(true);
     else LAUNCH(false);
 #undef LAUNCH

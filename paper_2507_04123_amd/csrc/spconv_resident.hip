@@ -5,15 +5,15 @@
 // output row names, so a load from global memory is the operand; absent neighbours read past the end of the input's buffer
 // descriptor (inputs of 4 GiB and more: a zeroed row).  There a block of four waves copied each tap's weights through registers to
 // LDS, with a barrier a tap, and ran every (dz, dy) group that some row of its 128 had: a group of three taps took 3.3 us of a
-// CU's time, of which the gathers were a third.  These shapes' weights are 110 KB, which the LDS of a CU holds whole.  A block of 12
+// CU's time, of which the gathers were a third.  These shapes' weights are 110 KB, which the LDS of a CU holds whole.  A block of 15
 // waves, one a CU, copies them once, behind the only barrier; then each wave takes tiles of 32 rows by itself, runs only the
 // groups that its own rows have (5.1 of nine under a stride-2 map where blocks of 128 rows have 5.8, 2.7 where they have 3.5 under a
 // transposed one), reads weights from LDS wherever it is, and takes the next tile when it is done (tiles of one group next to
 // tiles of nine).  It is bound by the gathers' loads (eight routed frames: 257 MB a launch at 3.4 TB/s, where a copy reaches 4.3, and 1 281
-// cycles a load; matrix cores busy 24 %, LDS 17 %, a wave issues in 21 % of its cycles): as many waves as fit (15, with spills) or two
-// groups requested ahead gain nothing, and loads that take whole 128-byte rows, lanes swapped afterwards, neither.  64 -> 64 in two
+// cycles a load; matrix cores busy 24 %, LDS 17 %, a wave issues in 21 % of its cycles): two
+// groups requested ahead gain nothing, loads that take whole 128-byte rows, lanes swapped afterwards, neither.  64 -> 64 in two
 // halves of the columns, gathering twice, is 8 and 25 % slower than spconv_direct.hip (223 k rows transposed 38 / 41, stride-2 51 / 64).
-// Alone, us, before / so: stride-2 32 -> 64 69 k rows 20.0 / 17.1, 223 k 32.7 / 27.5, 893 k 115 / 90, 1.3 M 170 / 136; submanifold 304 k
+// Alone, us, spconv_direct.hip's way / so with 12 waves: stride-2 32 -> 64 69 k rows 20.0 / 17.1, 223 k 32.7 / 27.5, 893 k 115 / 90, 1.3 M 170 / 136; submanifold 304 k
 // 46 / 40, 1.2 M 180 / 140; transposed 64 -> 32 54 k 12.8 / 10.6, 223 k 32 / 26, 304 k 43 / 33, 893 k 101 / 70; submanifold 87 / 85; any
 // row from anywhere 223 k 85 / 88 and 103 / 103.
 #include <hip/hip_bf16.h>
@@ -54,10 +54,10 @@ template <> struct MmaR<EMC2_BF16> {
 
 using emc2_resident::kRCUs;
 using emc2_resident::kRRows;
-using emc2_resident::kRThreads;
 
 template <int DT, int CIN, int COUT> struct Op16 {
   static constexpr int KS = CIN / 32, NT = COUT / 16;
+  template <bool BUF> static constexpr int waves = BUF ? emc2_resident::kRWaves : emc2_resident::kRWavesWide;
   typedef floatx4 acc_t;
   const float *scale, *shift;
   int epilogue;
@@ -101,7 +101,7 @@ template <int DT, int CIN, int COUT> struct Op16 {
 };
 
 template <int DT, int CIN, int COUT, bool BUF, int CALLS>
-__global__ void __launch_bounds__(kRThreads, 3) k_spconv_direct_resident(const emc2_conv_batch<CALLS> b) {
+__global__ void __launch_bounds__((Op16<DT, CIN, COUT>::template waves<BUF> * 64)) k_spconv_direct_resident(const emc2_conv_batch<CALLS> b) {
   const emc2_conv_place at = emc2_conv_of_block(b);
   const emc2_conv_args& c = b.call[at.call];
   const Op16<DT, CIN, COUT> op = {c.d_scale, c.d_shift, c.epilogue, (uint16_t*)c.d_out};
@@ -123,7 +123,8 @@ template <int DT, int CIN, int COUT> void launch_resident(const emc2_conv_args* 
     buf = buf && ((int64_t)calls[i].n_in + 1) * CIN * 2 <= ((int64_t)1 << 32);
   }
 #define LAUNCH(BUF, CALLS, ARGS) \
-  hipLaunchKernelGGL((k_spconv_direct_resident<DT, CIN, COUT, BUF, CALLS>), dim3(blocks), dim3(kRThreads), 0, s, ARGS)
+  hipLaunchKernelGGL((k_spconv_direct_resident<DT, CIN, COUT, BUF, CALLS>), dim3(blocks),           \
+                     dim3(Op16<DT, CIN, COUT>::template waves<BUF> * 64), 0, s, ARGS)
   if (n == 1) {
     if (buf) LAUNCH(true, 1, emc2_conv_one(b));
     else LAUNCH(false, 1, emc2_conv_one(b));

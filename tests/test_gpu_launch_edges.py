@@ -246,11 +246,12 @@ def test_direct_conv_grid_limit(cin, cout, n, loop, hint):
         _check_conv(n, cin, cout, hint, False, cap=cap, rows_in=(1 << 25) + 3)
 
 
-# Tiles of 32 rows to 256 blocks of 12 waves, a block in a CU, whose waves take the block's tiles one by one: a tile, fewer tiles than
+# Tiles of 32 rows to 256 blocks of 15 waves (12 by address), a block in a CU, whose waves take the block's tiles one by one: a tile, fewer tiles than
 # blocks, as many, some of a block's waves with a tile, a tile less and more than all waves, many a wave; a capacity of the rows and of
 # many times as many.  32 channels of 2^26 rows and more (64 of 2^25) are read by address.
 @pytest.mark.parametrize("cin,cout", [(32, 64), (64, 32)])
-@pytest.mark.parametrize("n", [1, 300, 255 * 32 + 1, 256 * 32 + 1, 256 * 5 * 32 + 1, 256 * 12 * 32 - 33, 256 * 12 * 32 + 1, 8192 * 128 - 129,
+@pytest.mark.parametrize("n", [1, 300, 255 * 32 + 1, 256 * 32 + 1, 256 * 5 * 32 + 1, 256 * 12 * 32 - 33, 256 * 12 * 32 + 1,
+                               256 * 15 * 32 - 33, 256 * 15 * 32 + 1, 8192 * 128 - 129,
                                8192 * 128 * 3 // 2 + 77])
 def test_resident_conv_grid_limit(cin, cout, n):
     for hint in (B.SUBM, B.STRIDED, B.MAP_ANY):
@@ -445,9 +446,9 @@ def test_quantised_conv_row_counts(n, cin, cout, e4m3):
     _check_quantised(n, n + 5, cin, cout, e4m3)
 
 
-# Levels of up to 98 304 rows run 32 rows a wave.  Larger ones (E4M3 only 64 -> 32, int8 all but 128 -> 32) run whole steps of 65 536
-# rows with 64 a wave, the rest too if it is half a step, else with 32; the grid holds the tiles, whatever the capacity: both
-# sides of each line, rests of a row, a tile and just under half a step, and few rows of a large capacity.
+# Tiles of 32 rows, taken by the waves of up to 256 blocks.  128 -> 64: 32 rows a wave of levels of up to 98 304 rows; larger ones in int8
+# run whole steps of 65 536 rows with 64 a wave, the rest too if it is half a step, else with 32; the grid holds the tiles, whatever the
+# capacity: both sides of each line, rests of a row, a tile and just under half a step, and few rows of a large capacity.
 @pytest.mark.parametrize("e4m3", [False, True])
 @pytest.mark.parametrize("cin,cout", [(64, 32), (64, 64), (128, 32), (128, 64)])
 @pytest.mark.parametrize("n,cap", [(98304, 98304), (98304, 98305), (98305, 98305), (131072, 131072), (131073, 131073), (131072 + 129, 300000),
