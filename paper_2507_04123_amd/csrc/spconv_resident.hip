@@ -9,13 +9,14 @@
 // waves, one a CU, copies them once, behind the only barrier; then each wave takes tiles of 32 rows by itself, runs only the
 // groups that its own rows have (5.1 of nine under a stride-2 map where blocks of 128 rows have 5.8, 2.7 where they have 3.5 under a
 // transposed one), reads weights from LDS wherever it is, and takes the next tile when it is done (tiles of one group next to
-// tiles of nine).  It is bound by the gathers' loads (eight routed frames: 257 MB a launch at 3.4 TB/s, where a copy reaches 4.3, and 1 281
-// cycles a load; matrix cores busy 24 %, LDS 17 %, a wave issues in 21 % of its cycles): two
-// groups requested ahead gain nothing, loads that take whole 128-byte rows, lanes swapped afterwards, neither.  64 -> 64 in two
-// halves of the columns, gathering twice, is 8 and 25 % slower than spconv_direct.hip (223 k rows transposed 38 / 41, stride-2 51 / 64).
-// Alone, us, spconv_direct.hip's way / so with 12 waves: stride-2 32 -> 64 69 k rows 20.0 / 17.1, 223 k 32.7 / 27.5, 893 k 115 / 90, 1.3 M 170 / 136; submanifold 304 k
-// 46 / 40, 1.2 M 180 / 140; transposed 64 -> 32 54 k 12.8 / 10.6, 223 k 32 / 26, 304 k 43 / 33, 893 k 101 / 70; submanifold 87 / 85; any
-// row from anywhere 223 k 85 / 88 and 103 / 103.
+// tiles of nine).  It is bound by the gathers' loads (eight routed frames: 265 MB a launch at 3.7 TB/s, where a copy reaches 4.3, and 1 483
+// cycles a load; matrix cores busy 25 %, LDS 18 %, a wave issues in 17 % of its cycles): two groups requested ahead gain nothing, loads
+// that take whole 128-byte rows, lanes swapped afterwards, neither.  64 -> 64 in two halves of the columns, gathering twice, is 8 and
+// 25 % slower than spconv_direct.hip (223 k rows transposed 38 / 41, stride-2 51 / 64).
+// Alone, us, spconv_direct.hip's way / so with 12 waves: stride-2 32 -> 64 69 k rows 20.0 / 17.1, 223 k 32.7 / 27.5, 893 k 115 / 90, 1.3 M
+// 170 / 136; submanifold 304 k 46 / 40, 1.2 M 180 / 140; transposed 64 -> 32 54 k 12.8 / 10.6, 223 k 32 / 26, 304 k 43 / 33, 893 k
+// 101 / 70; submanifold 87 / 85; any row from anywhere 223 k 85 / 88 and 103 / 103.  What the later order of the walk and 15 waves gave:
+// resident_walk.h.
 #include <hip/hip_bf16.h>
 #include <hip/hip_fp16.h>
 
