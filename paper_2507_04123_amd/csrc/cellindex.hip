@@ -310,12 +310,14 @@ __global__ void __launch_bounds__(256) k_marks_apply(cellword_t* __restrict__ id
   }
 }
 
-// The whole of a small grid (at most 8192 words) in one block, 8 words a thread.
+// The whole of a small grid (at most 8192 words) in one block, 8 words a thread.  A line is taken or left whole, beyond the grid's last word
+// too: the flag that take_marks lowers speaks for both its halves, and what an index of a larger grid left in the second would be found
+// by the next one.  (Slots are whole tiles.)
 __global__ void __launch_bounds__(1024) k_marks_small(cellword_t* __restrict__ idx, lineflag_t* __restrict__ flags,
                                                       uint32_t* __restrict__ marks, lineflag_t* __restrict__ mark_flags, int64_t n_words,
                                                       int64_t capacity, int32_t* __restrict__ d_total, int32_t* __restrict__ d_flags) {
   const int64_t base = (int64_t)threadIdx.x * 8;
-  const bool mine = base < n_words;
+  const bool mine = (base >> EMC2_LINE_SHIFT << EMC2_LINE_SHIFT) < n_words;
   const bool some = mine && mark_flags[base >> EMC2_LINE_SHIFT] != 0, stale = mine && flags[base >> EMC2_LINE_SHIFT] != 0;
   const Marks8 m = load_marks(marks, base, some);
   const uint32_t s = count_marks(m);

@@ -6,6 +6,7 @@ import torch
 from paper_2507_04123_amd import binding as B
 from paper_2507_04123_amd.configs import F16, VoxelSpec
 from paper_2507_04123_amd.pipeline import cells_of
+from test_gpu_stacks import _Bufs, _same
 
 pytestmark = pytest.mark.gpu
 
@@ -54,6 +55,113 @@ def test_slot_that_held_another_index(grid):
         want_c, want_n = _expected(keys, g)
         assert np.array_equal(coords.cpu().numpy(), want_c) and np.array_equal(nbr.cpu().numpy(), want_n)
     ctx.close()
+
+
+def _sites(ctx, how, keys, grid, slot=0):
+    """The sites `keys` of a grid of 32 cells a row (a word of the index is a row of y) left in `slot` by one of the three calls that build from
+    marks."""
+    rows, keys = grid[1], np.asarray(keys, np.int64)
+    cap = max(len(keys), 1)
+    i32 = dict(dtype=torch.int32, device="cuda")
+    coords, counts, n = torch.zeros((cap, 4), **i32), torch.zeros(cap, **i32), torch.zeros(1, **i32)
+    spec = VoxelSpec((0.0, 0.0, 0.0), (1.0, 1.0, 1.0), grid)
+    if how == "voxelize":
+        pts = np.full((cap, 4), -1.0, np.float32)                            # (without a site: a point outside)
+        pts[:len(keys), 0], pts[:len(keys), 1], pts[:len(keys), 2] = keys % 32 + 0.5, keys // 32 + 0.5, 0.5
+        ctx.voxelize(torch.from_numpy(pts).cuda(), None, spec, cap, coords, torch.zeros((cap, 4), device="cuda"), counts, n, index_slot=slot)
+    elif how == "pool":
+        depth = np.zeros((rows, 32), np.float32)                             # pixel (y, x) at depth 1 is cell (0, y, x)
+        depth.flat[keys] = 1.0
+        q = [1, 0, 0, 0.5, 0, 1, 0, 0.5, 0, 0, 0, 0.5]
+        img = torch.zeros((rows, 32, 8), dtype=torch.float16, device="cuda")
+        ctx.pool_image(img, torch.from_numpy(depth).cuda(), q, spec, B.POOL_MAX, cap, coords,
+                       torch.zeros((cap, 8), dtype=torch.float16, device="cuda"), counts, n, index_slot=slot)
+    else:
+        at = torch.zeros((cap, 4), **i32)
+        at[:len(keys)] = torch.from_numpy(np.stack([0 * keys, 0 * keys, keys // 32, keys % 32], axis=1).astype(np.int32)).cuda()
+        f, m, none = torch.zeros((cap, 8), dtype=torch.float16, device="cuda"), torch.full((1,), len(keys), **i32), torch.zeros(1, **i32)
+        ctx.fuse(F16, at, f, m, cap, at, f, none, cap, grid, 1, cap, coords, torch.zeros((cap, 16), dtype=torch.float16, device="cuda"), n,
+                 out_slot=slot)
+    ctx.status_sync()
+    assert int(n.item()) == len(keys)
+    return coords, n, cap
+
+
+def _line_and_around(words):
+    """Cells of the last line (16 words) of a grid of `words` words, and the cells of the words before and behind it."""
+    first = (words - 1) // 16 * 16
+    around = [w for w in (first - 1, *range(first + 16, first + 56)) if w >= 0]
+    return np.arange(first * 32, (first + 16) * 32), np.concatenate([np.arange(w * 32, w * 32 + 32) for w in around])
+
+
+def _small_sites(words, held):
+    return ([5] if words > 16 else []) + ([(words - 1) * 32 + 31] if held else [])
+
+
+# The last line of a smaller grid, full of an older index's sites: words of both its halves, of one, all of them are the grid's.  The line
+# holds a new site or none.  What the next larger grid finds in the line, through a map, a stride-2 level and a stack in the slot.
+@pytest.mark.parametrize("held", [False, True])
+@pytest.mark.parametrize("words", [1, 8, 9, 15, 16, 19, 24, 25, 8104])
+@pytest.mark.parametrize("rows", [8192, 8200])                                # in one block; in tiles
+@pytest.mark.parametrize("how", ["voxelize", "pool", "fuse"])
+def test_last_line_of_a_smaller_grid(how, rows, words, held):
+    large, small = (32, rows, 1), (32, words, 1)
+    line, around = _line_and_around(words)
+    ctx = B.Context(rows * 32, 8192, rows * 32, n_slots=1)
+    _sites(ctx, how, np.sort(np.concatenate([line, around])), large)
+    _sites(ctx, how, _small_sites(words, held), small)
+    coords, n, cap = _sites(ctx, how, around, large)
+    nbr = torch.full((27, cap), -5, dtype=torch.int32, device="cuda")
+    ctx.build_kmap(B.SUBM, coords, n, cap, large, 1, cap, nbr, n, in_slot=0)
+    ctx.status_sync()
+    want_c, want_n = _expected(around, large)
+    assert np.array_equal(coords.cpu().numpy(), want_c) and np.array_equal(nbr.cpu().numpy(), want_n)
+    ctx.close()
+
+
+@pytest.mark.parametrize("words", [8, 19, 25])
+def test_last_line_of_a_smaller_grid_then_a_strided_level(words):
+    fine, coarse = (64, 16384, 1), (32, 8192, 1)                              # 8 192 words: counted by one block, which asks no flags
+    line, around = _line_and_around(words)
+    got = []
+    for used in (True, False):
+        ctx = B.Context(8192 * 32, 8192, 64 * 16384, n_slots=2)
+        if used:
+            _sites(ctx, "voxelize", np.sort(np.concatenate([line, around])), coarse)
+            _sites(ctx, "voxelize", _small_sites(words, False), (32, words, 1))
+        pts = np.stack([2 * (around % 32) + 0.5, 2 * (around // 32) + 0.5, 0 * around + 0.5, 0 * around], axis=1).astype(np.float32)
+        cap = len(around)
+        i32 = dict(dtype=torch.int32, device="cuda")
+        c0, f0, k0, n0 = torch.zeros((cap, 4), **i32), torch.zeros((cap, 4), device="cuda"), torch.zeros(cap, **i32), torch.zeros(1, **i32)
+        ctx.voxelize(torch.from_numpy(pts).cuda(), None, VoxelSpec((0.0, 0.0, 0.0), (1.0, 1.0, 1.0), fine), cap, c0, f0, k0, n0, index_slot=1)
+        big = 4096
+        c1, n1, nbr = torch.zeros((big, 4), **i32), torch.zeros(1, **i32), torch.full((27, big), -5, **i32)
+        ctx.build_kmap(B.STRIDED, c0, n0, cap, fine, 1, big, nbr, n1, out_coords=c1, in_slot=1, out_slot=0)
+        ctx.status_sync()
+        m = int(n1.item())
+        got.append((m, c1[:m].cpu().numpy(), nbr[:, :m].cpu().numpy()))
+        ctx.close()
+    assert got[0][0] == got[1][0] == len(around)
+    assert np.array_equal(got[0][1], got[1][1]) and np.array_equal(got[0][2], got[1][2])
+
+
+@pytest.mark.parametrize("words", [8, 19, 25])
+@pytest.mark.parametrize("rows", [8192, 8200])                                # the stack in one launch; in several
+def test_last_line_of_a_smaller_grid_then_a_stack(rows, words):
+    large = (32, rows, 1)
+    line, around = _line_and_around(words)
+    spec = VoxelSpec((0.0, 0.0, 0.0), (1.0, 1.0, 1.0), large)
+    pts = np.stack([around % 32 + 0.5, around // 32 + 0.5, 0 * around + 0.5, 0 * around], axis=1).astype(np.float32)
+    pts, batch = torch.from_numpy(pts).cuda(), torch.zeros(len(around), dtype=torch.int32, device="cuda")
+    assert len(around) > 1024
+    a, b = _Bufs(large, 1, 1, 4096), _Bufs(large, 1, 1, 4096)
+    _sites(a.ctx, "voxelize", np.sort(np.concatenate([line, around])), large)
+    _sites(a.ctx, "voxelize", _small_sites(words, False), (32, words, 1))
+    b.call_by_call(pts, batch, spec)
+    B.build_stacks((B.StackC * 1)(a.stack(spec, batch)), 1, pts)
+    a.ctx.status_sync(), b.ctx.status_sync()
+    _same(a, b, f"{large} after {words} words")
+    a.ctx.close(), b.ctx.close()
 
 
 # runs of sites in one word: whole words, words of every second cell, runs over the ends of rows and of waves; in key order and not
