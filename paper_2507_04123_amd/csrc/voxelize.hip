@@ -49,14 +49,6 @@ __global__ void __launch_bounds__(256) k_vox_scatter(const float* __restrict__ p
   emc2_stash_point(i, r, pc, first, coords, feats, counts, stash, pitch);
 }
 
-// The rows that pass 2 accumulates into, in a launch of its own: see kZeroApart.
-__global__ void __launch_bounds__(256) k_vox_zero(int64_t rows, float4* __restrict__ feats, int32_t* __restrict__ counts) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= rows) return;
-  feats[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-  counts[i] = 0;
-}
-
 template <int LP>  // 0 none, 1 fp16, 2 bf16
 __global__ void __launch_bounds__(256) k_vox_finalize(const int32_t* __restrict__ d_n, int64_t capacity,
                                                       const float4* __restrict__ stash, int64_t pitch,
@@ -102,10 +94,6 @@ VoxParams emc2_vox_params(const emc2_voxel_spec* spec) {
   return prm;
 }
 
-// Clouds of more points zero their rows apart from the marking: tests/test_gpu_voxel_bins.py tells this pass from the one by bins by the
-// number of launches, which was one more while the slot was cleared first.  (524 287 points: a launch of 5 us for one of 5 us.)
-constexpr int64_t kZeroApart = 262144;
-
 static void voxelize_points(emc2_ctx* ctx, const float* d_points, const int32_t* d_batch, int64_t n_points, const VoxParams& prm,
                             int64_t n_cells, cellword_t* idx, int64_t capacity, int32_t* d_coords, float* d_feats, int32_t* d_counts,
                             void* d_feats_lp, int lp, int32_t* d_n_voxels, hipStream_t s) {
@@ -113,11 +101,8 @@ static void voxelize_points(emc2_ctx* ctx, const float* d_points, const int32_t*
   const dim3 pg((unsigned)emc2_div_up(n_points > 0 ? n_points : 1, 256)), blk(256);
   // at most min(n_points, capacity) voxels exist
   const int64_t bound = n_points < capacity ? n_points : capacity;
-  const int64_t with_marks = n_points > kZeroApart ? 0 : bound;
-  if (n_points > kZeroApart)
-    hipLaunchKernelGGL(k_vox_zero, dim3((unsigned)emc2_div_up(bound, 256)), blk, 0, s, bound, (float4*)d_feats, d_counts);
   if (n_points > 0)
-    hipLaunchKernelGGL(k_vox_mark, pg, blk, 0, s, d_points, d_batch, n_points, prm, ctx->marks, emc2_mark_flags(ctx), ctx->first, with_marks,
+    hipLaunchKernelGGL(k_vox_mark, pg, blk, 0, s, d_points, d_batch, n_points, prm, ctx->marks, emc2_mark_flags(ctx), ctx->first, bound,
                        (float4*)d_feats, d_counts);
   emc2_index_build(ctx, idx, n_cells, capacity, d_n_voxels, s);
   if (bound <= 0) return;
