@@ -134,6 +134,9 @@ bool emc2_grid_ok(const int32_t grid[3], int32_t n_batch, int64_t* n_cells);
 // frame takes 150 -> 135 us.  (A
 // stack keeps that launch, of 5 us: its first gather reads what lies about the marks, and the maps, which read the same places of
 // the index later, then find less of it in the caches: 120 000 points 33 -> 41 us, 300 000 47 -> 56.)
+// Dense grids keep it too (voxelize.hip and pool.hip say which): marks lie twice as close as the index's bits, and atomics on a line
+// are served one after the other.  Marks at the index's pitch would be as fast there, but slower on sparse grids: fusion 22.2 -> 25.7 us, the
+// bridge 132 -> 139.
 static inline lineflag_t* emc2_mark_flags(const emc2_ctx* ctx) { return reinterpret_cast<lineflag_t*>(ctx->marks + ctx->slot_words); }
 
 // cell-index construction (cellindex.hip); all asynchronous on `stream`

@@ -3,10 +3,12 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
+from helpers import assert_features_close
 from paper_2507_04123_amd import binding as B
 from paper_2507_04123_amd.configs import F16, VoxelSpec
 from paper_2507_04123_amd.pipeline import cells_of
-from test_gpu_stacks import _Bufs, _same
+from test_gpu_stacks import _Bufs, _kernels_in, _same
 
 pytestmark = pytest.mark.gpu
 
@@ -162,6 +164,78 @@ def test_last_line_of_a_smaller_grid_then_a_stack(rows, words):
     a.ctx.status_sync(), b.ctx.status_sync()
     _same(a, b, f"{large} after {words} words")
     a.ctx.close(), b.ctx.close()
+
+
+def _index_is(ctx, coords, n, cap, grid):
+    """The index in slot 0 against one rebuilt from the coordinates."""
+    nbr, ref = (torch.zeros((27, cap), dtype=torch.int32, device="cuda") for _ in range(2))
+    ctx.build_kmap(B.SUBM, coords, n, cap, grid, 1, cap, nbr, n, in_slot=0)
+    ctx.build_kmap(B.SUBM, coords, n, cap, grid, 1, cap, ref, n)
+    ctx.status_sync()
+    m = int(n.item())
+    assert torch.equal(nbr[:, :m], ref[:, :m])
+
+
+# Dense grids: bits in the slot instead of marks, a launch more.  Both sides of the lines at 8 192 and 73 728 points, of 2 and 24 cells a point;
+# grids of up to 8 192 words (one block) and more.
+@pytest.mark.parametrize("n,words,launches", [(8191, 2, 4), (8192, 2, 5), (8192, 512, 5), (8192, 513, 4), (73727, 4607, 5), (73727, 4608, 4),
+                                              (73728, 4608, 5), (73728, 8193, 6), (73728, 55296, 6), (73728, 55297, 5), (300001, 2100, 5)])
+def test_voxelize_dense_and_sparse_grids(n, words, launches):
+    grid = (32, words, 1)
+    rng = np.random.RandomState(n + words)
+    spec = VoxelSpec((0.0, 0.0, 0.0), (1.0, 1.0, 1.0), grid)
+    ctx = B.Context(n, n, 32 * max(words, 60000), n_slots=1)
+    _sites(ctx, "voxelize", np.arange(0, 32 * 60000, 300), (32, 60000, 1))        # what the slot holds before
+    i32 = dict(dtype=torch.int32, device="cuda")
+    for part in (1.0, 0.3):                      # the whole of the grid, then a part: lines that hold nothing any more
+        pts = np.stack([rng.uniform(0, 32, n), rng.uniform(0, part * words, n), rng.uniform(0, 1, n), rng.uniform(0, 1, n)], axis=1).astype(np.float32)
+        pts[::97, 0] = -1.0                      # dropped
+        dev = torch.from_numpy(pts).cuda()
+        coords, feats, counts, nv = torch.zeros((n, 4), **i32), torch.ones((n, 4), device="cuda"), torch.ones(n, **i32), torch.zeros(1, **i32)
+        call = lambda: ctx.voxelize(dev, None, spec, n, coords, feats, counts, nv)
+        call()
+        ctx.status_sync()
+        oc, om, on = oracle.voxelize(pts, None, spec.lo, spec.vs, spec.grid)
+        m = len(oc)
+        assert int(nv.item()) == m and np.array_equal(coords[:m].cpu().numpy(), oc) and np.array_equal(counts[:m].cpu().numpy(), on)
+        # sums of k points in fp32 against fp64: k * 2^-24 relative to the largest partial sum
+        assert_features_close(feats[:m].cpu().numpy(), om, max(4e-6, int(on.max()) * 2.0 ** -24), "means")
+        assert not feats[m:].any() and not counts[m:].any()
+        _index_is(ctx, coords, nv, n, grid)
+    assert _kernels_in(call) == launches
+    ctx.close()
+
+
+# Lines at 163 840 and 262 144 pixels, of a twelfth of a cell a pixel and of pixels / 2^19, by cells of the image's frame.
+@pytest.mark.parametrize("h,w,grid,nb,launches", [(511, 320, (128, 80, 1), 1, 7), (512, 320, (128, 80, 1), 1, 8), (512, 320, (128, 107, 1), 1, 7),
+                                                  (511, 512, (128, 128, 2), 1, 7), (512, 512, (128, 128, 8), 1, 8), (512, 512, (128, 128, 8), 3, 9),
+                                                  (512, 512, (128, 128, 9), 1, 7), (512, 512, (128, 128, 17), 1, 8), (700, 1000, (256, 256, 14), 1, 9),
+                                                  (700, 1000, (256, 256, 15), 1, 8)])
+def test_pool_dense_and_sparse_grids(h, w, grid, nb, launches):
+    rng = np.random.RandomState(h + grid[2])
+    npix, bi = h * w, nb - 1
+    spec = VoxelSpec((0.0, 0.0, 0.0), (w / grid[0], h / grid[1], 1.0), grid, nb)
+    ctx = B.Context(npix, npix, max(cells_of(grid, nb), 32 * 60000), n_slots=1)
+    _sites(ctx, "voxelize", np.arange(0, 32 * 60000, 300), (32, 60000, 1))
+    q = [1, 0, 0, 0.5, 0, 1, 0, 0.5, 0, 0, 0, 0.5]
+    i32 = dict(dtype=torch.int32, device="cuda")
+    for rows in (h, h // 4):
+        depth = np.zeros((h, w), np.float32)
+        depth[:rows] = rng.randint(0, 8, (rows, w)) != 0
+        img = rng.randint(-40, 40, (h, w, 8)).astype(np.float16)
+        dimg, ddep = torch.from_numpy(img).cuda(), torch.from_numpy(depth).cuda()
+        coords, feats, counts, n = torch.zeros((npix, 4), **i32), torch.zeros((npix, 8), dtype=torch.float16, device="cuda"), torch.zeros(npix, **i32), torch.zeros(1, **i32)
+        call = lambda: ctx.pool_image(dimg, ddep, q, spec, B.POOL_MAX, npix, coords, feats, counts, n, batch_index=bi)
+        call()
+        ctx.status_sync()
+        oc, of, on = oracle.pool_image(img, depth, q, spec.lo, spec.vs, spec.grid, oracle.POOL_MAX, nb, bi)
+        m = len(oc)
+        assert int(n.item()) == m and np.array_equal(coords[:m].cpu().numpy(), oc) and np.array_equal(counts[:m].cpu().numpy(), on)
+        assert np.array_equal(feats[:m].float().cpu().numpy(), of)
+        if nb == 1:
+            _index_is(ctx, coords, n, npix, grid)
+    assert _kernels_in(call) == launches
+    ctx.close()
 
 
 # runs of sites in one word: whole words, words of every second cell, runs over the ends of rows and of waves; in key order and not
