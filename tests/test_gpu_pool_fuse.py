@@ -100,6 +100,37 @@ def test_pool_image_ragged_image_sizes():
     ctx.close()
 
 
+def test_pool_image_exact_sums_round_once():
+    """Cells of 1 .. 400 pixels, sums of integers (exact in any order): every mean is the correctly rounded quotient's half, wherever in the
+    list the cell's rows begin, in every run.  Sums of odd multiples of n / 2 have quotients halfway between two halves."""
+    h, w, c = 400, 2000, 8
+    ctx = B.Context(h * w, h * w, w * 4, n_slots=1)
+    rng = np.random.RandomState(1)
+    rows = rng.randint(1, h + 1, w)                       # pixels of column x: the cell (0, 0, x)
+    depth = (np.arange(h)[:, None] < rows[None]).astype(np.float32)
+    img = np.zeros((h, w, c), np.int64)
+    img[:, :, :4] = rng.randint(-50, 50, (h, w, 4))
+    for k in range(4, 8):                                 # mean of column x: 1024 + an odd half
+        total = rows * (2 * rng.randint(1024, 1900, w) + 1) // 2 * (rows % 2 == 0) + rows * 1027 * (rows % 2)
+        base = total // rows
+        img[:, :, k] = base[None] + (np.arange(h)[:, None] < (total - base * rows)[None])
+    img16 = img.astype(np.float16)
+    assert np.array_equal(img16.astype(np.int64), img)
+    s = (img * (depth[:, :, None] != 0)).sum(axis=0)
+    assert np.abs(s).max() < 1 << 24                      # exact in fp32
+    want = (s.astype(np.float32) / rows[:, None].astype(np.float32)).astype(np.float16)
+    for x, k, v in ((3, 0, np.inf), (4, 1, -np.inf), (5, 2, np.nan)):
+        img16[0, x, k] = want[x, k] = v
+    spec = VoxelSpec((0.0, 0.0, 0.0), (1.0, float(h), 1.0), (w, 1, 1))
+    q = [1, 0, 0, 0.5, 0, 1, 0, 0.5, 0, 0, 0, 0.5]
+    for _ in range(3):
+        coords, feats, counts, n, nv = gpu_pool(ctx, img16, depth, q, spec, B.POOL_MEAN, w)
+        ctx.status_sync()
+        assert nv == w and np.array_equal(counts.cpu().numpy(), rows)
+        assert np.array_equal(feats.cpu().numpy(), want, equal_nan=True)
+    ctx.close()
+
+
 def test_pool_image_capacity_overflow_is_reported():
     ctx = B.Context(60 * 200, 60 * 200, 176 * 200 * 10, n_slots=1)
     pm, q, depth, img = make_scene(3, c=8)
