@@ -337,15 +337,24 @@ __global__ void __launch_bounds__(1024) k_marks_small(cellword_t* __restrict__ i
 
 }  // namespace
 
+static void zero_marks(emc2_ctx* ctx, hipStream_t stream) {
+  const int64_t bytes = 4 * ctx->slot_words + (ctx->slot_words >> EMC2_LINE_SHIFT);      // slots are whole tiles: a multiple of 128
+  hipLaunchKernelGGL(k_marks_zero, dim3(2048), dim3(256), 0, stream, (uint4*)ctx->marks, bytes / 16);
+}
+
 void emc2_marks_begin(emc2_ctx* ctx, hipStream_t stream) {
-  if (!ctx->marks_zeroed) {
-    const int64_t bytes = 4 * ctx->slot_words + (ctx->slot_words >> EMC2_LINE_SHIFT);      // slots are whole tiles: a multiple of 128
-    hipLaunchKernelGGL(k_marks_zero, dim3(2048), dim3(256), 0, stream, (uint4*)ctx->marks, bytes / 16);
-  }
+  ctx->marks_recorded = !ctx->marks_zeroed && emc2_capturing(stream);
+  if (!ctx->marks_zeroed) zero_marks(ctx, stream);
   ctx->marks_zeroed = false;
 }
 
-void emc2_marks_taken(emc2_ctx* ctx) { ctx->marks_zeroed = hipPeekAtLastError() == hipSuccess; }
+// The launches that set the marks and took them over are issued.  If one failed, the next call clears them, and, for graphs that were
+// recorded while they were zero, this one as well, if it still can.
+static void marks_taken(emc2_ctx* ctx, hipStream_t stream) {
+  const bool ok = hipPeekAtLastError() == hipSuccess;
+  if (!ok) zero_marks(ctx, stream);
+  ctx->marks_zeroed = ok && !ctx->marks_recorded;
+}
 
 void emc2_index_build(emc2_ctx* ctx, cellword_t* idx, int64_t n_cells, int64_t capacity, int32_t* d_total, hipStream_t stream) {
   const int64_t n_words = emc2_div_up(n_cells, 32), n_blocks = emc2_div_up(n_words, EMC2_SCAN_TILE);
@@ -365,7 +374,7 @@ void emc2_index_build(emc2_ctx* ctx, cellword_t* idx, int64_t n_cells, int64_t c
                          capacity, d_total, ctx->dev_words);
     }
   }
-  emc2_marks_taken(ctx);
+  marks_taken(ctx, stream);
 }
 
 void emc2_index_clear(emc2_ctx* ctx, cellword_t* idx, hipStream_t stream) {

@@ -80,6 +80,7 @@ struct emc2_ctx {
   int64_t n_partials;
   uint32_t* marks;          // [slot_words] occupancy bits of the index that is being built, [slot_words / 16] line flags behind them
   bool marks_zeroed;        // they are zero
+  bool marks_recorded;      // the present call's clearing of them was recorded into a graph, which may never run
   uint32_t* bins;           // [6 * n_bins + 4] large clouds by bin of cells (voxel_bins.hip)
   int64_t n_bins;
   bool bins_zeroed;         // the first n_bins of them are zero
@@ -126,6 +127,7 @@ __host__ __device__ __forceinline__ uint64_t emc2_line_of_key(uint64_t key) { re
 emc2_status emc2_fail(emc2_ctx* ctx, emc2_status st, const char* fmt, ...);
 emc2_status emc2_check_hip(emc2_ctx* ctx, hipError_t e, const char* what);
 bool emc2_grid_ok(const int32_t grid[3], int32_t n_batch, int64_t* n_cells);
+bool emc2_capturing(hipStream_t stream);   // launches on it are recorded (or it cannot be told)
 
 // Marks: occupancy bits of the index that a voxelization, pooling or fusion builds, 4 bytes per 32 cells, and a flag byte per 512 cells (64
 // bytes of bits), kept with the index's own.  Both are zero between calls: emc2_index_build, which takes the bits over into the slot, zeroes
@@ -140,10 +142,8 @@ bool emc2_grid_ok(const int32_t grid[3], int32_t n_batch, int64_t* n_cells);
 static inline lineflag_t* emc2_mark_flags(const emc2_ctx* ctx) { return reinterpret_cast<lineflag_t*>(ctx->marks + ctx->slot_words); }
 
 // cell-index construction (cellindex.hip); all asynchronous on `stream`
-// The marks are about to be set: zeroes them if a launch of an earlier call failed.  emc2_marks_taken: the launches that set them and took
-// them over are issued.
+// The marks are about to be set: zeroes them if a launch of an earlier call failed.
 void emc2_marks_begin(emc2_ctx* ctx, hipStream_t stream);
-void emc2_marks_taken(emc2_ctx* ctx);
 // the slot's index over ceil(n_cells/32) words from the marks, with prefix sums; min(total, capacity) to d_total and
 // EMC2_DEVFLAG_CAPACITY when total > capacity
 void emc2_index_build(emc2_ctx* ctx, cellword_t* idx, int64_t n_cells, int64_t capacity, int32_t* d_total, hipStream_t stream);

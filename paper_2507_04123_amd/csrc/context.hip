@@ -32,6 +32,11 @@ bool emc2_grid_ok(const int32_t grid[3], int32_t n_batch, int64_t* n_cells) {
   return true;
 }
 
+bool emc2_capturing(hipStream_t stream) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusActive;
+  return hipStreamIsCapturing(stream, &st) != hipSuccess || st != hipStreamCaptureStatusNone;
+}
+
 extern "C" emc2_status emc2_create(emc2_ctx** out, int device, int64_t max_points, int64_t max_voxels,
                                    int64_t max_cells, int32_t n_slots) {
   if (!out) return EMC2_ERR_INVALID_ARG;

@@ -547,8 +547,11 @@ void launch_bins(emc2_ctx* ctx, const float* d_points, const int32_t* d_batch, i
   uint4* parts = reinterpret_cast<uint4*>(ctx->pool_acc + 3 * quarter);
   const dim3 pg((unsigned)emc2_div_up(n_points, kMoveThreads * kMovePoints)), pb(kMoveThreads);
   const dim3 sg((unsigned)emc2_div_up(n, 1024)), sb(1024);
-  // The counts are zero between calls, unless a launch of the last one failed.
-  if (!ctx->bins_zeroed) hipLaunchKernelGGL(k_bin_zero, dim3((unsigned)emc2_div_up(ctx->n_bins, 1024)), sb, 0, s, counts, ctx->n_bins);
+  // The counts are zero between calls, unless a launch of the last one failed; a clearing that is only recorded may never run.  (A call that
+  // fails clears them too, if it still can, for graphs that were recorded while they were zero.)
+  const auto zero_counts = [&] { hipLaunchKernelGGL(k_bin_zero, dim3((unsigned)emc2_div_up(ctx->n_bins, 1024)), sb, 0, s, counts, ctx->n_bins); };
+  const bool recorded = !ctx->bins_zeroed && emc2_capturing(s);
+  if (!ctx->bins_zeroed) zero_counts();
   ctx->bins_zeroed = false;
   hipLaunchKernelGGL((k_bin_points<SHIFT, false>), pg, pb, 0, s, d_points, d_batch, n_points, prm, counts, nullptr, nullptr, state, nullptr);
   hipLaunchKernelGGL(k_bin_starts, sg, sb, 0, s, counts, n, 1u << SHIFT, starts, cursors, voxels, list, chunks, parts, state);
@@ -566,7 +569,9 @@ void launch_bins(emc2_ctx* ctx, const float* d_points, const int32_t* d_batch, i
   }
   if (lp == 0) VOXELS(0) else if (lp == 1) VOXELS(1) else VOXELS(2)
 #undef VOXELS
-  ctx->bins_zeroed = hipPeekAtLastError() == hipSuccess;
+  const bool ok = hipPeekAtLastError() == hipSuccess;
+  if (!ok) zero_counts();
+  ctx->bins_zeroed = ok && !recorded;
 }
 
 }  // namespace

@@ -238,6 +238,37 @@ def test_pool_dense_and_sparse_grids(h, w, grid, nb, launches):
     ctx.close()
 
 
+@pytest.mark.parametrize("n,grid,launches", [(500, (64, 50, 40), 4), (524288, (4096, 4096, 16), 7)])      # marks; counts of the bins
+def test_clearing_recorded_after_a_failed_call(n, grid, launches):
+    """A call that reports a failed launch may leave scratch behind that is not zero.  Until a launch that clears it has been issued every call
+    brings one; one that was recorded into a graph does not count, as nobody may ever replay it."""
+    hip = B.load_library()                        # (links the runtime)
+    rng = np.random.RandomState(n)
+    spec = VoxelSpec((0.0, 0.0, 0.0), (1.0, 1.0, 1.0), grid)
+    pts = torch.from_numpy((rng.uniform(0, 1, (n, 4)) * np.array(grid + (1,))).astype(np.float32)).cuda()
+    ctx = B.Context(n, n, cells_of(grid, 1), n_slots=1)
+    i32 = dict(dtype=torch.int32, device="cuda")
+    out, nv = [torch.zeros((n, 4), **i32), torch.zeros((n, 4), device="cuda"), torch.zeros(n, **i32)], torch.zeros(1, **i32)
+    call = lambda: ctx.voxelize(pts, None, spec, n, *out, nv)
+    call()
+    torch.cuda.synchronize()
+    want = [t.clone() for t in (*out, nv)]
+    assert _kernels_in(call) == launches
+    assert hip.hipSetDevice(9999) != 0            # an error of the runtime, left for the next who asks
+    with pytest.raises(B.Emc2Error) as e:
+        call()
+    assert e.value.status == B.ERR_DEVICE
+    assert _kernels_in(call) == launches + 1 and _kernels_in(call) == launches + 1
+    for t in (*out, nv):
+        t.fill_(-3)
+    call()
+    torch.cuda.synchronize()
+    m = int(nv.item())                            # (rows of coordinates beyond the count are not written)
+    assert torch.equal(nv, want[3]) and torch.equal(out[0][:m], want[0][:m]) and torch.equal(out[2], want[2])
+    assert _kernels_in(call) == launches
+    ctx.close()
+
+
 # runs of sites in one word: whole words, words of every second cell, runs over the ends of rows and of waves; in key order and not
 @pytest.mark.parametrize("shuffled", [False, True])
 @pytest.mark.parametrize("nl,ni", [(1, 1), (63, 65), (3000, 4097)])
