@@ -184,6 +184,11 @@ template <> struct Mma4<EMC2_BF16> {
 // 5.2, 118 k 9.8 / 7.9 / 7.7, 471 k 20.7 / 18.4 / 19.0, 942 k 34.0 / 29.5 / 30.6; 4 -> 32 17 k 10.4 / 7.6 / 7.2, 118 k 13.5 / 11.7 / 11.5, 471 k
 // 29.4 / 30.0 / 27.9, 942 k 48.8 / 46.3 / 45.2; 16 -> 16 17 k 12.6 / 8.7 / 7.9, 118 k 17.4 / 14.6 / 13.2, 471 k 31.9 / 30.7 / 30.2, 942 k 56.1 /
 // 51.5 / 50.5.  All 27 rows of 4 channels at once: 5.7, 8.4, 22.0, 35.4 (fewer waves); 27 entries and 9 rows of 16: 7.6, 13.6, 32.1, 54.4.
+// A block beyond the rows has nothing to do, and a capacity of all points has many of them: it leaves when it has seen the row count, which
+// comes while a thread's share of the weights does.  us, all blocks to the end / so: 16 -> 16 1 000 rows of 450 k 13.3 / 10.2, of 960 k
+// 22.3 / 10.2; 4 -> 16 8.7 / 6.5, 16.0 / 6.5; 4 -> 32 10.0 / 9.3, 17.0 / 9.4; full capacities, which have all weights of a thread in flight now:
+// 16 -> 16 222 k rows 21.4 / 19.9, 562 k 39.2 / 36.5; 4 -> 32 20.2 / 19.8, 33.0 / 32.6; 4 -> 16 12.6 / 12.5, 22.9 / 22.3.  The count first, then the
+// weights: 1 % longer than before.  The first entries before the weights: 4 -> 32 357 k 25 / 27.5, 16 -> 16 1 500 rows 5.8 / 6.0.
 template <int DT, int CIN, int COUT>
 __device__ __forceinline__ void run_rows(uint32_t block, const uint16_t* __restrict__ in, const uint16_t* __restrict__ w,
                                          const float* __restrict__ scale, const float* __restrict__ shift, int epilogue,
@@ -196,18 +201,26 @@ __device__ __forceinline__ void run_rows(uint32_t block, const uint16_t* __restr
   constexpr int RW = CIN / 2;                 // 32-bit words per input row
   static_assert(27 % EB == 0 && EB % TB == 0 && CIN % 4 == 0 && COUT % 8 == 0, "shapes this kernel covers");
   // weights as A operands: wl[((tap * KB + kb) * G + g) * 4 + j] = W[tap][4kb + 0..3][4g + j], 8 bytes
-  __shared__ u32x2_t wl[27 * KB * G * 4];
-  for (int e = threadIdx.x; e < 27 * KB * G * 4; e += 256) {
-    const int j = e & 3;
+  constexpr int WN = 27 * KB * G * 4, WT = (WN + 255) / 256;
+  __shared__ u32x2_t wl[WN];
+  u32x2_t wv[WT];                             // a thread's share, requested before the row count is looked at
+#pragma unroll
+  for (int i = 0; i < WT; ++i) {
+    const int e = min((int)threadIdx.x + 256 * i, WN - 1), j = e & 3;
     int f = e >> 2;
     const int g = f % G; f /= G;
     const int kb = f % KB;
     const int tap = f / KB;
     const uint16_t* src = w + ((int64_t)tap * CIN + 4 * kb) * COUT + 4 * g + j;
-    wl[e] = u32x2_t{(uint32_t)src[0] | ((uint32_t)src[COUT] << 16), (uint32_t)src[2 * COUT] | ((uint32_t)src[3 * COUT] << 16)};
+    wv[i] = u32x2_t{(uint32_t)src[0] | ((uint32_t)src[COUT] << 16), (uint32_t)src[2 * COUT] | ((uint32_t)src[3 * COUT] << 16)};
   }
   int64_t n = *d_n_out;
   if (n > capacity_out) n = capacity_out;
+  asm volatile("" ::: "memory");              // (else the loads sink below the branch)
+  if ((int64_t)block * 256 >= n) return;      // uniform for the block
+#pragma unroll
+  for (int i = 0; i < WT; ++i)
+    if ((int)threadIdx.x + 256 * i < WN) wl[threadIdx.x + 256 * i] = wv[i];
   const int lane = threadIdx.x & 63;
   const int64_t row = (int64_t)block * 256 + threadIdx.x;
   const bool live = row < n;

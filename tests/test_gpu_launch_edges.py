@@ -268,6 +268,33 @@ def test_narrow_conv_grid_limit(n):
     _check_conv(n, 32, 32, B.MAP_ANY, False, cap=4 * 8192 * 256 + 1)
 
 
+# Blocks of 256 rows; those beyond the count leave at once.  No row, the edges of a wave and of a block, a count above the capacity
+@pytest.mark.parametrize("dt", [torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("cin,cout", [(4, 16), (4, 32), (16, 16)])
+@pytest.mark.parametrize("n,cap", [(0, 1), (0, 300), (1, 1), (63, 70000), (64, 64), (255, 256), (256, 70000), (257, 70000), (1025, 1100), (600, 513)])
+def test_rows_conv_few_rows_of_a_capacity(n, cap, cin, cout, dt):
+    """Small whole numbers: every fp32 sum is exact in any order, and both 16-bit types hold it."""
+    rows, n_in = min(n, cap), 400
+    g = torch.Generator(device="cuda").manual_seed(n + cin + cout)
+    x = torch.randint(-1, 2, (n_in, cin), generator=g, device="cuda").to(dt)
+    w = torch.randint(-1, 2, (27, cin, cout), generator=g, device="cuda").to(dt)
+    nbr = torch.full((27, cap), 1 << 30, dtype=torch.int32, device="cuda")       # beyond the rows: entries that would be reported
+    nbr[:, :rows] = torch.randint(-n_in, n_in, (27, rows), generator=g, device="cuda").clamp_(min=-1).to(torch.int32)
+    exp = torch.zeros((rows, cout), device="cuda")
+    for k in range(27):
+        at = (nbr[k][:rows] >= 0).nonzero().squeeze(1)
+        exp[at] += x[nbr[k][at].long()].float() @ w[k].float()
+    assert rows == 0 or float(exp.abs().max()) <= 254
+    y = torch.full((cap, cout), 77.0, dtype=dt, device="cuda")
+    ctx = B.Context(16, 16, 64, n_slots=1)
+    scale, shift = torch.full((cout,), 0.5, device="cuda"), torch.full((cout,), 1.0, device="cuda")
+    ctx.spconv(F16 if dt == torch.float16 else BF16, x, w, scale, shift, EPI_AFFINE_RELU, nbr, torch.tensor([n], dtype=torch.int32, device="cuda"),
+               cap, y)
+    ctx.status_sync()
+    assert torch.equal(y[:rows].float(), (exp * 0.5 + 1.0).clamp_(min=0.0).to(dt).float()) and bool((y[rows:] == 77.0).all())
+    ctx.close()
+
+
 def _kernel(cin, cout, hint):
     ctx = B.Context(16, 16, 64, n_slots=1)
     name = ctx.spconv_kernel(F16, cin, cout, hint)
