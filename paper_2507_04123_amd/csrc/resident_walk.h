@@ -7,6 +7,12 @@
 // entries requested behind a tile's first group and rows behind the barrier and the stores, us: 32 -> 64 3 k rows 7.9 / 7.5, 304 k 41 / 38,
 // stride-2 69 k 14.5 / 13.9, 223 k 28.8 / 27.6; 64 -> 32 transposed 223 k 24.8 / 24.5, 22 k 10.8 / 10.3; all sizes and maps of five frames
 // 3.4 and 2.1 % on average.  Two groups of rows in flight instead of one: int8 64 -> 32 69 k 9.7 / 10.4, and 64 columns spill.
+// kRowsFirst: how a block copies its weights.  15 waves don't divide their pieces, and the loop that copies them waits for each turn's
+// loads, nine where 12 waves had one; with one, and the first rows requested behind it, a few tiles a wave take up to a fifth less.  us, 12 waves and
+// the loop / 15 / so: 16-bit 64 -> 32 submanifold 8 600 rows 7.9 / 8.6 / 7.3, 16 k 8.8 / 9.4 / 8.2, 69 k - / 25.0 / 24.6, stride-2 31 k 9.4 / 9.1 /
+// 8.5, any row from anywhere 15 k 8.3 / 9.5 / 7.6; int8 64 -> 64 stride-2 69 k (12 waves) 14.6 / - / 13.3, 64 -> 32 20 k - / 6.3 / 5.9, E4M3 6.8 / 6.5.
+// Shapes that lose by it keep the loop: 16-bit 32 -> 64 level up to 30 k rows, +1.2 % beyond; E4M3 64 -> 64 and 8-bit 128 -> 32 -2 to +1 % up to
+// 30 k rows, +1.4 % beyond.
 #pragma once
 
 #include "common.h"
@@ -19,15 +25,15 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 // Waves of a block, one block a CU, for registers up to 128 (what the LDS beside the weights holds the entries of) or 168 a lane; a form's
 // kernel takes the former unless it would spill: rows by address (inputs of 4 GiB and more) and int8 64 -> 64.  us, 12 / 15: 32 -> 64 submanifold
-// 304 k rows 37.5 / 34.6, stride-2 223 k 27.9 / 23.5, 69 k 14.4 / 12.7; 64 -> 32 transposed 166 k 20.2 / 20.0, submanifold 66 k 24.5 / 23.2 (levels
-// of up to 30 k rows up to 10 % slower under maps other than transposed ones); E4M3 64 -> 64 304 k 44.0 / 40.6; int8 128 -> 32 165 k 44.5 / 41.8.
+// 304 k rows 37.5 / 34.6, stride-2 223 k 27.9 / 23.5, 69 k 14.4 / 12.7; 64 -> 32 transposed 166 k 20.2 / 20.0, submanifold 66 k 24.5 / 23.2; E4M3 64 -> 64
+// 304 k 44.0 / 40.6; int8 128 -> 32 165 k 44.5 / 41.8.  (int8 64 -> 64 with fp16 results would fit with kRowsFirst: the same on average.)
 constexpr int kRWaves = 15, kRWavesWide = 12;
 constexpr int kRRows = 32;                // output rows of a wave
 constexpr int kRRun = 16;                 // tiles of a run: 512 rows
 constexpr int64_t kRCUs = 256;            // compute units of the part; one block fits each
 
 // OP: KS 64-byte parts of a row, NT column tiles of 16, the accumulator, run(weights, rows, accumulator) for 16 rows, 16 columns and a
-// part, and store(row, columns' accumulators), which a lane calls with channels 16j + 4q .. + 3 of its row: 16 * mt + m of the tile.
+// part, and store(row, columns' accumulators), which a lane calls with channels 16j + 4q .. + 3 of its row: 16 * mt + m of the tile; kRowsFirst.
 template <typename OP, bool BUF>
 __device__ __forceinline__ void walk(const OP& op, uint32_t block, uint32_t n_blocks, const void* __restrict__ in, const u32x4* __restrict__ wp,
                                      const int32_t* __restrict__ nbr, const int32_t* __restrict__ d_n_out, int64_t capacity_out,
@@ -124,8 +130,19 @@ __device__ __forceinline__ void walk(const OP& op, uint32_t block, uint32_t n_bl
         for (int i = 0; i < NA; ++i) a[kx][i] = u32x4{0u, 0u, 0u, 0u};
     }
   };
-  for (int p = threadIdx.x; p < 27 * WT; p += WAVES * 64) wl[p] = wp[p];
-  if (slot < tiles) begin();
+  if constexpr (OP::kRowsFirst) {
+    constexpr int WN = (27 * WT + WAVES * 64 - 1) / (WAVES * 64);
+    u32x4 w[WN];                            // a thread's share, all of it requested before the first rows and stored behind their requests
+#pragma unroll
+    for (int i = 0; i < WN; ++i) w[i] = wp[min((int)threadIdx.x + i * WAVES * 64, 27 * WT - 1)];
+    if (slot < tiles) begin();
+#pragma unroll
+    for (int i = 0; i < WN; ++i)
+      if ((int)threadIdx.x + i * WAVES * 64 < 27 * WT) wl[threadIdx.x + i * WAVES * 64] = w[i];
+  } else {
+    for (int p = threadIdx.x; p < 27 * WT; p += WAVES * 64) wl[p] = wp[p];
+    if (slot < tiles) begin();
+  }
   // the weights and the counter of the tiles are in LDS; the loads of the first rows stay in flight
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 

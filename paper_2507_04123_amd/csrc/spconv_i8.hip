@@ -11,7 +11,8 @@
 // themselves (resident_walk.h); 128 -> 64 takes the weights of a tap at a time.  The former for all shapes / so, us, submanifold, int8
 // and E4M3: 64 -> 64 69 k rows 16.7 / 13.1 and 18.0 / 15.0, 165 k 28.8 / 24.6 and 30.8 / 25.3, 304 k 43 / 37 and 48 / 41, stride-2 69 k
 // 19.6 / 15.0, transposed 223 k 28 / 22; 64 -> 32 69 k 14.2 / 10.1; 128 -> 32 304 k 87 / 57.  What that form lost: a barrier and a copy of
-// weights a tap, taps that none of a wave's rows have, and the last round of blocks.  Slower (2 to 9 %) are maps that name any row from anywhere.
+// weights a tap, taps that none of a wave's rows have, and the last round of blocks.  Maps that name any row from anywhere, for which it has fewer
+// waves to a CU, are 6 to 18 % faster so up to 30 k rows and within -9 and +7 % beyond (64 -> 64 223 k rows 35.0 / 37.0, E4M3 38.8 / 41.1).
 // Accumulation is exact (int32); the epilogue is
 // a fixed sequence of individually rounded fp32 operations, so results are bit-reproducible.
 #include <hip/hip_fp16.h>
@@ -427,6 +428,7 @@ template <int CIN, int COUT, int OUTQ, int F8> struct Op8 {
   static constexpr int KS = CIN / 64, NT = COUT / 16;
   template <bool BUF> static constexpr int waves =
       BUF && (F8 || CIN == 128 || COUT == 32) ? emc2_resident::kRWaves : emc2_resident::kRWavesWide;
+  static constexpr bool kRowsFirst = CIN == 64 && (COUT == 32 || !F8);
   typedef typename QAcc<F8>::type acc_t;
   const float *mul, *add;
   int relu;

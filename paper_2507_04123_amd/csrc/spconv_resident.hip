@@ -59,6 +59,7 @@ using emc2_resident::kRRows;
 template <int DT, int CIN, int COUT> struct Op16 {
   static constexpr int KS = CIN / 32, NT = COUT / 16;
   template <bool BUF> static constexpr int waves = BUF ? emc2_resident::kRWaves : emc2_resident::kRWavesWide;
+  static constexpr bool kRowsFirst = CIN == 64;
   typedef floatx4 acc_t;
   const float *scale, *shift;
   int epilogue;

@@ -485,6 +485,48 @@ def test_quantised_conv_rows_a_wave(n, cap, cin, cout, e4m3):
     _check_quantised(n, cap, cin, cout, e4m3)
 
 
+# Rows by buffer descriptor and (more rows vouched for than 4 GiB hold) by address, in every form of the kernels: shapes, operands, results.
+# Part of a tile, a tile and a row, a tile for every wave of 12 and of 15 in 256 blocks and a row more
+@pytest.mark.parametrize("n", [5, 33, 256 * 12 * 32 + 1, 256 * 15 * 32 + 1])
+@pytest.mark.parametrize("cin,cout", [(64, 32), (64, 64), (128, 32), (128, 64)])
+@pytest.mark.parametrize("e4m3,out", [(False, torch.float16), (False, torch.int8), (True, torch.float16), (True, torch.float32)])
+def test_quantised_conv_by_descriptor_and_by_address(e4m3, out, cin, cout, n):
+    """Small whole numbers: the sums, halved and clamped as the call says, are exact in every type."""
+    n_in, cap = 3000, n + 3
+    g = torch.Generator(device="cuda").manual_seed(n + cin + cout)
+    xv, wv = torch.randint(-2, 3, (n_in, cin), generator=g, device="cuda"), torch.randint(-1, 2, (27, cin, cout), generator=g, device="cuda")
+    nbr = torch.randint(-n_in, n_in, (27, cap), generator=g, device="cuda")
+    nbr = torch.where(nbr < 0, torch.where(nbr % 3 == 0, nbr * 500000, -1), nbr).to(torch.int32).contiguous()
+    exp = torch.zeros((n, cout), device="cuda")
+    for k in range(27):
+        at = (nbr[k, :n] >= 0).nonzero().squeeze(1)
+        exp[at] += xv[nbr[k, at].long()].float() @ wv[k].float()
+    ctx = B.Context(16, 16, 64, n_slots=1)
+    x, w = xv.to(torch.int8), wv.to(torch.int8)
+    if e4m3:
+        x, w = torch.empty((n_in, cin), dtype=torch.uint8, device="cuda"), torch.empty((27, cin, cout), dtype=torch.uint8, device="cuda")
+        ctx.quantize_e4m3(xv.float(), 1.0, x)
+        ctx.quantize_e4m3(wv.float(), 1.0, w)
+    wp = torch.empty((27 * cin * cout,), dtype=torch.int8, device="cuda")
+    ctx.pack_weights_i8(w.view(torch.int8), wp)
+    mul, add = torch.full((cout,), 0.5, device="cuda"), torch.arange(cout, device="cuda").float() - 9.0
+    want = (exp * 0.5 + add).clamp_(min=0.0)
+    assert float(exp.abs().max()) <= 1024
+    want = (want * 0.125).round().clamp_(max=127.0).to(torch.int8) if out == torch.int8 else want.to(out)
+    count = torch.tensor([n], dtype=torch.int32, device="cuda")
+    for rows_in in (n_in, (1 << 32) // cin + 3):
+        y = torch.full((cap, cout), 77, dtype=out, device="cuda")
+        if e4m3:
+            ctx.spconv_e4m3(x, wp, cin, cout, mul, add, True, nbr, count, cap, y, n_in_rows=rows_in)
+        elif out == torch.int8:
+            ctx.spconv_i8(x, wp, cin, cout, mul, add, True, nbr, count, cap, y, inv_out_scale=0.125, n_in_rows=rows_in)
+        else:
+            ctx.spconv_i8(x, wp, cin, cout, mul, add, True, nbr, count, cap, y, n_in_rows=rows_in)
+        ctx.status_sync()
+        assert torch.equal(y[:n], want) and bool((y[n:] == 77).all())
+    ctx.close()
+
+
 # A capacity of many times the rows; and the rows of thousands of blocks
 @pytest.mark.parametrize("cin,cout,e4m3", [(128, 32, False), (64, 64, True), (128, 32, True), (128, 64, True), (64, 64, False)])
 @pytest.mark.parametrize("n", [300, 8192 * 128 + 77])
