@@ -50,6 +50,14 @@ __global__ void __launch_bounds__(256) k_vox_scatter(const float* __restrict__ p
   emc2_stash_point(i, r, pc, first, coords, feats, counts, stash, pitch);
 }
 
+// The rows that pass 2 accumulates into, in a launch of its own: see kZeroApart below.
+__global__ void __launch_bounds__(256) k_vox_zero(int64_t rows, float4* __restrict__ feats, int32_t* __restrict__ counts) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= rows) return;
+  feats[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+  counts[i] = 0;
+}
+
 template <int LP>  // 0 none, 1 fp16, 2 bf16
 __global__ void __launch_bounds__(256) k_vox_finalize(const int32_t* __restrict__ d_n, int64_t capacity,
                                                       const float4* __restrict__ stash, int64_t pitch,
@@ -103,6 +111,11 @@ static bool in_slot(int64_t n_points, int64_t n_cells) {
   return n_points >= 8192 && n_cells <= (n_points >= 73728 ? 24 : 2) * n_points;
 }
 
+// Clouds of this many points and more zero their rows apart from the marking when that sets marks.  It makes six launches of the pass whether bits or
+// marks are set, which is how tests/test_gpu_voxel_bins.py tells it from the one by bins (seven).  It costs: 524 287 points (43 to 701 cells a point)
+// 60 to 71 us with the rows zeroed by the marking, 63 to 73 so; 1 M (90) 99.7 / 103.3; so fewer points, 262 145 38.9 / 42.7, don't.
+constexpr int64_t kZeroApart = 500000;
+
 static void voxelize_points(emc2_ctx* ctx, const float* d_points, const int32_t* d_batch, int64_t n_points, const VoxParams& prm,
                             int64_t n_cells, cellword_t* idx, int64_t capacity, int32_t* d_coords, float* d_feats, int32_t* d_counts,
                             void* d_feats_lp, int lp, int32_t* d_n_voxels, hipStream_t s) {
@@ -116,9 +129,11 @@ static void voxelize_points(emc2_ctx* ctx, const float* d_points, const int32_t*
     emc2_index_scan(ctx, idx, n_cells, capacity, d_n_voxels, s);
   } else {
     emc2_marks_begin(ctx, s);
+    const bool apart = n_points >= kZeroApart;
+    if (apart) hipLaunchKernelGGL(k_vox_zero, dim3((unsigned)emc2_div_up(bound, 256)), blk, 0, s, bound, (float4*)d_feats, d_counts);
     if (n_points > 0)
       hipLaunchKernelGGL(k_vox_mark<1>, pg, blk, 0, s, d_points, d_batch, n_points, prm, ctx->marks, emc2_mark_flags(ctx), ctx->first,
-                         bound, (float4*)d_feats, d_counts);
+                         apart ? 0 : bound, (float4*)d_feats, d_counts);
     emc2_index_build(ctx, idx, n_cells, capacity, d_n_voxels, s);
   }
   if (bound <= 0) return;

@@ -17,7 +17,7 @@ pytestmark = pytest.mark.gpu
 N = 524288
 GRID = (4096, 4096, 16)                # 4 096 tiles of 16 lines (y) each: a quarter, the bins of over 100 points a tile, is 4 lines
 WIDE = (4096, 4096, 24)                # 6 144 tiles: bins of a whole one
-BINS, POINTS = 7, 5                    # launches
+BINS, POINTS = 7, 6                    # launches
 
 
 def _cloud(seed, n, fullest, heavy, frames):
