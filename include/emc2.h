@@ -58,7 +58,8 @@ typedef struct emc2_ctx emc2_ctx;
  *   max_voxels : largest voxel count (capacity) of any level.
  *   max_cells  : largest n_batch*Gx*Gy*Gz of any grid that is voxelized or mapped.
  *   n_slots    : number of cell-index slots kept alive at once (>= 1; see emc2_voxelize).
- * Scratch is about 32 B per point + 76 B per voxel + 8 B per 32 cells per index slot.
+ * Scratch is about 32 B per point + 76 B per voxel + 8 B per 32 cells per index slot + 4 B per 32 cells once, for the occupancy
+ * marks of the index being built (each of the two with a flag byte per 512 cells).
  */
 emc2_status emc2_create(emc2_ctx** out, int device, int64_t max_points, int64_t max_voxels,
                         int64_t max_cells, int32_t n_slots);

@@ -188,7 +188,8 @@ template <> struct Mma4<EMC2_BF16> {
 // comes while a thread's share of the weights does.  us, all blocks to the end / so: 16 -> 16 1 000 rows of 450 k 13.3 / 10.2, of 960 k
 // 22.3 / 10.2; 4 -> 16 8.7 / 6.5, 16.0 / 6.5; 4 -> 32 10.0 / 9.3, 17.0 / 9.4; full capacities, which have all weights of a thread in flight now:
 // 16 -> 16 222 k rows 21.4 / 19.9, 562 k 39.2 / 36.5; 4 -> 32 20.2 / 19.8, 33.0 / 32.6; 4 -> 16 12.6 / 12.5, 22.9 / 22.3.  The count first, then the
-// weights: 1 % longer than before.  The first entries before the weights: 4 -> 32 357 k 25 / 27.5, 16 -> 16 1 500 rows 5.8 / 6.0.
+// weights: 1 % longer than before.  The first entries before the weights: 4 -> 32 357 k 25 / 27.5, 16 -> 16 1 500 rows 5.8 / 6.0.  (128 rows a wave are still the better ones of 4 -> 32 between
+// 205 k and 360 k rows under some maps: 222 k 18.6 / 19.8, 357 k 21.1 to 24.8 / 22.6 to 24.8, 303 k 24.4 / 22.2.)
 template <int DT, int CIN, int COUT>
 __device__ __forceinline__ void run_rows(uint32_t block, const uint16_t* __restrict__ in, const uint16_t* __restrict__ w,
                                          const float* __restrict__ scale, const float* __restrict__ shift, int epilogue,
