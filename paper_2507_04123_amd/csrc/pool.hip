@@ -501,14 +501,12 @@ __global__ void __launch_bounds__(256) k_fuse_gather(const VEC* __restrict__ fea
 
 }  // namespace
 
-// Bits set in the slot against marks, as in voxelize.hip.  us, marks / bits in the slot, an image of a road, cells of its frame a pixel in brackets: 1 440 000
-// pixels (0.04) 368 / 330, (1) 223 / 201, (2.3) 199 / 192, (7.8) 184 / 191; 960 000 (0.06) 236 / 185, (1.5) 136 / 130, (3.4) 126 / 132; 465 750 (0.02)
-// 187 / 152, (0.9) 79 / 76, (3) 76 / 78; 352 000 (0.03) 154 / 136, (0.26) 109 / 105, (0.8) 68 / 69; 243 000 (0.07) 57.7 / 55.1, (0.14) 90 / 101;
-// 192 000 (0.08) 46 / 44, (0.18) 98 / 100, (2.3) 40 / 46; 116 748 (0.08) 23.6 / 26.4.
-static bool in_slot(int64_t n_pixels, int64_t n_cells) {
-  if (n_pixels >= 262144) return n_cells <= (n_pixels * n_pixels) >> 19;
-  return n_pixels >= 163840 && n_cells <= n_pixels / 12;
-}
+// Bits set in the slot against marks, as in voxelize.hip.  us, marks / bits in the slot, means over three images of a road, cells of their frame a pixel in
+// brackets: 1 440 000 pixels (0.03) 420 / 367, (0.57) 263 / 234, (3.5) 197 / 190, one of them (7.8) 184 / 191; 960 000 (0.1) 222 / 184, (0.85) 152 / 136, (2.9)
+// 133 / 129, (5.2) 126 / 127; 465 750 (0.09) 113 / 103, (1.8) 77 / 75, (6.0) 70 / 72; 375 000 (0.25) 90 / 83, (2.2) 69 / 67, (7.5) 65 / 66; 240 000 (0.09)
+// 96 / 88, (0.39) 71 / 69, (0.94) 55 / 58; 195 000 (0.12) 93 / 94, (0.23) 72 / 69, (1.2) 52 / 58; 165 000 (0.14) 80 / 85, (0.57) 71 / 69, (1.4) 52 / 58.  So the
+// line is at a cell a pixel for 2^18 pixels, and at as many times that as there are pixels.
+static bool in_slot(int64_t n_pixels, int64_t n_cells) { return n_pixels >= 180000 && n_cells <= (n_pixels * n_pixels) >> 18; }
 
 extern "C" emc2_status emc2_pool_image(emc2_ctx* ctx, const void* d_img, const float* d_depth, int32_t H, int32_t W, int32_t C,
                                        const float Q[12], const emc2_voxel_spec* spec, int32_t batch_index,

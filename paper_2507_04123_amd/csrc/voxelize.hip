@@ -106,9 +106,10 @@ VoxParams emc2_vox_params(const emc2_voxel_spec* spec) {
 // Bits set in the slot, behind a launch that clears it, against marks: a launch more, but twice the lines for the atomics of points that
 // share them.  us, marks / bits in the slot, clouds of a frame's density, cells a point in brackets: 1 M points (0.7) 400 / 315, (5.8) 180 / 153, (14)
 // 134 / 136; 350 000 (17) 59.6 / 53.2, (32) 49.5 / 51.1; 120 000 (2.9) 57.9 / 52.1, (14) 37.9 / 35.7, (27) 28.8 / 28.7, (49) 27.0 / 28.3; 65 536
-// (0.5) 78 / 68, (2.2) 51.6 / 51.5, (6.7) 29.7 / 30.9, (21) 22.7 / 24.2; 17 003 (0.5) 41.0 / 39.6, (3.7) 20.6 / 21.1; 4 000 (2.2) 17.4 / 17.7.
+// (0.67) 68 / 61, (2.4) 48.4 / 46.2, (5.4) 36.4 / 35.3, (12) 29.2 / 28.6, (22) 26.1 / 26.0, (43) 20.9 / 23.8; 50 000 (0.88) 53.4 / 48.0, (4.5) 33.8 / 36.0, (13) 24.8 /
+// 26.0; 17 003 (0.5) 41.0 / 39.6, (3.7) 20.6 / 21.1; 4 000 (2.2) 17.4 / 17.7.
 static bool in_slot(int64_t n_points, int64_t n_cells) {
-  return n_points >= 8192 && n_cells <= (n_points >= 73728 ? 24 : 2) * n_points;
+  return n_points >= 8192 && n_cells <= (n_points >= 65536 ? 24 : 2) * n_points;
 }
 
 // Clouds of this many points and more zero their rows apart from the marking when that sets marks.  It makes six launches of the pass whether bits or

@@ -176,10 +176,10 @@ def _index_is(ctx, coords, n, cap, grid):
     assert torch.equal(nbr[:, :m], ref[:, :m])
 
 
-# Dense grids: bits in the slot instead of marks, a launch more.  Both sides of the lines at 8 192 and 73 728 points, of 2 and 24 cells a point;
+# Dense grids: bits in the slot instead of marks, a launch more.  Both sides of the lines at 8 192 and 65 536 points, of 2 and 24 cells a point;
 # grids of up to 8 192 words (one block) and more.
-@pytest.mark.parametrize("n,words,launches", [(8191, 2, 4), (8192, 2, 5), (8192, 512, 5), (8192, 513, 4), (73727, 4607, 5), (73727, 4608, 4),
-                                              (73728, 4608, 5), (73728, 8193, 6), (73728, 55296, 6), (73728, 55297, 5), (300001, 2100, 5)])
+@pytest.mark.parametrize("n,words,launches", [(8191, 2, 4), (8192, 2, 5), (8192, 512, 5), (8192, 513, 4), (65535, 4095, 5), (65535, 4096, 4),
+                                              (65536, 4097, 5), (65536, 8193, 6), (65536, 49152, 6), (65536, 49153, 5), (300001, 2100, 5)])
 def test_voxelize_dense_and_sparse_grids(n, words, launches):
     grid = (32, words, 1)
     rng = np.random.RandomState(n + words)
@@ -206,11 +206,10 @@ def test_voxelize_dense_and_sparse_grids(n, words, launches):
     ctx.close()
 
 
-# Lines at 163 840 and 262 144 pixels, of a twelfth of a cell a pixel and of pixels / 2^19, by cells of the image's frame.
-@pytest.mark.parametrize("h,w,grid,nb,launches", [(511, 320, (128, 80, 1), 1, 7), (512, 320, (128, 80, 1), 1, 8), (512, 320, (128, 107, 1), 1, 7),
-                                                  (511, 512, (128, 128, 2), 1, 7), (512, 512, (128, 128, 8), 1, 8), (512, 512, (128, 128, 8), 3, 9),
-                                                  (512, 512, (128, 128, 9), 1, 7), (512, 512, (128, 128, 17), 1, 8), (700, 1000, (256, 256, 14), 1, 9),
-                                                  (700, 1000, (256, 256, 15), 1, 8)])
+# Lines at 180 000 pixels and of pixels^2 / 2^18 cells of the image's frame.
+@pytest.mark.parametrize("h,w,grid,nb,launches", [(400, 449, (128, 128, 7), 1, 7), (400, 450, (128, 128, 7), 1, 8), (400, 450, (128, 128, 8), 1, 7),
+                                                  (512, 512, (128, 128, 16), 1, 8), (512, 512, (128, 128, 16), 3, 9), (512, 512, (128, 128, 17), 1, 8),
+                                                  (700, 1000, (256, 256, 28), 1, 9), (700, 1000, (256, 256, 29), 1, 8)])
 def test_pool_dense_and_sparse_grids(h, w, grid, nb, launches):
     rng = np.random.RandomState(h + grid[2])
     npix, bi = h * w, nb - 1
